@@ -155,8 +155,8 @@ size_t mla_decode_workspace_bytes(int B, int H, int d_c, int num_splits);
  *              accounts for it).  Every chunk is reduced with its own running
  *              softmax and the chunks are merged by log-sum-exp.  The result
  *              does not depend on the chunking beyond fp32 rounding.
- *              With MLA_FLAG_BALANCED (matrix-core kernel only, otherwise
- *              MLA_ERR_UNSUPPORTED) the cut is made differently: the page lists
+ *              With MLA_FLAG_BALANCED (matrix-core kernels with page_size 64
+ *              only, otherwise MLA_ERR_UNSUPPORTED) the cut is made differently: the page lists
  *              of all sequences, laid end to end, are cut into B * S ranges of
  *              equal length (+-1 page), one per workgroup; a range that
  *              crosses sequence boundaries gives one chunk per sequence.  Every
@@ -167,10 +167,12 @@ size_t mla_decode_workspace_bytes(int B, int H, int d_c, int num_splits);
  * Supported: io/cache dtype pairs (F32,F32), (BF16,BF16), (BF16,FP8_E4M3),
  * (F32,BF16), (F32,FP8_E4M3); 1 <= H <= 1024; d_c a multiple of 8 up to 512;
  * d_rope a multiple of 8 in [0, 64]; any page_size >= 1.
- * The matrix-core (MFMA) kernel is used for BF16 io with a BF16 or FP8 cache,
+ * The matrix-core (MFMA) kernels are used for BF16 io with a BF16 or FP8 cache,
  * page_size 64, d_rope 64 and d_c in {256, 512} (32 heads per workgroup; more
- * heads go to further workgroups); everything else runs on the portable
- * scalar-FMA kernel.
+ * heads go to further workgroups), and, with the uniform partition, for BF16
+ * caches of those shapes whose page_size is another multiple of 16 (there the
+ * softmax weights enter the value contraction as two bf16 terms); everything
+ * else runs on the portable scalar-FMA kernel.
  */
 int mla_decode_paged(const void* q_abs, const void* q_rope,
                      const void* kv_cache, const float* kv_scale,

@@ -135,6 +135,8 @@ int decode_launch(const DecodeCall& c, void* workspace)
     if (mfma && !balanced && decode_mfma_wide_supported(p, c.io_dtype, c.cache_dtype))
         e = launch_decode_mfma_wide(p, stream);
     else if (mfma) e = launch_decode_mfma(p, c.cache_dtype, stream, balanced);
+    else if (!(c.flags & MLA_FLAG_PORTABLE_KERNEL) && decode_stream_paged_supported(p, c.io_dtype, c.cache_dtype))
+        e = launch_decode_stream_paged(p, stream);
     else      e = launch_decode_portable(p, c.io_dtype, c.cache_dtype, stream);
     if (e != hipSuccess) return MLA_ERR_HIP;
     if (skip_merge) return MLA_OK;

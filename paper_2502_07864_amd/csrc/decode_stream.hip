@@ -34,6 +34,18 @@
 // pace there.  Both kinds meet at one workgroup barrier per tile (tile t's scores are written,
 // tile t + 1 has landed, everybody is done with tile t - 1, whose slot the producers then fill
 // again).
+//
+// Pages of 64 rows (a tile is half a page) are one form of the kernel; PAGED = true takes every
+// other page size that is a multiple of 16 rows: a tile's two 16-row blocks then lie in one page
+// each, looked up by themselves, and which of the two a load belongs to is a constant of the load
+// (16 rows are CPR / 4 groups of 64 chunks), so a tile costs one more scalar look-up and nothing per
+// lane.  Chunks begin at multiples of the page size, tiles are counted from the chunk's first row.
+// These sizes ran on the scalar-FMA kernel, which holds the weights in fp32; here a weight is two
+// bf16 terms (the rounded weight and the rounded remainder: 2^-17 of the weight is lost) and the value
+// contraction runs once per term on the same operand, which the accumulating wavefronts have the
+// time for.  8 sequences of 1500 .. 4096 rows in 16-row pages, 32 heads, d_c = 512, 16 chunks:
+// absorb + decode + merge + projection 133.2 us on the scalar-FMA kernel (121.8 of them its own), 28.0 us
+// here, the same distance from 64-bit results (2-norm, 3.1e-3 at the output).
 #include "mla_internal.h"
 #include "mfma_tile.h"
 #include <type_traits>
@@ -50,7 +62,8 @@ typedef __attribute__((ext_vector_type(8))) short s16x8;
 // BAL = true: the balanced partition (one-dimensional grid; a workgroup owns an equal share of the
 // pages of all sequences and works through the segments of sequences inside it, exactly as in
 // decode_mfma.hip, whose plan and slot numbering this is).
-template <int D_C, bool PROBE, bool BAL>
+// PAGED = true: pages of 16 k rows, k other than 4 (uniform partition only); weights in two terms.
+template <int D_C, bool PROBE, bool BAL, bool PAGED = false>
 __global__ __launch_bounds__(ST_THREADS, 1) void decode_stream_kernel(DecodeParams p)
 {
     constexpr int NBUF = 4;                     // ring slots: tile t (values), tile t + 1 (scores), two on their way
@@ -69,6 +82,7 @@ __global__ __launch_bounds__(ST_THREADS, 1) void decode_stream_kernel(DecodePara
     static_assert(CPR % 8 == 0, "chunk swizzle needs rows of whole 128-byte groups");
     static_assert(NLOAD * (NBUF + 1) < 64, "vmcnt is a 6-bit counter");
     static_assert(4 * 16 * RSO <= NBUF * TILE_B, "the epilogue's transposition space must fit in the tile ring");
+    static_assert(!PAGED || (!PROBE && !BAL && CPR % 4 == 0), "other page sizes: uniform partition; 16 rows must be whole groups of 64 chunks");
 
     __shared__ __attribute__((aligned(1024))) unsigned char smem[NBUF * TILE_B];
     // (the query rows [q_abs | q_rope] of the 32 heads travel like a cache tile, one row per head with
@@ -137,20 +151,40 @@ __global__ __launch_bounds__(ST_THREADS, 1) void decode_stream_kernel(DecodePara
     f32x4 st[NST];
 
     asm volatile("" :: "s"(warm));
-    L = max(0, min(L, p.max_pages * 64));
-    const int row0 = BAL ? seg_row0 : split * p.chunk_pages * 64;                  // first cached row of this chunk
-    const int row1 = BAL ? min(seg_row1, L) : min(row0 + p.chunk_pages * 64, L);   // one past its last row
+    const int page_rows = PAGED ? p.page_size : 64;
+    L = max(0, min(L, p.max_pages * page_rows));
+    // first cached row of this chunk and one past its last row (a page size of the caller's choice times
+    // the index of an empty trailing chunk may leave 32 bits)
+    const int row0 = BAL ? seg_row0 : PAGED ? (int)min((long long)L, (long long)split * p.chunk_pages * page_rows)
+                                            : split * p.chunk_pages * 64;
+    const int row1 = BAL ? min(seg_row1, L) : PAGED ? (int)min((long long)L, row0 + (long long)p.chunk_pages * page_rows)
+                                                    : min(row0 + p.chunk_pages * 64, L);
     if (row0 >= row1) {  // empty chunk: weight zero in the merge, partial output never read
         if (!PROBE && tid < HL) *lse_at(hb + tid) = -INFINITY;
         return;
     }
-    const int t0 = row0 / TILE_ROWS;                                // tiles [t0, t1) of the sequence
-    const int t1 = (row1 + TILE_ROWS - 1) / TILE_ROWS;
+    const int tb = PAGED ? row0 : 0;                                // tiles [t0, t1), tile t = rows tb + 32 t ..
+    const int t0 = PAGED ? 0 : row0 / TILE_ROWS;
+    const int t1 = (row1 - tb + TILE_ROWS - 1) / TILE_ROWS;
 
     // rows of tile t that belong to this chunk (0 if its page id is outside the pool)
     auto rows_valid = [&](int t) {
         int page = ptab[t >> 1];
         return (page >= 0 && page < p.num_pages) ? min(TILE_ROWS, row1 - t * TILE_ROWS) : 0;
+    };
+    // PAGED: rows of 16-row block rb of tile t that belong to this chunk (0 if its page id is outside the
+    // pool), and where in the pool the block begins; a block past the chunk looks nothing up
+    const int blocks_per_page = page_rows >> 4;
+    auto block_valid = [&](int t, int rb) -> int {
+        const int R = tb + t * TILE_ROWS + rb * 16;
+        if (R >= row1) return 0;
+        const int page = ptab[(R >> 4) / blocks_per_page];
+        return page >= 0 && page < p.num_pages ? min(16, row1 - R) : 0;
+    };
+    auto block_base = [&](int t, int rb) -> size_t {
+        const int blk = (tb + t * TILE_ROWS + rb * 16) >> 4;
+        const int page = ptab[blk / blocks_per_page];
+        return ((size_t)page * blocks_per_page + (size_t)(blk % blocks_per_page)) * (size_t)(16 * ROWB);
     };
 
     // ---- producers: tile staging, HBM -> LDS with direct-to-LDS 128-bit loads (inline assembly:
@@ -162,11 +196,38 @@ __global__ __launch_bounds__(ST_THREADS, 1) void decode_stream_kernel(DecodePara
     for (int k = 0; k < NLOAD; ++k) {
         int P = (k * 4 + w4) * 64 + lane;
         int r = P / CPR, pc = P % CPR;
-        goff[k] = (uint32_t)(r * ROWB + ((pc ^ swz_key(r)) << 4));
+        goff[k] = (uint32_t)((PAGED ? r & 15 : r) * ROWB + ((pc ^ swz_key(r)) << 4));
     }
     const unsigned char* kv = static_cast<const unsigned char*>(p.kv);
     // returns the number of loads this thread issued (0 or NLOAD; uniform)
     auto fetch_tile = [&](int t) -> int {
+        if constexpr (PAGED) {
+            const int v0 = block_valid(t, 0), v1 = block_valid(t, 1);
+            if (v0 <= 0 && v1 <= 0) return 0;
+            // a block that is not there is fetched from where the other one lies (and zeroed when the tile
+            // is published): every tile is NLOAD loads or none
+            const unsigned char* src0 = kv + block_base(t, v0 > 0 ? 0 : 1);
+            const unsigned char* src1 = kv + block_base(t, v1 > 0 ? 1 : 0);
+            const uint32_t dst = lds_base + (uint32_t)((t % NBUF) * TILE_B + w4 * 1024);
+            if (stream_once) {
+#pragma unroll
+                for (int k = 0; k < NLOAD; ++k) {
+                    const unsigned char* gp = (k * 4 + w4 < CPR / 4 ? src0 : src1) + goff[k];
+                    const uint32_t m0v = __builtin_amdgcn_readfirstlane(dst + k * 4096);
+                    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off nt"
+                                 :: "s"(m0v), "v"(gp) : "memory");
+                }
+            } else {
+#pragma unroll
+                for (int k = 0; k < NLOAD; ++k) {
+                    const unsigned char* gp = (k * 4 + w4 < CPR / 4 ? src0 : src1) + goff[k];
+                    const uint32_t m0v = __builtin_amdgcn_readfirstlane(dst + k * 4096);
+                    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
+                                 :: "s"(m0v), "v"(gp) : "memory");
+                }
+            }
+            return NLOAD;
+        } else {
         if (rows_valid(t) <= 0) return 0;   // a page outside the pool is never dereferenced
         const unsigned char* src = kv + (size_t)ptab[t >> 1] * PAGE_B + (size_t)(t & 1) * TILE_B;
         const uint32_t dst = lds_base + (uint32_t)(((t - t0) % NBUF) * TILE_B + w4 * 1024);
@@ -190,6 +251,7 @@ __global__ __launch_bounds__(ST_THREADS, 1) void decode_stream_kernel(DecodePara
             }
         }
         return NLOAD;
+        }
     };
 
     // producers: the query rows into their LDS area, chunk by chunk like a tile (rows of absent
@@ -265,7 +327,15 @@ __global__ __launch_bounds__(ST_THREADS, 1) void decode_stream_kernel(DecodePara
             __builtin_amdgcn_sched_barrier(0);
         }
         x = sacc * sc;
-        if (n_valid < TILE_ROWS || (t + 1) * TILE_ROWS > causal_from) {
+        if constexpr (PAGED) {                 // n_valid counts this block's rows
+            const int R = tb + t * TILE_ROWS + rb * 16;
+            if (n_valid < 16 || R + 16 > causal_from) {
+                const int seen = min(n_valid, visible_rows(p, L, hb + head) - R);
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (g * 4 + i >= seen) x[i] = -INFINITY;
+            }
+        } else if (n_valid < TILE_ROWS || (t + 1) * TILE_ROWS > causal_from) {
             const int seen = min(n_valid, visible_rows(p, L, hb + head) - t * TILE_ROWS);
 #pragma unroll
             for (int i = 0; i < 4; ++i)
@@ -279,15 +349,30 @@ __global__ __launch_bounds__(ST_THREADS, 1) void decode_stream_kernel(DecodePara
     // after scoring and what two transposing reads (one per 16-row block) deliver
     auto accumulate_tile = [&](LDS_AS unsigned char* tile, const f32x4 x0, const f32x4 x1) {
         const float m_use = m_run == -INFINITY ? 0.f : m_run;  // only while every row so far is masked
-        const uint32_t p01 = pack_bf16x2(fast_exp2(x0[0] - m_use), fast_exp2(x0[1] - m_use));
-        const uint32_t p23 = pack_bf16x2(fast_exp2(x0[2] - m_use), fast_exp2(x0[3] - m_use));
-        const uint32_t p45 = pack_bf16x2(fast_exp2(x1[0] - m_use), fast_exp2(x1[1] - m_use));
-        const uint32_t p67 = pack_bf16x2(fast_exp2(x1[2] - m_use), fast_exp2(x1[3] - m_use));
+        float e[8];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            e[i] = fast_exp2(x0[i] - m_use);
+            e[4 + i] = fast_exp2(x1[i] - m_use);
+        }
+        const uint32_t p01 = pack_bf16x2(e[0], e[1]), p23 = pack_bf16x2(e[2], e[3]);
+        const uint32_t p45 = pack_bf16x2(e[4], e[5]), p67 = pack_bf16x2(e[6], e[7]);
         l_run += ((bf16_bits_to_f32(p01 & 0xFFFFu) + bf16_bits_to_f32(p01 >> 16)) +
                   (bf16_bits_to_f32(p23 & 0xFFFFu) + bf16_bits_to_f32(p23 >> 16))) +
                  ((bf16_bits_to_f32(p45 & 0xFFFFu) + bf16_bits_to_f32(p45 >> 16)) +
                   (bf16_bits_to_f32(p67 & 0xFFFFu) + bf16_bits_to_f32(p67 >> 16)));
         const bf16x8 pb = __builtin_bit_cast(bf16x8, (u32x4){p01, p23, p45, p67});
+        bf16x8 pr = pb;                        // PAGED: second term of the weights
+        if constexpr (PAGED) {
+            const uint32_t hi2[4] = {p01, p23, p45, p67};
+            u32x4 r;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                r[j] = pack_bf16x2(e[2 * j] - bf16_bits_to_f32(hi2[j] & 0xFFFFu), e[2 * j + 1] - bf16_bits_to_f32(hi2[j] >> 16));
+                l_run += bf16_bits_to_f32(r[j] & 0xFFFFu) + bf16_bits_to_f32(r[j] >> 16);
+            }
+            pr = __builtin_bit_cast(bf16x8, r);
+        }
         s16x4 lo[WCT], hi[WCT];
         auto rd = [&](int i) {
             const int ct = ch * WCT + i;
@@ -307,6 +392,8 @@ __global__ __launch_bounds__(ST_THREADS, 1) void decode_stream_kernel(DecodePara
             for (int i = c0; i < c0 + VG && i < WCT; ++i) {
                 const s16x8 va = __builtin_shufflevector(lo[i], hi[i], 0, 1, 2, 3, 4, 5, 6, 7);
                 st[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, va), pb, st[i], 0, 0, 0);
+                if constexpr (PAGED)
+                    st[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, va), pr, st[i], 0, 0, 0);
             }
             __builtin_amdgcn_sched_barrier(0);
         }
@@ -356,7 +443,7 @@ __global__ __launch_bounds__(ST_THREADS, 1) void decode_stream_kernel(DecodePara
                 // place in the memory pipeline and hold the scores back)
                 if constexpr (!PROBE) {
                     f32x4 xs;
-                    score_block(lds, rb, t0, rows_valid(t0), xs);
+                    score_block(lds, rb, t0, PAGED ? block_valid(t0, rb) : rows_valid(t0), xs);
                     xbuf[0][hg][rb][lane] = xs;
                     asm volatile("" ::: "memory");
                 }
@@ -368,10 +455,20 @@ __global__ __launch_bounds__(ST_THREADS, 1) void decode_stream_kernel(DecodePara
         for (int t = t0; t < t1; ++t) {
             const int par = (t - t0) & 1;
             LDS_AS unsigned char* tile = lds + ((t - t0) % NBUF) * TILE_B;
-            const int n_valid = rows_valid(t);
+            const int n_valid = PAGED ? block_valid(t, 0) : rows_valid(t);
+            const int n_valid1 = PAGED ? block_valid(t, 1) : 0;
             // tile t's scores are in LDS, tile t + 1 has landed, and everybody is done with tile t - 1
             __syncthreads();
-            if (n_valid < TILE_ROWS) {
+            if (PAGED) {
+                if (n_valid < 16 || n_valid1 < 16) {
+                    // the chunk's end, or a page id outside the pool: as below, block by block
+                    for (int i = tid; i < 32 * CPR; i += ST_THREADS) {
+                        const int r = i / CPR;
+                        if ((r & 15) >= (r < 16 ? n_valid : n_valid1)) *(LDS_AS u32x4*)(tile + i * 16) = (u32x4){0u, 0u, 0u, 0u};
+                    }
+                    __syncthreads();
+                }
+            } else if (n_valid < TILE_ROWS) {
                 // ragged last tile (or a page id outside the pool): rows that are not part of the
                 // sequence become zeros so that whatever they hold stays out
                 for (int i = tid; i < (TILE_ROWS - n_valid) * CPR; i += ST_THREADS)
@@ -384,7 +481,8 @@ __global__ __launch_bounds__(ST_THREADS, 1) void decode_stream_kernel(DecodePara
                 if constexpr (!PROBE) {
                     if (t + 1 < t1) {
                         f32x4 xs;
-                        score_block(lds + ((t + 1 - t0) % NBUF) * TILE_B, rb, t + 1, rows_valid(t + 1), xs);
+                        score_block(lds + ((t + 1 - t0) % NBUF) * TILE_B, rb, t + 1,
+                                    PAGED ? block_valid(t + 1, rb) : rows_valid(t + 1), xs);
                         xbuf[par ^ 1][hg][rb][lane] = xs;
                     }
                 }
@@ -548,6 +646,26 @@ hipError_t launch_decode_stream(const DecodeParams& p, dim3 grid, hipStream_t s)
     dim3 block(ST_THREADS);
     if (p.d_c == 512)      decode_stream_kernel<512, false, false><<<grid, block, 0, s>>>(p);
     else if (p.d_c == 256) decode_stream_kernel<256, false, false><<<grid, block, 0, s>>>(p);
+    else return hipErrorInvalidValue;
+    return hipGetLastError();
+}
+
+// bf16 caches whose pages are 16, 32, 48, 80, ... rows: every such size that the matrix-core tiles can be
+// cut along, whatever the chunk length (the scalar-FMA kernel takes what is left: other multiples)
+bool decode_stream_paged_supported(const DecodeParams& p, mla_dtype io, mla_dtype cache)
+{
+    return io == MLA_BF16 && cache == MLA_BF16 && p.page_size % 16 == 0 && p.page_size != 64 && p.d_rope == 64 &&
+           (p.d_c == 256 || p.d_c == 512) &&
+           ((long long)p.B * p.num_splits + 7) / 8 * 8 * ((p.H + 31) / 32) <= 0x7FFFFFFFLL;
+}
+
+hipError_t launch_decode_stream_paged(const DecodeParams& p, hipStream_t s)
+{
+    const long long n = (long long)p.B * p.num_splits, Z = (p.H + 31) / 32;
+    dim3 grid(p.B, p.num_splits), block(ST_THREADS);
+    if (Z > 1) grid = dim3((unsigned)((n + 7) / 8 * 8 * Z));
+    if (p.d_c == 512)      decode_stream_kernel<512, false, false, true><<<grid, block, 0, s>>>(p);
+    else if (p.d_c == 256) decode_stream_kernel<256, false, false, true><<<grid, block, 0, s>>>(p);
     else return hipErrorInvalidValue;
     return hipGetLastError();
 }

@@ -197,6 +197,9 @@ hipError_t launch_decode_mfma(const DecodeParams& p, mla_dtype cache, hipStream_
 hipError_t launch_decode_stream(const DecodeParams& p, dim3 grid, hipStream_t s);
 // the same kernel under the balanced partition (needs p.plan; launch_decode_mfma's balanced grid)
 hipError_t launch_decode_stream_balanced(const DecodeParams& p, dim3 grid, hipStream_t s);
+// the same kernel for page sizes other than 64 (multiples of 16 rows; uniform partition)
+bool       decode_stream_paged_supported(const DecodeParams& p, mla_dtype io, mla_dtype cache);
+hipError_t launch_decode_stream_paged(const DecodeParams& p, hipStream_t s);
 // the same kernel's tile requests, waits and barriers alone (diagnostic: no query rows, arithmetic or output)
 hipError_t launch_decode_stream_probe(const DecodeParams& p, hipStream_t s);
 // uniform chunks, fp8 caches: wavefronts that turn tiles into softmax weights beside wavefronts that

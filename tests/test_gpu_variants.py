@@ -1,0 +1,85 @@
+"""GPU parity of the kernel variants that sizes, page sizes and alignment choose between, at the sizes
+where each can go wrong (edges of tiles and pages, remainders, smallest and largest of its range)."""
+import numpy as np
+import pytest
+
+import oracle
+from helpers import TOL, DeviceWorkload, lse_err, max_abs_rel, to_torch, widen_gpu
+from test_gpu_parity import check_decode, check_multi, gpu_q_abs, mla, q_abs_storage, run_decode  # noqa: F401
+from workloads import synth
+
+pytestmark = pytest.mark.gpu
+PORTABLE = 1
+
+# ------------------------------------------------------------------ bf16 caches, pages of 16 k rows
+
+PAGED_LENS = [0, 1, 15, 16, 17, 31, 32, 33, 47, 48, 49, 300, 1000]
+
+
+def paged_workload(page, d_c=512, H=32, lens=PAGED_LENS, seed=70, **kw):
+    return synth.make_workload("paged", B=len(lens), H=H, d_head=128, d_c=d_c, d_rope=64, seq_lens=lens, io_dtype="bf16",
+                               cache_dtype="bf16", page_size=page, free_frac=0.1, seed=seed, **kw)
+
+
+@pytest.mark.parametrize("page,d_c,H,splits", [(16, 512, 32, 1), (16, 256, 28, 3), (32, 512, 5, 32), (48, 512, 40, 2),
+                                               (80, 256, 32, 7), (128, 512, 32, 2), (1024, 256, 16, 1)])
+def test_decode_other_page_sizes(mla, page, d_c, H, splits):
+    """Against the oracle, and no further from it than the scalar-FMA kernel (which holds the weights in
+    fp32) by more than the fp32 sums' share: both round the partials and the result to bf16."""
+    w = paged_workload(page, d_c, H)
+    new, old = check_decode(mla, w, splits), check_decode(mla, w, splits, flags=PORTABLE)
+    assert new <= 1.5 * old + 2.0 ** -9
+    import torch
+    d = DeviceWorkload(w)
+    q = gpu_q_abs(mla, d)
+    (a, la), (b, lb) = run_decode(mla, d, q, splits), run_decode(mla, d, q, splits, PORTABLE)
+    torch.cuda.synchronize()
+    # the log-sum-exp is stored in fp32: with weights in two bf16 terms the two kernels agree to 2^-16 and the
+    # fp32 sums of the scores (576 products of size up to a few units: 1e-5)
+    assert lse_err(widen_gpu(la), widen_gpu(lb)) <= 1e-4
+    assert max_abs_rel(widen_gpu(a), widen_gpu(b)) <= 2.0 ** -7      # one bf16 step at the largest value
+
+
+def test_decode_other_page_sizes_bad_pages_and_late_dominant_score(mla):
+    """A page id outside the pool drops its 16 tokens only (first or second half of a 32-row tile, or both),
+    and a score far above the first tile's sends the chunk through the exact pass."""
+    import torch
+    w = paged_workload(16, lens=[256, 200, 64], seed=71)
+    bad = w.page_table.copy()
+    drop = [(0, 1), (0, 4), (0, 6), (0, 7), (1, 12), (2, 0)]
+    for b, i in drop:
+        bad[b, i] = w.num_pages + 3 if i % 2 else -1
+    pt = np.full_like(w.page_table, -1)
+    lens = w.seq_lens.copy()
+    for b in range(3):
+        keep = [i for i in range((w.seq_lens[b] + 15) // 16) if (b, i) not in drop]
+        pt[b, :len(keep)] = w.page_table[b, keep]
+        lens[b] = sum(min(16, w.seq_lens[b] - 16 * i) for i in keep)
+    for flags in (0, PORTABLE):
+        d = DeviceWorkload(w)
+        d.page_table = to_torch(bad, "i32")
+        q = gpu_q_abs(mla, d)
+        o, lse = run_decode(mla, d, q, 2, flags)
+        torch.cuda.synchronize()
+        ref, ref_lse = oracle.decode_absorbed(q_abs_storage(q), w.q_rope, w.pool, None, pt, lens, w.softmax_scale)
+        assert max_abs_rel(widen_gpu(o), ref) <= TOL["bf16"] and lse_err(widen_gpu(lse), ref_lse) <= 2e-2
+    rows = oracle.widen(oracle.gather_paged(w.pool, w.page_table, w.seq_lens, 256).view(np.uint16))
+    target = np.stack([rows[0, 217, :512], rows[1, 199, :512], rows[2, 63, :512]])
+    q1 = to_torch(synth.to_bf16_bits((40.0 * target[:, None, :].repeat(32, 1)).astype(np.float32)), "bf16")
+    d = DeviceWorkload(w)
+    o = mla.decode_paged(q1, torch.zeros((3, 32, 64), dtype=torch.bfloat16, device="cuda"), d.pool, d.page_table,
+                         d.seq_lens, w.softmax_scale, num_splits=1)
+    torch.cuda.synchronize()
+    assert np.abs(widen_gpu(o) - target[:, None, :]).max() <= 2e-2 * np.abs(target).max()
+
+
+@pytest.mark.parametrize("page,T", [(16, 2), (32, 3)])
+def test_multi_token_other_page_sizes(mla, page, T):
+    check_multi(mla, paged_workload(page, lens=[0, 1, 2, 16, 33, 47, 320], H=28, seed=72), T, 2, fused_tail=True)
+
+
+def test_other_page_sizes_keep_refusing_the_balanced_partition(mla):
+    w = paged_workload(16, lens=[64, 64])
+    d = DeviceWorkload(w)
+    with pytest.raises(mla.MlaError):
+        run_decode(mla, d, gpu_q_abs(mla, d), 2, mla.FLAG_BALANCED)
