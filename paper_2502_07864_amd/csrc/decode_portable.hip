@@ -2,272 +2,321 @@
 // pair and shape, the split-KV merge, and the page gather test hook.
 //
 // The decode kernel is the library's reference GPU path: it is the only path
-// for fp32 and fp8 caches and for shapes the matrix-core kernel does not
-// cover.  One workgroup handles (chunk, sequence, group of 8 heads): a tile of
-// 16 cached rows is widened to fp32 in LDS, scored against the 8 query rows,
-// folded into a running softmax (second line of the absorbed attention
-// equation, Sec. 3.3 of the paper) and accumulated into the latent output.
+// for fp32 caches and fp32 io and for shapes the matrix-core kernels do not
+// cover.  One workgroup handles (chunk, sequence, group of HG heads); its four
+// wavefronts take the chunk's rows four or eight at a time, in turn, and share nothing
+// until the end: a row lives in the registers of one wavefront, lane l holding
+// the four latent values 4 l .. 4 l + 3, the four from 256 further on, and (the
+// first lanes) four of the rope part, so the same registers serve the score
+// (second line of the absorbed attention equation, Sec. 3.3 of the paper) and the
+// latent sum, and no row passes through LDS.  The sums over the lanes of all its
+// scores are taken together, halving the values with every exchange of lane
+// halves.  A running softmax per wavefront, joined over the four at the end.
+//
+// The kernel is bound by latency on a small call (one short sequence) and by the
+// vector pipes on a large one (about 25 instructions per row and head for 17 useful
+// ones).  Its predecessor staged 16 rows at a time in LDS between four workgroup
+// barriers: one fp32 sequence of 1024 rows, 32 heads, d_c = 512, 16 chunks: 23.5 us on
+// 64 workgroups, 10.1 here; 4 sequences of 2000 rows in 28 chunks: 53.0 and 29.4; 16 bf16 sequences of 8192
+// rows in 63-row pages: 493 and 373; eight fp32 sequences of 4000 rows, every row read eight times from
+// L2: 108 and 101 (back to back in a graph).
 #include "mla_internal.h"
 #include <type_traits>
 
 namespace mla {
 namespace {
 
-constexpr int PT_THREADS = 256;
-constexpr int PT_HG = 8;        // heads per workgroup
-constexpr int PT_TOK = 16;      // cached rows per tile
-constexpr int PT_MAX_ROW = 576; // max d_c + d_rope
-constexpr int PT_PAD = 4;       // LDS row padding (floats): rows stay 16-byte aligned (128-bit reads) and
-                                // consecutive rows start one 16-byte unit apart
-constexpr int PT_MAX_COLS = 2;  // d_c <= 512 = 2 * 256 threads
-
-template <typename T> struct Load8;
-
-template <> struct Load8<float> {
-    static __device__ __forceinline__ void run(const void* base, size_t elem, const float*, size_t, float* out)
-    {
-        const float4* p = reinterpret_cast<const float4*>(static_cast<const float*>(base) + elem);
-        float4 a = p[0], b = p[1];
-        out[0] = a.x; out[1] = a.y; out[2] = a.z; out[3] = a.w;
-        out[4] = b.x; out[5] = b.y; out[6] = b.z; out[7] = b.w;
-    }
-};
+constexpr int PR_THREADS = 256;
+constexpr int PR_WAVES = 4;
+constexpr int PR_MAX_DC = 512;    // two groups of four latent values per lane; d_rope <= 64: one on the first 16 lanes
 
 struct bf16_tag {};
-template <> struct Load8<bf16_tag> {
-    static __device__ __forceinline__ void run(const void* base, size_t elem, const float*, size_t, float* out)
-    {
-        uint4 v = *reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(base) + elem);
-        uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            out[2 * i]     = bf16_bits_to_f32(w[i] & 0xFFFFu);
-            out[2 * i + 1] = bf16_bits_to_f32(w[i] >> 16);
-        }
-    }
-};
-
 struct fp8_tag {};
-template <> struct Load8<fp8_tag> {
-    static __device__ __forceinline__ void run(const void* base, size_t elem, const float* scale, size_t row, float* out)
+
+// four consecutive cached values as they are stored, and widened (fp8: the codes; a token's scale is
+// applied to its score and its weight)
+template <typename CT> struct Raw4;
+template <> struct Raw4<float> {
+    float4 v;
+    __device__ __forceinline__ void load(const void* base, size_t elem) { v = *reinterpret_cast<const float4*>(static_cast<const float*>(base) + elem); }
+    __device__ __forceinline__ void zero() { v = make_float4(0.f, 0.f, 0.f, 0.f); }
+    __device__ __forceinline__ float4 get() const { return v; }
+};
+template <> struct Raw4<bf16_tag> {
+    uint2 v;
+    __device__ __forceinline__ void load(const void* base, size_t elem) { v = *reinterpret_cast<const uint2*>(static_cast<const uint16_t*>(base) + elem); }
+    __device__ __forceinline__ void zero() { v = make_uint2(0u, 0u); }
+    __device__ __forceinline__ float4 get() const
     {
-        uint2 v = *reinterpret_cast<const uint2*>(static_cast<const uint8_t*>(base) + elem);
-        float s = scale[row];
-        uint32_t w[2] = {v.x, v.y};
-#pragma unroll
-        for (int i = 0; i < 8; ++i) out[i] = e4m3_to_f32((w[i >> 2] >> (8 * (i & 3))) & 0xFFu) * s;
+        return make_float4(bf16_bits_to_f32(v.x & 0xFFFFu), __uint_as_float(v.x & 0xFFFF0000u),
+                           bf16_bits_to_f32(v.y & 0xFFFFu), __uint_as_float(v.y & 0xFFFF0000u));
+    }
+};
+template <> struct Raw4<fp8_tag> {
+    uint32_t v;
+    __device__ __forceinline__ void load(const void* base, size_t elem) { v = *reinterpret_cast<const uint32_t*>(static_cast<const uint8_t*>(base) + elem); }
+    __device__ __forceinline__ void zero() { v = 0u; }
+    __device__ __forceinline__ float4 get() const
+    {
+        const auto lo = __builtin_amdgcn_cvt_pk_f32_fp8(v, false), hi = __builtin_amdgcn_cvt_pk_f32_fp8(v, true);
+        return make_float4(lo[0], lo[1], hi[0], hi[1]);
     }
 };
 
-// four consecutive query values (element index a multiple of 4)
-template <typename QT> __device__ __forceinline__ float4 load_q4(const void* p, size_t i);
-template <> __device__ __forceinline__ float4 load_q4<float>(const void* p, size_t i)
+// a + b over the lane halves (32) or over the halves of each 32 lanes (16): lanes of the first half get the
+// sum of `a`, lanes of the second the sum of `b`
+__device__ __forceinline__ float fold32(float a, float b)
 {
-    return *reinterpret_cast<const float4*>(static_cast<const float*>(p) + i);
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
-template <> __device__ __forceinline__ float4 load_q4<bf16_tag>(const void* p, size_t i)
+__device__ __forceinline__ float fold16(float a, float b)
 {
-    const uint2 v = *reinterpret_cast<const uint2*>(static_cast<const uint16_t*>(p) + i);
-    return make_float4(bf16_bits_to_f32(v.x & 0xFFFFu), bf16_bits_to_f32(v.x >> 16),
-                       bf16_bits_to_f32(v.y & 0xFFFFu), bf16_bits_to_f32(v.y >> 16));
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+// sum over 16 lanes, on all of them (rotations inside the row of 16)
+__device__ __forceinline__ float sum16(float v)
+{
+    v += __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(v), 0x128, 0xf, 0xf, false));   // row_ror:8
+    v += __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(v), 0x124, 0xf, 0xf, false));
+    v += __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(v), 0x122, 0xf, 0xf, false));
+    return v + __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(v), 0x121, 0xf, 0xf, false));
 }
 
-template <typename QT, typename CT>
-__global__ __launch_bounds__(PT_THREADS) void decode_portable_kernel(DecodeParams p)
+__device__ __forceinline__ float dot4(float4 a, float4 b, float s)
 {
-    __shared__ __attribute__((aligned(16))) float q_s[PT_HG][PT_MAX_ROW + PT_PAD];
-    __shared__ __attribute__((aligned(16))) float k_s[PT_TOK][PT_MAX_ROW + PT_PAD];
-    __shared__ __attribute__((aligned(16))) float s_s[PT_HG][PT_TOK];
-    __shared__ __attribute__((aligned(16))) float p_s[PT_TOK][PT_HG];     // weights, token-major: the 8 heads of a token are adjacent
-    __shared__ __attribute__((aligned(16))) float alpha_s[PT_HG];
-    __shared__ float m_s[PT_HG], l_s[PT_HG];
-    __shared__ int valid_s[PT_TOK];
+    return fmaf(a.w, b.w, fmaf(a.z, b.z, fmaf(a.y, b.y, fmaf(a.x, b.x, s))));
+}
 
-    const int tid = threadIdx.x;
-    const int split = blockIdx.x, b = blockIdx.y, h0 = blockIdx.z * PT_HG;
+// ROWS: rows of a wavefront's batch (the next batch is on its way while one is used): as many as fit
+// beside the queries and the sums of HG heads with two wavefronts per SIMD
+template <typename QT, typename CT, int HG, int ROWS>
+__global__ __launch_bounds__(PR_THREADS) void decode_portable_kernel(DecodeParams p)
+{
+    __shared__ __attribute__((aligned(16))) float o_s[PR_WAVES][HG][PR_MAX_DC];
+    __shared__ float m_s[PR_WAVES][HG], l_s[PR_WAVES][HG];
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // the head groups of one chunk of rows get linear ids 8 apart: same XCD, so all but the first find
+    // the rows in its L2
+    const int Z = (p.H + HG - 1) / HG;
+    const long id = (long)blockIdx.y * gridDim.x + blockIdx.x, rr = id >> 3;
+    const long wg = (rr / Z) * 8 + (id & 7);
+    if (wg >= (long)p.B * p.num_splits) return;           // padding of the last group of 8, and of the grid
+    const int h0 = (int)(rr % Z) * HG, split = (int)(wg % p.num_splits), b = (int)(wg / p.num_splits);
     const int row = p.d_c + p.d_rope;
-    const int nh = min(PT_HG, p.H - h0);
+    const int nh = min(HG, p.H - h0);
 
     int L = p.seq_lens[b];
     L = max(0, min(L, p.max_pages * p.page_size));
     const long chunk_tok = (long)p.chunk_pages * p.page_size;
-    const long j0l = min((long)L, (long)split * chunk_tok);
-    const long j1l = min((long)L, j0l + chunk_tok);
-    const int j0 = (int)j0l, j1 = (int)j1l;
+    const int j0 = (int)min((long)L, (long)split * chunk_tok);
+    const int j1 = (int)min((long)L, j0 + chunk_tok);
     if (j0 >= j1) {  // empty chunk: weight zero in the merge, partial output never read
         if (tid < nh) p.lse_part[part_index(b, h0 + tid, split, p.H, p.num_splits)] = -INFINITY;
         return;
     }
 
-    // query rows [q_abs | q_rope] of this head group -> LDS (fp32), four values per load, all of a
-    // thread's loads requested before the first is used (one after the other they would each wait
-    // out the memory latency)
-    {
-        constexpr int PT_NQ = (PT_HG * (PT_MAX_ROW / 4) + PT_THREADS - 1) / PT_THREADS;   // 5
-        const int q4_per_row = row / 4;
-        float4 qv[PT_NQ];
-#pragma unroll
-        for (int i = 0; i < PT_NQ; ++i) {
-            const int idx = tid + i * PT_THREADS;
-            const int h = idx / q4_per_row, k = (idx % q4_per_row) * 4;
-            qv[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (h < nh) {
-                const size_t bh = (size_t)b * p.H + h0 + h;
-                qv[i] = k < p.d_c ? load_q4<QT>(p.q_abs, bh * p.d_c + k)
-                                  : load_q4<QT>(p.q_rope, bh * p.d_rope + (k - p.d_c));
+    // this lane's columns: latent 4 lane and 256 + 4 lane, rope 4 lane
+    const bool has[3] = {4 * lane < p.d_c, 256 + 4 * lane < p.d_c, 4 * lane < p.d_rope};
+    // ---- where a batch's rows lie: lane r < ROWS looks up row r of the batch (-1: past the chunk, or on a
+    // page outside the pool)
+    auto locate = [&](int jb, long& at, float& scale) {
+        at = -1;
+        scale = 1.f;
+        const int j = jb + lane;
+        if (lane < ROWS && j < j1) {
+            const int page = p.page_table[(size_t)b * p.max_pages + j / p.page_size];
+            if (page >= 0 && page < p.num_pages) {
+                at = (long)page * p.page_size + j % p.page_size;
+                if constexpr (std::is_same<CT, fp8_tag>::value) scale = p.kv_scale[at];
             }
-        }
-#pragma unroll
-        for (int i = 0; i < PT_NQ; ++i) {
-            const int idx = tid + i * PT_THREADS;
-            const int h = idx / q4_per_row, k = (idx % q4_per_row) * 4;
-            if (h < PT_HG) *static_cast<float4*>(__builtin_assume_aligned(&q_s[h][k], 16)) = qv[i];
-        }
-    }
-    if (tid < PT_HG) { m_s[tid] = -INFINITY; l_s[tid] = 0.f; }
-
-    float acc[PT_MAX_COLS][PT_HG];
-#pragma unroll
-    for (int i = 0; i < PT_MAX_COLS; ++i)
-#pragma unroll
-        for (int h = 0; h < PT_HG; ++h) acc[i][h] = 0.f;
-
-    const int chunks_per_row = row / 8;
-    // softmax step (16 threads per head): the head's own upper limit of the sum (several query
-    // tokens per sequence)
-    const int my_limit = visible_rows(p, L, h0 + min(tid / PT_TOK, PT_HG - 1));
-    // ---- tile staging, one tile ahead in registers: a thread owns up to PT_NIT pieces (8 values of one
-    // row) of every tile; the next tile's pieces are requested before the current tile is used, so
-    // their latency runs under its arithmetic.  Rows outside the chunk or on a bad page are zero.
-    constexpr int PT_NIT = (PT_TOK * (PT_MAX_ROW / 8) + PT_THREADS - 1) / PT_THREADS;   // 5
-    int st_t[PT_NIT], st_c[PT_NIT];          // row of the tile and first column of each piece (-1: none)
-#pragma unroll
-    for (int i = 0; i < PT_NIT; ++i) {
-        const int idx = tid + i * PT_THREADS;
-        st_t[i] = idx < PT_TOK * chunks_per_row ? idx / chunks_per_row : -1;
-        st_c[i] = (idx % chunks_per_row) * 8;
-    }
-    float st_v[PT_NIT][8];
-    bool st_ok[PT_NIT];
-    auto fetch = [&](int t0) {
-#pragma unroll
-        for (int i = 0; i < PT_NIT; ++i) {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) st_v[i][e] = 0.f;
-            const int j = t0 + st_t[i];
-            bool ok = st_t[i] >= 0 && j < j1;
-            if (ok) {
-                const int page = p.page_table[(size_t)b * p.max_pages + j / p.page_size];
-                ok = page >= 0 && page < p.num_pages;
-                if (ok) {
-                    const size_t r = (size_t)page * p.page_size + (j % p.page_size);
-                    Load8<CT>::run(p.kv, r * row + st_c[i], p.kv_scale, r, st_v[i]);
-                }
-            }
-            st_ok[i] = ok;
         }
     };
-    fetch(j0);
-    for (int t0 = j0; t0 < j1; t0 += PT_TOK) {
-        __syncthreads();  // previous tile fully consumed (and q_s / m_s written)
+    struct Batch {
+        Raw4<CT> v[ROWS][3];
+        unsigned live;             // bit r: row r is there
+        float scale;               // lane r: scale of row r (fp8)
+    };
+    auto fetch = [&](long at, float scale, Batch& x) {
+        x.live = (unsigned)__ballot(at >= 0);
+        x.scale = scale;
 #pragma unroll
-        for (int i = 0; i < PT_NIT; ++i) {
-            if (st_t[i] >= 0) {
-                if (st_c[i] == 0) valid_s[st_t[i]] = st_ok[i] ? 1 : 0;
-                float4* dst = static_cast<float4*>(__builtin_assume_aligned(&k_s[st_t[i]][st_c[i]], 16));
-                dst[0] = make_float4(st_v[i][0], st_v[i][1], st_v[i][2], st_v[i][3]);
-                dst[1] = make_float4(st_v[i][4], st_v[i][5], st_v[i][6], st_v[i][7]);
+        for (int r = 0; r < ROWS; ++r) {
+            // a row that is not there is read from the start of the pool and left out of the sums
+            const long a = max(0L, (long)(((unsigned long)(unsigned)__builtin_amdgcn_readlane((int)(at >> 32), r) << 32) |
+                                          (unsigned)__builtin_amdgcn_readlane((int)at, r)));
+            const size_t base = (size_t)a * row + 4 * lane;
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                x.v[r][c].zero();
+                if (has[c]) x.v[r][c].load(p.kv, base + (c == 0 ? 0 : c == 1 ? 256 : p.d_c));
             }
         }
-        if (t0 + PT_TOK < j1) fetch(t0 + PT_TOK);
-        __syncthreads();
-        // ---- scores: (head, token) pair per two threads, each half of the row
-        if (tid < PT_HG * PT_TOK * 2) {
-            int pair = tid >> 1, half = tid & 1;
-            int h = pair / PT_TOK, t = pair % PT_TOK;
-            int kb = half * (row / 2), ke = kb + row / 2;
-            // 128-bit LDS reads (an LDS instruction costs the wavefront ~17 cycles of issue whatever
-            // its width), four partial sums
-            float d0 = 0.f, d1 = 0.f, d2 = 0.f, d3 = 0.f;
-#pragma unroll 8
-            for (int k = kb; k < ke; k += 4) {
-                // (rows are 16-byte aligned and row / 2 is a multiple of 4 values: said out loud, or the
-                // compiler falls back to 64-bit reads)
-                const float4 qv = *static_cast<const float4*>(__builtin_assume_aligned(&q_s[h][k], 16));
-                const float4 kv4 = *static_cast<const float4*>(__builtin_assume_aligned(&k_s[t][k], 16));
-                d0 = fmaf(qv.x, kv4.x, d0); d1 = fmaf(qv.y, kv4.y, d1);
-                d2 = fmaf(qv.z, kv4.z, d2); d3 = fmaf(qv.w, kv4.w, d3);
-            }
-            float dot = (d0 + d1) + (d2 + d3);
-            dot += __shfl_xor(dot, 1);
-            if (half == 0) s_s[h][t] = valid_s[t] ? dot * p.scale : -INFINITY;
+    };
+
+    long at;
+    float sc_at;
+    const int jstep = PR_WAVES * ROWS;
+    int jb = j0 + wave * ROWS;
+    locate(jb, at, sc_at);
+
+    // ---- query rows [q_abs | q_rope], this lane's columns
+    float4 q[HG][3];
+    int limit[HG];                // first row the head's query token does not see
+#pragma unroll
+    for (int h = 0; h < HG; ++h) {
+        const int hq = h0 + min(h, nh - 1);
+        const size_t bh = (size_t)b * p.H + hq;
+        limit[h] = h < nh ? visible_rows(p, L, hq) : 0;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            Raw4<QT> t;
+            t.zero();
+            if (has[c]) t.load(c < 2 ? p.q_abs : p.q_rope, c < 2 ? bh * p.d_c + c * 256 + 4 * lane : bh * p.d_rope + 4 * lane);
+            q[h][c] = t.get();
         }
-        __syncthreads();
-        // ---- running softmax: one thread per (head, token) of the tile, the 16 lanes of a head side
-        // by side in one wavefront (maximum and sum by lane shuffles)
-        if (tid < PT_HG * PT_TOK) {
-            const int h = tid / PT_TOK, t = tid % PT_TOK;
-            const float sv = t0 + t < my_limit ? s_s[h][t] : -INFINITY;
-            float tmax = sv;
+    }
+
+    float4 acc[HG][2];
+    float m[HG], l[HG];
 #pragma unroll
-            for (int o = PT_TOK / 2; o > 0; o >>= 1) tmax = fmaxf(tmax, __shfl_xor(tmax, o));
-            const float m_old = m_s[h];
-            const float m_new = fmaxf(m_old, tmax);
-            const float e = m_new == -INFINITY ? 0.f : expf(sv - m_new);
-            p_s[t][h] = e;
-            float sum = e;
+    for (int h = 0; h < HG; ++h) {
+        acc[h][0] = acc[h][1] = make_float4(0.f, 0.f, 0.f, 0.f);
+        m[h] = -INFINITY;
+        l[h] = 0.f;
+    }
+    const int g = lane >> 4;      // after the exchanges the 16 lanes of group g hold the scores of rows g, g + 4, ..
+    constexpr int NK = ROWS / 4;
+    static_assert(ROWS % 4 == 0 && ROWS <= 32, "rows of a lane group; bits of live");
+
+    auto consume = [&](const Batch& x, int jb) {
+        float s[HG][NK];
+        {
+            float d[HG][ROWS];
 #pragma unroll
-            for (int o = PT_TOK / 2; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
-            if (t == 0) {
-                const float a = m_new == -INFINITY ? 1.f : expf(m_old - m_new);  // exp(-inf) = 0 on the first tile
-                alpha_s[h] = a;
-                l_s[h] = l_s[h] * a + sum;
-                m_s[h] = m_new;
+            for (int r = 0; r < ROWS; ++r) {
+                const float4 k0 = x.v[r][0].get(), k1 = x.v[r][1].get(), k2 = x.v[r][2].get();
+#pragma unroll
+                for (int h = 0; h < HG; ++h) d[h][r] = dot4(q[h][2], k2, dot4(q[h][1], k1, dot4(q[h][0], k0, 0.f)));
+            }
+#pragma unroll
+            for (int h = 0; h < HG; ++h)
+#pragma unroll
+                for (int k = 0; k < NK; ++k)   // group g = 2 (upper half of the lanes) + (odd row of 16)
+                    s[h][k] = sum16(fold16(fold32(d[h][4 * k], d[h][4 * k + 2]), fold32(d[h][4 * k + 1], d[h][4 * k + 3])));
+        }
+        float sck[NK];
+#pragma unroll
+        for (int k = 0; k < NK; ++k) sck[k] = std::is_same<CT, fp8_tag>::value ? __shfl(x.scale, g + 4 * k) : 1.f;
+        float w[HG][NK];
+#pragma unroll
+        for (int h = 0; h < HG; ++h) {
+#pragma unroll
+            for (int k = 0; k < NK; ++k) {
+                const bool seen = ((x.live >> (g + 4 * k)) & 1u) && jb + g + 4 * k < limit[h];
+                s[h][k] = seen ? s[h][k] * sck[k] * p.scale : -INFINITY;
+            }
+            float tm = s[h][0];
+#pragma unroll
+            for (int k = 1; k < NK; ++k) tm = fmaxf(tm, s[h][k]);
+            tm = fmaxf(tm, __shfl_xor(tm, 16));
+            tm = fmaxf(tm, __shfl_xor(tm, 32));
+            const float m_new = fmaxf(m[h], tm);
+            if (__any(m_new != m[h])) {
+                const float a = m_new == -INFINITY ? 1.f : expf(m[h] - m_new);   // exp(-inf) = 0 on the first batch
+                l[h] *= a;
+#pragma unroll
+                for (int c = 0; c < 2; ++c) { acc[h][c].x *= a; acc[h][c].y *= a; acc[h][c].z *= a; acc[h][c].w *= a; }
+                m[h] = m_new;
+            }
+#pragma unroll
+            for (int k = 0; k < NK; ++k) {
+                const float e = m_new == -INFINITY ? 0.f : expf(s[h][k] - m_new);
+                l[h] += e;                       // this lane group's rows; joined at the end
+                w[h][k] = e * sck[k];
             }
         }
-        __syncthreads();
-        // ---- latent values: thread owns columns tid, tid+256
 #pragma unroll
-        for (int i = 0; i < PT_MAX_COLS; ++i) {
-            int c = tid + i * PT_THREADS;
-            if (c < p.d_c) {
-                static_assert(PT_HG == 8, "two 128-bit reads fetch the weights of a token");
-                {
-                    const float4 a0 = *reinterpret_cast<const float4*>(&alpha_s[0]);
-                    const float4 a1 = *reinterpret_cast<const float4*>(&alpha_s[4]);
-                    acc[i][0] *= a0.x; acc[i][1] *= a0.y; acc[i][2] *= a0.z; acc[i][3] *= a0.w;
-                    acc[i][4] *= a1.x; acc[i][5] *= a1.y; acc[i][6] *= a1.z; acc[i][7] *= a1.w;
+        for (int r = 0; r < ROWS; ++r) {
+            if ((x.live >> r) & 1u) {            // (uniform) what was read for an absent row is not even multiplied by zero
+                const float4 v0 = x.v[r][0].get(), v1 = x.v[r][1].get();
+#pragma unroll
+                for (int h = 0; h < HG; ++h) {
+                    const float wr = lane_value(w[h][r >> 2], 16 * (r & 3));
+                    acc[h][0].x = fmaf(wr, v0.x, acc[h][0].x); acc[h][0].y = fmaf(wr, v0.y, acc[h][0].y);
+                    acc[h][0].z = fmaf(wr, v0.z, acc[h][0].z); acc[h][0].w = fmaf(wr, v0.w, acc[h][0].w);
+                    acc[h][1].x = fmaf(wr, v1.x, acc[h][1].x); acc[h][1].y = fmaf(wr, v1.y, acc[h][1].y);
+                    acc[h][1].z = fmaf(wr, v1.z, acc[h][1].z); acc[h][1].w = fmaf(wr, v1.w, acc[h][1].w);
                 }
-#pragma unroll
-                for (int t = 0; t < PT_TOK; ++t) {
-                    const float v = k_s[t][c];
-                    const float4 w0 = *reinterpret_cast<const float4*>(&p_s[t][0]);
-                    const float4 w1 = *reinterpret_cast<const float4*>(&p_s[t][4]);
-                    acc[i][0] = fmaf(w0.x, v, acc[i][0]); acc[i][1] = fmaf(w0.y, v, acc[i][1]);
-                    acc[i][2] = fmaf(w0.z, v, acc[i][2]); acc[i][3] = fmaf(w0.w, v, acc[i][3]);
-                    acc[i][4] = fmaf(w1.x, v, acc[i][4]); acc[i][5] = fmaf(w1.y, v, acc[i][5]);
-                    acc[i][6] = fmaf(w1.z, v, acc[i][6]); acc[i][7] = fmaf(w1.w, v, acc[i][7]);
-                }
             }
         }
+    };
+
+    if (jb < j1) {
+        Batch x0, x1;
+        fetch(at, sc_at, x0);
+        locate(jb + jstep, at, sc_at);
+        while (true) {
+            fetch(at, sc_at, x1);                // the next batch (its rows may all be absent: nothing is used then)
+            locate(jb + 2 * jstep, at, sc_at);
+            consume(x0, jb);
+            jb += jstep;
+            if (jb >= j1) break;
+            fetch(at, sc_at, x0);
+            locate(jb + 2 * jstep, at, sc_at);
+            consume(x1, jb);
+            jb += jstep;
+            if (jb >= j1) break;
+        }
+    }
+
+    // ---- the four wavefronts' softmax states joined: every thread finishes columns of every head
+#pragma unroll
+    for (int h = 0; h < HG; ++h) {
+        float lt = l[h] + __shfl_xor(l[h], 16);
+        lt += __shfl_xor(lt, 32);
+        if (lane == 0) { m_s[wave][h] = m[h]; l_s[wave][h] = lt; }
+        if (has[0]) *reinterpret_cast<float4*>(&o_s[wave][h][4 * lane]) = acc[h][0];
+        if (has[1]) *reinterpret_cast<float4*>(&o_s[wave][h][256 + 4 * lane]) = acc[h][1];
     }
     __syncthreads();
+    for (int h = wave; h < nh; h += PR_WAVES) {
+        float mt = -INFINITY;
 #pragma unroll
-    for (int i = 0; i < PT_MAX_COLS; ++i) {
-        int c = tid + i * PT_THREADS;
-        if (c < p.d_c) {
-            for (int h = 0; h < nh; ++h) {
-                float l = l_s[h];
-                const float val = l > 0.f ? acc[i][h] / l : 0.f;
-                const size_t at = part_index(b, h0 + h, split, p.H, p.num_splits) * p.d_c + c;
-                if constexpr (std::is_same<QT, bf16_tag>::value) static_cast<uint16_t*>(p.o_part)[at] = (uint16_t)f32_to_bf16_bits(val);
-                else                                             static_cast<float*>(p.o_part)[at] = val;
+        for (int w = 0; w < PR_WAVES; ++w) mt = fmaxf(mt, m_s[w][h]);
+        float f[PR_WAVES], lt = 0.f;
+#pragma unroll
+        for (int w = 0; w < PR_WAVES; ++w) {
+            f[w] = mt == -INFINITY ? 0.f : expf(m_s[w][h] - mt);
+            lt = fmaf(l_s[w][h], f[w], lt);
+        }
+        const size_t pi = part_index(b, h0 + h, split, p.H, p.num_splits);
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            if (!has[c]) continue;
+            const int col = c * 256 + 4 * lane;
+            float o[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int w = 0; w < PR_WAVES; ++w) {
+                const float4 v = *reinterpret_cast<const float4*>(&o_s[w][h][col]);
+                o[0] = fmaf(f[w], v.x, o[0]); o[1] = fmaf(f[w], v.y, o[1]);
+                o[2] = fmaf(f[w], v.z, o[2]); o[3] = fmaf(f[w], v.w, o[3]);
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) o[i] = lt > 0.f ? o[i] / lt : 0.f;
+            if constexpr (std::is_same<QT, bf16_tag>::value) {
+                uint2 r;
+                r.x = f32_to_bf16_bits(o[0]) | (f32_to_bf16_bits(o[1]) << 16);
+                r.y = f32_to_bf16_bits(o[2]) | (f32_to_bf16_bits(o[3]) << 16);
+                *reinterpret_cast<uint2*>(static_cast<uint16_t*>(p.o_part) + pi * p.d_c + col) = r;
+            } else {
+                *reinterpret_cast<float4*>(static_cast<float*>(p.o_part) + pi * p.d_c + col) = make_float4(o[0], o[1], o[2], o[3]);
             }
         }
-    }
-    if (tid < nh) {
-        float l = l_s[tid];
-        p.lse_part[part_index(b, h0 + tid, split, p.H, p.num_splits)] = l > 0.f ? m_s[tid] + logf(l) : -INFINITY;
+        if (lane == 0) p.lse_part[pi] = lt > 0.f ? mt + logf(lt) : -INFINITY;
     }
 }
 
@@ -456,22 +505,33 @@ __global__ __launch_bounds__(256) void gather_kernel(const uint32_t* kv, const i
 
 }  // namespace
 
+template <typename QT, typename CT>
+static hipError_t launch_portable(const DecodeParams& p, hipStream_t s)
+{
+    // Four heads per workgroup read every row eight times for 32 heads (from L2, the groups of a chunk run
+    // side by side); two heads, when four leave CUs without a workgroup: then the call is as long as one
+    // workgroup's rows take (fp32, one sequence of 1024 rows in 16 chunks, 32 heads: 10.1 us with two,
+    // 13.5 with four; 4000 rows in 60 chunks: 28.8 and 21.9; 8 x 4000 rows: 218 and 101).  Eight heads leave
+    // one wavefront per SIMD: 151 us there, 22.9 on the one short sequence.
+    const long long n = ((long long)p.B * p.num_splits + 7) / 8 * 8;
+    const int hg = n * ((p.H + 3) / 4) >= 256 ? 4 : 2;
+    const long long wgs = n * ((p.H + hg - 1) / hg);
+    const long long gx = wgs < (1 << 20) ? wgs : 1 << 20, gy = (wgs + gx - 1) / gx;   // a grid dimension holds 2^32 threads
+    if (gy > 65535) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)gx, (unsigned)gy);
+    if (hg == 4) decode_portable_kernel<QT, CT, 4, 4><<<grid, PR_THREADS, 0, s>>>(p);
+    else         decode_portable_kernel<QT, CT, 2, 8><<<grid, PR_THREADS, 0, s>>>(p);
+    return hipGetLastError();
+}
+
 hipError_t launch_decode_portable(const DecodeParams& p, mla_dtype io, mla_dtype cache, hipStream_t s)
 {
-    dim3 grid(p.num_splits, p.B, (p.H + PT_HG - 1) / PT_HG), block(PT_THREADS);
-    if (io == MLA_F32 && cache == MLA_F32)
-        decode_portable_kernel<float, float><<<grid, block, 0, s>>>(p);
-    else if (io == MLA_F32 && cache == MLA_BF16)
-        decode_portable_kernel<float, bf16_tag><<<grid, block, 0, s>>>(p);
-    else if (io == MLA_F32 && cache == MLA_FP8_E4M3)
-        decode_portable_kernel<float, fp8_tag><<<grid, block, 0, s>>>(p);
-    else if (io == MLA_BF16 && cache == MLA_BF16)
-        decode_portable_kernel<bf16_tag, bf16_tag><<<grid, block, 0, s>>>(p);
-    else if (io == MLA_BF16 && cache == MLA_FP8_E4M3)
-        decode_portable_kernel<bf16_tag, fp8_tag><<<grid, block, 0, s>>>(p);
-    else
-        return hipErrorInvalidValue;
-    return hipGetLastError();
+    if (io == MLA_F32 && cache == MLA_F32) return launch_portable<float, float>(p, s);
+    if (io == MLA_F32 && cache == MLA_BF16) return launch_portable<float, bf16_tag>(p, s);
+    if (io == MLA_F32 && cache == MLA_FP8_E4M3) return launch_portable<float, fp8_tag>(p, s);
+    if (io == MLA_BF16 && cache == MLA_BF16) return launch_portable<bf16_tag, bf16_tag>(p, s);
+    if (io == MLA_BF16 && cache == MLA_FP8_E4M3) return launch_portable<bf16_tag, fp8_tag>(p, s);
+    return hipErrorInvalidValue;
 }
 
 hipError_t launch_merge(const MergeParams& p, mla_dtype io, hipStream_t s)

@@ -83,3 +83,39 @@ def test_other_page_sizes_keep_refusing_the_balanced_partition(mla):
     d = DeviceWorkload(w)
     with pytest.raises(mla.MlaError):
         run_decode(mla, d, gpu_q_abs(mla, d), 2, mla.FLAG_BALANCED)
+
+
+# ------------------------------------------------------------------ scalar-FMA decode and fp32 projections
+
+@pytest.mark.parametrize("io,cache,d_c,d_rope,page,H,splits", [
+    ("f32", "f32", 512, 64, 64, 32, 4), ("f32", "f32", 8, 8, 1, 1, 1), ("f32", "f32", 264, 16, 7, 3, 2),
+    ("f32", "bf16", 256, 0, 5, 5, 3), ("f32", "fp8_e4m3", 40, 64, 3, 33, 2), ("bf16", "fp8_e4m3", 512, 64, 16, 28, 5),
+    ("bf16", "bf16", 384, 64, 64, 66, 2), ("bf16", "bf16", 512, 32, 13, 2, 40)])
+def test_scalar_decode_shapes(mla, io, cache, d_c, d_rope, page, H, splits):
+    """Rows per wavefront batch (4 and 8) and per workgroup (16 and 32) on both sides, empty and one-row
+    sequences, columns that fill neither, one or both groups of 256, page sizes that cut every batch."""
+    lens = [0, 1, 3, 4, 5, 8, 9, 31, 32, 33, 65, 200]
+    w = synth.make_workload("scalar", B=len(lens), H=H, d_head=16, d_c=d_c, d_rope=d_rope, seq_lens=lens, io_dtype=io,
+                            cache_dtype=cache, page_size=page, free_frac=0.1, seed=81)
+    check_decode(mla, w, splits, flags=PORTABLE)
+
+
+def test_scalar_decode_many_chunks_take_four_heads_per_workgroup(mla):
+    w = synth.make_workload("scalar", B=40, H=30, d_head=16, d_c=128, d_rope=64, seq_lens=[37 * i for i in range(40)],
+                            io_dtype="f32", cache_dtype="f32", page_size=64, seed=82)
+    check_decode(mla, w, 8, flags=PORTABLE)
+
+
+@pytest.mark.parametrize("B,H,K,N", [(1, 32, 512, 128), (1, 2, 1, 4), (2, 3, 33, 36), (4, 40, 513, 64), (5, 2, 1030, 72),
+                                     (17, 3, 100, 260), (3, 2, 64, 130), (70, 9, 128, 512)])
+def test_fp32_projection_shapes(mla, B, H, K, N):
+    """1, 4 and 16 batch rows per workgroup, k remainders, columns that do not fill a tile, N % 4 != 0 (the
+    kernel of single columns), and W off its 16 bytes (the same kernel): fp32 sums of K products."""
+    import torch
+    r = synth.stream(83, B * 1000 + N)
+    x = torch.from_numpy(synth.normal(r, (B, H, K))).cuda()
+    buf = torch.from_numpy(synth.normal(r, (H * K * N + 1,), K ** -0.5)).cuda()
+    for w in (buf[:-1].clone().view(H, K, N), buf[1:].view(H, K, N)):
+        got = mla.absorb_q(x, w)
+        ref = torch.bmm(x.double().transpose(0, 1), w.double()).transpose(0, 1)
+        assert max_abs_rel(widen_gpu(got), ref.cpu().numpy()) <= 1e-5
