@@ -273,11 +273,11 @@ int mla_merge_partials(const void* workspace, size_t workspace_bytes,
 
 /*
  * Fused tail: mla_merge_partials followed by mla_out_proj in one call (one
- * kernel where the shapes allow: bf16 io, d_head 128, d_c 256 or 512, at most
- * 64 chunks of the uniform partition or any balanced one; otherwise the two
- * kernels back to back).  Same results as the two
- * calls: o_lat is the merged latent output rounded to the io dtype, and out is
- * computed from that rounded o_lat.
+ * kernel where the shapes allow: bf16 io, d_head 128, d_c 256 or 512, any
+ * balanced partition, at most 64 chunks of the uniform one or at most 256 with
+ * B * H <= 256; otherwise the two kernels back to back).  Same results as the
+ * two calls: o_lat is the merged latent output rounded to the io dtype, and out
+ * is computed from that rounded o_lat.
  *   workspace  [in]  as written by mla_decode_paged(..., MLA_FLAG_SKIP_MERGE)
  *   W_UV       [H, d_c, d_head] io dtype
  *   o_lat      [B, H, d_c] io dtype (output, required)

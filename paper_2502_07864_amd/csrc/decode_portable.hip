@@ -78,10 +78,10 @@ __device__ __forceinline__ float fold16(float a, float b)
 // sum over 16 lanes, on all of them (rotations inside the row of 16)
 __device__ __forceinline__ float sum16(float v)
 {
-    v += __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(v), 0x128, 0xf, 0xf, false));   // row_ror:8
-    v += __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(v), 0x124, 0xf, 0xf, false));
-    v += __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(v), 0x122, 0xf, 0xf, false));
-    return v + __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(v), 0x121, 0xf, 0xf, false));
+    v += dpp_move<0x128>(v);   // row_ror:8, 4, 2, 1
+    v += dpp_move<0x124>(v);
+    v += dpp_move<0x122>(v);
+    return v + dpp_move<0x121>(v);
 }
 
 __device__ __forceinline__ float dot4(float4 a, float4 b, float s)
@@ -420,7 +420,7 @@ __global__ __launch_bounds__(128) void merge_kernel(MergeParams p)
 
 // Streaming variant for d_c a multiple of 256: one wavefront per (sequence, head, block of 256
 // columns).  Lane s owns the log-sum-exp of chunk s; every lane streams one float4 per chunk with
-// the loads of up to 16 chunks in flight.  PLAN = false: uniform partition, at most 64 chunks.
+// the loads of up to 16 chunks in flight.  PLAN = false: uniform partition.
 // PLAN = true: the chunks the balanced partition's plan names for the sequence, any number of
 // them, 64 at a time.
 template <bool OUT_BF16, bool PLAN>
@@ -451,23 +451,26 @@ __global__ __launch_bounds__(256) void merge_wave_kernel(MergeParams p)
 #pragma unroll
     for (int i = 0; i < BATCH; ++i) v[i] = load_part4<OUT_BF16>(p.o_part, row(i));
 
-    const ChunkWeights cw = PLAN ? span_weights(p.lse_part, c, ls0, lane) : chunk_weights(ls0, S);
+    const ChunkWeights cw = span_weights(p.lse_part, c, ls0, lane);
 
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
     for (int blk = 0; blk < S; blk += 64) {
-        const float ls = blk ? span_lse(p.lse_part, c, blk, lane) : ls0;
+        const float wt = chunk_weight(cw, blk ? span_lse(p.lse_part, c, blk, lane) : ls0);
         for (int s0 = 0; s0 < min(64, S - blk); s0 += BATCH) {
             if (blk + s0 > 0) {
 #pragma unroll
                 for (int i = 0; i < BATCH; ++i) v[i] = load_part4<OUT_BF16>(p.o_part, row(blk + s0 + i));
             }
+            // sums of 16 chunks, added in order (the fused merge + projection forms the same ones)
+            float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
             for (int i = 0; i < BATCH; ++i) {
-                const float ws = chunk_weight_at(cw, ls, s0 + i);   // 0 at and past S
+                const float ws = lane_value(wt, s0 + i);   // 0 at and past S
                 const bool live = ws != 0.f;
-                acc.x = fmaf(ws, live ? v[i].x : 0.f, acc.x); acc.y = fmaf(ws, live ? v[i].y : 0.f, acc.y);
-                acc.z = fmaf(ws, live ? v[i].z : 0.f, acc.z); acc.w = fmaf(ws, live ? v[i].w : 0.f, acc.w);
+                a.x = fmaf(ws, live ? v[i].x : 0.f, a.x); a.y = fmaf(ws, live ? v[i].y : 0.f, a.y);
+                a.z = fmaf(ws, live ? v[i].z : 0.f, a.z); a.w = fmaf(ws, live ? v[i].w : 0.f, a.w);
             }
+            acc.x += a.x; acc.y += a.y; acc.z += a.z; acc.w += a.w;
         }
     }
     const size_t o = (size_t)bh * p.d_c + cb * 256 + lane * 4;
@@ -536,7 +539,7 @@ hipError_t launch_decode_portable(const DecodeParams& p, mla_dtype io, mla_dtype
 
 hipError_t launch_merge(const MergeParams& p, mla_dtype io, hipStream_t s)
 {
-    if (p.d_c % 256 == 0 && (p.plan || p.num_splits <= 64)) {
+    if (p.d_c % 256 == 0 && (p.plan || p.num_splits <= 256)) {
         const int waves = p.B * p.H * (p.d_c / 256);
         dim3 grid((waves + 3) / 4), block(256);
         if (io == MLA_BF16) {

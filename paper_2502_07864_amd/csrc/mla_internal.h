@@ -63,38 +63,79 @@ __device__ __forceinline__ float lane_value(float v, int lane)
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
 }
 
+// Sum and maximum over the wavefront, on every lane: rotations inside each row of 16 lanes, then the
+// exchange of neighbouring rows and of the two halves (no trip through LDS).
+template <int CTRL> __device__ __forceinline__ float dpp_move(float v)
+{
+    return __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(v), CTRL, 0xf, 0xf, false));
+}
+// sum of the four rows of 16 lanes, on every row
+__device__ __forceinline__ float sum_rows(float v)
+{
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    const auto q = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return __uint_as_float(q[0]) + __uint_as_float(q[1]);
+}
+__device__ __forceinline__ float wave_sum(float v)
+{
+    v += dpp_move<0x128>(v);   // row_ror:8, 4, 2, 1
+    v += dpp_move<0x124>(v);
+    v += dpp_move<0x122>(v);
+    v += dpp_move<0x121>(v);
+    return sum_rows(v);
+}
+__device__ __forceinline__ float wave_max(float v)
+{
+    v = fmaxf(v, dpp_move<0x128>(v));
+    v = fmaxf(v, dpp_move<0x124>(v));
+    v = fmaxf(v, dpp_move<0x122>(v));
+    v = fmaxf(v, dpp_move<0x121>(v));
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+    const auto q = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return fmaxf(__uint_as_float(q[0]), __uint_as_float(q[1]));
+}
+
 // Split-KV merge weights of one output row.  Lane s of the wave holds the log-sum-exp of
-// chunk s (-inf for s >= S and for empty chunks).  Every lane computes the same reference
-// (the maximum) and normaliser by reading the S values lane by lane, 16 at a time with
-// compile-time offsets and in index order: no chain of cross-lane shuffles, and a result that
-// does not depend on which wave computes it.  lse = m + log z (z = 0: every chunk empty).
+// chunk s (-inf for s >= S and for empty chunks) and its exponential; reference (the maximum) and
+// normaliser by wave_max / wave_sum, a fixed order that does not depend on which wave computes it.  (Reading
+// the S values lane by lane took 64 dependent steps per pass at 64 chunks, about 1.1 us of the merge
+// kernels.)  lse = m + log z (z = 0: every chunk empty).
 struct ChunkWeights {
     float m, z;      // maximum and sum_s e^{lse_s - m}
     float ref, inv;  // m (0 if every chunk is empty) and 1/z (0 if z = 0)
 };
 
-__device__ __forceinline__ ChunkWeights chunk_weights(float ls, int S)
+__device__ __forceinline__ ChunkWeights chunk_weights(float ls)
 {
     ChunkWeights cw;
-    cw.m = -INFINITY;
-    for (int s0 = 0; s0 < S; s0 += 16) {
-#pragma unroll
-        for (int i = 0; i < 16; ++i) cw.m = fmaxf(cw.m, lane_value(ls, s0 + i));
-    }
+    cw.m = wave_max(ls);
     cw.ref = cw.m == -INFINITY ? 0.f : cw.m;
-    cw.z = 0.f;
-    for (int s0 = 0; s0 < S; s0 += 16) {
-#pragma unroll
-        for (int i = 0; i < 16; ++i) cw.z += __expf(lane_value(ls, s0 + i) - cw.ref);   // e^{-inf} = 0
-    }
+    cw.z = wave_sum(__expf(ls - cw.ref));   // e^{-inf} = 0
     cw.inv = cw.z > 0.f ? 1.f / cw.z : 0.f;
     return cw;
 }
 
-// weight e^{lse_s - lse} of chunk s (s < 64; 0 for s >= S and for empty chunks), on every lane
-__device__ __forceinline__ float chunk_weight_at(const ChunkWeights& cw, float ls, int s)
+// the same for up to 64 N chunks (lane l holds those of chunks l, 64 + l, ..): blocks of 64 added in order
+template <int N> __device__ __forceinline__ ChunkWeights chunk_weights(const float (&ls)[N])
 {
-    return __expf(lane_value(ls, s) - cw.ref) * cw.inv;
+    ChunkWeights cw;
+    cw.m = wave_max(ls[0]);
+#pragma unroll
+    for (int k = 1; k < N; ++k) cw.m = fmaxf(cw.m, wave_max(ls[k]));
+    cw.ref = cw.m == -INFINITY ? 0.f : cw.m;
+    cw.z = wave_sum(__expf(ls[0] - cw.ref));
+#pragma unroll
+    for (int k = 1; k < N; ++k) cw.z += wave_sum(__expf(ls[k] - cw.ref));
+    cw.inv = cw.z > 0.f ? 1.f / cw.z : 0.f;
+    return cw;
+}
+
+// weight e^{lse_s - lse} of this lane's chunk (0 for s >= S and for empty chunks): chunk s's is lane s's
+__device__ __forceinline__ float chunk_weight(const ChunkWeights& cw, float ls)
+{
+    return __expf(ls - cw.ref) * cw.inv;
 }
 
 // Where the S partials of one (sequence, query row) lie: chunk s has its log-sum-exp at
@@ -127,23 +168,11 @@ __device__ __forceinline__ float span_lse(const float* lse_part, const ChunkSpan
 __device__ __forceinline__ ChunkWeights span_weights(const float* lse_part, const ChunkSpan& c, float ls0, int lane)
 {
     ChunkWeights cw;
-    cw.m = -INFINITY;
-    for (int blk = 0; blk < c.S; blk += 64) {
-        const float ls = blk ? span_lse(lse_part, c, blk, lane) : ls0;
-        for (int s0 = 0; s0 < min(64, c.S - blk); s0 += 16) {
-#pragma unroll
-            for (int i = 0; i < 16; ++i) cw.m = fmaxf(cw.m, lane_value(ls, s0 + i));
-        }
-    }
+    cw.m = wave_max(ls0);
+    for (int blk = 64; blk < c.S; blk += 64) cw.m = fmaxf(cw.m, wave_max(span_lse(lse_part, c, blk, lane)));
     cw.ref = cw.m == -INFINITY ? 0.f : cw.m;
-    cw.z = 0.f;
-    for (int blk = 0; blk < c.S; blk += 64) {
-        const float ls = blk ? span_lse(lse_part, c, blk, lane) : ls0;
-        for (int s0 = 0; s0 < min(64, c.S - blk); s0 += 16) {
-#pragma unroll
-            for (int i = 0; i < 16; ++i) cw.z += __expf(lane_value(ls, s0 + i) - cw.ref);
-        }
-    }
+    cw.z = wave_sum(__expf(ls0 - cw.ref));
+    for (int blk = 64; blk < c.S; blk += 64) cw.z += wave_sum(__expf(span_lse(lse_part, c, blk, lane) - cw.ref));
     cw.inv = cw.z > 0.f ? 1.f / cw.z : 0.f;
     return cw;
 }

@@ -119,3 +119,29 @@ def test_fp32_projection_shapes(mla, B, H, K, N):
         got = mla.absorb_q(x, w)
         ref = torch.bmm(x.double().transpose(0, 1), w.double()).transpose(0, 1)
         assert max_abs_rel(widen_gpu(got), ref.cpu().numpy()) <= 1e-5
+
+
+# ------------------------------------------------------------------ merge + projection of few batch rows
+
+@pytest.mark.parametrize("B,H,d_c,S", [(1, 32, 512, 16), (1, 32, 256, 3), (1, 5, 512, 1), (2, 32, 512, 16), (4, 32, 512, 32),
+                                       (2, 64, 256, 5), (7, 28, 512, 9), (1, 16, 512, 17), (4, 33, 256, 4),
+                                       (1, 32, 512, 32), (2, 32, 256, 33), (2, 28, 512, 100), (1, 256, 256, 64), (5, 64, 512, 70)])
+def test_fused_tail_few_batch_rows(mla, B, H, d_c, S):
+    """Output columns cut 2, 4 and 8 ways (and not at all), 4 to 256 chunks (one call of 70 chunks and more
+    rows than one workgroup per CU: two kernels): o_lat and lse bit for
+    bit those of the stand-alone merge, out within one bf16 rounding of the stored o_lat's projection."""
+    import torch
+    lens = [(64 * 37 * (i + 1)) % 2500 + i for i in range(B)]
+    lens[-1] = 0 if B > 1 else 900
+    w = synth.make_workload("few", B=B, H=H, d_head=128, d_c=d_c, d_rope=64, seq_lens=lens, io_dtype="bf16",
+                            cache_dtype="bf16", free_frac=0.1, seed=90 + B)
+    d = DeviceWorkload(w)
+    q = gpu_q_abs(mla, d)
+    ws = mla.decode_paged(q, d.q_rope, d.pool, d.page_table, d.seq_lens, w.softmax_scale, num_splits=S, flags=mla.FLAG_SKIP_MERGE)
+    o1, l1 = mla.merge_partials(ws, B, H, d_c, S, q.dtype, return_lse=True)
+    o2, out, l2 = mla.merge_out_proj(ws, d.W_UV, B, S, return_lse=True)
+    torch.cuda.synchronize()
+    assert o1.view(torch.int16).equal(o2.view(torch.int16)) and l1.view(torch.int32).equal(l2.view(torch.int32))
+    ref = oracle.out_proj(q_abs_storage(o2), w.W_UV)
+    # fp32 sums of d_c products, one rounding to bf16 (2^-9 of the value)
+    assert max_abs_rel(widen_gpu(out), ref) <= 2.0 ** -8
