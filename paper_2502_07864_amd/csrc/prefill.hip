@@ -2,8 +2,9 @@
 // are materialised per head from the cached latent rows,
 //     k_{j,h} = [W^{UK}_h c_j ; k^R_j],        v_{j,h} = W^{UV}_h c_j,
 // and the prompt's tokens attend causally to them.  This file holds the two kernels that build
-// the materialised rows; the attention itself runs on the 64-row matrix-core kernel, for which one
-// (sequence, head) pair is a sequence of its own whose cached rows are [k (128 + 64) | v (128)].
+// the materialised keys and values; the attention itself runs on prefill_attention.hip's kernel, for which
+// one (sequence, head) pair is a sequence of its own, and whose page layout (64 keys of 192 values, then
+// the values transposed, both in the order its reads want) is described there.
 //
 //   prefill_weights_kernel      Wcat[h] = [W^{UK}_h ; W^{UV}_h] as 256 rows of d_c values each (the
 //                               value projection is stored k-major by the caller and is transposed
@@ -13,16 +14,19 @@
 //                               on v_mfma_f32_16x16x32_bf16; a wavefront owns 32 tokens, keeps
 //                               their latent rows in registers as the B operand and walks the 16
 //                               row tiles of Wcat[h], which all four wavefronts read from LDS;
-//                               rows are rounded to bf16 and stored as
-//                               [k_nope | k_rope (copied from the cache) | v].
+//                               results are rounded to bf16 and stored 16 bytes per lane (the page
+//                               layout leaves a lane eight neighbouring values of a key, or of a
+//                               value dimension: the latter a contiguous kilobyte per wavefront).
 #include "mla_internal.h"
 #include "mfma_tile.h"
+#include <type_traits>
 
 namespace mla {
 namespace {
 
-constexpr int PF_ROW = 320;     // values per materialised row: 128 + 64 | 128
 constexpr int PF_DH = 128;      // head dimension
+constexpr int PF_KEY = 192;     // values per key: 128 + 64
+constexpr int PF_PAGE = 64 * (PF_KEY + PF_DH);    // values per materialised page: 64 keys, then the values transposed
 
 __global__ __launch_bounds__(256) void prefill_weights_kernel(const uint16_t* W_UK, const uint16_t* W_UV,
                                                               uint16_t* Wcat, int d_c)
@@ -68,28 +72,34 @@ __global__ __launch_bounds__(256, 2) void prefill_materialise_kernel(const uint1
     const bool in_seq = pg < max_pages && pg * 64 < L;
     const int page = in_seq ? page_table[(size_t)b * max_pages + pg] : -1;
     const bool active = in_seq && page >= 0 && page < num_pages;
-    // the pseudo-sequence (b, h) owns pages [bh * max_pages, +max_pages) of the materialised pool;
-    // a page id outside the cache pool is passed on as "skip these tokens"
+    // the pseudo-sequence (b, h) owns pages [bh * max_pages, +max_pages) of the materialised pool; a page id
+    // outside the cache pool is passed on as "skip these tokens" (-1), and its page, like the tokens past the
+    // sequence's end, gets zeros for values: what the skipped weights (zeros) are multiplied with
     const size_t page2 = (size_t)bh * max_pages + pg;
     if (in_seq && (wave & 1) == 0 && lane == 0) table2[page2] = active ? (int32_t)page2 : -1;
     const uint16_t* src = kv + (size_t)(active ? page : 0) * 64 * ROW;
-    uint16_t* dst = pool2 + (active ? page2 : 0) * 64 * PF_ROW;
+    uint16_t* dst = pool2 + (in_seq ? page2 : 0) * PF_PAGE;
     const int tok0 = (wave & 1) * 32;                 // this wavefront's first token inside its page
 
     bf16x8 cb[2][NKS];
-    if (active) {
+    if (in_seq) {
         // decoupled-rope part of the key: copied as it is (32 tokens x 8 pieces per wavefront)
         for (int i = lane; i < 32 * 8; i += 64) {
             const int tok = tok0 + (i >> 3), ch = i & 7;
-            *reinterpret_cast<u32x4*>(dst + tok * PF_ROW + PF_DH + ch * 8) =
+            *reinterpret_cast<u32x4*>(dst + tok * PF_KEY + PF_DH + ch * 8) =
                 *reinterpret_cast<const u32x4*>(src + tok * ROW + D_C + ch * 8);
         }
         // B operands: latent rows of tokens tok0 + 16 nt + n, k = 32 ks + 8g .. + 7
 #pragma unroll
-        for (int nt = 0; nt < 2; ++nt)
+        for (int nt = 0; nt < 2; ++nt) {
+            const bool there = active && pg * 64 + tok0 + nt * 16 + n < L;
 #pragma unroll
-            for (int ks = 0; ks < NKS; ++ks)
-                cb[nt][ks] = *reinterpret_cast<const bf16x8*>(src + (tok0 + nt * 16 + n) * ROW + ks * 32 + g * 8);
+            for (int ks = 0; ks < NKS; ++ks) {
+                u32x4 v = *reinterpret_cast<const u32x4*>(src + (tok0 + nt * 16 + n) * ROW + ks * 32 + g * 8);
+                if (!there) v = (u32x4){0u, 0u, 0u, 0u};
+                cb[nt][ks] = __builtin_bit_cast(bf16x8, v);
+            }
+        }
     }
 
     const unsigned char* W = reinterpret_cast<const unsigned char*>(Wcat + (size_t)h * 256 * D_C);
@@ -114,29 +124,42 @@ __global__ __launch_bounds__(256, 2) void prefill_materialise_kernel(const uint1
     __syncthreads();
     for (int c = 0; c < NCHUNK; ++c) {
         if (c + 1 < NCHUNK) load_chunk(c + 1);        // in flight while this chunk is used
-        if (active) {
+        if (in_seq) {
             f32x4 acc[2][2];
 #pragma unroll
             for (int ml = 0; ml < 2; ++ml)
 #pragma unroll
                 for (int nt = 0; nt < 2; ++nt) acc[ml][nt] = (f32x4){0.f, 0.f, 0.f, 0.f};
+            // keys: weights as the A operand (a lane ends with four dimensions of a token); values: tokens as the
+            // A operand (four tokens of a dimension)
+            auto product = [&](auto keys) {
 #pragma unroll
-            for (int ks = 0; ks < NKS; ++ks)
+                for (int ks = 0; ks < NKS; ++ks)
 #pragma unroll
-                for (int ml = 0; ml < 2; ++ml) {
-                    const bf16x8 a = *reinterpret_cast<const bf16x8*>(&wbuf[c & 1][(ml * 16 + n) * WROWB + ks * 64 + g * 16]);
-                    acc[ml][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, cb[0][ks], acc[ml][0], 0, 0, 0);
-                    acc[ml][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, cb[1][ks], acc[ml][1], 0, 0, 0);
-                }
-            // D: rows 4g .. 4g+3 of row tile mt = 2c + ml (output dimensions), column n (token)
+                    for (int ml = 0; ml < 2; ++ml) {
+                        const bf16x8 a = *reinterpret_cast<const bf16x8*>(&wbuf[c & 1][(ml * 16 + n) * WROWB + ks * 64 + g * 16]);
 #pragma unroll
-            for (int ml = 0; ml < 2; ++ml) {
-                const int mt = c * 2 + ml;
-                const int col = mt < 8 ? mt * 16 + g * 4 : PF_DH + 64 + (mt - 8) * 16 + g * 4;
+                        for (int nt = 0; nt < 2; ++nt)
+                            acc[ml][nt] = decltype(keys)::value ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, cb[nt][ks], acc[ml][nt], 0, 0, 0)
+                                                                : __builtin_amdgcn_mfma_f32_16x16x32_bf16(cb[nt][ks], a, acc[ml][nt], 0, 0, 0);
+                    }
+            };
+            auto pack8 = [&](const f32x4& lo, const f32x4& up) {
+                return (u32x4){pack_bf16x2(lo[0], lo[1]), pack_bf16x2(lo[2], lo[3]), pack_bf16x2(up[0], up[1]), pack_bf16x2(up[2], up[3])};
+            };
+            if (c < NCHUNK / 2) {
+                product(std::true_type{});
+                // 32 dimensions of 32 tokens: position 8g + 4 ml + i of the 32 is dimension 16 ml + 4g + i
 #pragma unroll
                 for (int nt = 0; nt < 2; ++nt)
-                    *reinterpret_cast<u32x2*>(dst + (tok0 + nt * 16 + n) * PF_ROW + col) =
-                        (u32x2){pack_bf16x2(acc[ml][nt][0], acc[ml][nt][1]), pack_bf16x2(acc[ml][nt][2], acc[ml][nt][3])};
+                    *reinterpret_cast<u32x4*>(dst + (tok0 + nt * 16 + n) * PF_KEY + c * 32 + g * 8) = pack8(acc[0][nt], acc[1][nt]);
+            } else {
+                product(std::false_type{});
+                // 32 tokens (this wavefront's half page) of 32 dimensions: key 4 nt + i of group g is token 16 nt + 4g + i
+                uint16_t* half = dst + 64 * PF_KEY + tok0 * PF_DH;
+#pragma unroll
+                for (int ml = 0; ml < 2; ++ml)
+                    *reinterpret_cast<u32x4*>(half + ((c - NCHUNK / 2) * 2 + ml) * 512 + lane * 8) = pack8(acc[ml][0], acc[ml][1]);
             }
         }
         if (c + 1 < NCHUNK) store_chunk((c + 1) & 1); // the other buffer: last read before the previous barrier

@@ -1,46 +1,57 @@
 // Causal attention of the MHA-paradigm prefill (Sec. 3.3, first of the two attention equations) over
-// the keys and values materialised per (sequence, head) by prefill.hip: rows of 320 bf16 values,
-// [k = W^{UK}_h c_j ; k^R_j (128 + 64) | v = W^{UV}_h c_j (128)], in pages of 64 rows, one pseudo-
-// sequence per (sequence, head).  Query token i of T sees the rows 0 .. L - T + i.
+// the keys and values materialised per (sequence, head) by prefill.hip, one pseudo-sequence per
+// (sequence, head).  Query token i of T sees the keys 0 .. L - T + i.
 //
 //     S^T [keys x queries]  = K [keys x 192] . Q^T [192 x queries]
 //     O^T [128 x queries]  += V^T [128 x keys] . P^T [keys x queries]
 //
+// A page of 64 keys is 40 KB: the keys [k = W^{UK}_h c_j ; k^R_j] as 64 rows of 192 bf16 values, then the
+// values TRANSPOSED, [half page][16-dimension tile][4 groups of 8 keys][16 dimensions][8 keys].  Both orders are made for the reads of this
+// kernel (the kernel that writes them has the choice for free): inside each 32 of the first 128 key
+// dimensions position 8g + 4m + i holds dimension 16m + 4g + i (the queries are loaded alike), and
+// key j of group g of a half page is its key 4g + j (j < 4) or 16 + 4g + j - 4, which is how the
+// exponentiated scores of two 16-key blocks lie in the registers after the first contraction.  So the
+// weights are, as they stand, the B operand of the second contraction, and its A operand is one plain
+// 128-bit LDS read per 16 dimensions, 16 bytes per lane in lane order: no bank conflict (row-major values
+// took two transposing 64-bit reads; [dimension][32 keys] puts the 16 lanes of a cycle on 8 of 16 units).
+//
 // Workgroup = 128 query rows of one (sequence, head) x all the keys they see; 4 wavefronts, each
 // with 32 query rows of its own (two groups of 16) and a private running softmax, so the only
-// workgroup barrier per tile is the one that publishes the tile (32 keys, direct-to-LDS loads,
-// ring of NBUF tiles).  Per tile a wavefront reads the whole tile from LDS once as the A operand
-// of the score contraction (two blocks of 16 keys) and once transposed for the value contraction;
-// every read feeds two MFMAs (the two query groups).  As in the decode kernels the transposed
-// formulation puts queries on the D columns: a lane owns one query per group, the exponentiated
-// scores of key blocks 0 and 1 are, as they stand, the B operand of v_mfma_f32_16x16x32_bf16
-// (k slot 8g + j = key 4g + j for j < 4, key 16 + 4g + j - 4 otherwise), and two transposing LDS
-// reads give the matching V^T.  No rescaling in the loop: the reference of a query is the maximum of
-// its first tile; a later score more than 2^64 above it is recorded and the workgroup then redoes
-// its keys with the exact maxima (one sweep that only scores, one that accumulates).
+// workgroup barrier per tile is the one that publishes a unit (32 keys and the values of the 32 before,
+// direct-to-LDS loads, ring of NBUF).  Every LDS read feeds two MFMAs (the two query groups).  The normaliser is a
+// product too: one MFMA with an A operand of ones per tile and group sums the rounded weights.  No
+// rescaling in the loop: the reference of a query is the maximum of its first tile; a later score more
+// than 2^64 above it is recorded and the workgroup then redoes its keys with the exact maxima (one sweep
+// that only scores, one that accumulates).
+//
+// What bounds it: the matrix pipes and the chip's power.  4 prompts of 8192 tokens, 32 heads (2.75 TFLOP): the form
+// before this one, which scored, weighed and accumulated one tile after the other from row-major values, took
+// 6.7 M cycles at 2.1 GHz with the matrix pipes busy 42 % of them; this one takes 5.0 M with 57 %, and the clock
+// falls to 1.8 GHz under the denser work: whole call 3036 -> 2794 us (a library product of 8192^3 reaches
+// 1.29 PFLOP/s on the same card; this kernel about 1.15).  8 x 500 new tokens on 700 .. 6000, 28 heads: 552 -> 423.
 #include "mla_internal.h"
 #include "mfma_tile.h"
+#include <type_traits>
 
 namespace mla {
 namespace {
 
-constexpr int PA_ROW = 320;                 // values per materialised row
-constexpr int PA_DK = 192;                  // key part
-constexpr int PA_DV = 128;                  // value part
+constexpr int PA_DK = 192;                  // values per key
+constexpr int PA_DV = 128;                  // dimensions of a value
 constexpr int PA_ROWS = 128;                // query rows per workgroup
 
 template <int NBUF, int WPE>
 __global__ __launch_bounds__(MF_THREADS, WPE) void prefill_attention_kernel(DecodeParams p)
 {
-    constexpr int ROWB = PA_ROW * 2;            // 640 bytes per row: 32 banks mod 64, as the decode tiles
-    constexpr int CPR = ROWB / 16;              // 40 chunks of 16 bytes
-    constexpr int PAGE_B = 64 * ROWB;
-    constexpr int TILE_B = TILE_ROWS * ROWB;    // 20480
-    constexpr int NLOAD = TILE_B / (MF_THREADS * 16);   // 5
+    constexpr int ROWB = PA_DK * 2;             // 384 bytes per key: 32 banks mod 64, as the decode tiles
+    constexpr int CPR = ROWB / 16;              // 24 chunks of 16 bytes
+    constexpr int K_B = TILE_ROWS * ROWB;       // 12288: a tile's keys
+    constexpr int V_B = TILE_ROWS * PA_DV * 2;  // 8192: its values
+    constexpr int TILE_B = K_B + V_B;
+    constexpr int PAGE_B = 2 * TILE_B;
+    constexpr int NLK = K_B / (MF_THREADS * 16), NLV = V_B / (MF_THREADS * 16);   // loads per thread: 3 and 2
     constexpr int NKS = PA_DK / 32;             // 6 k-steps of the score contraction
-    constexpr int NCT = PA_DV / 16;             // 8 column tiles of the value contraction
-    constexpr int VGR = 2;                      // column tiles per read-ahead group (value)
-    static_assert(NBUF >= 2 && NBUF <= 4 && (NBUF + 1) * NLOAD < 64, "ring depth; vmcnt is a 6-bit counter");
+    constexpr int NCT = PA_DV / 16;             // 8 row tiles of the value contraction
 
     __shared__ __attribute__((aligned(1024))) unsigned char smem[NBUF * TILE_B];
     LDS_AS unsigned char* lds = (LDS_AS unsigned char*)smem;
@@ -51,12 +62,27 @@ __global__ __launch_bounds__(MF_THREADS, WPE) void prefill_attention_kernel(Deco
 
     // Workgroup -> (pseudo-sequence, group of 128 query rows).  The groups of one sequence get
     // linear ids 8 apart (ids are dealt round-robin to the 8 XCDs: they run on one XCD and share the
-    // sequence's rows in its L2), the groups with the most keys first.
+    // sequence's rows in its L2), the groups with the most keys first, and the longest sequences first
+    // (up to 64 of them: every workgroup ranks the lengths by itself): a long one started last would run
+    // on alone at the end.  8 x 500 new tokens on contexts of 700 .. 6000 rows, 28 heads (the form before this one):
+    // 389 us in the order of the batch, 346 longest first.
     const int Z = (p.H + PA_ROWS - 1) / PA_ROWS;
     const int id = blockIdx.x, rr = id >> 3;
     const int zi = Z - 1 - rr % Z;
-    const int b = (rr / Z) * 8 + (id & 7);
+    int b = (rr / Z) * 8 + (id & 7);
     if (b >= p.B) return;                       // padding of the last group of 8
+    const int nseq = p.B / p.q_inner;
+    if (nseq > 1 && nseq <= 64) {
+        const int mine = lane < nseq ? p.seq_lens[lane * p.q_inner] : -1;
+        int rank = 0;
+        for (int j = 0; j < nseq; ++j) {
+            const int other = __builtin_amdgcn_readlane(mine, j);
+            rank += other > mine || (other == mine && j < lane);
+        }
+        const unsigned long long hit = __ballot(lane < nseq && rank == b / p.q_inner);
+        b = (__builtin_ffsll((long long)hit) - 1) * p.q_inner + b % p.q_inner;
+    }
+    b = __builtin_amdgcn_readfirstlane(b);      // (uniform, and said so: what hangs on it stays in scalar registers)
     const int hb = zi * PA_ROWS;
     const int HL = min(PA_ROWS, p.H - hb);      // query rows of this workgroup
     // rows of q / out: sequence b stands for (b / q_inner, b % q_inner), its tokens q_inner rows apart
@@ -64,7 +90,7 @@ __global__ __launch_bounds__(MF_THREADS, WPE) void prefill_attention_kernel(Deco
     auto io_row = [&](int h) -> size_t { return io_base + (size_t)h * p.q_inner; };
 
     const CONST_AS int32_t* ptab = (const CONST_AS int32_t*)(p.page_table + (size_t)b * p.max_pages);
-    const int L = max(0, min(p.seq_lens[b], p.max_pages * 64));
+    const int L = __builtin_amdgcn_readfirstlane(max(0, min(p.seq_lens[b], p.max_pages * 64)));
 
     // ---- this wave's 32 query rows -> registers (B operands of the score contraction)
     bf16x8 qreg[2][NKS];
@@ -77,15 +103,26 @@ __global__ __launch_bounds__(MF_THREADS, WPE) void prefill_attention_kernel(Deco
             const size_t qrow = io_row(hb + min(row, HL - 1));
 #pragma unroll
             for (int ks = 0; ks < NKS; ++ks) {
-                const uint16_t* src = ks < 4 ? qa + qrow * 128 + ks * 32 + g * 8 : qr + qrow * 64 + (ks - 4) * 32 + g * 8;
-                const uint4 v = *reinterpret_cast<const uint4*>(src);
-                qreg[hi][ks] = __builtin_bit_cast(bf16x8, row < HL ? v : make_uint4(0u, 0u, 0u, 0u));
+                u32x4 v;
+                if (ks < 4) {                   // the key dimensions' order inside each 32
+                    const uint16_t* src = qa + qrow * 128 + ks * 32 + g * 4;
+                    const u32x2 lo = *reinterpret_cast<const u32x2*>(src), up = *reinterpret_cast<const u32x2*>(src + 16);
+                    v = (u32x4){lo[0], lo[1], up[0], up[1]};
+                } else {
+                    v = *reinterpret_cast<const u32x4*>(qr + qrow * 64 + (ks - 4) * 32 + g * 8);
+                }
+                // a negative scale changes the sign of the queries: the largest score is then the largest
+                // scaled one
+                const uint32_t flip = p.scale < 0.f ? 0x80008000u : 0u;
+                v ^= (u32x4){flip, flip, flip, flip};
+                qreg[hi][ks] = __builtin_bit_cast(bf16x8, row < HL ? v : (u32x4){0u, 0u, 0u, 0u});
             }
         }
     }
 
+    auto visible = [&](int h) { return L - (p.q_len - 1 - h); };   // keys that query row h sees (one head: rows are tokens)
     // keys [0, row1): what the last query row of the workgroup sees (the rows are ordered by token)
-    const int row1 = min(L, visible_rows(p, L, min(hb + PA_ROWS, p.H) - 1));
+    const int row1 = min(L, visible(min(hb + PA_ROWS, p.H) - 1));
     auto store_nothing = [&]() {                // zeros and -inf for the rows of this workgroup
         for (int i = tid; i < HL * (PA_DV / 4); i += MF_THREADS)
             *reinterpret_cast<u32x2*>(static_cast<uint16_t*>(p.o_final) + io_row(hb + i / (PA_DV / 4)) * PA_DV +
@@ -98,87 +135,74 @@ __global__ __launch_bounds__(MF_THREADS, WPE) void prefill_attention_kernel(Deco
     }
     const int t1 = (row1 + TILE_ROWS - 1) / TILE_ROWS;            // tiles [0, t1)
     // first key that some query row of this workgroup must not see (its first row sees the least)
-    const int causal_from = visible_rows(p, L, hb);
+    const int causal_from = visible(hb);
 
-    // ---- tile staging: direct-to-LDS 128-bit loads, chunk swizzle as in the decode kernels
+    // ---- staging: direct-to-LDS 128-bit loads.  What a step of the sweep needs is the values of tile t and
+    // the keys of tile t + 1 (its scores are made while tile t is accumulated): that is one unit, in ring slot
+    // (t + 1) % NBUF; unit -1 is the keys of the first tile.
     const uint32_t lds_base = (uint32_t)(uintptr_t)lds;
-    uint32_t goff[NLOAD];
+    uint32_t koff[NLK];
 #pragma unroll
-    for (int k = 0; k < NLOAD; ++k) {
+    for (int k = 0; k < NLK; ++k) {             // keys: chunk swizzle as in the decode kernels
         const int P = (k * 4 + wave) * 64 + lane;
         const int r = P / CPR, pc = P % CPR;
-        goff[k] = (uint32_t)(r * ROWB + ((pc ^ swz_key(r)) << 4));
+        koff[k] = (uint32_t)(r * ROWB + ((pc ^ swz_key(r)) << 4));
     }
-    const unsigned char* kv = static_cast<const unsigned char*>(p.kv);
-    auto rows_valid = [&](int t) {
-        const int page = ptab[t >> 1];
-        return (page >= 0 && page < p.num_pages) ? min(TILE_ROWS, row1 - t * TILE_ROWS) : 0;
+    const uint32_t voff = (uint32_t)(lane * 16);    // values: as they lie
+    const unsigned char* pool = static_cast<const unsigned char*>(p.kv) + (size_t)b * p.max_pages * PAGE_B;
+    auto load16 = [&](const unsigned char* base, uint32_t off, uint32_t dst) {   // (base and dst are uniform)
+        const uint32_t m0v = __builtin_amdgcn_readfirstlane(dst);
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+                     :: "s"(m0v), "v"(off), "s"(base) : "memory");
     };
-    auto fetch_tile = [&](int t) -> int {       // number of loads this thread issued (0 or NLOAD; uniform)
-        if (rows_valid(t) <= 0) return 0;       // a page that was skipped is never dereferenced
-        const unsigned char* src = kv + (size_t)ptab[t >> 1] * PAGE_B + (size_t)(t & 1) * TILE_B;
-        const uint32_t dst = lds_base + (uint32_t)((t % NBUF) * TILE_B + wave * 1024);
+    auto slot_of = [&](int u) { return (uint32_t)(((u + 1) % NBUF) * TILE_B); };
+    // returns the number of loads this thread issued (uniform)
+    auto fetch_unit = [&](int u) -> int {
+        int n_issued = 0;
+        const uint32_t dst = lds_base + slot_of(u) + (uint32_t)(wave * 1024);
+        if (u + 1 < t1) {
+            const unsigned char* src = pool + (size_t)((u + 1) >> 1) * PAGE_B + ((u + 1) & 1) * K_B;
 #pragma unroll
-        for (int k = 0; k < NLOAD; ++k) {
-            const unsigned char* gp = src + goff[k];
-            const uint32_t m0v = __builtin_amdgcn_readfirstlane(dst + k * 4096);
-            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
-                         :: "s"(m0v), "v"(gp) : "memory");
+            for (int k = 0; k < NLK; ++k) load16(src, koff[k], dst + k * 4096);
+            n_issued = NLK;
         }
-        return NLOAD;
-    };
-    int ahead[NBUF - 1];        // loads issued for the tiles after the one being consumed, oldest first
-    bool ring_full = false;
-    auto start_ring = [&]() {
-        fetch_tile(0);
+        if (u >= 0 && u < t1) {
+            const unsigned char* src = pool + (size_t)(u >> 1) * PAGE_B + 2 * K_B + (u & 1) * V_B + wave * 1024;
 #pragma unroll
-        for (int i = 0; i < NBUF - 1; ++i) ahead[i] = 1 + i < t1 ? fetch_tile(1 + i) : 0;
-        ring_full = true;
+            for (int k = 0; k < NLV; ++k) load16(src + k * 4096, voff, dst + K_B + k * 4096);
+            n_issued += NLV;
+        }
+        return n_issued;
     };
-    auto stage_tile = [&](int t, LDS_AS unsigned char* tile) -> int {
-        const int n_valid = rows_valid(t);
-        int younger = 0;
-#pragma unroll
-        for (int i = 0; i < NBUF - 1; ++i) younger += ahead[i];
-        if (NBUF > 3 && younger >= 3 * NLOAD)      wait_vmcnt<3 * NLOAD>();
-        else if (NBUF > 2 && younger >= 2 * NLOAD) wait_vmcnt<2 * NLOAD>();
-        else if (younger >= NLOAD)                 wait_vmcnt<NLOAD>();
-        else                                       wait_vmcnt<0>();
-        // after the barrier everybody's loads of tile t have landed and every wave is done with
-        // tile t - 1, whose ring slot now receives tile t + NBUF - 1
+    int younger = 0;            // loads issued for the unit after the one the next step needs
+    // unit u is there, for everybody, and everybody is done with the step before: its slot receives unit u + 2
+    auto stage = [&](int u) {
+        if (younger >= NLK + NLV) wait_vmcnt<NLK + NLV>();
+        else if (younger >= NLK)  wait_vmcnt<NLK>();
+        else if (younger >= NLV)  wait_vmcnt<NLV>();
+        else                      wait_vmcnt<0>();
         __syncthreads();
-        if (!ring_full) {
-            const int tn = t + NBUF - 1;
-            ahead[NBUF - 2] = tn < t1 ? fetch_tile(tn) : 0;
-        }
-        ring_full = false;
-        if (n_valid < TILE_ROWS) {              // ragged last tile, or a skipped page: zeros, whatever the rows hold
-            for (int i = tid; i < (TILE_ROWS - n_valid) * CPR; i += MF_THREADS)
-                *(LDS_AS u32x4*)(tile + n_valid * ROWB + i * 16) = (u32x4){0u, 0u, 0u, 0u};
-            __syncthreads();
-        }
-#pragma unroll
-        for (int i = 0; i < NBUF - 2; ++i) ahead[i] = ahead[i + 1];
-        ahead[NBUF - 2] = 0;
-        return n_valid;
+        younger = fetch_unit(u + 2);
     };
+    static_assert(NBUF == 3 && NLK == 3 && NLV == 2, "a step's unit, the next one, and the one being requested");
+    auto start = [&]() {
+        fetch_unit(-1);
+        younger = fetch_unit(0);
+        stage(-1);
+    };
+    // keys of tile t that are there: a page the cache did not have is in place (its values are zeros) and no
+    // query sees it
+    auto rows_valid = [&](int t) { return ptab[t >> 1] >= 0 ? min(TILE_ROWS, row1 - t * TILE_ROWS) : 0; };
 
-    start_ring();
-    // pin the completion of the query loads here, outside the tile loop
-#pragma unroll
-    for (int hi = 0; hi < 2; ++hi)
-#pragma unroll
-        for (int ks = 0; ks < NKS; ++ks) asm volatile("" :: "v"(qreg[hi][ks]));
+    start();
 
     // ---- per-lane state: this lane's queries = column n of the D tiles of the two groups
     float m_ref[2] = {-INFINITY, -INFINITY};   // reference of the exponentials (log2 units)
-    float l_run[2] = {0.f, 0.f};               // this lane's share of the normaliser (its 8 keys per tile)
+    float top[2] = {-INFINITY, -INFINITY};     // largest score of the sweep so far, this lane's keys (unscaled)
+    f32x4 lacc[2];                             // normaliser (four times the same)
     f32x4 oacc[2][NCT];
-#pragma unroll
-    for (int hi = 0; hi < 2; ++hi)
-#pragma unroll
-        for (int ct = 0; ct < NCT; ++ct) oacc[hi][ct] = (f32x4){0.f, 0.f, 0.f, 0.f};
-    const float sc = p.scale * LOG2E;
+    // (never zero: a masked score is -inf and has to stay it)
+    const float sc = fmaxf(fabsf(p.scale) * LOG2E, 1.17549435e-38f);
     const int my_row = wave * 32 + n;           // + 16 hi; local to the workgroup
 
     // score A operand: key row 16 rb + n, chunk 4 ks + g
@@ -186,165 +210,178 @@ __global__ __launch_bounds__(MF_THREADS, WPE) void prefill_attention_kernel(Deco
     uint32_t a_base[2];
 #pragma unroll
     for (int e = 0; e < 2; ++e) a_base[e] = (uint32_t)(n * ROWB) + ((((uint32_t)(4 * e + g)) ^ a_key) << 4);
-    // value A operand (transposing reads): the lane supplies key row 4g + (n>>2) (and 16 more),
-    // 8 bytes at value column 16 ct + 4 (n&3)
-    const uint32_t v_key = (uint32_t)swz_key(g * 4 + (n >> 2));
-    uint32_t v_base[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e)
-        v_base[e] = (uint32_t)((g * 4 + (n >> 2)) * ROWB) + ((((uint32_t)(2 * e) + (uint32_t)((n & 3) >> 1)) ^ v_key) << 4) +
-                    (uint32_t)((n & 1) * 8) + (uint32_t)(PA_DK * 2);
+    // value A operand: dimension 16 ct + n, the eight keys of lane group g
+    const uint32_t v_base = (uint32_t)(K_B + lane * 16);
+    const bf16x8 ones = __builtin_bit_cast(bf16x8, (u32x4){0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u});
 
-    // S^T for the tile's 32 keys x this wave's 32 queries, log2 units, keys a query must not see
-    // (or that are not there) at -inf.  x[rb][hi][i] = key 16 rb + 4g + i, query 16 hi + n.
-    auto score_tile = [&](LDS_AS unsigned char* tile, int t, int n_valid, float (&x)[2][2][4]) {
-        f32x4 sacc[2][2];
-#pragma unroll
-        for (int rb = 0; rb < 2; ++rb)
-#pragma unroll
-            for (int hi = 0; hi < 2; ++hi) sacc[rb][hi] = (f32x4){0.f, 0.f, 0.f, 0.f};
-        bf16x8 a0[2][NKS];
-#pragma unroll
-        for (int ks = 0; ks < 2; ++ks)
-#pragma unroll
-            for (int rb = 0; rb < 2; ++rb)
-                a0[rb][ks] = *(LDS_AS bf16x8*)(tile + rb * 16 * ROWB + a_base[ks & 1] + (ks >> 1) * 128);
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int s0 = 0; s0 < NKS; s0 += 2) {
-#pragma unroll
-            for (int ks = s0 + 2; ks < s0 + 4 && ks < NKS; ++ks)
-#pragma unroll
-                for (int rb = 0; rb < 2; ++rb)
-                    a0[rb][ks] = *(LDS_AS bf16x8*)(tile + rb * 16 * ROWB + a_base[ks & 1] + (ks >> 1) * 128);
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int ks = s0; ks < s0 + 2 && ks < NKS; ++ks)
-#pragma unroll
-                for (int rb = 0; rb < 2; ++rb)
-#pragma unroll
-                    for (int hi = 0; hi < 2; ++hi)
-                        sacc[rb][hi] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0[rb][ks], qreg[hi][ks], sacc[rb][hi], 0, 0, 0);
-            __builtin_amdgcn_sched_barrier(0);
-        }
-#pragma unroll
-        for (int rb = 0; rb < 2; ++rb)
-#pragma unroll
-            for (int hi = 0; hi < 2; ++hi)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) x[rb][hi][i] = sacc[rb][hi][i] * sc;
-        if (n_valid < TILE_ROWS || (t + 1) * TILE_ROWS > causal_from) {
-            // ragged last tile, and the upper limit of each query (the sum runs up to its own position)
-#pragma unroll
-            for (int hi = 0; hi < 2; ++hi) {
-                const int seen = min(n_valid, visible_rows(p, L, hb + my_row + hi * 16) - t * TILE_ROWS);
-#pragma unroll
-                for (int rb = 0; rb < 2; ++rb)
-#pragma unroll
-                    for (int i = 0; i < 4; ++i)
-                        if (rb * 16 + g * 4 + i >= seen) x[rb][hi][i] = -INFINITY;
-            }
-        }
+    typedef f32x4 Scores[2][2];     // [block of 16 keys][query group]: keys 16 rb + 4g + i of query n, unscaled
+    auto max3 = [](float a, float b, float c) {
+        float r;                    // (a NaN loses, as in fmaxf; written out: fmaxf would quieten every operand first)
+        asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+        return r;
     };
-    auto lane_max = [&](const float (&x)[2][2][4], int hi) {
-        return fmaxf(fmaxf(fmaxf(x[0][hi][0], x[0][hi][1]), fmaxf(x[0][hi][2], x[0][hi][3])),
-                     fmaxf(fmaxf(x[1][hi][0], x[1][hi][1]), fmaxf(x[1][hi][2], x[1][hi][3])));
+    auto raise_top = [&](const Scores& x) {
+#pragma unroll
+        for (int hi = 0; hi < 2; ++hi)
+#pragma unroll
+            for (int rb = 0; rb < 2; ++rb) top[hi] = max3(max3(top[hi], x[rb][hi][0], x[rb][hi][1]), x[rb][hi][2], x[rb][hi][3]);
     };
     // maximum over the four lane groups (all 32 keys of the tile), on every lane
     auto over_groups = [&](float v) {
         v = fmaxf(v, __shfl_xor(v, 16));
         return fmaxf(v, __shfl_xor(v, 32));
     };
-
-    // weights against m_ref (rounded to bf16; the normaliser sums exactly the rounded weights), then
-    // O^T += V^T . P^T with the transposing reads one group of four column tiles ahead
-    auto accumulate_tile = [&](LDS_AS unsigned char* tile, const float (&x)[2][2][4]) {
-        bf16x8 pb[2];
+    // keys a query must not see (or that are not there) at -inf
+    auto mask = [&](Scores& x, int t) {
+        // (few tiles take this: what it compares with is worked out here and not kept in registers)
+        const int n_valid = rows_valid(t);
+        int first = 4 * g;
+        asm volatile("" : "+v"(first));
 #pragma unroll
         for (int hi = 0; hi < 2; ++hi) {
-            const float m_use = m_ref[hi] == -INFINITY ? 0.f : m_ref[hi];
-            uint32_t w[4];
+            const int seen = min(n_valid, visible(hb + my_row + hi * 16) - t * TILE_ROWS) - first;
 #pragma unroll
-            for (int rb = 0; rb < 2; ++rb) {
-                w[2 * rb]     = pack_bf16x2(fast_exp2(x[rb][hi][0] - m_use), fast_exp2(x[rb][hi][1] - m_use));
-                w[2 * rb + 1] = pack_bf16x2(fast_exp2(x[rb][hi][2] - m_use), fast_exp2(x[rb][hi][3] - m_use));
-            }
+            for (int rb = 0; rb < 2; ++rb)
 #pragma unroll
-            for (int j = 0; j < 4; ++j) l_run[hi] += bf16_bits_to_f32(w[j] & 0xFFFFu) + bf16_bits_to_f32(w[j] >> 16);
-            pb[hi] = __builtin_bit_cast(bf16x8, (u32x4){w[0], w[1], w[2], w[3]});
+                for (int i = 0; i < 4; ++i)
+                    if (rb * 16 + i >= seen) x[rb][hi][i] = -INFINITY;
         }
-        s16x4 lo[NCT], up[NCT];
+    };
+    auto full_tile = [&](int t) { return (t + 1) * TILE_ROWS <= causal_from && rows_valid(t) == TILE_ROWS; };
+
+    // ---- one step: S^T of the next tile (QK), the weights of this one from its scores x, the normaliser and the
+    // values (PV).  The weights (two exponentials, a conversion and two multiply-adds per pair of scores) are
+    // placed between the matrix instructions of the next tile's scores, which they do not depend on: both pipes
+    // of the SIMD work on one wavefront, where a step that scored, weighed and accumulated one tile in turn left
+    // each idle for the other's share (matrix pipes busy 42 %, vector pipes 45 %, LDS 20 % of the time).
+    // PV = false: the scores alone (the first tile's).
+    auto step = [&](auto pv_tag, LDS_AS unsigned char* unit, const Scores& x, Scores& y) {
+        constexpr bool PV = decltype(pv_tag)::value;
+        bf16x8 ka[2][NKS], va[NCT];
+        auto rk = [&](int ks) {
 #pragma unroll
-        for (int ct = 0; ct < VGR; ++ct) {
-            lo[ct] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_AS s16x4*)(tile + v_base[ct & 3] + (ct >> 2) * 128));
-            up[ct] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_AS s16x4*)(tile + v_base[ct & 3] + (ct >> 2) * 128 + 16 * ROWB));
+            for (int rb = 0; rb < 2; ++rb)
+                ka[rb][ks] = *(LDS_AS bf16x8*)(unit + rb * 16 * ROWB + a_base[ks & 1] + (ks >> 1) * 128);
+        };
+        auto rv = [&](int ct) { va[ct] = *(LDS_AS bf16x8*)(unit + v_base + ct * 1024); };
+        float m_use[2];
+        uint32_t w[2][4];
+        auto weigh = [&](int j) {               // pair j of 8: query group j / 4, scores 2 (j % 4) and the one after
+            const int hi = j >> 2, rb = (j >> 1) & 1, i = 2 * (j & 1);
+            w[hi][2 * rb + (j & 1)] = pack_bf16x2(fast_exp2(fmaf(x[rb][hi][i], sc, -m_use[hi])),
+                                                  fast_exp2(fmaf(x[rb][hi][i + 1], sc, -m_use[hi])));
+        };
+        if constexpr (PV) {
+#pragma unroll
+            for (int hi = 0; hi < 2; ++hi) m_use[hi] = m_ref[hi] == -INFINITY ? 0.f : m_ref[hi];
         }
+        rk(0);
+        rk(1);
         __builtin_amdgcn_sched_barrier(0);
+        {
 #pragma unroll
-        for (int c0 = 0; c0 < NCT; c0 += VGR) {
+            for (int ks = 0; ks < NKS; ++ks) {
+                if (ks + 2 < NKS) rk(ks + 2);
+                else if (PV) rv(ks + 2 - NKS);
 #pragma unroll
-            for (int ct = c0 + VGR; ct < c0 + 2 * VGR && ct < NCT; ++ct) {
-                lo[ct] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_AS s16x4*)(tile + v_base[ct & 3] + (ct >> 2) * 128));
-                up[ct] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_AS s16x4*)(tile + v_base[ct & 3] + (ct >> 2) * 128 + 16 * ROWB));
+                for (int rb = 0; rb < 2; ++rb)
+#pragma unroll
+                    for (int hi = 0; hi < 2; ++hi)
+                        y[rb][hi] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka[rb][ks], qreg[hi][ks],
+                                                                            ks == 0 ? (f32x4){0.f, 0.f, 0.f, 0.f} : y[rb][hi], 0, 0, 0);
+                if constexpr (PV) {
+                    if (ks == 0) { weigh(0); weigh(1); }
+                    else if (ks == 3) { weigh(4); weigh(5); }
+                    else weigh(ks < 3 ? ks + 1 : ks + 2);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // an LDS read
+                        __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);     // a matrix instruction
+                        __builtin_amdgcn_sched_group_barrier(0x2, 3, 0);     // vector instructions in its shadow
+                    }
+                }
+                __builtin_amdgcn_sched_barrier(0);
             }
-            __builtin_amdgcn_sched_barrier(0);
+        }
+        if constexpr (PV) {
+            bf16x8 pb[2];
 #pragma unroll
-            for (int ct = c0; ct < c0 + VGR && ct < NCT; ++ct) {
-                const bf16x8 va = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo[ct], up[ct], 0, 1, 2, 3, 4, 5, 6, 7));
+            for (int hi = 0; hi < 2; ++hi) pb[hi] = __builtin_bit_cast(bf16x8, (u32x4){w[hi][0], w[hi][1], w[hi][2], w[hi][3]});
+#pragma unroll
+            for (int hi = 0; hi < 2; ++hi) lacc[hi] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pb[hi], lacc[hi], 0, 0, 0);
+#pragma unroll
+            for (int ct = 0; ct < NCT; ++ct) {
+                if (ct + 2 < NCT) rv(ct + 2);
 #pragma unroll
                 for (int hi = 0; hi < 2; ++hi)
-                    oacc[hi][ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va, pb[hi], oacc[hi][ct], 0, 0, 0);
+                    oacc[hi][ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va[ct], pb[hi], oacc[hi][ct], 0, 0, 0);
+                if (ct & 1) __builtin_amdgcn_sched_barrier(0);
             }
-            __builtin_amdgcn_sched_barrier(0);
         }
     };
 
-    // ---- one sweep over the keys.  accumulate = false: only the exact maximum of every query is
-    // collected (into m_ref, per lane).  Returns whether some score exceeded its reference by more
-    // than FAST_GAP.
-    auto sweep = [&](bool accumulate) -> bool {
-        bool jumped = false;
-        for (int t = 0; t < t1; ++t) {
-            LDS_AS unsigned char* tile = lds + (t % NBUF) * TILE_B;
-            const int n_valid = stage_tile(t, tile);
-            float x[2][2][4];
-            score_tile(tile, t, n_valid, x);
-            const float lm[2] = {lane_max(x, 0), lane_max(x, 1)};
-            if (!accumulate) {
-                m_ref[0] = fmaxf(m_ref[0], lm[0]);
-                m_ref[1] = fmaxf(m_ref[1], lm[1]);
-                continue;
-            }
-            if (__any(m_ref[0] == -INFINITY || m_ref[1] == -INFINITY)) {   // as a rule: the first tile only
-#pragma unroll
-                for (int hi = 0; hi < 2; ++hi) {
-                    const float tm = over_groups(lm[hi]);
-                    if (m_ref[hi] == -INFINITY) m_ref[hi] = tm;
-                }
-            }
-            jumped |= lm[0] > m_ref[0] + FAST_GAP || lm[1] > m_ref[1] + FAST_GAP;
-            accumulate_tile(tile, x);
-        }
-        return jumped;
-    };
-
-    bool jumped = sweep(true);
-    if (__builtin_expect(__syncthreads_or(jumped), 0)) {
-        // ---- careful route (rare): exact maxima first, then the same accumulation against them
+    // the reference of a query: the maximum of its first tile with a visible key
+    bool unset = true;
+    auto set_reference = [&](const Scores& x) {
+        bool left = false;
 #pragma unroll
         for (int hi = 0; hi < 2; ++hi) {
-            m_ref[hi] = -INFINITY;
-            l_run[hi] = 0.f;
+            float tm = max3(x[0][hi][0], x[0][hi][1], x[0][hi][2]);
+            tm = max3(tm, x[0][hi][3], x[1][hi][0]);
+            tm = over_groups(max3(max3(tm, x[1][hi][1], x[1][hi][2]), x[1][hi][3], tm));
+            if (m_ref[hi] == -INFINITY) m_ref[hi] = tm == -INFINITY ? tm : tm * sc;
+            left |= m_ref[hi] == -INFINITY;
+        }
+        unset = __any(left);
+    };
+
+    // ---- sweeps over the keys.  ACCUMULATE against the references (set on the way where they are not yet); if some
+    // score exceeded its reference by more than FAST_GAP (rare), a sweep that only scores finds the exact maxima
+    // and the accumulation is done again against them.
+    enum { ACCUMULATE, MAXIMA, ACCUMULATE_AGAIN };
+    for (int pass = ACCUMULATE;;) {
+#pragma unroll
+        for (int hi = 0; hi < 2; ++hi) {
+            lacc[hi] = (f32x4){0.f, 0.f, 0.f, 0.f};
+            top[hi] = -INFINITY;
 #pragma unroll
             for (int ct = 0; ct < NCT; ++ct) oacc[hi][ct] = (f32x4){0.f, 0.f, 0.f, 0.f};
         }
-        start_ring();
-        sweep(false);
-        m_ref[0] = over_groups(m_ref[0]);
-        m_ref[1] = over_groups(m_ref[1]);
-        __syncthreads();         // every wave is done with the tiles of that sweep
-        start_ring();
-        sweep(true);
+        auto look_at = [&](Scores& x, int t) {   // scores of tile t, just made
+            if (!full_tile(t)) mask(x, t);
+            raise_top(x);
+            if (unset) set_reference(x);
+        };
+        // (one form of the step for all: the last one scores what the slot holds in the place of keys, the sweep
+        // for the maxima accumulates too, and neither result is used)
+        auto one = [&](int t, const Scores& x, Scores& y) {
+            stage(t);
+            step(std::true_type{}, lds + slot_of(t), x, y);
+            if (t + 1 < t1) look_at(y, t + 1);
+        };
+        Scores x, y;
+        step(std::false_type{}, lds + slot_of(-1), x, x);
+        look_at(x, 0);
+        for (int t = 0; t < t1; t += 2) {
+            one(t, x, y);
+            if (t + 1 < t1) one(t + 1, y, x);
+        }
+        if (pass == ACCUMULATE_AGAIN) break;
+        if (pass == ACCUMULATE) {
+            const bool jumped = top[0] * sc > m_ref[0] + FAST_GAP || top[1] * sc > m_ref[1] + FAST_GAP;
+            if (__builtin_expect(!__syncthreads_or(jumped), 1)) break;
+            pass = MAXIMA;
+            unset = false;
+        } else {
+#pragma unroll
+            for (int hi = 0; hi < 2; ++hi) {
+                const float tm = over_groups(top[hi]);
+                m_ref[hi] = tm == -INFINITY ? tm : tm * sc;
+            }
+            __syncthreads();     // every wave is done with the units of that sweep
+            pass = ACCUMULATE_AGAIN;
+        }
+        start();
     }
     __syncthreads();             // every wave is done with the tiles: the ring becomes exchange space
 
@@ -356,8 +393,7 @@ __global__ __launch_bounds__(MF_THREADS, WPE) void prefill_attention_kernel(Deco
     float lt[2];
 #pragma unroll
     for (int hi = 0; hi < 2; ++hi) {
-        float l = l_run[hi] + __shfl_xor(l_run[hi], 16);
-        lt[hi] = l + __shfl_xor(l, 32);
+        lt[hi] = lacc[hi][0];
         const float inv = lt[hi] > 0.f ? 1.f / lt[hi] : 0.f;
 #pragma unroll
         for (int ct = 0; ct < NCT; ++ct) {

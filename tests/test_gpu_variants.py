@@ -145,3 +145,41 @@ def test_fused_tail_few_batch_rows(mla, B, H, d_c, S):
     ref = oracle.out_proj(q_abs_storage(o2), w.W_UV)
     # fp32 sums of d_c products, one rounding to bf16 (2^-9 of the value)
     assert max_abs_rel(widen_gpu(out), ref) <= 2.0 ** -8
+
+
+# ------------------------------------------------------------------ prefill
+
+@pytest.mark.parametrize("T,lens,H,d_c,scale", [
+    (33, [33, 34, 64, 65, 96, 97, 400], 3, 256, None),       # keys on both sides of a tile and a page, one step and two
+    (129, [129, 130, 161, 1], 2, 512, None),                 # a second group of query rows with one row
+    (5, [(67 * i) % 300 + 1 for i in range(66)], 2, 256, None),   # more sequences than are ranked by length
+    (40, [200, 31, 0], 3, 256, -0.05), (40, [200, 31, 64], 3, 256, 0.0)])
+def test_prefill_edges(mla, T, lens, H, d_c, scale):
+    from test_gpu_parity import check_prefill
+    w = synth.make_workload("prefill", B=len(lens), H=H, d_head=128, d_c=d_c, d_rope=64, seq_lens=lens, io_dtype="bf16",
+                            cache_dtype="bf16", free_frac=0.1, seed=101, softmax_scale=scale)
+    check_prefill(mla, w, T)
+
+
+def test_prefill_skips_bad_pages(mla):
+    """A page outside the pool, first, in the middle and last: its tokens are left out."""
+    import torch
+    w = synth.make_workload("prefill", B=3, H=2, d_head=128, d_c=256, d_rope=64, seq_lens=[300, 200, 130], io_dtype="bf16",
+                            cache_dtype="bf16", free_frac=0.1, seed=102)
+    drop = [(0, 2), (1, 0), (2, 2)]
+    bad, pt, lens = w.page_table.copy(), np.full_like(w.page_table, -1), w.seq_lens.copy()
+    for b, i in drop:
+        bad[b, i] = w.num_pages + 1 if b else -1
+        keep = [k for k in range((w.seq_lens[b] + 63) // 64) if k != i]
+        pt[b, :len(keep)] = w.page_table[b, keep]
+        lens[b] = sum(min(64, w.seq_lens[b] - 64 * k) for k in keep)
+    d = DeviceWorkload(w)
+    T = 2
+    qn, qr = synth.multi_queries(w, T)
+    got = mla.prefill_mha(to_torch(qn, "bf16"), to_torch(qr, "bf16"), d.W_UK, d.W_UV, d.pool, to_torch(bad, "i32"), d.seq_lens,
+                          w.softmax_scale)
+    torch.cuda.synchronize()
+    # sequences 0 and 1 keep their newest rows; both tokens of the last one see all rows that are left
+    for b, t in ((slice(0, 1), slice(0, 2)), (slice(1, 2), slice(0, 2)), (slice(2, 3), slice(0, 1)), (slice(2, 3), slice(1, 2))):
+        ref = oracle.prefill_explicit(qn[b, t], qr[b, t], w.W_UK, w.W_UV, w.pool, None, pt[b], lens[b], w.softmax_scale, w.d_c)[0]
+        assert max_abs_rel(widen_gpu(got)[b, t], ref) <= TOL["bf16"]
