@@ -28,21 +28,34 @@ constexpr int PF_DH = 128;      // head dimension
 constexpr int PF_KEY = 192;     // values per key: 128 + 64
 constexpr int PF_PAGE = 64 * (PF_KEY + PF_DH);    // values per materialised page: 64 keys, then the values transposed
 
+// grid (d_c / 64, 4, heads): a block of 64 rows x 64 columns of Wcat[h]; rows 0 .. 127 are a copy, the others
+// go through LDS (the value projection's rows are columns here: read and written 128 bytes at a time)
 __global__ __launch_bounds__(256) void prefill_weights_kernel(const uint16_t* W_UK, const uint16_t* W_UV,
                                                               uint16_t* Wcat, int d_c)
 {
-    // grid (256 rows, heads); threads over the d_c columns of one row
-    const int r = blockIdx.x, h = blockIdx.y;
-    uint16_t* dst = Wcat + ((size_t)h * 256 + r) * d_c;
-    for (int c = threadIdx.x; c < d_c; c += blockDim.x)
-        dst[c] = r < PF_DH ? W_UK[((size_t)h * PF_DH + r) * d_c + c]                  // W_UK[h] is [d_head x d_c]
-                           : W_UV[((size_t)h * d_c + c) * PF_DH + (r - PF_DH)];       // W_UV[h] is [d_c x d_head]
+    __shared__ uint16_t block[64][66];
+    const int c0 = blockIdx.x * 64, r0 = blockIdx.y * 64, h = blockIdx.z;
+    const int x = threadIdx.x & 63, y = threadIdx.x >> 6;
+    uint16_t* dst = Wcat + ((size_t)h * 256 + r0) * d_c + c0;
+    if (r0 < PF_DH) {
+        const uint16_t* src = W_UK + ((size_t)h * PF_DH + r0) * d_c + c0;                 // W_UK[h] is [d_head x d_c]
+        for (int i = y; i < 64; i += 4) dst[(size_t)i * d_c + x] = src[(size_t)i * d_c + x];
+        return;
+    }
+    const uint16_t* src = W_UV + ((size_t)h * d_c + c0) * PF_DH + (r0 - PF_DH);          // W_UV[h] is [d_c x d_head]
+    for (int i = y; i < 64; i += 4) block[i][x] = src[(size_t)i * PF_DH + x];
+    __syncthreads();
+    for (int i = y; i < 64; i += 4) dst[(size_t)i * d_c + x] = block[x][i];
 }
 
 // One workgroup = two pages (128 tokens) of one (sequence, head).  Wcat[h] is streamed through LDS
-// in chunks of 32 rows (two row tiles, all d_c columns), double-buffered, rows padded by 16 bytes so
-// that the 16 rows of an A read fall in different banks; the four wavefronts share every chunk.
+// in chunks of 32 rows (two row tiles, all d_c columns), double-buffered, as direct-to-LDS loads; the four
+// wavefronts share every chunk.  Chunk position c ^ (row & 15) of a row holds its 16-byte piece c: the 16 lanes
+// that share a cycle of an A read (rows 0 .. 7 of one piece and 8 .. 15 of its neighbour, or the reverse) then
+// meet 16 different units (rows padded by 16 bytes, filled through registers, lost 3.2 of 8 cycles per read).
 // A wavefront owns 32 tokens (two column tiles) and keeps their latent rows in registers.
+// Bound by writing 640 bytes per (token, head) beside 0.25 MFLOP of products: 4 x 8192 tokens, 32 heads, d_c = 512
+// 395 -> 351 us (671 MB, 0.27 TFLOP), 26800 tokens, 28 heads, d_c = 256 190 -> 174 us (480 MB).
 template <int D_C>
 __global__ __launch_bounds__(256, 2) void prefill_materialise_kernel(const uint16_t* kv, const int32_t* page_table,
                                                                      const int32_t* seq_lens, const uint16_t* Wcat,
@@ -51,12 +64,14 @@ __global__ __launch_bounds__(256, 2) void prefill_materialise_kernel(const uint1
 {
     constexpr int ROW = D_C + 64;
     constexpr int NKS = D_C / 32;
-    constexpr int WROWB = D_C * 2 + 16;               // padded bytes per weight row in LDS
+    constexpr int WROWB = D_C * 2;                    // bytes per weight row
     constexpr int CHUNK_ROWS = 32;
+    constexpr int CHUNK_B = CHUNK_ROWS * WROWB;
     constexpr int NCHUNK = 256 / CHUNK_ROWS;          // 8
-    constexpr int PIECES = CHUNK_ROWS * (D_C / 8);    // 16-byte pieces per chunk (2048 / 1024)
-    constexpr int NPL = PIECES / 256;                 // pieces per thread (8 / 4)
-    __shared__ __attribute__((aligned(16))) unsigned char wbuf[2][CHUNK_ROWS * WROWB];
+    constexpr int NPL = CHUNK_B / 16 / 256;           // 16-byte pieces per thread and chunk (8 / 4)
+    constexpr int AH = 4;                             // k-steps that the LDS reads run ahead
+    __shared__ __attribute__((aligned(1024))) unsigned char wbuf[2 * CHUNK_B];
+    LDS_AS unsigned char* lds = (LDS_AS unsigned char*)wbuf;
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -103,27 +118,36 @@ __global__ __launch_bounds__(256, 2) void prefill_materialise_kernel(const uint1
     }
 
     const unsigned char* W = reinterpret_cast<const unsigned char*>(Wcat + (size_t)h * 256 * D_C);
-    u32x4 stage[NPL];
+    constexpr int RPL = 4096 / WROWB;                 // rows that one load of the workgroup covers (4 / 8)
+    uint32_t woff[16 / RPL];                          // (the swizzle repeats after 16 rows)
+#pragma unroll
+    for (int i = 0; i < 16 / RPL; ++i) {
+        const int q = i * 256 + tid, row = q / (D_C / 8), pos = q % (D_C / 8);
+        woff[i] = (uint32_t)(row * WROWB + ((pos ^ (row & 15)) << 4));
+    }
+    const uint32_t lds_base = (uint32_t)(uintptr_t)lds;
     auto load_chunk = [&](int c) {
+        const uint32_t dst = lds_base + (uint32_t)((c & 1) * CHUNK_B + wave * 1024);
 #pragma unroll
         for (int i = 0; i < NPL; ++i) {
-            const int q = i * 256 + tid;
-            stage[i] = *reinterpret_cast<const u32x4*>(W + ((size_t)(c * CHUNK_ROWS) * D_C + (size_t)q * 8) * 2);
+            const unsigned char* src = W + (size_t)c * CHUNK_B + (i / (16 / RPL)) * (16 * WROWB);
+            const uint32_t m0v = __builtin_amdgcn_readfirstlane(dst + i * 4096);
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+                         :: "s"(m0v), "v"(woff[i % (16 / RPL)]), "s"(src) : "memory");
         }
     };
-    auto store_chunk = [&](int buf) {
+    // A operand: weight row 16 ml + n, piece 4 ks + g
+    uint32_t a_base[4];
 #pragma unroll
-        for (int i = 0; i < NPL; ++i) {
-            const int q = i * 256 + tid;
-            const int row = q / (D_C / 8), col = q % (D_C / 8);
-            *reinterpret_cast<u32x4*>(&wbuf[buf][row * WROWB + col * 16]) = stage[i];
-        }
-    };
+    for (int e = 0; e < 4; ++e) a_base[e] = (uint32_t)(n * WROWB + (((4 * e + g) ^ n) << 4));
     load_chunk(0);
-    store_chunk(0);
-    __syncthreads();
     for (int c = 0; c < NCHUNK; ++c) {
-        if (c + 1 < NCHUNK) load_chunk(c + 1);        // in flight while this chunk is used
+        // my part of this chunk (requested a chunk ago) is there; the two results stored since may be on their way ...
+        if (c > 0 && in_seq) wait_vmcnt<2>();
+        else                 wait_vmcnt<0>();
+        __syncthreads();                              // ... and everybody's, and everybody is done with the one before
+        if (c + 1 < NCHUNK) load_chunk(c + 1);
+        LDS_AS unsigned char* chunk = lds + (c & 1) * CHUNK_B;
         if (in_seq) {
             f32x4 acc[2][2];
 #pragma unroll
@@ -133,16 +157,26 @@ __global__ __launch_bounds__(256, 2) void prefill_materialise_kernel(const uint1
             // keys: weights as the A operand (a lane ends with four dimensions of a token); values: tokens as the
             // A operand (four tokens of a dimension)
             auto product = [&](auto keys) {
+                bf16x8 a[2][NKS];
+                auto rd = [&](int ks) {
 #pragma unroll
-                for (int ks = 0; ks < NKS; ++ks)
+                    for (int ml = 0; ml < 2; ++ml)
+                        a[ml][ks] = *(LDS_AS bf16x8*)(chunk + ml * 16 * WROWB + a_base[ks & 3] + (ks >> 2) * 256);
+                };
 #pragma unroll
-                    for (int ml = 0; ml < 2; ++ml) {
-                        const bf16x8 a = *reinterpret_cast<const bf16x8*>(&wbuf[c & 1][(ml * 16 + n) * WROWB + ks * 64 + g * 16]);
+                for (int ks = 0; ks < AH; ++ks) rd(ks);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int ks = 0; ks < NKS; ++ks) {
+                    if (ks + AH < NKS) rd(ks + AH);
+#pragma unroll
+                    for (int ml = 0; ml < 2; ++ml)
 #pragma unroll
                         for (int nt = 0; nt < 2; ++nt)
-                            acc[ml][nt] = decltype(keys)::value ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, cb[nt][ks], acc[ml][nt], 0, 0, 0)
-                                                                : __builtin_amdgcn_mfma_f32_16x16x32_bf16(cb[nt][ks], a, acc[ml][nt], 0, 0, 0);
-                    }
+                            acc[ml][nt] = decltype(keys)::value ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[ml][ks], cb[nt][ks], acc[ml][nt], 0, 0, 0)
+                                                                : __builtin_amdgcn_mfma_f32_16x16x32_bf16(cb[nt][ks], a[ml][ks], acc[ml][nt], 0, 0, 0);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
             };
             auto pack8 = [&](const f32x4& lo, const f32x4& up) {
                 return (u32x4){pack_bf16x2(lo[0], lo[1]), pack_bf16x2(lo[2], lo[3]), pack_bf16x2(up[0], up[1]), pack_bf16x2(up[2], up[3])};
@@ -162,8 +196,6 @@ __global__ __launch_bounds__(256, 2) void prefill_materialise_kernel(const uint1
                     *reinterpret_cast<u32x4*>(half + ((c - NCHUNK / 2) * 2 + ml) * 512 + lane * 8) = pack8(acc[ml][0], acc[ml][1]);
             }
         }
-        if (c + 1 < NCHUNK) store_chunk((c + 1) & 1); // the other buffer: last read before the previous barrier
-        __syncthreads();
     }
 }
 
@@ -180,7 +212,7 @@ hipError_t launch_prefill_materialise(const void* kv, const int32_t* page_table,
                                       int32_t* lens2, int B, int heads, int d_c, int num_pages, int max_pages,
                                       hipStream_t s)
 {
-    prefill_weights_kernel<<<dim3(256, heads), 256, 0, s>>>(static_cast<const uint16_t*>(W_UK),
+    prefill_weights_kernel<<<dim3(d_c / 64, 4, heads), 256, 0, s>>>(static_cast<const uint16_t*>(W_UK),
                                                            static_cast<const uint16_t*>(W_UV),
                                                            static_cast<uint16_t*>(Wcat), d_c);
     hipError_t e = hipGetLastError();
