@@ -10,6 +10,7 @@ import os
 import shutil
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 from pathlib import Path
 
@@ -18,6 +19,7 @@ CSRC = PKG / "csrc"
 INCLUDE = PKG.parent / "include"
 OBJDIR = PKG / "_build"
 LIB = PKG / "libmla_gfx950.so"
+MARSHAL = PKG / ("_marshal" + sysconfig.get_config_var("EXT_SUFFIX"))
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rdc",
@@ -37,6 +39,24 @@ def hipcc() -> str:
 
 def sources():
     return sorted(CSRC.glob("*.hip"))
+
+
+def build_marshal() -> Path:
+    """The Python extension that hands tensors to the library's entry points (host code only, g++)."""
+    import torch
+    root = Path(torch.__file__).resolve().parent
+    rocm = Path(hipcc()).resolve().parents[1]
+    tmp = MARSHAL.with_suffix(".so.tmp")
+    cmd = ["g++", "-std=c++17", "-O2", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           f"-I{INCLUDE}", f"-I{sysconfig.get_paths()['include']}", f"-I{root / 'include'}",
+           f"-I{root / 'include' / 'torch' / 'csrc' / 'api' / 'include'}", f"-I{rocm / 'include'}",
+           str(CSRC / "marshal.cpp"), "-o", str(tmp), f"-L{root / 'lib'}", "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"g++ failed on marshal.cpp:\n{r.stdout}{r.stderr}")
+    os.replace(tmp, MARSHAL)
+    return MARSHAL
 
 
 def build_library(verbose: bool = False, extra_flags=()) -> Path:
@@ -70,8 +90,10 @@ def build_library(verbose: bool = False, extra_flags=()) -> Path:
 
     with ThreadPoolExecutor(max_workers=min(4, os.cpu_count() or 1)) as ex:
         check = ex.submit(check_pending_registers)
+        marshal = ex.submit(build_marshal)
         objs = list(ex.map(compile_one, sources()))
         check.result()
+        marshal.result()
     tmp = LIB.with_suffix(".so.tmp")
     cmd = [cc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", str(tmp), *map(str, objs)]
     r = subprocess.run(cmd, capture_output=True, text=True)

@@ -2,7 +2,8 @@
 
 Argument marshalling only: every function takes torch tensors that already
 live on the GPU, passes their device pointers and the current HIP stream to
-the C entry point of the same name, and returns the output tensor.  torch is
+the C entry point of the same name (the serving calls through a small
+extension, csrc/marshal.cpp), and returns the output tensor.  torch is
 used for device memory and streams; no arithmetic happens here and there is
 no fallback path: a missing library or a failing call raises.
 """
@@ -16,6 +17,7 @@ import torch
 
 _LIB_PATH = Path(__file__).resolve().parent / "libmla_gfx950.so"
 _lib = None
+_fast = None   # the marshalling extension (csrc/marshal.cpp), once lib() has handed it the entry points
 
 F32, BF16, FP8_E4M3 = 0, 1, 2
 FLAG_DEFAULT, FLAG_PORTABLE_KERNEL, FLAG_SKIP_MERGE, FLAG_BALANCED = 0, 1, 2, 4
@@ -35,7 +37,7 @@ class MlaError(RuntimeError):
 
 def lib() -> ctypes.CDLL:
     """Load libmla_gfx950.so (built in-tree by ``python -m paper_2502_07864_amd.build``)."""
-    global _lib
+    global _lib, _fast
     if _lib is None:
         if not _LIB_PATH.exists():
             raise FileNotFoundError(
@@ -82,7 +84,15 @@ def lib() -> ctypes.CDLL:
         L.mla_cache_append.restype = i
         L.mla_cache_append.argtypes = [vp, vp, vp, vp, vp, vp, vp, ctypes.c_size_t,
                                        i, i, i, i, i, i, i, f, i, i, vp]
-        _lib = L
+        try:
+            from . import _marshal
+        except ImportError as e:
+            raise FileNotFoundError(
+                f"the marshalling extension is missing ({e}): build it with `python -m paper_2502_07864_amd.build`") from e
+        _marshal.bind(*(ctypes.cast(getattr(L, n), vp).value for n in
+                        ("mla_absorb_q", "mla_out_proj", "mla_decode_paged_multi", "mla_merge_out_proj_multi",
+                         "mla_merge_partials", "mla_cache_append")))
+        _lib, _fast = L, _marshal
     return _lib
 
 
@@ -131,8 +141,17 @@ def _check(status: int, where: str):
         raise MlaError(status, where)
 
 
+# The serving calls try the marshalling extension first: it takes plain contiguous GPU tensors of the expected
+# types and shapes and returns the call's status; for anything else it returns None, having called nothing, and
+# the checks written out below decide (and raise).
+
 def absorb_q(q_nope: torch.Tensor, W_UK: torch.Tensor, out: Optional[torch.Tensor] = None) -> torch.Tensor:
     """q_abs[b,h,:] = q_nope[b,h,:] . W_UK[h];  q_nope [B,H,d_head], W_UK [H,d_head,d_c]."""
+    if out is not None and _fast is not None:
+        status = _fast.absorb_q(q_nope, W_UK, out)
+        if status is not None:
+            _check(status, "mla_absorb_q")
+            return out
     B, H, d_head = q_nope.shape
     H2, d_head2, d_c = W_UK.shape
     if (H2, d_head2) != (H, d_head) or W_UK.dtype != q_nope.dtype:
@@ -146,6 +165,11 @@ def absorb_q(q_nope: torch.Tensor, W_UK: torch.Tensor, out: Optional[torch.Tenso
 
 def out_proj(o_lat: torch.Tensor, W_UV: torch.Tensor, out: Optional[torch.Tensor] = None) -> torch.Tensor:
     """out[b,h,:] = o_lat[b,h,:] . W_UV[h];  o_lat [B,H,d_c], W_UV [H,d_c,d_head]."""
+    if out is not None and _fast is not None:
+        status = _fast.out_proj(o_lat, W_UV, out)
+        if status is not None:
+            _check(status, "mla_out_proj")
+            return out
     B, H, d_c = o_lat.shape
     H2, d_c2, d_head = W_UV.shape
     if (H2, d_c2) != (H, d_c) or W_UV.dtype != o_lat.dtype:
@@ -169,6 +193,13 @@ def decode_paged(q_abs: torch.Tensor, q_rope: Optional[torch.Tensor], kv_cache: 
     """Paged absorbed decode.  kv_cache [num_pages, page_size, d_c+d_rope];
     page_table int32 [B, max_pages_per_seq]; seq_lens int32 [B].
     Returns o_lat [B,H,d_c] (and lse [B,H] fp32 if return_lse or lse given)."""
+    if (_fast is not None and workspace is not None and (out is not None or flags & FLAG_SKIP_MERGE)
+            and not (return_lse and lse is None)):
+        status = _fast.decode(3, q_abs, q_rope, kv_cache, page_table, seq_lens, softmax_scale, num_splits, kv_scale,
+                              workspace, out, lse, flags)
+        if status is not None:
+            _check(status, "mla_decode_paged")
+            return workspace if flags & FLAG_SKIP_MERGE else (out, lse) if lse is not None else out
     B, H, d_c = q_abs.shape
     num_pages, page_size, row = kv_cache.shape
     d_rope = row - d_c
@@ -182,8 +213,8 @@ def decode_paged(q_abs: torch.Tensor, q_rope: Optional[torch.Tensor], kv_cache: 
         raise ValueError("page_table must be [B, max_pages_per_seq], seq_lens [B]")
     if kv_scale is not None and (kv_scale.dtype != torch.float32 or tuple(kv_scale.shape) != (num_pages, page_size)):
         raise ValueError("kv_scale must be float32 [num_pages, page_size]")
-    need = decode_workspace_bytes(B, H, d_c, num_splits)
     if workspace is None:
+        need = decode_workspace_bytes(B, H, d_c, num_splits)
         workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=q_abs.device)
     skip_merge = bool(flags & FLAG_SKIP_MERGE)
     if out is None and not skip_merge:
@@ -248,6 +279,13 @@ def decode_paged_multi(q_abs: torch.Tensor, q_rope: Optional[torch.Tensor], kv_c
     q_abs [B,q_len,H,d_c], q_rope [B,q_len,H,d_rope]; the cache already holds the query tokens'
     own rows (the last q_len of each sequence) and token i sees rows < seq_len - (q_len-1-i).
     Returns o_lat [B,q_len,H,d_c] (and lse [B,q_len,H] fp32 if return_lse or lse given)."""
+    if (_fast is not None and workspace is not None and (out is not None or flags & FLAG_SKIP_MERGE)
+            and not (return_lse and lse is None)):
+        status = _fast.decode(4, q_abs, q_rope, kv_cache, page_table, seq_lens, softmax_scale, num_splits, kv_scale,
+                              workspace, out, lse, flags)
+        if status is not None:
+            _check(status, "mla_decode_paged_multi")
+            return workspace if flags & FLAG_SKIP_MERGE else (out, lse) if lse is not None else out
     B, T, H, d_c = q_abs.shape
     num_pages, page_size, row = kv_cache.shape
     d_rope = row - d_c
@@ -261,8 +299,8 @@ def decode_paged_multi(q_abs: torch.Tensor, q_rope: Optional[torch.Tensor], kv_c
         raise ValueError("page_table must be [B, max_pages_per_seq], seq_lens [B]")
     if kv_scale is not None and (kv_scale.dtype != torch.float32 or tuple(kv_scale.shape) != (num_pages, page_size)):
         raise ValueError("kv_scale must be float32 [num_pages, page_size]")
-    need = decode_workspace_bytes(B, T * H, d_c, num_splits)
     if workspace is None:
+        need = decode_workspace_bytes(B, T * H, d_c, num_splits)
         workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=q_abs.device)
     skip_merge = bool(flags & FLAG_SKIP_MERGE)
     if out is None and not skip_merge:
@@ -286,6 +324,11 @@ def merge_out_proj_multi(workspace: torch.Tensor, W_UV: torch.Tensor, B: int, q_
                          lse: Optional[torch.Tensor] = None, return_lse: bool = False, flags: int = 0):
     """merge_out_proj after decode_paged_multi(flags=FLAG_SKIP_MERGE).
     Returns (o_lat [B,q_len,H,d_c], out [B,q_len,H,d_head][, lse [B,q_len,H]])."""
+    if _fast is not None and o_lat is not None and out is not None and not (return_lse and lse is None):
+        status = _fast.merge_out_proj(workspace, W_UV, o_lat, lse, out, B, q_len, num_splits, flags)
+        if status is not None:
+            _check(status, "mla_merge_out_proj_multi")
+            return (o_lat, out, lse) if lse is not None else (o_lat, out)
     H, d_c, d_head = W_UV.shape
     if o_lat is None:
         o_lat = torch.empty((B, q_len, H, d_c), dtype=W_UV.dtype, device=W_UV.device)
@@ -346,6 +389,11 @@ def merge_partials(workspace: torch.Tensor, B: int, H: int, d_c: int, num_splits
                    lse: Optional[torch.Tensor] = None, return_lse: bool = False, flags: int = 0):
     """Merge the per-chunk partials left in `workspace` by decode_paged(flags=FLAG_SKIP_MERGE);
     pass FLAG_BALANCED here iff the decode call had it."""
+    if _fast is not None and out is not None and not (return_lse and lse is None):
+        status = _fast.merge_partials(workspace, out, lse, B, H, d_c, num_splits, flags)
+        if status is not None:
+            _check(status, "mla_merge_partials")
+            return (out, lse) if lse is not None else out
     if out is None:
         out = torch.empty((B, H, d_c), dtype=dtype, device=workspace.device)
     if lse is None and return_lse:
@@ -363,6 +411,11 @@ def merge_out_proj(workspace: torch.Tensor, W_UV: torch.Tensor, B: int, num_spli
     """Merge the partials left by decode_paged(flags=FLAG_SKIP_MERGE) and apply W_UV [H,d_c,d_head]
     (pass FLAG_BALANCED here iff the decode call had it).
     Returns (o_lat [B,H,d_c], out [B,H,d_head][, lse])."""
+    if _fast is not None and o_lat is not None and out is not None and not (return_lse and lse is None):
+        status = _fast.merge_out_proj(workspace, W_UV, o_lat, lse, out, B, 1, num_splits, flags)
+        if status is not None:
+            _check(status, "mla_merge_out_proj")
+            return (o_lat, out, lse) if lse is not None else (o_lat, out)
     H, d_c, d_head = W_UV.shape
     if o_lat is None:
         o_lat = torch.empty((B, H, d_c), dtype=W_UV.dtype, device=W_UV.device)
@@ -415,6 +468,11 @@ def cache_append(x: torch.Tensor, W_DKVR: torch.Tensor, kv_cache: torch.Tensor, 
                  rope_base: float = 10000.0, workspace: Optional[torch.Tensor] = None) -> None:
     """Writes row [x . W[:, :d_c] | RoPE(x . W[:, d_c:], positions)] of one new token per sequence
     into kv_cache (in place) at logical position positions[b];  x [B, D], W_DKVR [D, d_c + d_rope]."""
+    if _fast is not None and workspace is not None:
+        status = _fast.cache_append(x, W_DKVR, kv_cache, kv_scale, page_table, positions, workspace, d_c, rope_base)
+        if status is not None:
+            _check(status, "mla_cache_append")
+            return
     B, D = x.shape
     D2, n = W_DKVR.shape
     num_pages, page_size, row = kv_cache.shape
