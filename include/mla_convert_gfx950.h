@@ -54,8 +54,9 @@ int mla_conv_rope_moments(const double* K, double* sigma,
 /*
  * Batched symmetric eigendecomposition (App. B: the columns of U are the eigenvectors
  * by descending eigenvalue; also the PCA of App. D.2).  Cyclic Jacobi rotations, one
- * workgroup per matrix up to m = 128; a larger matrix is spread over the chip, one launch per
- * rotation step, the batch is then processed one matrix after the other, and at most 16 sweeps are run.
+ * workgroup per matrix up to m = 128; a larger matrix is spread over the chip (rotations inside pairs of
+ * blocks of 16 indices, then their products applied), the batch is then processed one matrix after the
+ * other, and at most 16 sweeps are run.
  *   A      [batch, m, m]  in: symmetric matrices; out: eigenvectors in the COLUMNS, column c
  *                         belonging to evals[c]
  *   evals  [batch, m]     eigenvalues, descending

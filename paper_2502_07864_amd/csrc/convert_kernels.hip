@@ -139,17 +139,84 @@ __global__ __launch_bounds__(256) void balance_kernel(const double* K, int ldk, 
     }
 }
 
-// ------------------------------------------------------------------ batched Jacobi eigensolver
-// One workgroup per matrix.  A sweep is m - 1 (m even; else m) steps of a round-robin
-// schedule; a step rotates m/2 disjoint index pairs at once: first the rows of A
-// (A <- J^T A), then the columns of A and of V (A <- A J, V <- V J), J being the
-// product of the step's plane rotations.  Small matrices live in LDS, larger
-// ones in global memory (the waves of a workgroup share one vector cache, so a barrier
-// orders their accesses).  At the end the eigenvalues are ranked in descending order
-// and the columns of V are written over A in that order.
+// ------------------------------------------------------------------ Jacobi rotations of one workgroup
+// A step of the round-robin schedule rotates m/2 disjoint index pairs at once: A <- J^T A J, V <- V J, J being
+// the product of the step's plane rotations.  A and V have row pitch ld; an odd m has a bye (index m).  Bound by
+// the step's chain: the angles (two divisions, two square roots) of m/2 threads, a barrier, the rotations, a
+// barrier.  The workgroup's threads each take 2 x 2 blocks of A (the rows of one pair, the columns of another:
+// both rotations of a block in registers, rows first) and pairs of V.  (An earlier form rotated all rows, met a
+// barrier and rotated all columns, one element pair at a time, every element of A read and written twice: 32
+// matrices of order 64, 8 sweeps, 3.06 ms against 1.59.)
+struct Rotations {
+    int pp[64], qq[64];
+    double cc[64], ss[64];
+};
+
+__device__ __forceinline__ void round_robin_pair(int k, int step, int mp, int& p, int& q) {
+    if (k == 0) { p = mp - 1; q = step; }
+    else { p = (step + k) % (mp - 1); q = (step - k + (mp - 1)) % (mp - 1); }
+    if (p > q) { const int t = p; p = q; q = t; }
+}
+
+__device__ __forceinline__ void jacobi_step(double* A, double* V, int ld, int m, int step, Rotations& R, int tid, int nt) {
+    const int mp = m + (m & 1), half = mp / 2;
+    if (tid < half) {
+        int p, q;
+        round_robin_pair(tid, step, mp, p, q);
+        double c = 1.0, s = 0.0;
+        if (q < m) {
+            const double apq = A[p * ld + q];
+            const double app = A[p * ld + p], aqq = A[q * ld + q];
+            if (fabs(apq) > 1e-300 && fabs(apq) > 1e-18 * sqrt(fabs(app * aqq))) {
+                const double theta = (aqq - app) / (2.0 * apq);
+                const double t = (theta >= 0.0 ? 1.0 : -1.0) / (fabs(theta) + sqrt(theta * theta + 1.0));
+                c = 1.0 / sqrt(t * t + 1.0);
+                s = t * c;
+            }
+        }
+        R.pp[tid] = p; R.qq[tid] = q; R.cc[tid] = c; R.ss[tid] = s;
+    }
+    __syncthreads();
+    for (int idx = tid; idx < half * half; idx += nt) {
+        const int k1 = idx / half, k2 = idx % half;
+        const double s1 = R.ss[k1], s2 = R.ss[k2];
+        if (s1 == 0.0 && s2 == 0.0) continue;
+        const double c1 = R.cc[k1], c2 = R.cc[k2];
+        const int p1 = R.pp[k1] * ld, q1 = R.qq[k1] * ld, p2 = R.pp[k2], q2 = R.qq[k2];
+        const bool r = R.qq[k1] < m, t = q2 < m;         // (a bye has no second row / column)
+        const double app = A[p1 + p2], apq = t ? A[p1 + q2] : 0.0;
+        const double aqp = r ? A[q1 + p2] : 0.0, aqq = r && t ? A[q1 + q2] : 0.0;
+        const double pp = c1 * app - s1 * aqp, pq = c1 * apq - s1 * aqq;      // rows
+        const double qp = s1 * app + c1 * aqp, qq = s1 * apq + c1 * aqq;
+        const bool pair = k1 == k2;                      // the rotation was chosen to annihilate these two: exact zeros
+        A[p1 + p2] = c2 * pp - s2 * pq;                  // columns
+        if (t) A[p1 + q2] = pair ? 0.0 : s2 * pp + c2 * pq;
+        if (r) A[q1 + p2] = pair ? 0.0 : c2 * qp - s2 * qq;
+        if (r && t) A[q1 + q2] = s2 * qp + c2 * qq;
+    }
+    for (int idx = tid; idx < half * m; idx += nt) {
+        const int k = idx % half, i = idx / half;
+        const double s = R.ss[k];
+        if (s != 0.0) {
+            const double c = R.cc[k];
+            const int ip = i * ld + R.pp[k], iq = i * ld + R.qq[k];
+            const double vp = V[ip], vq = V[iq];
+            V[ip] = c * vp - s * vq;
+            V[iq] = s * vp + c * vq;
+        }
+    }
+    __syncthreads();
+}
+
+// ------------------------------------------------------------------ batched Jacobi eigensolver, order <= 128
+// One workgroup per matrix, a sweep = m - 1 (m even; else m) steps.  Small matrices live in LDS (rows padded by
+// one element), larger ones in global memory (the waves of a workgroup share one vector cache, so a barrier
+// orders their accesses).  At the end the eigenvalues are ranked in descending order and the columns of V are
+// written over A in that order.
 struct JacobiLds {
-    int pp[1024], qq[1024];
-    double cc[1024], ss[1024];
+    Rotations rot;
+    double diag[128];
+    int rank[128];
     double red[16];
 };
 
@@ -161,117 +228,66 @@ __global__ __launch_bounds__(1024) void jacobi_kernel(double* A_all, double* eva
     const int tid = threadIdx.x, nt = blockDim.x;
     double* Ag = A_all + (long)blockIdx.x * m * m;
     double* Vg = V_all + (long)blockIdx.x * m * m;
+    const int ld = in_lds ? m + 1 : m;
     double* A = in_lds ? lds_mat : Ag;
-    double* V = in_lds ? lds_mat + (long)m * m : Vg;
+    double* V = in_lds ? lds_mat + (long)m * ld : Vg;
 
     double tot = 0.0;
     for (int idx = tid; idx < m * m; idx += nt) {
         const double v = Ag[idx];
-        if (in_lds) A[idx] = v;
-        V[idx] = (idx / m == idx % m) ? 1.0 : 0.0;
+        const int i = idx / m, j = idx % m;
+        if (in_lds) A[i * ld + j] = v;
+        V[i * ld + j] = i == j ? 1.0 : 0.0;
         tot += v * v;
     }
     tot = block_sum(tot, L.red);                       // squared Frobenius norm (orthogonal similarity keeps it)
     const double tol2 = 1e-26 * tot;
 
-    const int mp = m + (m & 1), half = mp / 2;        // odd m: index m is a bye
+    const int mp = m + (m & 1);
     int used = -1;
     for (int sweep = 0; sweep <= max_sweeps; ++sweep) {
         double off = 0.0;
         for (int idx = tid; idx < m * m; idx += nt)
-            if (idx / m != idx % m) { const double v = A[idx]; off += v * v; }
+            if (idx / m != idx % m) { const double v = A[idx / m * ld + idx % m]; off += v * v; }
         off = block_sum(off, L.red);
         if (off <= tol2) { used = sweep > 0 ? sweep : 1; break; }
         if (sweep == max_sweeps) break;
-        for (int step = 0; step < mp - 1; ++step) {
-            for (int k = tid; k < half; k += nt) {
-                int p, q;
-                if (k == 0) { p = mp - 1; q = step; }
-                else { p = (step + k) % (mp - 1); q = (step - k + (mp - 1)) % (mp - 1); }
-                if (p > q) { const int t = p; p = q; q = t; }
-                double c = 1.0, s = 0.0;
-                if (q < m) {
-                    const double apq = A[(long)p * m + q];
-                    const double app = A[(long)p * m + p], aqq = A[(long)q * m + q];
-                    if (fabs(apq) > 1e-300 && fabs(apq) > 1e-18 * sqrt(fabs(app * aqq))) {
-                        const double theta = (aqq - app) / (2.0 * apq);
-                        const double t = (theta >= 0.0 ? 1.0 : -1.0) / (fabs(theta) + sqrt(theta * theta + 1.0));
-                        c = 1.0 / sqrt(t * t + 1.0);
-                        s = t * c;
-                    }
-                } else {
-                    q = p;                              // bye: nothing to rotate
-                }
-                L.pp[k] = p; L.qq[k] = q; L.cc[k] = c; L.ss[k] = s;
-            }
-            __syncthreads();
-            // rows p and q of A
-            for (int idx = tid; idx < half * m; idx += nt) {
-                const int k = idx / m, j = idx % m;
-                const double s = L.ss[k];
-                if (s != 0.0) {
-                    const double c = L.cc[k];
-                    const long ip = (long)L.pp[k] * m + j, iq = (long)L.qq[k] * m + j;
-                    const double ap = A[ip], aq = A[iq];
-                    A[ip] = c * ap - s * aq;
-                    A[iq] = s * ap + c * aq;
-                }
-            }
-            __syncthreads();
-            // columns p and q of A and of V
-            for (int idx = tid; idx < half * m; idx += nt) {
-                const int k = idx % half, i = idx / half;
-                const double s = L.ss[k];
-                if (s != 0.0) {
-                    const double c = L.cc[k];
-                    const long ip = (long)i * m + L.pp[k], iq = (long)i * m + L.qq[k];
-                    const double ap = A[ip], aq = A[iq];
-                    // the rotation was chosen to annihilate A[p][q] and A[q][p]: store exact zeros there
-                    A[ip] = i == L.qq[k] ? 0.0 : c * ap - s * aq;
-                    A[iq] = i == L.pp[k] ? 0.0 : s * ap + c * aq;
-                    const double vp = V[ip], vq = V[iq];
-                    V[ip] = c * vp - s * vq;
-                    V[iq] = s * vp + c * vq;
-                }
-            }
-            __syncthreads();
-        }
+        for (int step = 0; step < mp - 1; ++step) jacobi_step(A, V, ld, m, step, L.rot, tid, nt);
     }
 
-    // rank the diagonal in descending order (ties: lower index first); cc doubles as the diagonal store
-    double* diag = L.cc;                               // m <= 2048 entries: cc and ss are adjacent, 2048 doubles
-    int* rank = L.pp;                                  // pp and qq are adjacent, 2048 ints
+    // rank the diagonal in descending order (ties: lower index first)
     __syncthreads();
-    for (int i = tid; i < m; i += nt) diag[i] = A[(long)i * m + i];
+    for (int i = tid; i < m; i += nt) L.diag[i] = A[i * ld + i];
     __syncthreads();
     for (int i = tid; i < m; i += nt) {
-        const double di = diag[i];
+        const double di = L.diag[i];
         int r = 0;
-        for (int j = 0; j < m; ++j) { const double dj = diag[j]; r += (dj > di) || (dj == di && j < i); }
-        rank[i] = r;
+        for (int j = 0; j < m; ++j) { const double dj = L.diag[j]; r += (dj > di) || (dj == di && j < i); }
+        L.rank[i] = r;
         evals_all[(long)blockIdx.x * m + r] = di;
     }
     __syncthreads();
     for (int idx = tid; idx < m * m; idx += nt) {
         const int i = idx / m, c = idx % m;
-        Ag[(long)i * m + rank[c]] = V[idx];
+        Ag[(long)i * m + L.rank[c]] = V[i * ld + c];
     }
     if (tid == 0) info[blockIdx.x] = used;
 }
 
 // ------------------------------------------------------------------ Jacobi eigensolver, one large matrix
-// The same rotations as above, spread over the chip, one launch per step (one workgroup per index
-// pair: pending column rotations of the previous step on its two rows, then its own angle and row
-// rotation).  Launch order on the stream is the only synchronisation.  A sweep
-// starts with a norm launch that raises `done` once the off-diagonal part is small; later launches
+// Block Jacobi over the chip: the indices are cut into blocks of 16; a step of the round-robin schedule over the
+// blocks takes disjoint pairs of blocks.  jb_pair_kernel: the workgroup of pair P = (I, J) runs one sweep of
+// rotations on the 32 x 32 matrix A[P, P] in LDS, accumulating them in a 32 x 32 orthogonal matrix Z_P;
+// jb_update_kernel applies them: A[P, Q] <- Z_P^T A[P, Q] Z_Q, V[:, Q] <- V[:, Q] Z_Q, on the fp64 matrix
+// instructions, one workgroup per 32 x 32 tile.  Launch order on the stream is the only synchronisation.  A sweep
+// of order m is m/16 - 1 such steps of two launches and annihilates every pair of indices at least once; single
+// rotations spread over the chip took m - 1 launches that each rewrote A and V: order 768, 10 us a launch, 47 ms
+// for 6 sweeps (and 14 ms for the norms, by one workgroup, and for the launches behind convergence); this form
+// 47 us a step, 14 ms in all, 36 us of a step for the 31 dependent rotation steps of a pair.  A sweep starts with a norm pair of launches that raises `done` once the off-diagonal part is small; later launches
 // then return at once, so the host can enqueue the maximum number of sweeps without reading back.
 struct WideState { double tot; int done, sweeps; };
-
-__device__ __forceinline__ void round_robin_pair(int k, int step, int mp, int& p, int& q) {
-    if (k == 0) { p = mp - 1; q = step; }
-    else { p = (step + k) % (mp - 1); q = (step - k + (mp - 1)) % (mp - 1); }
-    if (p > q) { const int t = p; p = q; q = t; }
-}
+constexpr int JB = 16, JP = 2 * JB;                    // block, pair of blocks
+constexpr int JB_NORM_WGS = 64;
 
 __global__ __launch_bounds__(256) void jw_init_kernel(double* __restrict__ V, int m, WideState* st) {
     const long total = (long)m * m;
@@ -280,93 +296,99 @@ __global__ __launch_bounds__(256) void jw_init_kernel(double* __restrict__ V, in
     if (blockIdx.x == 0 && threadIdx.x == 0) { st->tot = 0.0; st->done = 0; st->sweeps = -1; }
 }
 
-__global__ __launch_bounds__(1024) void jw_norm_kernel(const double* __restrict__ A, int m, int sweep, WideState* st) {
+// partial squared norms (off the diagonal, on it) of a share of the rows; then their sums in order
+__global__ __launch_bounds__(256) void jw_partial_norm_kernel(const double* __restrict__ A, int m, double* __restrict__ part, const WideState* st) {
     __shared__ double red[16];
     if (st->done) return;
     double off = 0.0, dia = 0.0;
-    for (int idx = threadIdx.x; idx < m * m; idx += 1024) {
-        const double v = A[idx];
-        if (idx / m == idx % m) dia += v * v; else off += v * v;
-    }
+    for (int i = blockIdx.x; i < m; i += JB_NORM_WGS)
+        for (int j = threadIdx.x; j < m; j += 256) {
+            const double v = A[(long)i * m + j];
+            if (i == j) dia += v * v; else off += v * v;
+        }
     off = block_sum(off, red);
     dia = block_sum(dia, red);
+    if (threadIdx.x == 0) { part[2 * blockIdx.x] = off; part[2 * blockIdx.x + 1] = dia; }
+}
+
+__global__ __launch_bounds__(64) void jw_norm_kernel(const double* __restrict__ part, int sweep, WideState* st) {
+    static_assert(JB_NORM_WGS == 64, "one lane per partial norm");
+    if (st->done) return;
+    const double off = wave_sum(part[2 * threadIdx.x]), dia = wave_sum(part[2 * threadIdx.x + 1]);
     if (threadIdx.x == 0) {
         if (sweep == 0) st->tot = off + dia;
         if (off <= 1e-26 * st->tot) { st->done = 1; st->sweeps = sweep > 0 ? sweep : 1; }
     }
 }
 
-// One step in one launch.  The workgroup of pair (p, q) first applies the column rotations of the
-// PREVIOUS step (all its pairs, angles in cs_prev) to its own two rows of A and V -- every row belongs to
-// exactly one pair of the current step, so every row gets them exactly once -- then derives its own angle,
-// publishes it in cs_next and rotates its two rows of A.  The column rotations of the last step before a
-// norm check are flushed by jw_cols_kernel.
-__global__ __launch_bounds__(256) void jw_step_kernel(double* A, double* V, int m, int mp, int step, int has_prev,
-                                                      const double* __restrict__ cs_prev, double* __restrict__ cs_next,
-                                                      const WideState* st) {
+// index r of pair (I, J) in the matrix (>= m: not there)
+__device__ __forceinline__ int pair_index(int I, int J, int r) { return (r < JB ? I : J) * JB + (r & (JB - 1)); }
+
+__global__ __launch_bounds__(256) void jb_pair_kernel(double* A, double* __restrict__ Z, int m, int nbp, int step, const WideState* st) {
+    __shared__ double a[JP * (JP + 1)], z[JP * (JP + 1)];
+    __shared__ Rotations rot;
     if (st->done) return;
-    const int k = blockIdx.x, half = mp / 2;
-    int p, q;
-    round_robin_pair(k, step, mp, p, q);
-    const int nrows = q < m ? 2 : 1;                   // a bye: only row p exists
-    if (has_prev) {
-        const int prev = (step + mp - 2) % (mp - 1);
-        for (int idx = threadIdx.x; idx < nrows * half; idx += 256) {
-            const int i = idx < half ? p : q, kk = idx < half ? idx : idx - half;
-            const double c = cs_prev[2 * kk], s = cs_prev[2 * kk + 1];
-            if (s != 0.0) {
-                int pp, qq;
-                round_robin_pair(kk, prev, mp, pp, qq);
-                const long ip = (long)i * m + pp, iq = (long)i * m + qq;
-                const double ap = A[ip], aq = A[iq];
-                A[ip] = i == qq ? 0.0 : c * ap - s * aq;        // the annihilated pair gets exact zeros
-                A[iq] = i == pp ? 0.0 : s * ap + c * aq;
-                const double vp = V[ip], vq = V[iq];
-                V[ip] = c * vp - s * vq;
-                V[iq] = s * vp + c * vq;
-            }
-        }
-        __syncthreads();
+    const int tid = threadIdx.x;
+    int I, J;
+    round_robin_pair(blockIdx.x, step, nbp, I, J);
+    for (int idx = tid; idx < JP * JP; idx += 256) {
+        const int r = idx / JP, c = idx % JP, i = pair_index(I, J, r), j = pair_index(I, J, c);
+        a[r * (JP + 1) + c] = i < m && j < m ? A[(long)i * m + j] : 0.0;      // indices that are not there rotate with nothing
+        z[r * (JP + 1) + c] = r == c ? 1.0 : 0.0;
     }
-    double c = 1.0, s = 0.0;
-    if (q < m) {
-        const double apq = A[(long)p * m + q], app = A[(long)p * m + p], aqq = A[(long)q * m + q];
-        if (fabs(apq) > 1e-300 && fabs(apq) > 1e-18 * sqrt(fabs(app * aqq))) {
-            const double theta = (aqq - app) / (2.0 * apq);
-            const double t = (theta >= 0.0 ? 1.0 : -1.0) / (fabs(theta) + sqrt(theta * theta + 1.0));
-            c = 1.0 / sqrt(t * t + 1.0);
-            s = t * c;
-        }
-    }
-    __syncthreads();                                   // every thread holds the angle before a row changes
-    if (threadIdx.x == 0) { cs_next[2 * k] = c; cs_next[2 * k + 1] = s; }
-    if (s == 0.0) return;
-    for (int j = threadIdx.x; j < m; j += 256) {
-        const long ip = (long)p * m + j, iq = (long)q * m + j;
-        const double ap = A[ip], aq = A[iq];
-        A[ip] = c * ap - s * aq;
-        A[iq] = s * ap + c * aq;
+    __syncthreads();
+    for (int s = 0; s < JP - 1; ++s) jacobi_step(a, z, JP + 1, JP, s, rot, tid, 256);
+    for (int idx = tid; idx < JP * JP; idx += 256) {
+        const int r = idx / JP, c = idx % JP, i = pair_index(I, J, r), j = pair_index(I, J, c);
+        if (i < m && j < m) A[(long)i * m + j] = a[r * (JP + 1) + c];
+        Z[(long)blockIdx.x * JP * JP + idx] = z[r * (JP + 1) + c];
     }
 }
 
-__global__ __launch_bounds__(256) void jw_cols_kernel(double* A, double* V, int m, int mp, int step,
-                                                      const double* __restrict__ cs, const WideState* st) {
+// grid (column pair Q, row pair P or 32 rows of V, 2: A or V); four wavefronts, one 16 x 16 tile of the result each
+__global__ __launch_bounds__(256) void jb_update_kernel(double* A, double* V, const double* __restrict__ Z, int m, int nbp, int step,
+                                                        const WideState* st) {
+    typedef double f64x4 __attribute__((ext_vector_type(4)));
+    constexpr int LDT = JP + 1;
+    __shared__ double t[JP * LDT], zq[JP * LDT], zp[JP * LDT];
     if (st->done) return;
-    const int half = mp / 2;
-    const long idx = (long)blockIdx.x * 256 + threadIdx.x;
-    if (idx >= (long)half * m) return;
-    const int k = (int)(idx % half), i = (int)(idx / half);
-    const double c = cs[2 * k], s = cs[2 * k + 1];
-    if (s == 0.0) return;
-    int p, q;
-    round_robin_pair(k, step, mp, p, q);
-    const long ip = (long)i * m + p, iq = (long)i * m + q;
-    const double ap = A[ip], aq = A[iq];
-    A[ip] = i == q ? 0.0 : c * ap - s * aq;            // the annihilated pair gets exact zeros
-    A[iq] = i == p ? 0.0 : s * ap + c * aq;
-    const double vp = V[ip], vq = V[iq];
-    V[ip] = c * vp - s * vq;
-    V[iq] = s * vp + c * vq;
+    const int Q = blockIdx.x, P = blockIdx.y, tid = threadIdx.x;
+    const bool on_v = blockIdx.z == 1;
+    if (!on_v && P == Q) return;                       // the pair's own tile has been rotated where the angles were found
+    int I, J, K, L;
+    round_robin_pair(Q, step, nbp, I, J);
+    round_robin_pair(P, step, nbp, K, L);
+    double* M = on_v ? V : A;
+    auto row_of = [&](int r) { return on_v ? P * JP + r : pair_index(K, L, r); };
+    for (int idx = tid; idx < JP * JP; idx += 256) {
+        const int r = idx / JP, c = idx % JP, i = row_of(r), j = pair_index(I, J, c);
+        t[r * LDT + c] = i < m && j < m ? M[(long)i * m + j] : 0.0;
+        zq[r * LDT + c] = Z[(long)Q * JP * JP + idx];
+        if (!on_v) zp[r * LDT + c] = Z[(long)P * JP * JP + idx];
+    }
+    __syncthreads();
+    // v_mfma_f64_16x16x4: lane l supplies A[l % 16][l / 16], B[l / 16][l % 16], receives D[4 r + l / 16][l % 16]
+    const int lane = tid & 63, wave = tid >> 6, li = lane & 15, lq = lane >> 4;
+    const int r0 = (wave >> 1) * 16, c0 = (wave & 1) * 16;
+    f64x4 acc = (f64x4){0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int k = 0; k < JP; k += 4)
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(t[(r0 + li) * LDT + k + lq], zq[(k + lq) * LDT + c0 + li], acc, 0, 0, 0);
+    if (!on_v) {
+        __syncthreads();                               // everybody is done with t: it becomes T Z_Q
+#pragma unroll
+        for (int r = 0; r < 4; ++r) t[(r0 + 4 * r + lq) * LDT + c0 + li] = acc[r];
+        __syncthreads();
+        acc = (f64x4){0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int k = 0; k < JP; k += 4)
+            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(zp[(k + lq) * LDT + r0 + li], t[(k + lq) * LDT + c0 + li], acc, 0, 0, 0);
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int i = row_of(r0 + 4 * r + lq), j = pair_index(I, J, c0 + li);
+        if (i < m && j < m) M[(long)i * m + j] = acc[r];
+    }
 }
 
 __global__ __launch_bounds__(1024) void jw_rank_kernel(const double* __restrict__ A, int m, double* __restrict__ evals,
@@ -645,27 +667,34 @@ hipError_t launch_balance(const double* K, int ldk, const double* V, int ldv, co
     return hipGetLastError();
 }
 
-// scratch behind the batch of V matrices: angles, ranks, state of the wide solver
-constexpr size_t JACOBI_EXTRA_BYTES = 2 * (2 * 1024 * sizeof(double)) + EIG_MAX_M * sizeof(int) + 256;
-size_t jacobi_work_bytes(int batch, int m) { return (size_t)batch * m * m * sizeof(double) + JACOBI_EXTRA_BYTES; }
+// scratch behind the batch of V matrices (order > 128): the pairs' rotations, partial norms, ranks, state
+static size_t jacobi_extra_bytes(int m) {
+    if (m <= 128) return 256;
+    const size_t pairs = ((m + JB - 1) / JB + 1) / 2;
+    return pairs * JP * JP * sizeof(double) + 2 * JB_NORM_WGS * sizeof(double) + EIG_MAX_M * sizeof(int) + 256;
+}
+size_t jacobi_work_bytes(int batch, int m) { return (size_t)batch * m * m * sizeof(double) + jacobi_extra_bytes(m); }
 
 static hipError_t launch_jacobi_wide(double* A, double* evals, double* V, void* extra, int* info, int m, int max_sweeps, hipStream_t s) {
-    double* cs[2] = {static_cast<double*>(extra), static_cast<double*>(extra) + 2 * 1024};   // angles of step parity
-    int* rank = reinterpret_cast<int*>(cs[1] + 2 * 1024);
+    const int nb = (m + JB - 1) / JB, nbp = nb + (nb & 1), pairs = nbp / 2;
+    double* Z = static_cast<double*>(extra);
+    double* part = Z + (size_t)pairs * JP * JP;
+    int* rank = reinterpret_cast<int*>(part + 2 * JB_NORM_WGS);
     WideState* st = reinterpret_cast<WideState*>(rank + EIG_MAX_M);
-    const int mp = m + (m & 1), half = mp / 2;
     hipError_t e;
     jw_init_kernel<<<grid_for((long)m * m), 256, 0, s>>>(V, m, st);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    const int col_grid = (int)(((long)half * m + 255) / 256);
+    // tiles of A (pairs x pairs) and of V (32 rows x pairs) in one grid
+    const dim3 tiles(pairs, std::max(pairs, (m + JP - 1) / JP), 2);
     for (int sweep = 0; sweep <= max_sweeps; ++sweep) {
-        jw_norm_kernel<<<1, 1024, 0, s>>>(A, m, sweep, st);
+        jw_partial_norm_kernel<<<JB_NORM_WGS, 256, 0, s>>>(A, m, part, st);
+        jw_norm_kernel<<<1, 64, 0, s>>>(part, sweep, st);
         if ((e = hipGetLastError()) != hipSuccess) return e;
         if (sweep == max_sweeps) break;
-        for (int step = 0; step < mp - 1; ++step)
-            jw_step_kernel<<<half, 256, 0, s>>>(A, V, m, mp, step, step > 0, cs[(step + 1) & 1], cs[step & 1], st);
-        // the column rotations of the sweep's last step, before the norm is taken
-        jw_cols_kernel<<<col_grid, 256, 0, s>>>(A, V, m, mp, mp - 2, cs[(mp - 2) & 1], st);
+        for (int step = 0; step < nbp - 1; ++step) {
+            jb_pair_kernel<<<pairs, 256, 0, s>>>(A, Z, m, nbp, step, st);
+            jb_update_kernel<<<tiles, 256, 0, s>>>(A, V, Z, m, nbp, step, st);
+        }
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     jw_rank_kernel<<<1, 1024, 0, s>>>(A, m, evals, rank, st, info);
@@ -685,12 +714,13 @@ hipError_t launch_jacobi(double* A, double* evals, double* work, int* info, int 
         return hipSuccess;
     }
     const size_t head = (sizeof(JacobiLds) + 15) & ~size_t(15);
-    const size_t mats = 2 * (size_t)m * m * sizeof(double);
+    const size_t mats = 2 * (size_t)m * (m + 1) * sizeof(double);
     const int in_lds = head + mats <= 128 * 1024;
     const size_t bytes = head + (in_lds ? mats : 0);
     hipError_t e0 = allow_dynamic_lds(reinterpret_cast<const void*>(&jacobi_kernel), 128 * 1024);
     if (e0 != hipSuccess) return e0;
-    const int threads = m <= 64 ? 256 : 1024;
+    // a thread per 2 x 2 block of a step, up to the 1024 a workgroup can have
+    const int half = (m + 1) / 2, threads = std::min(1024, std::max(64, (half * half + 63) / 64 * 64));
     jacobi_kernel<<<batch, threads, bytes, s>>>(A, evals, work, info, m, max_sweeps, in_lds);
     return hipGetLastError();
 }

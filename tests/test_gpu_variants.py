@@ -183,3 +183,26 @@ def test_prefill_skips_bad_pages(mla):
     for b, t in ((slice(0, 1), slice(0, 2)), (slice(1, 2), slice(0, 2)), (slice(2, 3), slice(0, 1)), (slice(2, 3), slice(1, 2))):
         ref = oracle.prefill_explicit(qn[b, t], qr[b, t], w.W_UK, w.W_UV, w.pool, None, pt[b], lens[b], w.softmax_scale, w.d_c)[0]
         assert max_abs_rel(widen_gpu(got)[b, t], ref) <= TOL["bf16"]
+
+
+# ------------------------------------------------------------------ conversion: eigensolver
+
+@pytest.mark.parametrize("batch,m", [(1, 129), (2, 144), (1, 160), (1, 161), (1, 175), (1, 300), (5, 2), (3, 3), (4, 17), (2, 96), (2, 127), (1, 128)])
+def test_sym_eig_block_edges(mla, batch, m):
+    """Orders around whole and half blocks of 16 and pairs of 32 (an odd count of blocks has a bye, a last block few
+    indices), and the one-workgroup kernel with and without a bye, in LDS and past it: A U = U diag(evals),
+    orthogonal U, LAPACK's eigenvalues, to fp64 rounding of an order-m sum."""
+    import torch
+    from paper_2502_07864_amd import convert
+    r = synth.stream(111, m)
+    X = r.standard_normal((batch, m, m)) * (1.0 + np.arange(m)) ** -0.8
+    A = X.transpose(0, 2, 1) @ X
+    evals, U, info = convert.sym_eig(torch.from_numpy(A).cuda())
+    torch.cuda.synchronize()
+    evals, U = evals.cpu().numpy(), U.cpu().numpy()
+    assert (info.cpu().numpy() >= 1).all()
+    for b in range(batch):
+        norm = np.linalg.norm(A[b])
+        assert np.abs(U[b].T @ U[b] - np.eye(m)).max() <= 1e-12
+        assert np.abs(A[b] @ U[b] - U[b] * evals[b]).max() <= 1e-12 * norm
+        assert np.abs(evals[b] - np.linalg.eigvalsh(A[b])[::-1]).max() <= 1e-12 * norm
