@@ -206,3 +206,42 @@ def test_sym_eig_block_edges(mla, batch, m):
         assert np.abs(U[b].T @ U[b] - np.eye(m)).max() <= 1e-12
         assert np.abs(A[b] @ U[b] - U[b] * evals[b]).max() <= 1e-12 * norm
         assert np.abs(evals[b] - np.linalg.eigvalsh(A[b])[::-1]).max() <= 1e-12 * norm
+
+
+# ------------------------------------------------------------------ cache append
+
+@pytest.mark.parametrize("B,D,d_c,cache", [(1, 32, 16, "bf16"), (15, 96, 512, "bf16"), (16, 4096, 512, "f32"),
+                                           (17, 4128, 64, "bf16"), (64, 1056, 512, "f32"), (65, 1024, 512, "bf16"),
+                                           (128, 256, 256, "bf16"), (3, 8192, 240, "f32"), (3, 8224, 512, "bf16")])
+def test_cache_append_edges(mla, B, D, d_c, cache):
+    """bf16 projections around the borders of the one-kernel form (16 rows, 32 and 64 deep, 16 columns, one round of the
+    chip) against float64; rows with a position or page out of range, and everything else in the pool, untouched."""
+    import torch
+    n, rng = d_c + 64, np.random.default_rng(B + D)
+    x = synth.store(rng.standard_normal((B, D)).astype(np.float32), "bf16")
+    W = synth.store((rng.standard_normal((D, n)) / np.sqrt(D)).astype(np.float32), "bf16")
+    table = (np.arange(B)[:, None] * 2 + np.arange(2)).astype(np.int32)
+    pos = rng.integers(0, 32, B).astype(np.int32)
+    good = np.ones(B, bool)
+    if B > 4:
+        pos[1], pos[2], good[1:3] = -1, 32, False
+        table[3], good[3] = 2 * B, False
+    start = torch.full((2 * B, 16, n), 7.0, dtype=torch.float32 if cache == "f32" else torch.bfloat16, device="cuda")
+    pool = start.clone()
+    mla.cache_append(to_torch(x, "bf16"), to_torch(W, "bf16"), pool, to_torch(table, "i32"), to_torch(pos, "i32"), d_c)
+    torch.cuda.synchronize()
+    x64, W64 = oracle.widen(x).astype(np.float64), oracle.widen(W).astype(np.float64)
+    ref = x64 @ W64
+    turn = pos[:, None] * 10000.0 ** (-2.0 * np.arange(32) / 64)
+    re, im = ref[:, d_c::2].copy(), ref[:, d_c + 1::2].copy()
+    ref[:, d_c::2], ref[:, d_c + 1::2] = re * np.cos(turn) - im * np.sin(turn), re * np.sin(turn) + im * np.cos(turn)
+    # fp32 sums of D products in some order: D 2^-24 of the sum of magnitudes at most; both components of a pair
+    # enter the turned ones (|cos| + |sin| <= 1.5); then the cache's rounding
+    mag = np.abs(x64) @ np.abs(W64)
+    mag[:, d_c:] = 1.5 * np.repeat(np.maximum(mag[:, d_c::2], mag[:, d_c + 1::2]), 2, axis=1)
+    tol = D * 2.0 ** -24 * mag + (2.0 ** -23 if cache == "f32" else 2.0 ** -8) * np.abs(ref)
+    got, rows = widen_gpu(pool), np.arange(B)[good]
+    at = table[rows, pos[rows] // 16], pos[rows] % 16
+    assert (np.abs(got[at] - ref[rows]) <= tol[rows]).all()
+    got[at] = 7.0
+    assert (got == 7.0).all()
