@@ -53,6 +53,7 @@ int chol_qr(const double* Y, double* out, const TopWs& w, int m, int p, int* bad
     GemmF64 gram = gemm_tn(Y, p, Y, p, w.G, p, p, p, m, 1.0);
     gram.partial = w.part;
     gram.partial_doubles = w.part_doubles;
+    gram.symmetric = 1;
     hipError_t e = launch_gemm_f64(gram, s);
     if (e != hipSuccess) return MLA_ERR_HIP;
     e = launch_chol_inverse(w.G, w.X, w.tmp, p, bad, s);
@@ -188,7 +189,9 @@ int mla_conv_joint_moment(const double* K_nope, int ldk, const double* V, int ld
     const int m = a + b;
     hipError_t e = launch_balance(K_nope, ldk, V, ldv, alpha, C, n, a, b, s);
     if (e != hipSuccess) return MLA_ERR_HIP;
-    return st(launch_gemm_f64(gemm_tn(C, m, C, m, S, m, m, m, n, 1.0 / (double)n), s));
+    GemmF64 moment = gemm_tn(C, m, C, m, S, m, m, m, n, 1.0 / (double)n);
+    moment.symmetric = 1;
+    return st(launch_gemm_f64(moment, s));
 }
 
 size_t mla_conv_top_eig_workspace_bytes(int m, int p) {
@@ -265,7 +268,9 @@ int mla_convert_layer(const double* X, const double* W_K, const double* W_V, con
     MLA_TRY(launch_alpha(w.norms, alpha, n, s));
     // App. D.2: balanced activations, their moment, its leading eigenvectors
     MLA_TRY(launch_balance(w.C, mj, w.C + a, mj, alpha, w.C, n, a, gd, s));
-    MLA_TRY(launch_gemm_f64(gemm_tn(w.C, mj, w.C, mj, w.S, mj, mj, mj, n, 1.0 / (double)n), s));
+    GemmF64 moment = gemm_tn(w.C, mj, w.C, mj, w.S, mj, mj, mj, n, 1.0 / (double)n);
+    moment.symmetric = 1;
+    MLA_TRY(launch_gemm_f64(moment, s));
     int rc = top_eig(w.S, Q0, evals_joint, R_KV, top_ws(w.top, mj, p), info + groups, mj, r_kv, p, iters, s);
     if (rc != MLA_OK) return rc;
     // W^DKV' = R^T [W^DK_NoPE / alpha ; W^DV]

@@ -12,6 +12,8 @@ namespace conv {
 // accumulate: C += instead of C =.
 // partial / partial_doubles: optional scratch; when the tile count alone cannot fill the chip and K is
 // deep, the K range is cut into slices whose products go to the scratch and are summed in a fixed order.
+// symmetric: B is A transposed (M = N, no accumulate); the tiles below the diagonal are written as the mirror image of
+// those above, which has their bits: an entry and its image sum the same products in the same order.
 struct GemmF64 {
     const double* A; long sAm, sAk;
     const double* B; long sBk, sBn;
@@ -21,6 +23,7 @@ struct GemmF64 {
     const double* alpha_dev; int dev_mode;
     int accumulate;
     double* partial; size_t partial_doubles;
+    int symmetric = 0;
 };
 hipError_t launch_gemm_f64(const GemmF64& g, hipStream_t s);
 

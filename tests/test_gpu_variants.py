@@ -245,3 +245,19 @@ def test_cache_append_edges(mla, B, D, d_c, cache):
     assert (np.abs(got[at] - ref[rows]) <= tol[rows]).all()
     got[at] = 7.0
     assert (got == 7.0).all()
+
+
+# ------------------------------------------------------------------ conversion: symmetric products
+
+@pytest.mark.parametrize("n,m", [(1, 2), (17, 127), (40, 128), (33, 129), (300, 300), (64, 1000)])
+def test_joint_moment_mirrored_tiles(n, m):
+    """C^T C / n where only the tiles on and above the diagonal are multiplied: float64 values, and the bits of an
+    entry and its mirror image."""
+    import torch
+    from paper_2502_07864_amd import convert
+    C = np.random.default_rng(n + m).standard_normal((n, m))
+    K, V = (torch.from_numpy(np.ascontiguousarray(a)).cuda() for a in (C[:, :m // 2], C[:, m // 2:]))
+    S, _ = convert.joint_moment(K, V, torch.ones(1, dtype=torch.float64, device="cuda"))
+    S = S.cpu().numpy()
+    assert np.abs(S - C.T @ C / n).max() <= 2 * n * 2.0 ** -53 * (np.abs(C).T @ np.abs(C) / n).max()
+    assert np.array_equal(S, S.T)
