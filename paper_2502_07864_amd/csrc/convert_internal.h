@@ -44,10 +44,9 @@ hipError_t launch_balance(const double* K, int ldk, const double* V, int ldv, co
 // work: jacobi_work_bytes(batch, m) bytes
 size_t jacobi_work_bytes(int batch, int m);
 hipError_t launch_jacobi(double* A, double* evals, double* work, int* info, int batch, int m, int max_sweeps, hipStream_t s);
-// G (p x p, symmetric positive definite) -> lower Cholesky factor in place (blocks above the diagonal
-// are left undefined), X = its inverse (zero above the diagonal); *bad += clamped pivots.
-// tmp: chol_tmp_doubles(p) doubles of scratch.
-inline size_t chol_tmp_doubles(int p) { return 8 + (size_t)64 * p + (size_t)16 * 64 * p; }
+// X = the inverse of the lower Cholesky factor of G (p x p, symmetric positive definite), zero above the diagonal;
+// *bad += clamped pivots; G is overwritten.  tmp: chol_tmp_doubles(p) doubles of scratch.
+inline size_t chol_tmp_doubles(int p) { return 8 + (size_t)64 * p; }
 hipError_t launch_chol_inverse(double* G, double* X, double* tmp, int p, int* bad, hipStream_t s);
 hipError_t launch_symmetrise(double* T, int p, hipStream_t s);
 hipError_t launch_fill_int(int* dst, int value, int count, hipStream_t s);

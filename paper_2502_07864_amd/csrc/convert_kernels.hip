@@ -12,6 +12,8 @@ namespace mla {
 namespace conv {
 namespace {
 
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+
 // ------------------------------------------------------------------ block reductions
 __device__ __forceinline__ double wave_sum(double v) {
 #pragma unroll
@@ -348,7 +350,6 @@ __global__ __launch_bounds__(256) void jb_pair_kernel(double* A, double* __restr
 // grid (column pair Q, row pair P or 32 rows of V, 2: A or V); four wavefronts, one 16 x 16 tile of the result each
 __global__ __launch_bounds__(256) void jb_update_kernel(double* A, double* V, const double* __restrict__ Z, int m, int nbp, int step,
                                                         const WideState* st) {
-    typedef double f64x4 __attribute__((ext_vector_type(4)));
     constexpr int LDT = JP + 1;
     __shared__ double t[JP * LDT], zq[JP * LDT], zp[JP * LDT];
     if (st->done) return;
@@ -414,8 +415,6 @@ __global__ __launch_bounds__(256) void jw_permute_kernel(double* __restrict__ A_
 }
 
 // ------------------------------------------------------------------ Cholesky factor and its inverse
-// Blocked, 64 columns at a time; the matrix products between the blocks run on the matrix-core
-// kernel, the 64 x 64 pieces below in LDS.
 constexpr int NB = 64;
 
 // floor for the pivots: 1e-13 of the largest diagonal entry
@@ -433,145 +432,241 @@ __global__ __launch_bounds__(1024) void max_diag_kernel(const double* __restrict
     }
 }
 
-// Block column k0, step 1: one workgroup factors the nb x nb diagonal block in LDS.
-__global__ __launch_bounds__(256) void chol_diag_kernel(double* G, int p, int k0, int nb,
-                                                        const double* __restrict__ floor_in, int* bad) {
-    __shared__ double D[NB][NB + 1];
-    __shared__ double piv;
-    __shared__ int nbad;
-    const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
-    for (int idx = tid; idx < nb * nb; idx += 256) D[idx / nb][idx % nb] = G[(long)(k0 + idx / nb) * p + k0 + idx % nb];
-    if (tid == 0) nbad = 0;
-    const double floor_v = *floor_in;
-    __syncthreads();
-    for (int j = 0; j < nb; ++j) {
-        if (tid == 0) {
-            double v = D[j][j];
-            if (!(v > floor_v)) { v = floor_v; ++nbad; }
-            v = sqrt(v);
-            D[j][j] = v;
-            piv = v;
-        }
-        __syncthreads();
-        const double inv = 1.0 / piv;
-        for (int i = j + 1 + tid; i < nb; i += 256) D[i][j] *= inv;
-        __syncthreads();
-        for (int i = j + 1 + ty; i < nb; i += 16) {
-            const double lij = D[i][j];
-            for (int k = j + 1 + tx; k <= i; k += 16) D[i][k] -= lij * D[k][j];
-        }
-        __syncthreads();
+// One launch per block column k eliminates it from both halves of [G | I]: tile (i, j) of 64 x 64 with i > k is
+//     j > k:  G_ij -= L_ik L_jk^T,      L_ik = G_ik L_kk^{-T}
+//     j <= k: B_ij -= L_ik X_kj,        X_kj = L_kk^{-1} B_kj      (B starts as I and lives in X)
+// one workgroup each, all products on v_mfma_f64_16x16x4_f64; every workgroup multiplies the L_ik and L_jk or X_kj it
+// needs itself (K = 64: 1 us each), so that nothing is written that another one reads and a column is one launch.  The
+// workgroup of the next diagonal block goes on to factor and invert it: sixteen columns at a time in one wavefront's
+// registers (lane = row, pivots and multipliers by lane reads), the rest of the block on the matrix cores.  What
+// bounds it is that chain, column after column.  As separate kernels (block, panel solve, trailing product; then the
+// inverse row by row with two products each) order 768 took
+// 1330 us, now 300.
+constexpr int CP = 66;                     // row pitch of a block in LDS: 32 lanes that read 16 rows x 2 columns hit 32 units of 8 bytes
+
+// c[t] = rows 16 wave .., columns 16 t .. of P R^T (both 64 x 64, row-major); LOWER: R is zero above its diagonal.
+// Lane l holds row 4 r + l / 16, column l % 16 of a 16 x 16 tile in element r.
+template <bool LOWER>
+__device__ __forceinline__ void block_nt(const double* P, const double* R, int wave, int lane, f64x4 (&c)[4]) {
+    const double* a = P + (16 * wave + (lane & 15)) * CP + (lane >> 4);
+    const double* b = R + (lane & 15) * CP + (lane >> 4);
+#pragma unroll
+    for (int t = 0; t < 4; ++t) c[t] = (f64x4){0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int ks = 0; ks < 16; ++ks) {
+        const double x = a[4 * ks];
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+            if (!LOWER || ks < 4 * (t + 1)) c[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(x, b[16 * t * CP + 4 * ks], c[t], 0, 0, 0);
     }
-    for (int idx = tid; idx < nb * nb; idx += 256) {
-        const int i = idx / nb, k = idx % nb;
-        G[(long)(k0 + i) * p + k0 + k] = k <= i ? D[i][k] : 0.0;
+}
+
+__device__ __forceinline__ void block_put(double* S, int wave, int lane, const f64x4 (&c)[4]) {
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) S[(16 * wave + 4 * r + (lane >> 4)) * CP + 16 * t + (lane & 15)] = c[t][r];
+}
+
+// 64 x 64 block at (r0, c0) of a p x p matrix; rows and columns past the end are zero
+__device__ __forceinline__ void block_get(const double* __restrict__ G, long ld, int r0, int c0, int rows, int cols, int tid, double (&v)[16]) {
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+        const int r = r0 + (tid >> 6) + 4 * q, c = c0 + (tid & 63);
+        v[q] = r < rows && c < cols ? G[(long)r * ld + c] : 0.0;
+    }
+}
+template <bool T>
+__device__ __forceinline__ void block_stage(double* S, int tid, const double (&v)[16]) {
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+        const int r = (tid >> 6) + 4 * q, c = tid & 63;
+        S[T ? c * CP + r : r * CP + c] = v[q];
+    }
+}
+
+__device__ __forceinline__ double read_lane(double v, int lane) {
+    const long u = __double_as_longlong(v);
+    const unsigned lo = __builtin_amdgcn_readlane((int)u, lane), hi = __builtin_amdgcn_readlane((int)(u >> 32), lane);
+    return __longlong_as_double((long)hi << 32 | lo);
+}
+
+// S (64 x 64, its lower half; nb rows and columns of it) = L L^T -> V = L^{-1}.  Four wavefronts; pivots not above
+// floor_v are replaced by it and counted.
+__device__ __forceinline__ void factor_invert(double* S, double* V, double* dinv, int nb, double floor_v, int* bad, int tid) {
+    const int lane = tid & 63, wave = tid >> 6, li = lane & 15, kq = lane >> 4;
+    for (int idx = tid; idx < 64 * CP; idx += 256) {
+        const int r = idx / CP, c = idx % CP;
+        V[idx] = 0.0;
+        if (r >= nb) S[idx] = r == c ? 1.0 : 0.0;        // rows past the end: identity
+    }
+    __syncthreads();
+    int nbad = 0;
+    for (int sb = 0; sb < 4; ++sb) {
+        const int s0 = sb * 16;
+        if (wave == 0) {
+            double a[16], mine = 0.0;
+#pragma unroll
+            for (int c = 0; c < 16; ++c) a[c] = S[lane * CP + s0 + c];
+#pragma unroll
+            for (int j = 0; j < 16; ++j) {
+                double d = read_lane(a[j], s0 + j);
+                if (s0 + j < nb && !(d > floor_v)) { d = floor_v; ++nbad; }
+                const double inv = rsqrt(d);
+                if (lane == s0 + j) { a[j] = d; mine = inv; }
+                a[j] *= inv;
+#pragma unroll
+                for (int k = j + 1; k < 16; ++k) a[k] -= a[j] * read_lane(a[j], s0 + k);
+            }
+#pragma unroll
+            for (int c = 0; c < 16; ++c) S[lane * CP + s0 + c] = lane >= s0 + c ? a[c] : 0.0;
+            if (lane >= s0 && lane < s0 + 16) dinv[lane] = mine;
+        }
+        __syncthreads();
+        // what is left of the block: 16 x 16 tiles (bi, bj), bi >= bj > sb
+        const int left = 3 - sb;
+        for (int t = wave; t < left * (left + 1) / 2; t += 4) {
+            const int u = t < 1 ? 0 : t < 3 ? 1 : 2, bi = sb + 1 + u, bj = sb + 1 + t - u * (u + 1) / 2;
+            f64x4 c;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) c[r] = S[(16 * bi + 4 * r + kq) * CP + 16 * bj + li];
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks)
+                c = __builtin_amdgcn_mfma_f64_16x16x4f64(-S[(16 * bi + li) * CP + s0 + 4 * ks + kq], S[(16 * bj + li) * CP + s0 + 4 * ks + kq], c, 0, 0, 0);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) S[(16 * bi + 4 * r + kq) * CP + 16 * bj + li] = c[r];
+        }
+        __syncthreads();
     }
     if (tid == 0 && nbad) atomicAdd(bad, nbad);
-}
-
-// Step 2: workgroup w solves 64 rows of the panel below the factored block: L_rows = A_rows L_kk^{-T}.
-__global__ __launch_bounds__(256) void chol_solve_kernel(double* G, int p, int k0, int nb) {
-    __shared__ double D[NB][NB + 1], P[NB][NB + 1];
-    const int tid = threadIdx.x;
-    for (int idx = tid; idx < nb * nb; idx += 256) D[idx / nb][idx % nb] = G[(long)(k0 + idx / nb) * p + k0 + idx % nb];
-    const int r0 = k0 + nb + blockIdx.x * NB;
-    const int nr = min(NB, p - r0);
-    for (int idx = tid; idx < nr * nb; idx += 256) P[idx / nb][idx % nb] = G[(long)(r0 + idx / nb) * p + k0 + idx % nb];
-    __syncthreads();
-    if (tid < nr) {
-        for (int c = 0; c < nb; ++c) {
-            double v = P[tid][c];
-            for (int u = 0; u < c; ++u) v -= P[tid][u] * D[c][u];
-            P[tid][c] = v / D[c][c];
+    // inverse: diagonal 16 x 16 blocks, a wavefront each, lane = column ...
+    if (lane < 16) {
+        const double* L = S + 16 * wave * (CP + 1);
+        double x[16];
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            double v = r == lane ? 1.0 : 0.0;
+#pragma unroll
+            for (int k = 0; k < r; ++k) v -= L[r * CP + k] * x[k];
+            x[r] = v * dinv[16 * wave + r];
+            V[(16 * wave + r) * CP + 16 * wave + lane] = x[r];
         }
     }
     __syncthreads();
-    for (int idx = tid; idx < nr * nb; idx += 256) G[(long)(r0 + idx / nb) * p + k0 + idx % nb] = P[idx / nb][idx % nb];
-}
-
-// The same two steps for full 64 x 64 blocks with the rows held in registers (every loop unrolled, so all
-// register indices are static).  Factorisation: one wavefront, lane i owns row i; per step every lane
-// publishes its entry of column j in LDS and reads the others back as broadcasts, so a step is one LDS
-// round trip and no barrier (a single wavefront's LDS accesses complete in order).  Entries above
-// the diagonal are scratch.
-__global__ __launch_bounds__(64) void chol_diag64_kernel(double* G, int p, int k0,
-                                                         const double* __restrict__ floor_in, int* bad) {
-    __shared__ double col[NB];
-    const int i = threadIdx.x;
-    double* mine = G + (long)(k0 + i) * p + k0;
-    double row[NB];
+    // ... then X_ij = -X_ii sum_k L_ik X_kj, one distance from the diagonal after the other
+    for (int dist = 1; dist < 4; ++dist) {
+        const int bi = dist + wave, bj = wave;
+        if (bi < 4) {
+            f64x4 m = {0.0, 0.0, 0.0, 0.0}, c = {0.0, 0.0, 0.0, 0.0};
+            for (int k = bj; k < bi; ++k)
 #pragma unroll
-    for (int k = 0; k < NB; ++k) row[k] = mine[k];
-    const double floor_v = *floor_in;
-    int nbad = 0;
+                for (int ks = 0; ks < 4; ++ks)
+                    m = __builtin_amdgcn_mfma_f64_16x16x4f64(S[(16 * bi + li) * CP + 16 * k + 4 * ks + kq], V[(16 * k + 4 * ks + kq) * CP + 16 * bj + li], m, 0, 0, 0);
 #pragma unroll
-    for (int j = 0; j < NB; ++j) {
-        col[i] = row[j];
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        double d = col[j];
-        if (!(d > floor_v)) { d = floor_v; ++nbad; }
-        const double piv = sqrt(d), inv = 1.0 / piv;
-        row[j] = i == j ? piv : row[j] * inv;
+            for (int ks = 0; ks < 4; ++ks)      // (a result tile lies in the lanes as the right operand does)
+                c = __builtin_amdgcn_mfma_f64_16x16x4f64(-V[(16 * bi + li) * CP + 16 * bi + 4 * ks + kq], m[ks], c, 0, 0, 0);
 #pragma unroll
-        for (int k = j + 1; k < NB; ++k) row[k] -= row[j] * (col[k] * inv);   // col[k] * inv: the bits lane k stores
-        __builtin_amdgcn_wave_barrier();
-    }
-#pragma unroll
-    for (int k = 0; k < NB; ++k) mine[k] = k <= i ? row[k] : 0.0;
-    if (i == 0 && nbad) atomicAdd(bad, nbad);
-}
-
-// Panel solve: one wavefront per 64 rows, lane = row, the factored block (and the reciprocals of its
-// diagonal) broadcast from LDS.
-__global__ __launch_bounds__(64) void chol_solve64_kernel(double* G, int p, int k0) {
-    __shared__ double D[NB][NB], Dinv[NB];
-    const int tid = threadIdx.x;
-#pragma unroll 8
-    for (int idx = tid; idx < NB * NB; idx += 64) D[idx / NB][idx % NB] = G[(long)(k0 + idx / NB) * p + k0 + idx % NB];
-    __syncthreads();
-    Dinv[tid] = 1.0 / D[tid][tid];
-    __syncthreads();
-    const int r = k0 + NB + blockIdx.x * NB + tid;
-    if (r >= p) return;
-    double* mine = G + (long)r * p + k0;
-    double x[NB];
-#pragma unroll
-    for (int c = 0; c < NB; ++c) x[c] = mine[c];
-#pragma unroll
-    for (int c = 0; c < NB; ++c) {
-        double v0 = x[c], v1 = 0.0;                    // two chains: the sums are short but dependent
-#pragma unroll
-        for (int u = 0; u + 1 < c; u += 2) { v0 -= x[u] * D[c][u]; v1 -= x[u + 1] * D[c][u + 1]; }
-        if (c & 1) v0 -= x[c - 1] * D[c][c - 1];
-        x[c] = (v0 + v1) * Dinv[c];
-    }
-#pragma unroll
-    for (int c = 0; c < NB; ++c) mine[c] = x[c];
-}
-
-// X_jj = L_jj^{-1} for every diagonal block j (one workgroup each); thread c solves L x = e_c.
-__global__ __launch_bounds__(64) void tri_inverse_diag_kernel(const double* __restrict__ G, double* __restrict__ X, int p) {
-    __shared__ double D[NB][NB + 1], Y[NB][NB + 1];
-    const int k0 = blockIdx.x * NB, nb = min(NB, p - k0), c = threadIdx.x;
-    for (int idx = c; idx < nb * nb; idx += 64) D[idx / nb][idx % nb] = G[(long)(k0 + idx / nb) * p + k0 + idx % nb];
-    __syncthreads();
-    if (c < nb) {
-        for (int i = 0; i < c; ++i) Y[i][c] = 0.0;
-        Y[c][c] = 1.0 / D[c][c];
-        for (int i = c + 1; i < nb; ++i) {
-            double a = 0.0;
-            for (int k = c; k < i; ++k) a += D[i][k] * Y[k][c];
-            Y[i][c] = -a / D[i][i];
+            for (int r = 0; r < 4; ++r) V[(16 * bi + 4 * r + kq) * CP + 16 * bj + li] = c[r];
         }
+        __syncthreads();
     }
-    __syncthreads();
-    for (int idx = c; idx < nb * nb; idx += 64) X[(long)(k0 + idx / nb) * p + k0 + idx % nb] = Y[idx / nb][idx % nb];
 }
 
-__global__ __launch_bounds__(256) void fill_double_kernel(double* dst, double value, long count) {
-    for (long i = (long)blockIdx.x * 256 + threadIdx.x; i < count; i += (long)gridDim.x * 256) dst[i] = value;
+// Linv: p rows of 64, the inverse of diagonal block k in rows 64 k ..  k = -1: only the first diagonal block.
+__global__ __launch_bounds__(256) void chol_step_kernel(double* G, double* X, double* Linv, int p, int k,
+                                                        const double* __restrict__ floor_in, int* bad) {
+    __shared__ double A[NB * CP], Z[NB * CP], D[NB * CP], dinv[NB];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    int i = 0, j = 0;
+    if (k < 0) {
+        double v[16];
+        block_get(G, p, 0, 0, p, p, tid, v);
+        block_stage<false>(A, tid, v);
+    } else {
+        // tile of the lower triangle, row by row from row k + 1
+        const int t = (k + 1) * (k + 2) / 2 + (int)blockIdx.x;
+        i = (int)((sqrtf(8.0f * t + 1.0f) - 1.0f) * 0.5f);
+        while (i * (i + 1) / 2 > t) --i;
+        while ((i + 1) * (i + 2) / 2 <= t) ++i;
+        j = t - i * (i + 1) / 2;
+        const bool in_G = j > k;
+        double* C = in_G ? G : X;
+        double vd[16], va[16], vz[16];
+        block_get(Linv, NB, k * NB, 0, p, NB, tid, vd);
+        block_get(G, p, i * NB, k * NB, p, p, tid, va);
+        if (in_G) block_get(G, p, j * NB, k * NB, p, p, tid, vz);
+        else if (j < k) block_get(X, p, k * NB, j * NB, p, p, tid, vz);
+        else {
+#pragma unroll
+            for (int q = 0; q < 16; ++q) vz[q] = (tid >> 6) + 4 * q == (tid & 63) ? 1.0 : 0.0;
+        }
+        f64x4 c[4], u[4];
+        const int row = i * NB + 16 * wave + (lane >> 4), col = j * NB + (lane & 15);
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                c[t][r] = j != k && row + 4 * r < p && col + 16 * t < p ? C[(long)(row + 4 * r) * p + col + 16 * t] : 0.0;
+        block_stage<false>(D, tid, vd);
+        block_stage<false>(A, tid, va);
+        if (in_G) block_stage<false>(Z, tid, vz);
+        else block_stage<true>(Z, tid, vz);
+        __syncthreads();
+        f64x4 l[4];
+        block_nt<true>(A, D, wave, lane, l);          // L_ik
+        block_nt<true>(Z, D, wave, lane, u);          // L_jk, or X_kj transposed
+        __syncthreads();
+        block_put(A, wave, lane, l);
+        block_put(Z, wave, lane, u);
+        __syncthreads();
+        block_nt<false>(A, Z, wave, lane, u);
+        const bool next = i == k + 1 && j == k + 1;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            c[t] -= u[t];
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                if (!next && row + 4 * r < p && col + 16 * t < p) C[(long)(row + 4 * r) * p + col + 16 * t] = c[t][r];
+        }
+        if (!next) return;
+        __syncthreads();
+        block_put(A, wave, lane, c);
+    }
+    __syncthreads();
+    const int k1 = k + 1, nb = min(NB, p - k1 * NB);
+    factor_invert(A, D, dinv, nb, *floor_in, bad, tid);
+    for (int idx = tid; idx < nb * NB; idx += 256) Linv[(long)k1 * NB * NB + idx] = D[(idx >> 6) * CP + (idx & 63)];
+}
+
+// X = L^{-1}, its block rows scaled: X_ij = L_ii^{-1} B_ij below the diagonal, L_ii^{-1} on it, zero above
+__global__ __launch_bounds__(256) void chol_finish_kernel(double* X, const double* __restrict__ Linv, int p) {
+    __shared__ double Z[NB * CP], D[NB * CP];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int i = blockIdx.y, j = blockIdx.x;
+    double v[16];
+    if (i > j) {
+        double z[16];
+        block_get(Linv, NB, i * NB, 0, p, NB, tid, v);
+        block_get(X, p, i * NB, j * NB, p, p, tid, z);
+        block_stage<false>(D, tid, v);
+        block_stage<true>(Z, tid, z);
+        __syncthreads();
+        f64x4 c[4];
+        block_nt<false>(D, Z, wave, lane, c);
+        const int row = i * NB + 16 * wave + (lane >> 4), col = j * NB + (lane & 15);
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                if (row + 4 * r < p && col + 16 * t < p) X[(long)(row + 4 * r) * p + col + 16 * t] = c[t][r];
+        return;
+    }
+    if (i == j) block_get(Linv, NB, i * NB, 0, p, NB, tid, v);
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+        const int r = i * NB + (tid >> 6) + 4 * q, c = j * NB + (tid & 63);
+        if (r < p && c < p) X[(long)r * p + c] = i == j ? v[q] : 0.0;
+    }
 }
 
 __global__ __launch_bounds__(256) void symmetrise_kernel(double* T, int p) {
@@ -727,40 +822,18 @@ hipError_t launch_jacobi(double* A, double* evals, double* work, int* info, int 
 
 hipError_t launch_chol_inverse(double* G, double* X, double* tmp, int p, int* bad, hipStream_t s) {
     double* floor_v = tmp;                 // one double
-    double* T = tmp + 8;                   // 64 x p
-    double* part = T + (size_t)NB * p;     // K slices of the products below: 16 x 64 x p
-    hipError_t e;
+    double* Linv = tmp + 8;                // p x 64
     max_diag_kernel<<<1, 1024, 0, s>>>(G, p, floor_v);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
+    hipError_t e = hipGetLastError();
     const int nblk = (p + NB - 1) / NB;
-    // right-looking factorisation: panel, then trailing block  A22 -= L21 L21^T
-    for (int k = 0; k < nblk; ++k) {
-        const int k0 = k * NB, nb = std::min(NB, p - k0), rest = p - k0 - nb;
-        if (nb == NB) chol_diag64_kernel<<<1, 64, 0, s>>>(G, p, k0, floor_v, bad);
-        else chol_diag_kernel<<<1, 256, 0, s>>>(G, p, k0, nb, floor_v, bad);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-        if (rest > 0) {
-            if (nb == NB) chol_solve64_kernel<<<(rest + NB - 1) / NB, 64, 0, s>>>(G, p, k0);
-            else chol_solve_kernel<<<(rest + NB - 1) / NB, 256, 0, s>>>(G, p, k0, nb);
-            if ((e = hipGetLastError()) != hipSuccess) return e;
-            const double* L21 = G + (long)(k0 + nb) * p + k0;
-            GemmF64 g{L21, p, 1, L21, 1, p, G + (long)(k0 + nb) * (p + 1), p, rest, rest, nb, -1.0, nullptr, 0, 1, nullptr, 0};
-            if ((e = launch_gemm_f64(g, s)) != hipSuccess) return e;
-        }
+    for (int k = -1; k < nblk - 1 && e == hipSuccess; ++k) {
+        const int tiles = k < 0 ? 1 : nblk * (nblk + 1) / 2 - (k + 1) * (k + 2) / 2;
+        chol_step_kernel<<<tiles, 256, 0, s>>>(G, X, Linv, p, k, floor_v, bad);
+        e = hipGetLastError();
     }
-    // X = L^{-1}: diagonal blocks, then block row i:  X[i, :i] = -X_ii (L[i, :i] X[:i, :i])
-    fill_double_kernel<<<grid_for((long)p * p), 256, 0, s>>>(X, 0.0, (long)p * p);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    tri_inverse_diag_kernel<<<nblk, 64, 0, s>>>(G, X, p);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    for (int i = 1; i < nblk; ++i) {
-        const int i0 = i * NB, nb = std::min(NB, p - i0);
-        GemmF64 t{G + (long)i0 * p, p, 1, X, p, 1, T, p, nb, i0, i0, 1.0, nullptr, 0, 0, part, (size_t)16 * NB * p};
-        if ((e = launch_gemm_f64(t, s)) != hipSuccess) return e;
-        GemmF64 x{X + (long)i0 * (p + 1), p, 1, T, p, 1, X + (long)i0 * p, p, nb, i0, nb, -1.0, nullptr, 0, 0, nullptr, 0};
-        if ((e = launch_gemm_f64(x, s)) != hipSuccess) return e;
-    }
-    return hipSuccess;
+    if (e != hipSuccess) return e;
+    chol_finish_kernel<<<dim3(nblk, nblk), 256, 0, s>>>(X, Linv, p);
+    return hipGetLastError();
 }
 
 hipError_t launch_symmetrise(double* T, int p, hipStream_t s) {

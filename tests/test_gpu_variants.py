@@ -261,3 +261,23 @@ def test_joint_moment_mirrored_tiles(n, m):
     S = S.cpu().numpy()
     assert np.abs(S - C.T @ C / n).max() <= 2 * n * 2.0 ** -53 * (np.abs(C).T @ np.abs(C) / n).max()
     assert np.array_equal(S, S.T)
+
+
+# ------------------------------------------------------------------ conversion: Cholesky factor and inverse
+
+@pytest.mark.parametrize("p", [2, 5, 16, 17, 63, 64, 65, 100, 128, 191, 300])
+def test_cholesky_qr_block_edges(mla, p):
+    """Block widths around the 64-column blocks and their 16-column parts.  With S = I every step keeps the span of the
+    start block: R is an orthonormal basis of it to fp64 rounding of the sums of 2p products (the start block's
+    condition number is about (sqrt 2 + 1)^2 = 6: 64 leaves that and the ten or so products room)."""
+    import torch
+    from paper_2502_07864_amd import convert
+    m = 2 * p + 3
+    Q0 = np.random.default_rng(p).standard_normal((m, p))
+    evals, R, info = convert.top_eig(torch.eye(m, dtype=torch.float64, device="cuda"), torch.from_numpy(Q0).cuda(), p, 1)
+    evals, R, info = evals.cpu().numpy(), R.cpu().numpy(), info.cpu().numpy()
+    tol = 64 * m * 2.0 ** -53
+    assert info[0] == 0
+    assert np.abs(evals - 1.0).max() <= tol
+    assert np.abs(R.T @ R - np.eye(p)).max() <= tol
+    assert np.abs(Q0 - R @ (R.T @ Q0)).max() <= tol * np.abs(Q0).max()
