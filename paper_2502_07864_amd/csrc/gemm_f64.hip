@@ -45,6 +45,34 @@ __device__ __forceinline__ void fetch(const double* __restrict__ P, long s_mn, l
     }
 }
 
+// The same without a branch around each load (eight branches a step; C^T C of 4096 x 8128 5.40 -> 5.08 ms, an iteration
+// of 768 columns 2.22 -> 2.16): rows past the end re-read the last one (what they give is not stored), a
+// k past the end re-reads the step's first (zeroed before it is staged).  off: the thread's element offsets
+// from the tile's corner, of which `there` rows or columns are inside; left: k's from the corner on that are inside.
+template <bool K_CONTIG>
+__device__ __forceinline__ void offsets(long s_mn, long s_k, int there, int tid, unsigned (&off)[EPT]) {
+#pragma unroll
+    for (int i = 0; i < EPT; ++i)
+        off[i] = K_CONTIG ? (unsigned)(min((tid >> 4) + (THREADS / 16) * i, there - 1) * s_mn) : (unsigned)min(tid & 127, there - 1);
+}
+template <bool K_CONTIG>
+__device__ __forceinline__ int k_of(int tid, int i) { return K_CONTIG ? tid & 15 : (tid >> 7) + (THREADS / 128) * i; }
+
+template <bool K_CONTIG>
+__device__ __forceinline__ void fetch_near(const double* __restrict__ corner, long s_k, int left, int tid,
+                                           const unsigned (&off)[EPT], double (&r)[EPT]) {
+#pragma unroll
+    for (int i = 0; i < EPT; ++i) {
+        const int k = k_of<K_CONTIG>(tid, i);
+        r[i] = corner[off[i] + (unsigned)((k < left ? k : 0) * (K_CONTIG ? 1 : (int)s_k))];
+    }
+}
+template <bool K_CONTIG>
+__device__ __forceinline__ void zero_past(int left, int tid, double (&r)[EPT]) {
+#pragma unroll
+    for (int i = 0; i < EPT; ++i) r[i] = k_of<K_CONTIG>(tid, i) < left ? r[i] : 0.0;
+}
+
 template <bool K_CONTIG>
 __device__ __forceinline__ void stage(double* S, int tid, const double (&r)[EPT]) {
 #pragma unroll
@@ -57,8 +85,8 @@ __device__ __forceinline__ void stage(double* S, int tid, const double (&r)[EPT]
 // first tile of row tm when each row of tiles starts at the diagonal
 __host__ __device__ __forceinline__ int row_start(int tm, int tiles_n) { return tm * tiles_n - tm * (tm - 1) / 2; }
 
-template <bool A_KC, bool B_KC>
-__global__ __launch_bounds__(THREADS, 2) void gemm_f64_kernel(GemmF64 g, int tiles_n, int tiles, int splits, int kt_per) {
+template <bool A_KC, bool B_KC, bool NEAR>
+__global__ __launch_bounds__(THREADS, 4) void gemm_f64_kernel(GemmF64 g, int tiles_n, int tiles, int splits, int kt_per) {
     extern __shared__ double lds[];            // As[2][BK][LD], Bs[2][BK][LD]
     double* As = lds;
     double* Bs = lds + 2 * STAGE;
@@ -93,19 +121,36 @@ __global__ __launch_bounds__(THREADS, 2) void gemm_f64_kernel(GemmF64 g, int til
         for (int j = 0; j < 4; ++j) acc[i][j] = (f64x4){0.0, 0.0, 0.0, 0.0};
 
     double ra[EPT], rb[EPT];
-    fetch<A_KC>(g.A, g.sAm, g.sAk, m0, kt0 * BK, g.M, g.K, tid, ra);
-    fetch<B_KC>(g.B, g.sBn, g.sBk, n0, kt0 * BK, g.N, g.K, tid, rb);
-    stage<A_KC>(As, tid, ra);
-    stage<B_KC>(Bs, tid, rb);
+    unsigned oa[EPT], ob[EPT];
+    offsets<A_KC>(g.sAm, g.sAk, g.M - m0, tid, oa);
+    offsets<B_KC>(g.sBn, g.sBk, g.N - n0, tid, ob);
+    const double* A = g.A + (long)m0 * g.sAm;
+    const double* B = g.B + (long)n0 * g.sBn;
+    auto load = [&](int kt) {
+        if (NEAR) {
+            fetch_near<A_KC>(A + (long)kt * BK * g.sAk, g.sAk, g.K - kt * BK, tid, oa, ra);
+            fetch_near<B_KC>(B + (long)kt * BK * g.sBk, g.sBk, g.K - kt * BK, tid, ob, rb);
+        } else {
+            fetch<A_KC>(g.A, g.sAm, g.sAk, m0, kt * BK, g.M, g.K, tid, ra);
+            fetch<B_KC>(g.B, g.sBn, g.sBk, n0, kt * BK, g.N, g.K, tid, rb);
+        }
+    };
+    auto put = [&](int kt, int buf) {
+        if (NEAR && (kt + 1) * BK > g.K) {
+            zero_past<A_KC>(g.K - kt * BK, tid, ra);
+            zero_past<B_KC>(g.K - kt * BK, tid, rb);
+        }
+        stage<A_KC>(As + buf * STAGE, tid, ra);
+        stage<B_KC>(Bs + buf * STAGE, tid, rb);
+    };
+    load(kt0);
+    put(kt0, 0);
     __syncthreads();
 
     for (int kt = kt0; kt < kt1; ++kt) {
         const int buf = (kt - kt0) & 1;
         const bool more = kt + 1 < kt1;
-        if (more) {
-            fetch<A_KC>(g.A, g.sAm, g.sAk, m0, (kt + 1) * BK, g.M, g.K, tid, ra);
-            fetch<B_KC>(g.B, g.sBn, g.sBk, n0, (kt + 1) * BK, g.N, g.K, tid, rb);
-        }
+        if (more) load(kt + 1);
         const double* a_s = As + buf * STAGE + wm + li;
         const double* b_s = Bs + buf * STAGE + wn + li;
 #pragma unroll
@@ -122,10 +167,7 @@ __global__ __launch_bounds__(THREADS, 2) void gemm_f64_kernel(GemmF64 g, int til
                 for (int j = 0; j < 4; ++j)
                     acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i], b[j], acc[i][j], 0, 0, 0);
         }
-        if (more) {
-            stage<A_KC>(As + (buf ^ 1) * STAGE, tid, ra);
-            stage<B_KC>(Bs + (buf ^ 1) * STAGE, tid, rb);
-        }
+        if (more) put(kt + 1, buf ^ 1);
         __syncthreads();
     }
 
@@ -179,10 +221,10 @@ __global__ __launch_bounds__(256) void gemm_f64_reduce_kernel(GemmF64 g, int spl
     }
 }
 
-template <bool A_KC, bool B_KC>
+template <bool A_KC, bool B_KC, bool NEAR>
 hipError_t run(const GemmF64& g, hipStream_t s) {
     constexpr size_t lds_bytes = 4 * STAGE * sizeof(double);
-    hipError_t e0 = allow_dynamic_lds(reinterpret_cast<const void*>(&gemm_f64_kernel<A_KC, B_KC>), (int)lds_bytes);
+    hipError_t e0 = allow_dynamic_lds(reinterpret_cast<const void*>(&gemm_f64_kernel<A_KC, B_KC, NEAR>), (int)lds_bytes);
     if (e0 != hipSuccess) return e0;
     const int tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
     const int tiles = g.symmetric ? row_start(tiles_m, tiles_n) : tiles_m * tiles_n;
@@ -207,7 +249,7 @@ hipError_t run(const GemmF64& g, hipStream_t s) {
     splits = (nk + kt_per - 1) / kt_per;                 // no empty slice
     const int total = tiles * splits;
     const int grid = ((total + 7) / 8) * 8;
-    gemm_f64_kernel<A_KC, B_KC><<<grid, THREADS, lds_bytes, s>>>(g, tiles_n, tiles, splits, kt_per);
+    gemm_f64_kernel<A_KC, B_KC, NEAR><<<grid, THREADS, lds_bytes, s>>>(g, tiles_n, tiles, splits, kt_per);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || splits == 1) return e;
     const long cells = (long)g.M * g.N;
@@ -222,10 +264,13 @@ hipError_t launch_gemm_f64(const GemmF64& g, hipStream_t s) {
     if (g.symmetric && (g.M != g.N || g.accumulate)) return hipErrorInvalidValue;
     const bool a_kc = g.sAk == 1, b_kc = g.sBk == 1;
     if ((!a_kc && g.sAm != 1) || (!b_kc && g.sBn != 1)) return hipErrorInvalidValue;
-    if (a_kc && b_kc) return run<true, true>(g, s);
-    if (a_kc) return run<true, false>(g, s);
-    if (b_kc) return run<false, true>(g, s);
-    return run<false, false>(g, s);
+    // offsets within a tile are 32-bit while no stride is above 2^22 elements
+    const long far = 1L << 22;
+    const bool near = g.sAm <= far && g.sAk <= far && g.sBn <= far && g.sBk <= far;
+    if (a_kc && b_kc) return near ? run<true, true, true>(g, s) : run<true, true, false>(g, s);
+    if (a_kc) return near ? run<true, false, true>(g, s) : run<true, false, false>(g, s);
+    if (b_kc) return near ? run<false, true, true>(g, s) : run<false, true, false>(g, s);
+    return near ? run<false, false, true>(g, s) : run<false, false, false>(g, s);
 }
 
 }  // namespace conv

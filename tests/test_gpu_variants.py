@@ -281,3 +281,17 @@ def test_cholesky_qr_block_edges(mla, p):
     assert np.abs(evals - 1.0).max() <= tol
     assert np.abs(R.T @ R - np.eye(p)).max() <= tol
     assert np.abs(Q0 - R @ (R.T @ Q0)).max() <= tol * np.abs(Q0).max()
+
+
+# ------------------------------------------------------------------ conversion: matrix product, steps of K and strides
+
+@pytest.mark.parametrize("n,m,D", [(1, 1, 1), (3, 129, 15), (128, 128, 16), (129, 5, 17), (200, 260, 47), (2, 3, (1 << 22) + 4)])
+def test_fp64_product_edges(mla, n, m, D):
+    """X W^T around the 128-row tiles and the 16-deep steps (a last step of 1, 15, 16 columns), and with rows further
+    apart than 32-bit offsets within a tile reach: sums of D products in another order."""
+    import torch
+    from paper_2502_07864_amd import convert
+    rng = np.random.default_rng(n + m)
+    X, W = rng.standard_normal((n, D)), rng.standard_normal((m, D))
+    Y = convert.project(torch.from_numpy(X).cuda(), torch.from_numpy(W).cuda()).cpu().numpy()
+    assert (np.abs(Y - X @ W.T) <= 2 * min(D, 1 << 12) * 2.0 ** -53 * (np.abs(X) @ np.abs(W).T)).all()
