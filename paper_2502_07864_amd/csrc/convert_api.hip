@@ -58,7 +58,9 @@ int chol_qr(const double* Y, double* out, const TopWs& w, int m, int p, int* bad
     if (e != hipSuccess) return MLA_ERR_HIP;
     e = launch_chol_inverse(w.G, w.X, w.tmp, p, bad, s);
     if (e != hipSuccess) return MLA_ERR_HIP;
-    return st(launch_gemm_f64(gemm_nt(Y, p, w.X, p, out, p, m, p, p, 1.0), s));
+    GemmF64 q = gemm_nt(Y, p, w.X, p, out, p, m, p, p, 1.0);
+    q.lower = 1;
+    return st(launch_gemm_f64(q, s));
 }
 
 int top_eig(const double* S, const double* Q0, double* evals, double* R, const TopWs& w, int* info,

@@ -24,6 +24,7 @@ struct GemmF64 {
     int accumulate;
     double* partial; size_t partial_doubles;
     int symmetric = 0;
+    int lower = 0;          // B(k, n) = 0 for k > n (B is the transpose of a lower triangle): those k are left out; no partial
 };
 hipError_t launch_gemm_f64(const GemmF64& g, hipStream_t s);
 

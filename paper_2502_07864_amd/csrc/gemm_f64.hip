@@ -94,7 +94,7 @@ __global__ __launch_bounds__(THREADS, 4) void gemm_f64_kernel(GemmF64 g, int til
     // consecutive tiles (same rows of A) share an XCD: workgroup ids 8 apart run on one XCD
     const int total = tiles * splits;
     const int per = (total + 7) / 8;
-    const int item = (int)(blockIdx.x % 8) * per + (int)(blockIdx.x / 8);
+    const int item = g.lower ? (int)blockIdx.x : (int)(blockIdx.x % 8) * per + (int)(blockIdx.x / 8);
     if (item >= total) return;
     const int tile = item % tiles, z = item / tiles;     // z: slice of the K range
     int tm = tile / tiles_n, tn = tile % tiles_n;
@@ -104,9 +104,14 @@ __global__ __launch_bounds__(THREADS, 4) void gemm_f64_kernel(GemmF64 g, int til
         while (tile >= row_start(tm + 1, tiles_n)) ++tm;
         tn = tm + tile - row_start(tm, tiles_n);
     }
+    if (g.lower) {                             // deepest columns first; Y X^T of 8128 x 768, 23 a layer: 87.1 -> 86.3 ms a layer
+        const int tiles_m = tiles / tiles_n;
+        tm = tile % tiles_m;
+        tn = tiles_n - 1 - tile / tiles_m;
+    }
     const int m0 = tm * BM, n0 = tn * BN;
     const int nk_all = (g.K + BK - 1) / BK;
-    const int kt0 = z * kt_per, kt1 = min(nk_all, kt0 + kt_per);
+    const int kt0 = z * kt_per, kt1 = min(g.lower ? min(nk_all, (n0 + BN) / BK) : nk_all, kt0 + kt_per);
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = (wave >> 1) * 32, wn = (wave & 1) * 64;
@@ -262,6 +267,7 @@ hipError_t run(const GemmF64& g, hipStream_t s) {
 hipError_t launch_gemm_f64(const GemmF64& g, hipStream_t s) {
     if (g.M <= 0 || g.N <= 0 || g.K <= 0) return hipErrorInvalidValue;
     if (g.symmetric && (g.M != g.N || g.accumulate)) return hipErrorInvalidValue;
+    if (g.lower && (g.partial || g.symmetric)) return hipErrorInvalidValue;
     const bool a_kc = g.sAk == 1, b_kc = g.sBk == 1;
     if ((!a_kc && g.sAm != 1) || (!b_kc && g.sBn != 1)) return hipErrorInvalidValue;
     // offsets within a tile are 32-bit while no stride is above 2^22 elements
