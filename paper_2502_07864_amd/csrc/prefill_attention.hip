@@ -247,6 +247,25 @@ __global__ __launch_bounds__(MF_THREADS, WPE) void prefill_attention_kernel(Deco
                     if (rb * 16 + i >= seen) x[rb][hi][i] = -INFINITY;
         }
     };
+    // Tokens of the last tile that come after every query of this workgroup: their values become zeros, so that
+    // whatever they are (their weights are zeros, but 0 * inf is not) stays out.  Tokens past the sequence's end
+    // are zeros already.
+    auto drop_late_values = [&](int t) {
+        const int there = row1 - t * TILE_ROWS;
+        for (int u = tid; u < V_B / 16; u += MF_THREADS) {
+            LDS_AS u32x4* at = (LDS_AS u32x4*)(lds + slot_of(t) + K_B + u * 16);
+            const int first = 4 * ((u >> 4) & 3);        // key of the unit's first value; the fifth is 16 further on
+            u32x4 v = *at;
+#pragma unroll
+            for (int d = 0; d < 4; ++d) {
+                const int key = first + (d >> 1) * 16 + (d & 1) * 2;
+                v[d] = key + 1 < there ? v[d] : key < there ? v[d] & 0xFFFFu : 0u;
+            }
+            *at = v;
+        }
+        __syncthreads();
+    };
+    const bool late_values = row1 < L && row1 % TILE_ROWS != 0;
     auto full_tile = [&](int t) { return (t + 1) * TILE_ROWS <= causal_from && rows_valid(t) == TILE_ROWS; };
 
     // ---- one step: S^T of the next tile (QK), the weights of this one from its scores x, the normaliser and the
@@ -356,6 +375,7 @@ __global__ __launch_bounds__(MF_THREADS, WPE) void prefill_attention_kernel(Deco
         // for the maxima accumulates too, and neither result is used)
         auto one = [&](int t, const Scores& x, Scores& y) {
             stage(t);
+            if (late_values && t + 1 == t1) drop_late_values(t);
             step(std::true_type{}, lds + slot_of(t), x, y);
             if (t + 1 < t1) look_at(y, t + 1);
         };

@@ -185,6 +185,31 @@ def test_prefill_skips_bad_pages(mla):
         assert max_abs_rel(widen_gpu(got)[b, t], ref) <= TOL["bf16"]
 
 
+@pytest.mark.parametrize("T,L,late", [(200, 210, 150), (200, 225, 153), (129, 129, 128), (300, 331, 169), (256, 260, 132), (140, 191, 180)])
+def test_prefill_later_tokens_stay_out_whatever_they_hold(mla, T, L, late):
+    """A token behind every query of a group of 128, in the group's last tile of 32 (and in later ones), whose latent
+    row is infinite or NaN: the group's outputs keep the bits that they have without it."""
+    import torch
+    w = synth.make_workload("prefill", B=1, H=2, d_head=128, d_c=256, d_rope=64, seq_lens=[L], io_dtype="bf16",
+                            cache_dtype="bf16", free_frac=0.1, seed=103)
+    d = DeviceWorkload(w)
+    qn, qr = (to_torch(a, "bf16") for a in synth.multi_queries(w, T))
+
+    def run(pool):
+        return mla.prefill_mha(qn, qr, d.W_UK, d.W_UV, pool, d.page_table, d.seq_lens, w.softmax_scale, return_lse=True)
+
+    clean, clean_lse = run(d.pool)
+    assert late >= L - T + 128                                   # behind what the first 128 queries see
+    for value in (float("inf"), float("nan")):
+        pool = d.pool.clone()
+        for t in range(late, L, 7):
+            pool[int(w.page_table[0, t // 64]), t % 64, t % 256] = value
+        out, lse = run(pool)
+        torch.cuda.synchronize()
+        assert torch.isfinite(out[:, :128]).all() and torch.equal(out[:, :128], clean[:, :128])
+        assert torch.equal(lse[:, :128], clean_lse[:, :128])
+
+
 # ------------------------------------------------------------------ conversion: eigensolver
 
 @pytest.mark.parametrize("batch,m", [(1, 129), (2, 144), (1, 160), (1, 161), (1, 175), (1, 300), (5, 2), (3, 3), (4, 17), (2, 96), (2, 127), (1, 128)])
