@@ -171,8 +171,8 @@ size_t mla_decode_workspace_bytes(int B, int H, int d_c, int num_splits);
  * page_size 64, d_rope 64 and d_c in {256, 512} (32 heads per workgroup; more
  * heads go to further workgroups), and, with the uniform partition, for BF16
  * caches of those shapes whose page_size is another multiple of 16 (there the
- * softmax weights enter the value contraction as two bf16 terms); everything
- * else runs on the portable scalar-FMA kernel.
+ * softmax stays in fp32 and its weights enter the value contraction as three
+ * bf16 terms); everything else runs on the portable scalar-FMA kernels.
  */
 int mla_decode_paged(const void* q_abs, const void* q_rope,
                      const void* kv_cache, const float* kv_scale,

@@ -40,12 +40,15 @@
 // each, looked up by themselves, and which of the two a load belongs to is a constant of the load
 // (16 rows are CPR / 4 groups of 64 chunks), so a tile costs one more scalar look-up and nothing per
 // lane.  Chunks begin at multiples of the page size, tiles are counted from the chunk's first row.
-// These sizes ran on the scalar-FMA kernel, which holds the weights in fp32; here a weight is two
-// bf16 terms (the rounded weight and the rounded remainder: 2^-17 of the weight is lost) and the value
-// contraction runs once per term on the same operand, which the accumulating wavefronts have the
-// time for.  8 sequences of 1500 .. 4096 rows in 16-row pages, 32 heads, d_c = 512, 16 chunks:
-// absorb + decode + merge + projection 133.2 us on the scalar-FMA kernel (121.8 of them its own), 28.0 us
-// here, the same distance from 64-bit results (2-norm, 3.1e-3 at the output).
+// These sizes ran on the scalar-FMA kernel, which holds weights, normaliser and log-sum-exp in fp32, and so does
+// this form: exponentials and logarithms by the fp32 functions (the other form's run on the hardware's, in log2
+// units, and its normaliser sums rounded weights), and a weight enters the value contraction as three bf16 terms
+// (the rounded weight, the rounded remainder, what is left: 8 bits each, exact), once per term on the same
+// operand.  Two terms and log2 units gave log-sum-exps four to five times as far from 64-bit ones as the scalar
+// kernel's (2e-6 and 4e-7 on 2 .. 33 rows, 5e-6 and 1e-6 on 100 .. 1000 with sharper scores) and saved 2.5 us of
+// the step below.  8 sequences of 1500 .. 4096 rows in 16-row pages, 32 heads, d_c = 512, 16 chunks: absorb +
+// decode + merge + projection 133.2 us on the scalar-FMA kernel (121.8 of them its own), 30.2 us here, the same
+// distance from 64-bit results (2-norm, 3.1e-3 at the output).
 #include "mla_internal.h"
 #include "mfma_tile.h"
 #include <type_traits>
@@ -62,7 +65,7 @@ typedef __attribute__((ext_vector_type(8))) short s16x8;
 // BAL = true: the balanced partition (one-dimensional grid; a workgroup owns an equal share of the
 // pages of all sequences and works through the segments of sequences inside it, exactly as in
 // decode_mfma.hip, whose plan and slot numbering this is).
-// PAGED = true: pages of 16 k rows, k other than 4 (uniform partition only); weights in two terms.
+// PAGED = true: pages of 16 k rows, k other than 4 (uniform partition only); fp32 softmax, weights in three terms.
 template <int D_C, bool PROBE, bool BAL, bool PAGED = false>
 __global__ __launch_bounds__(ST_THREADS, 1) void decode_stream_kernel(DecodeParams p)
 {
@@ -279,11 +282,14 @@ __global__ __launch_bounds__(ST_THREADS, 1) void decode_stream_kernel(DecodePara
 
     // ---- running softmax state (consumers); this lane's head = column n of the D tiles, its rows
     // 4g .. 4g+3 of each of the tile's two 16-row blocks
-    float m_run = -INFINITY;   // reference of the exponentials, scaled scores in log2 units
+    float m_run = -INFINITY;   // reference of the exponentials (a scaled score)
     float l_run = 0.f;         // this lane's share of the running sum (its 8 rows per tile)
 #pragma unroll
     for (int i = 0; i < NST; ++i) st[i] = (f32x4){0.f, 0.f, 0.f, 0.f};
-    const float sc = p.scale * LOG2E;
+    // scores are held in log2 units, with PAGED in natural ones
+    const float sc = PAGED ? p.scale : p.scale * LOG2E;
+    constexpr float UNIT = PAGED ? LN2 : 1.f;      // one log2 unit
+    auto exp_of = [](float x) { return PAGED ? expf(x) : fast_exp2(x); };
     // score A operand: row 16 rb + n, chunk 4 ks + g
     const uint32_t a_row = (uint32_t)(n * ROWB);
     const uint32_t a_key = (uint32_t)swz_key(n);
@@ -306,7 +312,7 @@ __global__ __launch_bounds__(ST_THREADS, 1) void decode_stream_kernel(DecodePara
         return fmaxf(v, __shfl_xor(v, 32));
     };
 
-    // S^T = K . Q^T for 16-row block rb of a tile x 16 heads, scaled to log2 units, rows outside the
+    // S^T = K . Q^T for 16-row block rb of a tile x 16 heads, scaled, rows outside the
     // chunk or beyond the query row's own position at -inf
     auto score_block = [&](LDS_AS unsigned char* tile, int rb, int t, int n_valid, f32x4& x) {
         f32x4 sacc = (f32x4){0.f, 0.f, 0.f, 0.f};
@@ -321,9 +327,20 @@ __global__ __launch_bounds__(ST_THREADS, 1) void decode_stream_kernel(DecodePara
 #pragma unroll
             for (int ks = s0 + SG; ks < s0 + 2 * SG && ks < NKS; ++ks) rd(ks);
             __builtin_amdgcn_sched_barrier(0);
+            // (PAGED: the sums of 32 products are added by the vector pipe, which rounds to nearest, a group at a time;
+            // one chain through the accumulator operand left scores about 40 twice to three times as far from 64-bit ones)
+            f32x4 part[SG];
 #pragma unroll
-            for (int ks = s0; ks < s0 + SG && ks < NKS; ++ks)
-                sacc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0[ks], __builtin_bit_cast(bf16x8, st[ks]), sacc, 0, 0, 0);
+            for (int ks = s0; ks < s0 + SG && ks < NKS; ++ks) {
+                if constexpr (PAGED) part[ks - s0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0[ks], __builtin_bit_cast(bf16x8, st[ks]), (f32x4){0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+                else                 sacc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0[ks], __builtin_bit_cast(bf16x8, st[ks]), sacc, 0, 0, 0);
+            }
+            if constexpr (PAGED) {
+#pragma unroll
+                for (int j = 1; j < SG; ++j)
+                    if (s0 + j < NKS) part[0] += part[j];
+                sacc += part[0];
+            }
             __builtin_amdgcn_sched_barrier(0);
         }
         x = sacc * sc;
@@ -352,26 +369,29 @@ __global__ __launch_bounds__(ST_THREADS, 1) void decode_stream_kernel(DecodePara
         float e[8];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            e[i] = fast_exp2(x0[i] - m_use);
-            e[4 + i] = fast_exp2(x1[i] - m_use);
+            e[i] = exp_of(x0[i] - m_use);
+            e[4 + i] = exp_of(x1[i] - m_use);
         }
         const uint32_t p01 = pack_bf16x2(e[0], e[1]), p23 = pack_bf16x2(e[2], e[3]);
         const uint32_t p45 = pack_bf16x2(e[4], e[5]), p67 = pack_bf16x2(e[6], e[7]);
-        l_run += ((bf16_bits_to_f32(p01 & 0xFFFFu) + bf16_bits_to_f32(p01 >> 16)) +
-                  (bf16_bits_to_f32(p23 & 0xFFFFu) + bf16_bits_to_f32(p23 >> 16))) +
-                 ((bf16_bits_to_f32(p45 & 0xFFFFu) + bf16_bits_to_f32(p45 >> 16)) +
-                  (bf16_bits_to_f32(p67 & 0xFFFFu) + bf16_bits_to_f32(p67 >> 16)));
         const bf16x8 pb = __builtin_bit_cast(bf16x8, (u32x4){p01, p23, p45, p67});
-        bf16x8 pr = pb;                        // PAGED: second term of the weights
+        bf16x8 pr = pb, ps = pb;               // PAGED: second and third term of the weights
         if constexpr (PAGED) {
-            const uint32_t hi2[4] = {p01, p23, p45, p67};
-            u32x4 r;
+            l_run += ((e[0] + e[1]) + (e[2] + e[3])) + ((e[4] + e[5]) + (e[6] + e[7]));
+            u32x4 hi2 = (u32x4){p01, p23, p45, p67}, r, q;
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                r[j] = pack_bf16x2(e[2 * j] - bf16_bits_to_f32(hi2[j] & 0xFFFFu), e[2 * j + 1] - bf16_bits_to_f32(hi2[j] >> 16));
-                l_run += bf16_bits_to_f32(r[j] & 0xFFFFu) + bf16_bits_to_f32(r[j] >> 16);
+                const float r0 = e[2 * j] - bf16_bits_to_f32(hi2[j] & 0xFFFFu), r1 = e[2 * j + 1] - bf16_bits_to_f32(hi2[j] >> 16);
+                r[j] = pack_bf16x2(r0, r1);
+                q[j] = pack_bf16x2(r0 - bf16_bits_to_f32(r[j] & 0xFFFFu), r1 - bf16_bits_to_f32(r[j] >> 16));
             }
             pr = __builtin_bit_cast(bf16x8, r);
+            ps = __builtin_bit_cast(bf16x8, q);
+        } else {
+            l_run += ((bf16_bits_to_f32(p01 & 0xFFFFu) + bf16_bits_to_f32(p01 >> 16)) +
+                      (bf16_bits_to_f32(p23 & 0xFFFFu) + bf16_bits_to_f32(p23 >> 16))) +
+                     ((bf16_bits_to_f32(p45 & 0xFFFFu) + bf16_bits_to_f32(p45 >> 16)) +
+                      (bf16_bits_to_f32(p67 & 0xFFFFu) + bf16_bits_to_f32(p67 >> 16)));
         }
         s16x4 lo[WCT], hi[WCT];
         auto rd = [&](int i) {
@@ -392,8 +412,10 @@ __global__ __launch_bounds__(ST_THREADS, 1) void decode_stream_kernel(DecodePara
             for (int i = c0; i < c0 + VG && i < WCT; ++i) {
                 const s16x8 va = __builtin_shufflevector(lo[i], hi[i], 0, 1, 2, 3, 4, 5, 6, 7);
                 st[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, va), pb, st[i], 0, 0, 0);
-                if constexpr (PAGED)
+                if constexpr (PAGED) {
                     st[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, va), pr, st[i], 0, 0, 0);
+                    st[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, va), ps, st[i], 0, 0, 0);
+                }
             }
             __builtin_amdgcn_sched_barrier(0);
         }
@@ -496,13 +518,13 @@ __global__ __launch_bounds__(ST_THREADS, 1) void decode_stream_kernel(DecodePara
                         const float tmax = over_groups(lmax);
                         if (m_run == -INFINITY) m_run = tmax;
                     }
-                    jumped |= lmax > m_run + FAST_GAP;
+                    jumped |= lmax > m_run + FAST_GAP * UNIT;
                 } else {
                     const float tmax = over_groups(lmax);
                     if (m_run == -INFINITY) m_run = tmax;  // nothing accumulated yet: nothing to rescale
-                    if (__any(tmax > m_run + RESCALE_GAP)) {
-                        const float m_new = tmax > m_run + RESCALE_GAP ? tmax : m_run;
-                        const float alpha = fast_exp2(m_run - m_new);   // 1 for the lanes that keep their reference
+                    if (__any(tmax > m_run + RESCALE_GAP * UNIT)) {
+                        const float m_new = tmax > m_run + RESCALE_GAP * UNIT ? tmax : m_run;
+                        const float alpha = exp_of(m_run - m_new);   // 1 for the lanes that keep their reference
                         l_run *= alpha;
 #pragma unroll
                         for (int i = 0; i < WCT; ++i) st[i] *= alpha;
@@ -563,7 +585,7 @@ __global__ __launch_bounds__(ST_THREADS, 1) void decode_stream_kernel(DecodePara
             if (j * RPI + rl < nrow)
                 __builtin_nontemporal_store(v[j], reinterpret_cast<u32x4*>(dst0 + (size_t)(j * RPI) * row_stride));
         if (ch == 0 && head < HL && g == 0)
-            *lse_at(hb + head) = lt > 0.f ? (m_run + __builtin_amdgcn_logf(lt)) * LN2 : -INFINITY;
+            *lse_at(hb + head) = !(lt > 0.f) ? -INFINITY : PAGED ? m_run + logf(lt) : (m_run + __builtin_amdgcn_logf(lt)) * LN2;
     }
     };  // run_segment
 
