@@ -673,11 +673,13 @@ hipError_t launch_decode_stream(const DecodeParams& p, dim3 grid, hipStream_t s)
 }
 
 // bf16 caches whose pages are 16, 32, 48, 80, ... rows: every such size that the matrix-core tiles can be
-// cut along, whatever the chunk length (the scalar-FMA kernel takes what is left: other multiples)
+// cut along, whatever the chunk length.  The scalar-FMA kernels take what is left: other multiples, and tensors
+// that are not on 16 bytes (a view into a larger buffer), which direct-to-LDS loads are not documented to take.
 bool decode_stream_paged_supported(const DecodeParams& p, mla_dtype io, mla_dtype cache)
 {
     return io == MLA_BF16 && cache == MLA_BF16 && p.page_size % 16 == 0 && p.page_size != 64 && p.d_rope == 64 &&
            (p.d_c == 256 || p.d_c == 512) &&
+           ((reinterpret_cast<uintptr_t>(p.kv) | reinterpret_cast<uintptr_t>(p.q_abs) | reinterpret_cast<uintptr_t>(p.q_rope)) & 15u) == 0 &&
            ((long long)p.B * p.num_splits + 7) / 8 * 8 * ((p.H + 31) / 32) <= 0x7FFFFFFFLL;
 }
 

@@ -98,6 +98,27 @@ def test_multi_token_other_page_sizes(mla, page, T):
     check_multi(mla, paged_workload(page, lens=[0, 1, 2, 16, 33, 47, 320], H=28, seed=72), T, 2, fused_tail=True)
 
 
+@pytest.mark.parametrize("moved", ["kv", "q", "rope"])
+def test_other_page_sizes_off_16_bytes_run_on_the_scalar_kernel(mla, moved):
+    """A cache or queries that begin 8 bytes into a buffer: the bits of the scalar-FMA kernel, which needs no more."""
+    import torch
+    w = paged_workload(16, 256, 8, lens=[0, 5, 40, 333], seed=75)
+    d = DeviceWorkload(w)
+    q = gpu_q_abs(mla, d)
+
+    def shifted(t):
+        buf = torch.empty(t.numel() + 4, dtype=t.dtype, device="cuda")
+        view = buf[4:].view(t.shape)
+        view.copy_(t)
+        assert view.is_contiguous() and view.data_ptr() % 16 == 8
+        return view
+
+    kv, qa, qr = (shifted(t) if moved == name else t for name, t in (("kv", d.pool), ("q", q), ("rope", d.q_rope)))
+    (o, lse), (ref, ref_lse) = (mla.decode_paged(a, b, c, d.page_table, d.seq_lens, w.softmax_scale, num_splits=2, return_lse=True, flags=flags)
+                                for a, b, c, flags in ((qa, qr, kv, 0), (q, d.q_rope, d.pool, PORTABLE)))
+    assert torch.equal(o, ref) and torch.equal(lse, ref_lse)
+
+
 def test_other_page_sizes_keep_refusing_the_balanced_partition(mla):
     w = paged_workload(16, lens=[64, 64])
     d = DeviceWorkload(w)
