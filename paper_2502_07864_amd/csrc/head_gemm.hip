@@ -107,7 +107,8 @@ __global__ __launch_bounds__(HG_THREADS) void head_gemm_kernel(const void* X, co
 // each in 128-bit loads, and a workgroup's whole share of a 512-row pass (32 KB at the launcher's choice of
 // NT) is requested before the batch rows are staged, so a call waits for memory once where the kernel above,
 // one column and eight loads of 4 bytes per lane, waited four times.  Sums over the rows of a wavefront by
-// lane exchanges, over the wavefronts through LDS.  BT: batch rows per workgroup (1, 4 or 16).
+// lane exchanges, over the wavefronts through LDS.  BT: batch rows per workgroup (1, 4 or 16).  For deep products:
+// where the line lies is said at the launcher's rule.
 // One fp32 row of 32 heads: absorb 128 -> 512 and projection 512 -> 128 (8.4 MB of W each) 6.6 -> 4.3 and
 // 8.7 -> 5.3 us.
 template <int NT, int BT>
@@ -315,7 +316,18 @@ hipError_t launch_head_gemm(const void* X, const void* W, void* Y, int B, int H,
     const long per_col_tile = (long)H * ((B + HG_BT - 1) / HG_BT);
     int nt = HG_NT;
     while (nt > 16 && (long)((N + nt - 1) / nt) * per_col_tile < 256) nt /= 2;
-    if (io == MLA_F32 && N % 4 == 0 && reinterpret_cast<uintptr_t>(W) % 16 == 0) {     // rows of W on 16 bytes: four columns per load
+    // fp32, rows of W on 16 bytes: four columns per load, where the sums over a workgroup's lanes (an exchange per batch
+    // row and column) are paid for by a deep enough product.  us, one column per lane -> four, back to back in a graph:
+    // 1 row, 32 heads, 128 -> 512: 6.1 -> 4.0, 64 -> 512: 4.5 -> 3.9, 16 -> 2048: 6.4 -> 6.7; 4 rows, 128 -> 512: 6.4 -> 5.1,
+    // 64 -> 512: 4.7 -> 4.8, 4 heads 4.4 -> 4.6; 3 rows, 128 -> 576 (more than a workgroup per CU): 8 heads 4.6 -> 5.3.
+    // 16-row form (its sums take the registers of more than one workgroup per CU): 64 rows, 512 -> 128: 34.4 -> 24.4,
+    // 5 rows 11.7 -> 14.0, 8 rows, 1024 -> 64: 19.8 -> 21.1; 64 rows, 128 -> 512: 21.5 -> 36.3; 256 rows, 512 -> 128
+    // (1024 workgroups): 74.4 -> 110.
+    const bool one_round = (long long)((N + nt - 1) / nt) * per_col_tile <= 256;
+    const bool wide = B == 1 ? K >= 64
+                    : B <= 4 ? K >= 256 || (K >= 128 && (long long)H * N >= 8192 && one_round)
+                             : B >= 12 && K >= HG_KC && (long long)K * B >= HG_KC * HG_BT && one_round;
+    if (io == MLA_F32 && wide && N % 4 == 0 && reinterpret_cast<uintptr_t>(W) % 16 == 0) {
         const float *x = static_cast<const float*>(X), *w = static_cast<const float*>(W);
         float* y = static_cast<float*>(Y);
         if (nt == 64) return launch_f32<64>(x, w, y, B, H, K, N, s);

@@ -148,10 +148,12 @@ def test_scalar_decode_many_chunks_take_four_heads_per_workgroup(mla):
 
 
 @pytest.mark.parametrize("B,H,K,N", [(1, 32, 512, 128), (1, 2, 1, 4), (2, 3, 33, 36), (4, 40, 513, 64), (5, 2, 1030, 72),
-                                     (17, 3, 100, 260), (3, 2, 64, 130), (70, 9, 128, 512)])
+                                     (17, 3, 100, 260), (3, 2, 64, 130), (70, 9, 128, 512), (1, 3, 63, 64), (1, 3, 64, 68), (4, 2, 127, 64),
+                                     (2, 5, 128, 20), (3, 16, 128, 512), (3, 16, 127, 512), (15, 2, 512, 64), (16, 2, 511, 64), (16, 2, 512, 68), (33, 3, 700, 132), (64, 64, 512, 128)])
 def test_fp32_projection_shapes(mla, B, H, K, N):
-    """1, 4 and 16 batch rows per workgroup, k remainders, columns that do not fill a tile, N % 4 != 0 (the
-    kernel of single columns), and W off its 16 bytes (the same kernel): fp32 sums of K products."""
+    """1, 4 and 16 batch rows per workgroup on both sides of the rule (depth, rows, workgroups), k remainders, columns
+    that do not fill a tile, N % 4 != 0 (the kernel of single columns), and W off its 16 bytes (the same kernel):
+    fp32 sums of K products."""
     import torch
     r = synth.stream(83, B * 1000 + N)
     x = torch.from_numpy(synth.normal(r, (B, H, K))).cuda()
