@@ -1,8 +1,8 @@
 // Portable (scalar-FMA, fp32) kernels: paged decode for every supported dtype
 // pair and shape, the split-KV merge, and the page gather test hook.
 //
-// The decode kernel is the library's reference GPU path: it is the only path
-// for fp32 caches and fp32 io and for shapes the matrix-core kernels do not
+// The decode kernels here and in decode_tiles.hip (whichever is the faster) are the library's reference GPU
+// path: the only one for fp32 caches and fp32 io and for shapes the matrix-core kernels do not
 // cover.  One workgroup handles (chunk, sequence, group of HG heads); its four
 // wavefronts take the chunk's rows four or eight at a time, in turn, and share nothing
 // until the end: a row lives in the registers of one wavefront, lane l holding
@@ -15,7 +15,7 @@
 //
 // The kernel is bound by latency on a small call (one short sequence) and by the
 // vector pipes on a large one (about 25 instructions per row and head for 17 useful
-// ones).  Its predecessor staged 16 rows at a time in LDS between four workgroup
+// ones).  The tiles stage 16 rows at a time in LDS between four workgroup
 // barriers: one fp32 sequence of 1024 rows, 32 heads, d_c = 512, 16 chunks: 23.5 us on
 // 64 workgroups, 10.1 here; 4 sequences of 2000 rows in 28 chunks: 53.0 and 29.4; 16 bf16 sequences of 8192
 // rows in 63-row pages: 493 and 373; eight fp32 sequences of 4000 rows, every row read eight times from
@@ -508,16 +508,35 @@ __global__ __launch_bounds__(256) void gather_kernel(const uint32_t* kv, const i
 
 }  // namespace
 
-template <typename QT, typename CT>
-static hipError_t launch_portable(const DecodeParams& p, hipStream_t s)
+// Which form takes a call.  Both kernels hold two workgroups per CU, so their times go in rounds of 512 workgroups,
+// whatever the rest; measured on 32 .. 65536 workgroups of 200 rows each, back to back in a graph, us:
+//   rows in registers, 2 heads per workgroup: up to 256 workgroups 22, up to 512 40 (fp32 cache) and 28 (others);
+//     4 heads: up to 256 31, up to 512 40, 768 63, 1024 73, 1536 107, 2048 137, 4096 268, whatever the width (a row
+//     costs a whole wavefront, and is read once per 4 heads); 8 heads leave one wavefront per SIMD and are slower still;
+//   16-row tiles in LDS, 8 heads: fp32, d_c = 64 / 256: up to 256 32 / 44, 512 38 / 54, 1024 72 / 102, 2048 139 / 200;
+//     fp8 38 / 61, 42 / 67, 83 / 131, 162 / 259: a round costs what the width does (fp32 30 us at d_c = 8, 39 at 128, 70
+//     at 384), and 12 us more past 256, the second column of its threads.
+// So the tiles take narrow latent rows with many heads and chunks (32 heads, 8 x 4000 fp32 rows, d_c = 64: 49 us
+// against 95), and the registers wide rows (d_c = 512: 100 against 109) and whatever does not fill the chip (one
+// sequence of 1024 rows, 32 heads, d_c = 64: 11.0 against 14.2).
+enum Form { ROWS_2_HEADS, ROWS_4_HEADS, TILES_8_HEADS };
+
+static Form faster_form(const DecodeParams& p, mla_dtype cache)
 {
-    // Four heads per workgroup read every row eight times for 32 heads (from L2, the groups of a chunk run
-    // side by side); two heads, when four leave CUs without a workgroup: then the call is as long as one
-    // workgroup's rows take (fp32, one sequence of 1024 rows in 16 chunks, 32 heads: 10.1 us with two,
-    // 13.5 with four; 4000 rows in 60 chunks: 28.8 and 21.9; 8 x 4000 rows: 218 and 101).  Eight heads leave
-    // one wavefront per SIMD: 151 us there, 22.9 on the one short sequence.
+    const long long n = (long long)p.B * p.num_splits, n8 = (n + 7) / 8 * 8;
+    const long long w2 = n8 * ((p.H + 1) / 2), w4 = n8 * ((p.H + 3) / 4), w8 = n * ((p.H + 7) / 8);
+    const double two = w2 <= 256 ? 22.0 : w2 > 512 ? INFINITY : cache == MLA_F32 ? 40.0 : 28.0;
+    const double four = 33.0 * (double)((w4 - 1) / 512) + ((w4 - 1) % 512 < 256 ? 31.0 : 40.0);
+    const double round = (cache == MLA_F32 ? 28.0 + p.d_c / 10.0 : cache == MLA_BF16 ? 30.0 + p.d_c / 9.5 : 33.0 + p.d_c / 8.0) +
+                         (p.d_c > 256 ? 12.0 : 0.0);
+    const double tiles = w8 <= 256 ? 0.95 * round : round * (double)((w8 + 511) / 512);
+    return tiles < two && tiles < four ? TILES_8_HEADS : two < four ? ROWS_2_HEADS : ROWS_4_HEADS;
+}
+
+template <typename QT, typename CT>
+static hipError_t launch_portable(const DecodeParams& p, int hg, hipStream_t s)
+{
     const long long n = ((long long)p.B * p.num_splits + 7) / 8 * 8;
-    const int hg = n * ((p.H + 3) / 4) >= 256 ? 4 : 2;
     const long long wgs = n * ((p.H + hg - 1) / hg);
     const long long gx = wgs < (1 << 20) ? wgs : 1 << 20, gy = (wgs + gx - 1) / gx;   // a grid dimension holds 2^32 threads
     if (gy > 65535) return hipErrorInvalidValue;
@@ -529,11 +548,14 @@ static hipError_t launch_portable(const DecodeParams& p, hipStream_t s)
 
 hipError_t launch_decode_portable(const DecodeParams& p, mla_dtype io, mla_dtype cache, hipStream_t s)
 {
-    if (io == MLA_F32 && cache == MLA_F32) return launch_portable<float, float>(p, s);
-    if (io == MLA_F32 && cache == MLA_BF16) return launch_portable<float, bf16_tag>(p, s);
-    if (io == MLA_F32 && cache == MLA_FP8_E4M3) return launch_portable<float, fp8_tag>(p, s);
-    if (io == MLA_BF16 && cache == MLA_BF16) return launch_portable<bf16_tag, bf16_tag>(p, s);
-    if (io == MLA_BF16 && cache == MLA_FP8_E4M3) return launch_portable<bf16_tag, fp8_tag>(p, s);
+    const Form form = faster_form(p, cache);
+    if (form == TILES_8_HEADS) return launch_decode_tiles(p, io, cache, s);
+    const int hg = form == ROWS_2_HEADS ? 2 : 4;
+    if (io == MLA_F32 && cache == MLA_F32) return launch_portable<float, float>(p, hg, s);
+    if (io == MLA_F32 && cache == MLA_BF16) return launch_portable<float, bf16_tag>(p, hg, s);
+    if (io == MLA_F32 && cache == MLA_FP8_E4M3) return launch_portable<float, fp8_tag>(p, hg, s);
+    if (io == MLA_BF16 && cache == MLA_BF16) return launch_portable<bf16_tag, bf16_tag>(p, hg, s);
+    if (io == MLA_BF16 && cache == MLA_FP8_E4M3) return launch_portable<bf16_tag, fp8_tag>(p, hg, s);
     return hipErrorInvalidValue;
 }
 

@@ -219,6 +219,8 @@ __device__ __forceinline__ float e4m3_to_f32(uint32_t code)
 // ---- launchers (each returns hipGetLastError() of its launch) --------------
 
 hipError_t launch_decode_portable(const DecodeParams& p, mla_dtype io, mla_dtype cache, hipStream_t s);
+// the same results from 16-row tiles in LDS (launch_decode_portable passes it the calls it is better at)
+hipError_t launch_decode_tiles(const DecodeParams& p, mla_dtype io, mla_dtype cache, hipStream_t s);
 bool       decode_mfma_supported(const DecodeParams& p, mla_dtype io, mla_dtype cache);
 hipError_t launch_decode_mfma(const DecodeParams& p, mla_dtype cache, hipStream_t s, bool balanced = false);
 // uniform chunks of at most 32 tiles, bf16 caches: the kernel with separate requesting and consuming

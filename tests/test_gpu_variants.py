@@ -131,10 +131,13 @@ def test_other_page_sizes_keep_refusing_the_balanced_partition(mla):
 @pytest.mark.parametrize("io,cache,d_c,d_rope,page,H,splits", [
     ("f32", "f32", 512, 64, 64, 32, 4), ("f32", "f32", 8, 8, 1, 1, 1), ("f32", "f32", 264, 16, 7, 3, 2),
     ("f32", "bf16", 256, 0, 5, 5, 3), ("f32", "fp8_e4m3", 40, 64, 3, 33, 2), ("bf16", "fp8_e4m3", 512, 64, 16, 28, 5),
-    ("bf16", "bf16", 384, 64, 64, 66, 2), ("bf16", "bf16", 512, 32, 13, 2, 40)])
+    ("bf16", "bf16", 384, 64, 64, 66, 2), ("bf16", "bf16", 512, 32, 13, 2, 40),
+    ("f32", "f32", 8, 0, 5, 8, 8), ("f32", "bf16", 64, 64, 13, 12, 16), ("bf16", "bf16", 256, 64, 63, 32, 4), ("bf16", "fp8_e4m3", 192, 64, 7, 40, 8),
+    ("f32", "f32", 128, 64, 64, 9, 16), ("f32", "fp8_e4m3", 8, 8, 1, 17, 64)])
 def test_scalar_decode_shapes(mla, io, cache, d_c, d_rope, page, H, splits):
-    """Rows per wavefront batch (4 and 8) and per workgroup (16 and 32) on both sides, empty and one-row
-    sequences, columns that fill neither, one or both groups of 256, page sizes that cut every batch."""
+    """Rows in registers (few workgroups, wide rows) and 16-row tiles in LDS (many, narrow): rows per wavefront batch
+    (4 and 8), per workgroup (16 and 32) and per tile on both sides, empty and one-row sequences, columns that fill
+    neither, one or both groups of 256, head groups that are not full, page sizes that cut every batch."""
     lens = [0, 1, 3, 4, 5, 8, 9, 31, 32, 33, 65, 200]
     w = synth.make_workload("scalar", B=len(lens), H=H, d_head=16, d_c=d_c, d_rope=d_rope, seq_lens=lens, io_dtype=io,
                             cache_dtype=cache, page_size=page, free_frac=0.1, seed=81)
