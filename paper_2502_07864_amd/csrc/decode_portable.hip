@@ -422,8 +422,9 @@ __global__ __launch_bounds__(128) void merge_kernel(MergeParams p)
 // columns).  Lane s owns the log-sum-exp of chunk s; every lane streams one float4 per chunk with
 // the loads of up to 16 chunks in flight.  PLAN = false: uniform partition.
 // PLAN = true: the chunks the balanced partition's plan names for the sequence, any number of
-// them, 64 at a time.
-template <bool OUT_BF16, bool PLAN>
+// them, 64 at a time.  MANY: 65 to 256 chunks of the uniform partition, weights by expf (these calls ran on the
+// general kernel, which has them so).
+template <bool OUT_BF16, bool PLAN, bool MANY>
 __global__ __launch_bounds__(256) void merge_wave_kernel(MergeParams p)
 {
     const int lane = threadIdx.x & 63;
@@ -451,11 +452,11 @@ __global__ __launch_bounds__(256) void merge_wave_kernel(MergeParams p)
 #pragma unroll
     for (int i = 0; i < BATCH; ++i) v[i] = load_part4<OUT_BF16>(p.o_part, row(i));
 
-    const ChunkWeights cw = span_weights(p.lse_part, c, ls0, lane);
+    const ChunkWeights cw = span_weights<MANY>(p.lse_part, c, ls0, lane);
 
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
     for (int blk = 0; blk < S; blk += 64) {
-        const float wt = chunk_weight(cw, blk ? span_lse(p.lse_part, c, blk, lane) : ls0);
+        const float wt = chunk_weight<MANY>(cw, blk ? span_lse(p.lse_part, c, blk, lane) : ls0);
         for (int s0 = 0; s0 < min(64, S - blk); s0 += BATCH) {
             if (blk + s0 > 0) {
 #pragma unroll
@@ -565,11 +566,13 @@ hipError_t launch_merge(const MergeParams& p, mla_dtype io, hipStream_t s)
         const int waves = p.B * p.H * (p.d_c / 256);
         dim3 grid((waves + 3) / 4), block(256);
         if (io == MLA_BF16) {
-            if (p.plan) merge_wave_kernel<true, true><<<grid, block, 0, s>>>(p);
-            else        merge_wave_kernel<true, false><<<grid, block, 0, s>>>(p);
+            if (p.plan)                 merge_wave_kernel<true, true, false><<<grid, block, 0, s>>>(p);
+            else if (p.num_splits > 64) merge_wave_kernel<true, false, true><<<grid, block, 0, s>>>(p);
+            else                        merge_wave_kernel<true, false, false><<<grid, block, 0, s>>>(p);
         } else {
-            if (p.plan) merge_wave_kernel<false, true><<<grid, block, 0, s>>>(p);
-            else        merge_wave_kernel<false, false><<<grid, block, 0, s>>>(p);
+            if (p.plan)                 merge_wave_kernel<false, true, false><<<grid, block, 0, s>>>(p);
+            else if (p.num_splits > 64) merge_wave_kernel<false, false, true><<<grid, block, 0, s>>>(p);
+            else                        merge_wave_kernel<false, false, false><<<grid, block, 0, s>>>(p);
         }
         return hipGetLastError();
     }

@@ -224,7 +224,8 @@ __global__ __launch_bounds__(FT_THREADS) void merge_out_proj_kernel(MergeParams 
 // projection as two kernels) 15.0 and 7.1.
 constexpr int FEW_MAXS = 256;                     // chunks: 16 groups
 
-template <int D_C, int NS>
+// MANY: 65 to FEW_MAXS chunks, weights by expf as in the stand-alone merge.
+template <int D_C, int NS, bool MANY>
 __global__ __launch_bounds__(FT_THREADS) void merge_out_proj_few_kernel(MergeParams p, const uint16_t* W_UV, uint16_t* out)
 {
     constexpr int CB = D_C / 256;                 // blocks of 256 latent columns
@@ -242,7 +243,8 @@ __global__ __launch_bounds__(FT_THREADS) void merge_out_proj_few_kernel(MergePar
     const ChunkSpan c{part_index(b, h, 0, p.H, p.num_splits), 1, p.num_splits};
     const int tasks = (c.S + BATCH - 1) / BATCH * CB;   // task = (group of 16 chunks, block of columns)
 
-    float lsb[FEW_MAXS / 64];                     // lane l: log-sum-exp of chunks l, 64 + l, ..
+    constexpr int NLS = MANY ? FEW_MAXS / 64 : 1;
+    float lsb[NLS];                               // lane l: log-sum-exp of chunks l, 64 + l, ..
     u32x2 v[BATCH];
     auto load_rows = [&](int task) {              // rows past the last chunk re-read it (weight zero)
 #pragma unroll
@@ -251,7 +253,7 @@ __global__ __launch_bounds__(FT_THREADS) void merge_out_proj_few_kernel(MergePar
     };
     if (wave < tasks) {
 #pragma unroll
-        for (int k = 0; k < FEW_MAXS / 64; ++k) lsb[k] = k * 64 < c.S ? span_lse(p.lse_part, c, k * 64, lane) : -INFINITY;
+        for (int k = 0; k < NLS; ++k) lsb[k] = k * 64 < c.S ? span_lse(p.lse_part, c, k * 64, lane) : -INFINITY;
         load_rows(wave);
     }
     const int piece = tid % CC, k0 = tid / CC;
@@ -265,11 +267,14 @@ __global__ __launch_bounds__(FT_THREADS) void merge_out_proj_few_kernel(MergePar
 
     ChunkWeights cw{};
     if (wave < tasks) {
-        cw = c.S <= 64 ? chunk_weights(lsb[0]) : chunk_weights(lsb);
+        if constexpr (MANY) cw = chunk_weights(lsb);
+        else                cw = chunk_weights(lsb[0]);
         for (int task = wave; task < tasks; task += FT_WAVES) {
             if (task != wave) load_rows(task);
             const int s0 = task / CB * BATCH;
-            const float wt = chunk_weight(cw, s0 < 64 ? lsb[0] : s0 < 128 ? lsb[1] : s0 < 192 ? lsb[2] : lsb[3]);
+            float ls = lsb[0];
+            if constexpr (MANY) ls = s0 < 64 ? lsb[0] : s0 < 128 ? lsb[1] : s0 < 192 ? lsb[2] : lsb[3];
+            const float wt = chunk_weight<MANY>(cw, ls);
             f32x4 a = (f32x4){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int i = 0; i < BATCH; ++i) {
@@ -331,14 +336,14 @@ __global__ __launch_bounds__(FT_THREADS) void merge_out_proj_few_kernel(MergePar
     }
 }
 
-template <int D_C>
+template <int D_C, bool MANY>
 void launch_few(const MergeParams& p, const uint16_t* W, uint16_t* o, int ns, hipStream_t s)
 {
     const dim3 grid(p.H, p.B, ns), block(FT_THREADS);
-    if (ns == 8)      merge_out_proj_few_kernel<D_C, 8><<<grid, block, 0, s>>>(p, W, o);
-    else if (ns == 4) merge_out_proj_few_kernel<D_C, 4><<<grid, block, 0, s>>>(p, W, o);
-    else if (ns == 2) merge_out_proj_few_kernel<D_C, 2><<<grid, block, 0, s>>>(p, W, o);
-    else              merge_out_proj_few_kernel<D_C, 1><<<grid, block, 0, s>>>(p, W, o);
+    if (ns == 8)      merge_out_proj_few_kernel<D_C, 8, MANY><<<grid, block, 0, s>>>(p, W, o);
+    else if (ns == 4) merge_out_proj_few_kernel<D_C, 4, MANY><<<grid, block, 0, s>>>(p, W, o);
+    else if (ns == 2) merge_out_proj_few_kernel<D_C, 2, MANY><<<grid, block, 0, s>>>(p, W, o);
+    else              merge_out_proj_few_kernel<D_C, 1, MANY><<<grid, block, 0, s>>>(p, W, o);
 }
 
 }  // namespace
@@ -365,8 +370,10 @@ hipError_t launch_merge_out_proj(const MergeParams& p, const void* W_UV, void* o
     int ns = 1;
     while (ns < 8 && (long)p.H * p.B * ns * 2 <= 256) ns *= 2;
     if (!p.plan && p.num_splits > 16 && (long)p.H * p.B <= 256) {
-        if (p.d_c == 512) launch_few<512>(p, W, o, ns, s);
-        else              launch_few<256>(p, W, o, ns, s);
+        if (p.d_c == 512 && p.num_splits > 64) launch_few<512, true>(p, W, o, ns, s);
+        else if (p.d_c == 512)                 launch_few<512, false>(p, W, o, ns, s);
+        else if (p.num_splits > 64)            launch_few<256, true>(p, W, o, ns, s);
+        else                                   launch_few<256, false>(p, W, o, ns, s);
         return hipGetLastError();
     }
     if (p.d_c == 512 && p.plan)  merge_out_proj_kernel<512, true><<<grid, block, 0, s>>>(p, W, o, BG);

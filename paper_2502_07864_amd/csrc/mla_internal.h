@@ -102,6 +102,14 @@ __device__ __forceinline__ float wave_max(float v)
 // normaliser by wave_max / wave_sum, a fixed order that does not depend on which wave computes it.  (Reading
 // the S values lane by lane took 64 dependent steps per pass at 64 chunks, about 1.1 us of the merge
 // kernels.)  lse = m + log z (z = 0: every chunk empty).
+//
+// EXACT: expf, for more than 64 chunks of the uniform partition; otherwise the hardware's exponential, whose
+// argument is rounded once more (|x| 2^-24 of the weight: 5e-7 at a weight of e^-12).
+template <bool EXACT> __device__ __forceinline__ float merge_exp(float x)
+{
+    if constexpr (EXACT) return expf(x);
+    else                 return __expf(x);
+}
 struct ChunkWeights {
     float m, z;      // maximum and sum_s e^{lse_s - m}
     float ref, inv;  // m (0 if every chunk is empty) and 1/z (0 if z = 0)
@@ -112,12 +120,12 @@ __device__ __forceinline__ ChunkWeights chunk_weights(float ls)
     ChunkWeights cw;
     cw.m = wave_max(ls);
     cw.ref = cw.m == -INFINITY ? 0.f : cw.m;
-    cw.z = wave_sum(__expf(ls - cw.ref));   // e^{-inf} = 0
+    cw.z = wave_sum(merge_exp<false>(ls - cw.ref));   // e^{-inf} = 0
     cw.inv = cw.z > 0.f ? 1.f / cw.z : 0.f;
     return cw;
 }
 
-// the same for up to 64 N chunks (lane l holds those of chunks l, 64 + l, ..): blocks of 64 added in order
+// the same for 65 to 64 N chunks (lane l holds those of chunks l, 64 + l, ..): blocks of 64 added in order
 template <int N> __device__ __forceinline__ ChunkWeights chunk_weights(const float (&ls)[N])
 {
     ChunkWeights cw;
@@ -125,17 +133,17 @@ template <int N> __device__ __forceinline__ ChunkWeights chunk_weights(const flo
 #pragma unroll
     for (int k = 1; k < N; ++k) cw.m = fmaxf(cw.m, wave_max(ls[k]));
     cw.ref = cw.m == -INFINITY ? 0.f : cw.m;
-    cw.z = wave_sum(__expf(ls[0] - cw.ref));
+    cw.z = wave_sum(merge_exp<true>(ls[0] - cw.ref));
 #pragma unroll
-    for (int k = 1; k < N; ++k) cw.z += wave_sum(__expf(ls[k] - cw.ref));
+    for (int k = 1; k < N; ++k) cw.z += wave_sum(merge_exp<true>(ls[k] - cw.ref));
     cw.inv = cw.z > 0.f ? 1.f / cw.z : 0.f;
     return cw;
 }
 
 // weight e^{lse_s - lse} of this lane's chunk (0 for s >= S and for empty chunks): chunk s's is lane s's
-__device__ __forceinline__ float chunk_weight(const ChunkWeights& cw, float ls)
+template <bool EXACT = false> __device__ __forceinline__ float chunk_weight(const ChunkWeights& cw, float ls)
 {
-    return __expf(ls - cw.ref) * cw.inv;
+    return merge_exp<EXACT>(ls - cw.ref) * cw.inv;
 }
 
 // Where the S partials of one (sequence, query row) lie: chunk s has its log-sum-exp at
@@ -164,15 +172,15 @@ __device__ __forceinline__ float span_lse(const float* lse_part, const ChunkSpan
 }
 
 // chunk_weights for a span of any length: the same operations in the same order over blocks of 64
-// chunks (ls0 = span_lse of block 0), so that up to 64 chunks the result is chunk_weights' bit for bit
-__device__ __forceinline__ ChunkWeights span_weights(const float* lse_part, const ChunkSpan& c, float ls0, int lane)
+// chunks (ls0 = span_lse of block 0), so that the result is chunk_weights' bit for bit
+template <bool EXACT = false> __device__ __forceinline__ ChunkWeights span_weights(const float* lse_part, const ChunkSpan& c, float ls0, int lane)
 {
     ChunkWeights cw;
     cw.m = wave_max(ls0);
     for (int blk = 64; blk < c.S; blk += 64) cw.m = fmaxf(cw.m, wave_max(span_lse(lse_part, c, blk, lane)));
     cw.ref = cw.m == -INFINITY ? 0.f : cw.m;
-    cw.z = wave_sum(__expf(ls0 - cw.ref));
-    for (int blk = 64; blk < c.S; blk += 64) cw.z += wave_sum(__expf(span_lse(lse_part, c, blk, lane) - cw.ref));
+    cw.z = wave_sum(merge_exp<EXACT>(ls0 - cw.ref));
+    for (int blk = 64; blk < c.S; blk += 64) cw.z += wave_sum(merge_exp<EXACT>(span_lse(lse_part, c, blk, lane) - cw.ref));
     cw.inv = cw.z > 0.f ? 1.f / cw.z : 0.f;
     return cw;
 }

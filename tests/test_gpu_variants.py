@@ -167,6 +167,28 @@ def test_fp32_projection_shapes(mla, B, H, K, N):
         assert max_abs_rel(widen_gpu(got), ref.cpu().numpy()) <= 1e-5
 
 
+# ------------------------------------------------------------------ merge of many chunks
+
+@pytest.mark.parametrize("S", [17, 40, 64])
+def test_merge_of_many_chunks_keeps_fp32_weights(mla, S):
+    """68 to 256 chunks of one row in fp32, one with weight 1 and a value of 0, the others at e^-x with a value of 1, x
+    from 8 to 80: the result is the sum of their weights over the sum of all.  expf (2 units in the last place at
+    most), S sums and a handful of products in fp32; the hardware's exponential is off by x 2^-24 and more."""
+    import torch
+    n = 4 * S
+    table, lens = torch.arange(n, dtype=torch.int32, device="cuda").view(1, n), torch.tensor([n], dtype=torch.int32, device="cuda")
+    q = torch.zeros(1, 1, 256, device="cuda")
+    q[0, 0, 0] = 1.0
+    worst = 0.0
+    for x in np.linspace(8.0, 80.0, 73).astype(np.float32) + np.float32(0.37):
+        kv = torch.zeros(n, 1, 256, device="cuda")
+        kv[1:, 0, 0], kv[1:, 0, 1] = -float(x), 1.0
+        o = mla.decode_paged(q, None, kv, table, lens, 1.0, num_splits=S)
+        rest = (n - 1) * np.exp(-float(x))
+        worst = max(worst, abs(o[0, 0, 1].item() / (rest / (1.0 + rest)) - 1.0))
+    assert worst <= 2.0 ** -22 + 8 * 2.0 ** -24, worst
+
+
 # ------------------------------------------------------------------ merge + projection of few batch rows
 
 @pytest.mark.parametrize("B,H,d_c,S", [(1, 32, 512, 16), (1, 32, 256, 3), (1, 5, 512, 1), (2, 32, 512, 16), (4, 32, 512, 32),
