@@ -562,7 +562,12 @@ hipError_t launch_decode_portable(const DecodeParams& p, mla_dtype io, mla_dtype
 
 hipError_t launch_merge(const MergeParams& p, mla_dtype io, hipStream_t s)
 {
-    if (p.d_c % 256 == 0 && (p.plan || p.num_splits <= 256)) {
+    // Uniform partitions of 65 to 256 chunks: the streaming kernel, but for bf16 rows that fill the chip, of which the
+    // general one has more in flight (d_c = 256 / 512, us, general -> streaming: 1 x 32 rows of 80 chunks 9.5 -> 8.0 and 10.0 ->
+    // 9.4, 8 x 32 of 200 18.1 -> 18.7 and 20.3 -> 22.3, 64 x 32 of 100 20.1 -> 21.0 and 34.9 -> 34.9; fp32 64 x 32 of 100 36.1
+    // -> 34.9 and 79.9 -> 79.0).  Up to 256 rows it stays: the fused merge + projection forms the same bits there.
+    const bool streams = p.plan || p.num_splits <= 64 || (p.num_splits <= 256 && (io == MLA_F32 || (long long)p.B * p.H <= 256));
+    if (p.d_c % 256 == 0 && streams) {
         const int waves = p.B * p.H * (p.d_c / 256);
         dim3 grid((waves + 3) / 4), block(256);
         if (io == MLA_BF16) {
