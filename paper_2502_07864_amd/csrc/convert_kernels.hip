@@ -441,7 +441,8 @@ __global__ __launch_bounds__(1024) void max_diag_kernel(const double* __restrict
 // registers (lane = row, pivots and multipliers by lane reads), the rest of the block on the matrix cores.  What
 // bounds it is that chain, column after column.  As separate kernels (block, panel solve, trailing product; then the
 // inverse row by row with two products each) order 768 took
-// 1330 us, now 300.
+// 1330 us, now 300.  Parts of 16 and columns past the end of the last block are left out: a call of top_eig with 5
+// columns and 5 iterations (eight of these) 345 us as separate kernels, 455 with them, 370 without.
 constexpr int CP = 66;                     // row pitch of a block in LDS: 32 lanes that read 16 rows x 2 columns hit 32 units of 8 bytes
 
 // c[t] = rows 16 wave .., columns 16 t .. of P R^T (both 64 x 64, row-major); LOWER: R is zero above its diagonal.
@@ -502,7 +503,8 @@ __device__ __forceinline__ void factor_invert(double* S, double* V, double* dinv
     }
     __syncthreads();
     int nbad = 0;
-    for (int sb = 0; sb < 4; ++sb) {
+    const int nsb = (nb + 15) / 16;                      // parts of 16 that hold rows: the others are left alone
+    for (int sb = 0; sb < nsb; ++sb) {
         const int s0 = sb * 16;
         if (wave == 0) {
             double a[16], mine = 0.0;
@@ -510,8 +512,12 @@ __device__ __forceinline__ void factor_invert(double* S, double* V, double* dinv
             for (int c = 0; c < 16; ++c) a[c] = S[lane * CP + s0 + c];
 #pragma unroll
             for (int j = 0; j < 16; ++j) {
+                if (s0 + j >= nb) {                      // (uniform) a row past the end
+                    if (lane == s0 + j) mine = 1.0;
+                    continue;
+                }
                 double d = read_lane(a[j], s0 + j);
-                if (s0 + j < nb && !(d > floor_v)) { d = floor_v; ++nbad; }
+                if (!(d > floor_v)) { d = floor_v; ++nbad; }
                 const double inv = rsqrt(d);
                 if (lane == s0 + j) { a[j] = d; mine = inv; }
                 a[j] *= inv;
@@ -524,7 +530,7 @@ __device__ __forceinline__ void factor_invert(double* S, double* V, double* dinv
         }
         __syncthreads();
         // what is left of the block: 16 x 16 tiles (bi, bj), bi >= bj > sb
-        const int left = 3 - sb;
+        const int left = nsb - 1 - sb;
         for (int t = wave; t < left * (left + 1) / 2; t += 4) {
             const int u = t < 1 ? 0 : t < 3 ? 1 : 2, bi = sb + 1 + u, bj = sb + 1 + t - u * (u + 1) / 2;
             f64x4 c;
@@ -540,7 +546,7 @@ __device__ __forceinline__ void factor_invert(double* S, double* V, double* dinv
     }
     if (tid == 0 && nbad) atomicAdd(bad, nbad);
     // inverse: diagonal 16 x 16 blocks, a wavefront each, lane = column ...
-    if (lane < 16) {
+    if (lane < 16 && wave < nsb) {
         const double* L = S + 16 * wave * (CP + 1);
         double x[16];
 #pragma unroll
@@ -554,9 +560,9 @@ __device__ __forceinline__ void factor_invert(double* S, double* V, double* dinv
     }
     __syncthreads();
     // ... then X_ij = -X_ii sum_k L_ik X_kj, one distance from the diagonal after the other
-    for (int dist = 1; dist < 4; ++dist) {
+    for (int dist = 1; dist < nsb; ++dist) {
         const int bi = dist + wave, bj = wave;
-        if (bi < 4) {
+        if (bi < nsb) {
             f64x4 m = {0.0, 0.0, 0.0, 0.0}, c = {0.0, 0.0, 0.0, 0.0};
             for (int k = bj; k < bi; ++k)
 #pragma unroll
