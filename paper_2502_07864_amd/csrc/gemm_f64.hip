@@ -99,7 +99,7 @@ __global__ __launch_bounds__(THREADS, 4) void gemm_f64_kernel(GemmF64 g, int til
     const int tile = item % tiles, z = item / tiles;     // z: slice of the K range
     int tm = tile / tiles_n, tn = tile % tiles_n;
     if (g.symmetric) {                         // tiles on and above the diagonal, row by row
-        tm = (int)(((2 * tiles_n + 1) - sqrt((double)(2 * tiles_n + 1) * (2 * tiles_n + 1) - 8.0 * tile)) * 0.5);
+        tm = (int)(((2 * tiles_n + 1) - sqrtf((2.f * tiles_n + 1.f) * (2.f * tiles_n + 1.f) - 8.f * tile)) * 0.5f);
         while (tm > 0 && tile < row_start(tm, tiles_n)) --tm;           // (the root's rounding)
         while (tile >= row_start(tm + 1, tiles_n)) ++tm;
         tn = tm + tile - row_start(tm, tiles_n);
@@ -227,11 +227,16 @@ __global__ __launch_bounds__(256) void gemm_f64_reduce_kernel(GemmF64 g, int spl
 }
 
 template <bool A_KC, bool B_KC, bool NEAR>
-hipError_t run(const GemmF64& g, hipStream_t s) {
+hipError_t run(GemmF64 g, hipStream_t s) {
     constexpr size_t lds_bytes = 4 * STAGE * sizeof(double);
     hipError_t e0 = allow_dynamic_lds(reinterpret_cast<const void*>(&gemm_f64_kernel<A_KC, B_KC, NEAR>), (int)lds_bytes);
     if (e0 != hipSuccess) return e0;
     const int tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
+    // Half the tiles of a symmetric product are worth the scattered stores of their mirror images where the others leave
+    // or shorten a round: in K slices, or past one workgroup per CU (C^T C, us, all tiles -> half: 100 x 400 28 -> 41, 200 x
+    // 1400 50 -> 57, 4096 x 1000 634 -> 618, 300 x 4000 222 -> 174).  The bits are the same: an entry and its image sum the
+    // same products in the same order.
+    if (!g.partial && (long)tiles_m * tiles_n <= 256) g.symmetric = 0;
     const int tiles = g.symmetric ? row_start(tiles_m, tiles_n) : tiles_m * tiles_n;
     const int nk = (g.K + BK - 1) / BK;
     // K slices: only when scratch is there, the tiles leave most of the 256 CUs idle and every slice
@@ -270,9 +275,10 @@ hipError_t launch_gemm_f64(const GemmF64& g, hipStream_t s) {
     if (g.lower && (g.partial || g.symmetric)) return hipErrorInvalidValue;
     const bool a_kc = g.sAk == 1, b_kc = g.sBk == 1;
     if ((!a_kc && g.sAm != 1) || (!b_kc && g.sBn != 1)) return hipErrorInvalidValue;
-    // offsets within a tile are 32-bit while no stride is above 2^22 elements
+    // Offsets within a tile are 32-bit while no stride is above 2^22 elements; working them out pays from some 24 steps on
+    // (us, plain loads -> offsets: K = 10 10.2 -> 11.6, 100 24.4 -> 25.2, 300 52.7 -> 52.8, 400 69.8 -> 68.6, 2000 328 -> 314).
     const long far = 1L << 22;
-    const bool near = g.sAm <= far && g.sAk <= far && g.sBn <= far && g.sBk <= far;
+    const bool near = g.K >= 24 * BK && g.sAm <= far && g.sAk <= far && g.sBn <= far && g.sBk <= far;
     if (a_kc && b_kc) return near ? run<true, true, true>(g, s) : run<true, true, false>(g, s);
     if (a_kc) return near ? run<true, false, true>(g, s) : run<true, false, false>(g, s);
     if (b_kc) return near ? run<false, true, true>(g, s) : run<false, true, false>(g, s);
