@@ -6,6 +6,7 @@
 #include <algorithm>
 #include <mutex>
 #include <set>
+#include <type_traits>
 #include <utility>
 
 namespace mla {
@@ -494,6 +495,8 @@ __device__ __forceinline__ double read_lane(double v, int lane) {
 
 // S (64 x 64, its lower half; nb rows and columns of it) = L L^T -> V = L^{-1}.  Four wavefronts; pivots not above
 // floor_v are replaced by it and counted.
+// WHOLE: nb = 64, known at compile time.
+template <bool WHOLE>
 __device__ __forceinline__ void factor_invert(double* S, double* V, double* dinv, int nb, double floor_v, int* bad, int tid) {
     const int lane = tid & 63, wave = tid >> 6, li = lane & 15, kq = lane >> 4;
     for (int idx = tid; idx < 64 * CP; idx += 256) {
@@ -503,27 +506,31 @@ __device__ __forceinline__ void factor_invert(double* S, double* V, double* dinv
     }
     __syncthreads();
     int nbad = 0;
-    const int nsb = (nb + 15) / 16;                      // parts of 16 that hold rows: the others are left alone
+    const int nsb = WHOLE ? 4 : (nb + 15) / 16;          // parts of 16 that hold rows: the others are left alone
     for (int sb = 0; sb < nsb; ++sb) {
         const int s0 = sb * 16;
         if (wave == 0) {
             double a[16], mine = 0.0;
 #pragma unroll
             for (int c = 0; c < 16; ++c) a[c] = S[lane * CP + s0 + c];
+            auto columns = [&](auto whole) {             // (whole: all 16 rows are there, and nothing asks)
 #pragma unroll
-            for (int j = 0; j < 16; ++j) {
-                if (s0 + j >= nb) {                      // (uniform) a row past the end
-                    if (lane == s0 + j) mine = 1.0;
-                    continue;
+                for (int j = 0; j < 16; ++j) {
+                    if (!decltype(whole)::value && s0 + j >= nb) {       // a row past the end
+                        if (lane == s0 + j) mine = 1.0;
+                        continue;
+                    }
+                    double d = read_lane(a[j], s0 + j);
+                    if (!(d > floor_v)) { d = floor_v; ++nbad; }
+                    const double inv = rsqrt(d);
+                    if (lane == s0 + j) { a[j] = d; mine = inv; }
+                    a[j] *= inv;
+#pragma unroll
+                    for (int k = j + 1; k < 16; ++k) a[k] -= a[j] * read_lane(a[j], s0 + k);
                 }
-                double d = read_lane(a[j], s0 + j);
-                if (!(d > floor_v)) { d = floor_v; ++nbad; }
-                const double inv = rsqrt(d);
-                if (lane == s0 + j) { a[j] = d; mine = inv; }
-                a[j] *= inv;
-#pragma unroll
-                for (int k = j + 1; k < 16; ++k) a[k] -= a[j] * read_lane(a[j], s0 + k);
-            }
+            };
+            if (WHOLE || s0 + 16 <= nb) columns(std::true_type{});
+            else                        columns(std::false_type{});
 #pragma unroll
             for (int c = 0; c < 16; ++c) S[lane * CP + s0 + c] = lane >= s0 + c ? a[c] : 0.0;
             if (lane >= s0 && lane < s0 + 16) dinv[lane] = mine;
@@ -640,7 +647,8 @@ __global__ __launch_bounds__(256) void chol_step_kernel(double* G, double* X, do
     }
     __syncthreads();
     const int k1 = k + 1, nb = min(NB, p - k1 * NB);
-    factor_invert(A, D, dinv, nb, *floor_in, bad, tid);
+    if (nb == NB) factor_invert<true>(A, D, dinv, nb, *floor_in, bad, tid);
+    else          factor_invert<false>(A, D, dinv, nb, *floor_in, bad, tid);
     for (int idx = tid; idx < nb * NB; idx += 256) Linv[(long)k1 * NB * NB + idx] = D[(idx >> 6) * CP + (idx & 63)];
 }
 
