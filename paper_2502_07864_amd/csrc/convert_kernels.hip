@@ -161,6 +161,8 @@ __device__ __forceinline__ void round_robin_pair(int k, int step, int mp, int& p
     if (p > q) { const int t = p; p = q; q = t; }
 }
 
+// TOGETHER: blocks of A and pairs of V in one pass, for workgroups with a thread for each.
+template <bool TOGETHER>
 __device__ __forceinline__ void jacobi_step(double* A, double* V, int ld, int m, int step, Rotations& R, int tid, int nt) {
     const int mp = m + (m & 1), half = mp / 2;
     if (tid < half) {
@@ -180,10 +182,10 @@ __device__ __forceinline__ void jacobi_step(double* A, double* V, int ld, int m,
         R.pp[tid] = p; R.qq[tid] = q; R.cc[tid] = c; R.ss[tid] = s;
     }
     __syncthreads();
-    for (int idx = tid; idx < half * half; idx += nt) {
+    auto block = [&](int idx) {
         const int k1 = idx / half, k2 = idx % half;
         const double s1 = R.ss[k1], s2 = R.ss[k2];
-        if (s1 == 0.0 && s2 == 0.0) continue;
+        if (s1 == 0.0 && s2 == 0.0) return;
         const double c1 = R.cc[k1], c2 = R.cc[k2];
         const int p1 = R.pp[k1] * ld, q1 = R.qq[k1] * ld, p2 = R.pp[k2], q2 = R.qq[k2];
         const bool r = R.qq[k1] < m, t = q2 < m;         // (a bye has no second row / column)
@@ -196,8 +198,8 @@ __device__ __forceinline__ void jacobi_step(double* A, double* V, int ld, int m,
         if (t) A[p1 + q2] = pair ? 0.0 : s2 * pp + c2 * pq;
         if (r) A[q1 + p2] = pair ? 0.0 : c2 * qp - s2 * qq;
         if (r && t) A[q1 + q2] = s2 * qp + c2 * qq;
-    }
-    for (int idx = tid; idx < half * m; idx += nt) {
+    };
+    auto v_pair = [&](int idx) {
         const int k = idx % half, i = idx / half;
         const double s = R.ss[k];
         if (s != 0.0) {
@@ -207,6 +209,16 @@ __device__ __forceinline__ void jacobi_step(double* A, double* V, int ld, int m,
             V[ip] = c * vp - s * vq;
             V[iq] = s * vp + c * vq;
         }
+    };
+    const int blocks = half * half;
+    if (TOGETHER) {
+        for (int idx = tid; idx < blocks + half * m; idx += nt) {
+            if (idx < blocks) block(idx);
+            else              v_pair(idx - blocks);
+        }
+    } else {
+        for (int idx = tid; idx < blocks; idx += nt) block(idx);
+        for (int idx = tid; idx < half * m; idx += nt) v_pair(idx);
     }
     __syncthreads();
 }
@@ -223,6 +235,7 @@ struct JacobiLds {
     double red[16];
 };
 
+template <bool TOGETHER>
 __global__ __launch_bounds__(1024) void jacobi_kernel(double* A_all, double* evals_all, double* V_all, int* info,
                                                       int m, int max_sweeps, int in_lds) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -255,7 +268,7 @@ __global__ __launch_bounds__(1024) void jacobi_kernel(double* A_all, double* eva
         off = block_sum(off, L.red);
         if (off <= tol2) { used = sweep > 0 ? sweep : 1; break; }
         if (sweep == max_sweeps) break;
-        for (int step = 0; step < mp - 1; ++step) jacobi_step(A, V, ld, m, step, L.rot, tid, nt);
+        for (int step = 0; step < mp - 1; ++step) jacobi_step<TOGETHER>(A, V, ld, m, step, L.rot, tid, nt);
     }
 
     // rank the diagonal in descending order (ties: lower index first)
@@ -340,7 +353,7 @@ __global__ __launch_bounds__(256) void jb_pair_kernel(double* A, double* __restr
         z[r * (JP + 1) + c] = r == c ? 1.0 : 0.0;
     }
     __syncthreads();
-    for (int s = 0; s < JP - 1; ++s) jacobi_step(a, z, JP + 1, JP, s, rot, tid, 256);
+    for (int s = 0; s < JP - 1; ++s) jacobi_step<false>(a, z, JP + 1, JP, s, rot, tid, 256);
     for (int idx = tid; idx < JP * JP; idx += 256) {
         const int r = idx / JP, c = idx % JP, i = pair_index(I, J, r), j = pair_index(I, J, c);
         if (i < m && j < m) A[(long)i * m + j] = a[r * (JP + 1) + c];
@@ -826,11 +839,15 @@ hipError_t launch_jacobi(double* A, double* evals, double* work, int* info, int 
     const size_t mats = 2 * (size_t)m * (m + 1) * sizeof(double);
     const int in_lds = head + mats <= 128 * 1024;
     const size_t bytes = head + (in_lds ? mats : 0);
-    hipError_t e0 = allow_dynamic_lds(reinterpret_cast<const void*>(&jacobi_kernel), 128 * 1024);
+    // A thread for each 2 x 2 block and pair of V of a step while 1024 are about enough, else one per block (64 matrices, us:
+    // order 16 161 -> 122, 32 384 -> 297, 40 502 -> 463; but 48 750 -> 778, 56 1085 -> 1170).
+    const int half = (m + 1) / 2, blocks = half * half, items = blocks + half * m;
+    const bool together = items <= 1280;
+    const int threads = std::min(1024, std::max(64, ((together ? items : blocks) + 63) / 64 * 64));
+    const auto kernel = together ? &jacobi_kernel<true> : &jacobi_kernel<false>;
+    hipError_t e0 = allow_dynamic_lds(reinterpret_cast<const void*>(kernel), 128 * 1024);
     if (e0 != hipSuccess) return e0;
-    // a thread per 2 x 2 block of a step, up to the 1024 a workgroup can have
-    const int half = (m + 1) / 2, threads = std::min(1024, std::max(64, (half * half + 63) / 64 * 64));
-    jacobi_kernel<<<batch, threads, bytes, s>>>(A, evals, work, info, m, max_sweeps, in_lds);
+    kernel<<<batch, threads, bytes, s>>>(A, evals, work, info, m, max_sweeps, in_lds);
     return hipGetLastError();
 }
 
