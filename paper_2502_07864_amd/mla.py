@@ -5,11 +5,13 @@ live on the GPU, passes their device pointers and the current HIP stream to
 the C entry point of the same name (the serving calls through a small
 extension, csrc/marshal.cpp), and returns the output tensor.  torch is
 used for device memory and streams; no arithmetic happens here and there is
-no fallback path: a missing library or a failing call raises.
+no fallback path: a missing library or a failing call raises.  (Without the extension the
+same calls are made from here.)
 """
 from __future__ import annotations
 
 import ctypes
+import warnings
 from pathlib import Path
 from typing import Optional
 
@@ -33,6 +35,20 @@ class MlaError(RuntimeError):
     def __init__(self, status: int, where: str):
         self.status = status
         super().__init__(f"{where}: {status_string(status)} ({status})")
+
+
+def _load_marshal(L: ctypes.CDLL):
+    """The marshalling extension with the library's entry points in hand, or None: every call then goes from Python."""
+    try:
+        from . import _marshal
+    except ImportError as e:
+        warnings.warn(f"the marshalling extension is not loaded ({e}): the serving calls pass their arguments from Python, "
+                      "some 5 us of host time more each; build it with `python -m paper_2502_07864_amd.build`", RuntimeWarning)
+        return None
+    _marshal.bind(*(ctypes.cast(getattr(L, n), ctypes.c_void_p).value for n in
+                    ("mla_absorb_q", "mla_out_proj", "mla_decode_paged_multi", "mla_merge_out_proj_multi",
+                     "mla_merge_partials", "mla_cache_append")))
+    return _marshal
 
 
 def lib() -> ctypes.CDLL:
@@ -84,15 +100,7 @@ def lib() -> ctypes.CDLL:
         L.mla_cache_append.restype = i
         L.mla_cache_append.argtypes = [vp, vp, vp, vp, vp, vp, vp, ctypes.c_size_t,
                                        i, i, i, i, i, i, i, f, i, i, vp]
-        try:
-            from . import _marshal
-        except ImportError as e:
-            raise FileNotFoundError(
-                f"the marshalling extension is missing ({e}): build it with `python -m paper_2502_07864_amd.build`") from e
-        _marshal.bind(*(ctypes.cast(getattr(L, n), vp).value for n in
-                        ("mla_absorb_q", "mla_out_proj", "mla_decode_paged_multi", "mla_merge_out_proj_multi",
-                         "mla_merge_partials", "mla_cache_append")))
-        _lib, _fast = L, _marshal
+        _lib, _fast = L, _load_marshal(L)
     return _lib
 
 

@@ -11,6 +11,43 @@ def test_the_extension_is_the_one_in_the_package():
     assert mla._fast.__file__.startswith(str(mla._LIB_PATH.parent))
 
 
+def test_the_library_loads_without_the_extension(monkeypatch):
+    """A package without _marshal (or one built for another torch) still loads, says so, and keeps every check."""
+    import sys
+    from paper_2502_07864_amd import convert
+    monkeypatch.setitem(sys.modules, "paper_2502_07864_amd._marshal", None)      # importing it raises ImportError
+    import paper_2502_07864_amd
+    monkeypatch.delattr(paper_2502_07864_amd, "_marshal", raising=False)
+    monkeypatch.setattr(mla, "_lib", None)
+    monkeypatch.setattr(mla, "_fast", None)
+    monkeypatch.setattr(convert, "_ready", False)
+    with pytest.warns(RuntimeWarning, match="marshalling extension is not loaded"):
+        mla.lib()
+    assert mla._fast is None and mla.version().startswith("mla-gfx950")
+    assert convert.lib().mla_conv_top_eig_workspace_bytes(64, 8) > 0
+    with pytest.raises(ValueError, match="GPU tensor"):
+        mla.absorb_q(torch.zeros(1, 2, 4), torch.zeros(2, 4, 8), out=torch.zeros(1, 2, 8))
+
+
+def test_the_library_builds_where_the_extension_cannot(monkeypatch, tmp_path):
+    """Neither a missing torch nor a failing compiler keeps the library from being built."""
+    import sys
+    from paper_2502_07864_amd import build
+    monkeypatch.setattr(build, "MARSHAL", tmp_path / "_marshal.so")
+    (tmp_path / "bin").mkdir()
+    failing = tmp_path / "bin" / "g++"
+    failing.write_text("#!/bin/sh\nexit 1\n")
+    failing.chmod(0o755)
+    monkeypatch.setattr(build.shutil, "which", lambda name: str(failing) if name == "g++" else None)
+    monkeypatch.setattr(build, "hipcc", lambda: "/opt/rocm/bin/hipcc")
+    with pytest.warns(RuntimeWarning, match="failed on marshal.cpp"):
+        assert build.build_marshal() is None
+    monkeypatch.setitem(sys.modules, "torch", None)
+    with pytest.warns(RuntimeWarning, match="not built"):
+        assert build.build_marshal() is None
+    assert not (tmp_path / "_marshal.so").exists()
+
+
 @pytest.mark.parametrize("bad", [torch.zeros(1, 2, 4), torch.zeros(1, 2, 4, dtype=torch.float64), None, 3, "x",
                                  torch.zeros(2, 1, 4).transpose(0, 1)])
 def test_arguments_it_does_not_take_are_left_to_the_binding(bad):
