@@ -3,9 +3,10 @@
 // A decode step is three calls whose kernels together take 14 to 20 us at small sizes; checking the tensors,
 // asking for the stream and converting some twenty arguments each in Python took 6 to 8 us per call, so that
 // the host set the pace below about 25 us per step.  The functions here read the tensors' fields directly and
-// call the C entry point they are given.  They accept exactly what needs no message: plain torch tensors, all
-// arguments of the expected types and shapes.  For anything else they return None without having called
-// anything, and mla.py goes through its own checks, which raise what they have always raised.
+// call the C entry point they are given.  They accept what mla.py's checks let through, as far as it is plain torch
+// tensors, integers and floats: inputs of the expected types and shapes, tables of int32, and outputs of the
+// expected element size with room for the result (their own shape and type are the caller's).  For anything else
+// they return None without having called anything, and mla.py goes through its own checks, which raise.
 // No arithmetic, no allocation, no state beyond the entry points' addresses; the interpreter lock is released
 // around the call as ctypes does.
 #include <torch/csrc/autograd/python_variable.h>
@@ -32,8 +33,6 @@ const at::Tensor& tensor(PyObject* o)
     if (!t.is_cuda() || !t.is_contiguous()) throw No();
     return t;
 }
-void* pointer(PyObject* o) { return tensor(o).data_ptr(); }
-void* pointer_or_null(PyObject* o) { return o == Py_None ? nullptr : pointer(o); }
 
 long integer(PyObject* o)
 {
@@ -70,6 +69,16 @@ void require(bool ok)
     if (!ok) throw No();
 }
 
+// an output (or scratch) with room for n elements of `size` bytes
+void* room(PyObject* o, int64_t n, size_t size)
+{
+    const at::Tensor& t = tensor(o);
+    require((size_t)t.element_size() == size && t.numel() >= n);
+    return t.data_ptr();
+}
+void* room_or_null(PyObject* o, int64_t n, size_t size) { return o == Py_None ? nullptr : room(o, n, size); }
+size_t size_of(mla_dtype io) { return io == MLA_F32 ? 4 : 2; }
+
 // f(): the status of the call it makes
 template <typename F> PyObject* guarded(F f)
 {
@@ -94,9 +103,9 @@ template <typename P> PyObject* projection(P p, PyObject* const* a, Py_ssize_t n
         require(n == 3);
         const at::Tensor &x = tensor(a[0]), &W = tensor(a[1]);
         require(x.dim() == 3 && W.dim() == 3 && W.size(0) == x.size(1) && W.size(1) == x.size(2) && W.scalar_type() == x.scalar_type());
-        void *px = x.data_ptr(), *pw = W.data_ptr(), *po = pointer(a[2]), *s = stream_of(x);
         const int B = dim(x.size(0)), H = dim(x.size(1)), K = dim(x.size(2)), N = dim(W.size(2));
         const mla_dtype io = io_type(x);
+        void *px = x.data_ptr(), *pw = W.data_ptr(), *po = room(a[2], (int64_t)B * H * N, size_of(io)), *s = stream_of(x);
         return unlocked([&] { return p(px, pw, po, B, H, K, N, io, s); });
     });
 }
@@ -134,14 +143,15 @@ PyObject* decode(PyObject*, PyObject* const* a, Py_ssize_t n)
             require(s.scalar_type() == at::kFloat && s.dim() == 2 && s.size(0) == pages && s.size(1) == page);
             ps = static_cast<const float*>(s.data_ptr());
         }
-        void *pq = q.data_ptr(), *pkv = kv.data_ptr(), *pws = ws.data_ptr(), *po = pointer_or_null(a[9]), *pl = pointer_or_null(a[10]);
+        const mla_dtype io = io_type(q), cache = cache_type(kv);
+        void *pq = q.data_ptr(), *pkv = kv.data_ptr(), *pws = ws.data_ptr();
+        void *po = room_or_null(a[9], q.numel(), size_of(io)), *pl = room_or_null(a[10], B * T * H, 4);
         const auto* pt = static_cast<const int32_t*>(table.data_ptr());
         const auto* pn = static_cast<const int32_t*>(lens.data_ptr());
         const size_t bytes = ws.nbytes();
         const float scale = real(a[5]);
         const int splits = (int)integer(a[6]), flags = (int)integer(a[11]);
         const int b = dim(B), t = dim(T), h = dim(H), dc = dim(d_c), dr = dim(d_rope), pg = dim(page), np = dim(pages), mp = dim(table.size(1));
-        const mla_dtype io = io_type(q), cache = cache_type(kv);
         void* s = stream_of(q);
         return unlocked([&] {
             return p_decode(pq, pr, pkv, ps, pt, pn, po, static_cast<float*>(pl), pws, bytes, b, t, h, dc, dr, pg, np, mp, splits, scale, io,
@@ -157,10 +167,13 @@ PyObject* merge_out_proj(PyObject*, PyObject* const* a, Py_ssize_t n)
         require(n == 9);
         const at::Tensor &ws = tensor(a[0]), &W = tensor(a[1]);
         require(W.dim() == 3);
-        void *pws = ws.data_ptr(), *pw = W.data_ptr(), *po = pointer(a[2]), *pl = pointer_or_null(a[3]), *pout = pointer(a[4]);
         const int B = (int)integer(a[5]), T = (int)integer(a[6]), S = (int)integer(a[7]), flags = (int)integer(a[8]);
         const int H = dim(W.size(0)), d_c = dim(W.size(1)), d_head = dim(W.size(2));
         const mla_dtype io = io_type(W);
+        require(B >= 0 && B <= 65535 && T >= 0 && T <= 65535 && (int64_t)B * T <= 65535 && H <= 65535);   // (no more is taken: the products below fit)
+        const int64_t rows = (int64_t)B * T * H;
+        void *pws = ws.data_ptr(), *pw = W.data_ptr(), *po = room(a[2], rows * d_c, size_of(io)), *pl = room_or_null(a[3], rows, 4),
+             *pout = room(a[4], rows * d_head, size_of(io));
         const size_t bytes = ws.nbytes();
         void* s = stream_of(ws);
         return unlocked([&] {
@@ -175,9 +188,10 @@ PyObject* merge_partials(PyObject*, PyObject* const* a, Py_ssize_t n)
     return guarded([&] {
         require(n == 8);
         const at::Tensor &ws = tensor(a[0]), &out = tensor(a[1]);
-        void *pws = ws.data_ptr(), *po = out.data_ptr(), *pl = pointer_or_null(a[2]);
         const int B = (int)integer(a[3]), H = (int)integer(a[4]), d_c = (int)integer(a[5]), S = (int)integer(a[6]), flags = (int)integer(a[7]);
         const mla_dtype io = io_type(out);
+        require(B >= 0 && B <= 65535 && H >= 0 && H <= 65535 && d_c >= 0);
+        void *pws = ws.data_ptr(), *po = room(a[1], (int64_t)B * H * d_c, size_of(io)), *pl = room_or_null(a[2], (int64_t)B * H, 4);
         const size_t bytes = ws.nbytes();
         void* s = stream_of(ws);
         return unlocked([&] { return p_merge_partials(pws, bytes, po, static_cast<float*>(pl), B, H, d_c, S, io, (unsigned)flags, s); });
@@ -192,8 +206,10 @@ PyObject* cache_append(PyObject*, PyObject* const* a, Py_ssize_t n)
         const at::Tensor &x = tensor(a[0]), &W = tensor(a[1]), &kv = tensor(a[2]), &table = tensor(a[4]), &pos = tensor(a[5]), &ws = tensor(a[6]);
         require(x.dim() == 2 && W.dim() == 2 && kv.dim() == 3 && table.dim() == 2);
         require(W.size(0) == x.size(1) && W.size(1) == kv.size(2) && W.scalar_type() == x.scalar_type());
+        require(table.scalar_type() == at::kInt && table.size(0) >= x.size(0) && pos.scalar_type() == at::kInt && pos.numel() >= x.size(0));
         const int d_c = (int)integer(a[7]);
-        void *px = x.data_ptr(), *pw = W.data_ptr(), *pkv = kv.data_ptr(), *ps = pointer_or_null(a[3]), *pws = ws.data_ptr();
+        void *px = x.data_ptr(), *pw = W.data_ptr(), *pkv = kv.data_ptr(), *ps = room_or_null(a[3], kv.size(0) * kv.size(1), 4),
+             *pws = ws.data_ptr();
         const auto* pt = static_cast<const int32_t*>(table.data_ptr());
         const auto* pp = static_cast<const int32_t*>(pos.data_ptr());
         const int B = dim(x.size(0)), D = dim(x.size(1)), d_rope = dim(W.size(1)) - d_c, page = dim(kv.size(1)), pages = dim(kv.size(0)),

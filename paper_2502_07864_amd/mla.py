@@ -149,9 +149,15 @@ def _check(status: int, where: str):
         raise MlaError(status, where)
 
 
-# The serving calls try the marshalling extension first: it takes plain contiguous GPU tensors of the expected
-# types and shapes and returns the call's status; for anything else it returns None, having called nothing, and
-# the checks written out below decide (and raise).
+def _room(t: Optional[torch.Tensor], n: int, size: int, name: str):
+    """The call writes (or reads) n elements of `size` bytes there; shape and type are the caller's."""
+    if t is not None and (t.element_size() != size or t.numel() < n):
+        raise ValueError(f"{name} must hold {n} elements of {size} bytes, got {t.numel()} of {t.element_size()}")
+
+
+# The serving calls try the marshalling extension first: it takes plain contiguous GPU tensors that pass the checks
+# written out below and returns the call's status; for anything else it returns None, having called nothing, and
+# those checks decide (and raise).
 
 def absorb_q(q_nope: torch.Tensor, W_UK: torch.Tensor, out: Optional[torch.Tensor] = None) -> torch.Tensor:
     """q_abs[b,h,:] = q_nope[b,h,:] . W_UK[h];  q_nope [B,H,d_head], W_UK [H,d_head,d_c]."""
@@ -166,8 +172,10 @@ def absorb_q(q_nope: torch.Tensor, W_UK: torch.Tensor, out: Optional[torch.Tenso
         raise ValueError("W_UK must be [H, d_head, d_c] of q_nope's dtype")
     if out is None:
         out = torch.empty((B, H, d_c), dtype=q_nope.dtype, device=q_nope.device)
-    _check(lib().mla_absorb_q(_dev(q_nope, "q_nope"), _dev(W_UK, "W_UK"), _dev(out, "out"),
-                              B, H, d_head, d_c, _io_code(q_nope), _stream(q_nope)), "mla_absorb_q")
+    args = (_dev(q_nope, "q_nope"), _dev(W_UK, "W_UK"), _dev(out, "out"),
+            B, H, d_head, d_c, _io_code(q_nope), _stream(q_nope))
+    _room(out, B * H * d_c, q_nope.element_size(), "out")
+    _check(lib().mla_absorb_q(*args), "mla_absorb_q")
     return out
 
 
@@ -184,8 +192,10 @@ def out_proj(o_lat: torch.Tensor, W_UV: torch.Tensor, out: Optional[torch.Tensor
         raise ValueError("W_UV must be [H, d_c, d_head] of o_lat's dtype")
     if out is None:
         out = torch.empty((B, H, d_head), dtype=o_lat.dtype, device=o_lat.device)
-    _check(lib().mla_out_proj(_dev(o_lat, "o_lat"), _dev(W_UV, "W_UV"), _dev(out, "out"),
-                              B, H, d_c, d_head, _io_code(o_lat), _stream(o_lat)), "mla_out_proj")
+    args = (_dev(o_lat, "o_lat"), _dev(W_UV, "W_UV"), _dev(out, "out"),
+            B, H, d_c, d_head, _io_code(o_lat), _stream(o_lat))
+    _room(out, B * H * d_head, o_lat.element_size(), "out")
+    _check(lib().mla_out_proj(*args), "mla_out_proj")
     return out
 
 
@@ -229,13 +239,16 @@ def decode_paged(q_abs: torch.Tensor, q_rope: Optional[torch.Tensor], kv_cache: 
         out = torch.empty((B, H, d_c), dtype=q_abs.dtype, device=q_abs.device)
     if lse is None and return_lse:
         lse = torch.empty((B, H), dtype=torch.float32, device=q_abs.device)
-    _check(lib().mla_decode_paged(
-        _dev(q_abs, "q_abs"), _dev(q_rope, "q_rope"), _dev(kv_cache, "kv_cache"),
-        _dev(kv_scale, "kv_scale"), _dev(page_table, "page_table"), _dev(seq_lens, "seq_lens"),
-        _dev(out, "out"), _dev(lse, "lse"), _dev(workspace, "workspace"),
-        workspace.numel() * workspace.element_size(), B, H, d_c, d_rope, page_size, num_pages,
-        page_table.shape[1], num_splits, float(softmax_scale), _io_code(q_abs),
-        _cache_code(kv_cache), int(flags), _stream(q_abs)), "mla_decode_paged")
+    args = (_dev(q_abs, "q_abs"), _dev(q_rope, "q_rope"), _dev(kv_cache, "kv_cache"),
+            _dev(kv_scale, "kv_scale"), _dev(page_table, "page_table"), _dev(seq_lens, "seq_lens"),
+            _dev(out, "out"), _dev(lse, "lse"), _dev(workspace, "workspace"),
+            workspace.numel() * workspace.element_size(), B, H, d_c, d_rope, page_size, num_pages,
+            page_table.shape[1], num_splits, float(softmax_scale), _io_code(q_abs),
+            _cache_code(kv_cache), int(flags), _stream(q_abs))
+    if not skip_merge:
+        _room(out, q_abs.numel(), q_abs.element_size(), "out")
+        _room(lse, B * H, 4, "lse")
+    _check(lib().mla_decode_paged(*args), "mla_decode_paged")
     if skip_merge:
         return workspace
     return (out, lse) if lse is not None else out
@@ -315,13 +328,16 @@ def decode_paged_multi(q_abs: torch.Tensor, q_rope: Optional[torch.Tensor], kv_c
         out = torch.empty((B, T, H, d_c), dtype=q_abs.dtype, device=q_abs.device)
     if lse is None and return_lse:
         lse = torch.empty((B, T, H), dtype=torch.float32, device=q_abs.device)
-    _check(lib().mla_decode_paged_multi(
-        _dev(q_abs, "q_abs"), _dev(q_rope, "q_rope"), _dev(kv_cache, "kv_cache"),
-        _dev(kv_scale, "kv_scale"), _dev(page_table, "page_table"), _dev(seq_lens, "seq_lens"),
-        _dev(out, "out"), _dev(lse, "lse"), _dev(workspace, "workspace"),
-        workspace.numel() * workspace.element_size(), B, T, H, d_c, d_rope, page_size, num_pages,
-        page_table.shape[1], num_splits, float(softmax_scale), _io_code(q_abs),
-        _cache_code(kv_cache), int(flags), _stream(q_abs)), "mla_decode_paged_multi")
+    args = (_dev(q_abs, "q_abs"), _dev(q_rope, "q_rope"), _dev(kv_cache, "kv_cache"),
+            _dev(kv_scale, "kv_scale"), _dev(page_table, "page_table"), _dev(seq_lens, "seq_lens"),
+            _dev(out, "out"), _dev(lse, "lse"), _dev(workspace, "workspace"),
+            workspace.numel() * workspace.element_size(), B, T, H, d_c, d_rope, page_size, num_pages,
+            page_table.shape[1], num_splits, float(softmax_scale), _io_code(q_abs),
+            _cache_code(kv_cache), int(flags), _stream(q_abs))
+    if not skip_merge:
+        _room(out, q_abs.numel(), q_abs.element_size(), "out")
+        _room(lse, B * T * H, 4, "lse")
+    _check(lib().mla_decode_paged_multi(*args), "mla_decode_paged_multi")
     if skip_merge:
         return workspace
     return (out, lse) if lse is not None else out
@@ -344,11 +360,15 @@ def merge_out_proj_multi(workspace: torch.Tensor, W_UV: torch.Tensor, B: int, q_
         out = torch.empty((B, q_len, H, d_head), dtype=W_UV.dtype, device=W_UV.device)
     if lse is None and return_lse:
         lse = torch.empty((B, q_len, H), dtype=torch.float32, device=W_UV.device)
-    _check(lib().mla_merge_out_proj_multi(_dev(workspace, "workspace"),
-                                          workspace.numel() * workspace.element_size(), _dev(W_UV, "W_UV"),
-                                          _dev(o_lat, "o_lat"), _dev(lse, "lse"), _dev(out, "out"), B, q_len, H,
-                                          d_c, d_head, num_splits, _io_code(W_UV), int(flags),
-                                          _stream(workspace)), "mla_merge_out_proj_multi")
+    args = (_dev(workspace, "workspace"),
+            workspace.numel() * workspace.element_size(), _dev(W_UV, "W_UV"),
+            _dev(o_lat, "o_lat"), _dev(lse, "lse"), _dev(out, "out"), B, q_len, H,
+            d_c, d_head, num_splits, _io_code(W_UV), int(flags),
+            _stream(workspace))
+    _room(o_lat, B * q_len * H * d_c, W_UV.element_size(), "o_lat")
+    _room(out, B * q_len * H * d_head, W_UV.element_size(), "out")
+    _room(lse, B * q_len * H, 4, "lse")
+    _check(lib().mla_merge_out_proj_multi(*args), "mla_merge_out_proj_multi")
     return (o_lat, out, lse) if lse is not None else (o_lat, out)
 
 
@@ -406,10 +426,13 @@ def merge_partials(workspace: torch.Tensor, B: int, H: int, d_c: int, num_splits
         out = torch.empty((B, H, d_c), dtype=dtype, device=workspace.device)
     if lse is None and return_lse:
         lse = torch.empty((B, H), dtype=torch.float32, device=workspace.device)
-    _check(lib().mla_merge_partials(_dev(workspace, "workspace"),
-                                    workspace.numel() * workspace.element_size(),
-                                    _dev(out, "out"), _dev(lse, "lse"), B, H, d_c, num_splits,
-                                    _io_code(out), int(flags), _stream(workspace)), "mla_merge_partials")
+    args = (_dev(workspace, "workspace"),
+            workspace.numel() * workspace.element_size(),
+            _dev(out, "out"), _dev(lse, "lse"), B, H, d_c, num_splits,
+            _io_code(out), int(flags), _stream(workspace))
+    _room(out, B * H * d_c, out.element_size(), "out")
+    _room(lse, B * H, 4, "lse")
+    _check(lib().mla_merge_partials(*args), "mla_merge_partials")
     return (out, lse) if lse is not None else out
 
 
@@ -431,11 +454,14 @@ def merge_out_proj(workspace: torch.Tensor, W_UV: torch.Tensor, B: int, num_spli
         out = torch.empty((B, H, d_head), dtype=W_UV.dtype, device=W_UV.device)
     if lse is None and return_lse:
         lse = torch.empty((B, H), dtype=torch.float32, device=W_UV.device)
-    _check(lib().mla_merge_out_proj(_dev(workspace, "workspace"),
-                                    workspace.numel() * workspace.element_size(), _dev(W_UV, "W_UV"),
-                                    _dev(o_lat, "o_lat"), _dev(lse, "lse"), _dev(out, "out"), B, H, d_c,
-                                    d_head, num_splits, _io_code(W_UV), int(flags), _stream(workspace)),
-           "mla_merge_out_proj")
+    args = (_dev(workspace, "workspace"),
+            workspace.numel() * workspace.element_size(), _dev(W_UV, "W_UV"),
+            _dev(o_lat, "o_lat"), _dev(lse, "lse"), _dev(out, "out"), B, H, d_c,
+            d_head, num_splits, _io_code(W_UV), int(flags), _stream(workspace))
+    _room(o_lat, B * H * d_c, W_UV.element_size(), "o_lat")
+    _room(out, B * H * d_head, W_UV.element_size(), "out")
+    _room(lse, B * H, 4, "lse")
+    _check(lib().mla_merge_out_proj(*args), "mla_merge_out_proj")
     return (o_lat, out, lse) if lse is not None else (o_lat, out)
 
 
@@ -490,9 +516,15 @@ def cache_append(x: torch.Tensor, W_DKVR: torch.Tensor, kv_cache: torch.Tensor, 
     if workspace is None:
         workspace = torch.empty(max(16, append_workspace_bytes(B, D, d_c, d_rope, x.dtype)),
                                 dtype=torch.uint8, device=x.device)
-    _check(lib().mla_cache_append(_dev(x, "x"), _dev(W_DKVR, "W_DKVR"), _dev(kv_cache, "kv_cache"),
-                                  _dev(kv_scale, "kv_scale"), _dev(page_table, "page_table"),
-                                  _dev(positions, "positions"), _dev(workspace, "workspace"),
-                                  workspace.numel(), B, D, d_c, d_rope, page_size, num_pages,
-                                  page_table.shape[1], float(rope_base), _io_code(x),
-                                  _cache_code(kv_cache), _stream(x)), "mla_cache_append")
+    args = (_dev(x, "x"), _dev(W_DKVR, "W_DKVR"), _dev(kv_cache, "kv_cache"),
+            _dev(kv_scale, "kv_scale"), _dev(page_table, "page_table"),
+            _dev(positions, "positions"), _dev(workspace, "workspace"),
+            workspace.numel(), B, D, d_c, d_rope, page_size, num_pages,
+            page_table.shape[1], float(rope_base), _io_code(x),
+            _cache_code(kv_cache), _stream(x))
+    if page_table.dtype != torch.int32 or positions.dtype != torch.int32:
+        raise TypeError("page_table and positions must be int32")
+    if page_table.dim() != 2 or page_table.shape[0] < B or positions.numel() < B:
+        raise ValueError("page_table must be [B, max_pages_per_seq], positions [B]")
+    _room(kv_scale, num_pages * page_size, 4, "kv_scale")
+    _check(lib().mla_cache_append(*args), "mla_cache_append")
