@@ -9,10 +9,9 @@ namespace conv {
 // C[m, n] = scale * sum_k A(m, k) B(k, n), where A(m, k) = A[m*sAm + k*sAk] and
 // B(k, n) = B[k*sBk + n*sBn]; for each operand one of the two strides is 1.
 // scale = alpha, times *alpha_dev (dev_mode 1) or divided by it (dev_mode 2).
-// accumulate: C += instead of C =.
 // partial / partial_doubles: optional scratch; when the tile count alone cannot fill the chip and K is
 // deep, the K range is cut into slices whose products go to the scratch and are summed in a fixed order.
-// symmetric: B is A transposed (M = N, no accumulate); the tiles below the diagonal are written as the mirror image of
+// symmetric: B is A transposed (M = N); the tiles below the diagonal are written as the mirror image of
 // those above, which has their bits: an entry and its image sum the same products in the same order.
 struct GemmF64 {
     const double* A; long sAm, sAk;
@@ -21,7 +20,6 @@ struct GemmF64 {
     int M, N, K;
     double alpha;
     const double* alpha_dev; int dev_mode;
-    int accumulate;
     double* partial; size_t partial_doubles;
     int symmetric = 0;
     int lower = 0;          // B(k, n) = 0 for k > n (B is the transpose of a lower triangle): those k are left out; no partial

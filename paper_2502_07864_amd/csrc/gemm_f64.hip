@@ -116,7 +116,7 @@ __global__ __launch_bounds__(THREADS, 4) void gemm_f64_kernel(GemmF64 g, int til
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = (wave >> 1) * 32, wn = (wave & 1) * 64;
     const int li = lane & 15, kq = lane >> 4;
-    // a wavefront whose 64 x 64 part lies outside the matrix (edge tiles) stages data but multiplies nothing
+    // a wavefront whose 32 x 64 part lies outside the matrix (edge tiles) stages data but multiplies nothing
     const bool inside = m0 + wm < g.M && n0 + wn < g.N;
 
     f64x4 acc[2][4];
@@ -203,13 +203,13 @@ __global__ __launch_bounds__(THREADS, 4) void gemm_f64_kernel(GemmF64 g, int til
                 const int col = n0 + wn + j * 16 + li;
                 if (row < g.M && col < g.N) {
                     double* c = g.C + (long)row * g.ldc + col;
-                    *c = g.accumulate ? *c + scale * acc[i][j][r] : scale * acc[i][j][r];
+                    *c = scale * acc[i][j][r];
                     if (g.symmetric && tm != tn) g.C[(long)col * g.ldc + row] = scale * acc[i][j][r];
                 }
             }
 }
 
-// C (=|+=) scale * sum over the K slices, slices added in index order
+// C = scale * sum over the K slices, slices added in index order
 __global__ __launch_bounds__(256) void gemm_f64_reduce_kernel(GemmF64 g, int splits) {
     const long total = (long)g.M * g.N;
     double scale = g.alpha;
@@ -221,7 +221,7 @@ __global__ __launch_bounds__(256) void gemm_f64_reduce_kernel(GemmF64 g, int spl
         double a = 0.0;
         for (int z = 0; z < splits; ++z) a += g.partial[(size_t)z * total + idx];
         double* c = g.C + row * g.ldc + col;
-        *c = g.accumulate ? *c + scale * a : scale * a;
+        *c = scale * a;
         if (g.symmetric && row / BM != col / BN) g.C[col * g.ldc + row] = scale * a;
     }
 }
@@ -271,7 +271,7 @@ hipError_t run(GemmF64 g, hipStream_t s) {
 
 hipError_t launch_gemm_f64(const GemmF64& g, hipStream_t s) {
     if (g.M <= 0 || g.N <= 0 || g.K <= 0) return hipErrorInvalidValue;
-    if (g.symmetric && (g.M != g.N || g.accumulate)) return hipErrorInvalidValue;
+    if (g.symmetric && g.M != g.N) return hipErrorInvalidValue;
     if (g.lower && (g.partial || g.symmetric)) return hipErrorInvalidValue;
     const bool a_kc = g.sAk == 1, b_kc = g.sBk == 1;
     if ((!a_kc && g.sAm != 1) || (!b_kc && g.sBn != 1)) return hipErrorInvalidValue;
