@@ -9,10 +9,11 @@ using namespace mla::conv;
 namespace {
 
 constexpr int JACOBI_MAX_SWEEPS = 60;
-// Rayleigh-Ritz matrix of the power iteration (chip-wide solver above order 128): 6-8 sweeps are what it
-// takes; the sweeps enqueued beyond convergence still cost their launches (2.5 us each, 1150 per sweep at
-// order 576), so the cap is kept close.  A matrix that needs more is reported through info (-1).
-constexpr int RITZ_MAX_SWEEPS = 10;
+// Rayleigh-Ritz matrix of the power iteration (block solver above order 128).  After some iterations it is nearly
+// diagonal (6 or 7 sweeps); a block that was iterated little over a moment of low rank takes up to 14.  Every sweep
+// enqueued beyond convergence costs its launches, which return at once: 96 at order 768, 0.24 ms.  A matrix
+// that needs more is reported through info (-1).
+constexpr int RITZ_MAX_SWEEPS = 16;
 
 inline size_t align256(size_t b) { return (b + 255) & ~size_t(255); }
 inline int st(hipError_t e) { return e == hipSuccess ? MLA_OK : MLA_ERR_HIP; }

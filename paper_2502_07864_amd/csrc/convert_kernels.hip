@@ -827,7 +827,10 @@ static hipError_t launch_jacobi_wide(double* A, double* evals, double* V, void* 
 hipError_t launch_jacobi(double* A, double* evals, double* work, int* info, int batch, int m, int max_sweeps, hipStream_t s) {
     if (m > 128) {                                     // large matrices: the whole chip works on one at a time
         void* extra = work + (size_t)batch * m * m;
-        const int sweeps = std::min(max_sweeps, 16);   // every sweep enqueued costs its launches even after convergence
+        // every sweep enqueued costs its launches even after convergence (order 768: 0.24 ms).  Single rotations over the whole
+        // matrix took up to 16 where they converged; sweeps over pairs of blocks take as many or fewer on full, graded and
+        // nearly diagonal spectra, but up to 7 more on low ranks and multiple eigenvalues (rank 40 or 100 of 256: 12 and 17 to 20)
+        const int sweeps = std::min(max_sweeps, 24);
         for (int b = 0; b < batch; ++b) {
             hipError_t e = launch_jacobi_wide(A + (size_t)b * m * m, evals + (size_t)b * m, work + (size_t)b * m * m,
                                               extra, info + b, m, sweeps, s);

@@ -301,6 +301,38 @@ def test_sym_eig_block_edges(mla, batch, m):
         assert np.abs(evals[b] - np.linalg.eigvalsh(A[b])[::-1]).max() <= 1e-12 * norm
 
 
+@pytest.mark.parametrize("kind,m", [("rank", 256), ("rank", 144), ("clusters", 256)])
+def test_sym_eig_low_rank_and_multiple_eigenvalues_converge(mla, kind, m):
+    """Matrices of few distinct eigenvalues take the solver over pairs of blocks 15 to 20 sweeps, more than the 16 that
+    single rotations over the whole matrix needed at most: still converged, and as a Rayleigh-Ritz matrix too."""
+    import torch
+    from paper_2502_07864_amd import convert
+    r = np.random.default_rng(0)
+    mats = []
+    for k in ((10, 40, 100) if kind == "rank" else (2, 3, 5)):
+        if kind == "rank":
+            X = r.standard_normal((m, k))
+            A = X @ X.T
+        else:
+            q, _ = np.linalg.qr(r.standard_normal((m, m)))
+            d = np.repeat(np.arange(k, 0, -1.0), [m // k] * (k - 1) + [m - (k - 1) * (m // k)]) + 1e-6 * r.standard_normal(m)
+            A = (q * d) @ q.T
+        mats.append((A + A.T) / 2)
+    A = np.stack(mats)
+    evals, U, info = convert.sym_eig(torch.from_numpy(A).cuda())
+    evals, U, info = evals.cpu().numpy(), U.cpu().numpy(), info.cpu().numpy()
+    assert (info >= 1).all(), info
+    for b in range(len(A)):
+        norm = np.linalg.norm(A[b])
+        assert np.abs(U[b].T @ U[b] - np.eye(m)).max() <= 1e-12
+        assert np.abs(A[b] @ U[b] - U[b] * evals[b]).max() <= 1e-12 * norm
+    if kind == "rank":
+        # a block as wide as the space that is not iterated at all: the Rayleigh-Ritz matrix is a rotated S
+        ritz, _, info = convert.top_eig(torch.from_numpy(A[0]).cuda(), torch.from_numpy(r.standard_normal((m, m))).cuda(), 10, 0)
+        assert info[1].item() >= 1, info
+        assert np.abs(ritz.cpu().numpy()[:10] - np.linalg.eigvalsh(A[0])[::-1][:10]).max() <= 1e-10 * np.linalg.norm(A[0])
+
+
 # ------------------------------------------------------------------ cache append
 
 @pytest.mark.parametrize("B,D,d_c,cache", [(1, 32, 16, "bf16"), (15, 96, 512, "bf16"), (16, 4096, 512, "f32"),
