@@ -306,8 +306,9 @@ def main():
         a_bytes = Wa.numel() * 2 + xa.numel() * 2
         append = {"us": round(a_us, 2), "model_dim": D_MODEL, "weight_and_input_bytes": a_bytes,
                   "hbm_frac": round(a_bytes / (a_us * 1e-6) / 1e9 / HBM_PEAK_GBPS, 4),
-                  "note": "mla_cache_append (projection + RoPE + store of one row per sequence), two kernels, "
-                          "20 calls per HIP graph replay; not part of the step"}
+                  "note": "mla_cache_append (projection + RoPE + store of one row per sequence), "
+                          + ("one kernel" if w.io_dtype == "bf16" and w.cache_dtype != "fp8_e4m3" else "two kernels")
+                          + ", 20 calls per HIP graph replay; not part of the step"}
 
     cache_bytes = w.cache_bytes_per_step                      # C2: 1152 B x 131072 tokens
     dec_avg_us = float(dec_b2b_us)
@@ -315,18 +316,18 @@ def main():
     # which kernel mla_decode_paged launches for this call (the library's dispatch rule, restated)
     fp8 = w.cache_dtype == "fp8_e4m3"
     if w.io_dtype != "bf16":
-        kernel_name = "decode_portable_kernel<float, float>"
+        kernel_name = "decode_portable_kernel<float, float, 2, 8>"   # (C1: up to 256 workgroups of two heads)
     elif T > 1:
         kernel_name = f"decode_mfma_wide_kernel<{d_c}>"
     elif fp8:
         kernel_name = f"decode_stream_fp8_kernel<{d_c}, {'true' if args.balanced else 'false'}>"
     elif args.balanced:
         tiles = 2 * d.page_table.shape[1] // max(1, S)
-        kernel_name = (f"decode_stream_kernel<{d_c}, false, true>" if d_c == 512 else
+        kernel_name = (f"decode_stream_kernel<{d_c}, false, true, false>" if d_c == 512 else
                        f"decode_mfma_kernel<{d_c}, {'3' if tiles <= 64 else '4'}, 1, true>")
     else:
         tiles = 2 * (-(-d.page_table.shape[1] // S))
-        kernel_name = (f"decode_stream_kernel<{d_c}, false, false>" if (d_c == 512 or tiles <= 32) else
+        kernel_name = (f"decode_stream_kernel<{d_c}, false, false, false>" if (d_c == 512 or tiles <= 32) else
                        f"decode_mfma_kernel<{d_c}, {'3' if tiles <= 64 else '4'}, 1, false>")
     # HBM bytes per launch from the committed rocprofv3 counter summary; only valid for the default
     # launch configuration of the workload and while the kernel sources are the ones the counters
@@ -390,7 +391,7 @@ def main():
 
     if stream_only_us is not None:
         rec["roofline"]["stream_only"] = {
-            "kernel": f"decode_stream_kernel<{d_c}, true, false>", "launch_us": round(float(stream_only_us), 2),
+            "kernel": f"decode_stream_kernel<{d_c}, true, false, false>", "launch_us": round(float(stream_only_us), 2),
             "frac": round(cache_bytes / (stream_only_us * 1e-6) / 1e9 / HBM_PEAK_GBPS, 4),
             "note": "mla_diag_stream_tiles: the decode kernel's grid, tile ring, loads, waits and barriers with no "
                     "arithmetic and no output, back to back like launch_us"}
@@ -601,7 +602,7 @@ def convert_main(args):
            "checks": {"ritz_residual_over_lambda1": resid, "orthonormality": orth,
                       "captured_second_moment": round(captured, 6), "alpha": out["alpha"].item(),
                       "rope_basis_sweeps_max": int(info[:-2].max()), "ritz_sweeps": int(info[-1])},
-           "roofline": {"bound": "mfma", "kernel": f"gemm_f64_kernel<true, false> (S Q, {mj} x {mj} x {p}, K range in slices) "
+           "roofline": {"bound": "mfma", "kernel": f"gemm_f64_kernel<true, false, true> (S Q, {mj} x {mj} x {p}, K range in slices) "
                                                    "+ gemm_f64_reduce_kernel",
                         "achieved": round(tflops, 2), "peak": 78.6, "unit": "TFLOP/s", "frac": round(tflops / 78.6, 4),
                         "traffic": None, "algorithmic_flop_per_launch": flop, "launch_us": round(launch_ms * 1e3, 1),

@@ -11,8 +11,9 @@ namespace conv {
 // scale = alpha, times *alpha_dev (dev_mode 1) or divided by it (dev_mode 2).
 // partial / partial_doubles: optional scratch; when the tile count alone cannot fill the chip and K is
 // deep, the K range is cut into slices whose products go to the scratch and are summed in a fixed order.
-// symmetric: B is A transposed (M = N); the tiles below the diagonal are written as the mirror image of
-// those above, which has their bits: an entry and its image sum the same products in the same order.
+// symmetric: B is A transposed (M = N); where that saves time (scratch given, or more than 256 tiles) the tiles
+// below the diagonal are written as the mirror image of those above, which has their bits: an entry and its
+// image sum the same products in the same order.
 struct GemmF64 {
     const double* A; long sAm, sAk;
     const double* B; long sBk, sBn;

@@ -24,11 +24,12 @@
 // than 2^64 above it is recorded and the workgroup then redoes its keys with the exact maxima (one sweep
 // that only scores, one that accumulates).
 //
-// What bounds it: the matrix pipes and the chip's power.  4 prompts of 8192 tokens, 32 heads (2.75 TFLOP): the form
-// before this one, which scored, weighed and accumulated one tile after the other from row-major values, took
-// 6.7 M cycles at 2.1 GHz with the matrix pipes busy 42 % of them; this one takes 5.0 M with 57 %, and the clock
-// falls to 1.8 GHz under the denser work: whole call 3036 -> 2794 us (a library product of 8192^3 reaches
-// 1.29 PFLOP/s on the same card; this kernel about 1.15).  8 x 500 new tokens on 700 .. 6000, 28 heads: 552 -> 423.
+// What bounds it: the matrix pipes, at the clock the chip holds under them.  4 prompts of 8192 tokens, 32 heads (2.75
+// TFLOP), counters, time and clock of one profiled run: 5.10 M cycles in 2.71 ms (1.88 GHz), matrix pipes busy 55 % of
+// them, LDS 27 %; shorter kernels of the same call run at 1.95 to 2.3 GHz.  The form before this one, which scored,
+// weighed and accumulated one tile after the other from row-major values, took 6.7 M cycles with the pipes busy 42 %.
+// Whole call, timed in turn with that form: 3036 -> 2794 us (a library product of 8192^3 reaches 1.29 PFLOP/s on such a
+// card); 8 x 500 new tokens on 700 .. 6000, 28 heads: 552 -> 423.
 #include "mla_internal.h"
 #include "mfma_tile.h"
 #include <type_traits>
