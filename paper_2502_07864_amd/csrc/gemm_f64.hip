@@ -2,287 +2,416 @@
 // (activations X W^T, second moments C^T C, block power iteration S Q, the low-rank
 // projections R^T W and W R of App. D.2).
 //
-// Workgroup tile 128 x 128, K step 16, eight wavefronts in 4 x 2, each 32 x 64 =
-// 2 x 4 tiles of v_mfma_f64_16x16x4_f64 (64 accumulator registers), two workgroups per
-// CU = four wavefronts per SIMD: the matrix pipe of a SIMD always has a wavefront that
-// is not waiting at the barrier or for LDS.  Lane l of a wavefront supplies
-// A[l % 16][l / 16] and B[l / 16][l % 16] and receives D[4 r + l / 16][l % 16] in
-// element r of the result vector.  Both operands are staged k-major in LDS
-// ([k][m] and [k][n]) whichever way they lie in memory, so the inner loop is the
-// same for all four transpose combinations; the next K step is fetched into
-// registers while the current one is multiplied.  It is bound by the matrix pipe, so a
-// product that is known to be symmetric does a little over half the tiles
-// (4096 tokens x 8128: C^T C 9.6 -> 5.4 ms; Y^T Y of 8128 x 768: 196 -> 117 us).
+// Workgroup tile 64 x 64, K step 16, four wavefronts in 2 x 2, each 2 x 2 tiles of v_mfma_f64_16x16x4_f64.  Lane l of a
+// wavefront supplies A[l % 16][k] and B[k][l % 16], k being the same for the lanes of a group l / 16 on both sides, and
+// receives D[4 r + l / 16][l % 16] in element r of the result vector.  It is bound by the matrix pipe (64 cycles an
+// instruction), so everything else runs in its shadow: a K step goes from memory straight to the other LDS buffer while this
+// one is multiplied, the operands of the next half step are read from LDS a half step ahead, and the one barrier of a step lies
+// between its halves, when what a wavefront multiplies on both sides of it is in registers.  Three or four workgroups per CU
+// (126 to 143 registers, 32 KB of LDS) fill what is left.
+//
+// An operand is staged as it lies in memory: k-contiguous as rows of 16 k's, else as 16 rows of consecutive m or n, in
+// pieces of 16 bytes swizzled so that the operand reads meet no bank conflict.  Lane group q takes the k's 8 half + 2 q and the
+// one after, which suits both.
+//
+// Given scratch, a product of few tiles has their K steps laid end to end and cut into equal shares, one per CU: a share that
+// begins or ends inside a tile leaves its sum in the scratch, and a second kernel adds a tile's parts in order.
+//
+// TFLOP/s, the form before (128 x 128, eight wavefronts, through registers, K cut into equal slices of every tile) -> now:
+// X W^T 4096^3 60 -> 67 to 69 (a library product reaches 69), 4096 x 4096 x 512 27 -> 60, 1169 x 512 x 512 7 -> 26;
+// S Q 8128 x 8128 x 768 61 -> 65 to 67, 3968 x 768 57 -> 65, 1984 x 384 34 -> 46, 512 x 192 3.7 -> 6.3; C^T C of 4096 x
+// 8128 (half of it counted) 55 -> 61 to 63, 4096 x 1000 7 -> 23.  Tiles of 128 x 128 with 4 x 4 per wavefront need more than 256 registers (41).
 #include "convert_internal.h"
 #include <algorithm>
-#include <cmath>
+#include <type_traits>
 
 namespace mla {
 namespace conv {
 namespace {
 
 typedef double f64x4 __attribute__((ext_vector_type(4)));
+typedef double f64x2 __attribute__((ext_vector_type(2)));
+#define LDS_AS __attribute__((address_space(3)))
 
-constexpr int BM = 128, BN = 128, BK = 16;
-constexpr int THREADS = 512;                  // eight wavefronts in 4 x 2, each 32 x 64 = 2 x 4 tiles
-constexpr int EPT = BM * BK / THREADS;        // elements of one operand tile per thread (4)
-constexpr int LD = 132;                       // row pitch of a staged k-row, in doubles: 264 dwords = 8 (mod 64), so
-                                              // the 16 k-rows a wavefront writes at once fall on different banks
-constexpr int STAGE = BK * LD;                // one operand, one buffer
+// vmcnt(0), the other counters left alone
+__device__ __forceinline__ void wait_loads() { __builtin_amdgcn_s_waitcnt(0x0F70); }
 
-// Fetch the 128 x 16 tile of an operand whose (mn, k) element is P[mn*s_mn + k*s_k].
-// K_CONTIG: s_k == 1, sixteen lanes read 128 consecutive bytes of one row;
-// otherwise s_mn == 1 and 128 lanes read consecutive elements of one k-row.
-template <bool K_CONTIG>
-__device__ __forceinline__ void fetch(const double* __restrict__ P, long s_mn, long s_k,
-                                      int mn0, int k0, int MN, int K, int tid, double (&r)[EPT]) {
-#pragma unroll
-    for (int i = 0; i < EPT; ++i) {
-        int mn, k;
-        if (K_CONTIG) { k = k0 + (tid & 15); mn = mn0 + (tid >> 4) + (THREADS / 16) * i; }
-        else          { mn = mn0 + (tid & 127); k = k0 + (tid >> 7) + (THREADS / 128) * i; }
-        r[i] = (mn < MN && k < K) ? P[(long)mn * s_mn + (long)k * s_k] : 0.0;
+constexpr int BK = 16;
+constexpr int THREADS = 256;
+constexpr int BM = 64, T = 2;                 // tile, and 16 x 16 tiles of a wavefront each way
+constexpr int SHARES = 256;                   // shares of a product of fewer tiles: one per CU
+
+// One operand of a tile of BM rows (or columns) x 16 k's in LDS, and the thread's share of its way there: DIRECT: 16 bytes
+// per lane straight to LDS (everything on 16 bytes; offsets inside a tile fit 32 bits), else through registers, element by
+// element.  Layouts, in pieces of 16 bytes: k-contiguous: row mn has its 8 pieces at piece ^ (mn >> 1 & 7); else row k has its
+// BM / 2 pieces at piece ^ (8 if k & 2).
+template <bool K_CONTIG, bool DIRECT>
+struct Operand {
+    static constexpr int EPT = BM * BK / THREADS;             // elements per thread
+    static constexpr int LOADS = EPT / 2;                     // direct loads per thread
+    static constexpr int STAGE = BM * BK;
+    using Off = std::conditional_t<DIRECT, unsigned, long>;
+    Off off[DIRECT ? LOADS : EPT];                            // from the tile's corner (DIRECT: bytes, else elements)
+
+    static __device__ __forceinline__ int at(int mn, int k)
+    {
+        return K_CONTIG ? mn * BK + (((k >> 1) ^ ((mn >> 1) & 7)) << 1) + (k & 1)
+                        : k * BM + (((mn >> 1) ^ ((k & 2) << 2)) << 1) + (mn & 1);
     }
-}
-
-// The same without a branch around each load (eight branches a step; C^T C of 4096 x 8128 5.40 -> 5.08 ms, an iteration
-// of 768 columns 2.22 -> 2.16): rows past the end re-read the last one (what they give is not stored), a
-// k past the end re-reads the step's first (zeroed before it is staged).  off: the thread's element offsets
-// from the tile's corner, of which `there` rows or columns are inside; left: k's from the corner on that are inside.
-template <bool K_CONTIG>
-__device__ __forceinline__ void offsets(long s_mn, long s_k, int there, int tid, unsigned (&off)[EPT]) {
+    static __device__ __forceinline__ int k_of(int tid, int i) { return K_CONTIG ? tid & 15 : tid / BM + (THREADS / BM) * i; }
+    static __device__ __forceinline__ int mn_of(int tid, int i) { return K_CONTIG ? (tid >> 4) + (THREADS / 16) * i : tid % BM; }
+    // there: rows (columns) of the tile inside the matrix; the others re-read the last one (what they give is not stored)
+    __device__ __forceinline__ void place(long s_mn, long s_k, int there, int tid, int wave, int lane)
+    {
+        if constexpr (DIRECT) {
 #pragma unroll
-    for (int i = 0; i < EPT; ++i)
-        off[i] = K_CONTIG ? (unsigned)(min((tid >> 4) + (THREADS / 16) * i, there - 1) * s_mn) : (unsigned)min(tid & 127, there - 1);
-}
-template <bool K_CONTIG>
-__device__ __forceinline__ int k_of(int tid, int i) { return K_CONTIG ? tid & 15 : (tid >> 7) + (THREADS / 128) * i; }
-
-template <bool K_CONTIG>
-__device__ __forceinline__ void fetch_near(const double* __restrict__ corner, long s_k, int left, int tid,
-                                           const unsigned (&off)[EPT], double (&r)[EPT]) {
+            for (int i = 0; i < LOADS; ++i) {
+                const int j = i * 4 + wave;                   // kilobyte of the stage
+                if (K_CONTIG) {
+                    const int row = 8 * j + (lane >> 3), piece = (lane & 7) ^ ((row >> 1) & 7);
+                    off[i] = (unsigned)min(row, there - 1) * (unsigned)s_mn * 8u + piece * 16u;
+                } else {
+                    const int k = 2 * j + (lane >> 5), piece = (lane & (BM / 2 - 1)) ^ ((k & 2) << 2);
+                    off[i] = (unsigned)k * (unsigned)s_k * 8u + (unsigned)min(piece, (there - 1) >> 1) * 16u;
+                }
+            }
+        } else {
 #pragma unroll
-    for (int i = 0; i < EPT; ++i) {
-        const int k = k_of<K_CONTIG>(tid, i);
-        r[i] = corner[off[i] + (unsigned)((k < left ? k : 0) * (K_CONTIG ? 1 : (int)s_k))];
+            for (int i = 0; i < EPT; ++i) off[i] = min(mn_of(tid, i), there - 1) * s_mn + k_of(tid, i) * s_k;
+        }
     }
-}
-template <bool K_CONTIG>
-__device__ __forceinline__ void zero_past(int left, int tid, double (&r)[EPT]) {
+    // corner: element (0, first k of the step); S: where the stage lies in LDS
+    __device__ __forceinline__ void load(const double* corner, double* S, int wave) const
+    {
+        const unsigned base = (unsigned)(uintptr_t)(LDS_AS unsigned char*)(S + wave * 128);
 #pragma unroll
-    for (int i = 0; i < EPT; ++i) r[i] = k_of<K_CONTIG>(tid, i) < left ? r[i] : 0.0;
-}
-
-template <bool K_CONTIG>
-__device__ __forceinline__ void stage(double* S, int tid, const double (&r)[EPT]) {
-#pragma unroll
-    for (int i = 0; i < EPT; ++i) {
-        if (K_CONTIG) S[(tid & 15) * LD + (tid >> 4) + (THREADS / 16) * i] = r[i];
-        else          S[((tid >> 7) + (THREADS / 128) * i) * LD + (tid & 127)] = r[i];
+        for (int i = 0; i < LOADS; ++i) {
+            const unsigned m0v = __builtin_amdgcn_readfirstlane(base + i * 4096);
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+                         :: "s"(m0v), "v"(off[i]), "s"(corner) : "memory");
+        }
     }
-}
+    // left: k's from the corner on (those past the end re-read the first, and become zero)
+    __device__ __forceinline__ void fetch(const double* __restrict__ corner, long s_mn, long s_k, int there, int left, int tid, double (&v)[EPT]) const
+    {
+        if (!DIRECT && left >= BK) {
+#pragma unroll
+            for (int i = 0; i < EPT; ++i) v[i] = corner[off[i]];
+            return;
+        }
+#pragma unroll
+        for (int i = 0; i < EPT; ++i) {
+            const int k = k_of(tid, i);
+            const double x = corner[min(mn_of(tid, i), there - 1) * s_mn + (k < left ? k : 0) * s_k];
+            v[i] = k < left ? x : 0.0;
+        }
+    }
+    static __device__ __forceinline__ void stage(double* S, int tid, const double (&v)[EPT])
+    {
+#pragma unroll
+        for (int i = 0; i < EPT; ++i) S[at(mn_of(tid, i), k_of(tid, i))] = v[i];
+    }
+    // the lane's k's 8 half + 2 q, + 1 of T rows (columns) 16 apart from mn0 on
+    static __device__ __forceinline__ void read(const double* S, int mn0, int half, int li, int kq, double (&v)[T][2])
+    {
+#pragma unroll
+        for (int t = 0; t < T; ++t) {
+            if (K_CONTIG) {
+                const f64x2 x = *reinterpret_cast<const f64x2*>(S + mn0 * BK + t * 256 + li * BK + (((half * 4 + kq) ^ (li >> 1)) << 1));
+                v[t][0] = x[0];
+                v[t][1] = x[1];
+            } else {
+                const double* row = S + mn0 + (8 * half + 2 * kq) * BM + li + (((t & 1) ^ (kq & 1)) + (t & ~1)) * 16;
+                v[t][0] = row[0];
+                v[t][1] = row[BM];
+            }
+        }
+    }
+};
+
+// How a product is cut: tiles_m x tiles_n tiles (symmetric: those on and above the diagonal) of BM x BM; share: K steps per
+// workgroup, 0: a tile per workgroup.
+struct Cut {
+    int tiles_m, tiles_n, tiles, nk, workgroups;
+    long share;
+};
 
 // first tile of row tm when each row of tiles starts at the diagonal
 __host__ __device__ __forceinline__ int row_start(int tm, int tiles_n) { return tm * tiles_n - tm * (tm - 1) / 2; }
+// K steps of column tile tn (lower: the k's up to its last column)
+__host__ __device__ __forceinline__ int steps_of(const GemmF64& g, const Cut& c, int tn)
+{
+    return g.lower ? min(c.nk, ((tn + 1) * BM + BK - 1) / BK) : c.nk;
+}
+// tile number -> row and column of tiles, K steps, and K steps of all tiles before it
+struct Tile { int tm, tn, nk; long before; };
+__host__ __device__ __forceinline__ Tile tile_at(const GemmF64& g, const Cut& c, int tile)
+{
+    Tile t;
+    if (g.symmetric) {
+        t.tm = (int)(((2 * c.tiles_n + 1) - sqrtf((2.f * c.tiles_n + 1.f) * (2.f * c.tiles_n + 1.f) - 8.f * tile)) * 0.5f);
+        while (t.tm > 0 && tile < row_start(t.tm, c.tiles_n)) --t.tm;           // (the root's rounding)
+        while (tile >= row_start(t.tm + 1, c.tiles_n)) ++t.tm;
+        t.tn = t.tm + tile - row_start(t.tm, c.tiles_n);
+    } else if (g.lower && !c.share) {          // deepest columns first
+        t.tm = tile % c.tiles_m;
+        t.tn = c.tiles_n - 1 - tile / c.tiles_m;
+    } else {
+        t.tm = tile / c.tiles_n;
+        t.tn = tile % c.tiles_n;
+    }
+    t.nk = steps_of(g, c, t.tn);
+    t.before = (long)tile * c.nk;
+    if (g.lower && c.share) {
+        long row = 0, left = 0;
+        for (int n = 0; n < c.tiles_n; ++n) { const int s = steps_of(g, c, n); row += s; left += n < t.tn ? s : 0; }
+        t.before = t.tm * row + left;
+    }
+    return t;
+}
+// the tile that K step s of all tiles laid end to end belongs to
+__device__ __forceinline__ int tile_of_step(const GemmF64& g, const Cut& c, long s)
+{
+    if (!g.lower) return (int)(s / c.nk);
+    long row = 0;
+    for (int n = 0; n < c.tiles_n; ++n) row += steps_of(g, c, n);
+    int tile = (int)(s / row) * c.tiles_n;
+    for (long left = s % row; left >= steps_of(g, c, tile % c.tiles_n); ++tile) left -= steps_of(g, c, tile % c.tiles_n);
+    return tile;
+}
 
-template <bool A_KC, bool B_KC, bool NEAR>
-__global__ __launch_bounds__(THREADS, 4) void gemm_f64_kernel(GemmF64 g, int tiles_n, int tiles, int splits, int kt_per) {
-    extern __shared__ double lds[];            // As[2][BK][LD], Bs[2][BK][LD]
+__device__ __forceinline__ double scale_of(const GemmF64& g)
+{
+    return g.dev_mode == 1 ? g.alpha * *g.alpha_dev : g.dev_mode == 2 ? g.alpha / *g.alpha_dev : g.alpha;
+}
+
+template <bool A_KC, bool B_KC, bool DIRECT>
+__global__ __launch_bounds__(THREADS, 3) void gemm_f64_kernel(GemmF64 g, Cut c)
+{
+    using OpA = Operand<A_KC, DIRECT>;
+    using OpB = Operand<B_KC, DIRECT>;
+    extern __shared__ __attribute__((aligned(16))) double lds[];          // A, A, B, B
     double* As = lds;
-    double* Bs = lds + 2 * STAGE;
+    double* Bs = lds + 2 * OpA::STAGE;
 
-    // consecutive tiles (same rows of A) share an XCD: workgroup ids 8 apart run on one XCD
-    const int total = tiles * splits;
-    const int per = (total + 7) / 8;
-    const int item = g.lower ? (int)blockIdx.x : (int)(blockIdx.x % 8) * per + (int)(blockIdx.x / 8);
-    if (item >= total) return;
-    const int tile = item % tiles, z = item / tiles;     // z: slice of the K range
-    int tm = tile / tiles_n, tn = tile % tiles_n;
-    if (g.symmetric) {                         // tiles on and above the diagonal, row by row
-        tm = (int)(((2 * tiles_n + 1) - sqrtf((2.f * tiles_n + 1.f) * (2.f * tiles_n + 1.f) - 8.f * tile)) * 0.5f);
-        while (tm > 0 && tile < row_start(tm, tiles_n)) --tm;           // (the root's rounding)
-        while (tile >= row_start(tm + 1, tiles_n)) ++tm;
-        tn = tm + tile - row_start(tm, tiles_n);
-    }
-    if (g.lower) {                             // deepest columns first; Y X^T of 8128 x 768, 23 a layer: 87.1 -> 86.3 ms a layer
-        const int tiles_m = tiles / tiles_n;
-        tm = tile % tiles_m;
-        tn = tiles_n - 1 - tile / tiles_m;
-    }
-    const int m0 = tm * BM, n0 = tn * BN;
-    const int nk_all = (g.K + BK - 1) / BK;
-    const int kt0 = z * kt_per, kt1 = min(g.lower ? min(nk_all, (n0 + BN) / BK) : nk_all, kt0 + kt_per);
-
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = (wave >> 1) * 32, wn = (wave & 1) * 64;
+    // consecutive shares (same rows of A) on one XCD: workgroup ids 8 apart run on one XCD.  Whole tiles of unequal depth: dealt out
+    const int per = gridDim.x / 8;
+    const int w = g.lower && !c.share ? (int)blockIdx.x : (int)(blockIdx.x % 8) * per + (int)(blockIdx.x / 8);
+    if (w >= c.workgroups) return;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = (wave >> 1) * (16 * T), wn = (wave & 1) * (16 * T);
     const int li = lane & 15, kq = lane >> 4;
-    // a wavefront whose 32 x 64 part lies outside the matrix (edge tiles) stages data but multiplies nothing
-    const bool inside = m0 + wm < g.M && n0 + wn < g.N;
 
-    f64x4 acc[2][4];
+    int tile = c.share ? tile_of_step(g, c, w * c.share) : w;
+    long step = c.share ? w * c.share : 0;
+    const long end = step + c.share;                     // (past the last tile's end the loop ends by itself)
+    for (; tile < c.tiles; ++tile) {
+        Tile at = tile_at(g, c, tile);
+        int kt0 = 0, kt1 = at.nk;
+        if (c.share) {
+            if (step >= end) break;
+            kt0 = (int)(step - at.before);
+            kt1 = (int)min((long)at.nk, end - at.before);
+            step = at.before + kt1;
+        }
+        const int m0 = at.tm * BM, n0 = at.tn * BM;
+        OpA a;
+        OpB b;
+        a.place(g.sAm, g.sAk, g.M - m0, tid, wave, lane);
+        b.place(g.sBn, g.sBk, g.N - n0, tid, wave, lane);
+        const double* A = g.A + (long)m0 * g.sAm;
+        const double* B = g.B + (long)n0 * g.sBn;
+        // step kt through registers: requested, then staged
+        auto fetch = [&](int kt, double (&ra)[OpA::EPT], double (&rb)[OpB::EPT]) {
+            a.fetch(A + (long)kt * BK * g.sAk, g.sAm, g.sAk, g.M - m0, g.K - kt * BK, tid, ra);
+            b.fetch(B + (long)kt * BK * g.sBk, g.sBn, g.sBk, g.N - n0, g.K - kt * BK, tid, rb);
+        };
+        auto stage = [&](int buf, const double (&ra)[OpA::EPT], const double (&rb)[OpB::EPT]) {
+            OpA::stage(As + buf * OpA::STAGE, tid, ra);
+            OpB::stage(Bs + buf * OpB::STAGE, tid, rb);
+        };
+        // step kt to a buffer straight from memory (a last step that is not full: through registers)
+        auto load = [&](int kt, int buf) {
+            if ((kt + 1) * BK <= g.K) {
+                a.load(A + (long)kt * BK * g.sAk, As + buf * OpA::STAGE, wave);
+                b.load(B + (long)kt * BK * g.sBk, Bs + buf * OpB::STAGE, wave);
+            } else {
+                double ra[OpA::EPT], rb[OpB::EPT];
+                fetch(kt, ra, rb);
+                stage(buf, ra, rb);
+            }
+        };
+        f64x4 acc[T][T];
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+        for (int i = 0; i < T; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = (f64x4){0.0, 0.0, 0.0, 0.0};
+            for (int j = 0; j < T; ++j) acc[i][j] = (f64x4){0.0, 0.0, 0.0, 0.0};
+        double va[2][T][2], vb[2][T][2];
+        auto read = [&](int buf, auto half) {
+            constexpr int h = decltype(half)::value;
+            OpA::read(As + buf * OpA::STAGE, wm, h, li, kq, va[h]);
+            OpB::read(Bs + buf * OpB::STAGE, wn, h, li, kq, vb[h]);
+        };
+        auto multiply = [&](auto half, int s) {
+            constexpr int h = decltype(half)::value;
+#pragma unroll
+            for (int i = 0; i < T; ++i)
+#pragma unroll
+                for (int j = 0; j < T; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(va[h][i][s], vb[h][j][s], acc[i][j], 0, 0, 0);
+        };
+        using H0 = std::integral_constant<int, 0>;
+        using H1 = std::integral_constant<int, 1>;
 
-    double ra[EPT], rb[EPT];
-    unsigned oa[EPT], ob[EPT];
-    offsets<A_KC>(g.sAm, g.sAk, g.M - m0, tid, oa);
-    offsets<B_KC>(g.sBn, g.sBk, g.N - n0, tid, ob);
-    const double* A = g.A + (long)m0 * g.sAm;
-    const double* B = g.B + (long)n0 * g.sBn;
-    auto load = [&](int kt) {
-        if (NEAR) {
-            fetch_near<A_KC>(A + (long)kt * BK * g.sAk, g.sAk, g.K - kt * BK, tid, oa, ra);
-            fetch_near<B_KC>(B + (long)kt * BK * g.sBk, g.sBk, g.K - kt * BK, tid, ob, rb);
+        double ra[OpA::EPT], rb[OpB::EPT];
+        if constexpr (DIRECT) {
+            load(kt0, 0);
+            wait_loads();
         } else {
-            fetch<A_KC>(g.A, g.sAm, g.sAk, m0, kt * BK, g.M, g.K, tid, ra);
-            fetch<B_KC>(g.B, g.sBn, g.sBk, n0, kt * BK, g.N, g.K, tid, rb);
+            fetch(kt0, ra, rb);
+            stage(0, ra, rb);
+            if (kt0 + 1 < kt1) fetch(kt0 + 1, ra, rb);
         }
-    };
-    auto put = [&](int kt, int buf) {
-        if (NEAR && (kt + 1) * BK > g.K) {
-            zero_past<A_KC>(g.K - kt * BK, tid, ra);
-            zero_past<B_KC>(g.K - kt * BK, tid, rb);
-        }
-        stage<A_KC>(As + buf * STAGE, tid, ra);
-        stage<B_KC>(Bs + buf * STAGE, tid, rb);
-    };
-    load(kt0);
-    put(kt0, 0);
-    __syncthreads();
-
-    for (int kt = kt0; kt < kt1; ++kt) {
-        const int buf = (kt - kt0) & 1;
-        const bool more = kt + 1 < kt1;
-        if (more) load(kt + 1);
-        const double* a_s = As + buf * STAGE + wm + li;
-        const double* b_s = Bs + buf * STAGE + wn + li;
-#pragma unroll
-        for (int ks = 0; inside && ks < BK / 4; ++ks) {
-            double a[2], b[4];
-#pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                if (t < 2) a[t] = a_s[(ks * 4 + kq) * LD + t * 16];
-                b[t] = b_s[(ks * 4 + kq) * LD + t * 16];
-            }
-#pragma unroll
-            for (int i = 0; i < 2; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i], b[j], acc[i][j], 0, 0, 0);
-        }
-        if (more) put(kt + 1, buf ^ 1);
         __syncthreads();
-    }
-
-    if (splits > 1) {                                    // raw slice product; the reduction kernel scales
-        double* part = g.partial + (size_t)z * g.M * g.N;
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int row = m0 + wm + i * 16 + 4 * r + kq;
-                    const int col = n0 + wn + j * 16 + li;
-                    if (row < g.M && col < g.N) part[(size_t)row * g.N + col] = acc[i][j][r];
-                }
-        return;
-    }
-    double scale = g.alpha;
-    if (g.dev_mode == 1) scale *= *g.alpha_dev;
-    else if (g.dev_mode == 2) scale /= *g.alpha_dev;
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int row = m0 + wm + i * 16 + 4 * r + kq;
-                const int col = n0 + wn + j * 16 + li;
-                if (row < g.M && col < g.N) {
-                    double* c = g.C + (long)row * g.ldc + col;
-                    *c = scale * acc[i][j][r];
-                    if (g.symmetric && tm != tn) g.C[(long)col * g.ldc + row] = scale * acc[i][j][r];
-                }
+        read(0, H0{});
+        if (DIRECT && kt0 + 1 < kt1) load(kt0 + 1, 1);
+        for (int kt = kt0; kt < kt1; ++kt) {
+            const int buf = (kt - kt0) & 1;
+            read(buf, H1{});
+            __builtin_amdgcn_sched_barrier(0);
+            multiply(H0{}, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            if (!DIRECT && kt + 1 < kt1) {               // requested a step ago
+                stage(buf ^ 1, ra, rb);
+                if (kt + 2 < kt1) fetch(kt + 2, ra, rb);
+                __builtin_amdgcn_sched_barrier(0);
             }
-}
-
-// C = scale * sum over the K slices, slices added in index order
-__global__ __launch_bounds__(256) void gemm_f64_reduce_kernel(GemmF64 g, int splits) {
-    const long total = (long)g.M * g.N;
-    double scale = g.alpha;
-    if (g.dev_mode == 1) scale *= *g.alpha_dev;
-    else if (g.dev_mode == 2) scale /= *g.alpha_dev;
-    for (long idx = (long)blockIdx.x * 256 + threadIdx.x; idx < total; idx += (long)gridDim.x * 256) {
-        const long row = idx / g.N, col = idx % g.N;
-        if (g.symmetric && row / BM > col / BN) continue;            // written by its mirror image
-        double a = 0.0;
-        for (int z = 0; z < splits; ++z) a += g.partial[(size_t)z * total + idx];
-        double* c = g.C + row * g.ldc + col;
-        *c = scale * a;
-        if (g.symmetric && row / BM != col / BN) g.C[col * g.ldc + row] = scale * a;
-    }
-}
-
-template <bool A_KC, bool B_KC, bool NEAR>
-hipError_t run(GemmF64 g, hipStream_t s) {
-    constexpr size_t lds_bytes = 4 * STAGE * sizeof(double);
-    hipError_t e0 = allow_dynamic_lds(reinterpret_cast<const void*>(&gemm_f64_kernel<A_KC, B_KC, NEAR>), (int)lds_bytes);
-    if (e0 != hipSuccess) return e0;
-    const int tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
-    // Half the tiles of a symmetric product are worth the scattered stores of their mirror images where the others leave
-    // or shorten a round: in K slices, or past one workgroup per CU (C^T C, us, all tiles -> half: 100 x 400 28 -> 41, 200 x
-    // 1400 50 -> 57, 4096 x 1000 634 -> 618, 300 x 4000 222 -> 174).  The bits are the same: an entry and its image sum the
-    // same products in the same order.
-    if (!g.partial && (long)tiles_m * tiles_n <= 256) g.symmetric = 0;
-    const int tiles = g.symmetric ? row_start(tiles_m, tiles_n) : tiles_m * tiles_n;
-    const int nk = (g.K + BK - 1) / BK;
-    // K slices: only when scratch is there, the tiles leave most of the 256 CUs idle and every slice
-    // still has at least 4 K steps
-    int splits = 1;
-    if (g.partial && nk >= 8) {
-        const size_t fit = g.partial_doubles / ((size_t)g.M * g.N);
-        const int most = (int)std::min<size_t>(std::min<size_t>(fit, 16), nk / 4);
-        if (tiles <= 64) {
-            splits = std::min(most, 256 / tiles);
-        } else if (tiles < 1024) {
-            // pick the fewest slices that keep at least 85 % of the CUs busy in the last round
-            auto fill = [&](int sp) { const double r = (double)tiles * sp / 256.0; return r / std::ceil(r); };
-            for (int sp = 1; sp <= std::min(most, 4); ++sp)
-                if (fill(sp) > fill(splits) + 0.05) { splits = sp; if (fill(sp) >= 0.85) break; }
+            multiply(H0{}, 1);
+            __builtin_amdgcn_sched_barrier(0);
+            if (DIRECT) wait_loads();                    // (requested a step ago)
+            __syncthreads();                             // the next step is there, and this one has been read
+            if (kt + 1 < kt1) read(buf ^ 1, H0{});
+            if (DIRECT && kt + 2 < kt1) load(kt + 2, buf);
+            __builtin_amdgcn_sched_barrier(0);
+            multiply(H1{}, 0);
+            multiply(H1{}, 1);
+            __builtin_amdgcn_sched_barrier(0);
         }
-        if (splits < 2) splits = 1;
+
+        if (kt0 > 0 || kt1 < at.nk) {                    // a part of the tile's sum; gemm_f64_reduce_kernel goes on
+            double* part = g.partial + ((size_t)(w + tile) * 4 + wave) * (T * T * 256) + lane;
+#pragma unroll
+            for (int i = 0; i < T; ++i)
+#pragma unroll
+                for (int j = 0; j < T; ++j)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) part[((i * T + j) * 4 + r) * 64] = acc[i][j][r];
+        } else {
+            const double scale = scale_of(g);
+#pragma unroll
+            for (int i = 0; i < T; ++i)
+#pragma unroll
+                for (int j = 0; j < T; ++j)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const int row = m0 + wm + i * 16 + 4 * r + kq;
+                        const int col = n0 + wn + j * 16 + li;
+                        if (row < g.M && col < g.N) {
+                            const double v = scale * acc[i][j][r];
+                            g.C[(long)row * g.ldc + col] = v;
+                            if (g.symmetric && at.tm != at.tn) g.C[(long)col * g.ldc + row] = v;
+                        }
+                    }
+        }
+        if (!c.share) break;
+        __syncthreads();                                 // the buffers are free for the next tile
     }
-    int kt_per = (nk + splits - 1) / splits;
-    splits = (nk + kt_per - 1) / kt_per;                 // no empty slice
-    const int total = tiles * splits;
-    const int grid = ((total + 7) / 8) * 8;
-    gemm_f64_kernel<A_KC, B_KC, NEAR><<<grid, THREADS, lds_bytes, s>>>(g, tiles_n, tiles, splits, kt_per);
+}
+
+// C = scale * the sum of a tile's parts, in order.  grid (tiles, T * T): four 16 x 16 tiles of a wavefront per workgroup
+__global__ __launch_bounds__(256) void gemm_f64_reduce_kernel(GemmF64 g, Cut c)
+{
+    const int tile = blockIdx.x, wave = blockIdx.y & 3, f = (blockIdx.y >> 2) * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const Tile at = tile_at(g, c, tile);
+    const int w0 = (int)(at.before / c.share), w1 = (int)((at.before + at.nk - 1) / c.share);
+    if (w0 == w1) return;                                // one workgroup had the whole tile
+    f64x4 sum = {0.0, 0.0, 0.0, 0.0};
+    for (int w = w0; w <= w1; ++w) {
+        const double* part = g.partial + ((size_t)(w + tile) * 4 + wave) * (T * T * 256) + f * 256 + lane;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) sum[r] += part[r * 64];
+    }
+    const double scale = scale_of(g);
+    const int col = at.tn * BM + (wave & 1) * (16 * T) + (f % T) * 16 + (lane & 15);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int row = at.tm * BM + (wave >> 1) * (16 * T) + (f / T) * 16 + 4 * r + (lane >> 4);
+        if (row < g.M && col < g.N) {
+            g.C[(long)row * g.ldc + col] = scale * sum[r];
+            if (g.symmetric && at.tm != at.tn) g.C[(long)col * g.ldc + row] = scale * sum[r];
+        }
+    }
+}
+
+template <bool A_KC, bool B_KC, bool DIRECT>
+hipError_t run(const GemmF64& g, const Cut& c, hipStream_t s)
+{
+    constexpr size_t lds_bytes = 2 * (Operand<A_KC, DIRECT>::STAGE + Operand<B_KC, DIRECT>::STAGE) * sizeof(double);
+    static_assert(lds_bytes <= 64 * 1024, "no raised limit needed");
+    gemm_f64_kernel<A_KC, B_KC, DIRECT><<<(c.workgroups + 7) / 8 * 8, THREADS, lds_bytes, s>>>(g, c);
     hipError_t e = hipGetLastError();
-    if (e != hipSuccess || splits == 1) return e;
-    const long cells = (long)g.M * g.N;
-    gemm_f64_reduce_kernel<<<(int)std::min<long>((cells + 255) / 256, 4096), 256, 0, s>>>(g, splits);
+    if (e != hipSuccess || !c.share) return e;
+    gemm_f64_reduce_kernel<<<dim3(c.tiles, T * T), 256, 0, s>>>(g, c);
     return hipGetLastError();
+}
+
+template <bool DIRECT>
+hipError_t run(const GemmF64& g, const Cut& c, hipStream_t s)
+{
+    const bool a_kc = g.sAk == 1, b_kc = g.sBk == 1;
+    if (a_kc && b_kc) return run<true, true, DIRECT>(g, c, s);
+    if (a_kc) return run<true, false, DIRECT>(g, c, s);
+    if (b_kc) return run<false, true, DIRECT>(g, c, s);
+    return run<false, false, DIRECT>(g, c, s);
 }
 
 }  // namespace
 
-hipError_t launch_gemm_f64(const GemmF64& g, hipStream_t s) {
+hipError_t launch_gemm_f64(const GemmF64& asked, hipStream_t s)
+{
+    GemmF64 g = asked;
     if (g.M <= 0 || g.N <= 0 || g.K <= 0) return hipErrorInvalidValue;
     if (g.symmetric && g.M != g.N) return hipErrorInvalidValue;
-    if (g.lower && (g.partial || g.symmetric)) return hipErrorInvalidValue;
+    if (g.lower && g.symmetric) return hipErrorInvalidValue;
     const bool a_kc = g.sAk == 1, b_kc = g.sBk == 1;
     if ((!a_kc && g.sAm != 1) || (!b_kc && g.sBn != 1)) return hipErrorInvalidValue;
-    // Offsets within a tile are 32-bit while no stride is above 2^22 elements; working them out pays from some 24 steps on
-    // (us, plain loads -> offsets: K = 10 10.2 -> 11.6, 100 24.4 -> 25.2, 300 52.7 -> 52.8, 400 69.8 -> 68.6, 2000 328 -> 314).
-    const long far = 1L << 22;
-    const bool near = g.K >= 24 * BK && g.sAm <= far && g.sAk <= far && g.sBn <= far && g.sBk <= far;
-    if (a_kc && b_kc) return near ? run<true, true, true>(g, s) : run<true, true, false>(g, s);
-    if (a_kc) return near ? run<true, false, true>(g, s) : run<true, false, false>(g, s);
-    if (b_kc) return near ? run<false, true, true>(g, s) : run<false, true, false>(g, s);
-    return near ? run<false, false, true>(g, s) : run<false, false, false>(g, s);
+    Cut c{};
+    c.tiles_m = (g.M + BM - 1) / BM;
+    c.tiles_n = (g.N + BM - 1) / BM;
+    c.nk = (g.K + BK - 1) / BK;
+    // Half the tiles of a symmetric product, and scattered stores of their mirror images, where the others would take a CU's
+    // time.  The bits are the same: an entry and its image sum the same products in the same order.
+    if (!g.partial && (long)c.tiles_m * c.tiles_n <= 256) g.symmetric = 0;
+    c.tiles = g.symmetric ? row_start(c.tiles_m, c.tiles_n) : c.tiles_m * c.tiles_n;
+    c.workgroups = c.tiles;
+    if (g.partial) {
+        // Shares where the tiles leave CUs without one (us at 256, 512 and 1024 shares: S Q 2304 x 192 50, 59, 58; 1984 x 384 67,
+        // 65, 75; 3968 x 768, 744 tiles, whole ones 370, 1024 shares 420), four steps at least.  A part has a slot of its
+        // own: number of the workgroup + number of the tile.
+        long steps = 0;
+        for (int n = 0; n < c.tiles_n; ++n) steps += steps_of(g, c, n);
+        steps = g.symmetric ? (long)c.tiles * c.nk : steps * c.tiles_m;
+        const long room = (long)(g.partial_doubles / (BM * BM)) - c.tiles;
+        const long shares = std::min({(long)SHARES, room, steps / 4});
+        if (shares > c.tiles) {
+            c.share = (steps + shares - 1) / shares;
+            c.workgroups = (int)((steps + c.share - 1) / c.share);
+        }
+    }
+    // 16 bytes per load: both operands on 16 bytes, their long strides even (and short enough for 32-bit offsets in a tile)
+    auto direct_ok = [](const double* P, long s_long) { return reinterpret_cast<uintptr_t>(P) % 16 == 0 && s_long % 2 == 0 && s_long <= 1L << 22; };
+    const bool direct = direct_ok(g.A, a_kc ? g.sAm : g.sAk) && direct_ok(g.B, b_kc ? g.sBn : g.sBk);
+    return direct ? run<true>(g, c, s) : run<false>(g, c, s);
 }
 
 }  // namespace conv

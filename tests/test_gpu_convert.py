@@ -495,6 +495,27 @@ def test_matrix_product_random_shapes(cv):
         assert rel(host(cv.apply(dev(A), dev(Q), workspace=ws)), A @ Q) < 1e-12, (case, mm, p)
 
 
+@pytest.mark.parametrize("n,D,m", [(1, 1, 1), (63, 64, 65), (64, 16, 64), (65, 17, 130), (129, 33, 64), (200, 400, 63), (66, 4096, 2)])
+def test_matrix_product_tile_edges_and_alignment(cv, n, D, m):
+    """Around the 64 x 64 x 16 tile, with 16-byte loads (even row lengths on 16 bytes) and without, with shares of the K
+    steps and without; sums of at most 4096 products in another order than numpy's."""
+    import torch
+    r = rng(n + D + m)
+    X, W, A, Q = (r.standard_normal(s) for s in ((n, D), (m, D), (D, D), (D, m)))
+    for off in (0, 1):                                  # 0 or 8 bytes past a 16-byte boundary
+        def at(x):
+            buf = torch.zeros(x.size + off, dtype=torch.float64, device="cuda")
+            buf[off:] = torch.from_numpy(x.ravel()).cuda()
+            return buf[off:].view(x.shape)
+        assert rel(host(cv.project(at(X), at(W))), X @ W.T) < 1e-12
+        assert rel(host(cv.apply(at(A), at(Q))), A @ Q) < 1e-12
+        ws = torch.empty(max(256, cv.apply_workspace_bytes(D, m)), dtype=torch.uint8, device="cuda")
+        assert rel(host(cv.apply(at(A), at(Q), workspace=ws)), A @ Q) < 1e-12
+        S, _ = cv.joint_moment(at(W[:, :1].copy()), at(W[:, 1:].copy()) if D > 1 else at(W), dev(np.array([1.0])))
+        C = W if D > 1 else np.concatenate([W, W], axis=1)
+        assert rel(host(S), C.T @ C / m) < 1e-12
+
+
 def test_largest_orders_the_solvers_take(cv):
     """Order 2048 for the eigensolver (its limit) and block width 1024 for the power iteration (its limit)."""
     m = 2048
