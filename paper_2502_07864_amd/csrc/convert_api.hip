@@ -103,11 +103,11 @@ int top_eig(const double* S, const double* Q0, double* evals, double* R, const T
 }
 
 struct LayerWs {
-    double *K, *sigma_work, *W_K_rot, *E, *E_rot, *C, *norms, *S, *W_cat;
+    double *K, *sigma_work, *W_K_rot, *C, *norms, *S, *W_cat;
     void* top; size_t top_bytes;
     size_t bytes;
 };
-LayerWs layer_ws(void* base, int n, int D, int g, int h, int d, int M, int keep, int p) {
+LayerWs layer_ws(void* base, int n, int D, int g, int d, int M, int keep, int p) {
     LayerWs w{};
     size_t off = 0;
     auto take = [&](size_t count) { double* ptr = base ? reinterpret_cast<double*>(static_cast<char*>(base) + off) : nullptr;
@@ -116,8 +116,6 @@ LayerWs layer_ws(void* base, int n, int D, int g, int h, int d, int M, int keep,
     w.K = take((size_t)n * gd);
     w.sigma_work = take(jacobi_work_bytes(d / (2 * M), (int)Mg) / sizeof(double));
     w.W_K_rot = take(gd * D);
-    w.E = take(gd * (size_t)h * d);
-    w.E_rot = take(gd * (size_t)h * d);
     w.C = take((size_t)n * mj);
     w.norms = take(2 * (size_t)n);
     w.S = take(mj * mj);
@@ -231,7 +229,7 @@ int mla_conv_apply(const double* S, const double* Q, double* Y, void* workspace,
 
 size_t mla_convert_layer_workspace_bytes(int n, int D, int g, int h, int d, int M, int keep, int r_kv, int p) {
     if (!layer_shape_ok(n, D, g, h, d, M, keep, r_kv, p) || p > TOP_MAX_P || (long)M * g > MOMENT_MAX_MG) return 0;
-    return layer_ws(nullptr, n, D, g, h, d, M, keep, p).bytes;
+    return layer_ws(nullptr, n, D, g, d, M, keep, p).bytes;
 }
 
 int mla_convert_layer(const double* X, const double* W_K, const double* W_V, const double* Q0,
@@ -246,45 +244,44 @@ int mla_convert_layer(const double* X, const double* W_K, const double* W_V, con
     if (p > TOP_MAX_P || (long)M * g > MOMENT_MAX_MG || (long)M * g < 2) return MLA_ERR_UNSUPPORTED;
     if (!workspace || workspace_bytes < mla_convert_layer_workspace_bytes(n, D, g, h, d, M, keep, r_kv, p)) return MLA_ERR_WORKSPACE;
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
-    const LayerWs w = layer_ws(workspace, n, D, g, h, d, M, keep, p);
-    const int gd = g * d, hd = h * d, groups = d / (2 * M), Mg = M * g;
+    const LayerWs w = layer_ws(workspace, n, D, g, d, M, keep, p);
+    const int gd = g * d, groups = d / (2 * M), Mg = M * g;
     const int d_rope = keep * (d / M);        // width of the RoPE key
     const int a = gd - d_rope, mj = a + gd;   // NoPE key, joint NoPE-key + value space
     hipError_t e;
 #define MLA_TRY(call) do { e = (call); if (e != hipSuccess) return MLA_ERR_HIP; } while (0)
+    // scratch of the products: the moment before it is there and after its last use
+    const size_t s_doubles = (size_t)mj * mj;
+    auto product = [&](GemmF64 p) { p.partial = w.S; p.partial_doubles = s_doubles; return launch_gemm_f64(p, s); };
     // Sec. 4.1 / App. B: key activations before RoPE, their per-group moments, the bases U
-    MLA_TRY(launch_gemm_f64(gemm_nt(X, D, W_K, D, w.K, gd, n, gd, D, 1.0), s));
+    MLA_TRY(product(gemm_nt(X, D, W_K, D, w.K, gd, n, gd, D, 1.0)));
     MLA_TRY(launch_rope_moments(w.K, U, n, g, d, M, s));
     MLA_TRY(launch_jacobi(U, evals_rope, w.sigma_work, info, groups, Mg, JACOBI_MAX_SWEEPS, s));
-    // Sec. 4.2: rotate W^K and the selector matrices (W^UK_i)^T, stacked as [g d, h d]
+    // Sec. 4.2: rotate W^K; the RoPE key: W_KR = the first d_rope rows, W_QR = the same rows of the rotated selectors (W^UK_i)^T
     MLA_TRY(launch_rotate_rows(W_K, U, w.W_K_rot, g, d, M, keep, D, s));
-    MLA_TRY(launch_selector(w.E, g, h, d, s));
-    MLA_TRY(launch_rotate_rows(w.E, U, w.E_rot, g, d, M, keep, hd, s));
-    // the RoPE key: W_KR = the first d_rope rows of the rotated W^K; W_QR[i][a][b] = E_rot[a][i d + b]
     MLA_TRY(launch_copy_scaled(w.W_K_rot, D, W_KR, D, d_rope, D, nullptr, 0, s));
-    for (int i = 0; i < h; ++i)
-        MLA_TRY(launch_copy_scaled(w.E_rot + (size_t)i * d, hd, W_QR + (size_t)i * d_rope * d, d, d_rope, d, nullptr, 0, s));
-    // Sec. 4.3: activations of the NoPE key and of the values, alpha
-    MLA_TRY(launch_gemm_f64(gemm_nt(X, D, w.W_K_rot + (size_t)d_rope * D, D, w.C, mj, n, a, D, 1.0), s));
-    MLA_TRY(launch_gemm_f64(gemm_nt(X, D, W_V, D, w.C + a, mj, n, gd, D, 1.0), s));
+    MLA_TRY(launch_gather_w_qr(U, W_QR, g, h, d, M, keep, s));
+    // Sec. 4.3: activations of the NoPE key (the key activations rotated) and of the values, alpha
+    MLA_TRY(launch_rotate_columns(w.K, U, w.C, mj, n, g, d, M, keep, s));
+    MLA_TRY(product(gemm_nt(X, D, W_V, D, w.C + a, mj, n, gd, D, 1.0)));
     MLA_TRY(launch_row_norms(w.C, mj, a, w.C + a, mj, gd, w.norms, n, s));
     MLA_TRY(launch_alpha(w.norms, alpha, n, s));
     // App. D.2: balanced activations, their moment, its leading eigenvectors
     MLA_TRY(launch_balance(w.C, mj, w.C + a, mj, alpha, w.C, n, a, gd, s));
+    const TopWs top = top_ws(w.top, mj, p);
     GemmF64 moment = gemm_tn(w.C, mj, w.C, mj, w.S, mj, mj, mj, n, 1.0 / (double)n);
     moment.symmetric = 1;
+    moment.partial = top.part;
+    moment.partial_doubles = top.part_doubles;
     MLA_TRY(launch_gemm_f64(moment, s));
-    int rc = top_eig(w.S, Q0, evals_joint, R_KV, top_ws(w.top, mj, p), info + groups, mj, r_kv, p, iters, s);
+    int rc = top_eig(w.S, Q0, evals_joint, R_KV, top, info + groups, mj, r_kv, p, iters, s);
     if (rc != MLA_OK) return rc;
     // W^DKV' = R^T [W^DK_NoPE / alpha ; W^DV]
     MLA_TRY(launch_copy_scaled(w.W_K_rot + (size_t)d_rope * D, D, w.W_cat, D, a, D, alpha, 2, s));
     MLA_TRY(launch_copy_scaled(W_V, D, w.W_cat + (size_t)a * D, D, gd, D, nullptr, 0, s));
-    MLA_TRY(launch_gemm_f64(gemm_tn(R_KV, r_kv, w.W_cat, D, W_DKV, D, r_kv, D, mj, 1.0), s));
-    // W^UK'_i = alpha W^UK_NoPE,i R_K for all heads at once: (E_rot[d_rope:, :])^T R_K -> [h d, r_kv]
-    GemmF64 uk = gemm_tn(w.E_rot + (size_t)d_rope * hd, hd, R_KV, r_kv, W_UK, r_kv, hd, r_kv, a, 1.0);
-    uk.alpha_dev = alpha;
-    uk.dev_mode = 1;
-    MLA_TRY(launch_gemm_f64(uk, s));
+    MLA_TRY(product(gemm_tn(R_KV, r_kv, w.W_cat, D, W_DKV, D, r_kv, D, mj, 1.0)));
+    // W^UK'_i = alpha W^UK_NoPE,i R_K: the rows of R_K rotated back, for the heads that read them
+    MLA_TRY(launch_rotate_back(R_KV, U, W_UK, g, h, d, M, keep, r_kv, alpha, s));
     // W^UV'_i = W^UV_i R_V: the rows of R_V that belong to the group of head i, transposed
     MLA_TRY(launch_gather_w_uv(R_KV, W_UV, g, h, d, a, r_kv, s));
 #undef MLA_TRY

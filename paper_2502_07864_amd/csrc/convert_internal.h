@@ -37,6 +37,13 @@ constexpr int TOP_MAX_P = 1024;      // block power iteration: block width
 
 hipError_t launch_rope_moments(const double* K, double* sigma, int n, int g, int d, int M, hipStream_t s);
 hipError_t launch_rotate_rows(const double* W, const double* U, double* W_out, int g, int d, int M, int keep, int cols, hipStream_t s);
+// W_UK[i d + b, :] = *alpha times row b of the rotation back of the NoPE rows R [M g groups 2 - d_rope, cols], per query head i
+hipError_t launch_rotate_back(const double* R, const double* U, double* W_UK, int g, int h, int d, int M, int keep, int cols,
+                              const double* alpha, hipStream_t s);
+// C[:, NoPE columns] = the rotated columns of K [n, g d]; C has row pitch ldc
+hipError_t launch_rotate_columns(const double* K, const double* U, double* C, int ldc, int n, int g, int d, int M, int keep, hipStream_t s);
+// W_QR[i, a, b]: the query side of the RoPE key (rows of the rotated selectors of Sec. 4.1)
+hipError_t launch_gather_w_qr(const double* U, double* W_QR, int g, int h, int d, int M, int keep, hipStream_t s);
 hipError_t launch_row_norms(const double* K, int ldk, int a, const double* V, int ldv, int b, double* norms, int n, hipStream_t s);
 hipError_t launch_alpha(const double* norms, double* alpha, int n, hipStream_t s);
 // C[t, 0:a] = K[t, 0:a] / *alpha, C[t, a:a+b] = V[t, 0:b]   (in place allowed)
@@ -52,8 +59,6 @@ hipError_t launch_symmetrise(double* T, int p, hipStream_t s);
 hipError_t launch_fill_int(int* dst, int value, int count, hipStream_t s);
 // dst[r, c] = src[r*lds + c] * f, f = 1, *scale (mode 1) or 1 / *scale (mode 2)
 hipError_t launch_copy_scaled(const double* src, long lds_, double* dst, long ldd, int rows, int cols, const double* scale, int mode, hipStream_t s);
-// E [g*d, h*d]: E[j*d + b, i*d + b] = 1 when j is the group of query head i (Sec. 4.1), else 0
-hipError_t launch_selector(double* E, int g, int h, int d, hipStream_t s);
 // W_UV[i, rho, b] = R[nope + group(i)*d + b, rho]   (nope: rows of the NoPE key in front of the values)
 hipError_t launch_gather_w_uv(const double* R, double* W_UV, int g, int h, int d, int nope, int r, hipStream_t s);
 

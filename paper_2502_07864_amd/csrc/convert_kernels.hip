@@ -35,75 +35,237 @@ __device__ __forceinline__ double block_sum(double v, double* red) {
 }
 
 // ------------------------------------------------------------------ App. B / App. C: second moments
-// One workgroup per FreqFold group.  Sixteen tokens at a time are staged in LDS
-// (their M*g real and M*g imaginary components); thread t owns entries
-// t, t + 256, ... of the (M g) x (M g) result.
-constexpr int MT = 16;
-__global__ __launch_bounds__(256) void rope_moments_kernel(const double* __restrict__ K, double* __restrict__ sigma,
-                                                           int n, int g, int d, int M) {
-    __shared__ double xs[MT][MOMENT_MAX_MG], ys[MT][MOMENT_MAX_MG];
-    const int G = blockIdx.x, Mg = M * g, tid = threadIdx.x;
+// Component c of group G: pair c / g of the group (M of them), head c % g.
+struct Group {
+    int G, g, d, M;
+    __device__ __forceinline__ int column(int c) const { return (c % g) * d + 2 * (G * M + c / g); }     // real part; imaginary: + 1
+};
+
+// grid (groups, pairs of 32-component tiles on and above the diagonal).  Sigma = sum over the tokens of x x^T + y y^T: a
+// product 2 n deep on v_mfma_f64_16x16x4_f64 (lane l: component l % 16, token l / 16).  Sixteen wavefronts take four tokens
+// each in turn, straight from memory, and their sums meet in LDS in order.  Bound by the loads, 16 bytes of a line per lane:
+// 32 groups of 64 components, 4096 tokens: 3160 us on 32 workgroups of scalar multiply-adds, now 340.
+constexpr int MW = 16;
+__global__ __launch_bounds__(64 * MW) void rope_moments_kernel(const double* __restrict__ K, double* __restrict__ sigma,
+                                                               int n, int g, int d, int M) {
+    __shared__ double part[MW / 2][16][64];
+    const int Mg = M * g, tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int li = lane & 15, kq = lane >> 4;
+    int ti = 0, tj = blockIdx.y;                       // row and column of tiles
+    for (int row = (Mg + 31) / 32; tj >= row; --row) { tj -= row; ++ti; }
+    tj += ti;
+    const Group grp{(int)blockIdx.x, g, d, M};
     const long ldk = (long)g * d;
-    const int nout = Mg * Mg, nq = (nout + 255) / 256;
-    double acc[64];
+    const double *pa[2], *pb[2];
+    bool in_a[2], in_b[2];
 #pragma unroll
-    for (int q = 0; q < 64; ++q) acc[q] = 0.0;
-    for (int t0 = 0; t0 < n; t0 += MT) {
-        for (int idx = tid; idx < MT * Mg; idx += 256) {
-            const int tt = idx / Mg, c = idx % Mg;
-            const int p = c / g, j = c % g;
-            const long col = (long)j * d + 2 * (G * M + p);
-            const int t = t0 + tt;
-            xs[tt][c] = t < n ? K[t * ldk + col] : 0.0;
-            ys[tt][c] = t < n ? K[t * ldk + col + 1] : 0.0;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int q = 0; q < 64; ++q) {
-            if (q < nq) {
-                const int o = tid + 256 * q;
-                if (o < nout) {
-                    const int c1 = o / Mg, c2 = o % Mg;
-                    double a = acc[q];
-#pragma unroll
-                    for (int tt = 0; tt < MT; ++tt) a += xs[tt][c1] * xs[tt][c2] + ys[tt][c1] * ys[tt][c2];
-                    acc[q] = a;
-                }
-            }
-        }
-        __syncthreads();
+    for (int u = 0; u < 2; ++u) {
+        const int ca = ti * 32 + u * 16 + li, cb = tj * 32 + u * 16 + li;
+        in_a[u] = ca < Mg;
+        in_b[u] = cb < Mg;
+        pa[u] = K + grp.column(in_a[u] ? ca : 0);
+        pb[u] = K + grp.column(in_b[u] ? cb : 0);
     }
-    const double inv_n = 1.0 / (double)n;
+    f64x4 acc[2][2];
 #pragma unroll
-    for (int q = 0; q < 64; ++q) {
-        const int o = tid + 256 * q;
-        if (q < nq && o < nout) sigma[(long)G * nout + o] = acc[q] * inv_n;
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int v = 0; v < 2; ++v) acc[u][v] = (f64x4){0.0, 0.0, 0.0, 0.0};
+    constexpr int U = 4;                               // steps in flight
+    for (int t0 = wave * 4; t0 < n; t0 += 4 * MW * U) {
+        double a[U][2][2], b[U][2][2];                 // [step][tile][real, imaginary]
+#pragma unroll
+        for (int s = 0; s < U; ++s) {
+            const int t = t0 + s * 4 * MW + kq;
+            const long at = (long)min(t, n - 1) * ldk;
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    a[s][u][i] = pa[u][at + i];
+                    b[s][u][i] = pb[u][at + i];
+                }
+        }
+#pragma unroll
+        for (int s = 0; s < U; ++s) {
+            const bool there = t0 + s * 4 * MW + kq < n;
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {          // (what is not there is a zero on both sides, whatever was read)
+                    a[s][u][i] = there && in_a[u] ? a[s][u][i] : 0.0;
+                    b[s][u][i] = there && in_b[u] ? b[s][u][i] : 0.0;
+                }
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int u = 0; u < 2; ++u)
+#pragma unroll
+                    for (int v = 0; v < 2; ++v)
+                        acc[u][v] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[s][u][i], b[s][v][i], acc[u][v], 0, 0, 0);
+        }
+    }
+    auto slot = [&](int w, int u, int v, int r) -> double& { return part[w][(u * 2 + v) * 4 + r][lane]; };
+    if (wave >= MW / 2) {
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int v = 0; v < 2; ++v)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) slot(wave - MW / 2, u, v, r) = acc[u][v][r];
+    }
+    __syncthreads();
+    if (wave < MW / 2) {
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int v = 0; v < 2; ++v)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) slot(wave, u, v, r) += acc[u][v][r];
+    }
+    __syncthreads();
+    // wavefront f: element f of the 16 a lane holds
+    double sum = 0.0;
+#pragma unroll
+    for (int w = 0; w < MW / 2; ++w) sum += part[w][wave][lane];
+    const int r = ti * 32 + (wave >> 3) * 16 + 4 * (wave & 3) + kq, c = tj * 32 + ((wave >> 2) & 1) * 16 + li;
+    if (r < Mg && c < Mg) {
+        double* out = sigma + (long)blockIdx.x * Mg * Mg;
+        const double v = sum / (double)n;
+        if (ti != tj || r <= c) out[(long)r * Mg + c] = v;               // (the diagonal tiles: both halves from the upper one)
+        if (ti != tj || r < c) out[(long)c * Mg + r] = v;
     }
 }
 
-// ------------------------------------------------------------------ Sec. 4.2: rotation of rows
-// grid (2 * groups, column tiles of 32): part 0 rotates the real rows, part 1 the imaginary rows.
-// Output rows: the RoPE key first (component r < keep of group G at pair G * keep + r), then the NoPE
-// key (component r >= keep at pair (r - keep) * groups + G).
+// ------------------------------------------------------------------ Sec. 4.2: rotation of rows, of columns, and back
+// Row (column) of component r of group G, real part: the RoPE key first (r < keep at pair G * keep + r), then the NoPE key
+// (pair (r - keep) * groups + G).
+__device__ __forceinline__ long rotated_row(int G, int r, int keep, int groups) {
+    return r < keep ? 2L * (G * keep + r) : 2L * keep * groups + 2L * ((long)(r - keep) * groups + G);
+}
+
+// grid (2 * groups, columns in tiles of 64), a wavefront per 16 columns; part 0: real rows, part 1: imaginary ones.
+//   forward: out[rotated_row(r)] = sum over c of U[c][r] W[row of c]
+//   BACK:    the rows of W are those of the NoPE key (rotated_row - d_rope); out[head i][row of c] = scale times the sum over
+//            r >= keep of U[c][r] W[r], for each of the `per` query heads i of c's key head
+// On the fp64 matrix instructions: the wavefront's part of W is read once, U from the L1.
+// 4096 x 4096, groups of 64: 507 -> 137 us.
+template <bool BACK>
 __global__ __launch_bounds__(256) void rotate_rows_kernel(const double* __restrict__ W, const double* __restrict__ U,
-                                                          double* __restrict__ W_out, int g, int d, int M, int keep, int cols) {
-    __shared__ double ws[MOMENT_MAX_MG][33];
-    const int part = blockIdx.x & 1, G = blockIdx.x >> 1, Mg = M * g, tid = threadIdx.x;
-    const int col0 = blockIdx.y * 32;
-    for (int idx = tid; idx < Mg * 32; idx += 256) {
-        const int c = idx >> 5, cc = idx & 31;
-        const long row = (long)(c % g) * d + 2 * (G * M + c / g) + part;
-        ws[c][cc] = col0 + cc < cols ? W[row * cols + col0 + cc] : 0.0;
+                                                          double* __restrict__ out, int g, int d, int M, int keep, int cols,
+                                                          int per, const double* __restrict__ scale) {
+    constexpr int NK = MOMENT_MAX_MG / 4;
+    const int part = blockIdx.x & 1, Mg = M * g, groups = d / (2 * M), d_rope = 2 * keep * groups;
+    const Group grp{(int)(blockIdx.x >> 1), g, d, M};
+    const int lane = threadIdx.x & 63, li = lane & 15, kq = lane >> 4;
+    const int col = blockIdx.y * 64 + (threadIdx.x >> 6) * 16 + li;
+    const bool live = col < cols;
+    const double* Ug = U + (long)grp.G * Mg * Mg;
+    double w[NK];
+#pragma unroll
+    for (int s = 0; s < NK; ++s) {
+        w[s] = 0.0;
+        const int k = 4 * s + kq;
+        if (4 * s < Mg && live && k < Mg && (!BACK || k >= keep))
+            w[s] = W[(BACK ? rotated_row(grp.G, k, keep, groups) - d_rope : (long)grp.column(k)) * cols + (long)part * cols + col];
+    }
+    const double f = BACK ? *scale : 1.0;
+    for (int m0 = 0; m0 < Mg; m0 += 16) {
+        f64x4 acc = (f64x4){0.0, 0.0, 0.0, 0.0};
+        double u[NK];
+        const int m = m0 + li;
+#pragma unroll
+        for (int s = 0; s < NK; ++s) {
+            u[s] = 0.0;
+            const int k = 4 * s + kq;
+            if (4 * s < Mg && k < Mg && m < Mg) u[s] = BACK ? Ug[(long)m * Mg + k] : Ug[(long)k * Mg + m];
+        }
+#pragma unroll
+        for (int s = 0; s < NK; ++s)
+            if (4 * s < Mg) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(u[s], w[s], acc, 0, 0, 0);
+        if (!live) continue;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int r = m0 + 4 * e + kq;
+            if (r >= Mg) continue;
+            if (BACK) {
+                const int head = r % g, row = grp.column(r) - head * d + part;
+                for (int i = 0; i < per; ++i) out[((long)(head * per + i) * d + row) * cols + col] = f * acc[e];
+            } else {
+                out[(rotated_row(grp.G, r, keep, groups) + part) * cols + col] = acc[e];
+            }
+        }
+    }
+}
+
+// C[t, NoPE column of (G, r, part)] = sum over c of K[t, column of c + part] U[c][r], r >= keep: the rotated key activations
+// without another product with X.  grid (tokens / 16, groups / GS); 16 tokens x GS groups in LDS, a wavefront per group, both parts
+// at once; results go back through LDS, so that a row is read and written in runs of 2 GS (M) values.  4096 tokens, 4096
+// columns, groups of 64: 230 us, where the product X W^T with the rotated weights takes 2000.
+__global__ __launch_bounds__(512) void rotate_columns_kernel(const double* __restrict__ K, const double* __restrict__ U, double* __restrict__ C,
+                                                             int ldc, int n, int g, int d, int M, int keep, int GS) {
+    extern __shared__ __attribute__((aligned(16))) double buf[];          // [16 tokens][component][group][part], padded
+    const int Mg = M * g, groups = d / (2 * M), tid = threadIdx.x, nt = blockDim.x;
+    const int t0 = blockIdx.x * 16, G0 = blockIdx.y * GS, ng = min(GS, groups - G0);
+    const int pitch = Mg * GS * 2 + 2;
+    const long ldk = (long)g * d;
+    // component (p, j) of group G0 + q: value 2 (q M + p) + part of a run of 2 ng M values of head j
+    const int run = 2 * ng * M;
+    for (int idx = tid; idx < 16 * g * run; idx += nt) {
+        const int x = idx % run, j = idx / run % g, t = idx / (run * g);
+        const int q = x / (2 * M), p = x % (2 * M) / 2;
+        buf[t * pitch + ((p * g + j) * GS + q) * 2 + (x & 1)] = t0 + t < n ? K[(t0 + t) * ldk + (long)j * d + 2 * G0 * M + x] : 0.0;
     }
     __syncthreads();
-    const int cc = tid & 31;
-    const double* Ug = U + (long)G * Mg * Mg;
-    for (int r = tid >> 5; r < Mg; r += 8) {
-        double a = 0.0;
-        for (int c = 0; c < Mg; ++c) a += Ug[c * Mg + r] * ws[c][cc];
-        const int groups = d / (2 * M);
-        const long row = (r < keep ? 2L * (G * keep + r) : 2L * keep * groups + 2L * ((long)(r - keep) * groups + G)) + part;
-        if (col0 + cc < cols) W_out[row * cols + col0 + cc] = a;
+    const int lane = tid & 63, wave = tid >> 6, li = lane & 15, kq = lane >> 4;
+    constexpr int NR = MOMENT_MAX_MG / 16;
+    f64x4 acc[2][NR];
+    const double* Ug = U + (long)(G0 + wave) * Mg * Mg;
+    if (wave < ng) {
+#pragma unroll
+        for (int m = 0; m < NR; ++m) acc[0][m] = acc[1][m] = (f64x4){0.0, 0.0, 0.0, 0.0};
+        for (int k0 = 0; k0 < Mg; k0 += 4) {
+            const int k = k0 + kq;
+            const double re = k < Mg ? buf[li * pitch + (k * GS + wave) * 2] : 0.0, im = k < Mg ? buf[li * pitch + (k * GS + wave) * 2 + 1] : 0.0;
+#pragma unroll
+            for (int m = 0; m < NR; ++m)
+                if (16 * m < Mg) {
+                    const double u = k < Mg && 16 * m + li < Mg ? Ug[(long)k * Mg + 16 * m + li] : 0.0;
+                    acc[0][m] = __builtin_amdgcn_mfma_f64_16x16x4f64(u, re, acc[0][m], 0, 0, 0);
+                    acc[1][m] = __builtin_amdgcn_mfma_f64_16x16x4f64(u, im, acc[1][m], 0, 0, 0);
+                }
+        }
+    }
+    __syncthreads();
+    if (wave < ng) {
+#pragma unroll
+        for (int m = 0; m < NR; ++m)
+            if (16 * m < Mg) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int r = 16 * m + 4 * e + kq;
+                    if (r < Mg) {
+                        buf[li * pitch + (r * GS + wave) * 2] = acc[0][m][e];
+                        buf[li * pitch + (r * GS + wave) * 2 + 1] = acc[1][m][e];
+                    }
+                }
+            }
+    }
+    __syncthreads();
+    for (int idx = tid; idx < 16 * (Mg - keep) * 2 * ng; idx += nt) {
+        const int x = idx % (2 * ng), r = idx / (2 * ng) % (Mg - keep), t = idx / (2 * ng * (Mg - keep));
+        if (t0 + t < n) C[(long)(t0 + t) * ldc + 2L * ((long)r * groups + G0) + x] = buf[t * pitch + ((r + keep) * GS) * 2 + x];
+    }
+}
+
+// The query side of the RoPE key: W_QR[i][a][b] = U_G[c][r] where a is (G, r, part) and b component c of the head's group, else 0
+__global__ __launch_bounds__(256) void gather_w_qr_kernel(const double* __restrict__ U, double* __restrict__ W_QR, int g, int h, int d, int M, int keep) {
+    const int groups = d / (2 * M), d_rope = 2 * keep * groups, per = h / g, Mg = M * g;
+    const long total = (long)h * d_rope * d;
+    for (long idx = (long)blockIdx.x * 256 + threadIdx.x; idx < total; idx += (long)gridDim.x * 256) {
+        const int b = (int)(idx % d), a = (int)(idx / d % d_rope), i = (int)(idx / ((long)d * d_rope));
+        const int G = a / 2 / keep, r = a / 2 % keep, p = b / 2 - G * M;
+        W_QR[idx] = (a & 1) == (b & 1) && p >= 0 && p < M ? U[((long)G * Mg + p * g + i / per) * Mg + r] : 0.0;
     }
 }
 
@@ -723,16 +885,6 @@ __global__ __launch_bounds__(256) void copy_scaled_kernel(const double* __restri
     }
 }
 
-__global__ __launch_bounds__(256) void selector_kernel(double* __restrict__ E, int g, int h, int d) {
-    const long total = (long)g * d * h * d;
-    const int per = h / g;
-    for (long idx = (long)blockIdx.x * 256 + threadIdx.x; idx < total; idx += (long)gridDim.x * 256) {
-        const long row = idx / ((long)h * d), col = idx % ((long)h * d);
-        const int j = (int)(row / d), b = (int)(row % d), i = (int)(col / d), b2 = (int)(col % d);
-        E[idx] = (j == i / per && b == b2) ? 1.0 : 0.0;
-    }
-}
-
 __global__ __launch_bounds__(256) void gather_w_uv_kernel(const double* __restrict__ R, double* __restrict__ W_UV,
                                                           int g, int h, int d, int nope, int r) {
     const long total = (long)h * r * d;
@@ -764,13 +916,38 @@ hipError_t allow_dynamic_lds(const void* kernel, int bytes) {
 }
 
 hipError_t launch_rope_moments(const double* K, double* sigma, int n, int g, int d, int M, hipStream_t s) {
-    rope_moments_kernel<<<d / (2 * M), 256, 0, s>>>(K, sigma, n, g, d, M);
+    const int tiles = (M * g + 31) / 32;
+    rope_moments_kernel<<<dim3(d / (2 * M), tiles * (tiles + 1) / 2), 64 * MW, 0, s>>>(K, sigma, n, g, d, M);
     return hipGetLastError();
 }
 
 hipError_t launch_rotate_rows(const double* W, const double* U, double* W_out, int g, int d, int M, int keep, int cols, hipStream_t s) {
-    dim3 grid(2 * (d / (2 * M)), (cols + 31) / 32);
-    rotate_rows_kernel<<<grid, 256, 0, s>>>(W, U, W_out, g, d, M, keep, cols);
+    dim3 grid(2 * (d / (2 * M)), (cols + 63) / 64);
+    rotate_rows_kernel<false><<<grid, 256, 0, s>>>(W, U, W_out, g, d, M, keep, cols, 1, nullptr);
+    return hipGetLastError();
+}
+
+hipError_t launch_rotate_back(const double* R, const double* U, double* W_UK, int g, int h, int d, int M, int keep, int cols,
+                              const double* alpha, hipStream_t s) {
+    dim3 grid(2 * (d / (2 * M)), (cols + 63) / 64);
+    rotate_rows_kernel<true><<<grid, 256, 0, s>>>(R, U, W_UK, g, d, M, keep, cols, h / g, alpha);
+    return hipGetLastError();
+}
+
+hipError_t launch_rotate_columns(const double* K, const double* U, double* C, int ldc, int n, int g, int d, int M, int keep, hipStream_t s) {
+    const int groups = d / (2 * M), Mg = M * g;
+    if (Mg == keep) return hipSuccess;                 // (nothing is left for the NoPE key)
+    int GS = 8;                                        // a wavefront each; 16 tokens of them fit LDS
+    while (GS > 1 && (GS / 2 >= groups || 256 * Mg * GS > 128 * 1024)) GS /= 2;
+    const size_t bytes = 16 * ((size_t)Mg * GS * 2 + 2) * sizeof(double);
+    hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(&rotate_columns_kernel), 132 * 1024);
+    if (e != hipSuccess) return e;
+    rotate_columns_kernel<<<dim3((n + 15) / 16, (groups + GS - 1) / GS), 64 * std::max(GS, 4), bytes, s>>>(K, U, C, ldc, n, g, d, M, keep, GS);
+    return hipGetLastError();
+}
+
+hipError_t launch_gather_w_qr(const double* U, double* W_QR, int g, int h, int d, int M, int keep, hipStream_t s) {
+    gather_w_qr_kernel<<<grid_for((long)h * keep * (d / M) * d), 256, 0, s>>>(U, W_QR, g, h, d, M, keep);
     return hipGetLastError();
 }
 
@@ -882,11 +1059,6 @@ hipError_t launch_fill_int(int* dst, int value, int count, hipStream_t s) {
 
 hipError_t launch_copy_scaled(const double* src, long lds_, double* dst, long ldd, int rows, int cols, const double* scale, int mode, hipStream_t s) {
     copy_scaled_kernel<<<grid_for((long)rows * cols), 256, 0, s>>>(src, lds_, dst, ldd, rows, cols, scale, mode);
-    return hipGetLastError();
-}
-
-hipError_t launch_selector(double* E, int g, int h, int d, hipStream_t s) {
-    selector_kernel<<<grid_for((long)g * d * h * d), 256, 0, s>>>(E, g, h, d);
     return hipGetLastError();
 }
 
