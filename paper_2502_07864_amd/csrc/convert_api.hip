@@ -64,7 +64,23 @@ int chol_qr(const double* Y, double* out, const TopWs& w, int m, int p, int* bad
     return st(launch_gemm_f64(q, s));
 }
 
-int top_eig(const double* S, const double* Q0, double* evals, double* R, const TopWs& w, int* info,
+// The symmetric matrix whose leading eigenvectors are wanted: S [m x m], or C^T C / n by its factor C [n x m] (Z: n x p of scratch)
+struct Symmetric {
+    const double* S;
+    const double* C;
+    int n;
+    double* Z;
+};
+
+// Y = S Q
+hipError_t apply(const Symmetric& a, const double* Q, double* Y, const TopWs& w, int m, int p, hipStream_t s) {
+    auto product = [&](GemmF64 g) { g.partial = w.part; g.partial_doubles = w.part_doubles; return launch_gemm_f64(g, s); };
+    if (a.S) return product(gemm_nn(a.S, m, Q, p, Y, p, m, p, m, 1.0));
+    hipError_t e = product(gemm_nn(a.C, m, Q, p, a.Z, p, a.n, p, m, 1.0));
+    return e != hipSuccess ? e : product(gemm_tn(a.C, m, a.Z, p, Y, p, m, p, a.n, 1.0 / (double)a.n));
+}
+
+int top_eig(const Symmetric& S, const double* Q0, double* evals, double* R, const TopWs& w, int* info,
             int m, int r, int p, int iters, hipStream_t s) {
     hipError_t e = launch_fill_int(info, 0, 2, s);
     if (e != hipSuccess) return MLA_ERR_HIP;
@@ -73,33 +89,29 @@ int top_eig(const double* S, const double* Q0, double* evals, double* R, const T
     if ((rc = chol_qr(Q0, w.Y, w, m, p, info, s)) != MLA_OK) return rc;
     if ((rc = chol_qr(w.Y, w.Q, w, m, p, info, s)) != MLA_OK) return rc;
     for (int it = 0; it < iters; ++it) {
-        GemmF64 sq = gemm_nn(S, m, w.Q, p, w.Y, p, m, p, m, 1.0);
-        sq.partial = w.part;
-        sq.partial_doubles = w.part_doubles;
-        e = launch_gemm_f64(sq, s);
+        e = apply(S, w.Q, w.Y, w, m, p, s);
         if (e != hipSuccess) return MLA_ERR_HIP;
         if ((rc = chol_qr(w.Y, w.Q, w, m, p, info, s)) != MLA_OK) return rc;
     }
     // second pass restores orthonormality to rounding level before the Rayleigh-Ritz step
     if ((rc = chol_qr(w.Q, w.Y, w, m, p, info, s)) != MLA_OK) return rc;
-    e = launch_copy_scaled(w.Y, p, w.Q, p, m, p, nullptr, 0, s);
-    if (e != hipSuccess) return MLA_ERR_HIP;
-    // T = Q^T S Q, T = Z diag(evals) Z^T, R = Q Z[:, :r]
-    GemmF64 sq = gemm_nn(S, m, w.Q, p, w.Y, p, m, p, m, 1.0);
-    sq.partial = w.part;
-    sq.partial_doubles = w.part_doubles;
-    e = launch_gemm_f64(sq, s);
-    if (e != hipSuccess) return MLA_ERR_HIP;
-    GemmF64 ritz = gemm_tn(w.Q, p, w.Y, p, w.T, p, p, p, m, 1.0);
-    ritz.partial = w.part;
-    ritz.partial_doubles = w.part_doubles;
-    e = launch_gemm_f64(ritz, s);
+    // T = Q^T S Q (S by its factor: (C Q)^T (C Q) / n), T = Z diag(evals) Z^T, R = Q Z[:, :r]
+    auto product = [&](GemmF64 g) { g.partial = w.part; g.partial_doubles = w.part_doubles; return launch_gemm_f64(g, s); };
+    if (S.S) {
+        e = apply(S, w.Y, w.Q, w, m, p, s);
+        if (e == hipSuccess) e = product(gemm_tn(w.Y, p, w.Q, p, w.T, p, p, p, m, 1.0));
+    } else {
+        e = product(gemm_nn(S.C, m, w.Y, p, S.Z, p, S.n, p, m, 1.0));
+        GemmF64 ritz = gemm_tn(S.Z, p, S.Z, p, w.T, p, p, p, S.n, 1.0 / (double)S.n);
+        ritz.symmetric = 1;
+        if (e == hipSuccess) e = product(ritz);
+    }
     if (e != hipSuccess) return MLA_ERR_HIP;
     e = launch_symmetrise(w.T, p, s);
     if (e != hipSuccess) return MLA_ERR_HIP;
     e = launch_jacobi(w.T, evals, w.Z, info + 1, 1, p, p > 128 ? RITZ_MAX_SWEEPS : JACOBI_MAX_SWEEPS, s);
     if (e != hipSuccess) return MLA_ERR_HIP;
-    return st(launch_gemm_f64(gemm_nn(w.Q, p, w.T, p, R, r, m, r, p, 1.0), s));
+    return st(launch_gemm_f64(gemm_nn(w.Y, p, w.T, p, R, r, m, r, p, 1.0), s));
 }
 
 struct LayerWs {
@@ -207,7 +219,7 @@ int mla_conv_top_eig(const double* S, const double* Q0, double* evals, double* R
     if (m <= 0 || r <= 0 || p < r || p > m || iters < 0 || p < 2) return MLA_ERR_SHAPE;
     if (p > TOP_MAX_P) return MLA_ERR_UNSUPPORTED;
     if (!workspace || workspace_bytes < mla_conv_top_eig_workspace_bytes(m, p)) return MLA_ERR_WORKSPACE;
-    return top_eig(S, Q0, evals, R, top_ws(workspace, m, p), info, m, r, p, iters, static_cast<hipStream_t>(hip_stream));
+    return top_eig(Symmetric{S, nullptr, 0, nullptr}, Q0, evals, R, top_ws(workspace, m, p), info, m, r, p, iters, static_cast<hipStream_t>(hip_stream));
 }
 
 size_t mla_conv_apply_workspace_bytes(int m, int p) {
@@ -269,12 +281,21 @@ int mla_convert_layer(const double* X, const double* W_K, const double* W_V, con
     // App. D.2: balanced activations, their moment, its leading eigenvectors
     MLA_TRY(launch_balance(w.C, mj, w.C + a, mj, alpha, w.C, n, a, gd, s));
     const TopWs top = top_ws(w.top, mj, p);
-    GemmF64 moment = gemm_tn(w.C, mj, w.C, mj, w.S, mj, mj, mj, n, 1.0 / (double)n);
-    moment.symmetric = 1;
-    moment.partial = top.part;
-    moment.partial_doubles = top.part_doubles;
-    MLA_TRY(launch_gemm_f64(moment, s));
-    int rc = top_eig(w.S, Q0, evals_joint, R_KV, top, info + groups, mj, r_kv, p, iters, s);
+    // The power iteration needs the moment S = C^T C / n only in products with a block, 2 m^2 p operations each; by the factor they
+    // take 4 n m p and S itself (n m^2) is not formed.  Whichever is less: n a little above m / 2 is where they meet (4096 tokens,
+    // m = 8128, block 768, 20 iterations: 75.0 ms a layer by S, 69.3 by the factor).
+    Symmetric moment{nullptr, w.C, n, w.S};
+    const double by_factor = (4.0 * iters + 2.0) * n * mj * p + 1.0 * n * p * p;
+    const double by_moment = 1.0 * n * mj * mj + (2.0 * iters + 2.0) * mj * mj * p + 2.0 * mj * p * p;
+    if (by_moment <= by_factor || (size_t)n * p > s_doubles) {
+        GemmF64 ctc = gemm_tn(w.C, mj, w.C, mj, w.S, mj, mj, mj, n, 1.0 / (double)n);
+        ctc.symmetric = 1;
+        ctc.partial = top.part;
+        ctc.partial_doubles = top.part_doubles;
+        MLA_TRY(launch_gemm_f64(ctc, s));
+        moment = Symmetric{w.S, nullptr, 0, nullptr};
+    }
+    int rc = top_eig(moment, Q0, evals_joint, R_KV, top, info + groups, mj, r_kv, p, iters, s);
     if (rc != MLA_OK) return rc;
     // W^DKV' = R^T [W^DK_NoPE / alpha ; W^DV]
     MLA_TRY(launch_copy_scaled(w.W_K_rot + (size_t)d_rope * D, D, w.W_cat, D, a, D, alpha, 2, s));
