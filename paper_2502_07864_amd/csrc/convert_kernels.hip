@@ -307,80 +307,131 @@ __global__ __launch_bounds__(256) void balance_kernel(const double* K, int ldk, 
 // ------------------------------------------------------------------ Jacobi rotations of one workgroup
 // A step of the round-robin schedule rotates m/2 disjoint index pairs at once: A <- J^T A J, V <- V J, J being
 // the product of the step's plane rotations.  A and V have row pitch ld; an odd m has a bye (index m).  Bound by
-// the step's chain: the angles (two divisions, two square roots) of m/2 threads, a barrier, the rotations, a
-// barrier.  The workgroup's threads each take 2 x 2 blocks of A (the rows of one pair, the columns of another:
-// both rotations of a block in registers, rows first) and pairs of V.  (An earlier form rotated all rows, met a
-// barrier and rotated all columns, one element pair at a time, every element of A read and written twice: 32
-// matrices of order 64, 8 sweeps, 3.06 ms against 1.59.)
+// the step's chain: the angles of m/2 threads, a barrier, the rotations, a barrier.  Up to order 64 a thread owns the 2 x 2
+// block of A where the rows of one pair meet the columns of another and two rows of V in the latter's columns: it reads them
+// while the angles are worked out, and both rotations of a block are applied in registers, rows first.
 struct Rotations {
-    int pp[64], qq[64];
-    double cc[64], ss[64];
+    double2 cs[64];                                    // cosine, sine
 };
 
 __device__ __forceinline__ void round_robin_pair(int k, int step, int mp, int& p, int& q) {
+    p = step + k;
+    q = step - k;
+    if (p >= mp - 1) p -= mp - 1;
+    if (q < 0) q += mp - 1;
     if (k == 0) { p = mp - 1; q = step; }
-    else { p = (step + k) % (mp - 1); q = (step - k + (mp - 1)) % (mp - 1); }
     if (p > q) { const int t = p; p = q; q = t; }
 }
 
-// TOGETHER: blocks of A and pairs of V in one pass, for workgroups with a thread for each.
-template <bool TOGETHER>
-__device__ __forceinline__ void jacobi_step(double* A, double* V, int ld, int m, int step, Rotations& R, int tid, int nt) {
+// The rotation that annihilates apq.  With a = (aqq - app) / 2 and h = |(a, apq)|: cos 2 phi = |a| / h, so c = sqrt((1 + |a| / h) / 2)
+// and s = |apq| / (2 h c), signed like a apq: two reciprocal square roots in a chain, where t = 1 / (theta + sqrt(theta^2 + 1)),
+// c = 1 / sqrt(t^2 + 1) took two divisions more.  Scaled by the largest entry's exponent, so that no square leaves the range.
+__device__ __forceinline__ double2 rotation(double app, double aqq, double apq) {
+    const int e = -__builtin_amdgcn_frexp_exp(fmax(fmax(fabs(app), fabs(aqq)), fabs(apq)));
+    const double x = __builtin_amdgcn_ldexp(app, e), y = __builtin_amdgcn_ldexp(aqq, e), b = __builtin_amdgcn_ldexp(apq, e);
+    if (!(fabs(apq) > 1e-300 && b * b > 1e-36 * fabs(x * y))) return make_double2(1.0, 0.0);
+    const double a = 0.5 * (y - x);
+    const double r = rsqrt(fma(a, a, b * b));
+    const double c2 = fma(0.5 * fabs(a), r, 0.5);
+    const double rc = rsqrt(c2);
+    const double s = 0.5 * fabs(b) * r * rc;
+    return make_double2(c2 * rc, a == 0.0 || (a > 0.0) == (b > 0.0) ? s : -s);
+}
+
+// a block's entries after both rotations; `pair`: its rows and columns are the same pair, whose off-diagonal entries the rotation
+// was chosen to annihilate: exact zeros
+__device__ __forceinline__ void rotate_block(double (&x)[4], double2 r1, double2 r2, bool pair) {
+    const double pp = r1.x * x[0] - r1.y * x[2], pq = r1.x * x[1] - r1.y * x[3];      // rows
+    const double qp = r1.y * x[0] + r1.x * x[2], qq = r1.y * x[1] + r1.x * x[3];
+    const bool zero = pair && r1.y != 0.0;
+    x[0] = r2.x * pp - r2.y * pq;                      // columns
+    x[1] = zero ? 0.0 : r2.y * pp + r2.x * pq;
+    x[2] = zero ? 0.0 : r2.x * qp - r2.y * qq;
+    x[3] = r2.y * qp + r2.x * qq;
+}
+
+// One step, m <= 64, a thread (k1, k2) for each of the (m/2)^2 blocks (threads past them: k1 = half).
+__device__ __forceinline__ void jacobi_step(double* A, double* V, int ld, int m, int step, Rotations& R, int tid, int half, int k1, int k2) {
+    const int mp = 2 * half;
+    const bool own = k1 < half;
+    int p1, q1, p2, q2;
+    round_robin_pair(own ? k1 : 0, step, mp, p1, q1);
+    round_robin_pair(k2, step, mp, p2, q2);
+    const bool r = q1 < m, t = q2 < m;                 // (a bye has no second row / column)
+    const int i0 = 2 * k1, i1 = 2 * k1 + 1;            // rows of V
+    double x[4] = {0.0, 0.0, 0.0, 0.0}, v[4] = {0.0, 0.0, 0.0, 0.0};
+    if (own) {
+        x[0] = A[p1 * ld + p2];
+        if (t) x[1] = A[p1 * ld + q2];
+        if (r) x[2] = A[q1 * ld + p2];
+        if (r && t) x[3] = A[q1 * ld + q2];
+        if (t) {
+            v[0] = V[i0 * ld + p2];
+            v[1] = V[i0 * ld + q2];
+            if (i1 < m) {
+                v[2] = V[i1 * ld + p2];
+                v[3] = V[i1 * ld + q2];
+            }
+        }
+    }
+    if (tid < half) {
+        int p, q;
+        round_robin_pair(tid, step, mp, p, q);
+        R.cs[tid] = q < m ? rotation(A[p * ld + p], A[q * ld + q], A[p * ld + q]) : make_double2(1.0, 0.0);
+    }
+    __syncthreads();
+    if (own) {
+        const double2 r1 = R.cs[k1], r2 = R.cs[k2];
+        rotate_block(x, r1, r2, k1 == k2);
+        A[p1 * ld + p2] = x[0];
+        if (t) A[p1 * ld + q2] = x[1];
+        if (r) A[q1 * ld + p2] = x[2];
+        if (r && t) A[q1 * ld + q2] = x[3];
+        if (t && r2.y != 0.0) {
+            V[i0 * ld + p2] = r2.x * v[0] - r2.y * v[1];
+            V[i0 * ld + q2] = r2.y * v[0] + r2.x * v[1];
+            if (i1 < m) {
+                V[i1 * ld + p2] = r2.x * v[2] - r2.y * v[3];
+                V[i1 * ld + q2] = r2.y * v[2] + r2.x * v[3];
+            }
+        }
+    }
+    __syncthreads();
+}
+
+// One step of any order: the blocks, then the pairs of V, as many to a thread as it takes.
+__device__ __forceinline__ void jacobi_step_any(double* A, double* V, int ld, int m, int step, Rotations& R, int tid, int nt) {
     const int mp = m + (m & 1), half = mp / 2;
     if (tid < half) {
         int p, q;
         round_robin_pair(tid, step, mp, p, q);
-        double c = 1.0, s = 0.0;
-        if (q < m) {
-            const double apq = A[p * ld + q];
-            const double app = A[p * ld + p], aqq = A[q * ld + q];
-            if (fabs(apq) > 1e-300 && fabs(apq) > 1e-18 * sqrt(fabs(app * aqq))) {
-                const double theta = (aqq - app) / (2.0 * apq);
-                const double t = (theta >= 0.0 ? 1.0 : -1.0) / (fabs(theta) + sqrt(theta * theta + 1.0));
-                c = 1.0 / sqrt(t * t + 1.0);
-                s = t * c;
-            }
-        }
-        R.pp[tid] = p; R.qq[tid] = q; R.cc[tid] = c; R.ss[tid] = s;
+        R.cs[tid] = q < m ? rotation(A[p * ld + p], A[q * ld + q], A[p * ld + q]) : make_double2(1.0, 0.0);
     }
     __syncthreads();
-    auto block = [&](int idx) {
+    for (int idx = tid; idx < half * half; idx += nt) {
         const int k1 = idx / half, k2 = idx % half;
-        const double s1 = R.ss[k1], s2 = R.ss[k2];
-        if (s1 == 0.0 && s2 == 0.0) return;
-        const double c1 = R.cc[k1], c2 = R.cc[k2];
-        const int p1 = R.pp[k1] * ld, q1 = R.qq[k1] * ld, p2 = R.pp[k2], q2 = R.qq[k2];
-        const bool r = R.qq[k1] < m, t = q2 < m;         // (a bye has no second row / column)
-        const double app = A[p1 + p2], apq = t ? A[p1 + q2] : 0.0;
-        const double aqp = r ? A[q1 + p2] : 0.0, aqq = r && t ? A[q1 + q2] : 0.0;
-        const double pp = c1 * app - s1 * aqp, pq = c1 * apq - s1 * aqq;      // rows
-        const double qp = s1 * app + c1 * aqp, qq = s1 * apq + c1 * aqq;
-        const bool pair = k1 == k2;                      // the rotation was chosen to annihilate these two: exact zeros
-        A[p1 + p2] = c2 * pp - s2 * pq;                  // columns
-        if (t) A[p1 + q2] = pair ? 0.0 : s2 * pp + c2 * pq;
-        if (r) A[q1 + p2] = pair ? 0.0 : c2 * qp - s2 * qq;
-        if (r && t) A[q1 + q2] = s2 * qp + c2 * qq;
-    };
-    auto v_pair = [&](int idx) {
+        const double2 r1 = R.cs[k1], r2 = R.cs[k2];
+        if (r1.y == 0.0 && r2.y == 0.0) continue;
+        int p1, q1, p2, q2;
+        round_robin_pair(k1, step, mp, p1, q1);
+        round_robin_pair(k2, step, mp, p2, q2);
+        const bool r = q1 < m, t = q2 < m;
+        double x[4] = {A[p1 * ld + p2], t ? A[p1 * ld + q2] : 0.0, r ? A[q1 * ld + p2] : 0.0, r && t ? A[q1 * ld + q2] : 0.0};
+        rotate_block(x, r1, r2, k1 == k2);
+        A[p1 * ld + p2] = x[0];
+        if (t) A[p1 * ld + q2] = x[1];
+        if (r) A[q1 * ld + p2] = x[2];
+        if (r && t) A[q1 * ld + q2] = x[3];
+    }
+    for (int idx = tid; idx < half * m; idx += nt) {
         const int k = idx % half, i = idx / half;
-        const double s = R.ss[k];
-        if (s != 0.0) {
-            const double c = R.cc[k];
-            const int ip = i * ld + R.pp[k], iq = i * ld + R.qq[k];
-            const double vp = V[ip], vq = V[iq];
-            V[ip] = c * vp - s * vq;
-            V[iq] = s * vp + c * vq;
-        }
-    };
-    const int blocks = half * half;
-    if (TOGETHER) {
-        for (int idx = tid; idx < blocks + half * m; idx += nt) {
-            if (idx < blocks) block(idx);
-            else              v_pair(idx - blocks);
-        }
-    } else {
-        for (int idx = tid; idx < blocks; idx += nt) block(idx);
-        for (int idx = tid; idx < half * m; idx += nt) v_pair(idx);
+        const double2 c = R.cs[k];
+        if (c.y == 0.0) continue;
+        int p, q;
+        round_robin_pair(k, step, mp, p, q);
+        const double vp = V[i * ld + p], vq = V[i * ld + q];
+        V[i * ld + p] = c.x * vp - c.y * vq;
+        V[i * ld + q] = c.y * vp + c.x * vq;
     }
     __syncthreads();
 }
@@ -397,7 +448,8 @@ struct JacobiLds {
     double red[16];
 };
 
-template <bool TOGETHER>
+// SMALL: order <= 64, a thread per 2 x 2 block
+template <bool SMALL>
 __global__ __launch_bounds__(1024) void jacobi_kernel(double* A_all, double* evals_all, double* V_all, int* info,
                                                       int m, int max_sweeps, int in_lds) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -421,7 +473,7 @@ __global__ __launch_bounds__(1024) void jacobi_kernel(double* A_all, double* eva
     tot = block_sum(tot, L.red);                       // squared Frobenius norm (orthogonal similarity keeps it)
     const double tol2 = 1e-26 * tot;
 
-    const int mp = m + (m & 1);
+    const int mp = m + (m & 1), half = mp / 2, k1 = tid / half, k2 = tid % half;
     int used = -1;
     for (int sweep = 0; sweep <= max_sweeps; ++sweep) {
         double off = 0.0;
@@ -430,7 +482,10 @@ __global__ __launch_bounds__(1024) void jacobi_kernel(double* A_all, double* eva
         off = block_sum(off, L.red);
         if (off <= tol2) { used = sweep > 0 ? sweep : 1; break; }
         if (sweep == max_sweeps) break;
-        for (int step = 0; step < mp - 1; ++step) jacobi_step<TOGETHER>(A, V, ld, m, step, L.rot, tid, nt);
+        for (int step = 0; step < mp - 1; ++step) {
+            if (SMALL) jacobi_step(A, V, ld, m, step, L.rot, tid, half, k1, k2);
+            else       jacobi_step_any(A, V, ld, m, step, L.rot, tid, nt);
+        }
     }
 
     // rank the diagonal in descending order (ties: lower index first)
@@ -515,7 +570,7 @@ __global__ __launch_bounds__(256) void jb_pair_kernel(double* A, double* __restr
         z[r * (JP + 1) + c] = r == c ? 1.0 : 0.0;
     }
     __syncthreads();
-    for (int s = 0; s < JP - 1; ++s) jacobi_step<false>(a, z, JP + 1, JP, s, rot, tid, 256);
+    for (int s = 0; s < JP - 1; ++s) jacobi_step(a, z, JP + 1, JP, s, rot, tid, JP / 2, tid / (JP / 2), tid % (JP / 2));
     for (int idx = tid; idx < JP * JP; idx += 256) {
         const int r = idx / JP, c = idx % JP, i = pair_index(I, J, r), j = pair_index(I, J, c);
         if (i < m && j < m) A[(long)i * m + j] = a[r * (JP + 1) + c];
@@ -1019,12 +1074,8 @@ hipError_t launch_jacobi(double* A, double* evals, double* work, int* info, int 
     const size_t mats = 2 * (size_t)m * (m + 1) * sizeof(double);
     const int in_lds = head + mats <= 128 * 1024;
     const size_t bytes = head + (in_lds ? mats : 0);
-    // A thread for each 2 x 2 block and pair of V of a step while 1024 are about enough, else one per block (64 matrices, us:
-    // order 16 161 -> 122, 32 384 -> 297, 40 502 -> 463; but 48 750 -> 778, 56 1085 -> 1170).
-    const int half = (m + 1) / 2, blocks = half * half, items = blocks + half * m;
-    const bool together = items <= 1280;
-    const int threads = std::min(1024, std::max(64, ((together ? items : blocks) + 63) / 64 * 64));
-    const auto kernel = together ? &jacobi_kernel<true> : &jacobi_kernel<false>;
+    const int half = (m + 1) / 2, threads = std::min(1024, std::max(64, (half * half + 63) / 64 * 64));
+    const auto kernel = m <= 64 ? &jacobi_kernel<true> : &jacobi_kernel<false>;
     hipError_t e0 = allow_dynamic_lds(reinterpret_cast<const void*>(kernel), 128 * 1024);
     if (e0 != hipSuccess) return e0;
     kernel<<<batch, threads, bytes, s>>>(A, evals, work, info, m, max_sweeps, in_lds);
