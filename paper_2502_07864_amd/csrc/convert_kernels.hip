@@ -314,28 +314,35 @@ struct Rotations {
     double2 cs[64];                                    // cosine, sine
 };
 
+// Pair k of a step, 0 <= step < mp - 1: (step, mp - 1) or (step + k, step - k) modulo mp - 1; the bye of an odd m is in q.
 __device__ __forceinline__ void round_robin_pair(int k, int step, int mp, int& p, int& q) {
     p = step + k;
     q = step - k;
     if (p >= mp - 1) p -= mp - 1;
     if (q < 0) q += mp - 1;
-    if (k == 0) { p = mp - 1; q = step; }
-    if (p > q) { const int t = p; p = q; q = t; }
+    if (k == 0) q = mp - 1;
 }
 
-// The rotation that annihilates apq.  With a = (aqq - app) / 2 and h = |(a, apq)|: cos 2 phi = |a| / h, so c = sqrt((1 + |a| / h) / 2)
-// and s = |apq| / (2 h c), signed like a apq: two reciprocal square roots in a chain, where t = 1 / (theta + sqrt(theta^2 + 1)),
-// c = 1 / sqrt(t^2 + 1) took two divisions more.  Scaled by the largest entry's exponent, so that no square leaves the range.
+// 1 / sqrt(x) of a normal x: the instruction's 2^-23 or so, e = 1 - x y^2 taken out to its third power
+__device__ __forceinline__ double inv_sqrt(double x) {
+    const double y = __builtin_amdgcn_rsq(x), e = fma(-x * y, y, 1.0);
+    return fma(y * e, fma(e, 0.375, 0.5), y);
+}
+
+// The rotation (cosine, sine) that annihilates apq.  With a = (aqq - app) / 2 and h = |(a, apq)|: cos 2 phi = |a| / h, so
+// c = sqrt((1 + |a| / h) / 2) and s = |apq| / (2 h c), signed like a apq: two reciprocal square roots in a chain, where
+// t = 1 / (theta + sqrt(theta^2 + 1)), c = 1 / sqrt(t^2 + 1) took two divisions more.  Scaled by the largest entry's exponent,
+// so that no square leaves the range.
 __device__ __forceinline__ double2 rotation(double app, double aqq, double apq) {
     const int e = -__builtin_amdgcn_frexp_exp(fmax(fmax(fabs(app), fabs(aqq)), fabs(apq)));
     const double x = __builtin_amdgcn_ldexp(app, e), y = __builtin_amdgcn_ldexp(aqq, e), b = __builtin_amdgcn_ldexp(apq, e);
-    if (!(fabs(apq) > 1e-300 && b * b > 1e-36 * fabs(x * y))) return make_double2(1.0, 0.0);
+    const bool turns = fabs(apq) > 1e-300 && b * b > 1e-36 * fabs(x * y);
     const double a = 0.5 * (y - x);
-    const double r = rsqrt(fma(a, a, b * b));
+    const double r = inv_sqrt(fma(a, a, b * b));
     const double c2 = fma(0.5 * fabs(a), r, 0.5);
-    const double rc = rsqrt(c2);
+    const double rc = inv_sqrt(c2);
     const double s = 0.5 * fabs(b) * r * rc;
-    return make_double2(c2 * rc, a == 0.0 || (a > 0.0) == (b > 0.0) ? s : -s);
+    return make_double2(turns ? c2 * rc : 1.0, !turns ? 0.0 : a == 0.0 || (a > 0.0) == (b > 0.0) ? s : -s);
 }
 
 // a block's entries after both rotations; `pair`: its rows and columns are the same pair, whose off-diagonal entries the rotation
@@ -350,49 +357,50 @@ __device__ __forceinline__ void rotate_block(double (&x)[4], double2 r1, double2
     x[3] = r2.y * qp + r2.x * qq;
 }
 
-// One step, m <= 64, a thread (k1, k2) for each of the (m/2)^2 blocks (threads past them: k1 = half).
+// One step, m <= 64, a thread (k1, k2) for each of the (m/2)^2 blocks (threads past them: k1 = half).  EVEN: no bye.
+template <bool EVEN>
 __device__ __forceinline__ void jacobi_step(double* A, double* V, int ld, int m, int step, Rotations& R, int tid, int half, int k1, int k2) {
     const int mp = 2 * half;
     const bool own = k1 < half;
     int p1, q1, p2, q2;
     round_robin_pair(own ? k1 : 0, step, mp, p1, q1);
     round_robin_pair(k2, step, mp, p2, q2);
-    const bool r = q1 < m, t = q2 < m;                 // (a bye has no second row / column)
-    const int i0 = 2 * k1, i1 = 2 * k1 + 1;            // rows of V
-    double x[4] = {0.0, 0.0, 0.0, 0.0}, v[4] = {0.0, 0.0, 0.0, 0.0};
-    if (own) {
-        x[0] = A[p1 * ld + p2];
-        if (t) x[1] = A[p1 * ld + q2];
-        if (r) x[2] = A[q1 * ld + p2];
-        if (r && t) x[3] = A[q1 * ld + q2];
-        if (t) {
-            v[0] = V[i0 * ld + p2];
-            v[1] = V[i0 * ld + q2];
-            if (i1 < m) {
-                v[2] = V[i1 * ld + p2];
-                v[3] = V[i1 * ld + q2];
-            }
-        }
-    }
+    const bool r = EVEN || q1 < m, t = EVEN || q2 < m;               // (a bye has no second row / column)
+    const int i0 = own ? 2 * k1 : 0, i1 = EVEN || i0 + 1 < m ? i0 + 1 : i0;        // rows of V
+    double app = 0.0, aqq = 0.0, apq = 0.0;
     if (tid < half) {
         int p, q;
         round_robin_pair(tid, step, mp, p, q);
-        R.cs[tid] = q < m ? rotation(A[p * ld + p], A[q * ld + q], A[p * ld + q]) : make_double2(1.0, 0.0);
+        if (!EVEN && q >= m) q = p;
+        app = A[p * ld + p];
+        aqq = A[q * ld + q];
+        apq = !EVEN && q == p ? 0.0 : A[p * ld + q];
     }
+    double* const a11 = A + p1 * ld + p2;
+    double* const a12 = t ? A + p1 * ld + q2 : a11;
+    double* const a21 = r ? A + q1 * ld + p2 : a11;
+    double* const a22 = r && t ? A + q1 * ld + q2 : a11;
+    double* const v = V + p2;
+    double* const w = V + (t ? q2 : p2);
+    double x[4] = {*a11, *a12, *a21, *a22};
+    const double v0 = v[i0 * ld], w0 = w[i0 * ld], v1 = v[i1 * ld], w1 = w[i1 * ld];
+    if (tid < half) R.cs[tid] = rotation(app, aqq, apq);
     __syncthreads();
     if (own) {
         const double2 r1 = R.cs[k1], r2 = R.cs[k2];
+        if (!EVEN && !t) x[1] = x[3] = 0.0;
+        if (!EVEN && !r) x[2] = x[3] = 0.0;
         rotate_block(x, r1, r2, k1 == k2);
-        A[p1 * ld + p2] = x[0];
-        if (t) A[p1 * ld + q2] = x[1];
-        if (r) A[q1 * ld + p2] = x[2];
-        if (r && t) A[q1 * ld + q2] = x[3];
-        if (t && r2.y != 0.0) {
-            V[i0 * ld + p2] = r2.x * v[0] - r2.y * v[1];
-            V[i0 * ld + q2] = r2.y * v[0] + r2.x * v[1];
-            if (i1 < m) {
-                V[i1 * ld + p2] = r2.x * v[2] - r2.y * v[3];
-                V[i1 * ld + q2] = r2.y * v[2] + r2.x * v[3];
+        if (r && t) *a22 = x[3];
+        if (r) *a21 = x[2];
+        if (t) *a12 = x[1];
+        *a11 = x[0];
+        if (t) {
+            v[i0 * ld] = r2.x * v0 - r2.y * w0;
+            w[i0 * ld] = r2.y * v0 + r2.x * w0;
+            if (EVEN || i1 != i0) {
+                v[i1 * ld] = r2.x * v1 - r2.y * w1;
+                w[i1 * ld] = r2.y * v1 + r2.x * w1;
             }
         }
     }
@@ -448,8 +456,8 @@ struct JacobiLds {
     double red[16];
 };
 
-// SMALL: order <= 64, a thread per 2 x 2 block
-template <bool SMALL>
+// SMALL: order <= 64, a thread per 2 x 2 block (EVEN order or not)
+template <bool SMALL, bool EVEN>
 __global__ __launch_bounds__(1024) void jacobi_kernel(double* A_all, double* evals_all, double* V_all, int* info,
                                                       int m, int max_sweeps, int in_lds) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -483,7 +491,7 @@ __global__ __launch_bounds__(1024) void jacobi_kernel(double* A_all, double* eva
         if (off <= tol2) { used = sweep > 0 ? sweep : 1; break; }
         if (sweep == max_sweeps) break;
         for (int step = 0; step < mp - 1; ++step) {
-            if (SMALL) jacobi_step(A, V, ld, m, step, L.rot, tid, half, k1, k2);
+            if (SMALL) jacobi_step<EVEN>(A, V, ld, m, step, L.rot, tid, half, k1, k2);
             else       jacobi_step_any(A, V, ld, m, step, L.rot, tid, nt);
         }
     }
@@ -557,24 +565,52 @@ __global__ __launch_bounds__(64) void jw_norm_kernel(const double* __restrict__ 
 // index r of pair (I, J) in the matrix (>= m: not there)
 __device__ __forceinline__ int pair_index(int I, int J, int r) { return (r < JB ? I : J) * JB + (r & (JB - 1)); }
 
+// A thread (k1, k2) owns a 2 x 2 block of a and two rows of z as in jacobi_step, but works out both of its rotations itself and
+// writes to the other buffer of a: one barrier a step and no exchange of angles (four wavefronts have the vector pipes for it).
+// A step 1.16 us as two phases with the angles between them, 1.0 with the blocks read beside the angles, now 0.37.
 __global__ __launch_bounds__(256) void jb_pair_kernel(double* A, double* __restrict__ Z, int m, int nbp, int step, const WideState* st) {
-    __shared__ double a[JP * (JP + 1)], z[JP * (JP + 1)];
-    __shared__ Rotations rot;
+    constexpr int LD = JP + 1, HALF = JP / 2;
+    __shared__ double a[2][JP * LD], z[JP * LD];
     if (st->done) return;
     const int tid = threadIdx.x;
     int I, J;
     round_robin_pair(blockIdx.x, step, nbp, I, J);
     for (int idx = tid; idx < JP * JP; idx += 256) {
         const int r = idx / JP, c = idx % JP, i = pair_index(I, J, r), j = pair_index(I, J, c);
-        a[r * (JP + 1) + c] = i < m && j < m ? A[(long)i * m + j] : 0.0;      // indices that are not there rotate with nothing
-        z[r * (JP + 1) + c] = r == c ? 1.0 : 0.0;
+        a[0][r * LD + c] = i < m && j < m ? A[(long)i * m + j] : 0.0;      // indices that are not there rotate with nothing
+        z[r * LD + c] = r == c ? 1.0 : 0.0;
     }
     __syncthreads();
-    for (int s = 0; s < JP - 1; ++s) jacobi_step(a, z, JP + 1, JP, s, rot, tid, JP / 2, tid / (JP / 2), tid % (JP / 2));
+    const int k1 = tid / HALF, k2 = tid % HALF;
+    double* const z0 = z + 2 * k1 * LD;
+    double* const z1 = z0 + LD;
+    for (int s = 0; s < JP - 1; ++s) {
+        const double* x = a[s & 1];
+        double* y = a[(s & 1) ^ 1];
+        int p1, q1, p2, q2;
+        round_robin_pair(k1, s, JP, p1, q1);
+        round_robin_pair(k2, s, JP, p2, q2);
+        const double d1p = x[p1 * (LD + 1)], d1q = x[q1 * (LD + 1)], o1 = x[p1 * LD + q1];
+        const double d2p = x[p2 * (LD + 1)], d2q = x[q2 * (LD + 1)], o2 = x[p2 * LD + q2];
+        double b[4] = {x[p1 * LD + p2], x[p1 * LD + q2], x[q1 * LD + p2], x[q1 * LD + q2]};
+        const double v0 = z0[p2], w0 = z0[q2], v1 = z1[p2], w1 = z1[q2];
+        const double2 r1 = rotation(d1p, d1q, o1), r2 = rotation(d2p, d2q, o2);
+        rotate_block(b, r1, r2, k1 == k2);
+        y[p1 * LD + p2] = b[0];
+        y[p1 * LD + q2] = b[1];
+        y[q1 * LD + p2] = b[2];
+        y[q1 * LD + q2] = b[3];
+        z0[p2] = r2.x * v0 - r2.y * w0;
+        z0[q2] = r2.y * v0 + r2.x * w0;
+        z1[p2] = r2.x * v1 - r2.y * w1;
+        z1[q2] = r2.y * v1 + r2.x * w1;
+        __syncthreads();
+    }
+    const double* x = a[(JP - 1) & 1];
     for (int idx = tid; idx < JP * JP; idx += 256) {
         const int r = idx / JP, c = idx % JP, i = pair_index(I, J, r), j = pair_index(I, J, c);
-        if (i < m && j < m) A[(long)i * m + j] = a[r * (JP + 1) + c];
-        Z[(long)blockIdx.x * JP * JP + idx] = z[r * (JP + 1) + c];
+        if (i < m && j < m) A[(long)i * m + j] = x[r * LD + c];
+        Z[(long)blockIdx.x * JP * JP + idx] = z[r * LD + c];
     }
 }
 
@@ -1075,7 +1111,7 @@ hipError_t launch_jacobi(double* A, double* evals, double* work, int* info, int 
     const int in_lds = head + mats <= 128 * 1024;
     const size_t bytes = head + (in_lds ? mats : 0);
     const int half = (m + 1) / 2, threads = std::min(1024, std::max(64, (half * half + 63) / 64 * 64));
-    const auto kernel = m <= 64 ? &jacobi_kernel<true> : &jacobi_kernel<false>;
+    const auto kernel = m > 64 ? &jacobi_kernel<false, false> : m % 2 ? &jacobi_kernel<true, false> : &jacobi_kernel<true, true>;
     hipError_t e0 = allow_dynamic_lds(reinterpret_cast<const void*>(kernel), 128 * 1024);
     if (e0 != hipSuccess) return e0;
     kernel<<<batch, threads, bytes, s>>>(A, evals, work, info, m, max_sweeps, in_lds);
