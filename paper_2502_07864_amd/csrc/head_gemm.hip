@@ -112,7 +112,7 @@ __global__ __launch_bounds__(HG_THREADS) void head_gemm_kernel(const void* X, co
 // One fp32 row of 32 heads: absorb 128 -> 512 and projection 512 -> 128 (8.4 MB of W each) 6.6 -> 4.3 and
 // 8.7 -> 5.3 us.
 template <int NT, int BT>
-__global__ __launch_bounds__(HG_THREADS) void head_gemm_f32_kernel(const float* X, const float* W, float* Y, int B, int H, int K, int N)
+__global__ __launch_bounds__(HG_THREADS) void head_gemm_f32_kernel(const float* X, const float* W, float* Y, int B, int H, int K, int N, bool by_head)
 {
     constexpr int CL = NT / 4;             // lanes per row of W
     constexpr int KR = HG_THREADS / CL;    // rows of W the workgroup reads at once
@@ -120,7 +120,8 @@ __global__ __launch_bounds__(HG_THREADS) void head_gemm_f32_kernel(const float* 
     __shared__ __attribute__((aligned(16))) float x_t[HG_KC][BT];
     __shared__ __attribute__((aligned(16))) float red_s[4][BT][NT];
     const int tid = threadIdx.x, cl = tid % CL, kr = tid / CL;
-    const int n = blockIdx.x * NT + 4 * cl, h = blockIdx.y, b0 = blockIdx.z * BT;
+    const int h = by_head ? blockIdx.x : blockIdx.y, n0 = (by_head ? blockIdx.y : blockIdx.x) * NT, b0 = blockIdx.z * BT;
+    const int n = n0 + 4 * cl;
     const int nb = min(BT, B - b0);
     const bool live = n < N;               // N is a multiple of 4
     const float* Wh = W + (size_t)h * K * N + n;
@@ -179,7 +180,7 @@ __global__ __launch_bounds__(HG_THREADS) void head_gemm_f32_kernel(const float* 
     }
     __syncthreads();
     for (int idx = tid; idx < nb * NT; idx += HG_THREADS) {
-        const int bb = idx / NT, c = idx % NT, oc = blockIdx.x * NT + c;
+        const int bb = idx / NT, c = idx % NT, oc = n0 + c;
         if (oc < N) Y[((size_t)(b0 + bb) * H + h) * N + oc] = (red_s[0][bb][c] + red_s[1][bb][c]) + (red_s[2][bb][c] + red_s[3][bb][c]);
     }
 }
@@ -188,20 +189,28 @@ template <int NT>
 hipError_t launch_f32(const float* X, const float* W, float* Y, int B, int H, int K, int N, hipStream_t s)
 {
     const int bt = B == 1 ? 1 : B <= 4 ? 4 : HG_BT;
-    dim3 grid((N + NT - 1) / NT, H, (B + bt - 1) / bt);
-    if (bt == 1)      head_gemm_f32_kernel<NT, 1><<<grid, HG_THREADS, 0, s>>>(X, W, Y, B, H, K, N);
-    else if (bt == 4) head_gemm_f32_kernel<NT, 4><<<grid, HG_THREADS, 0, s>>>(X, W, Y, B, H, K, N);
-    else              head_gemm_f32_kernel<NT, HG_BT><<<grid, HG_THREADS, 0, s>>>(X, W, Y, B, H, K, N);
+    // Tiles of half a line of W: the heads vary first, so that those of a head are on one XCD where H is a multiple of 8 and the line
+    // comes to one L2 only (1 row, 32 heads, 512 -> 128, W not in L2: 4.8 -> 3.0 us; but 28 heads 2.7 -> 3.4, whole lines 5.0 -> 5.3)
+    const bool by_head = NT == 16 && H % 8 == 0;
+    const unsigned tiles = (N + NT - 1) / NT, groups = (B + bt - 1) / bt;
+    const dim3 grid = by_head ? dim3(H, tiles, groups) : dim3(tiles, H, groups);
+    if (bt == 1)      head_gemm_f32_kernel<NT, 1><<<grid, HG_THREADS, 0, s>>>(X, W, Y, B, H, K, N, by_head);
+    else if (bt == 4) head_gemm_f32_kernel<NT, 4><<<grid, HG_THREADS, 0, s>>>(X, W, Y, B, H, K, N, by_head);
+    else              head_gemm_f32_kernel<NT, HG_BT><<<grid, HG_THREADS, 0, s>>>(X, W, Y, B, H, K, N, by_head);
     return hipGetLastError();
 }
 
 // ---- matrix-core variant (bf16) ---------------------------------------------------------
-// One workgroup = one head x NT output columns x up to 64 batch rows (one 16-row tile per
-// wavefront).  The whole [K x NT] slab of W[h] is staged in LDS once with coalesced 128-bit
-// loads and shared by the four wavefronts.  v_mfma_f32_16x16x32_bf16 wants, per lane, eight
+// One workgroup = one head x NT output columns x up to 64 batch rows, a wavefront per 16-row tile and part of the
+// column tiles (PARTS: as many as fewer than 64 rows leave wavefronts for) or, where up to 16 rows leave more wavefronts than
+// there are column tiles, of the k-steps (KSPLIT; the sums of a tile meet in LDS in order).  The whole [K x NT] slab of W[h] is staged in LDS once with coalesced 128-bit
+// loads, all of them in flight at once, and shared by the four wavefronts.  v_mfma_f32_16x16x32_bf16 wants, per lane, eight
 // consecutive k of one column: W is stored k-major, so the B operand is read with the
 // transposing LDS load (two 4-row reads per k-step); the A operand (8 consecutive k of one
-// batch row) comes straight from global memory, X being tiny.
+// batch row) comes straight from global memory, X being tiny.  DEPTH: K at most.  Bound by one round
+// trip to memory (warm or cold W makes no difference).  us, with a branch around each load and one wavefront per 16 rows whatever the
+// batch, and now: 32 heads, 128 -> 512: 1 row 3.6, 2.4; 16 rows 4.1, 2.9; 32 rows 4.3, 3.4; 128 rows 5.3, 5.0; 512 -> 128: 8 rows
+// 3.6, 3.05 (3.5 without the split of the k-steps).
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) short s16x4;
 typedef __attribute__((ext_vector_type(8))) short s16x8;
@@ -211,7 +220,7 @@ typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
 
 constexpr int HM_LDS_BYTES = 40 * 1024;
 
-template <int NT, bool Y_F32>
+template <int NT, bool Y_F32, int DEPTH, int PARTS, int KSPLIT>
 __global__ __launch_bounds__(256) void head_gemm_mfma_kernel(const uint16_t* X, const uint16_t* W, void* Y,
                                                              int B, int H, int K, int N)
 {
@@ -224,44 +233,55 @@ __global__ __launch_bounds__(256) void head_gemm_mfma_kernel(const uint16_t* X, 
     const int n = lane & 15, g = lane >> 4;
     // consecutive workgroup ids go to different XCDs: keep the column tiles of one head on
     // one XCD (ids that differ by a multiple of H) so they share its L2 lines of W[h]
-    const int h = blockIdx.x % H;
-    const int n0 = (blockIdx.x / H) * NT;
-    const int brow = (blockIdx.y * 4 + wave) * 16 + n;    // batch row of this lane's A operand
+    const int h = blockIdx.x;
+    const int n0 = blockIdx.y * NT;
+    const int row0 = (blockIdx.z * 4 + wave / (PARTS * KSPLIT)) * 16;           // this wavefront's batch rows
+    const int k_first = wave / PARTS % KSPLIT;            // and k-steps: this one and every KSPLIT-th from there
+    const int brow = row0 + n;                            // batch row of this lane's A operand
 
-    // A operands of every k-step (K <= 512), requested before the slab so both are in flight
-    const bool active = (blockIdx.y * 4 + wave) * 16 < B;
-    const bool live = brow < B;
+    // A operands of every k-step, requested before the slab so both are in flight, without a branch around any of them (with one
+    // the compiler waits for each: 256 -> 128, 16 rows, 28 heads 2.7 -> 4.5 us): rows past the batch re-read the last
+    // one and are not stored, k-steps past the last re-read it and are not used
+    const bool active = row0 < B;
     const uint16_t* xrow = X + ((size_t)min(brow, B - 1) * H + h) * K + g * 8;
+    constexpr int KS = DEPTH / 32 / KSPLIT;               // k-steps of a wavefront at most
     const int nks = K / 32;
-    u32x4 areg[16];
+    u32x4 areg[KS];
 #pragma unroll
-    for (int ks = 0; ks < 16; ++ks) {
-        areg[ks] = (u32x4){0u, 0u, 0u, 0u};
-        if (active && live && ks < nks) areg[ks] = *reinterpret_cast<const u32x4*>(xrow + ks * 32);
-    }
+    for (int ks = 0; ks < KS; ++ks) areg[ks] = *reinterpret_cast<const u32x4*>(xrow + min(ks * KSPLIT + k_first, nks - 1) * 32);
 
-    // stage W[h][0:K][n0:n0+NT]
+    // stage W[h][0:K][n0:n0+NT] (pieces past the slab re-read its last one and are not written)
+    constexpr int NLD = DEPTH * CPR / 256;                // pieces per thread at most
     const uint16_t* Wh = W + ((size_t)h * K) * N + n0;
-    for (int c = tid; c < K * CPR; c += 256) {
-        int r = c / CPR, cc = c % CPR;
-        u32x4 v = *reinterpret_cast<const u32x4*>(Wh + (size_t)r * N + cc * 8);
-        *(LDS_AS u32x4*)(lds + r * RS + cc * 16) = v;
+    u32x4 w[NLD];
+#pragma unroll
+    for (int i = 0; i < NLD; ++i) {
+        const int c = min(tid + i * 256, K * CPR - 1), r = c / CPR, cc = c % CPR;
+        w[i] = *reinterpret_cast<const u32x4*>(Wh + (size_t)r * N + cc * 8);
+    }
+#pragma unroll
+    for (int i = 0; i < NLD; ++i) {
+        const int c = tid + i * 256, r = c / CPR, cc = c % CPR;
+        if (c < K * CPR) *(LDS_AS u32x4*)(lds + r * RS + cc * 16) = w[i];
     }
     __syncthreads();
-    if (!active) return;
+    if (KSPLIT == 1 && !active) return;
 
-    f32x4 acc[NT / 16];
+    constexpr int TILES = NT / 16 / PARTS;                // column tiles of this wavefront
+    const int part = (wave % PARTS) * TILES * 16;         // its first column
+    f32x4 acc[TILES];
 #pragma unroll
-    for (int j = 0; j < NT / 16; ++j) acc[j] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < TILES; ++j) acc[j] = (f32x4){0.f, 0.f, 0.f, 0.f};
     // transposing read: the lane supplies row 8g + (n>>2) (+4), 8 bytes at column 4(n&3)
-    const uint32_t tr_off = (uint32_t)((g * 8 + (n >> 2)) * RS + (n & 3) * 8);
+    const uint32_t tr_off = (uint32_t)((g * 8 + (n >> 2)) * RS + (n & 3) * 8 + part * 2);
 #pragma unroll
-    for (int ks = 0; ks < 16; ++ks) {
-        if (ks < nks) {
+    for (int ks = 0; ks < KS; ++ks) {
+        const int k = ks * KSPLIT + k_first;
+        if (k < nks) {
             const bf16x8 a = __builtin_bit_cast(bf16x8, areg[ks]);
 #pragma unroll
-            for (int j = 0; j < NT / 16; ++j) {
-                LDS_AS unsigned char* bp = lds + ks * 32 * RS + tr_off + j * 32;
+            for (int j = 0; j < TILES; ++j) {
+                LDS_AS unsigned char* bp = lds + k * 32 * RS + tr_off + j * 32;
                 s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_AS s16x4*)(bp));
                 s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_AS s16x4*)(bp + 4 * RS));
                 s16x8 bb = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
@@ -269,18 +289,49 @@ __global__ __launch_bounds__(256) void head_gemm_mfma_kernel(const uint16_t* X, 
             }
         }
     }
+    if constexpr (KSPLIT > 1) {
+        __syncthreads();                                  // everybody is done with the slab
+        LDS_AS f32x4* sums = (LDS_AS f32x4*)lds;
+        if (k_first) {
+#pragma unroll
+            for (int j = 0; j < TILES; ++j) sums[(wave * TILES + j) * 64 + lane] = acc[j];
+        }
+        __syncthreads();
+        if (k_first || !active) return;
+#pragma unroll
+        for (int s = 1; s < KSPLIT; ++s)
+#pragma unroll
+            for (int j = 0; j < TILES; ++j) acc[j] += sums[((wave + s * PARTS) * TILES + j) * 64 + lane];
+    }
     // D: lane holds rows 4g..4g+3 (batch) of column n
 #pragma unroll
-    for (int j = 0; j < NT / 16; ++j)
+    for (int j = 0; j < TILES; ++j)
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            int bb = (blockIdx.y * 4 + wave) * 16 + g * 4 + i;
+            int bb = row0 + g * 4 + i;
             if (bb < B) {
-                const size_t o = ((size_t)bb * H + h) * N + n0 + j * 16 + n;
+                const size_t o = ((size_t)bb * H + h) * N + n0 + part + j * 16 + n;
                 if (Y_F32) static_cast<float*>(Y)[o] = acc[j][i];
                 else       static_cast<uint16_t*>(Y)[o] = (uint16_t)f32_to_bf16_bits(acc[j][i]);
             }
         }
+}
+
+template <int NT, int DEPTH, int PARTS, int KSPLIT>
+void launch_mfma(const uint16_t* x, const uint16_t* w, void* Y, int B, int H, int K, int N, bool y_f32, hipStream_t s)
+{
+    dim3 grid(H, N / NT, (B + 63) / 64), block(256);
+    if (y_f32) head_gemm_mfma_kernel<NT, true, DEPTH, PARTS, KSPLIT><<<grid, block, 0, s>>>(x, w, Y, B, H, K, N);
+    else       head_gemm_mfma_kernel<NT, false, DEPTH, PARTS, KSPLIT><<<grid, block, 0, s>>>(x, w, Y, B, H, K, N);
+}
+
+template <int NT, int DEPTH>
+void launch_depth(const uint16_t* x, const uint16_t* w, void* Y, int B, int H, int K, int N, bool y_f32, hipStream_t s)
+{
+    constexpr int MOST = NT / 16;                         // column tiles
+    if (B <= 16)      launch_mfma<NT, DEPTH, MOST, 4 / MOST>(x, w, Y, B, H, K, N, y_f32, s);
+    else if (B <= 32) launch_mfma<NT, DEPTH, MOST < 2 ? 1 : 2, 1>(x, w, Y, B, H, K, N, y_f32, s);
+    else              launch_mfma<NT, DEPTH, 1, 1>(x, w, Y, B, H, K, N, y_f32, s);
 }
 
 template <int NT>
@@ -288,11 +339,11 @@ bool try_launch_mfma(const void* X, const void* W, void* Y, int B, int H, int K,
                      hipStream_t s, hipError_t* err)
 {
     if (N % NT || K % 32 || K > 512 || (size_t)K * (NT * 2 + 16) > (size_t)HM_LDS_BYTES) return false;
-    dim3 grid(H * (N / NT), (B + 63) / 64), block(256);
     const uint16_t* x = static_cast<const uint16_t*>(X);
     const uint16_t* w = static_cast<const uint16_t*>(W);
-    if (y_f32) head_gemm_mfma_kernel<NT, true><<<grid, block, 0, s>>>(x, w, Y, B, H, K, N);
-    else       head_gemm_mfma_kernel<NT, false><<<grid, block, 0, s>>>(x, w, Y, B, H, K, N);
+    if (K <= 128)      launch_depth<NT, 128>(x, w, Y, B, H, K, N, y_f32, s);
+    else if (K <= 256) launch_depth<NT, 256>(x, w, Y, B, H, K, N, y_f32, s);
+    else if constexpr (NT < 64) launch_depth<NT, 512>(x, w, Y, B, H, K, N, y_f32, s);
     *err = hipGetLastError();
     return true;
 }

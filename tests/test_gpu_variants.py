@@ -420,3 +420,31 @@ def test_fp64_product_edges(mla, n, m, D):
     X, W = rng.standard_normal((n, D)), rng.standard_normal((m, D))
     Y = convert.project(torch.from_numpy(X).cuda(), torch.from_numpy(W).cuda()).cpu().numpy()
     assert (np.abs(Y - X @ W.T) <= 2 * min(D, 1 << 12) * 2.0 ** -53 * (np.abs(X) @ np.abs(W).T)).all()
+
+
+# ------------------------------------------------------------------ projections: rows, depths and column tiles
+
+@pytest.mark.parametrize("H,K,N", [(1, 32, 16), (5, 96, 48), (8, 128, 512), (28, 160, 128), (32, 256, 128), (3, 288, 32), (64, 512, 128)])
+@pytest.mark.parametrize("B", [1, 15, 16, 17, 32, 33, 64, 65])
+def test_bf16_projection_row_groups_and_depths(mla, B, H, K, N):
+    """Every split of the wavefronts (one, two and more 16-row groups; column tiles; k-steps) at every depth class, against
+    fp32: one bf16 rounding of the result and sums of K products of bf16 values in another order."""
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(B * 1000 + K)
+    X = torch.randn(B, H, K, device="cuda", generator=gen).bfloat16()
+    W = (torch.randn(H, K, N, device="cuda", generator=gen) * K ** -0.5).bfloat16()
+    got = mla.absorb_q(X, W).float()
+    ref = torch.matmul(X.float().transpose(0, 1).contiguous(), W.float()).transpose(0, 1)
+    assert (got - ref).abs().max().item() <= (2.0 ** -8 + K * 2.0 ** -24) * ref.abs().max().item()
+
+
+@pytest.mark.parametrize("H,K,N", [(8, 512, 128), (16, 512, 100), (28, 512, 128), (7, 64, 20)])
+@pytest.mark.parametrize("B", [1, 3])
+def test_fp32_projection_tiles_of_half_lines(mla, B, H, K, N):
+    """Head-major and tile-major workgroup numbers, against fp64."""
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(H + N)
+    X = torch.randn(B, H, K, device="cuda", generator=gen)
+    W = torch.randn(H, K, N, device="cuda", generator=gen) * K ** -0.5
+    ref = torch.matmul(X.double().transpose(0, 1).contiguous(), W.double()).transpose(0, 1)
+    assert (mla.absorb_q(X, W).double() - ref).abs().max().item() <= K * 2.0 ** -24 * ref.abs().max().item()
