@@ -16,6 +16,12 @@
 //   value phase:  wave (a, hp) accumulates the d_c/2 columns [a d_c/2, (a+1) d_c/2) for the 32
 //                 query rows of pair hp over all 32 tile rows (K = 32: v_mfma_f32_16x16x32_bf16,
 //                 one pair of transposing LDS reads feeds two MFMAs).
+// One step scores tile t + 1 and accumulates tile t: the matrix instructions of the two phases and their LDS reads alternate,
+// so that neither waits for the other's operands, and there is one workgroup barrier per tile (it publishes tile t + 1 and the
+// weights of tile t).  Bound by the stream since; with the phases one after the other and a barrier each (one wavefront
+// per SIMD, nothing to fill a phase's start) a tile took 4000 cycles of the 2600 that its rows take to arrive: 16 sequences x 8192
+// rows, two query tokens, 32 heads: 37.6 -> 33.0 us (2.1 of it at the start: query rows without a branch for each load, page ids ahead);
+// the requests spread over the step instead of in front of it: 35.1.
 // Every accumulator is touched by MFMA only; nothing is rescaled in the loop.  The reference of a
 // query row is the maximum of its first tile with a visible row (both halves of the tile, exchanged
 // through LDS once); a later score that exceeds it by more than FAST_GAP is recorded, and the chunk
@@ -28,6 +34,7 @@
 // wave a = 1 holds, and two transposing reads (rows 4g.., rows 16+4g..) give the matching V^T.
 #include "mla_internal.h"
 #include "mfma_tile.h"
+#include <type_traits>
 
 namespace mla {
 namespace {
@@ -35,7 +42,8 @@ namespace {
 constexpr int WD_ROWS = 64;      // query rows per workgroup
 constexpr int WD_NBUF = 4;       // tiles in the LDS ring
 
-template <int D_C>
+// ALONE: one group of query rows, whose workgroup is the rows' only reader (its loads are non-temporal, see decode_mfma.hip)
+template <int D_C, bool ALONE>
 __global__ __launch_bounds__(MF_THREADS, 1) void decode_mfma_wide_kernel(DecodeParams p)
 {
     constexpr int NBUF = WD_NBUF;
@@ -47,9 +55,8 @@ __global__ __launch_bounds__(MF_THREADS, 1) void decode_mfma_wide_kernel(DecodeP
     constexpr int NLOAD = TILE_B / (MF_THREADS * 16);  // 16-byte loads per thread per tile (9 / 5)
     constexpr int NKS = ROW / 32;               // k-steps of the score contraction (18 / 10)
     constexpr int CTW = D_C / 32;               // column tiles of the value contraction per wavefront (16 / 8)
-    constexpr int SG = NKS % 3 == 0 ? 3 : 2;    // k-steps per read-ahead group (score)
-    constexpr int VG = 4;                       // column tiles per read-ahead group (value)
-    constexpr int AH = 2;                       // groups the LDS reads run ahead of the MFMAs
+    constexpr int AH = 3;                       // pairs (k-step, column tile) the LDS reads run ahead of the MFMAs
+    static_assert(CTW <= NKS, "a column tile rides with each of the first k-steps");
     static_assert(2 * NLOAD * 2 < 64, "vmcnt is a 6-bit counter");
 
     __shared__ __attribute__((aligned(1024))) unsigned char smem[NBUF * TILE_B];
@@ -68,9 +75,9 @@ __global__ __launch_bounds__(MF_THREADS, 1) void decode_mfma_wide_kernel(DecodeP
     // Workgroup -> (sequence, chunk, group of 64 query rows).  One group: the two-dimensional grid
     // of the 32-row kernel (sequence rotated by the chunk index).  More: one-dimensional, the
     // groups of a chunk 8 ids apart (same XCD, same time: all but the first find the rows in L2).
-    const int Z = (p.H + WD_ROWS - 1) / WD_ROWS;
     int cx = blockIdx.x, cy = blockIdx.y, zi = 0;
-    if (Z > 1) {
+    if (!ALONE) {
+        const int Z = (p.H + WD_ROWS - 1) / WD_ROWS;
         const int id = blockIdx.x, r = id >> 3;
         zi = r % Z;
         const int c = (r / Z) * 8 + (id & 7);
@@ -94,26 +101,26 @@ __global__ __launch_bounds__(MF_THREADS, 1) void decode_mfma_wide_kernel(DecodeP
     int L = seq_lens_c[b];
 
     // ---- the 64 query rows [q_abs | q_rope], laid out like two cache tiles (one row per query
-    // row, same chunk swizzle, absent rows zero), travel through the last two ring slots
+    // row, same chunk swizzle, absent rows a copy of the last), travel through the last two ring slots
     const uint32_t lds_base = (uint32_t)(uintptr_t)lds;
     LDS_AS unsigned char* qslot = lds + (NBUF - 2) * TILE_B;
     {
         const unsigned char* qa = static_cast<const unsigned char*>(p.q_abs) + ((size_t)b * p.H + hb) * D_C * 2;
         const unsigned char* qr = static_cast<const unsigned char*>(p.q_rope) + ((size_t)b * p.H + hb) * 128;
         const uint32_t dst = lds_base + (uint32_t)((NBUF - 2) * TILE_B + wave * 1024);
+        int r = (wave * 64 + lane) / CPR, c = (wave * 64 + lane) % CPR;        // piece k: MF_THREADS further on
 #pragma unroll
         for (int k = 0; k < 2 * NLOAD; ++k) {
-            const int P = (k * 4 + wave) * 64 + lane;
-            const int r = P / CPR, c = (P % CPR) ^ swz_key(r);
-            if (r < HL) {
-                const unsigned char* gp = c < D_C / 8 ? qa + ((size_t)r * D_C + c * 8) * 2
-                                                      : qr + ((size_t)r * 64 + (c - D_C / 8) * 8) * 2;
-                const uint32_t m0v = __builtin_amdgcn_readfirstlane(dst + k * 4096);
-                asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
-                             :: "s"(m0v), "v"(gp) : "memory");
-            } else {
-                *(LDS_AS u32x4*)(qslot + P * 16) = (u32x4){0u, 0u, 0u, 0u};
-            }
+            const int rr = min(r, HL - 1), cc = c ^ swz_key(r);
+            const bool latent = cc < D_C / 8;
+            const uint32_t off = (uint32_t)(latent ? rr * (D_C * 2) + cc * 16 : rr * 128 + (cc - D_C / 8) * 16);
+            const unsigned char* gp = (latent ? qa : qr) + off;
+            const uint32_t m0v = __builtin_amdgcn_readfirstlane(dst + k * 4096);
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
+                         :: "s"(m0v), "v"(gp) : "memory");
+            r += MF_THREADS / CPR;
+            c += MF_THREADS % CPR;
+            if (c >= CPR) { c -= CPR; ++r; }
         }
     }
 
@@ -135,44 +142,52 @@ __global__ __launch_bounds__(MF_THREADS, 1) void decode_mfma_wide_kernel(DecodeP
 
     // ---- tile staging: HBM -> LDS with direct-to-LDS 128-bit loads (as in the 32-row kernel)
     uint32_t goff[NLOAD];
+    {
+        int r = (wave * 64 + lane) / CPR, c = (wave * 64 + lane) % CPR;
 #pragma unroll
-    for (int k = 0; k < NLOAD; ++k) {
-        int P = (k * 4 + wave) * 64 + lane;
-        int r = P / CPR, pc = P % CPR;
-        goff[k] = (uint32_t)(r * ROWB + ((pc ^ swz_key(r)) << 4));
+        for (int k = 0; k < NLOAD; ++k) {
+            goff[k] = (uint32_t)(r * ROWB + ((c ^ swz_key(r)) << 4));
+            r += MF_THREADS / CPR;
+            c += MF_THREADS % CPR;
+            if (c >= CPR) { c -= CPR; ++r; }
+        }
     }
     const unsigned char* kv = static_cast<const unsigned char*>(p.kv);
-    auto rows_valid = [&](int t) {
-        int page = ptab[t >> 1];
-        return (page >= 0 && page < p.num_pages) ? min(TILE_ROWS, row1 - t * TILE_ROWS) : 0;
-    };
-    auto fetch_tile = [&](int t) -> int {
-        if (rows_valid(t) <= 0) return 0;   // a page outside the pool is never dereferenced
-        const unsigned char* src = kv + (size_t)ptab[t >> 1] * PAGE_B + (size_t)(t & 1) * TILE_B;
+    // Page ids of the tiles from the one last staged on (pages[i]: i tiles after it), looked up a tile before they are asked for: the
+    // look-up is a round trip to the scalar cache, and a tile used to wait for two of them (one after the other).
+    int pages[NBUF];
+    auto page_of = [&](int t) { return ptab[min(t >> 1, p.max_pages - 1)]; };
+    auto rows_valid = [&](int page, int t) { return (page >= 0 && page < p.num_pages) ? min(TILE_ROWS, row1 - t * TILE_ROWS) : 0; };
+    auto fetch_tile = [&](int page, int t) -> int {
+        if (rows_valid(page, t) <= 0) return 0;   // a page outside the pool is never dereferenced
+        const unsigned char* src = kv + (size_t)page * PAGE_B + (size_t)(t & 1) * TILE_B;
         const uint32_t dst = lds_base + (uint32_t)(((t - t0) % NBUF) * TILE_B + wave * 1024);
 #pragma unroll
         for (int k = 0; k < NLOAD; ++k) {
-            const unsigned char* gp = src + goff[k];
             const uint32_t m0v = __builtin_amdgcn_readfirstlane(dst + k * 4096);
-            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
-                         :: "s"(m0v), "v"(gp) : "memory");
+            if (ALONE)
+                asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt"
+                             :: "s"(m0v), "v"(goff[k]), "s"(src) : "memory");
+            else
+                asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+                             :: "s"(m0v), "v"(goff[k]), "s"(src) : "memory");
         }
         return NLOAD;
     };
 
-    // `ahead` holds the loads issued for the tiles after the one being consumed, oldest first
-    int ahead[NBUF - 1];
-    bool ring_full = false;   // the tile NBUF - 1 ahead has been requested before the first stage step
-    // request the first tiles; `upto` of them (the last two slots hold the query rows at first)
-    auto start_ring = [&](int upto) -> int {
+    // ahead[i]: loads issued for tile i after the last one staged.  The first NBUF tiles are requested up front; staging tile u
+    // requests tile u + 2, into the slot of tile u - 2, whose values are used up behind the barrier.
+    int ahead[NBUF];
+    auto request = [&](int first, int last) -> int {    // tiles t0 + first .. t0 + last - 1
+        int issued = 0;
 #pragma unroll
-        for (int i = 0; i < NBUF - 1; ++i) ahead[i] = 0;
-        const int first = fetch_tile(t0);
-#pragma unroll
-        for (int i = 0; i < NBUF - 1; ++i)
-            if (1 + i < upto && t0 + 1 + i < t1) ahead[i] = fetch_tile(t0 + 1 + i);
-        ring_full = upto == NBUF;
-        return first;
+        for (int i = 0; i < NBUF; ++i)
+            if (i >= first && i < last) {
+                pages[i] = page_of(t0 + i);
+                ahead[i] = t0 + i < t1 ? fetch_tile(pages[i], t0 + i) : 0;
+                issued += ahead[i];
+            }
+        return issued;
     };
     auto wait_younger = [&](int younger) {
         if (younger >= 3 * NLOAD)      wait_vmcnt<3 * NLOAD>();
@@ -180,40 +195,35 @@ __global__ __launch_bounds__(MF_THREADS, 1) void decode_mfma_wide_kernel(DecodeP
         else if (younger >= NLOAD)     wait_vmcnt<NLOAD>();
         else                           wait_vmcnt<0>();
     };
-    // publish tile t (and keep the stream going); returns its number of valid rows
-    auto stage_tile = [&](int t, LDS_AS unsigned char* tile) -> int {
-        const int n_valid = rows_valid(t);
+    // publish tile u (and keep the stream going); returns its number of valid rows
+    auto stage_tile = [&](int u) -> int {
         int younger = 0;
 #pragma unroll
-        for (int i = 0; i < NBUF - 1; ++i) younger += ahead[i];
+        for (int i = 1; i < NBUF; ++i) younger += ahead[i];
         wait_younger(younger);
-        // after the barrier everybody's loads of tile t have landed and every wave is done with
-        // tile t - 1 (both phases), whose ring slot now receives tile t + NBUF - 1
+        // after the barrier everybody's loads of tile u have landed and every wave is done with the values of tile u - 2
         __syncthreads();
-        if (!ring_full) {
-            const int tn = t + NBUF - 1;
-            ahead[NBUF - 2] = tn < t1 ? fetch_tile(tn) : 0;
-        }
-        ring_full = false;
-        if (n_valid < TILE_ROWS) {
-            for (int i = tid; i < (TILE_ROWS - n_valid) * CPR; i += MF_THREADS)
-                *(LDS_AS u32x4*)(tile + n_valid * ROWB + i * 16) = (u32x4){0u, 0u, 0u, 0u};
-            __syncthreads();
-        }
+        const int n_valid = rows_valid(pages[0], u);
 #pragma unroll
-        for (int i = 0; i < NBUF - 2; ++i) ahead[i] = ahead[i + 1];
-        ahead[NBUF - 2] = 0;
+        for (int i = 0; i < NBUF - 1; ++i) ahead[i] = ahead[i + 1];
+        ahead[NBUF - 1] = 0;
+        if (u >= t0 + 2 && u + 2 < t1) ahead[1] = fetch_tile(pages[2], u + 2);
+#pragma unroll
+        for (int i = 0; i < NBUF - 1; ++i) pages[i] = pages[i + 1];
+        pages[NBUF - 1] = page_of(u + NBUF);
         return n_valid;
+    };
+    auto slot_of = [&](int t) { return lds + ((t - t0) % NBUF) * TILE_B; };
+    // Rows of a tile that are not there become zeros, for the value contraction (their weights are zeros, what the slot holds need not
+    // be finite); its scores are masked, so the barrier before the values is early enough.
+    auto clear_absent_rows = [&](int t, int n_valid) {
+        LDS_AS unsigned char* tile = slot_of(t);
+        for (int i = tid; i < (TILE_ROWS - n_valid) * CPR; i += MF_THREADS)
+            *(LDS_AS u32x4*)(tile + n_valid * ROWB + i * 16) = (u32x4){0u, 0u, 0u, 0u};
     };
 
     // ---- query rows -> registers (B operands of the score contraction, resident for the chunk)
-    const int first_issued = start_ring(NBUF - 2);
-    {
-        int later = first_issued;
-#pragma unroll
-        for (int i = 0; i < NBUF - 1; ++i) later += ahead[i];
-        wait_younger(later);     // the query rows only: the tile loads requested after them stay in flight
-    }
+    wait_younger(request(0, NBUF - 2));      // the query rows only: the tile loads requested after them stay in flight
     __syncthreads();
     bf16x8 qreg[2][NKS];
     {
@@ -227,10 +237,7 @@ __global__ __launch_bounds__(MF_THREADS, 1) void decode_mfma_wide_kernel(DecodeP
         }
     }
     __syncthreads();
-    // the two slots join the ring
-#pragma unroll
-    for (int i = NBUF - 3; i < NBUF - 1; ++i) ahead[i] = t0 + 1 + i < t1 ? fetch_tile(t0 + 1 + i) : 0;
-    ring_full = true;
+    request(NBUF - 2, NBUF);                 // the two slots join the ring
 
     // ---- per-lane state.  Score phase: this lane's query rows = column n of the two D tiles.
     const int head0 = hp * 32 + n;                    // + 16 hi; local to the workgroup
@@ -259,30 +266,49 @@ __global__ __launch_bounds__(MF_THREADS, 1) void decode_mfma_wide_kernel(DecodeP
         v_base[e] = v_row + ((((uint32_t)(2 * e) + (uint32_t)((n & 3) >> 1)) ^ v_key) << 4) + (uint32_t)((n & 1) * 8) +
                     (uint32_t)(a * D_C);     // column half a starts d_c/2 elements = d_c bytes into the row
 
-    // S^T for this wave's 16 tile rows x 32 query rows, log2 units, rows a query row must not see
-    // (or that are not there) at -inf; lmax = maximum over this lane's 4 tile rows per query row
-    // (the cross-lane step to the maximum over the wave's 16 rows costs two LDS round trips and is
-    // taken only where that maximum is needed)
-    auto score_tile = [&](LDS_AS unsigned char* tile, int t, int n_valid, float (&x)[2][4], float (&lmax)[2]) {
-        f32x4 sacc[2] = {(f32x4){0.f, 0.f, 0.f, 0.f}, (f32x4){0.f, 0.f, 0.f, 0.f}};
-        bf16x8 a0[NKS];
+    // Scores of a tile (S^T for this wave's 16 tile rows x 32 query rows) and O^T += V^T . P^T of another for this wave's column half
+    // and its 32 query rows, all 32 tile rows.
+    auto step = [&](auto qk_tag, auto pv_tag, LDS_AS unsigned char* tile_s, f32x4 (&sacc)[2], LDS_AS unsigned char* tile_v,
+                    LDS_AS unsigned char* pbuf) {
+        constexpr bool QK = decltype(qk_tag)::value, PV = decltype(pv_tag)::value;
+        bf16x8 a0[NKS], pb[2];
+        s16x4 lo[CTW], up[CTW];
+        auto rd = [&](int i) {
+            if (QK && i < NKS) a0[i] = *(LDS_AS bf16x8*)(tile_s + a_base[i & 1] + (i >> 1) * 128);
+            if (PV && i < CTW) {
+                lo[i] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_AS s16x4*)(tile_v + v_base[i & 3] + (i >> 2) * 128));
+                up[i] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_AS s16x4*)(tile_v + v_base[i & 3] + (i >> 2) * 128 + 16 * ROWB));
+            }
+        };
+        if (PV) {
 #pragma unroll
-        for (int ks = 0; ks < AH * SG && ks < NKS; ++ks)
-            a0[ks] = *(LDS_AS bf16x8*)(tile + a_base[ks & 1] + (ks >> 1) * 128);
+            for (int hi = 0; hi < 2; ++hi) pb[hi] = *(LDS_AS bf16x8*)(pbuf + (head0 + hi * 16) * 64 + g * 16);
+        }
+#pragma unroll
+        for (int i = 0; i < AH; ++i) rd(i);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int s0 = 0; s0 < NKS; s0 += SG) {
-#pragma unroll
-            for (int ks = s0 + AH * SG; ks < s0 + (AH + 1) * SG && ks < NKS; ++ks)
-                a0[ks] = *(LDS_AS bf16x8*)(tile + a_base[ks & 1] + (ks >> 1) * 128);
+        for (int i = 0; i < NKS; ++i) {
+            rd(i + AH);
             __builtin_amdgcn_sched_barrier(0);
+            if (QK) {
 #pragma unroll
-            for (int ks = s0; ks < s0 + SG && ks < NKS; ++ks) {
-                sacc[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0[ks], qreg[0][ks], sacc[0], 0, 0, 0);
-                sacc[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0[ks], qreg[1][ks], sacc[1], 0, 0, 0);
+                for (int hi = 0; hi < 2; ++hi)
+                    sacc[hi] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0[i], qreg[hi][i], i ? sacc[hi] : (f32x4){0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+            }
+            if (PV && i < CTW) {
+                const bf16x8 va = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo[i], up[i], 0, 1, 2, 3, 4, 5, 6, 7));
+#pragma unroll
+                for (int hi = 0; hi < 2; ++hi) oacc[hi][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va, pb[hi], oacc[hi][i], 0, 0, 0);
             }
             __builtin_amdgcn_sched_barrier(0);
         }
+    };
+
+    // Scores in log2 units, rows a query row must not see (or that are not there) at -inf; lmax = maximum over this lane's 4 tile
+    // rows per query row (the cross-lane step to the maximum over the wave's 16 rows costs two LDS round trips and is taken only
+    // where that maximum is needed)
+    auto look_at = [&](const f32x4 (&sacc)[2], int t, int n_valid, float (&x)[2][4], float (&lmax)[2]) {
 #pragma unroll
         for (int hi = 0; hi < 2; ++hi)
 #pragma unroll
@@ -292,7 +318,7 @@ __global__ __launch_bounds__(MF_THREADS, 1) void decode_mfma_wide_kernel(DecodeP
             // up to the query token's own position)
 #pragma unroll
             for (int hi = 0; hi < 2; ++hi) {
-                const int seen = min(n_valid, visible_rows(p, L, hb + head0 + hi * 16) - t * TILE_ROWS);
+                const int seen = min(n_valid, visible_rows(p, L, hb + min(head0 + hi * 16, HL - 1)) - t * TILE_ROWS);
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
                     if (a * 16 + g * 4 + i >= seen) x[hi][i] = -INFINITY;
@@ -322,83 +348,55 @@ __global__ __launch_bounds__(MF_THREADS, 1) void decode_mfma_wide_kernel(DecodeP
         v[1] = fmaxf(v[1], xch[(a ^ 1) * WD_ROWS + head0 + 16]);
     };
 
-    // O^T += V^T . P^T for this wave's column half and its 32 query rows, all 32 tile rows
-    auto accumulate_tile = [&](LDS_AS unsigned char* tile, LDS_AS unsigned char* pbuf) {
-        const bf16x8 pb0 = *(LDS_AS bf16x8*)(pbuf + (head0) * 64 + g * 16);
-        const bf16x8 pb1 = *(LDS_AS bf16x8*)(pbuf + (head0 + 16) * 64 + g * 16);
-        s16x4 lo[CTW], hi[CTW];
-#pragma unroll
-        for (int ct = 0; ct < AH * VG && ct < CTW; ++ct) {
-            lo[ct] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_AS s16x4*)(tile + v_base[ct & 3] + (ct >> 2) * 128));
-            hi[ct] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_AS s16x4*)(tile + v_base[ct & 3] + (ct >> 2) * 128 + 16 * ROWB));
+    // ---- the weights of tile t from its scores, against m_ref; while `need_ref`, m_ref is still being established from the first
+    // tile with a visible row.  jumped: some score exceeded its reference by more than FAST_GAP (this wave's rows).
+    bool jumped = false, need_ref = true;
+    bool row_has_ref = false;              // lane l: query row l has its reference (while need_ref)
+    auto weigh = [&](const f32x4 (&sacc)[2], int t, int n_valid) {
+        LDS_AS unsigned char* pbuf = p_lds + ((t - t0) & 1) * (WD_ROWS * 64);
+        float x[2][4], lmax[2];
+        look_at(sacc, t, n_valid, x, lmax);
+        if (need_ref) {
+            float both[2] = {lmax[0], lmax[1]};
+            over_groups(both);
+            exchange_max(both);
+            if (m_ref[0] == -INFINITY) m_ref[0] = both[0];
+            if (m_ref[1] == -INFINITY) m_ref[1] = both[1];
+            // every wave looks at all 64 rows, so all of them drop the exchange at the same tile
+            row_has_ref |= fmaxf(xch[lane], xch[WD_ROWS + lane]) != -INFINITY;
+            need_ref = __ballot(row_has_ref) != ~0ull;
         }
-        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int c0 = 0; c0 < CTW; c0 += VG) {
-#pragma unroll
-            for (int ct = c0 + AH * VG; ct < c0 + (AH + 1) * VG && ct < CTW; ++ct) {
-                lo[ct] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_AS s16x4*)(tile + v_base[ct & 3] + (ct >> 2) * 128));
-                hi[ct] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_AS s16x4*)(tile + v_base[ct & 3] + (ct >> 2) * 128 + 16 * ROWB));
-            }
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int ct = c0; ct < c0 + VG && ct < CTW; ++ct) {
-                const bf16x8 va = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo[ct], hi[ct], 0, 1, 2, 3, 4, 5, 6, 7));
-                oacc[0][ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va, pb0, oacc[0][ct], 0, 0, 0);
-                oacc[1][ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va, pb1, oacc[1][ct], 0, 0, 0);
-            }
-            __builtin_amdgcn_sched_barrier(0);
+        for (int hi = 0; hi < 2; ++hi) {
+            jumped |= lmax[hi] > m_ref[hi] + FAST_GAP;
+            const float m_use = m_ref[hi] == -INFINITY ? 0.f : m_ref[hi];
+            const uint32_t p01 = pack_bf16x2(fast_exp2(x[hi][0] - m_use), fast_exp2(x[hi][1] - m_use));
+            const uint32_t p23 = pack_bf16x2(fast_exp2(x[hi][2] - m_use), fast_exp2(x[hi][3] - m_use));
+            // the normaliser sums exactly the rounded weights that get multiplied
+            l_run[hi] += (bf16_bits_to_f32(p01 & 0xFFFFu) + bf16_bits_to_f32(p01 >> 16)) +
+                         (bf16_bits_to_f32(p23 & 0xFFFFu) + bf16_bits_to_f32(p23 >> 16));
+            // k slots 4a .. 4a+3 of lane group g of query row head0 + 16 hi
+            *(LDS_AS u32x2*)(pbuf + (head0 + hi * 16) * 64 + g * 16 + a * 8) = (u32x2){p01, p23};
         }
     };
-
-    // ---- one sweep over the chunk's tiles.  accumulate = false: only the exact maximum of every
-    // query row is collected (into m_ref, this wave's rows).  accumulate = true: weights against
-    // m_ref and the value contraction; while `need_ref`, m_ref is still being established from
-    // the first tile with a visible row.  Returns whether some score exceeded its reference by
-    // more than FAST_GAP (this wave's rows).
-    auto sweep = [&](bool accumulate, bool need_ref) -> bool {
-        bool jumped = false;
-        bool row_has_ref = false;          // lane l: query row l has its reference (while need_ref)
-        for (int t = t0; t < t1; ++t) {
-            LDS_AS unsigned char* tile = lds + ((t - t0) % NBUF) * TILE_B;
-            LDS_AS unsigned char* pbuf = p_lds + ((t - t0) & 1) * (WD_ROWS * 64);
-            const int n_valid = stage_tile(t, tile);
-            float x[2][4], lmax[2];
-            score_tile(tile, t, n_valid, x, lmax);
-            if (!accumulate) {
-                m_ref[0] = fmaxf(m_ref[0], lmax[0]);      // per lane; combined after the sweep
-                m_ref[1] = fmaxf(m_ref[1], lmax[1]);
-                continue;
-            }
-            if (need_ref) {
-                float both[2] = {lmax[0], lmax[1]};
-                over_groups(both);
-                exchange_max(both);
-                if (m_ref[0] == -INFINITY) m_ref[0] = both[0];
-                if (m_ref[1] == -INFINITY) m_ref[1] = both[1];
-                // every wave looks at all 64 rows, so all of them drop the exchange at the same tile
-                row_has_ref |= fmaxf(xch[lane], xch[WD_ROWS + lane]) != -INFINITY;
-                need_ref = __ballot(row_has_ref) != ~0ull;
-            }
-#pragma unroll
-            for (int hi = 0; hi < 2; ++hi) {
-                jumped |= lmax[hi] > m_ref[hi] + FAST_GAP;
-                const float m_use = m_ref[hi] == -INFINITY ? 0.f : m_ref[hi];
-                const uint32_t p01 = pack_bf16x2(fast_exp2(x[hi][0] - m_use), fast_exp2(x[hi][1] - m_use));
-                const uint32_t p23 = pack_bf16x2(fast_exp2(x[hi][2] - m_use), fast_exp2(x[hi][3] - m_use));
-                // the normaliser sums exactly the rounded weights that get multiplied
-                l_run[hi] += (bf16_bits_to_f32(p01 & 0xFFFFu) + bf16_bits_to_f32(p01 >> 16)) +
-                             (bf16_bits_to_f32(p23 & 0xFFFFu) + bf16_bits_to_f32(p23 >> 16));
-                // k slots 4a .. 4a+3 of lane group g of query row head0 + 16 hi
-                *(LDS_AS u32x2*)(pbuf + (head0 + hi * 16) * 64 + g * 16 + a * 8) = (u32x2){p01, p23};
-            }
-            __syncthreads();     // both halves' weights of this tile are in place
-            accumulate_tile(tile, pbuf);
+    // ---- one sweep over the chunk's tiles
+    auto accumulate = [&]() {
+        f32x4 sacc[2];
+        int n_valid = stage_tile(t0);
+        if (n_valid < TILE_ROWS) clear_absent_rows(t0, n_valid);
+        step(std::true_type{}, std::false_type{}, slot_of(t0), sacc, lds, p_lds);
+        weigh(sacc, t0, n_valid);
+        for (int t = t0; t + 1 < t1; ++t) {
+            n_valid = stage_tile(t + 1);   // (the weights of tile t, too)
+            if (n_valid < TILE_ROWS) clear_absent_rows(t + 1, n_valid);
+            step(std::true_type{}, std::true_type{}, slot_of(t + 1), sacc, slot_of(t), p_lds + ((t - t0) & 1) * (WD_ROWS * 64));
+            weigh(sacc, t + 1, n_valid);
         }
-        return jumped;
+        __syncthreads();
+        step(std::false_type{}, std::true_type{}, lds, sacc, slot_of(t1 - 1), p_lds + ((t1 - 1 - t0) & 1) * (WD_ROWS * 64));
     };
 
-    bool jumped = sweep(true, true);
+    accumulate();
     if (__builtin_expect(__syncthreads_or(jumped), 0)) {
         // ---- careful route (rare): exact maxima first, then the same accumulation against them
         m_ref[0] = m_ref[1] = -INFINITY;
@@ -407,13 +405,22 @@ __global__ __launch_bounds__(MF_THREADS, 1) void decode_mfma_wide_kernel(DecodeP
         for (int hi = 0; hi < 2; ++hi)
 #pragma unroll
             for (int ct = 0; ct < CTW; ++ct) oacc[hi][ct] = (f32x4){0.f, 0.f, 0.f, 0.f};
-        start_ring(NBUF);
-        sweep(false, false);
+        request(0, NBUF);
+        for (int t = t0; t < t1; ++t) {    // the exact maximum of every query row, this wave's rows
+            f32x4 sacc[2];
+            float x[2][4], lmax[2];
+            const int n_valid = stage_tile(t);
+            step(std::true_type{}, std::false_type{}, slot_of(t), sacc, lds, p_lds);
+            look_at(sacc, t, n_valid, x, lmax);
+            m_ref[0] = fmaxf(m_ref[0], lmax[0]);          // per lane; combined after the sweep
+            m_ref[1] = fmaxf(m_ref[1], lmax[1]);
+        }
         __syncthreads();         // every wave is done with the tiles, and with the exchange area
         over_groups(m_ref);
         exchange_max(m_ref);
-        start_ring(NBUF);
-        sweep(true, false);
+        request(0, NBUF);
+        need_ref = false;
+        accumulate();
     }
     __syncthreads();             // every wave is done with the tiles: the ring becomes exchange space
 
@@ -493,8 +500,10 @@ hipError_t launch_decode_mfma_wide(const DecodeParams& p, hipStream_t s)
     const long long nchunk = (long long)p.B * p.num_splits, Z = (p.H + WD_ROWS - 1) / WD_ROWS;
     dim3 grid(p.B, p.num_splits), block(MF_THREADS);
     if (Z > 1) grid = dim3((unsigned)((nchunk + 7) / 8 * 8 * Z));
-    if (p.d_c == 512)      decode_mfma_wide_kernel<512><<<grid, block, 0, s>>>(p);
-    else if (p.d_c == 256) decode_mfma_wide_kernel<256><<<grid, block, 0, s>>>(p);
+    if (p.d_c == 512 && Z == 1)      decode_mfma_wide_kernel<512, true><<<grid, block, 0, s>>>(p);
+    else if (p.d_c == 512)           decode_mfma_wide_kernel<512, false><<<grid, block, 0, s>>>(p);
+    else if (p.d_c == 256 && Z == 1) decode_mfma_wide_kernel<256, true><<<grid, block, 0, s>>>(p);
+    else if (p.d_c == 256)           decode_mfma_wide_kernel<256, false><<<grid, block, 0, s>>>(p);
     else return hipErrorInvalidValue;
     return hipGetLastError();
 }
