@@ -177,17 +177,22 @@ __global__ __launch_bounds__(ST_THREADS, 1) void decode_stream_kernel(DecodePara
     };
     // PAGED: rows of 16-row block rb of tile t that belong to this chunk (0 if its page id is outside the
     // pool), and where in the pool the block begins; a block past the chunk looks nothing up
+    // (a power of two of blocks to a page, as a rule: shifts, and no division of the uniform numbers by way of the vector pipe; the
+    // others divide)
     const int blocks_per_page = page_rows >> 4;
+    const bool pow2 = (blocks_per_page & (blocks_per_page - 1)) == 0;
+    const int page_shift = 31 - __builtin_clz(blocks_per_page);
+    auto page_of_block = [&](int blk) { return pow2 ? blk >> page_shift : blk / blocks_per_page; };
     auto block_valid = [&](int t, int rb) -> int {
         const int R = tb + t * TILE_ROWS + rb * 16;
         if (R >= row1) return 0;
-        const int page = ptab[(R >> 4) / blocks_per_page];
+        const int page = ptab[page_of_block(R >> 4)];
         return page >= 0 && page < p.num_pages ? min(16, row1 - R) : 0;
     };
     auto block_base = [&](int t, int rb) -> size_t {
         const int blk = (tb + t * TILE_ROWS + rb * 16) >> 4;
-        const int page = ptab[blk / blocks_per_page];
-        return ((size_t)page * blocks_per_page + (size_t)(blk % blocks_per_page)) * (size_t)(16 * ROWB);
+        const int in_table = page_of_block(blk);
+        return ((size_t)ptab[in_table] * blocks_per_page + (size_t)(blk - in_table * blocks_per_page)) * (size_t)(16 * ROWB);
     };
 
     // ---- producers: tile staging, HBM -> LDS with direct-to-LDS 128-bit loads (inline assembly:
