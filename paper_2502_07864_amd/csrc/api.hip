@@ -386,7 +386,7 @@ int mla_prefill_mha(const void* q_nope, const void* q_rope, const void* W_UK, co
     int32_t* table2 = reinterpret_cast<int32_t*>(ws + wl.table_off);
     int32_t* lens2 = reinterpret_cast<int32_t*>(ws + wl.lens_off);
     hipError_t e = launch_prefill_materialise(kv_cache, page_table, seq_lens, W_UK, W_UV, ws, pool2, table2, lens2,
-                                              B, heads, d_c, num_pages, max_pages_per_seq, stream);
+                                              B, q_len, heads, d_c, num_pages, max_pages_per_seq, stream);
     if (e != hipSuccess) return MLA_ERR_HIP;
     // the attention: every (sequence, head) pair is a sequence of q_len query rows over its own rows
     DecodeParams p;

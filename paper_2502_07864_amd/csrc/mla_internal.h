@@ -251,7 +251,7 @@ hipError_t launch_prefill_attention(const DecodeParams& p, hipStream_t s);  // c
 bool       prefill_supported(int d_head, int d_c, int d_rope, int page_size, mla_dtype io, mla_dtype cache);
 hipError_t launch_prefill_materialise(const void* kv, const int32_t* page_table, const int32_t* seq_lens,
                                       const void* W_UK, const void* W_UV, void* Wcat, void* pool2, int32_t* table2,
-                                      int32_t* lens2, int B, int heads, int d_c, int num_pages, int max_pages,
+                                      int32_t* lens2, int B, int q_len, int heads, int d_c, int num_pages, int max_pages,
                                       hipStream_t s);
 hipError_t launch_merge(const MergeParams& p, mla_dtype io, hipStream_t s);
 hipError_t launch_gather(const void* kv, const int32_t* page_table, const int32_t* seq_lens,

@@ -6,28 +6,222 @@
 // one (sequence, head) pair is a sequence of its own, and whose page layout (64 keys of 192 values, then
 // the values transposed, both in the order its reads want) is described there.
 //
-//   prefill_weights_kernel      Wcat[h] = [W^{UK}_h ; W^{UV}_h] as 256 rows of d_c values each (the
-//                               value projection is stored k-major by the caller and is transposed
-//                               here once), so that both products read their weights row-wise.
-//   prefill_materialise_kernel  one workgroup per (pair of pages, sequence, head):
-//                               Y^T [256 x 128 tokens] = Wcat[h] [256 x d_c] . C^T [d_c x 128 tokens]
-//                               on v_mfma_f32_16x16x32_bf16; a wavefront owns 32 tokens, keeps
-//                               their latent rows in registers as the B operand and walks the 16
-//                               row tiles of Wcat[h], which all four wavefronts read from LDS;
-//                               results are rounded to bf16 and stored 16 bytes per lane (the page
-//                               layout leaves a lane eight neighbouring values of a key, or of a
-//                               value dimension: the latter a contiguous kilobyte per wavefront).
+//   Y^T [256 x tokens] = [W^{UK}_h ; (W^{UV}_h)^T] [256 x d_c] . C^T [d_c x tokens]
+//
+// on v_mfma_f32_16x16x32_bf16.  A workgroup keeps the weights of one head (d_c = 512: its keys' or its values' half) in LDS for as
+// long as it lives; its 16 (8) wavefronts take the head's half pages of all sequences in turn, each on its own: latent
+// rows into registers as one operand, 128-bit LDS reads of the weights as the other, results rounded to bf16 and stored 16
+// bytes per lane (the page layout leaves a lane eight neighbouring values of a key, or of a value dimension: the
+// latter a contiguous kilobyte per wavefront).  No barrier and no weight traffic after the start.
 #include "mla_internal.h"
 #include "mfma_tile.h"
+#include <algorithm>
 #include <type_traits>
 
 namespace mla {
 namespace {
 
+typedef __attribute__((ext_vector_type(8))) short s16x8;
+
 constexpr int PF_DH = 128;      // head dimension
 constexpr int PF_KEY = 192;     // values per key: 128 + 64
 constexpr int PF_PAGE = 64 * (PF_KEY + PF_DH);    // values per materialised page: 64 keys, then the values transposed
 
+// Weights in LDS: row r (a dimension of the keys or of the values) of d_c values, its 16-byte piece c at position c ^ (r & 15):
+// the 16 lanes that share a cycle of an operand read meet 16 different units.  The values' weights are stored k-major by the caller
+// and are transposed once, at the start, by the transposing LDS read.
+// Bound by the matrix pipe and the LDS reads that feed it (1 KB for two instructions of a wavefront), by the latent rows and by
+// writing 640 bytes per (token, head): 26800 tokens, 28 heads, d_c = 256, 145 us; weights streamed through the LDS by every
+// workgroup, laid out by a launch of its own, took 172 + 9.  Two pages, 28 heads, d_c = 512: 11.3 (15 + 8).
+// Whole pages per wavefront (eight of them): 149; a wavefront's rows requested a unit ahead: 160 to 200 (registers).
+template <int D_C> constexpr int PM_WAVES = 4096 / D_C;            // wavefronts of a workgroup: 16 / 8
+
+template <int D_C>
+__global__ __launch_bounds__(PM_WAVES<D_C> * 64, PM_WAVES<D_C> / 4) void prefill_materialise_kernel(const uint16_t* kv, const int32_t* page_table,
+                                                                               const int32_t* seq_lens, const uint16_t* W_UK, const uint16_t* W_UV,
+                                                                               uint16_t* pool2, int32_t* table2, int32_t* lens2,
+                                                                               int B, int heads, int num_pages, int max_pages)
+{
+    constexpr int ROW = D_C + 64;
+    constexpr int NKS = D_C / 32;
+    constexpr int WROWB = D_C * 2;                    // bytes per weight row
+    constexpr int PARTS = D_C / 256;                  // kinds of workgroups: keys and values, or one of them
+    constexpr int NT = 2;                             // 16-token tiles of a wavefront: half a page
+    constexpr int WAVES = PM_WAVES<D_C>;
+    constexpr int HALF_B = PF_DH * WROWB;             // the weights of the keys, or of the values
+    constexpr int THREADS = WAVES * 64;
+    constexpr int NLD = HALF_B / 16 / THREADS;        // 16-byte pieces per thread of either (4 / 16)
+    constexpr int AH = D_C == 256 ? 2 : 4;            // k-steps that the LDS reads run ahead (as the registers allow)
+    __shared__ __attribute__((aligned(1024))) unsigned char wbuf[2 / PARTS * HALF_B];
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n = lane & 15, g = lane >> 4;
+    const int h = blockIdx.x / PARTS, part = blockIdx.x % PARTS;
+    const bool keys = PARTS == 1 || part == 0, values = PARTS == 1 || part == 1;
+    LDS_AS unsigned char* w_keys = (LDS_AS unsigned char*)wbuf;
+    LDS_AS unsigned char* w_values = w_keys + (2 / PARTS - 1) * HALF_B;
+    const CONST_AS int32_t* lens = (const CONST_AS int32_t*)seq_lens;
+
+    // ---- the weights: all requested at once
+    {
+        u32x4 wk[NLD], wv[NLD];
+        if (keys) {
+#pragma unroll
+            for (int i = 0; i < NLD; ++i)
+                wk[i] = *reinterpret_cast<const u32x4*>(W_UK + (size_t)h * PF_DH * D_C + (i * THREADS + tid) * 8);
+        }
+        if (values) {
+#pragma unroll
+            for (int i = 0; i < NLD; ++i)
+                wv[i] = *reinterpret_cast<const u32x4*>(W_UV + (size_t)h * PF_DH * D_C + (i * THREADS + tid) * 8);
+        }
+        if (blockIdx.y == 0 && keys)
+            for (int b = tid; b < B; b += THREADS) lens2[(size_t)b * heads + h] = max(0, min(seq_lens[b], max_pages * 64));
+        if (keys) {
+#pragma unroll
+            for (int i = 0; i < NLD; ++i) {           // W_UK[h] is [d_head x d_c]
+                const int q = i * THREADS + tid, row = q / (D_C / 8), c = q % (D_C / 8);
+                *(LDS_AS u32x4*)(w_keys + row * WROWB + ((c ^ (row & 15)) << 4)) = wk[i];
+            }
+        }
+        if (values) {                                 // W_UV[h] is [d_c x d_head]: as it lies ...
+#pragma unroll
+            for (int i = 0; i < NLD; ++i) *(LDS_AS u32x4*)(w_values + (i * THREADS + tid) * 16) = wv[i];
+        }
+        __syncthreads();
+        if (values) {                                 // ... then the wavefront's (16 dimensions x 32 k) tiles transposed
+            constexpr int SHARE = PF_DH / 16 * NKS / WAVES;                    // (4 / 16)
+            s16x8 t[SHARE];
+#pragma unroll
+            for (int i = 0; i < SHARE; ++i) {
+                // the lane supplies row 32 ks + 8g + (n >> 2) (and 4 more), 8 bytes at column 16 dt + 4 (n & 3)
+                const int dt = (wave * SHARE + i) / NKS, ks = (wave * SHARE + i) % NKS;
+                LDS_AS unsigned char* at = w_values + (ks * 32 + g * 8 + (n >> 2)) * (PF_DH * 2) + dt * 32 + (n & 3) * 8;
+                const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_AS s16x4*)at);
+                const s16x4 up = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_AS s16x4*)(at + 4 * PF_DH * 2));
+                t[i] = __builtin_shufflevector(lo, up, 0, 1, 2, 3, 4, 5, 6, 7);
+            }
+            __syncthreads();
+#pragma unroll
+            for (int i = 0; i < SHARE; ++i) {
+                const int row = (wave * SHARE + i) / NKS * 16 + n, ks = (wave * SHARE + i) % NKS;
+                *(LDS_AS s16x8*)(w_values + row * WROWB + (((4 * ks + g) ^ (row & 15)) << 4)) = t[i];
+            }
+        }
+        __syncthreads();
+    }
+
+    // A operand: weight row 16 rt + n, piece 4 ks + g
+    uint32_t a_base[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) a_base[e] = (uint32_t)(n * WROWB + (((4 * e + g) ^ n) << 4));
+
+    // ---- this wavefront's share of the half pages of all sequences laid end to end: pages are dealt to the workgroups of the
+    // head first, so that few of them keep as many CUs busy as there are
+    const int stride = gridDim.y * WAVES;
+    auto units_of = [&](int b) { return ((max(0, min(lens[b], max_pages * 64)) + 63) >> 6) * 2; };
+    int b = 0, first = 0, here = units_of(0);         // sequence b's units begin at `first`
+    for (int u = 2 * (blockIdx.y + gridDim.y * (wave >> 1)) + (wave & 1);; u += stride) {
+        while (u >= first + here) {
+            first += here;
+            if (++b >= B) return;
+            here = units_of(b);
+        }
+        const int pg = (u - first) >> 1, tok0 = ((u - first) & 1) * 32;   // page, and this wavefront's first token inside it
+        const int L = max(0, min(lens[b], max_pages * 64));
+        const int page = ((const CONST_AS int32_t*)(page_table + (size_t)b * max_pages))[pg];
+        const bool active = page >= 0 && page < num_pages;
+        // the pseudo-sequence (b, h) owns pages [bh * max_pages, +max_pages) of the materialised pool; a page id
+        // outside the cache pool is passed on as "skip these tokens" (-1), and its page, like the tokens past the
+        // sequence's end, gets zeros for values: what the skipped weights (zeros) are multiplied with
+        const size_t page2 = ((size_t)b * heads + h) * max_pages + pg;
+        if (keys && tok0 == 0 && lane == 0) table2[page2] = active ? (int32_t)page2 : -1;
+        const uint16_t* src = kv + (size_t)(active ? page : 0) * 64 * ROW;
+        uint16_t* dst = pool2 + page2 * PF_PAGE;
+
+        // latent rows of tokens tok0 + 16 nt + n, k = 32 ks + 8g .. + 7
+        bf16x8 cb[NT][NKS];
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+            for (int ks = 0; ks < NKS; ++ks)
+                cb[nt][ks] = *reinterpret_cast<const bf16x8*>(src + (tok0 + nt * 16 + n) * ROW + ks * 32 + g * 8);
+        if (keys) {
+            // decoupled-rope part of the key: copied as it is (16 NT tokens x 8 pieces)
+            u32x4 rope[2 * NT];
+#pragma unroll
+            for (int i = 0; i < 2 * NT; ++i)
+                rope[i] = *reinterpret_cast<const u32x4*>(src + (tok0 + i * 8 + (lane >> 3)) * ROW + D_C + (lane & 7) * 8);
+#pragma unroll
+            for (int i = 0; i < 2 * NT; ++i)
+                *reinterpret_cast<u32x4*>(dst + (tok0 + i * 8 + (lane >> 3)) * PF_KEY + PF_DH + (lane & 7) * 8) = rope[i];
+        }
+        if (!active || pg * 64 + tok0 + NT * 16 > L) {
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) {
+                const bool there = active && pg * 64 + tok0 + nt * 16 + n < L;
+#pragma unroll
+                for (int ks = 0; ks < NKS; ++ks)
+                    if (!there) cb[nt][ks] = __builtin_bit_cast(bf16x8, (u32x4){0u, 0u, 0u, 0u});
+            }
+        }
+
+        // 32 dimensions (two row tiles of the weights) x the wavefront's tokens.  Keys: weights as the A operand (a lane ends with four
+        // dimensions of a token); values: tokens as the A operand (four tokens of a dimension)
+        f32x4 acc[2][NT];
+        auto product = [&](auto of_keys, LDS_AS unsigned char* rows) {
+            bf16x8 a[2][NKS];
+            auto rd = [&](int ks) {
+#pragma unroll
+                for (int ml = 0; ml < 2; ++ml)
+                    a[ml][ks] = *(LDS_AS bf16x8*)(rows + ml * 16 * WROWB + a_base[ks & 3] + (ks >> 2) * 256);
+            };
+#pragma unroll
+            for (int ks = 0; ks < AH; ++ks) rd(ks);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int ks = 0; ks < NKS; ++ks) {
+                if (ks + AH < NKS) rd(ks + AH);
+#pragma unroll
+                for (int ml = 0; ml < 2; ++ml)
+#pragma unroll
+                    for (int nt = 0; nt < NT; ++nt) {
+                        const f32x4 c = ks ? acc[ml][nt] : (f32x4){0.f, 0.f, 0.f, 0.f};
+                        acc[ml][nt] = decltype(of_keys)::value ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[ml][ks], cb[nt][ks], c, 0, 0, 0)
+                                                               : __builtin_amdgcn_mfma_f32_16x16x32_bf16(cb[nt][ks], a[ml][ks], c, 0, 0, 0);
+                    }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        };
+        auto pack8 = [&](const f32x4& lo, const f32x4& up) {
+            return (u32x4){pack_bf16x2(lo[0], lo[1]), pack_bf16x2(lo[2], lo[3]), pack_bf16x2(up[0], up[1]), pack_bf16x2(up[2], up[3])};
+        };
+        if (keys) {
+            for (int c = 0; c < PF_DH / 32; ++c) {
+                product(std::true_type{}, w_keys + c * 32 * WROWB);
+                // 32 dimensions of the tokens: position 8g + 4 ml + i of the 32 is dimension 16 ml + 4g + i
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt)
+                    *reinterpret_cast<u32x4*>(dst + (tok0 + nt * 16 + n) * PF_KEY + c * 32 + g * 8) = pack8(acc[0][nt], acc[1][nt]);
+            }
+        }
+        if (values) {
+            for (int c = 0; c < PF_DH / 32; ++c) {
+                product(std::false_type{}, w_values + c * 32 * WROWB);
+                // half pages of 32 tokens, 32 dimensions: key 4 nt + i of group g is token 16 nt + 4g + i
+#pragma unroll
+                for (int ml = 0; ml < 2; ++ml)
+#pragma unroll
+                    for (int nt = 0; nt < NT; nt += 2)
+                        *reinterpret_cast<u32x4*>(dst + 64 * PF_KEY + (tok0 + nt * 16) * PF_DH + (c * 2 + ml) * 512 + lane * 8) =
+                            pack8(acc[ml][nt], acc[ml][nt + 1]);
+            }
+        }
+    }
+}
+
+// Wcat[h] = [W^{UK}_h ; (W^{UV}_h)^T] as 256 rows of d_c values each, for the kernel below.
 // grid (d_c / 64, 4, heads): a block of 64 rows x 64 columns of Wcat[h]; rows 0 .. 127 are a copy, the others
 // go through LDS (the value projection's rows are columns here: read and written 128 bytes at a time)
 __global__ __launch_bounds__(256) void prefill_weights_kernel(const uint16_t* W_UK, const uint16_t* W_UV,
@@ -48,16 +242,16 @@ __global__ __launch_bounds__(256) void prefill_weights_kernel(const uint16_t* W_
     for (int i = y; i < 64; i += 4) dst[(size_t)i * d_c + x] = block[x][i];
 }
 
-// One workgroup = two pages (128 tokens) of one (sequence, head).  Wcat[h] is streamed through LDS
+// ---- many pages.  One workgroup = two pages (128 tokens) of one (sequence, head).  Wcat[h] is streamed through LDS
 // in chunks of 32 rows (two row tiles, all d_c columns), double-buffered, as direct-to-LDS loads; the four
 // wavefronts share every chunk.  Chunk position c ^ (row & 15) of a row holds its 16-byte piece c: the 16 lanes
 // that share a cycle of an A read (rows 0 .. 7 of one piece and 8 .. 15 of its neighbour, or the reverse) then
 // meet 16 different units (rows padded by 16 bytes, filled through registers, lost 3.2 of 8 cycles per read).
 // A wavefront owns 32 tokens (two column tiles) and keeps their latent rows in registers.
-// Bound by writing 640 bytes per (token, head) beside 0.25 MFLOP of products: 4 x 8192 tokens, 32 heads, d_c = 512
-// 395 -> 351 us (671 MB, 0.27 TFLOP), 26800 tokens, 28 heads, d_c = 256 190 -> 174 us (480 MB).
+// The first weights are asked for before anything else, page and length by scalar loads: 4 x 8192 tokens, 32 heads, d_c = 512
+// 348 -> 333 us (and 11 for the weights' layout); the figures against the kernel above stand at the rule below.
 template <int D_C>
-__global__ __launch_bounds__(256, 2) void prefill_materialise_kernel(const uint16_t* kv, const int32_t* page_table,
+__global__ __launch_bounds__(256, 2) void prefill_stream_kernel(const uint16_t* kv, const int32_t* page_table,
                                                                      const int32_t* seq_lens, const uint16_t* Wcat,
                                                                      uint16_t* pool2, int32_t* table2, int32_t* lens2,
                                                                      int heads, int num_pages, int max_pages)
@@ -78,14 +272,14 @@ __global__ __launch_bounds__(256, 2) void prefill_materialise_kernel(const uint1
     const int n = lane & 15, g = lane >> 4;
     const int bh = blockIdx.y;
     const int b = bh / heads, h = bh % heads;
-    const int L = max(0, min(seq_lens[b], max_pages * 64));
+    const int L = max(0, min(((const CONST_AS int32_t*)seq_lens)[b], max_pages * 64));
     if (blockIdx.x == 0 && tid == 0) lens2[bh] = L;
     if (blockIdx.x * 128 >= L) return;
 
     // this wavefront's page (waves 0, 1: the first of the pair; 2, 3: the second)
     const int pg = blockIdx.x * 2 + (wave >> 1);
     const bool in_seq = pg < max_pages && pg * 64 < L;
-    const int page = in_seq ? page_table[(size_t)b * max_pages + pg] : -1;
+    const int page = in_seq ? ((const CONST_AS int32_t*)(page_table + (size_t)b * max_pages))[pg] : -1;
     const bool active = in_seq && page >= 0 && page < num_pages;
     // the pseudo-sequence (b, h) owns pages [bh * max_pages, +max_pages) of the materialised pool; a page id
     // outside the cache pool is passed on as "skip these tokens" (-1), and its page, like the tokens past the
@@ -95,27 +289,6 @@ __global__ __launch_bounds__(256, 2) void prefill_materialise_kernel(const uint1
     const uint16_t* src = kv + (size_t)(active ? page : 0) * 64 * ROW;
     uint16_t* dst = pool2 + (in_seq ? page2 : 0) * PF_PAGE;
     const int tok0 = (wave & 1) * 32;                 // this wavefront's first token inside its page
-
-    bf16x8 cb[2][NKS];
-    if (in_seq) {
-        // decoupled-rope part of the key: copied as it is (32 tokens x 8 pieces per wavefront)
-        for (int i = lane; i < 32 * 8; i += 64) {
-            const int tok = tok0 + (i >> 3), ch = i & 7;
-            *reinterpret_cast<u32x4*>(dst + tok * PF_KEY + PF_DH + ch * 8) =
-                *reinterpret_cast<const u32x4*>(src + tok * ROW + D_C + ch * 8);
-        }
-        // B operands: latent rows of tokens tok0 + 16 nt + n, k = 32 ks + 8g .. + 7
-#pragma unroll
-        for (int nt = 0; nt < 2; ++nt) {
-            const bool there = active && pg * 64 + tok0 + nt * 16 + n < L;
-#pragma unroll
-            for (int ks = 0; ks < NKS; ++ks) {
-                u32x4 v = *reinterpret_cast<const u32x4*>(src + (tok0 + nt * 16 + n) * ROW + ks * 32 + g * 8);
-                if (!there) v = (u32x4){0u, 0u, 0u, 0u};
-                cb[nt][ks] = __builtin_bit_cast(bf16x8, v);
-            }
-        }
-    }
 
     const unsigned char* W = reinterpret_cast<const unsigned char*>(Wcat + (size_t)h * 256 * D_C);
     constexpr int RPL = 4096 / WROWB;                 // rows that one load of the workgroup covers (4 / 8)
@@ -140,7 +313,34 @@ __global__ __launch_bounds__(256, 2) void prefill_materialise_kernel(const uint1
     uint32_t a_base[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) a_base[e] = (uint32_t)(n * WROWB + (((4 * e + g) ^ n) << 4));
+    // Everything a workgroup reads before its first product is requested at once: a chunk of weights, the decoupled-rope part of
+    // its keys (32 tokens x 8 pieces per wavefront, copied as it is) and the latent rows.
     load_chunk(0);
+    bf16x8 cb[2][NKS];
+    if (in_seq) {
+        u32x4 rope[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            rope[i] = *reinterpret_cast<const u32x4*>(src + (tok0 + i * 8 + (lane >> 3)) * ROW + D_C + (lane & 7) * 8);
+        // B operands: latent rows of tokens tok0 + 16 nt + n, k = 32 ks + 8g .. + 7
+#pragma unroll
+        for (int nt = 0; nt < 2; ++nt)
+#pragma unroll
+            for (int ks = 0; ks < NKS; ++ks)
+                cb[nt][ks] = *reinterpret_cast<const bf16x8*>(src + (tok0 + nt * 16 + n) * ROW + ks * 32 + g * 8);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            *reinterpret_cast<u32x4*>(dst + (tok0 + i * 8 + (lane >> 3)) * PF_KEY + PF_DH + (lane & 7) * 8) = rope[i];
+        if (!active || pg * 64 + tok0 + 32 > L) {
+#pragma unroll
+            for (int nt = 0; nt < 2; ++nt) {
+                const bool there = active && pg * 64 + tok0 + nt * 16 + n < L;
+#pragma unroll
+                for (int ks = 0; ks < NKS; ++ks)
+                    if (!there) cb[nt][ks] = __builtin_bit_cast(bf16x8, (u32x4){0u, 0u, 0u, 0u});
+            }
+        }
+    }
     for (int c = 0; c < NCHUNK; ++c) {
         // my part of this chunk (requested a chunk ago) is there; the two results stored since may be on their way ...
         if (c > 0 && in_seq) wait_vmcnt<2>();
@@ -209,23 +409,43 @@ bool prefill_supported(int d_head, int d_c, int d_rope, int page_size, mla_dtype
 
 hipError_t launch_prefill_materialise(const void* kv, const int32_t* page_table, const int32_t* seq_lens,
                                       const void* W_UK, const void* W_UV, void* Wcat, void* pool2, int32_t* table2,
-                                      int32_t* lens2, int B, int heads, int d_c, int num_pages, int max_pages,
+                                      int32_t* lens2, int B, int q_len, int heads, int d_c, int num_pages, int max_pages,
                                       hipStream_t s)
 {
-    prefill_weights_kernel<<<dim3(d_c / 64, 4, heads), 256, 0, s>>>(static_cast<const uint16_t*>(W_UK),
-                                                           static_cast<const uint16_t*>(W_UV),
-                                                           static_cast<uint16_t*>(Wcat), d_c);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    dim3 grid((max_pages + 1) / 2, B * heads);
-    if (d_c == 512)
-        prefill_materialise_kernel<512><<<grid, 256, 0, s>>>(static_cast<const uint16_t*>(kv), page_table, seq_lens,
-                                                             static_cast<const uint16_t*>(Wcat), static_cast<uint16_t*>(pool2),
-                                                             table2, lens2, heads, num_pages, max_pages);
-    else
-        prefill_materialise_kernel<256><<<grid, 256, 0, s>>>(static_cast<const uint16_t*>(kv), page_table, seq_lens,
-                                                             static_cast<const uint16_t*>(Wcat), static_cast<uint16_t*>(pool2),
-                                                             table2, lens2, heads, num_pages, max_pages);
+    const uint16_t *rows = static_cast<const uint16_t*>(kv), *uk = static_cast<const uint16_t*>(W_UK), *uv = static_cast<const uint16_t*>(W_UV);
+    uint16_t* pool = static_cast<uint16_t*>(pool2);
+    // Weights in LDS (no launch of their own, no barriers): while there are few pages x heads, and, d_c = 256, for short query
+    // runs over very many.  Whole calls, in a row, this form / streamed weights, us:
+    //   16 heads d_c = 256, 8213 tokens (2064 pages x heads) 366 / 383; 4 x 1024, 28 heads (1792) 102 / 108; 3 x 2087, d_c = 512
+    //   (1584) 152 / 160; 32 heads, 4000 tokens, d_c = 512 (2016) 272 / 277; 4 x 1400, 28 heads (2464) 146 / 155 and 169 / 182.
+    //   Beyond: 4 x 1765, 28 heads (3136) 219 / 205; 2 x 9260 (8120) 1639 / 1518: the kernel itself is no slower there (107 and
+    //   111 + 9), but the attention after it is (1.50 and 1.38 ms; the first calls of a run are equal: the clock that the chip holds).
+    //   500 queries on 8 x 6000 (21000) 404 / 422; 512 on 4 x 8000 (14000) 487 / 505; 400 on 16000 (7000) 507 / 486; 1000 on 8000 (3500) 280 / 267;
+    //   128 on 8 x 4000, d_c = 512 (16128) 515 / 498: every latent row is read twice at that width.
+    const long long work = (long long)B * max_pages * heads;
+    const bool resident = work <= 2560 || (d_c == 256 && q_len <= 512 && work >= 8192);
+    if (!resident) {
+        uint16_t* cat = static_cast<uint16_t*>(Wcat);
+        prefill_weights_kernel<<<dim3(d_c / 64, 4, heads), 256, 0, s>>>(uk, uv, cat, d_c);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        const dim3 grid((max_pages + 1) / 2, B * heads);
+        if (d_c == 512) prefill_stream_kernel<512><<<grid, 256, 0, s>>>(rows, page_table, seq_lens, cat, pool, table2, lens2, heads, num_pages, max_pages);
+        else            prefill_stream_kernel<256><<<grid, 256, 0, s>>>(rows, page_table, seq_lens, cat, pool, table2, lens2, heads, num_pages, max_pages);
+        return hipGetLastError();
+    }
+    // One workgroup per CU (its weights fill the LDS), the same number for every head, in one round where that keeps nine tenths of
+    // the CUs busy, else in the first number of rounds that does; never more than there can be pages for.
+    const int kinds = heads * (d_c / 256);
+    int per = 1;
+    for (int rounds = 1; rounds <= 8; ++rounds) {
+        per = std::max(1, 256 * rounds / kinds);
+        if (kinds * per >= 230 * rounds || kinds >= 256 * rounds) break;
+    }
+    per = (int)std::min<long long>(per, (long long)B * max_pages);
+    const dim3 grid(kinds, per);
+    if (d_c == 512) prefill_materialise_kernel<512><<<grid, PM_WAVES<512> * 64, 0, s>>>(rows, page_table, seq_lens, uk, uv, pool, table2, lens2, B, heads, num_pages, max_pages);
+    else            prefill_materialise_kernel<256><<<grid, PM_WAVES<256> * 64, 0, s>>>(rows, page_table, seq_lens, uk, uv, pool, table2, lens2, B, heads, num_pages, max_pages);
     return hipGetLastError();
 }
 

@@ -253,6 +253,35 @@ def test_prefill_skips_bad_pages(mla):
         assert max_abs_rel(widen_gpu(got)[b, t], ref) <= TOL["bf16"]
 
 
+@pytest.mark.parametrize("T,lens,H,d_c,drop", [
+    (2, [31, 32, 33, 63, 64, 65, 1, 0], 3, 256, ()), (2, [31, 32, 33, 63, 64, 65, 1, 0], 3, 512, ()),   # half pages, whole, one row
+    (1, [(131 * i) % 190 for i in range(40)], 28, 256, ((7, 1), (39, 0))),     # more half pages than wavefronts
+    (1, [(131 * i) % 190 for i in range(32)], 28, 512, ((7, 1), (31, 0))),     # 96 pages: weights in LDS
+    (3, [1400, 33, 0, 129, 64], 28, 512, ((0, 0), (0, 20))), (2, [1400, 33, 0, 129, 64], 28, 256, ((0, 0), (0, 20))),   # streamed
+    (1, [1251, 31, 63, 128], 32, 512, ()), (1, [1281, 31, 63, 128], 32, 256, ()),   # 2560 pages x heads: not yet; 2688
+    (1, [(37 * i) % 65 for i in range(256)], 32, 256, ()), (1, [(37 * i) % 65 for i in range(255)], 32, 256, ())])   # 8192: weights in LDS again; 8160
+def test_prefill_materialised_rows(mla, T, lens, H, d_c, drop):
+    """Keys and values of both kernels that write them: sequences that end inside, at and after a half page, empty
+    ones, pages outside the pool; the tokens of such a page count as absent."""
+    import torch
+    w = synth.make_workload("prefill", B=len(lens), H=H, d_head=128, d_c=d_c, d_rope=64, seq_lens=lens, io_dtype="bf16",
+                            cache_dtype="bf16", free_frac=0.1, seed=131)
+    bad, pt, n = w.page_table.copy(), w.page_table.copy(), w.seq_lens.copy()
+    for b, i in sorted(drop, reverse=True):           # the oracle gets the sequence without that page
+        bad[b, i] = w.num_pages + 3 if i else -1
+        if i * 64 < n[b]:
+            n[b] -= min(64, n[b] - 64 * i)
+            pt[b] = np.append(np.delete(pt[b], i), -1)
+    d = DeviceWorkload(w)
+    qn, qr = synth.multi_queries(w, T)
+    got, lse = mla.prefill_mha(to_torch(qn, "bf16"), to_torch(qr, "bf16"), d.W_UK, d.W_UV, d.pool, to_torch(bad, "i32"), d.seq_lens,
+                               w.softmax_scale, return_lse=True)
+    torch.cuda.synchronize()
+    ref, ref_lse = oracle.prefill_explicit(qn, qr, w.W_UK, w.W_UV, w.pool, None, pt, n, w.softmax_scale, w.d_c)
+    assert max_abs_rel(widen_gpu(got), ref) <= TOL["bf16"]
+    assert lse_err(widen_gpu(lse), ref_lse) <= 2e-2
+
+
 @pytest.mark.parametrize("T,L,late", [(200, 210, 150), (200, 225, 153), (129, 129, 128), (300, 331, 169), (256, 260, 132), (140, 191, 180)])
 def test_prefill_later_tokens_stay_out_whatever_they_hold(mla, T, L, late):
     """A token behind every query of a group of 128, in the group's last tile of 32 (and in later ones), whose latent
