@@ -318,7 +318,7 @@ def main():
     if w.io_dtype != "bf16":
         kernel_name = "decode_portable_kernel<float, float, 2, 8>"   # (C1: up to 256 workgroups of two heads)
     elif T > 1:
-        kernel_name = f"decode_mfma_wide_kernel<{d_c}>"
+        kernel_name = f"decode_mfma_wide_kernel<{d_c}, {'true' if T * H <= 64 else 'false'}>"
     elif fp8:
         kernel_name = f"decode_stream_fp8_kernel<{d_c}, {'true' if args.balanced else 'false'}>"
     elif args.balanced:
@@ -489,7 +489,7 @@ def prefill_main(args):
            "config": {"workload": WORKLOADS[args.workload], "batch": B, "q_len": T, "heads": H,
                       "context_max": int(w.seq_lens.max())},
            "tokens_per_s": round(B * T / (ms * 1e-3), 1),
-           "roofline": {"bound": "mfma", "kernel": "prefill_attention_kernel<3, 2> + prefill_materialise_kernel<512>",
+           "roofline": {"bound": "mfma", "kernel": "prefill_attention_kernel<3, 2> + prefill_stream_kernel<512>",
                         "achieved": round(tflops, 1), "peak": 2500.0, "unit": "TFLOP/s",
                         "frac": round(tflops / 2500.0, 4), "traffic": None,
                         "algorithmic_flop_per_step": attn_flop + mat_flop,
@@ -602,12 +602,12 @@ def convert_main(args):
            "checks": {"ritz_residual_over_lambda1": resid, "orthonormality": orth,
                       "captured_second_moment": round(captured, 6), "alpha": out["alpha"].item(),
                       "rope_basis_sweeps_max": int(info[:-2].max()), "ritz_sweeps": int(info[-1])},
-           "roofline": {"bound": "mfma", "kernel": f"gemm_f64_kernel<true, false, true> (S Q, {mj} x {mj} x {p}, K range in slices) "
+           "roofline": {"bound": "mfma", "kernel": f"gemm_f64_kernel<true, false, true> (S Q, {mj} x {mj} x {p}, K steps in equal shares) "
                                                    "+ gemm_f64_reduce_kernel",
                         "achieved": round(tflops, 2), "peak": 78.6, "unit": "TFLOP/s", "frac": round(tflops / 78.6, 4),
                         "traffic": None, "algorithmic_flop_per_launch": flop, "launch_us": round(launch_ms * 1e3, 1),
                         "timing": f"mean of {reps} back-to-back mla_conv_apply calls (product kernel, then the kernel "
-                                  "that sums the slices) between two HIP events on the launch stream"}}
+                                  "that adds the parts of a tile) between two HIP events on the launch stream"}}
     if not args.no_cpu_baseline:
         # the numpy chain on a half-size layer (16 heads: moment matrix 3968 x 3968); the GPU chain on the
         # same sample is timed beside it (no scaling applied: the eigensolvers do not scale linearly)

@@ -9,8 +9,8 @@ namespace conv {
 // C[m, n] = scale * sum_k A(m, k) B(k, n), where A(m, k) = A[m*sAm + k*sAk] and
 // B(k, n) = B[k*sBk + n*sBn]; for each operand one of the two strides is 1.
 // scale = alpha, times *alpha_dev (dev_mode 1) or divided by it (dev_mode 2).
-// partial / partial_doubles: optional scratch; when the tile count alone cannot fill the chip and K is
-// deep, the K range is cut into slices whose products go to the scratch and are summed in a fixed order.
+// partial / partial_doubles: optional scratch; when the tiles alone do not fill the chip evenly, their K steps are laid end to
+// end and cut into equal shares; a share's part of a tile goes to the scratch, and the parts are summed in a fixed order.
 // symmetric: B is A transposed (M = N); where that saves time (scratch given, or more than 256 tiles) the tiles
 // below the diagonal are written as the mirror image of those above, which has their bits: an entry and its
 // image sum the same products in the same order.
@@ -23,7 +23,7 @@ struct GemmF64 {
     const double* alpha_dev; int dev_mode;
     double* partial; size_t partial_doubles;
     int symmetric = 0;
-    int lower = 0;          // B(k, n) = 0 for k > n (B is the transpose of a lower triangle): those k are left out; no partial
+    int lower = 0;          // B(k, n) = 0 for k > n (B is the transpose of a lower triangle): those k are left out; not together with symmetric
 };
 hipError_t launch_gemm_f64(const GemmF64& g, hipStream_t s);
 
