@@ -708,7 +708,8 @@ __global__ __launch_bounds__(1024) void max_diag_kernel(const double* __restrict
 // registers (lane = row, pivots and multipliers by lane reads), the rest of the block on the matrix cores.  What
 // bounds it is that chain, column after column.  As separate kernels (block, panel solve, trailing product; then the
 // inverse row by row with two products each) order 768 took
-// 1330 us, now 300.  Parts of 16 and columns past the end of the last block are left out: a call of top_eig with 5
+// 1330 us, then 300 (a column 27.5; with the pivots' reciprocal roots refined from the instruction's estimate, the rows of the small
+// inverses side by side and the square tiles' one product less 24.1, the pass 284).  Parts of 16 and columns past the end of the last block are left out: a call of top_eig with 5
 // columns and 5 iterations (eight of these) 345 us as separate kernels, 455 with them, 370 without.
 constexpr int CP = 66;                     // row pitch of a block in LDS: 32 lanes that read 16 rows x 2 columns hit 32 units of 8 bytes
 
@@ -788,7 +789,7 @@ __device__ __forceinline__ void factor_invert(double* S, double* V, double* dinv
                     }
                     double d = read_lane(a[j], s0 + j);
                     if (!(d > floor_v)) { d = floor_v; ++nbad; }
-                    const double inv = rsqrt(d);
+                    const double inv = inv_sqrt(d);      // (d is at least 1e-300)
                     if (lane == s0 + j) { a[j] = d; mine = inv; }
                     a[j] *= inv;
 #pragma unroll
@@ -823,12 +824,13 @@ __device__ __forceinline__ void factor_invert(double* S, double* V, double* dinv
         const double* L = S + 16 * wave * (CP + 1);
         double x[16];
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            double v = r == lane ? 1.0 : 0.0;
+        for (int r = 0; r < 16; ++r) x[r] = r == lane ? 1.0 : 0.0;
 #pragma unroll
-            for (int k = 0; k < r; ++k) v -= L[r * CP + k] * x[k];
-            x[r] = v * dinv[16 * wave + r];
-            V[(16 * wave + r) * CP + 16 * wave + lane] = x[r];
+        for (int k = 0; k < 16; ++k) {                   // (a row's terms in the order of k, the rows side by side)
+            x[k] *= dinv[16 * wave + k];
+            V[(16 * wave + k) * CP + 16 * wave + lane] = x[k];
+#pragma unroll
+            for (int r = k + 1; r < 16; ++r) x[r] -= L[r * CP + k] * x[k];
         }
     }
     __syncthreads();
@@ -873,7 +875,9 @@ __global__ __launch_bounds__(256) void chol_step_kernel(double* G, double* X, do
         double vd[16], va[16], vz[16];
         block_get(Linv, NB, k * NB, 0, p, NB, tid, vd);
         block_get(G, p, i * NB, k * NB, p, p, tid, va);
-        if (in_G) block_get(G, p, j * NB, k * NB, p, p, tid, vz);
+        const bool square = i == j;                   // L_jk is L_ik: the next diagonal block is one of these
+        if (square) {
+        } else if (in_G) block_get(G, p, j * NB, k * NB, p, p, tid, vz);
         else if (j < k) block_get(X, p, k * NB, j * NB, p, p, tid, vz);
         else {
 #pragma unroll
@@ -888,17 +892,18 @@ __global__ __launch_bounds__(256) void chol_step_kernel(double* G, double* X, do
                 c[t][r] = j != k && row + 4 * r < p && col + 16 * t < p ? C[(long)(row + 4 * r) * p + col + 16 * t] : 0.0;
         block_stage<false>(D, tid, vd);
         block_stage<false>(A, tid, va);
-        if (in_G) block_stage<false>(Z, tid, vz);
+        if (square) {
+        } else if (in_G) block_stage<false>(Z, tid, vz);
         else block_stage<true>(Z, tid, vz);
         __syncthreads();
         f64x4 l[4];
         block_nt<true>(A, D, wave, lane, l);          // L_ik
-        block_nt<true>(Z, D, wave, lane, u);          // L_jk, or X_kj transposed
+        if (!square) block_nt<true>(Z, D, wave, lane, u);   // L_jk, or X_kj transposed
         __syncthreads();
         block_put(A, wave, lane, l);
-        block_put(Z, wave, lane, u);
+        if (!square) block_put(Z, wave, lane, u);
         __syncthreads();
-        block_nt<false>(A, Z, wave, lane, u);
+        block_nt<false>(A, square ? A : Z, wave, lane, u);
         const bool next = i == k + 1 && j == k + 1;
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
