@@ -707,10 +707,10 @@ __global__ __launch_bounds__(1024) void max_diag_kernel(const double* __restrict
 // workgroup of the next diagonal block goes on to factor and invert it: sixteen columns at a time in one wavefront's
 // registers (lane = row, pivots and multipliers by lane reads), the rest of the block on the matrix cores.  What
 // bounds it is that chain, column after column.  As separate kernels (block, panel solve, trailing product; then the
-// inverse row by row with two products each) order 768 took
-// 1330 us, then 300 (a column 27.5; with the pivots' reciprocal roots refined from the instruction's estimate, the rows of the small
-// inverses side by side and the square tiles' one product less 24.1, the pass 284).  Parts of 16 and columns past the end of the last block are left out: a call of top_eig with 5
-// columns and 5 iterations (eight of these) 345 us as separate kernels, 455 with them, 370 without.
+// inverse row by row with two products each) order 768 took 1330 us, then 300 (a column 27.5); with the pivots' reciprocal
+// roots refined from the instruction's estimate, the rows of the small inverses side by side and one product for a square
+// tile 284 (24.1).  Parts of 16 and columns past the end of the last block are left out: a call of top_eig with 5 columns
+// and 5 iterations (eight of these) 345 us as separate kernels, 455 with them, 370 without.
 constexpr int CP = 66;                     // row pitch of a block in LDS: 32 lanes that read 16 rows x 2 columns hit 32 units of 8 bytes
 
 // c[t] = rows 16 wave .., columns 16 t .. of P R^T (both 64 x 64, row-major); LOWER: R is zero above its diagonal.
