@@ -202,15 +202,18 @@ hipError_t launch_f32(const float* X, const float* W, float* Y, int B, int H, in
 
 // ---- matrix-core variant (bf16) ---------------------------------------------------------
 // One workgroup = one head x NT output columns x up to 64 batch rows, a wavefront per 16-row tile and part of the
-// column tiles (PARTS: as many as fewer than 64 rows leave wavefronts for) or, where up to 16 rows leave more wavefronts than
-// there are column tiles, of the k-steps (KSPLIT; the sums of a tile meet in LDS in order).  The whole [K x NT] slab of W[h] is staged in LDS once with coalesced 128-bit
-// loads, all of them in flight at once, and shared by the four wavefronts.  v_mfma_f32_16x16x32_bf16 wants, per lane, eight
-// consecutive k of one column: W is stored k-major, so the B operand is read with the
-// transposing LDS load (two 4-row reads per k-step); the A operand (8 consecutive k of one
-// batch row) comes straight from global memory, X being tiny.  DEPTH: K at most.  Bound by one round
-// trip to memory (warm or cold W makes no difference).  us, with a branch around each load and one wavefront per 16 rows whatever the
-// batch, and now: 32 heads, 128 -> 512: 1 row 3.6, 2.4; 16 rows 4.1, 2.9; 32 rows 4.3, 3.4; 128 rows 5.3, 5.0; 512 -> 128: 8 rows
-// 3.6, 3.05 (3.5 without the split of the k-steps).
+// column tiles (PARTS: as many as fewer than 64 rows leave wavefronts for).  The whole [K x NT] slab of W[h] is staged in LDS
+// once with coalesced 128-bit loads, all of them in flight at once, and shared by the four wavefronts.
+// v_mfma_f32_16x16x32_bf16 wants, per lane, eight consecutive k of one column: W is stored k-major, so the B operand is read
+// with the transposing LDS load (two 4-row reads per k-step); the A operand (8 consecutive k of one batch row) comes straight
+// from global memory, X being tiny.  A row's k-steps are added in order by one wavefront whatever the batch, so that a
+// row's bits don't depend on how many rows are beside it; sharing the k-steps of up to 16 rows out over the wavefronts as
+// well gave 512 -> 128, 32 heads, 8 rows 2.8 us for 3.1.
+// DEPTH: K is DEPTH or DEPTH - 32, so only the last k-step is asked about and no load repeats more than one (127 rows, 28
+// heads, 320 -> 512: 12.4 us as part of a class for 257 .. 512, 9.3 now).
+// Bound by one round trip to memory (warm or cold W makes no difference).  us, with a branch around each load and one wavefront
+// per 16 rows whatever the batch, and now: 32 heads, 128 -> 512: 1 row 3.4, 2.1; 16 rows 3.9, 2.6; 32 rows 4.1, 2.9; 128 rows
+// 5.1, 4.5; 512 -> 128: 8 rows 3.4, 3.1; 64 rows 4.6, 4.2.
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) short s16x4;
 typedef __attribute__((ext_vector_type(8))) short s16x8;
@@ -220,13 +223,13 @@ typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
 
 constexpr int HM_LDS_BYTES = 40 * 1024;
 
-template <int NT, bool Y_F32, int DEPTH, int PARTS, int KSPLIT>
+template <int NT, bool Y_F32, int DEPTH, int PARTS>
 __global__ __launch_bounds__(256) void head_gemm_mfma_kernel(const uint16_t* X, const uint16_t* W, void* Y,
                                                              int B, int H, int K, int N)
 {
     constexpr int RS = NT * 2 + 16;          // LDS row stride in bytes (padded: rows shift banks)
     constexpr int CPR = NT / 8;              // 16-byte chunks per slab row
-    __shared__ __attribute__((aligned(16))) unsigned char smem[HM_LDS_BYTES];
+    __shared__ __attribute__((aligned(16))) unsigned char smem[DEPTH * RS];
     LDS_AS unsigned char* lds = (LDS_AS unsigned char*)smem;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -235,23 +238,21 @@ __global__ __launch_bounds__(256) void head_gemm_mfma_kernel(const uint16_t* X, 
     // one XCD (ids that differ by a multiple of H) so they share its L2 lines of W[h]
     const int h = blockIdx.x;
     const int n0 = blockIdx.y * NT;
-    const int row0 = (blockIdx.z * 4 + wave / (PARTS * KSPLIT)) * 16;           // this wavefront's batch rows
-    const int k_first = wave / PARTS % KSPLIT;            // and k-steps: this one and every KSPLIT-th from there
+    const int row0 = (blockIdx.z * 4 + wave / PARTS) * 16;                      // this wavefront's batch rows
     const int brow = row0 + n;                            // batch row of this lane's A operand
 
     // A operands of every k-step, requested before the slab so both are in flight, without a branch around any of them (with one
     // the compiler waits for each: 256 -> 128, 16 rows, 28 heads 2.7 -> 4.5 us): rows past the batch re-read the last
-    // one and are not stored, k-steps past the last re-read it and are not used
+    // one and are not stored, a k-step past the last re-reads it and is not used
     const bool active = row0 < B;
     const uint16_t* xrow = X + ((size_t)min(brow, B - 1) * H + h) * K + g * 8;
-    constexpr int KS = DEPTH / 32 / KSPLIT;               // k-steps of a wavefront at most
-    const int nks = K / 32;
+    constexpr int KS = DEPTH / 32;                        // k-steps: KS or KS - 1
     u32x4 areg[KS];
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) areg[ks] = *reinterpret_cast<const u32x4*>(xrow + min(ks * KSPLIT + k_first, nks - 1) * 32);
+    for (int ks = 0; ks < KS; ++ks) areg[ks] = *reinterpret_cast<const u32x4*>(xrow + (ks < KS - 1 ? ks * 32 : K - 32));
 
     // stage W[h][0:K][n0:n0+NT] (pieces past the slab re-read its last one and are not written)
-    constexpr int NLD = DEPTH * CPR / 256;                // pieces per thread at most
+    constexpr int NLD = (DEPTH * CPR + 255) / 256;        // pieces per thread at most
     const uint16_t* Wh = W + ((size_t)h * K) * N + n0;
     u32x4 w[NLD];
 #pragma unroll
@@ -265,7 +266,7 @@ __global__ __launch_bounds__(256) void head_gemm_mfma_kernel(const uint16_t* X, 
         if (c < K * CPR) *(LDS_AS u32x4*)(lds + r * RS + cc * 16) = w[i];
     }
     __syncthreads();
-    if (KSPLIT == 1 && !active) return;
+    if (!active) return;
 
     constexpr int TILES = NT / 16 / PARTS;                // column tiles of this wavefront
     const int part = (wave % PARTS) * TILES * 16;         // its first column
@@ -276,32 +277,17 @@ __global__ __launch_bounds__(256) void head_gemm_mfma_kernel(const uint16_t* X, 
     const uint32_t tr_off = (uint32_t)((g * 8 + (n >> 2)) * RS + (n & 3) * 8 + part * 2);
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
-        const int k = ks * KSPLIT + k_first;
-        if (k < nks) {
+        if (ks < KS - 1 || K == DEPTH) {
             const bf16x8 a = __builtin_bit_cast(bf16x8, areg[ks]);
 #pragma unroll
             for (int j = 0; j < TILES; ++j) {
-                LDS_AS unsigned char* bp = lds + k * 32 * RS + tr_off + j * 32;
+                LDS_AS unsigned char* bp = lds + ks * 32 * RS + tr_off + j * 32;
                 s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_AS s16x4*)(bp));
                 s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_AS s16x4*)(bp + 4 * RS));
                 s16x8 bb = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
                 acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, __builtin_bit_cast(bf16x8, bb), acc[j], 0, 0, 0);
             }
         }
-    }
-    if constexpr (KSPLIT > 1) {
-        __syncthreads();                                  // everybody is done with the slab
-        LDS_AS f32x4* sums = (LDS_AS f32x4*)lds;
-        if (k_first) {
-#pragma unroll
-            for (int j = 0; j < TILES; ++j) sums[(wave * TILES + j) * 64 + lane] = acc[j];
-        }
-        __syncthreads();
-        if (k_first || !active) return;
-#pragma unroll
-        for (int s = 1; s < KSPLIT; ++s)
-#pragma unroll
-            for (int j = 0; j < TILES; ++j) acc[j] += sums[((wave + s * PARTS) * TILES + j) * 64 + lane];
     }
     // D: lane holds rows 4g..4g+3 (batch) of column n
 #pragma unroll
@@ -317,21 +303,25 @@ __global__ __launch_bounds__(256) void head_gemm_mfma_kernel(const uint16_t* X, 
         }
 }
 
-template <int NT, int DEPTH, int PARTS, int KSPLIT>
+template <int NT, int DEPTH, int PARTS>
 void launch_mfma(const uint16_t* x, const uint16_t* w, void* Y, int B, int H, int K, int N, bool y_f32, hipStream_t s)
 {
     dim3 grid(H, N / NT, (B + 63) / 64), block(256);
-    if (y_f32) head_gemm_mfma_kernel<NT, true, DEPTH, PARTS, KSPLIT><<<grid, block, 0, s>>>(x, w, Y, B, H, K, N);
-    else       head_gemm_mfma_kernel<NT, false, DEPTH, PARTS, KSPLIT><<<grid, block, 0, s>>>(x, w, Y, B, H, K, N);
+    if (y_f32) head_gemm_mfma_kernel<NT, true, DEPTH, PARTS><<<grid, block, 0, s>>>(x, w, Y, B, H, K, N);
+    else       head_gemm_mfma_kernel<NT, false, DEPTH, PARTS><<<grid, block, 0, s>>>(x, w, Y, B, H, K, N);
 }
 
-template <int NT, int DEPTH>
+// the class of depths that K (a multiple of 32) belongs to, and the wavefronts' share of the column tiles
+template <int NT, int DEPTH = 64>
 void launch_depth(const uint16_t* x, const uint16_t* w, void* Y, int B, int H, int K, int N, bool y_f32, hipStream_t s)
 {
     constexpr int MOST = NT / 16;                         // column tiles
-    if (B <= 16)      launch_mfma<NT, DEPTH, MOST, 4 / MOST>(x, w, Y, B, H, K, N, y_f32, s);
-    else if (B <= 32) launch_mfma<NT, DEPTH, MOST < 2 ? 1 : 2, 1>(x, w, Y, B, H, K, N, y_f32, s);
-    else              launch_mfma<NT, DEPTH, 1, 1>(x, w, Y, B, H, K, N, y_f32, s);
+    if constexpr (DEPTH <= 512 && DEPTH * (NT * 2 + 16) <= HM_LDS_BYTES) {
+        if (K > DEPTH)    launch_depth<NT, DEPTH + 64>(x, w, Y, B, H, K, N, y_f32, s);
+        else if (B <= 16) launch_mfma<NT, DEPTH, MOST>(x, w, Y, B, H, K, N, y_f32, s);
+        else if (B <= 32) launch_mfma<NT, DEPTH, MOST < 2 ? 1 : 2>(x, w, Y, B, H, K, N, y_f32, s);
+        else              launch_mfma<NT, DEPTH, 1>(x, w, Y, B, H, K, N, y_f32, s);
+    }
 }
 
 template <int NT>
@@ -341,9 +331,7 @@ bool try_launch_mfma(const void* X, const void* W, void* Y, int B, int H, int K,
     if (N % NT || K % 32 || K > 512 || (size_t)K * (NT * 2 + 16) > (size_t)HM_LDS_BYTES) return false;
     const uint16_t* x = static_cast<const uint16_t*>(X);
     const uint16_t* w = static_cast<const uint16_t*>(W);
-    if (K <= 128)      launch_depth<NT, 128>(x, w, Y, B, H, K, N, y_f32, s);
-    else if (K <= 256) launch_depth<NT, 256>(x, w, Y, B, H, K, N, y_f32, s);
-    else if constexpr (NT < 64) launch_depth<NT, 512>(x, w, Y, B, H, K, N, y_f32, s);
+    launch_depth<NT>(x, w, Y, B, H, K, N, y_f32, s);
     *err = hipGetLastError();
     return true;
 }

@@ -467,6 +467,19 @@ def test_bf16_projection_row_groups_and_depths(mla, B, H, K, N):
     assert (got - ref).abs().max().item() <= (2.0 ** -8 + K * 2.0 ** -24) * ref.abs().max().item()
 
 
+@pytest.mark.parametrize("H,K,N", [(28, 128, 256), (28, 256, 128), (32, 512, 128), (32, 128, 256), (64, 352, 128), (32, 128, 512)])
+def test_bf16_projection_rows_keep_their_bits_in_any_batch(mla, H, K, N):
+    """A row's k-steps are added in the same order whatever the batch, so a row has the same bits alone, among 16 and
+    among 70: no tolerance."""
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(K + N)
+    X = torch.randn(70, H, K, device="cuda", generator=gen).bfloat16()
+    W = (torch.randn(H, K, N, device="cuda", generator=gen) * K ** -0.5).bfloat16()
+    whole = mla.absorb_q(X, W)
+    for B in (1, 7, 16, 17, 33, 64):
+        assert torch.equal(mla.absorb_q(X[:B].contiguous(), W), whole[:B])
+
+
 @pytest.mark.parametrize("H,K,N", [(8, 512, 128), (16, 512, 100), (28, 512, 128), (7, 64, 20)])
 @pytest.mark.parametrize("B", [1, 3])
 def test_fp32_projection_tiles_of_half_lines(mla, B, H, K, N):
