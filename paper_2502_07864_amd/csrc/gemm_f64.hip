@@ -138,46 +138,26 @@ struct Cut {
 
 // first tile of row tm when each row of tiles starts at the diagonal
 __host__ __device__ __forceinline__ int row_start(int tm, int tiles_n) { return tm * tiles_n - tm * (tm - 1) / 2; }
-// K steps of column tile tn (lower: the k's up to its last column)
-__host__ __device__ __forceinline__ int steps_of(const GemmF64& g, const Cut& c, int tn)
-{
-    return g.lower ? min(c.nk, ((tn + 1) * BM + BK - 1) / BK) : c.nk;
-}
-// tile number -> row and column of tiles, K steps, and K steps of all tiles before it
-struct Tile { int tm, tn, nk; long before; };
-__host__ __device__ __forceinline__ Tile tile_at(const GemmF64& g, const Cut& c, int tile)
+// tile number -> row and column of tiles, K steps
+struct Tile { int tm, tn, nk; };
+__device__ __forceinline__ Tile tile_at(const GemmF64& g, const Cut& c, int tile)
 {
     Tile t;
+    t.nk = c.nk;
     if (g.symmetric) {
         t.tm = (int)(((2 * c.tiles_n + 1) - sqrtf((2.f * c.tiles_n + 1.f) * (2.f * c.tiles_n + 1.f) - 8.f * tile)) * 0.5f);
         while (t.tm > 0 && tile < row_start(t.tm, c.tiles_n)) --t.tm;           // (the root's rounding)
         while (tile >= row_start(t.tm + 1, c.tiles_n)) ++t.tm;
         t.tn = t.tm + tile - row_start(t.tm, c.tiles_n);
-    } else if (g.lower && !c.share) {          // deepest columns first
+    } else if (g.lower) {                      // deepest columns first: the k's up to a column tile's last column
         t.tm = tile % c.tiles_m;
         t.tn = c.tiles_n - 1 - tile / c.tiles_m;
+        t.nk = min(c.nk, ((t.tn + 1) * BM + BK - 1) / BK);
     } else {
         t.tm = tile / c.tiles_n;
         t.tn = tile % c.tiles_n;
     }
-    t.nk = steps_of(g, c, t.tn);
-    t.before = (long)tile * c.nk;
-    if (g.lower && c.share) {
-        long row = 0, left = 0;
-        for (int n = 0; n < c.tiles_n; ++n) { const int s = steps_of(g, c, n); row += s; left += n < t.tn ? s : 0; }
-        t.before = t.tm * row + left;
-    }
     return t;
-}
-// the tile that K step s of all tiles laid end to end belongs to
-__device__ __forceinline__ int tile_of_step(const GemmF64& g, const Cut& c, long s)
-{
-    if (!g.lower) return (int)(s / c.nk);
-    long row = 0;
-    for (int n = 0; n < c.tiles_n; ++n) row += steps_of(g, c, n);
-    int tile = (int)(s / row) * c.tiles_n;
-    for (long left = s % row; left >= steps_of(g, c, tile % c.tiles_n); ++tile) left -= steps_of(g, c, tile % c.tiles_n);
-    return tile;
 }
 
 __device__ __forceinline__ double scale_of(const GemmF64& g)
@@ -196,23 +176,24 @@ __global__ __launch_bounds__(THREADS, 3) void gemm_f64_kernel(GemmF64 g, Cut c)
 
     // consecutive shares (same rows of A) on one XCD: workgroup ids 8 apart run on one XCD.  Whole tiles of unequal depth: dealt out
     const int per = gridDim.x / 8;
-    const int w = g.lower && !c.share ? (int)blockIdx.x : (int)(blockIdx.x % 8) * per + (int)(blockIdx.x / 8);
+    const int w = g.lower ? (int)blockIdx.x : (int)(blockIdx.x % 8) * per + (int)(blockIdx.x / 8);
     if (w >= c.workgroups) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = (wave >> 1) * (16 * T), wn = (wave & 1) * (16 * T);
     const int li = lane & 15, kq = lane >> 4;
 
-    int tile = c.share ? tile_of_step(g, c, w * c.share) : w;
+    int tile = c.share ? (int)(w * c.share / c.nk) : w;
     long step = c.share ? w * c.share : 0;
     const long end = step + c.share;                     // (past the last tile's end the loop ends by itself)
     for (; tile < c.tiles; ++tile) {
-        Tile at = tile_at(g, c, tile);
+        const Tile at = tile_at(g, c, tile);
         int kt0 = 0, kt1 = at.nk;
         if (c.share) {
             if (step >= end) break;
-            kt0 = (int)(step - at.before);
-            kt1 = (int)min((long)at.nk, end - at.before);
-            step = at.before + kt1;
+            const long before = (long)tile * c.nk;
+            kt0 = (int)(step - before);
+            kt1 = (int)min((long)c.nk, end - before);
+            step = before + kt1;
         }
         const int m0 = at.tm * BM, n0 = at.tn * BM;
         OpA a;
@@ -333,7 +314,8 @@ __global__ __launch_bounds__(256) void gemm_f64_reduce_kernel(GemmF64 g, Cut c)
 {
     const int tile = blockIdx.x, wave = blockIdx.y & 3, f = (blockIdx.y >> 2) * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
     const Tile at = tile_at(g, c, tile);
-    const int w0 = (int)(at.before / c.share), w1 = (int)((at.before + at.nk - 1) / c.share);
+    const long before = (long)tile * c.nk;
+    const int w0 = (int)(before / c.share), w1 = (int)((before + c.nk - 1) / c.share);
     if (w0 == w1) return;                                // one workgroup had the whole tile
     f64x4 sum = {0.0, 0.0, 0.0, 0.0};
     for (int w = w0; w <= w1; ++w) {
@@ -394,13 +376,11 @@ hipError_t launch_gemm_f64(const GemmF64& asked, hipStream_t s)
     if (!g.partial && (long)c.tiles_m * c.tiles_n <= 256) g.symmetric = 0;
     c.tiles = g.symmetric ? row_start(c.tiles_m, c.tiles_n) : c.tiles_m * c.tiles_n;
     c.workgroups = c.tiles;
-    if (g.partial) {
+    if (g.partial && !g.lower) {
         // Shares where the tiles leave CUs without one (us at 256, 512 and 1024 shares: S Q 2304 x 192 50, 59, 58; 1984 x 384 67,
         // 65, 75; 3968 x 768, 744 tiles, whole ones 370, 1024 shares 420), four steps at least.  A part has a slot of its
         // own: number of the workgroup + number of the tile.
-        long steps = 0;
-        for (int n = 0; n < c.tiles_n; ++n) steps += steps_of(g, c, n);
-        steps = g.symmetric ? (long)c.tiles * c.nk : steps * c.tiles_m;
+        const long steps = (long)c.tiles * c.nk;
         const long room = (long)(g.partial_doubles / (BM * BM)) - c.tiles;
         const long shares = std::min({(long)SHARES, room, steps / 4});
         if (shares > c.tiles) {
