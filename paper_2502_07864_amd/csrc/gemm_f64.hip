@@ -14,13 +14,15 @@
 // pieces of 16 bytes swizzled so that the operand reads meet no bank conflict.  Lane group q takes the k's 8 half + 2 q and the
 // one after, which suits both.
 //
-// Given scratch, a product of few tiles has their K steps laid end to end and cut into equal shares, one per CU: a share that
-// begins or ends inside a tile leaves its sum in the scratch, and a second kernel adds a tile's parts in order.
+// Given scratch, a product of few tiles has their K steps laid end to end and cut into equal shares, one or two per CU (three
+// where the tiles are a little more than two): of a share's sums, a tile's first part lies in the result, a later one
+// in the scratch, a whole one is done; a second kernel adds a tile's parts in order.
 //
 // TFLOP/s, the form before (128 x 128, eight wavefronts, through registers, K cut into equal slices of every tile) -> now:
 // X W^T 4096^3 60 -> 67 to 69 (a library product reaches 69), 4096 x 4096 x 512 27 -> 60, 1169 x 512 x 512 7 -> 26;
-// S Q 8128 x 8128 x 768 61 -> 65 to 67, 3968 x 768 57 -> 65, 1984 x 384 34 -> 46, 512 x 192 3.7 -> 6.3; C^T C of 4096 x
-// 8128 (half of it counted) 55 -> 61 to 63, 4096 x 1000 7 -> 23.  Tiles of 128 x 128 with 4 x 4 per wavefront need more than 256 registers (41).
+// S Q 8128 x 8128 x 768 61 -> 65 to 67, 3968 x 768 57 -> 65, 1984 x 384 34 -> 49, 512 x 192 3.7 -> 6.3; C^T C of 4096 x
+// 8128 (half of it counted) 55 -> 61 to 64, 4096 x 1000 7 -> 23.  Narrow ones are bound by reading S: 8128 x 32 309 -> 168 us.
+// Tiles of 128 x 128 with 4 x 4 per wavefront need more than 256 registers (41).
 #include "convert_internal.h"
 #include <algorithm>
 #include <type_traits>
@@ -39,7 +41,6 @@ __device__ __forceinline__ void wait_loads() { __builtin_amdgcn_s_waitcnt(0x0F70
 constexpr int BK = 16;
 constexpr int THREADS = 256;
 constexpr int BM = 64, T = 2;                 // tile, and 16 x 16 tiles of a wavefront each way
-constexpr int SHARES = 256;                   // shares of a product of fewer tiles: one per CU
 
 // One operand of a tile of BM rows (or columns) x 16 k's in LDS, and the thread's share of its way there: DIRECT: 16 bytes
 // per lane straight to LDS (everything on 16 bytes; offsets inside a tile fit 32 bits), else through registers, element by
@@ -130,9 +131,9 @@ struct Operand {
 };
 
 // How a product is cut: tiles_m x tiles_n tiles (symmetric: those on and above the diagonal) of BM x BM; share: K steps per
-// workgroup, 0: a tile per workgroup.
+// workgroup, 0: a tile per workgroup; cols: columns of a part in the scratch.
 struct Cut {
-    int tiles_m, tiles_n, tiles, nk, workgroups;
+    int tiles_m, tiles_n, tiles, nk, workgroups, cols;
     long share;
 };
 
@@ -279,28 +280,31 @@ __global__ __launch_bounds__(THREADS, 3) void gemm_f64_kernel(GemmF64 g, Cut c)
             __builtin_amdgcn_sched_barrier(0);
         }
 
-        if (kt0 > 0 || kt1 < at.nk) {                    // a part of the tile's sum; gemm_f64_reduce_kernel goes on
-            double* part = g.partial + ((size_t)(w + tile) * 4 + wave) * (T * T * 256) + lane;
+        if (kt0 > 0) {                                   // a later part of the tile's sum; gemm_f64_reduce_kernel goes on
+            double* part = g.partial + (size_t)w * BM * c.cols;
 #pragma unroll
             for (int i = 0; i < T; ++i)
 #pragma unroll
-                for (int j = 0; j < T; ++j)
+                for (int j = 0; j < T; ++j) {
+                    const int col = wn + j * 16 + li;
+                    if (col >= c.cols) continue;
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) part[((i * T + j) * 4 + r) * 64] = acc[i][j][r];
-        } else {
-            const double scale = scale_of(g);
+                    for (int r = 0; r < 4; ++r) part[(wm + i * 16 + 4 * r + kq) * c.cols + col] = acc[i][j][r];
+                }
+        } else {                                         // the whole sum, or its first part in its place
+            const bool whole = kt1 == at.nk;
+            const double scale = whole ? scale_of(g) : 1.0;
 #pragma unroll
             for (int i = 0; i < T; ++i)
 #pragma unroll
                 for (int j = 0; j < T; ++j)
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
-                        const int row = m0 + wm + i * 16 + 4 * r + kq;
-                        const int col = n0 + wn + j * 16 + li;
+                        const int row = m0 + wm + i * 16 + 4 * r + kq, col = n0 + wn + j * 16 + li;
                         if (row < g.M && col < g.N) {
                             const double v = scale * acc[i][j][r];
                             g.C[(long)row * g.ldc + col] = v;
-                            if (g.symmetric && at.tm != at.tn) g.C[(long)col * g.ldc + row] = v;
+                            if (g.symmetric && at.tm != at.tn && whole) g.C[(long)col * g.ldc + row] = v;
                         }
                     }
         }
@@ -317,22 +321,25 @@ __global__ __launch_bounds__(256) void gemm_f64_reduce_kernel(GemmF64 g, Cut c)
     const long before = (long)tile * c.nk;
     const int w0 = (int)(before / c.share), w1 = (int)((before + c.nk - 1) / c.share);
     if (w0 == w1) return;                                // one workgroup had the whole tile
+    const int in_row = (wave >> 1) * (16 * T) + (f / T) * 16 + (lane >> 4), in_col = (wave & 1) * (16 * T) + (f % T) * 16 + (lane & 15);
+    if (in_col >= c.cols) return;
+    const int row = at.tm * BM + in_row, col = at.tn * BM + in_col;
     f64x4 sum = {0.0, 0.0, 0.0, 0.0};
-    for (int w = w0; w <= w1; ++w) {
-        const double* part = g.partial + ((size_t)(w + tile) * 4 + wave) * (T * T * 256) + f * 256 + lane;
 #pragma unroll
-        for (int r = 0; r < 4; ++r) sum[r] += part[r * 64];
+    for (int r = 0; r < 4; ++r)
+        if (row + 4 * r < g.M && col < g.N) sum[r] = g.C[(long)(row + 4 * r) * g.ldc + col];
+    for (int w = w0 + 1; w <= w1; ++w) {
+        const double* part = g.partial + (size_t)w * BM * c.cols + in_row * c.cols + in_col;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) sum[r] += part[4 * r * c.cols];
     }
     const double scale = scale_of(g);
-    const int col = at.tn * BM + (wave & 1) * (16 * T) + (f % T) * 16 + (lane & 15);
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const int row = at.tm * BM + (wave >> 1) * (16 * T) + (f / T) * 16 + 4 * r + (lane >> 4);
-        if (row < g.M && col < g.N) {
-            g.C[(long)row * g.ldc + col] = scale * sum[r];
-            if (g.symmetric && at.tm != at.tn) g.C[(long)col * g.ldc + row] = scale * sum[r];
+    for (int r = 0; r < 4; ++r)
+        if (row + 4 * r < g.M && col < g.N) {
+            g.C[(long)(row + 4 * r) * g.ldc + col] = scale * sum[r];
+            if (g.symmetric && at.tm != at.tn) g.C[(long)col * g.ldc + row + 4 * r] = scale * sum[r];
         }
-    }
 }
 
 template <bool A_KC, bool B_KC, bool DIRECT>
@@ -376,13 +383,19 @@ hipError_t launch_gemm_f64(const GemmF64& asked, hipStream_t s)
     if (!g.partial && (long)c.tiles_m * c.tiles_n <= 256) g.symmetric = 0;
     c.tiles = g.symmetric ? row_start(c.tiles_m, c.tiles_n) : c.tiles_m * c.tiles_n;
     c.workgroups = c.tiles;
+    c.cols = std::min(g.N, BM);
     if (g.partial && !g.lower) {
-        // Shares where the tiles leave CUs without one (us at 256, 512 and 1024 shares: S Q 2304 x 192 50, 59, 58; 1984 x 384 67,
-        // 65, 75; 3968 x 768, 744 tiles, whole ones 370, 1024 shares 420), four steps at least.  A part has a slot of its
-        // own: number of the workgroup + number of the tile.
+        // Shares where whole tiles leave CUs without one, or with one less than others: one per CU, four steps at least; two
+        // from 8192 steps on, where a share is long enough to pay for its ends and the other one fills its waits; three
+        // a little above two tiles per CU.  S Q, us at whole tiles, 256, 512 and 768 shares: 1000 x 65 (2016 steps) 51, 20, 26, 26;
+        // 2000 x 128 (8000) 77, 29, 30, 32; 4096 x 32 (16384) 154, 45, 42, 45; 8128 x 128 (254 tiles) 376, 372, 287, 285;
+        // 2304 x 512 (288) 151, -, 101, 96; 3000 x 512 (376) 196, -, 166, 157; 3000 x 600 (470) 198, -, 210, 209; 4096 x 513
+        // (576) 449, -, 389, 355; 8128 x 300 (635) 750, -, 799, 798; 3968 x 768 (744) 366, -, 402, 418.  In between (384, 640) one of
+        // three CUs has a share more than the others.
         const long steps = (long)c.tiles * c.nk;
-        const long room = (long)(g.partial_doubles / (BM * BM)) - c.tiles;
-        const long shares = std::min({(long)SHARES, room, steps / 4});
+        const long room = (long)(g.partial_doubles / ((size_t)BM * c.cols));
+        const bool two = steps >= 8192 && c.tiles <= 400 && room >= 448, three = c.tiles > 512 && c.tiles <= 600 && room >= 768;
+        const long shares = std::min({three ? 768L : two ? 512L : 256L, room, steps / 4});
         if (shares > c.tiles) {
             c.share = (steps + shares - 1) / shares;
             c.workgroups = (int)((steps + c.share - 1) / c.share);

@@ -516,6 +516,21 @@ def test_matrix_product_tile_edges_and_alignment(cv, n, D, m):
         assert rel(host(S), C.T @ C / m) < 1e-12
 
 
+@pytest.mark.parametrize("m,p,scratch", [(1000, 2, 1), (1000, 33, 1), (1001, 65, 1), (4096, 64, 1), (7300, 31, 1), (3600, 128, 1),
+                                         (2001, 513, 1), (4001, 520, 1), (4096, 600, 1), (1000, 65, 0.5), (1000, 65, 0)])
+def test_matrix_product_shares(cv, m, p, scratch):
+    """One share of the K steps per CU, two, three, whole tiles, and as many as a short scratch has room for; parts of few columns.
+    A sum of m products in another order than torch's: m 2^-53 of the sum of their magnitudes, twice."""
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(m + p)
+    S, Q = (torch.randn(s, generator=gen, device="cuda", dtype=torch.float64) for s in ((m, m), (m, p)))
+    ws = torch.empty(int(cv.apply_workspace_bytes(m, p) * scratch), dtype=torch.uint8, device="cuda") if scratch else None
+    got = cv.apply(S, Q, workspace=ws)
+    bound = 2 * m * 2.0 ** -53 * (S.abs() @ Q.abs())
+    assert ((got - S @ Q).abs() <= bound).all()
+    assert torch.equal(got, cv.apply(S, Q, workspace=ws))
+
+
 def test_largest_orders_the_solvers_take(cv):
     """Order 2048 for the eigensolver (its limit) and block width 1024 for the power iteration (its limit)."""
     m = 2048
