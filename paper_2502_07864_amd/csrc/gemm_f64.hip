@@ -23,6 +23,8 @@
 // S Q 8128 x 8128 x 768 61 -> 65 to 67, 3968 x 768 57 -> 65, 1984 x 384 34 -> 49, 512 x 192 3.7 -> 6.3; C^T C of 4096 x
 // 8128 (half of it counted) 55 -> 61 to 64, 4096 x 1000 7 -> 23.  Narrow ones are bound by reading S: 8128 x 32 309 -> 168 us.
 // Tiles of 128 x 128 with 4 x 4 per wavefront need more than 256 registers (41).
+// Registers: 124 of X W^T leave four workgroups per CU, as the 128 that its odd pitches are held to do (2000 x 333 x 2000 65 ->
+// 53 us); the others have three (C^T C held to four: 4096 x 3000 685 -> 788 us).
 #include "convert_internal.h"
 #include <algorithm>
 #include <type_traits>
@@ -167,7 +169,7 @@ __device__ __forceinline__ double scale_of(const GemmF64& g)
 }
 
 template <bool A_KC, bool B_KC, bool DIRECT>
-__global__ __launch_bounds__(THREADS, 3) void gemm_f64_kernel(GemmF64 g, Cut c)
+__global__ __launch_bounds__(THREADS, A_KC && B_KC ? 4 : 3) void gemm_f64_kernel(GemmF64 g, Cut c)
 {
     using OpA = Operand<A_KC, DIRECT>;
     using OpB = Operand<B_KC, DIRECT>;
@@ -280,16 +282,19 @@ __global__ __launch_bounds__(THREADS, 3) void gemm_f64_kernel(GemmF64 g, Cut c)
             __builtin_amdgcn_sched_barrier(0);
         }
 
+        // (the lane's place in a tile anew: what follows from it needs no registers during the product)
+        int lx = li, ly = kq;
+        asm volatile("" : "+v"(lx), "+v"(ly));
         if (kt0 > 0) {                                   // a later part of the tile's sum; gemm_f64_reduce_kernel goes on
             double* part = g.partial + (size_t)w * BM * c.cols;
 #pragma unroll
             for (int i = 0; i < T; ++i)
 #pragma unroll
                 for (int j = 0; j < T; ++j) {
-                    const int col = wn + j * 16 + li;
+                    const int col = wn + j * 16 + lx;
                     if (col >= c.cols) continue;
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) part[(wm + i * 16 + 4 * r + kq) * c.cols + col] = acc[i][j][r];
+                    for (int r = 0; r < 4; ++r) part[(wm + i * 16 + 4 * r + ly) * c.cols + col] = acc[i][j][r];
                 }
         } else {                                         // the whole sum, or its first part in its place
             const bool whole = kt1 == at.nk;
@@ -300,7 +305,7 @@ __global__ __launch_bounds__(THREADS, 3) void gemm_f64_kernel(GemmF64 g, Cut c)
                 for (int j = 0; j < T; ++j)
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
-                        const int row = m0 + wm + i * 16 + 4 * r + kq, col = n0 + wn + j * 16 + li;
+                        const int row = m0 + wm + i * 16 + 4 * r + ly, col = n0 + wn + j * 16 + lx;
                         if (row < g.M && col < g.N) {
                             const double v = scale * acc[i][j][r];
                             g.C[(long)row * g.ldc + col] = v;
