@@ -531,6 +531,18 @@ def test_matrix_product_shares(cv, m, p, scratch):
     assert torch.equal(got, cv.apply(S, Q, workspace=ws))
 
 
+@pytest.mark.parametrize("n,a,b", [(5, 545, 545), (40, 600, 633), (3, 513, 512)])
+def test_joint_moment_of_mirrored_tiles(cv, n, a, b):
+    """More than 256 tiles: the lower ones are turned over in LDS; the same bits above and below the diagonal."""
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    K, V = (torch.randn(s, generator=gen, device="cuda", dtype=torch.float64) for s in ((n, a), (n, b)))
+    S, _ = cv.joint_moment(K, V, dev(np.array([1.0])))
+    C = torch.cat([K, V], 1)
+    assert ((S - C.t() @ C / n).abs() <= 2 * (n + 1) * 2.0 ** -53 * (C.t().abs() @ C.abs() / n)).all()
+    assert torch.equal(S, S.t().contiguous())
+
+
 def test_largest_orders_the_solvers_take(cv):
     """Order 2048 for the eigensolver (its limit) and block width 1024 for the power iteration (its limit)."""
     m = 2048
