@@ -148,26 +148,27 @@ __device__ __forceinline__ long rotated_row(int G, int r, int keep, int groups) 
 //   forward: out[rotated_row(r)] = sum over c of U[c][r] W[row of c]
 //   BACK:    the rows of W are those of the NoPE key (rotated_row - d_rope); out[head i][row of c] = scale times the sum over
 //            r >= keep of U[c][r] W[r], for each of the `per` query heads i of c's key head
-// On the fp64 matrix instructions: the wavefront's part of W is read once, U from the L1.
-// 4096 x 4096, groups of 64: 507 -> 137 us.
-template <bool BACK>
+// On the fp64 matrix instructions: the wavefront's part of W is read once, U from the L1.  Bound by memory; NK: 4 NK
+// components at most (16, 32, 64 or 128), so that a small group has few loads, all in flight at once (those past its end
+// re-read its last one and become zeros).  us, scalar multiply-adds, one form for 128 components, now: 4096 x 4096, groups of 64:
+// 468, 137, 82; 1024 x 4096, groups of 8: 35, 72, 17.
+template <bool BACK, int NK>
 __global__ __launch_bounds__(256) void rotate_rows_kernel(const double* __restrict__ W, const double* __restrict__ U,
                                                           double* __restrict__ out, int g, int d, int M, int keep, int cols,
                                                           int per, const double* __restrict__ scale) {
-    constexpr int NK = MOMENT_MAX_MG / 4;
     const int part = blockIdx.x & 1, Mg = M * g, groups = d / (2 * M), d_rope = 2 * keep * groups;
     const Group grp{(int)(blockIdx.x >> 1), g, d, M};
     const int lane = threadIdx.x & 63, li = lane & 15, kq = lane >> 4;
     const int col = blockIdx.y * 64 + (threadIdx.x >> 6) * 16 + li;
     const bool live = col < cols;
     const double* Ug = U + (long)grp.G * Mg * Mg;
+    const int first = BACK ? keep : 0;                 // of the components that W has rows of
     double w[NK];
 #pragma unroll
     for (int s = 0; s < NK; ++s) {
-        w[s] = 0.0;
-        const int k = 4 * s + kq;
-        if (4 * s < Mg && live && k < Mg && (!BACK || k >= keep))
-            w[s] = W[(BACK ? rotated_row(grp.G, k, keep, groups) - d_rope : (long)grp.column(k)) * cols + (long)part * cols + col];
+        const int k = 4 * s + kq, there = max(first, min(k, Mg - 1));
+        const double x = W[(BACK ? rotated_row(grp.G, there, keep, groups) - d_rope : (long)grp.column(there)) * cols + (long)part * cols + min(col, cols - 1)];
+        w[s] = k >= first && k < Mg ? x : 0.0;
     }
     const double f = BACK ? *scale : 1.0;
     for (int m0 = 0; m0 < Mg; m0 += 16) {
@@ -176,9 +177,9 @@ __global__ __launch_bounds__(256) void rotate_rows_kernel(const double* __restri
         const int m = m0 + li;
 #pragma unroll
         for (int s = 0; s < NK; ++s) {
-            u[s] = 0.0;
-            const int k = 4 * s + kq;
-            if (4 * s < Mg && k < Mg && m < Mg) u[s] = BACK ? Ug[(long)m * Mg + k] : Ug[(long)k * Mg + m];
+            const int k = min(4 * s + kq, Mg - 1), c = min(m, Mg - 1);      // (columns past the end are not stored)
+            const double x = BACK ? Ug[c * Mg + k] : Ug[k * Mg + c];
+            u[s] = 4 * s + kq < Mg ? x : 0.0;
         }
 #pragma unroll
         for (int s = 0; s < NK; ++s)
@@ -1017,17 +1018,23 @@ hipError_t launch_rope_moments(const double* K, double* sigma, int n, int g, int
     return hipGetLastError();
 }
 
-hipError_t launch_rotate_rows(const double* W, const double* U, double* W_out, int g, int d, int M, int keep, int cols, hipStream_t s) {
-    dim3 grid(2 * (d / (2 * M)), (cols + 63) / 64);
-    rotate_rows_kernel<false><<<grid, 256, 0, s>>>(W, U, W_out, g, d, M, keep, cols, 1, nullptr);
+template <bool BACK>
+static hipError_t rotate_rows(const double* W, const double* U, double* out, int g, int d, int M, int keep, int cols, int per,
+                              const double* scale, hipStream_t s) {
+    const dim3 grid(2 * (d / (2 * M)), (cols + 63) / 64);
+    const auto kernel = M * g <= 16 ? &rotate_rows_kernel<BACK, 4> : M * g <= 32 ? &rotate_rows_kernel<BACK, 8>
+                      : M * g <= 64 ? &rotate_rows_kernel<BACK, 16> : &rotate_rows_kernel<BACK, MOMENT_MAX_MG / 4>;
+    kernel<<<grid, 256, 0, s>>>(W, U, out, g, d, M, keep, cols, per, scale);
     return hipGetLastError();
+}
+
+hipError_t launch_rotate_rows(const double* W, const double* U, double* W_out, int g, int d, int M, int keep, int cols, hipStream_t s) {
+    return rotate_rows<false>(W, U, W_out, g, d, M, keep, cols, 1, nullptr, s);
 }
 
 hipError_t launch_rotate_back(const double* R, const double* U, double* W_UK, int g, int h, int d, int M, int keep, int cols,
                               const double* alpha, hipStream_t s) {
-    dim3 grid(2 * (d / (2 * M)), (cols + 63) / 64);
-    rotate_rows_kernel<true><<<grid, 256, 0, s>>>(R, U, W_UK, g, d, M, keep, cols, h / g, alpha);
-    return hipGetLastError();
+    return rotate_rows<true>(R, U, W_UK, g, d, M, keep, cols, h / g, alpha, s);
 }
 
 hipError_t launch_rotate_columns(const double* K, const double* U, double* C, int ldc, int n, int g, int d, int M, int keep, hipStream_t s) {

@@ -130,6 +130,16 @@ def test_rotate_rows(cv, g, d, M, keep, cols):
     assert rel(got, co.rotate_rows(W, U, g, d, M, keep)) < 1e-12
 
 
+@pytest.mark.parametrize("g,d,M,keep,cols", [(1, 4, 1, 1, 1), (16, 8, 1, 1, 65), (17, 8, 1, 1, 16), (8, 16, 4, 3, 70), (11, 12, 3, 1, 15),
+                                             (32, 8, 2, 2, 64), (13, 20, 5, 4, 130), (32, 16, 4, 1, 17)])
+def test_rotate_rows_group_sizes(cv, g, d, M, keep, cols):
+    """Groups of 1, 16, 17, 32, 33, 64, 65 and 128 components: each number of loads a wavefront may have, full and not."""
+    r = rng(g * M)
+    W = r.standard_normal((g * d, cols))
+    U = r.standard_normal((d // (2 * M), M * g, M * g))
+    assert rel(host(cv.rotate_rows(dev(W), dev(U), g, d, M, keep)), co.rotate_rows(W, U, g, d, M, keep)) < 1e-12
+
+
 @pytest.mark.parametrize("n,a,b", [(100, 48, 64), (1, 3, 5), (333, 130, 7)])
 def test_kv_balance_and_joint_moment(cv, n, a, b):
     r = rng(n + a)
