@@ -56,7 +56,7 @@ int mla_conv_rope_moments(const double* K, double* sigma,
  * by descending eigenvalue; also the PCA of App. D.2).  Cyclic Jacobi rotations, one
  * workgroup per matrix up to m = 128; a larger matrix is spread over the chip (rotations inside pairs of
  * blocks of 16 indices, then their products applied), the batch is then processed one matrix after the
- * other, and at most 24 sweeps are run.
+ * other, and at most 26 sweeps are run.
  *   A      [batch, m, m]  in: symmetric matrices; out: eigenvectors in the COLUMNS, column c
  *                         belonging to evals[c]
  *   evals  [batch, m]     eigenvalues, descending

@@ -563,6 +563,15 @@ __global__ __launch_bounds__(64) void jw_norm_kernel(const double* __restrict__ 
     }
 }
 
+// blocks I < J of pair k of a step: the rotations inside a pair take its indices in their order in the matrix (in the
+// schedule's order, orders with multiple eigenvalues took up to a sweep more)
+__device__ __forceinline__ void block_pair(int k, int step, int nbp, int& I, int& J) {
+    int p, q;
+    round_robin_pair(k, step, nbp, p, q);
+    I = min(p, q);
+    J = max(p, q);
+}
+
 // index r of pair (I, J) in the matrix (>= m: not there)
 __device__ __forceinline__ int pair_index(int I, int J, int r) { return (r < JB ? I : J) * JB + (r & (JB - 1)); }
 
@@ -575,7 +584,7 @@ __global__ __launch_bounds__(256) void jb_pair_kernel(double* A, double* __restr
     if (st->done) return;
     const int tid = threadIdx.x;
     int I, J;
-    round_robin_pair(blockIdx.x, step, nbp, I, J);
+    block_pair(blockIdx.x, step, nbp, I, J);
     for (int idx = tid; idx < JP * JP; idx += 256) {
         const int r = idx / JP, c = idx % JP, i = pair_index(I, J, r), j = pair_index(I, J, c);
         a[0][r * LD + c] = i < m && j < m ? A[(long)i * m + j] : 0.0;      // indices that are not there rotate with nothing
@@ -625,8 +634,8 @@ __global__ __launch_bounds__(256) void jb_update_kernel(double* A, double* V, co
     const bool on_v = blockIdx.z == 1;
     if (!on_v && P == Q) return;                       // the pair's own tile has been rotated where the angles were found
     int I, J, K, L;
-    round_robin_pair(Q, step, nbp, I, J);
-    round_robin_pair(P, step, nbp, K, L);
+    block_pair(Q, step, nbp, I, J);
+    block_pair(P, step, nbp, K, L);
     double* M = on_v ? V : A;
     auto row_of = [&](int r) { return on_v ? P * JP + r : pair_index(K, L, r); };
     for (int idx = tid; idx < JP * JP; idx += 256) {
@@ -1109,8 +1118,9 @@ hipError_t launch_jacobi(double* A, double* evals, double* work, int* info, int 
         void* extra = work + (size_t)batch * m * m;
         // every sweep enqueued costs its launches even after convergence (order 768: 0.24 ms).  Single rotations over the whole
         // matrix took up to 16 where they converged; sweeps over pairs of blocks take as many or fewer on full, graded and
-        // nearly diagonal spectra, but up to 7 more on low ranks and multiple eigenvalues (rank 40 or 100 of 256: 12 and 17 to 20)
-        const int sweeps = std::min(max_sweeps, 24);
+        // nearly diagonal spectra, but up to 7 more on low ranks and multiple eigenvalues (rank 40 or 100 of 256: 12 and 17 to 20;
+        // three eigenvalues 85 times each: 24 or 25)
+        const int sweeps = std::min(max_sweeps, 26);
         for (int b = 0; b < batch; ++b) {
             hipError_t e = launch_jacobi_wide(A + (size_t)b * m * m, evals + (size_t)b * m, work + (size_t)b * m * m,
                                               extra, info + b, m, sweeps, s);

@@ -437,6 +437,23 @@ def test_cholesky_qr_block_edges(mla, p):
     assert np.abs(Q0 - R @ (R.T @ Q0)).max() <= tol * np.abs(Q0).max()
 
 
+@pytest.mark.parametrize("m,seed", [(200, 0), (256, 0), (256, 1), (256, 2), (256, 3)])
+def test_sym_eig_of_three_multiple_eigenvalues(mla, m, seed):
+    """Eigenvalues 1, 2 and 3, a third of the order each: the slowest spectrum for sweeps over pairs of blocks still converges."""
+    import torch
+    from paper_2502_07864_amd import convert
+    Q, _ = np.linalg.qr(synth.stream(112 + seed, m).standard_normal((m, m)))
+    want = np.arange(m) // (m // 3) + 1.0
+    A = (Q * want) @ Q.T
+    A = (A + A.T) / 2
+    evals, U, info = convert.sym_eig(torch.from_numpy(A[None]).cuda())
+    evals, U = evals.cpu().numpy()[0], U.cpu().numpy()[0]
+    assert int(info[0]) >= 1
+    assert np.abs(U.T @ U - np.eye(m)).max() <= 1e-12
+    assert np.abs(evals - np.sort(want)[::-1]).max() <= 1e-12 * np.linalg.norm(A)
+    assert np.abs(A @ U - U * evals).max() <= 1e-12 * np.linalg.norm(A)
+
+
 # ------------------------------------------------------------------ conversion: matrix product, steps of K and strides
 
 @pytest.mark.parametrize("n,m,D", [(1, 1, 1), (3, 129, 15), (128, 128, 16), (129, 5, 17), (200, 260, 47), (2, 3, (1 << 22) + 4)])
