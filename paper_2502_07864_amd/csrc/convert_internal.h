@@ -52,8 +52,10 @@ hipError_t launch_balance(const double* K, int ldk, const double* V, int ldv, co
 size_t jacobi_work_bytes(int batch, int m);
 hipError_t launch_jacobi(double* A, double* evals, double* work, int* info, int batch, int m, int max_sweeps, hipStream_t s);
 // X = the inverse of the lower Cholesky factor of G (p x p, symmetric positive definite), zero above the diagonal;
-// *bad += clamped pivots; G is overwritten.  tmp: chol_tmp_doubles(p) doubles of scratch.
-inline size_t chol_tmp_doubles(int p) { return 8 + (size_t)64 * p; }
+// *bad += clamped pivots; G is overwritten.  p <= TOP_MAX_P.  tmp: chol_tmp_doubles(p) doubles of scratch.
+constexpr int CHOL_HEAD = 24;        // of them, in front: the pivots' floor, a word of marks per 64 columns
+static_assert(1 + TOP_MAX_P / 64 <= CHOL_HEAD, "room for the marks");
+inline size_t chol_tmp_doubles(int p) { return CHOL_HEAD + (size_t)64 * p; }
 hipError_t launch_chol_inverse(double* G, double* X, double* tmp, int p, int* bad, hipStream_t s);
 hipError_t launch_symmetrise(double* T, int p, hipStream_t s);
 hipError_t launch_fill_int(int* dst, int value, int count, hipStream_t s);

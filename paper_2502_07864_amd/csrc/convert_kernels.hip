@@ -771,10 +771,13 @@ __device__ __forceinline__ double read_lane(double v, int lane) {
 }
 
 // S (64 x 64, its lower half; nb rows and columns of it) = L L^T -> V = L^{-1}.  Four wavefronts; pivots not above
-// floor_v are replaced by it and counted.
+// floor_v are replaced by it, counted and marked in *marks (bit: column).  What stands below such a pivot is rounding: L has
+// zeros there (here, and in the blocks below, whose kernel reads the marks).  Kept, it is divided by a pivot that may be
+// hundreds of times smaller, and from a block that lacks some ten ranks on the factors grew past 1e308.
 // WHOLE: nb = 64, known at compile time.
 template <bool WHOLE>
-__device__ __forceinline__ void factor_invert(double* S, double* V, double* dinv, int nb, double floor_v, int* bad, int tid) {
+__device__ __forceinline__ void factor_invert(double* S, double* V, double* dinv, int nb, double floor_v, int* bad,
+                                              unsigned long long* marks, int tid) {
     const int lane = tid & 63, wave = tid >> 6, li = lane & 15, kq = lane >> 4;
     for (int idx = tid; idx < 64 * CP; idx += 256) {
         const int r = idx / CP, c = idx % CP;
@@ -782,7 +785,7 @@ __device__ __forceinline__ void factor_invert(double* S, double* V, double* dinv
         if (r >= nb) S[idx] = r == c ? 1.0 : 0.0;        // rows past the end: identity
     }
     __syncthreads();
-    int nbad = 0;
+    unsigned long long dropped = 0;
     const int nsb = WHOLE ? 4 : (nb + 15) / 16;          // parts of 16 that hold rows: the others are left alone
     for (int sb = 0; sb < nsb; ++sb) {
         const int s0 = sb * 16;
@@ -798,7 +801,11 @@ __device__ __forceinline__ void factor_invert(double* S, double* V, double* dinv
                         continue;
                     }
                     double d = read_lane(a[j], s0 + j);
-                    if (!(d > floor_v)) { d = floor_v; ++nbad; }
+                    if (!(d > floor_v)) {
+                        d = floor_v;
+                        a[j] = 0.0;
+                        dropped |= 1ull << (s0 + j);
+                    }
                     const double inv = inv_sqrt(d);      // (d is at least 1e-300)
                     if (lane == s0 + j) { a[j] = d; mine = inv; }
                     a[j] *= inv;
@@ -828,7 +835,10 @@ __device__ __forceinline__ void factor_invert(double* S, double* V, double* dinv
         }
         __syncthreads();
     }
-    if (tid == 0 && nbad) atomicAdd(bad, nbad);
+    if (tid == 0) {
+        *marks = dropped;
+        if (dropped) atomicAdd(bad, __popcll(dropped));
+    }
     // inverse: diagonal 16 x 16 blocks, a wavefront each, lane = column ...
     if (lane < 16 && wave < nsb) {
         const double* L = S + 16 * wave * (CP + 1);
@@ -863,8 +873,9 @@ __device__ __forceinline__ void factor_invert(double* S, double* V, double* dinv
     }
 }
 
-// Linv: p rows of 64, the inverse of diagonal block k in rows 64 k ..  k = -1: only the first diagonal block.
-__global__ __launch_bounds__(256) void chol_step_kernel(double* G, double* X, double* Linv, int p, int k,
+// Linv: p rows of 64, the inverse of diagonal block k in rows 64 k ..; marks[k]: its clamped pivots.  k = -1: only the first
+// diagonal block.
+__global__ __launch_bounds__(256) void chol_step_kernel(double* G, double* X, double* Linv, unsigned long long* marks, int p, int k,
                                                         const double* __restrict__ floor_in, int* bad) {
     __shared__ double A[NB * CP], Z[NB * CP], D[NB * CP], dinv[NB];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -909,6 +920,15 @@ __global__ __launch_bounds__(256) void chol_step_kernel(double* G, double* X, do
         f64x4 l[4];
         block_nt<true>(A, D, wave, lane, l);          // L_ik
         if (!square) block_nt<true>(Z, D, wave, lane, u);   // L_jk, or X_kj transposed
+        const unsigned long long dropped = marks[k];
+        if (dropped) {
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+                if (dropped >> (16 * t + (lane & 15)) & 1) {
+                    l[t] = (f64x4){0.0, 0.0, 0.0, 0.0};
+                    if (!square && in_G) u[t] = (f64x4){0.0, 0.0, 0.0, 0.0};
+                }
+        }
         __syncthreads();
         block_put(A, wave, lane, l);
         if (!square) block_put(Z, wave, lane, u);
@@ -928,8 +948,8 @@ __global__ __launch_bounds__(256) void chol_step_kernel(double* G, double* X, do
     }
     __syncthreads();
     const int k1 = k + 1, nb = min(NB, p - k1 * NB);
-    if (nb == NB) factor_invert<true>(A, D, dinv, nb, *floor_in, bad, tid);
-    else          factor_invert<false>(A, D, dinv, nb, *floor_in, bad, tid);
+    if (nb == NB) factor_invert<true>(A, D, dinv, nb, *floor_in, bad, marks + k1, tid);
+    else          factor_invert<false>(A, D, dinv, nb, *floor_in, bad, marks + k1, tid);
     for (int idx = tid; idx < nb * NB; idx += 256) Linv[(long)k1 * NB * NB + idx] = D[(idx >> 6) * CP + (idx & 63)];
 }
 
@@ -1142,13 +1162,14 @@ hipError_t launch_jacobi(double* A, double* evals, double* work, int* info, int 
 
 hipError_t launch_chol_inverse(double* G, double* X, double* tmp, int p, int* bad, hipStream_t s) {
     double* floor_v = tmp;                 // one double
-    double* Linv = tmp + 8;                // p x 64
+    auto* marks = reinterpret_cast<unsigned long long*>(tmp + 1);      // a word per block column
+    double* Linv = tmp + CHOL_HEAD;        // p x 64
     max_diag_kernel<<<1, 1024, 0, s>>>(G, p, floor_v);
     hipError_t e = hipGetLastError();
     const int nblk = (p + NB - 1) / NB;
     for (int k = -1; k < nblk - 1 && e == hipSuccess; ++k) {
         const int tiles = k < 0 ? 1 : nblk * (nblk + 1) / 2 - (k + 1) * (k + 2) / 2;
-        chol_step_kernel<<<tiles, 256, 0, s>>>(G, X, Linv, p, k, floor_v, bad);
+        chol_step_kernel<<<tiles, 256, 0, s>>>(G, X, Linv, marks, p, k, floor_v, bad);
         e = hipGetLastError();
     }
     if (e != hipSuccess) return e;

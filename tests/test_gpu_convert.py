@@ -436,6 +436,42 @@ def test_top_eig_reports_a_start_block_that_lacks_rank(cv):
     assert np.isfinite(host(evals)).all() and np.isfinite(host(R)).all()
 
 
+@pytest.mark.parametrize("m,p,rank,iters", [(500, 200, 150, 5), (300, 64, 40, 5), (300, 200, 100, 5), (480, 96, 50, 20), (1000, 384, 300, 20),
+                                            (200, 64, 20, 10), (100, 16, 3, 5)])
+@pytest.mark.parametrize("seed", [0, 1, 2])
+def test_top_eig_of_a_matrix_of_lower_rank_than_the_block(cv, m, p, rank, iters, seed):
+    """Fewer tokens than block columns: the pivots that are left are rounding and are counted; the vectors that the matrix
+    has come out as they do without them."""
+    r = rng(1000 * seed + p)
+    C = r.standard_normal((rank, m)) * np.arange(1, m + 1) ** -0.7
+    S = C.T @ C / rank
+    k = min(rank, p // 2)
+    evals, R, info = (host(x) for x in cv.top_eig(dev(S), dev(r.standard_normal((m, p))), k, iters=iters))
+    assert info[0] > 0 and info[1] >= 1
+    assert np.isfinite(evals).all() and np.isfinite(R).all()
+    norm = np.linalg.norm(S)
+    assert np.abs(evals[:k] - np.linalg.eigvalsh(S)[::-1][:k]).max() < 1e-12 * norm
+    assert np.linalg.norm(S @ R - R * evals[:k]) < 1e-11 * norm
+    assert np.abs(R.T @ R - np.eye(k)).max() < 1e-9
+
+
+def test_convert_layer_on_fewer_tokens_than_block_columns(cv):
+    """50 tokens, a block of 96: the layer converted reproduces the value map on those tokens."""
+    g, h, d, M, keep, D, n, r_kv, p = 4, 8, 64, 2, 1, 256, 50, 64, 96
+    for seed in range(4):
+        r = rng(seed)
+        X = r.standard_normal((n, D)) * np.arange(1, D + 1) ** -0.7
+        W_K, W_V = r.standard_normal((g * d, D)) / 16, r.standard_normal((g * d, D)) / 16
+        out = cv.convert_layer(dev(X), dev(W_K), dev(W_V), dev(r.standard_normal((2 * g * d - keep * (d // M), p))), g, h, d, M, r_kv,
+                               iters=20, keep=keep)
+        got = {k: host(v) for k, v in out.items()}
+        assert all(np.isfinite(v).all() for v in got.values()) and got["info"][-2] > 0 and got["info"][-1] >= 1
+        V = X @ W_V.T
+        for i in range(h):
+            want = V[:, (i * g // h) * d:(i * g // h + 1) * d]
+            assert np.abs(X @ got["W_DKV"].T @ got["W_UV"][i] - want).max() < 1e-9 * np.abs(V).max()
+
+
 def test_sym_eig_reports_a_sweep_limit_that_is_too_low(cv):
     """One sweep does not diagonalise a random matrix: info = -1, the output is still an orthogonal matrix."""
     for m in (24, 200):                                 # single-workgroup path and chip-wide path
