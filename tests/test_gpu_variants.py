@@ -282,6 +282,17 @@ def test_prefill_materialised_rows(mla, T, lens, H, d_c, drop):
     assert lse_err(widen_gpu(lse), ref_lse) <= 2e-2
 
 
+@pytest.mark.parametrize("d_c", [256, 512])
+@pytest.mark.parametrize("lens", [[(37 * i) % 130 for i in range(200)], [0] * 70 + [65, 0, 128] + [0] * 64 + [1], [1] * 64 + [64] * 64, [0] * 130])
+def test_prefill_of_many_sequences(mla, lens, d_c):
+    """The sequences of a call in groups of 64, one per lane: whole groups and a part of one, empty sequences at their
+    ends, groups without a row."""
+    from test_gpu_parity import check_prefill
+    w = synth.make_workload("prefill", B=len(lens), H=2, d_head=128, d_c=d_c, d_rope=64, seq_lens=lens, io_dtype="bf16",
+                            cache_dtype="bf16", free_frac=0.1, seed=132)
+    check_prefill(mla, w, 1)
+
+
 @pytest.mark.parametrize("T,L,late", [(200, 210, 150), (200, 225, 153), (129, 129, 128), (300, 331, 169), (256, 260, 132), (140, 191, 180)])
 def test_prefill_later_tokens_stay_out_whatever_they_hold(mla, T, L, late):
     """A token behind every query of a group of 128, in the group's last tile of 32 (and in later ones), whose latent
