@@ -1,8 +1,8 @@
 // Prefill in the "MHA paradigm" (Sec. 3.3, first of the two attention equations): keys and values
 // are materialised per head from the cached latent rows,
 //     k_{j,h} = [W^{UK}_h c_j ; k^R_j],        v_{j,h} = W^{UV}_h c_j,
-// and the prompt's tokens attend causally to them.  This file holds the two kernels that build
-// the materialised keys and values; the attention itself runs on prefill_attention.hip's kernel, for which
+// and the prompt's tokens attend causally to them.  This file holds the kernels that build
+// the materialised keys and values (one with a head's weights in LDS, one that streams them, and the one that lays them out for it); the attention itself runs on prefill_attention.hip's kernel, for which
 // one (sequence, head) pair is a sequence of its own, and whose page layout (64 keys of 192 values, then
 // the values transposed, both in the order its reads want) is described there.
 //
@@ -40,7 +40,7 @@ template <int D_C>
 __global__ __launch_bounds__(PM_WAVES<D_C> * 64, PM_WAVES<D_C> / 4) void prefill_materialise_kernel(const uint16_t* kv, const int32_t* page_table,
                                                                                const int32_t* seq_lens, const uint16_t* W_UK, const uint16_t* W_UV,
                                                                                uint16_t* pool2, int32_t* table2, int32_t* lens2,
-                                                                               int B, int heads, int num_pages, int max_pages)
+                                                                               int B, int heads, int num_pages, int max_pages, bool by_page)
 {
     constexpr int ROW = D_C + 64;
     constexpr int NKS = D_C / 32;
@@ -57,7 +57,8 @@ __global__ __launch_bounds__(PM_WAVES<D_C> * 64, PM_WAVES<D_C> / 4) void prefill
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n = lane & 15, g = lane >> 4;
-    const int h = blockIdx.x / PARTS, part = blockIdx.x % PARTS;
+    const int kind = by_page ? blockIdx.y : blockIdx.x, share = by_page ? blockIdx.x : blockIdx.y, shares = by_page ? gridDim.x : gridDim.y;
+    const int h = kind / PARTS, part = kind % PARTS;
     const bool keys = PARTS == 1 || part == 0, values = PARTS == 1 || part == 1;
     LDS_AS unsigned char* w_keys = (LDS_AS unsigned char*)wbuf;
     LDS_AS unsigned char* w_values = w_keys + (2 / PARTS - 1) * HALF_B;
@@ -91,7 +92,7 @@ __global__ __launch_bounds__(PM_WAVES<D_C> * 64, PM_WAVES<D_C> / 4) void prefill
                 wv[i] = *reinterpret_cast<const u32x4*>(W_UV + (size_t)h * PF_DH * D_C + (i * THREADS + tid) * 8);
         }
         look_at(0);
-        if (blockIdx.y == 0 && keys)
+        if (share == 0 && keys)
             for (int b = tid; b < B; b += THREADS) lens2[(size_t)b * heads + h] = max(0, min(seq_lens[b], max_pages * 64));
         if (keys) {
 #pragma unroll
@@ -134,8 +135,8 @@ __global__ __launch_bounds__(PM_WAVES<D_C> * 64, PM_WAVES<D_C> / 4) void prefill
 
     // ---- this wavefront's share of the half pages of all sequences laid end to end: pages are dealt to the workgroups of the
     // head first, so that few of them keep as many CUs busy as there are
-    const int stride = gridDim.y * WAVES;
-    for (int u = 2 * (blockIdx.y + gridDim.y * (wave >> 1)) + (wave & 1);; u += stride) {
+    const int stride = shares * WAVES;
+    for (int u = 2 * (share + shares * (wave >> 1)) + (wave & 1);; u += stride) {
         for (int all; u >= before + (all = __builtin_amdgcn_readlane(upto, 63)); look_at(group)) {
             before += all;
             group += 64;
@@ -432,16 +433,23 @@ hipError_t launch_prefill_materialise(const void* kv, const int32_t* page_table,
 {
     const uint16_t *rows = static_cast<const uint16_t*>(kv), *uk = static_cast<const uint16_t*>(W_UK), *uv = static_cast<const uint16_t*>(W_UV);
     uint16_t* pool = static_cast<uint16_t*>(pool2);
-    // Weights in LDS (no launch of their own, no barriers): while there are few pages x heads, and, d_c = 256, for short query
-    // runs over very many.  Whole calls, in a row, this form / streamed weights, us:
-    //   16 heads d_c = 256, 8213 tokens (2064 pages x heads) 366 / 383; 4 x 1024, 28 heads (1792) 102 / 108; 3 x 2087, d_c = 512
-    //   (1584) 152 / 160; 32 heads, 4000 tokens, d_c = 512 (2016) 272 / 277; 4 x 1400, 28 heads (2464) 146 / 155 and 169 / 182.
-    //   Beyond: 4 x 1765, 28 heads (3136) 219 / 205; 2 x 9260 (8120) 1639 / 1518: the kernel itself is no slower there (107 and
-    //   111 + 9), but the attention after it is (1.50 and 1.38 ms; the first calls of a run are equal: the clock that the chip holds).
-    //   500 queries on 8 x 6000 (21000) 404 / 422; 512 on 4 x 8000 (14000) 487 / 505; 400 on 16000 (7000) 507 / 486; 1000 on 8000 (3500) 280 / 267;
-    //   128 on 8 x 4000, d_c = 512 (16128) 515 / 498: every latent row is read twice at that width.
-    const long long work = (long long)B * max_pages * heads;
-    const bool resident = work <= 2560 || (d_c == 256 && q_len <= 512 && work >= 8192);
+    // Weights in LDS (no launch of their own, no barriers) or streamed.  Whole calls, sustained, in LDS / streamed, us (pages x heads in
+    // brackets; 28 heads unless said):
+    // - few pages x heads, whose launches and weights count: d_c = 256, 1000 tokens (448) 45 / 51; 4 x 1000, 512 queries (1792)
+    //   70 / 78; 4 x 1400, 512 (2464) 88 / 103; 8000, 512 (3500) 249 / 252; 2 x 4000, 512 (3528) 160 / 155.  d_c = 512, 1000 tokens
+    //   51 / 56; 3 x 2087, 16 heads (1584) 102 / 108; 4096, 512 (1792) 153 / 150; 8 x 500, 64 (1792) 70 / 69; 4 x 1400, 512 122 / 130;
+    //   4 x 2000, 512 (3584) 174 / 166.
+    // - but the attention behind it is the slower for it the longer it takes itself (its reads of the pool meet other XCDs' writes;
+    //   the first calls of a run are equal): d_c = 256, prompts of 2000 (896) 90 / 92, 3000 (1316) 156 / 154, 4000, 32 heads (2016)
+    //   236 / 232, 5700 (2520) 402 / 366.
+    // - d_c = 256, short query runs of enough (sequence, head) pairs for a workgroup of the attention on most CUs: 8 x 1000, 64
+    //   queries 79 / 92, 512 136 / 143, 700 166 / 164; 8 x 2500, 64 215 / 225, 512 322 / 321; 8 x 6000, 512 722 / 756, 1024
+    //   1072 / 1086, 2048 1694 / 1669; 16 x 2000, 512 490 / 505, 1024 710 / 703; 32 x 300, 128 109 / 126; 1000 x 64, 32 775 / 887.
+    //   Fewer pairs: 7 x 4000, 64 295 / 304, 512 464 / 447; 4 x 5000, 64 248 / 241, 512 314 / 305; 2 x 16000, 64 574 / 590, 512
+    //   618 / 597; 20000, 64 605 / 609, 512 628 / 606.  d_c = 512 reads every latent row twice: 8 x 2500, 64 288 / 282; 16 x 2000,
+    //   512 612 / 605; 8 x 6000, 512 891 / 906.
+    const long long pages = (long long)B * max_pages, work = pages * heads;
+    const bool resident = (work <= 2560 && (d_c == 512 || q_len <= 3072)) || (d_c == 256 && q_len <= 512 && (long long)B * heads >= 224);
     if (!resident) {
         uint16_t* cat = static_cast<uint16_t*>(Wcat);
         prefill_weights_kernel<<<dim3(d_c / 64, 4, heads), 256, 0, s>>>(uk, uv, cat, d_c);
@@ -452,18 +460,23 @@ hipError_t launch_prefill_materialise(const void* kv, const int32_t* page_table,
         else            prefill_stream_kernel<256><<<grid, 256, 0, s>>>(rows, page_table, seq_lens, cat, pool, table2, lens2, heads, num_pages, max_pages);
         return hipGetLastError();
     }
-    // One workgroup per CU (its weights fill the LDS), the same number for every head, in one round where that keeps nine tenths of
-    // the CUs busy, else in the first number of rounds that does; never more than there can be pages for.
-    const int kinds = heads * (d_c / 256);
+    // One workgroup per CU (its weights fill the LDS), the same number for every head: of one to eight rounds of them the number
+    // that takes the least time, a round's weights counted as 0.3 of the page that a pair of wavefronts takes next (1000
+    // tokens, 28 heads, d_c = 512: four per kind 51 us, two rounds of nine 56).
+    const int kinds = heads * (d_c / 256), pairs = (d_c == 512 ? PM_WAVES<512> : PM_WAVES<256>) / 2;
     int per = 1;
+    double least = 1e30;
     for (int rounds = 1; rounds <= 8; ++rounds) {
-        per = std::max(1, 256 * rounds / kinds);
-        if (kinds * per >= 230 * rounds || kinds >= 256 * rounds) break;
+        const int n = (int)std::min<long long>(std::max(1, 256 * rounds / kinds), pages);
+        const double time = (double)(((long long)kinds * n + 255) / 256) * (0.3 + (double)((pages + (long long)n * pairs - 1) / ((long long)n * pairs)));
+        if (time < least) { least = time; per = n; }
     }
-    per = (int)std::min<long long>(per, (long long)B * max_pages);
-    const dim3 grid(kinds, per);
-    if (d_c == 512) prefill_materialise_kernel<512><<<grid, PM_WAVES<512> * 64, 0, s>>>(rows, page_table, seq_lens, uk, uv, pool, table2, lens2, B, heads, num_pages, max_pages);
-    else            prefill_materialise_kernel<256><<<grid, PM_WAVES<256> * 64, 0, s>>>(rows, page_table, seq_lens, uk, uv, pool, table2, lens2, B, heads, num_pages, max_pages);
+    // A multiple of eight heads: the shares vary first, so that a page's latent rows are read on few XCDs (8 heads, one to an XCD
+    // otherwise, d_c = 256, 32 x 1000 tokens, 64 queries 94 -> 81 us; but 28 heads 84 -> 91, 4000 x 4 200 -> 201)
+    const bool by_page = kinds % 8 == 0 && d_c == 256;
+    const dim3 grid = by_page ? dim3(per, kinds) : dim3(kinds, per);
+    if (d_c == 512) prefill_materialise_kernel<512><<<grid, PM_WAVES<512> * 64, 0, s>>>(rows, page_table, seq_lens, uk, uv, pool, table2, lens2, B, heads, num_pages, max_pages, by_page);
+    else            prefill_materialise_kernel<256><<<grid, PM_WAVES<256> * 64, 0, s>>>(rows, page_table, seq_lens, uk, uv, pool, table2, lens2, B, heads, num_pages, max_pages, by_page);
     return hipGetLastError();
 }
 

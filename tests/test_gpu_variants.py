@@ -253,16 +253,27 @@ def test_prefill_skips_bad_pages(mla):
         assert max_abs_rel(widen_gpu(got)[b, t], ref) <= TOL["bf16"]
 
 
-@pytest.mark.parametrize("T,lens,H,d_c,drop", [
-    (2, [31, 32, 33, 63, 64, 65, 1, 0], 3, 256, ()), (2, [31, 32, 33, 63, 64, 65, 1, 0], 3, 512, ()),   # half pages, whole, one row
-    (1, [(131 * i) % 190 for i in range(40)], 28, 256, ((7, 1), (39, 0))),     # more half pages than wavefronts
-    (1, [(131 * i) % 190 for i in range(32)], 28, 512, ((7, 1), (31, 0))),     # 96 pages: weights in LDS
-    (3, [1400, 33, 0, 129, 64], 28, 512, ((0, 0), (0, 20))), (2, [1400, 33, 0, 129, 64], 28, 256, ((0, 0), (0, 20))),   # streamed
-    (1, [1251, 31, 63, 128], 32, 512, ()), (1, [1281, 31, 63, 128], 32, 256, ()),   # 2560 pages x heads: not yet; 2688
-    (1, [(37 * i) % 65 for i in range(256)], 32, 256, ()), (1, [(37 * i) % 65 for i in range(255)], 32, 256, ())])   # 8192: weights in LDS again; 8160
-def test_prefill_materialised_rows(mla, T, lens, H, d_c, drop):
+def weights_in_lds(B, T, lens, H, d_c):
+    """The launcher's choice between the two kernels that write the keys and values."""
+    pages = B * max(1, max((n + 63) // 64 for n in lens))
+    return (pages * H <= 2560 and (d_c == 512 or T <= 3072)) or (d_c == 256 and T <= 512 and B * H >= 224)
+
+
+@pytest.mark.parametrize("T,lens,H,d_c,drop,in_lds", [
+    (2, [31, 32, 33, 63, 64, 65, 1, 0], 3, 256, (), True), (2, [31, 32, 33, 63, 64, 65, 1, 0], 3, 512, (), True),   # half pages, whole, one row
+    (1, [(131 * i) % 190 for i in range(40)], 28, 256, ((7, 1), (39, 0), (2, 0)), True),     # more pages than pairs of wavefronts
+    (1, [(131 * i) % 190 for i in range(30)], 28, 512, ((7, 1), (29, 0), (2, 0)), True),     # 2520 pages x heads
+    (2, [700, 129, 0, 64, 250], 3, 256, ((0, 0), (0, 9), (4, 2)), True), (2, [700, 129, 0, 64, 250], 3, 512, ((0, 0), (0, 9), (4, 2)), True),
+    (3, [1400, 33, 0, 129, 64], 28, 512, ((0, 0), (0, 20)), False), (2, [1400, 33, 0, 129, 64], 28, 256, ((0, 0), (0, 20)), False),
+    (1, [1251, 31, 63, 128], 32, 512, (), True), (1, [1281, 31, 63, 128], 32, 256, (), False),     # 2560 pages x heads, 2688
+    (1, [730, 31, 63, 128, 0, 1, 200, 333], 28, 256, ((7, 5),), True),                       # 224 pairs of sequence and head
+    (1, [850, 31, 63, 128, 0, 1, 200], 28, 256, ((0, 13),), False),                          # 196
+    (1, [(37 * i) % 65 for i in range(256)], 32, 256, (), True), (1, [(37 * i) % 65 for i in range(256)], 32, 512, (), False),
+    (3072, [3072], 1, 256, (), True), (3073, [3073], 1, 256, (), False)])
+def test_prefill_materialised_rows(mla, T, lens, H, d_c, drop, in_lds):
     """Keys and values of both kernels that write them: sequences that end inside, at and after a half page, empty
     ones, pages outside the pool; the tokens of such a page count as absent."""
+    assert weights_in_lds(len(lens), T, lens, H, d_c) == in_lds
     import torch
     w = synth.make_workload("prefill", B=len(lens), H=H, d_head=128, d_c=d_c, d_rope=64, seq_lens=lens, io_dtype="bf16",
                             cache_dtype="bf16", free_frac=0.1, seed=131)
