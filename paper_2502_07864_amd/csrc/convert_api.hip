@@ -282,10 +282,13 @@ int mla_convert_layer(const double* X, const double* W_K, const double* W_V, con
     MLA_TRY(launch_balance(w.C, mj, w.C + a, mj, alpha, w.C, n, a, gd, s));
     const TopWs top = top_ws(w.top, mj, p);
     // The power iteration needs the moment S = C^T C / n only in products with a block, 2 m^2 p operations each; by the factor they
-    // take 4 n m p and S itself (n m^2) is not formed.  Whichever is less: n a little above m / 2 is where they meet (4096 tokens,
-    // m = 8128, block 768, 20 iterations: 75.0 ms a layer by S, 69.3 by the factor).
+    // take 4 n m p and S itself (n m^2) is not formed, but a step has one product more, which costs about 12 us (8e8 operations)
+    // whatever its size.  Whichever is less; ms a layer by the factor / by S (20 iterations unless said): m = 8128, p = 768, 4096
+    // tokens 69.3 / 75.0; m = 4032, p = 560: 1024 19.7 / 22.9, 2048 23.4 / 23.9, 2300 25.8 / 25.5; m = 1984, p = 320: 512 9.13 / 9.31,
+    // 768 9.46 / 9.44, 1100 9.90 / 9.61; 4 iterations 768 6.89 / 6.97, 1100 7.12 / 7.14, 1400 7.27 / 7.26; m = 480, p = 80: 64 2.92 / 2.92,
+    // 256 3.12 / 2.93.
     Symmetric moment{nullptr, w.C, n, w.S};
-    const double by_factor = (4.0 * iters + 2.0) * n * mj * p + 1.0 * n * p * p;
+    const double by_factor = (4.0 * iters + 2.0) * n * mj * p + 1.0 * n * p * p + 8e8 * iters;
     const double by_moment = 1.0 * n * mj * mj + (2.0 * iters + 2.0) * mj * mj * p + 2.0 * mj * p * p;
     if (by_moment <= by_factor || (size_t)n * p > s_doubles) {
         GemmF64 ctc = gemm_tn(w.C, mj, w.C, mj, w.S, mj, mj, mj, n, 1.0 / (double)n);

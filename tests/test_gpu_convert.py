@@ -308,6 +308,32 @@ def test_gpu_converted_layer_decodes_like_the_oracles_converted_layer(cv, M, kee
     assert np.abs(got - want).max() < 2e-5 * max(1.0, np.abs(want).max())
 
 
+def iterates_by_the_factor(n, m, p, iters):
+    """The library's choice between C^T (C Q) / n and S Q in the power iteration: operations, 8e8 for a step's extra product."""
+    by_factor = (4 * iters + 2) * n * m * p + n * p * p + 8e8 * iters
+    return by_factor < n * m * m + (2 * iters + 2) * m * m * p + 2 * m * p * p and n * p <= m * m
+
+
+@pytest.mark.parametrize("g,d,n,p,iters,by_factor", [(8, 128, 300, 128, 20, True), (8, 128, 330, 128, 20, False), (8, 128, 129, 127, 4, True),
+                                                     (4, 64, 100, 80, 20, False), (8, 64, 40, 512, 20, True)])
+def test_convert_layer_iterates_as_top_eig_does(cv, g, d, n, p, iters, by_factor):
+    """Both forms of the iteration, on both sides of the rule, against top_eig of the moment itself from the same block: the
+    values to rounding, the spaces as far as blocks of condition 1e6 to 1e7 leave them (1.6e-5, four times that)."""
+    M, keep, D, r_kv = 2, 1, 256, min(64, n // 2)
+    d_rope = co.rope_width(d, M, keep)
+    m = 2 * g * d - d_rope
+    assert iterates_by_the_factor(n, m, p, iters) == by_factor
+    X, W_K, W_V, Q0 = chain_case(g, g, d, D, n, M, keep, r_kv, p, seed=n)
+    out = cv.convert_layer(dev(X), dev(W_K), dev(W_V), dev(Q0), g, g, d, M, r_kv, iters=iters, keep=keep)
+    W_rot = cv.rotate_rows(dev(W_K), out["U"], g, d, M, keep)
+    S, _ = cv.joint_moment(cv.project(dev(X), W_rot[d_rope:].contiguous()), cv.project(dev(X), dev(W_V)), out["alpha"])
+    evals, R, info = (host(x) for x in cv.top_eig(S, dev(Q0), r_kv, iters))
+    got = host(out["evals_joint"])
+    assert host(out["info"])[-1] >= 1 and info[1] >= 1
+    assert np.abs(got[:r_kv] - evals[:r_kv]).max() < 1e-10 * evals[0]
+    assert projector_gap(host(out["R_KV"]), R) < 6e-5
+
+
 # ------------------------------------------------------------------ the benchmark shape, by properties
 
 def test_convert_layer_at_the_llama2_7b_layer_shape_by_properties(cv):
