@@ -495,8 +495,8 @@ def test_fp64_product_edges(mla, n, m, D):
 @pytest.mark.parametrize("H,K,N", [(1, 32, 16), (5, 96, 48), (8, 128, 512), (28, 160, 128), (32, 256, 128), (3, 288, 32), (64, 512, 128)])
 @pytest.mark.parametrize("B", [1, 15, 16, 17, 32, 33, 64, 65])
 def test_bf16_projection_row_groups_and_depths(mla, B, H, K, N):
-    """Every split of the wavefronts (one, two and more 16-row groups; column tiles; k-steps) at every depth class, against
-    fp32: one bf16 rounding of the result and sums of K products of bf16 values in another order."""
+    """One, two and more 16-row groups, one workgroup of them and two, against fp32: one bf16 rounding of the result and sums of
+    K products of bf16 values in another order."""
     import torch
     gen = torch.Generator(device="cuda").manual_seed(B * 1000 + K)
     X = torch.randn(B, H, K, device="cuda", generator=gen).bfloat16()
@@ -504,6 +504,29 @@ def test_bf16_projection_row_groups_and_depths(mla, B, H, K, N):
     got = mla.absorb_q(X, W).float()
     ref = torch.matmul(X.float().transpose(0, 1).contiguous(), W.float()).transpose(0, 1)
     assert (got - ref).abs().max().item() <= (2.0 ** -8 + K * 2.0 ** -24) * ref.abs().max().item()
+
+
+def bf16_column_tile(B, H, K, N):
+    """The launcher's column tile: the widest that divides N, whose slab of W fits LDS and that gives a workgroup per CU, else the
+    narrowest."""
+    fits = [t for t in (64, 32, 16) if N % t == 0 and K * (2 * t + 16) <= 40 * 1024]
+    return next((t for t in fits if t > 16 and H * (N // t) * ((B + 63) // 64) >= 256), fits[-1])
+
+
+@pytest.mark.parametrize("tile,H,N,K", [(*shape, K) for shape in ((16, 2, 48), (32, 86, 96), (64, 64, 256))
+                                        for K in range(32, (257 if shape[0] == 64 else 513), 32)])
+def test_bf16_projection_column_tiles_at_every_depth(mla, tile, H, N, K):
+    """16, 32 and 64 columns at both depths of every class, every split of the wavefronts over up to 16, 32 and more rows, against
+    fp32 as above."""
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(tile + K)
+    X = torch.randn(65, H, K, device="cuda", generator=gen).bfloat16()
+    W = (torch.randn(H, K, N, device="cuda", generator=gen) * K ** -0.5).bfloat16()
+    ref = torch.matmul(X.float().transpose(0, 1).contiguous(), W.float()).transpose(0, 1)
+    for B in (1, 16, 17, 32, 33, 64, 65):
+        assert bf16_column_tile(B, H, K, N) == tile
+        err = (mla.absorb_q(X[:B].contiguous(), W).float() - ref[:B]).abs().max().item()
+        assert err <= (2.0 ** -8 + K * 2.0 ** -24) * ref[:B].abs().max().item()
 
 
 @pytest.mark.parametrize("H,K,N", [(28, 128, 256), (28, 256, 128), (32, 512, 128), (32, 128, 256), (64, 352, 128), (32, 128, 512)])
