@@ -481,6 +481,9 @@ def prefill_main(args):
     attn_flop = float(visible) * H * (2 * (w.d_head + w.d_rope) + 2 * w.d_head)
     mat_flop = float(lens.sum()) * H * 2 * w.d_c * 2 * w.d_head
     tflops = (attn_flop + mat_flop) / (ms * 1e-3) / 1e12
+    # the library's choice between the two kernels that write the keys and values
+    in_lds = (B * w.max_pages_per_seq * H <= 2560 and (w.d_c == 512 or T <= 3072)) or (w.d_c == 256 and T <= 512 and B * H >= 224)
+    materialise = f"prefill_{'materialise' if in_lds else 'stream'}_kernel<{w.d_c}>"
     rec = {"metric": f"MLA prefill ms (MHA paradigm: materialise + causal attention), {args.workload} cache, "
                      f"{T} newest tokens per sequence, 1 GPU",
            "value": round(ms, 3), "unit": "ms/step", "n_gpus": 1, "steps": steps, "warmup": warmup,
@@ -489,7 +492,7 @@ def prefill_main(args):
            "config": {"workload": WORKLOADS[args.workload], "batch": B, "q_len": T, "heads": H,
                       "context_max": int(w.seq_lens.max())},
            "tokens_per_s": round(B * T / (ms * 1e-3), 1),
-           "roofline": {"bound": "mfma", "kernel": "prefill_attention_kernel<3, 2> + prefill_stream_kernel<512>",
+           "roofline": {"bound": "mfma", "kernel": f"prefill_attention_kernel<3, 2> + {materialise}",
                         "achieved": round(tflops, 1), "peak": 2500.0, "unit": "TFLOP/s",
                         "frac": round(tflops / 2500.0, 4), "traffic": None,
                         "algorithmic_flop_per_step": attn_flop + mat_flop,
@@ -584,11 +587,12 @@ def convert_main(args):
     launch_ms = e0.elapsed_time(e1) / reps
     flop = 2.0 * mj * mj * p
     tflops = flop / (launch_ms * 1e-3) / 1e12
-    # algorithmic flop of the chain: activations, moments, iterations (S Q, Gram, Q = Y L^-T), projections
+    # flop of the chain: activations (two products and a rotation), the power iteration by the factor of the moment or by the moment
+    # (the library takes whichever is less), Gram and Q = Y L^-T, projections
     gd = g * d
-    chain_flop = (2.0 * n * D * gd + 2.0 * n * D * (gd - d_rope) + 2.0 * n * D * gd + 2.0 * mj * mj * n
-                  + (iters + 1) * flop + (iters + 4) * 2 * (2.0 * mj * p * p)
-                  + 2.0 * r_kv * D * mj + 2.0 * h * d * r_kv * (gd - d_rope))
+    iteration = min((4.0 * iters + 2.0) * n * mj * p + 2.0 * n * p * p, 2.0 * mj * mj * n + (iters + 1) * flop + 2.0 * mj * p * p)
+    chain_flop = (2 * 2.0 * n * D * gd + 2.0 * n * gd * M * g + iteration + (iters + 4) * 2 * (2.0 * mj * p * p)
+                  + 2.0 * r_kv * D * mj + 2.0 * gd * r_kv * M * g)
     rec = {"metric": "GQA->MLA conversion of one LLaMA-2-7B-shaped layer, ms (fp64), 1 GPU",
            "value": round(ms, 2), "unit": "ms/layer", "n_gpus": 1, "steps": steps, "warmup": warmup,
            "ms_per_step": round(ms, 4), "higher_is_better": False, "scaling": "weak", "vs_baseline": None,
