@@ -125,8 +125,8 @@ size_t mla_conv_top_eig_workspace_bytes(int m, int p);
  * iteration above spends its time in; with Q = R it gives the residual S R - R diag(evals)).
  *   S [m, m], Q [m, p], Y [m, p] (distinct from Q).
  *   workspace: optional scratch of mla_conv_apply_workspace_bytes(m, p) bytes (NULL, 0: none).  With
- *   it, a product whose output tiles alone would leave CUs idle in the last round is computed in
- *   slices of the K range that are summed in a fixed order, as inside mla_conv_top_eig. */
+ *   it, a product whose output tiles alone would leave CUs idle is cut into equal shares of all tiles'
+ *   K steps, and the parts of a tile are summed in a fixed order, as inside mla_conv_top_eig. */
 size_t mla_conv_apply_workspace_bytes(int m, int p);
 int mla_conv_apply(const double* S, const double* Q, double* Y, void* workspace, size_t workspace_bytes,
                    int m, int p, void* hip_stream);

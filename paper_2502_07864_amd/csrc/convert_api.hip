@@ -29,7 +29,7 @@ inline GemmF64 gemm_tn(const double* A, long lda, const double* B, long ldb, dou
     return GemmF64{A, 1, lda, B, ldb, 1, C, ldc, M, N, K, alpha, nullptr, 0};   // C = A^T B (A is K x M)
 }
 
-constexpr int GRAM_SLICES = 16;     // K slices of the p x p products of tall blocks
+constexpr int GRAM_ROOM = 16;       // p x p products of tall blocks: room for the parts of their tiles, in results
 struct TopWs { double *Y, *Q, *G, *X, *T, *Z, *tmp, *part; size_t part_doubles; size_t bytes; };
 TopWs top_ws(void* base, int m, int p) {
     TopWs w{};
@@ -43,7 +43,7 @@ TopWs top_ws(void* base, int m, int p) {
     w.T = take((size_t)p * p);
     w.Z = take(jacobi_work_bytes(1, p) / sizeof(double));
     w.tmp = take(chol_tmp_doubles(p));
-    w.part_doubles = std::max((size_t)GRAM_SLICES * p * p, (size_t)4 * m * p);
+    w.part_doubles = std::max((size_t)GRAM_ROOM * p * p, (size_t)4 * m * p);
     w.part = take(w.part_doubles);
     w.bytes = off;
     return w;

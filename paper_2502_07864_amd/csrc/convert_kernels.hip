@@ -525,8 +525,9 @@ __global__ __launch_bounds__(1024) void jacobi_kernel(double* A_all, double* eva
 // of order m is m/16 - 1 such steps of two launches and annihilates every pair of indices at least once; single
 // rotations spread over the chip took m - 1 launches that each rewrote A and V: order 768, 10 us a launch, 47 ms
 // for 6 sweeps (and 14 ms for the norms, by one workgroup, and for the launches behind convergence); this form
-// 47 us a step, 14 ms in all, 36 us of a step for the 31 dependent rotation steps of a pair.  A sweep starts with a norm pair of launches that raises `done` once the off-diagonal part is small; later launches
-// then return at once, so the host can enqueue the maximum number of sweeps without reading back.
+// 34 us a step, 11 ms in all, 23 us of a step for the pairs (31 dependent rotation steps) and 11 for the update.  A sweep
+// starts with a norm pair of launches that raises `done` once the off-diagonal part is small; later launches then return at
+// once, so the host can enqueue the maximum number of sweeps without reading back.
 struct WideState { double tot; int done, sweeps; };
 constexpr int JB = 16, JP = 2 * JB;                    // block, pair of blocks
 constexpr int JB_NORM_WGS = 64;
@@ -577,7 +578,8 @@ __device__ __forceinline__ int pair_index(int I, int J, int r) { return (r < JB 
 
 // A thread (k1, k2) owns a 2 x 2 block of a and two rows of z as in jacobi_step, but works out both of its rotations itself and
 // writes to the other buffer of a: one barrier a step and no exchange of angles (four wavefronts have the vector pipes for it).
-// A step 1.16 us as two phases with the angles between them, 1.0 with the blocks read beside the angles, now 0.37.
+// Launch of order 768 (24 pairs) over its 31 rotation steps: 1.16 us a step as two phases with the angles between them, 1.0 with
+// the blocks read beside the angles, now 0.74.
 __global__ __launch_bounds__(256) void jb_pair_kernel(double* A, double* __restrict__ Z, int m, int nbp, int step, const WideState* st) {
     constexpr int LD = JP + 1, HALF = JP / 2;
     __shared__ double a[2][JP * LD], z[JP * LD];

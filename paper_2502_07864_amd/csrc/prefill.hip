@@ -1,10 +1,10 @@
 // Prefill in the "MHA paradigm" (Sec. 3.3, first of the two attention equations): keys and values
 // are materialised per head from the cached latent rows,
 //     k_{j,h} = [W^{UK}_h c_j ; k^R_j],        v_{j,h} = W^{UV}_h c_j,
-// and the prompt's tokens attend causally to them.  This file holds the kernels that build
-// the materialised keys and values (one with a head's weights in LDS, one that streams them, and the one that lays them out for it); the attention itself runs on prefill_attention.hip's kernel, for which
-// one (sequence, head) pair is a sequence of its own, and whose page layout (64 keys of 192 values, then
-// the values transposed, both in the order its reads want) is described there.
+// and the prompt's tokens attend causally to them.  This file holds the kernels that build the materialised keys and
+// values (one with a head's weights in LDS, one that streams them, and the one that lays them out for it); the attention
+// itself runs on prefill_attention.hip's kernel, for which one (sequence, head) pair is a sequence of its own, and whose page
+// layout (64 keys of 192 values, then the values transposed, both in the order its reads want) is described there.
 //
 //   Y^T [256 x tokens] = [W^{UK}_h ; (W^{UV}_h)^T] [256 x d_c] . C^T [d_c x tokens]
 //
