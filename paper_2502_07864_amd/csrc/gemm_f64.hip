@@ -25,8 +25,8 @@
 // S Q 8128 x 8128 x 768 61 -> 65 to 67, 3968 x 768 57 -> 65, 1984 x 384 34 -> 49, 512 x 192 3.7 -> 6.3; C^T C of 4096 x
 // 8128 (half of it counted) 55 -> 61 to 64, 4096 x 1000 7 -> 23.  Narrow ones are bound by reading S: 8128 x 32 309 -> 168 us.
 // Tiles of 128 x 128 with 4 x 4 per wavefront need more than 256 registers (41).
-// Registers: 124 of X W^T leave four workgroups per CU, as the 128 that its odd pitches are held to do (2000 x 333 x 2000 65 ->
-// 53 us); the others have three (C^T C held to four: 4096 x 3000 685 -> 788 us).
+// Registers: 124 of X W^T leave four workgroups per CU, as the 128 that its odd pitches are held to do (three more wait in scratch
+// while the K loop runs; 2000 x 333 x 2000 65 -> 53 us); the others have three (C^T C held to four: 4096 x 3000 685 -> 788 us).
 #include "convert_internal.h"
 #include <algorithm>
 #include <type_traits>
