@@ -64,18 +64,23 @@ __global__ __launch_bounds__(PM_WAVES<D_C> * 64, PM_WAVES<D_C> / 4) void prefill
     LDS_AS unsigned char* w_values = w_keys + (2 / PARTS - 1) * HALF_B;
 
     // Sequences in groups of 64, one per lane: its length, and the half pages of the group up to its end.  (One after the other
-    // by scalar loads: 256 sequences of a page, one head, 50 us for the whole call, now 20.)
+    // by scalar loads: 256 sequences of a page, one head, 50 us for the whole call, now 20.)  The first group's lengths are asked for
+    // before the weights and added up while these are on their way.
     int len, upto;
-    auto look_at = [&](int from) {
-        const int b = from + lane;
-        len = b < B ? max(0, min(seq_lens[b], max_pages * 64)) : 0;
+    auto length_of = [&](int b) { return b < B ? seq_lens[b] : 0; };
+    auto add_up = [&](int length) {
+        len = max(0, min(length, max_pages * 64));
         upto = ((len + 63) >> 6) * 2;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const int v = __shfl_up(upto, o);
-            upto += lane >= o ? v : 0;
-        }
+        // running sum over the lanes: within rows of 16, then each row's total to the rows behind it
+        upto += __builtin_amdgcn_update_dpp(0, upto, 0x111, 0xf, 0xf, false);       // row_shr 1, 2, 4, 8
+        upto += __builtin_amdgcn_update_dpp(0, upto, 0x112, 0xf, 0xf, false);
+        upto += __builtin_amdgcn_update_dpp(0, upto, 0x114, 0xf, 0xf, false);
+        upto += __builtin_amdgcn_update_dpp(0, upto, 0x118, 0xf, 0xf, false);
+        upto += __builtin_amdgcn_update_dpp(0, upto, 0x142, 0xa, 0xf, false);       // row_bcast 15: rows 1 and 3
+        upto += __builtin_amdgcn_update_dpp(0, upto, 0x143, 0xc, 0xf, false);       // row_bcast 31: rows 2 and 3
     };
+    const int first_length = length_of(lane);
+    __builtin_amdgcn_sched_barrier(0);
     int group = 0, before = 0;                        // the group's first sequence, half pages before it
 
     // ---- the weights: all requested at once
@@ -91,7 +96,8 @@ __global__ __launch_bounds__(PM_WAVES<D_C> * 64, PM_WAVES<D_C> / 4) void prefill
             for (int i = 0; i < NLD; ++i)
                 wv[i] = *reinterpret_cast<const u32x4*>(W_UV + (size_t)h * PF_DH * D_C + (i * THREADS + tid) * 8);
         }
-        look_at(0);
+        __builtin_amdgcn_sched_barrier(0);
+        add_up(first_length);
         if (share == 0 && keys)
             for (int b = tid; b < B; b += THREADS) lens2[(size_t)b * heads + h] = max(0, min(seq_lens[b], max_pages * 64));
         if (keys) {
@@ -137,7 +143,7 @@ __global__ __launch_bounds__(PM_WAVES<D_C> * 64, PM_WAVES<D_C> / 4) void prefill
     // head first, so that few of them keep as many CUs busy as there are
     const int stride = shares * WAVES;
     for (int u = 2 * (share + shares * (wave >> 1)) + (wave & 1);; u += stride) {
-        for (int all; u >= before + (all = __builtin_amdgcn_readlane(upto, 63)); look_at(group)) {
+        for (int all; u >= before + (all = __builtin_amdgcn_readlane(upto, 63)); add_up(length_of(group + lane))) {
             before += all;
             group += 64;
             if (group >= B) return;
