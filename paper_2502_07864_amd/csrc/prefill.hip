@@ -477,9 +477,13 @@ hipError_t launch_prefill_materialise(const void* kv, const int32_t* page_table,
         const double time = (double)(((long long)kinds * n + 255) / 256) * (0.3 + (double)((pages + (long long)n * pairs - 1) / ((long long)n * pairs)));
         if (time < least) { least = time; per = n; }
     }
-    // A multiple of eight heads: the shares vary first, so that a page's latent rows are read on few XCDs (8 heads, one to an XCD
-    // otherwise, d_c = 256, 32 x 1000 tokens, 64 queries 94 -> 81 us; but 28 heads 84 -> 91, 4000 x 4 200 -> 201)
-    const bool by_page = kinds % 8 == 0 && d_c == 256;
+    // A multiple of eight heads, which would each stay on one XCD: the shares vary first where there are many pages, so that a page's
+    // latent rows are read on one XCD only; with few, reading the weights on all of them costs more.  us by head / by page, d_c = 256,
+    // 8 heads: 8 x 250 tokens (32 pages) 22.9 / 25.9, 10000 (157) 267 / 268, 28 x 800 (364) 68.7 / 58.3, 128 x 200 (512) 87 / 70; 16: 1000
+    // (16) 40.5 / 43.6, 14 x 800 (182) 61.2 / 58.9, 32 x 350 (192) 62.5 / 58.2; 24: 32 x 250 (128) 66.0 / 66.3, 64 x 130 (192) 99.2 / 97.2;
+    // 32: 4 x 1000 (64) 57.6 / 59.7, 64 x 130 (192) 145 / 148, 16 x 1000 (256) 193 / 190; 40: 32 x 1000 (512) 480 / 479, 8 x 6000
+    // (752) 1002 / 1024.  Not multiples of eight: 28 heads by page 84 -> 91, 4000 x 4 200 -> 201.
+    const bool by_page = d_c == 256 && heads % 8 == 0 && heads <= 32 && pages > std::max(160, 6 * heads);
     const dim3 grid = by_page ? dim3(per, kinds) : dim3(kinds, per);
     if (d_c == 512) prefill_materialise_kernel<512><<<grid, PM_WAVES<512> * 64, 0, s>>>(rows, page_table, seq_lens, uk, uv, pool, table2, lens2, B, heads, num_pages, max_pages, by_page);
     else            prefill_materialise_kernel<256><<<grid, PM_WAVES<256> * 64, 0, s>>>(rows, page_table, seq_lens, uk, uv, pool, table2, lens2, B, heads, num_pages, max_pages, by_page);

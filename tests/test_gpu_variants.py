@@ -304,6 +304,18 @@ def test_prefill_of_many_sequences(mla, lens, d_c):
     check_prefill(mla, w, 1)
 
 
+@pytest.mark.parametrize("H,B,pages,by_page", [(8, 32, 5, False), (8, 28, 6, True), (16, 16, 10, False), (16, 16, 11, True), (24, 12, 14, True),
+                                               (32, 8, 24, False), (32, 8, 25, True), (40, 6, 41, False)])
+def test_prefill_order_of_the_workgroups(mla, H, B, pages, by_page):
+    """Multiples of eight heads with their weights in LDS: workgroups of a head, or of a page, first."""
+    from test_gpu_parity import check_prefill
+    lens = [pages * 64 - (29 * b) % 64 for b in range(B)]
+    assert weights_in_lds(B, 1, lens, H, 256) and (H <= 32 and B * pages > max(160, 6 * H)) == by_page
+    w = synth.make_workload("prefill", B=B, H=H, d_head=128, d_c=256, d_rope=64, seq_lens=lens, io_dtype="bf16",
+                            cache_dtype="bf16", free_frac=0.1, seed=133)
+    check_prefill(mla, w, 1)
+
+
 @pytest.mark.parametrize("T,L,late", [(200, 210, 150), (200, 225, 153), (129, 129, 128), (300, 331, 169), (256, 260, 132), (140, 191, 180)])
 def test_prefill_later_tokens_stay_out_whatever_they_hold(mla, T, L, late):
     """A token behind every query of a group of 128, in the group's last tile of 32 (and in later ones), whose latent
