@@ -468,14 +468,16 @@ hipError_t launch_prefill_materialise(const void* kv, const int32_t* page_table,
     }
     // One workgroup per CU (its weights fill the LDS), the same number for every head: of one to eight rounds of them the number
     // that takes the least time, a round's weights counted as 0.3 of the page that a pair of wavefronts takes next (1000
-    // tokens, 28 heads, d_c = 512: four per kind 51 us, two rounds of nine 56).
+    // tokens, 28 heads, d_c = 512: four per kind 51 us, two rounds of nine 56).  More rounds have to save an eighth (d_c = 512: a
+    // twentieth) of that: 8 x 6000 tokens, 500 queries, 40 heads, three rounds counted as 0.975 of one 1004 / 972, 44 heads, two as
+    // 0.95 1131 / 1091; 8 x 1000, 44 heads, three as 0.91 114 / 106; but d_c = 512, 1000 tokens, 72 heads, three as 0.91 76 / 81.
     const int kinds = heads * (d_c / 256), pairs = (d_c == 512 ? PM_WAVES<512> : PM_WAVES<256>) / 2;
     int per = 1;
     double least = 1e30;
     for (int rounds = 1; rounds <= 8; ++rounds) {
         const int n = (int)std::min<long long>(std::max(1, 256 * rounds / kinds), pages);
         const double time = (double)(((long long)kinds * n + 255) / 256) * (0.3 + (double)((pages + (long long)n * pairs - 1) / ((long long)n * pairs)));
-        if (time < least) { least = time; per = n; }
+        if (time < (d_c == 512 ? 0.95 : 0.88) * least) { least = time; per = n; }
     }
     // A multiple of eight heads, which would each stay on one XCD: the shares vary first where there are many pages, so that a page's
     // latent rows are read on one XCD only; with few, reading the weights on all of them costs more.  us by head / by page, d_c = 256,
