@@ -395,8 +395,10 @@ hipError_t launch_gemm_f64(const GemmF64& asked, hipStream_t s)
     c.tiles = g.symmetric ? row_start(c.tiles_m, c.tiles_n) : c.tiles_m * c.tiles_n;
     c.workgroups = c.tiles;
     c.cols = std::min(g.N, BM);
-    if (g.partial && !g.lower) {
-        // Shares where whole tiles leave CUs without one, or with one less than others: one per CU, four steps at least; two
+    if (g.partial && !g.lower && c.nk >= 12) {
+        // Shares where whole tiles leave CUs without one, or with one less than others, and the sums are deep enough for the second
+        // launch (S Q of order 90, 8 columns, 6 steps 9.2 us, without 7.0; 130 x 130, 9 steps 11.6, 8.8; 152 x 152, 10 steps 10.0, 9.5; 177 x 20,
+        // 12 steps 9.6, whole tiles 12.6; 186 x 8 8.9, 10.5; but 192 x 64 9.2, 8.8): one per CU, four steps at least; two
         // from 8192 steps on, where a share is long enough to pay for its ends and the other one fills its waits; three
         // a little above two tiles per CU.  S Q, us at whole tiles, 256, 512 and 768 shares: 1000 x 65 (2016 steps) 51, 20, 26, 26;
         // 2000 x 128 (8000) 77, 29, 30, 32; 4096 x 32 (16384) 154, 45, 42, 45; 8128 x 128 (254 tiles) 376, 372, 287, 285;

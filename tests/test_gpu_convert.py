@@ -589,9 +589,11 @@ def test_matrix_product_tile_edges_and_alignment(cv, n, D, m):
 
 
 @pytest.mark.parametrize("m,p,scratch", [(1000, 2, 1), (1000, 33, 1), (1001, 65, 1), (4096, 64, 1), (7300, 31, 1), (3600, 128, 1),
-                                         (2001, 513, 1), (4001, 520, 1), (4096, 600, 1), (1000, 65, 0.5), (1000, 65, 0)])
+                                         (2001, 513, 1), (4001, 520, 1), (4096, 600, 1), (1000, 65, 0.5), (1000, 65, 0),
+                                         (176, 65, 1), (177, 65, 1), (90, 2, 1)])
 def test_matrix_product_shares(cv, m, p, scratch):
-    """One share of the K steps per CU, two, three, whole tiles, and as many as a short scratch has room for; parts of few columns.
+    """One share of the K steps per CU, two, three, whole tiles, and as many as a short scratch has room for; parts of few columns;
+    sums of 11 steps, which are not cut, and of 12.
     A sum of m products in another order than torch's: m 2^-53 of the sum of their magnitudes, twice."""
     import torch
     gen = torch.Generator(device="cuda").manual_seed(m + p)
