@@ -803,7 +803,8 @@ __device__ __forceinline__ void factor_invert(double* S, double* V, double* dinv
                         continue;
                     }
                     double d = read_lane(a[j], s0 + j);
-                    if (!(d > floor_v)) {
+                    if (__builtin_expect(!(d > floor_v), 0)) {
+                        asm volatile("");                // (a branch: selects would lie in every pivot's chain)
                         d = floor_v;
                         a[j] = 0.0;
                         dropped |= 1ull << (s0 + j);
@@ -896,6 +897,7 @@ __global__ __launch_bounds__(256) void chol_step_kernel(double* G, double* X, do
         const bool in_G = j > k;
         double* C = in_G ? G : X;
         double vd[16], va[16], vz[16];
+        const unsigned long long dropped = marks[k];  // (asked for with the blocks: behind the products 0.7 us a column)
         block_get(Linv, NB, k * NB, 0, p, NB, tid, vd);
         block_get(G, p, i * NB, k * NB, p, p, tid, va);
         const bool square = i == j;                   // L_jk is L_ik: the next diagonal block is one of these
@@ -922,7 +924,6 @@ __global__ __launch_bounds__(256) void chol_step_kernel(double* G, double* X, do
         f64x4 l[4];
         block_nt<true>(A, D, wave, lane, l);          // L_ik
         if (!square) block_nt<true>(Z, D, wave, lane, u);   // L_jk, or X_kj transposed
-        const unsigned long long dropped = marks[k];
         if (dropped) {
 #pragma unroll
             for (int t = 0; t < 4; ++t)
