@@ -64,12 +64,14 @@ int chol_qr(const double* Y, double* out, const TopWs& w, int m, int p, int* bad
     return st(launch_gemm_f64(q, s));
 }
 
-// The symmetric matrix whose leading eigenvectors are wanted: S [m x m], or C^T C / n by its factor C [n x m] (Z: n x p of scratch)
+// The symmetric matrix whose leading eigenvectors are wanted: S [m x m], or C^T C / n by its factor C [n x m] (Z: n x p of
+// scratch), with or without K = C C^T / n [n x n] (Z may lie over K)
 struct Symmetric {
     const double* S;
     const double* C;
     int n;
     double* Z;
+    const double* K = nullptr;
 };
 
 // Y = S Q
@@ -88,15 +90,28 @@ int top_eig(const Symmetric& S, const double* Q0, double* evals, double* R, cons
     // orthonormal start block (two passes: the start block is the caller's and may be badly conditioned)
     if ((rc = chol_qr(Q0, w.Y, w, m, p, info, s)) != MLA_OK) return rc;
     if ((rc = chol_qr(w.Y, w.Q, w, m, p, info, s)) != MLA_OK) return rc;
-    for (int it = 0; it < iters; ++it) {
-        e = apply(S, w.Q, w.Y, w, m, p, s);
+    auto product = [&](GemmF64 g) { g.partial = w.part; g.partial_doubles = w.part_doubles; return launch_gemm_f64(g, s); };
+    if (S.K) {      // S^iters Q spans what C^T K^(iters - 1) (C Q) does: all steps but the ends of the first and the last among n rows
+        e = product(gemm_nn(S.C, m, w.Q, p, w.Y, p, S.n, p, m, 1.0));
+        for (int it = 1; e == hipSuccess && it < iters; ++it) {
+            if ((rc = chol_qr(w.Y, w.Q, w, S.n, p, info, s)) != MLA_OK) return rc;
+            e = product(gemm_nn(S.K, S.n, w.Q, p, w.Y, p, S.n, p, S.n, 1.0));
+        }
+        if (e != hipSuccess) return MLA_ERR_HIP;
+        if ((rc = chol_qr(w.Y, w.Q, w, S.n, p, info, s)) != MLA_OK) return rc;
+        e = product(gemm_tn(S.C, m, w.Q, p, w.Y, p, m, p, S.n, 1.0));
         if (e != hipSuccess) return MLA_ERR_HIP;
         if ((rc = chol_qr(w.Y, w.Q, w, m, p, info, s)) != MLA_OK) return rc;
+    } else {
+        for (int it = 0; it < iters; ++it) {
+            e = apply(S, w.Q, w.Y, w, m, p, s);
+            if (e != hipSuccess) return MLA_ERR_HIP;
+            if ((rc = chol_qr(w.Y, w.Q, w, m, p, info, s)) != MLA_OK) return rc;
+        }
     }
     // second pass restores orthonormality to rounding level before the Rayleigh-Ritz step
     if ((rc = chol_qr(w.Q, w.Y, w, m, p, info, s)) != MLA_OK) return rc;
     // T = Q^T S Q (S by its factor: (C Q)^T (C Q) / n), T = Z diag(evals) Z^T, R = Q Z[:, :r]
-    auto product = [&](GemmF64 g) { g.partial = w.part; g.partial_doubles = w.part_doubles; return launch_gemm_f64(g, s); };
     if (S.S) {
         e = apply(S, w.Y, w.Q, w, m, p, s);
         if (e == hipSuccess) e = product(gemm_tn(w.Y, p, w.Q, p, w.T, p, p, p, m, 1.0));
@@ -283,14 +298,27 @@ int mla_convert_layer(const double* X, const double* W_K, const double* W_V, con
     const TopWs top = top_ws(w.top, mj, p);
     // The power iteration needs the moment S = C^T C / n only in products with a block, 2 m^2 p operations each; by the factor they
     // take 4 n m p and S itself (n m^2) is not formed, but a step has one product more, which costs about 12 us (8e8 operations)
-    // whatever its size.  Whichever is less; ms a layer by the factor / by S (20 iterations unless said): m = 8128, p = 768, 4096
+    // whatever its size.  Ms a layer by the factor / by S (20 iterations unless said): m = 8128, p = 768, 4096
     // tokens 69.3 / 75.0; m = 4032, p = 560: 1024 19.7 / 22.9, 2048 23.4 / 23.9, 2300 25.8 / 25.5; m = 1984, p = 320: 512 9.13 / 9.31,
     // 768 9.46 / 9.44, 1100 9.90 / 9.61; 4 iterations 768 6.89 / 6.97, 1100 7.12 / 7.14, 1400 7.27 / 7.26; m = 480, p = 80: 64 2.92 / 2.92,
     // 256 3.12 / 2.93.
+    // Fewer tokens than dimensions: with K = C C^T / n (n^2 m), S^iters Q = C^T K^(iters - 1) C Q / n, so that all steps but the ends
+    // of the first and the last are products of 2 n^2 p among n rows, as their orthonormal blocks are; a Cholesky pass more of the m
+    // rows, 2.4e7 p operations' time.  The better of the others / by K: 8128, 768, 4096 tokens 63.4 / 42.8; 4032, 768: 768 23.6 / 20.1,
+    // 2016 29.0 / 23.3, 3024 30.0 / 27.1, 3830 30.9 / 31.1; 1984, 320: 320 7.8 / 7.2, 992 8.7 / 8.2, 1884 8.9 / 9.1.
     Symmetric moment{nullptr, w.C, n, w.S};
     const double by_factor = (4.0 * iters + 2.0) * n * mj * p + 1.0 * n * p * p + 8e8 * iters;
     const double by_moment = 1.0 * n * mj * mj + (2.0 * iters + 2.0) * mj * mj * p + 2.0 * mj * p * p;
-    if (by_moment <= by_factor || (size_t)n * p > s_doubles) {
+    const double by_tokens = 1.0 * n * n * mj + 2.0 * (iters - 1) * n * n * p + 6.0 * n * mj * p + 1.0 * n * p * p +
+                             2.0 * (mj - 1.0 * iters * (mj - n)) * p * p + 2.4e7 * p;
+    if (iters >= 1 && n >= p && n < mj && by_tokens < std::min(by_moment, by_factor)) {
+        GemmF64 cct = gemm_nt(w.C, mj, w.C, mj, w.S, n, n, n, mj, 1.0 / (double)n);
+        cct.symmetric = 1;
+        cct.partial = top.part;
+        cct.partial_doubles = top.part_doubles;
+        MLA_TRY(launch_gemm_f64(cct, s));
+        moment.K = w.S;
+    } else if (by_moment <= by_factor || (size_t)n * p > s_doubles) {
         GemmF64 ctc = gemm_tn(w.C, mj, w.C, mj, w.S, mj, mj, mj, n, 1.0 / (double)n);
         ctc.symmetric = 1;
         ctc.partial = top.part;

@@ -170,7 +170,8 @@ __device__ __forceinline__ double scale_of(const GemmF64& g)
     return g.dev_mode == 1 ? g.alpha * *g.alpha_dev : g.dev_mode == 2 ? g.alpha / *g.alpha_dev : g.alpha;
 }
 
-template <bool A_KC, bool B_KC, bool DIRECT>
+// MIRROR: turns tiles over (C C^T has an instantiation of its own: in that of X W^T the code cost small layers 0.5 %)
+template <bool A_KC, bool B_KC, bool DIRECT, bool MIRROR>
 __global__ __launch_bounds__(THREADS, A_KC && B_KC ? 4 : 3) void gemm_f64_kernel(GemmF64 g, Cut c)
 {
     using OpA = Operand<A_KC, DIRECT>;
@@ -299,7 +300,7 @@ __global__ __launch_bounds__(THREADS, A_KC && B_KC ? 4 : 3) void gemm_f64_kernel
                     for (int r = 0; r < 4; ++r) part[(wm + i * 16 + 4 * r + ly) * c.cols + col] = acc[i][j][r];
                 }
         } else {                                         // the whole sum, or its first part in its place
-            const bool whole = kt1 == at.nk, mirror = !A_KC && !B_KC && g.symmetric && at.tm != at.tn && whole;
+            const bool whole = kt1 == at.nk, mirror = MIRROR && g.symmetric && at.tm != at.tn && whole;
             const double scale = whole ? scale_of(g) : 1.0;
 #pragma unroll
             for (int i = 0; i < T; ++i)
@@ -352,12 +353,12 @@ __global__ __launch_bounds__(256) void gemm_f64_reduce_kernel(GemmF64 g, Cut c)
         }
 }
 
-template <bool A_KC, bool B_KC, bool DIRECT>
+template <bool A_KC, bool B_KC, bool DIRECT, bool MIRROR = !A_KC && !B_KC>
 hipError_t run(const GemmF64& g, const Cut& c, hipStream_t s)
 {
     constexpr size_t lds_bytes = 2 * (Operand<A_KC, DIRECT>::STAGE + Operand<B_KC, DIRECT>::STAGE) * sizeof(double);
     static_assert(lds_bytes <= 64 * 1024, "no raised limit needed");
-    gemm_f64_kernel<A_KC, B_KC, DIRECT><<<(c.workgroups + 7) / 8 * 8, THREADS, lds_bytes, s>>>(g, c);
+    gemm_f64_kernel<A_KC, B_KC, DIRECT, MIRROR><<<(c.workgroups + 7) / 8 * 8, THREADS, lds_bytes, s>>>(g, c);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || !c.share) return e;
     gemm_f64_reduce_kernel<<<dim3(c.tiles, T * T), 256, 0, s>>>(g, c);
@@ -368,7 +369,7 @@ template <bool DIRECT>
 hipError_t run(const GemmF64& g, const Cut& c, hipStream_t s)
 {
     const bool a_kc = g.sAk == 1, b_kc = g.sBk == 1;
-    if (a_kc && b_kc) return run<true, true, DIRECT>(g, c, s);
+    if (a_kc && b_kc) return g.symmetric ? run<true, true, DIRECT, true>(g, c, s) : run<true, true, DIRECT, false>(g, c, s);
     if (a_kc) return run<true, false, DIRECT>(g, c, s);
     if (b_kc) return run<false, true, DIRECT>(g, c, s);
     return run<false, false, DIRECT>(g, c, s);
@@ -384,7 +385,7 @@ hipError_t launch_gemm_f64(const GemmF64& asked, hipStream_t s)
     if (g.lower && g.symmetric) return hipErrorInvalidValue;
     const bool a_kc = g.sAk == 1, b_kc = g.sBk == 1;
     if ((!a_kc && g.sAm != 1) || (!b_kc && g.sBn != 1)) return hipErrorInvalidValue;
-    if (g.symmetric && a_kc) g.symmetric = 0;            // (one column: there is nothing to mirror)
+    if (a_kc != b_kc) g.symmetric = 0;
     Cut c{};
     c.tiles_m = (g.M + BM - 1) / BM;
     c.tiles_n = (g.N + BM - 1) / BM;

@@ -334,6 +334,24 @@ def test_convert_layer_iterates_as_top_eig_does(cv, g, d, n, p, iters, by_factor
     assert projector_gap(host(out["R_KV"]), R) < 6e-5
 
 
+@pytest.mark.parametrize("g,d,n,p,iters", [(8, 128, 128, 128, 20), (8, 128, 131, 128, 20), (8, 128, 1201, 130, 20), (8, 64, 950, 65, 20),
+                                           (8, 128, 500, 100, 2), (8, 128, 300, 64, 1), (4, 64, 479, 40, 30)])
+def test_convert_layer_iterates_among_tokens(cv, g, d, n, p, iters):
+    """Few tokens: the steps of the iteration as products with C C^T, whose blocks have a row per token (square blocks, odd
+    sizes, one step, nearly as many tokens as dimensions).  Against top_eig of the moment itself from the same block, with the
+    bounds of the other forms."""
+    M, keep, D, r_kv = 2, 1, 256, min(32, p // 2)
+    d_rope = co.rope_width(d, M, keep)
+    X, W_K, W_V, Q0 = chain_case(g, g, d, D, n, M, keep, r_kv, p, seed=n)
+    out = cv.convert_layer(dev(X), dev(W_K), dev(W_V), dev(Q0), g, g, d, M, r_kv, iters=iters, keep=keep)
+    W_rot = cv.rotate_rows(dev(W_K), out["U"], g, d, M, keep)
+    S, _ = cv.joint_moment(cv.project(dev(X), W_rot[d_rope:].contiguous()), cv.project(dev(X), dev(W_V)), out["alpha"])
+    evals, R, info = (host(x) for x in cv.top_eig(S, dev(Q0), r_kv, iters))
+    assert host(out["info"])[-1] >= 1 and info[1] >= 1
+    assert np.abs(host(out["evals_joint"])[:r_kv] - evals[:r_kv]).max() < 1e-10 * evals[0]
+    assert projector_gap(host(out["R_KV"]), R) < 6e-5
+
+
 # ------------------------------------------------------------------ the benchmark shape, by properties
 
 def test_convert_layer_at_the_llama2_7b_layer_shape_by_properties(cv):
