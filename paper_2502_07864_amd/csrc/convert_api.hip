@@ -11,7 +11,7 @@ namespace {
 constexpr int JACOBI_MAX_SWEEPS = 60;
 // Rayleigh-Ritz matrix of the power iteration (block solver above order 128).  After some iterations it is nearly
 // diagonal (6 or 7 sweeps); a block that was iterated little over a moment of low rank takes up to 14.  Every sweep
-// enqueued beyond convergence costs its launches, which return at once: 96 at order 768, 0.24 ms.  A matrix
+// enqueued beyond convergence costs its launches, which return at once: 49 at order 768, 0.08 ms.  A matrix
 // that needs more is reported through info (-1).
 constexpr int RITZ_MAX_SWEEPS = 16;
 
@@ -124,7 +124,8 @@ int top_eig(const Symmetric& S, const double* Q0, double* evals, double* R, cons
     if (e != hipSuccess) return MLA_ERR_HIP;
     e = launch_symmetrise(w.T, p, s);
     if (e != hipSuccess) return MLA_ERR_HIP;
-    e = launch_jacobi(w.T, evals, w.Z, info + 1, 1, p, p > 128 ? RITZ_MAX_SWEEPS : JACOBI_MAX_SWEEPS, s);
+    e = launch_jacobi(w.T, evals, w.Z, info + 1, 1, p, p > 128 ? RITZ_MAX_SWEEPS : JACOBI_MAX_SWEEPS, s,
+                      JacobiSpare{w.G, w.X, (size_t)p * p});
     if (e != hipSuccess) return MLA_ERR_HIP;
     return st(launch_gemm_f64(gemm_nn(w.Y, p, w.T, p, R, r, m, r, p, 1.0), s));
 }

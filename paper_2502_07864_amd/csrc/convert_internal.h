@@ -50,7 +50,10 @@ hipError_t launch_alpha(const double* norms, double* alpha, int n, hipStream_t s
 hipError_t launch_balance(const double* K, int ldk, const double* V, int ldv, const double* alpha, double* C, int n, int a, int b, hipStream_t s);
 // work: jacobi_work_bytes(batch, m) bytes
 size_t jacobi_work_bytes(int batch, int m);
-hipError_t launch_jacobi(double* A, double* evals, double* work, int* info, int batch, int m, int max_sweeps, hipStream_t s);
+// spare, orders above 128: room for a second matrix and for `doubles` more, with which a step is one launch instead of two
+struct JacobiSpare { double* matrix = nullptr; double* rest = nullptr; size_t doubles = 0; };
+hipError_t launch_jacobi(double* A, double* evals, double* work, int* info, int batch, int m, int max_sweeps, hipStream_t s,
+                         const JacobiSpare& spare = {});
 // X = the inverse of the lower Cholesky factor of G (p x p, symmetric positive definite), zero above the diagonal;
 // *bad += clamped pivots; G is overwritten.  p <= TOP_MAX_P.  tmp: chol_tmp_doubles(p) doubles of scratch.
 constexpr int CHOL_HEAD = 24;        // of them, in front: the pivots' floor, a word of marks per 64 columns

@@ -518,18 +518,22 @@ __global__ __launch_bounds__(1024) void jacobi_kernel(double* A_all, double* eva
 
 // ------------------------------------------------------------------ Jacobi eigensolver, one large matrix
 // Block Jacobi over the chip: the indices are cut into blocks of 16; a step of the round-robin schedule over the
-// blocks takes disjoint pairs of blocks.  jb_pair_kernel: the workgroup of pair P = (I, J) runs one sweep of
-// rotations on the 32 x 32 matrix A[P, P] in LDS, accumulating them in a 32 x 32 orthogonal matrix Z_P;
-// jb_update_kernel applies them: A[P, Q] <- Z_P^T A[P, Q] Z_Q, V[:, Q] <- V[:, Q] Z_Q, on the fp64 matrix
-// instructions, one workgroup per 32 x 32 tile.  Launch order on the stream is the only synchronisation.  A sweep
-// of order m is m/16 - 1 such steps of two launches and annihilates every pair of indices at least once; single
-// rotations spread over the chip took m - 1 launches that each rewrote A and V: order 768, 10 us a launch, 47 ms
-// for 6 sweeps (and 14 ms for the norms, by one workgroup, and for the launches behind convergence); this form
-// 34 us a step, 11 ms in all, 23 us of a step for the pairs (31 dependent rotation steps) and 11 for the update.  A sweep
+// blocks takes disjoint pairs of blocks.  The workgroup of pair P = (I, J) rotates the 32 x 32 matrix A[P, P] in LDS,
+// accumulating its rotations in a 32 x 32 orthogonal matrix Z_P: every index of I with every one of J, and in every fourth
+// step those inside I and J first (they meet again in the next pairs; sweeps that took all 31 rotation steps every time
+// converged no sooner, on full, graded, low-rank and multiple spectra).  The tiles' workgroups apply the rotations:
+// A[P, Q] <- Z_P^T A[P, Q] Z_Q, V[:, Q] <- V[:, Q] Z_Q, on the fp64 matrix instructions.  Launch order on the stream is the
+// only synchronisation.  A sweep of order m is m/16 - 1 such steps and annihilates every pair of indices at least once; single
+// rotations spread over the chip took m - 1 launches that each rewrote A and V: order 768, 47 ms for 6 sweeps.
+// What bounds it is the chain of rotation steps of a pair, so given a second matrix of scratch (the Rayleigh-Ritz matrix) a
+// launch applies a step's rotations, from one matrix to the other, while the next step's pairs work out the
+// block they need of its result for themselves.  Order 768, a step: 34 us as two launches with all rotation steps (23 + 11), now
+// 13.0, 21.0 with the inner rotations; 16.4 where the whole matrix was read and written.  A sweep
 // starts with a norm pair of launches that raises `done` once the off-diagonal part is small; later launches then return at
 // once, so the host can enqueue the maximum number of sweeps without reading back.
-struct WideState { double tot; int done, sweeps; };
+struct WideState { double tot; int done, sweeps, at; };    // at: sweeps before `done` was raised
 constexpr int JB = 16, JP = 2 * JB;                    // block, pair of blocks
+constexpr int JB_INNER = 4;                            // steps between rotations inside the blocks
 constexpr int JB_NORM_WGS = 64;
 
 __global__ __launch_bounds__(256) void jw_init_kernel(double* __restrict__ V, int m, WideState* st) {
@@ -539,15 +543,16 @@ __global__ __launch_bounds__(256) void jw_init_kernel(double* __restrict__ V, in
     if (blockIdx.x == 0 && threadIdx.x == 0) { st->tot = 0.0; st->done = 0; st->sweeps = -1; }
 }
 
-// partial squared norms (off the diagonal, on it) of a share of the rows; then their sums in order
+// partial squared norms (off the diagonal, on it) of a share of the rows, from the blocks on and above the diagonal; then their
+// sums in order
 __global__ __launch_bounds__(256) void jw_partial_norm_kernel(const double* __restrict__ A, int m, double* __restrict__ part, const WideState* st) {
     __shared__ double red[16];
     if (st->done) return;
     double off = 0.0, dia = 0.0;
     for (int i = blockIdx.x; i < m; i += JB_NORM_WGS)
-        for (int j = threadIdx.x; j < m; j += 256) {
+        for (int j = i / JB * JB + threadIdx.x; j < m; j += 256) {
             const double v = A[(long)i * m + j];
-            if (i == j) dia += v * v; else off += v * v;
+            if (i == j) dia += v * v; else off += j / JB == i / JB ? v * v : 2.0 * (v * v);
         }
     off = block_sum(off, red);
     dia = block_sum(dia, red);
@@ -560,7 +565,7 @@ __global__ __launch_bounds__(64) void jw_norm_kernel(const double* __restrict__ 
     const double off = wave_sum(part[2 * threadIdx.x]), dia = wave_sum(part[2 * threadIdx.x + 1]);
     if (threadIdx.x == 0) {
         if (sweep == 0) st->tot = off + dia;
-        if (off <= 1e-26 * st->tot) { st->done = 1; st->sweeps = sweep > 0 ? sweep : 1; }
+        if (off <= 1e-26 * st->tot) { st->done = 1; st->sweeps = sweep > 0 ? sweep : 1; st->at = sweep; }
     }
 }
 
@@ -572,108 +577,243 @@ __device__ __forceinline__ void block_pair(int k, int step, int nbp, int& I, int
     I = min(p, q);
     J = max(p, q);
 }
+// the pair that block b belongs to in a step
+__device__ __forceinline__ int pair_of(int b, int step, int nbp) {
+    const int d = b >= step ? b - step : b - step + nbp - 1;       // (b, step < nbp - 1)
+    return b == nbp - 1 ? 0 : d < nbp / 2 ? d : nbp - 1 - d;
+}
 
 // index r of pair (I, J) in the matrix (>= m: not there)
 __device__ __forceinline__ int pair_index(int I, int J, int r) { return (r < JB ? I : J) * JB + (r & (JB - 1)); }
+// where the symmetric matrix has element (i, j): only its blocks on and above the diagonal are kept up
+__device__ __forceinline__ long upper(int i, int j, int m) { return i / JB <= j / JB ? (long)i * m + j : (long)j * m + i; }
 
-// A thread (k1, k2) owns a 2 x 2 block of a and two rows of z as in jacobi_step, but works out both of its rotations itself and
-// writes to the other buffer of a: one barrier a step and no exchange of angles (four wavefronts have the vector pipes for it).
-// Launch of order 768 (24 pairs) over its 31 rotation steps: 1.16 us a step as two phases with the angles between them, 1.0 with
-// the blocks read beside the angles, now 0.74.
-__global__ __launch_bounds__(256) void jb_pair_kernel(double* A, double* __restrict__ Z, int m, int nbp, int step, const WideState* st) {
-    constexpr int LD = JP + 1, HALF = JP / 2;
-    __shared__ double a[2][JP * LD], z[JP * LD];
-    if (st->done) return;
-    const int tid = threadIdx.x;
+// What a step reads and writes.  A to B: the matrix (blocks on and above the diagonal) before and after the rotations; Z, D: rotations and rotated 32 x 32 matrix of
+// every pair.  Without D, A is B and a pair's rotated matrix goes straight to its place.
+struct WideStep {
+    const double* A; double* B; double* V;
+    const double* Z; const double* D;                  // of `step`, which is applied (step < 0: nothing is)
+    double* Z_next; double* D_next;                    // of `next`, whose pairs are rotated (next < 0: none are)
+    int m, nbp, step, next;
+    const WideState* st;
+};
+constexpr int WLD = JP + 1;
+struct WideLds { double a[2][JP * WLD], z[JP * WLD]; };
+
+// v_mfma_f64_16x16x4: lane l supplies A[l % 16][l / 16], B[l / 16][l % 16], receives D[4 r + l / 16][l % 16]
+__device__ __forceinline__ f64x4 mfma_f64(double a, double b, f64x4 c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
+
+__host__ __device__ __forceinline__ int eights(int n) { return (n + 7) / 8 * 8; }
+
+// element (r, c) of pair (I, J) to its place (what lies below the diagonal blocks isn't kept up)
+__device__ __forceinline__ void put_pair(double* B, int m, int I, int J, int r, int c, double v) {
+    const int i = pair_index(I, J, r), j = pair_index(I, J, c);
+    if (i < m && j < m && (r < JB || c >= JB)) B[(long)i * m + j] = v;
+}
+
+// A thread (k1, k2) owns the 2 x 2 block of a where the rows of one rotation meet the columns of another, and two rows of z in the
+// latter's columns; it writes to the other buffer of a, so that a rotation step has one barrier.  Every 16 lanes work out the
+// step's 16 rotations, a lane each; those of the rows come from another lane.  Order 768 (24 pairs), a rotation step: 1.16 us as two
+// phases with the angles between them, 0.74 with both rotations of a block worked out by its thread, now 0.54 (no shorter
+// without the branches of rotation(): the dependent fp64 operations and the trips through LDS are what it takes).
+__device__ void wide_pair(const WideStep& w, WideLds& L, int k, int tid) {
     int I, J;
-    block_pair(blockIdx.x, step, nbp, I, J);
-    for (int idx = tid; idx < JP * JP; idx += 256) {
-        const int r = idx / JP, c = idx % JP, i = pair_index(I, J, r), j = pair_index(I, J, c);
-        a[0][r * LD + c] = i < m && j < m ? A[(long)i * m + j] : 0.0;      // indices that are not there rotate with nothing
-        z[r * LD + c] = r == c ? 1.0 : 0.0;
+    block_pair(k, w.next, w.nbp, I, J);
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), li = lane & 15, lq = lane >> 4;
+    double* const a0 = L.a[0];
+    if (w.step < 0 || !w.D) {                          // the matrix as it lies there
+        const int r = tid >> 4, c = tid & 15, i = I * JB, j = J * JB;
+        auto at = [&](int row, int col) { return row < w.m && col < w.m ? w.A[(long)row * w.m + col] : 0.0; };
+        const double di = at(i + r, i + c), dj = at(j + r, j + c), v = at(i + r, j + c);      // indices that are not there rotate with nothing
+        a0[r * WLD + c] = di;
+        a0[(JB + r) * WLD + JB + c] = dj;
+        a0[r * WLD + JB + c] = v;
+        a0[(JB + c) * WLD + r] = v;
+    } else {
+        // after the rotations of `step`: the diagonal blocks have been rotated in their pairs; [I, J] is Z_P[:, I]^T A[P, Q] Z_Q[:, J]
+        const int P = pair_of(I, w.step, w.nbp), Q = pair_of(J, w.step, w.nbp);
+        int PI, PJ, QI, QJ;
+        block_pair(P, w.step, w.nbp, PI, PJ);
+        block_pair(Q, w.step, w.nbp, QI, QJ);
+        const int hp = I == PI ? 0 : JB, hq = J == QI ? 0 : JB;
+        const double* const Zp = w.Z + (long)P * JP * JP + hp;
+        const double* const Zq = w.Z + (long)Q * JP * JP + hq;
+        // wavefront (rows 16 ra of P, columns 16 cb of Q): T = A[ra, cb] Z_Q[cb, J], then its share Z_P[ra, I]^T T of the sum
+        const int ra = (wave & 1) * JB, cb = (wave >> 1) * JB;
+        double x[4], zq[4], zp[4];
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            const int i = pair_index(PI, PJ, ra + li), j = pair_index(QI, QJ, cb + 4 * s + lq);
+            x[s] = i < w.m && j < w.m ? w.A[upper(i, j, w.m)] : 0.0;
+            zq[s] = Zq[(cb + 4 * s + lq) * JP + li];
+            zp[s] = Zp[(ra + 4 * s + lq) * JP + li];
+        }
+        const double di = w.D[(long)P * JP * JP + (hp + (tid >> 4)) * JP + hp + (tid & 15)];
+        const double dj = w.D[(long)Q * JP * JP + (hq + (tid >> 4)) * JP + hq + (tid & 15)];
+        f64x4 t = {0.0, 0.0, 0.0, 0.0}, sum = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int s = 0; s < 4; ++s) t = mfma_f64(x[s], zq[s], t);
+#pragma unroll
+        for (int s = 0; s < 4; ++s) sum = mfma_f64(zp[s], t[s], sum);     // (a result tile lies in the lanes as the right operand does)
+        double* const part = L.a[1];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) part[wave * 256 + (4 * r + lq) * JB + li] = sum[r];
+        __syncthreads();
+        const int r = tid >> 4, c = tid & 15;
+        const double v = ((part[tid] + part[256 + tid]) + part[512 + tid]) + part[768 + tid];
+        a0[r * WLD + c] = di;
+        a0[(JB + r) * WLD + JB + c] = dj;
+        a0[r * WLD + JB + c] = v;
+        a0[(JB + c) * WLD + r] = v;
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const int idx = tid + 256 * u;
+        L.z[idx / JP * WLD + idx % JP] = idx / JP == idx % JP ? 1.0 : 0.0;
     }
     __syncthreads();
-    const int k1 = tid / HALF, k2 = tid % HALF;
-    double* const z0 = z + 2 * k1 * LD;
-    double* const z1 = z0 + LD;
-    for (int s = 0; s < JP - 1; ++s) {
-        const double* x = a[s & 1];
-        double* y = a[(s & 1) ^ 1];
-        int p1, q1, p2, q2;
-        round_robin_pair(k1, s, JP, p1, q1);
-        round_robin_pair(k2, s, JP, p2, q2);
-        const double d1p = x[p1 * (LD + 1)], d1q = x[q1 * (LD + 1)], o1 = x[p1 * LD + q1];
-        const double d2p = x[p2 * (LD + 1)], d2q = x[q2 * (LD + 1)], o2 = x[p2 * LD + q2];
-        double b[4] = {x[p1 * LD + p2], x[p1 * LD + q2], x[q1 * LD + p2], x[q1 * LD + q2]};
+    const int k1 = tid >> 4, k2 = tid & 15;
+    double* const z0 = L.z + 2 * k1 * WLD;
+    double* const z1 = z0 + WLD;
+    int cur = 0;
+    auto rotate = [&](int p1, int q1, int p2, int q2) {
+        const double* x = L.a[cur];
+        double* y = L.a[cur ^ 1];
+        const double dp = x[p2 * (WLD + 1)], dq = x[q2 * (WLD + 1)], o = x[p2 * WLD + q2];
+        double b[4] = {x[p1 * WLD + p2], x[p1 * WLD + q2], x[q1 * WLD + p2], x[q1 * WLD + q2]};
         const double v0 = z0[p2], w0 = z0[q2], v1 = z1[p2], w1 = z1[q2];
-        const double2 r1 = rotation(d1p, d1q, o1), r2 = rotation(d2p, d2q, o2);
+        const double2 r2 = rotation(dp, dq, o);
+        const double2 r1 = make_double2(__shfl(r2.x, k1), __shfl(r2.y, k1));
         rotate_block(b, r1, r2, k1 == k2);
-        y[p1 * LD + p2] = b[0];
-        y[p1 * LD + q2] = b[1];
-        y[q1 * LD + p2] = b[2];
-        y[q1 * LD + q2] = b[3];
+        y[p1 * WLD + p2] = b[0];
+        y[p1 * WLD + q2] = b[1];
+        y[q1 * WLD + p2] = b[2];
+        y[q1 * WLD + q2] = b[3];
         z0[p2] = r2.x * v0 - r2.y * w0;
         z0[q2] = r2.y * v0 + r2.x * w0;
         z1[p2] = r2.x * v1 - r2.y * w1;
         z1[q2] = r2.y * v1 + r2.x * w1;
+        cur ^= 1;
         __syncthreads();
-    }
-    const double* x = a[(JP - 1) & 1];
-    for (int idx = tid; idx < JP * JP; idx += 256) {
-        const int r = idx / JP, c = idx % JP, i = pair_index(I, J, r), j = pair_index(I, J, c);
-        if (i < m && j < m) A[(long)i * m + j] = x[r * LD + c];
-        Z[(long)blockIdx.x * JP * JP + idx] = z[r * LD + c];
+    };
+    if (w.next % JB_INNER == 0)
+        for (int s = 0; s < JB - 1; ++s) {             // both blocks: rotations 0 .. 7 and 8 .. 15
+            int p1, q1, p2, q2;
+            round_robin_pair(k1 & 7, s, JB, p1, q1);
+            round_robin_pair(k2 & 7, s, JB, p2, q2);
+            rotate(p1 + (k1 & 8) * 2, q1 + (k1 & 8) * 2, p2 + (k2 & 8) * 2, q2 + (k2 & 8) * 2);
+        }
+    for (int s = 0; s < JB; ++s) rotate(k1, JB + ((k1 + s) & 15), k2, JB + ((k2 + s) & 15));
+    const double* x = L.a[cur];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const int idx = tid + 256 * u, r = idx / JP, c = idx % JP;
+        if (w.D_next) w.D_next[(long)k * JP * JP + idx] = x[r * WLD + c];
+        else          put_pair(w.B, w.m, I, J, r, c, x[r * WLD + c]);
+        w.Z_next[(long)k * JP * JP + idx] = L.z[r * WLD + c];
     }
 }
 
-// grid (column pair Q, row pair P or 32 rows of V, 2: A or V); four wavefronts, one 16 x 16 tile of the result each
-__global__ __launch_bounds__(256) void jb_update_kernel(double* A, double* V, const double* __restrict__ Z, int m, int nbp, int step,
-                                                        const WideState* st) {
-    constexpr int LDT = JP + 1;
-    __shared__ double t[JP * LDT], zq[JP * LDT], zp[JP * LDT];
-    if (st->done) return;
-    const int Q = blockIdx.x, P = blockIdx.y, tid = threadIdx.x;
-    const bool on_v = blockIdx.z == 1;
-    if (!on_v && P == Q) return;                       // the pair's own tile has been rotated where the angles were found
-    int I, J, K, L;
-    block_pair(Q, step, nbp, I, J);
-    block_pair(P, step, nbp, K, L);
-    double* M = on_v ? V : A;
-    auto row_of = [&](int r) { return on_v ? P * JP + r : pair_index(K, L, r); };
-    for (int idx = tid; idx < JP * JP; idx += 256) {
-        const int r = idx / JP, c = idx % JP, i = row_of(r), j = pair_index(I, J, c);
-        t[r * LDT + c] = i < m && j < m ? M[(long)i * m + j] : 0.0;
-        zq[r * LDT + c] = Z[(long)Q * JP * JP + idx];
-        if (!on_v) zp[r * LDT + c] = Z[(long)P * JP * JP + idx];
+// tile (P, Q), P <= Q, of A, or 32 rows P of V in the columns of Q; a wavefront has one 16 x 16 tile of the result
+__device__ void wide_tile(const WideStep& w, WideLds& L, int P, int Q, bool on_v, int tid) {
+    double* const t = L.a[0];
+    double* const zq = L.a[1];
+    double* const zp = L.z;
+    int I, J, K, M;
+    block_pair(Q, w.step, w.nbp, I, J);
+    block_pair(P, w.step, w.nbp, K, M);
+    if (!on_v && P == Q) {                             // rotated where the angles were found
+        if (w.D)
+            for (int idx = tid; idx < JP * JP; idx += 256) put_pair(w.B, w.m, I, J, idx / JP, idx % JP, w.D[(long)P * JP * JP + idx]);
+        return;
+    }
+    double x[4], y[4], z[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const int idx = tid + 256 * u;
+        y[u] = w.Z[(long)Q * JP * JP + idx];
+        if (on_v) {
+            const int i = P * JP + idx / JP, j = pair_index(I, J, idx % JP);
+            x[u] = i < w.m && j < w.m ? w.V[(long)i * w.m + j] : 0.0;
+        } else {                                       // a block of 16 x 16 each, in the order it is stored in
+            const int bi = u & 2 ? M : K, bj = u & 1 ? J : I, i = min(bi, bj) * JB + (tid >> 4), j = max(bi, bj) * JB + (tid & 15);
+            x[u] = i < w.m && j < w.m ? w.A[(long)i * w.m + j] : 0.0;
+            z[u] = w.Z[(long)P * JP * JP + idx];
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const int idx = tid + 256 * u, at = idx / JP * WLD + idx % JP;
+        zq[at] = y[u];
+        if (on_v) t[at] = x[u];
+        else {
+            const bool turn = (u & 2 ? M : K) > (u & 1 ? J : I);
+            const int r = turn ? tid & 15 : tid >> 4, c = turn ? tid >> 4 : tid & 15;
+            t[((u & 2) * 8 + r) * WLD + (u & 1) * 16 + c] = x[u];
+            zp[at] = z[u];
+        }
     }
     __syncthreads();
-    // v_mfma_f64_16x16x4: lane l supplies A[l % 16][l / 16], B[l / 16][l % 16], receives D[4 r + l / 16][l % 16]
-    const int lane = tid & 63, wave = tid >> 6, li = lane & 15, lq = lane >> 4;
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), li = lane & 15, lq = lane >> 4;
     const int r0 = (wave >> 1) * 16, c0 = (wave & 1) * 16;
     f64x4 acc = (f64x4){0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-    for (int k = 0; k < JP; k += 4)
-        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(t[(r0 + li) * LDT + k + lq], zq[(k + lq) * LDT + c0 + li], acc, 0, 0, 0);
+    for (int k = 0; k < JP; k += 4) acc = mfma_f64(t[(r0 + li) * WLD + k + lq], zq[(k + lq) * WLD + c0 + li], acc);
+    const int bj = wave & 1 ? J : I;
+    int row = P * JP + r0, col = bj * JB;
     if (!on_v) {
         __syncthreads();                               // everybody is done with t: it becomes T Z_Q
 #pragma unroll
-        for (int r = 0; r < 4; ++r) t[(r0 + 4 * r + lq) * LDT + c0 + li] = acc[r];
+        for (int r = 0; r < 4; ++r) t[(r0 + 4 * r + lq) * WLD + c0 + li] = acc[r];
         __syncthreads();
         acc = (f64x4){0.0, 0.0, 0.0, 0.0};
+        const int bi = wave >> 1 ? M : K;
+        // the block, or its transpose where it is kept: the operands change places
+        const double* const a = bi < bj ? zp + r0 : t + c0;
+        const double* const b = bi < bj ? t + c0 : zp + r0;
 #pragma unroll
-        for (int k = 0; k < JP; k += 4)
-            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(zp[(k + lq) * LDT + r0 + li], t[(k + lq) * LDT + c0 + li], acc, 0, 0, 0);
+        for (int k = 0; k < JP; k += 4) acc = mfma_f64(a[(k + lq) * WLD + li], b[(k + lq) * WLD + li], acc);
+        row = min(bi, bj) * JB;
+        col = max(bi, bj) * JB;
     }
+    double* const dst = on_v ? w.V : w.B;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-        const int i = row_of(r0 + 4 * r + lq), j = pair_index(I, J, c0 + li);
-        if (i < m && j < m) M[(long)i * m + j] = acc[r];
+        const int i = row + 4 * r + lq, j = col + li;
+        if (i < w.m && j < w.m) dst[(long)i * w.m + j] = acc[r];
     }
 }
 
-__global__ __launch_bounds__(1024) void jw_rank_kernel(const double* __restrict__ A, int m, double* __restrict__ evals,
-                                                       int* __restrict__ rank, const WideState* st, int* info) {
+// grid: the pairs of `next`, if there is one, in a multiple of eight; if there is a `step`: its tiles of A on and above the diagonal in a
+// multiple of eight, then those of V, rows first, in a multiple of eight: workgroup ids 8 apart run on one XCD, whose L2 has a row
+// block of V from the step before.
+__global__ __launch_bounds__(256) void wide_step_kernel(WideStep w) {
+    __shared__ WideLds L;
+    if (w.st->done) return;
+    const int pairs = w.nbp / 2, tid = threadIdx.x;
+    int at = blockIdx.x;
+    if (w.next >= 0) {
+        if (at < pairs) wide_pair(w, L, at, tid);
+        at -= eights(pairs);
+        if (at < 0) return;
+    }
+    const int upper_tiles = pairs * (pairs + 1) / 2;
+    if (at < upper_tiles) {
+        int P = (int)((sqrtf(8.0f * at + 1.0f) - 1.0f) * 0.5f);         // tile (Q, P) of the lower triangle, row by row
+        while (P * (P + 1) / 2 > at) --P;
+        while ((P + 1) * (P + 2) / 2 <= at) ++P;
+        wide_tile(w, L, at - P * (P + 1) / 2, P, false, tid);
+        return;
+    }
+    at -= eights(upper_tiles);
+    const int rows = eights((w.m + JP - 1) / JP);
+    if (at >= 0 && at % rows * JP < w.m) wide_tile(w, L, at % rows, at / rows, true, tid);
+}
+
+__global__ __launch_bounds__(1024) void jw_rank_kernel(const double* __restrict__ even, const double* __restrict__ odd, int last, int m,
+                                                       double* __restrict__ evals, int* __restrict__ rank, const WideState* st, int* info) {
     __shared__ double diag[EIG_MAX_M];
+    const double* A = (st->done ? st->at : last) & 1 ? odd : even;     // the matrix after that many sweeps
     for (int i = threadIdx.x; i < m; i += 1024) diag[i] = A[(long)i * m + i];
     __syncthreads();
     for (int i = threadIdx.x; i < m; i += 1024) {
@@ -1109,44 +1249,55 @@ static size_t jacobi_extra_bytes(int m) {
 }
 size_t jacobi_work_bytes(int batch, int m) { return (size_t)batch * m * m * sizeof(double) + jacobi_extra_bytes(m); }
 
-static hipError_t launch_jacobi_wide(double* A, double* evals, double* V, void* extra, int* info, int m, int max_sweeps, hipStream_t s) {
+static hipError_t launch_jacobi_wide(double* A, double* evals, double* V, void* extra, int* info, int m, int max_sweeps,
+                                     const JacobiSpare& spare, hipStream_t s) {
     const int nb = (m + JB - 1) / JB, nbp = nb + (nb & 1), pairs = nbp / 2;
+    const size_t each = (size_t)pairs * JP * JP;
     double* Z = static_cast<double*>(extra);
-    double* part = Z + (size_t)pairs * JP * JP;
+    double* part = Z + each;
     int* rank = reinterpret_cast<int*>(part + 2 * JB_NORM_WGS);
     WideState* st = reinterpret_cast<WideState*>(rank + EIG_MAX_M);
     hipError_t e;
     jw_init_kernel<<<grid_for((long)m * m), 256, 0, s>>>(V, m, st);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    // tiles of A (pairs x pairs) and of V (32 rows x pairs) in one grid
-    const dim3 tiles(pairs, std::max(pairs, (m + JP - 1) / JP), 2);
+    const int tiles = eights(pairs * (pairs + 1) / 2) + eights((m + JP - 1) / JP) * pairs, steps = nbp - 1;
+    const bool two = spare.matrix && spare.doubles >= 3 * each;
+    double* const mat[2] = {A, two ? spare.matrix : A};
+    double* const Zs[2] = {Z, two ? spare.rest : Z};
+    double* const Ds[2] = {two ? spare.rest + each : nullptr, two ? spare.rest + 2 * each : nullptr};
+    // (a sweep has an odd number of steps: after `sweep` of them the matrix lies in mat[sweep & 1]; step n is the n-th of all)
     for (int sweep = 0; sweep <= max_sweeps; ++sweep) {
-        jw_partial_norm_kernel<<<JB_NORM_WGS, 256, 0, s>>>(A, m, part, st);
+        jw_partial_norm_kernel<<<JB_NORM_WGS, 256, 0, s>>>(mat[sweep & 1], m, part, st);
         jw_norm_kernel<<<1, 64, 0, s>>>(part, sweep, st);
         if ((e = hipGetLastError()) != hipSuccess) return e;
         if (sweep == max_sweeps) break;
-        for (int step = 0; step < nbp - 1; ++step) {
-            jb_pair_kernel<<<pairs, 256, 0, s>>>(A, Z, m, nbp, step, st);
-            jb_update_kernel<<<tiles, 256, 0, s>>>(A, V, Z, m, nbp, step, st);
+        for (int step = 0; step < steps; ++step) {
+            const int x = (sweep + step) & 1;          // parity of n
+            if (!two || (sweep == 0 && step == 0))
+                wide_step_kernel<<<pairs, 256, 0, s>>>(WideStep{mat[x], mat[x], V, nullptr, nullptr, Zs[x], Ds[x], m, nbp, -1, step, st});
+            const bool last = sweep + 1 == max_sweeps && step + 1 == steps;
+            const int next = !two || last ? -1 : step + 1 < steps ? step + 1 : 0;
+            wide_step_kernel<<<tiles + (next < 0 ? 0 : eights(pairs)), 256, 0, s>>>(
+                WideStep{mat[x], mat[x ^ 1], V, Zs[x], Ds[x], Zs[x ^ 1], Ds[x ^ 1], m, nbp, step, next, st});
         }
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
-    jw_rank_kernel<<<1, 1024, 0, s>>>(A, m, evals, rank, st, info);
+    jw_rank_kernel<<<1, 1024, 0, s>>>(mat[0], mat[1], max_sweeps, m, evals, rank, st, info);
     jw_permute_kernel<<<grid_for((long)m * m), 256, 0, s>>>(A, V, rank, m);
     return hipGetLastError();
 }
 
-hipError_t launch_jacobi(double* A, double* evals, double* work, int* info, int batch, int m, int max_sweeps, hipStream_t s) {
+hipError_t launch_jacobi(double* A, double* evals, double* work, int* info, int batch, int m, int max_sweeps, hipStream_t s, const JacobiSpare& spare) {
     if (m > 128) {                                     // large matrices: the whole chip works on one at a time
         void* extra = work + (size_t)batch * m * m;
-        // every sweep enqueued costs its launches even after convergence (order 768: 0.24 ms).  Single rotations over the whole
+        // every sweep enqueued costs its launches even after convergence.  Single rotations over the whole
         // matrix took up to 16 where they converged; sweeps over pairs of blocks take as many or fewer on full, graded and
         // nearly diagonal spectra, but up to 7 more on low ranks and multiple eigenvalues (rank 40 or 100 of 256: 12 and 17 to 20;
         // three eigenvalues 85 times each: 24 or 25)
         const int sweeps = std::min(max_sweeps, 26);
         for (int b = 0; b < batch; ++b) {
             hipError_t e = launch_jacobi_wide(A + (size_t)b * m * m, evals + (size_t)b * m, work + (size_t)b * m * m,
-                                              extra, info + b, m, sweeps, s);
+                                              extra, info + b, m, sweeps, spare, s);
             if (e != hipSuccess) return e;
         }
         return hipSuccess;

@@ -396,6 +396,25 @@ def test_sym_eig_low_rank_and_multiple_eigenvalues_converge(mla, kind, m):
         assert np.abs(ritz.cpu().numpy()[:10] - np.linalg.eigvalsh(A[0])[::-1][:10]).max() <= 1e-10 * np.linalg.norm(A[0])
 
 
+@pytest.mark.parametrize("m", [129, 143, 144, 145, 161, 176, 177, 300])
+def test_ritz_matrix_block_edges(mla, m):
+    """The solver with a second matrix of scratch (Rayleigh-Ritz matrices above order 128): a block as wide as the space, so that
+    the matrix is S in another basis.  Odd and even numbers of blocks of 16, a last one of one row and a full one; the bounds
+    of the eigensolver by itself."""
+    import torch
+    from paper_2502_07864_amd import convert
+    r = np.random.default_rng(m)
+    S = r.standard_normal((m, m))
+    S = S + S.T
+    evals, R, info = convert.top_eig(torch.from_numpy(S).cuda(), torch.from_numpy(r.standard_normal((m, m))).cuda(), m, 0)
+    evals, R = evals.cpu().numpy(), R.cpu().numpy()
+    norm = np.linalg.norm(S)
+    assert info[0].item() == 0 and info[1].item() >= 1
+    assert np.abs(evals - np.linalg.eigvalsh(S)[::-1]).max() <= 1e-12 * norm
+    assert np.abs(R.T @ R - np.eye(m)).max() <= 1e-12
+    assert np.abs(S @ R - R * evals).max() <= 1e-12 * norm
+
+
 # ------------------------------------------------------------------ cache append
 
 @pytest.mark.parametrize("B,D,d_c,cache", [(1, 32, 16, "bf16"), (15, 96, 512, "bf16"), (16, 4096, 512, "f32"),
