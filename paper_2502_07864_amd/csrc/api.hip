@@ -127,6 +127,7 @@ int decode_launch(const DecodeCall& c, void* workspace)
     p.chunk_pages = (c.max_pages_per_seq + S - 1) / S;
     p.q_len = c.q_len; p.heads = c.heads;
     p.q_inner = 1; p.o_final = nullptr; p.lse_final = nullptr;
+    p.rope_kv = nullptr; p.rope_pitch = 0;
     p.scale = c.softmax_scale;
 
     const bool balanced = (c.flags & MLA_FLAG_BALANCED) != 0;
@@ -383,20 +384,20 @@ int mla_prefill_mha(const void* q_nope, const void* q_rope, const void* W_UK, co
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     char* ws = static_cast<char*>(workspace);
     void* pool2 = ws + wl.pool_off;
-    int32_t* table2 = reinterpret_cast<int32_t*>(ws + wl.table_off);
     int32_t* lens2 = reinterpret_cast<int32_t*>(ws + wl.lens_off);
-    hipError_t e = launch_prefill_materialise(kv_cache, page_table, seq_lens, W_UK, W_UV, ws, pool2, table2, lens2,
+    hipError_t e = launch_prefill_materialise(kv_cache, page_table, seq_lens, W_UK, W_UV, ws, pool2, lens2,
                                               B, q_len, heads, d_c, num_pages, max_pages_per_seq, stream);
     if (e != hipSuccess) return MLA_ERR_HIP;
     // the attention: every (sequence, head) pair is a sequence of q_len query rows over its own rows
     DecodeParams p;
     p.q_abs = q_nope; p.q_rope = q_rope; p.kv = pool2; p.kv_scale = nullptr;
-    p.page_table = table2; p.seq_lens = lens2;
+    p.page_table = page_table; p.seq_lens = lens2;
     p.o_part = nullptr; p.lse_part = nullptr; p.plan = nullptr;
     p.B = (int)pseudo; p.H = q_len; p.d_c = d_head; p.d_rope = d_rope; p.page_size = page_size;
-    p.num_pages = (int)(pseudo * max_pages_per_seq); p.max_pages = max_pages_per_seq;
+    p.num_pages = num_pages; p.max_pages = max_pages_per_seq;
     p.num_splits = 1; p.chunk_pages = max_pages_per_seq;
     p.q_len = q_len; p.heads = 1; p.q_inner = heads; p.o_final = out; p.lse_final = lse;
+    p.rope_kv = static_cast<const uint16_t*>(kv_cache) + d_c; p.rope_pitch = (d_c + d_rope) * 2;
     p.scale = softmax_scale;
     e = launch_prefill_attention(p, stream);
     return e == hipSuccess ? MLA_OK : MLA_ERR_HIP;

@@ -4,7 +4,8 @@
 // and the prompt's tokens attend causally to them.  This file holds the kernels that build the materialised keys and
 // values (one with a head's weights in LDS, one that streams them, and the one that lays them out for it); the attention
 // itself runs on prefill_attention.hip's kernel, for which one (sequence, head) pair is a sequence of its own, and whose page
-// layout (64 keys of 192 values, then the values transposed, both in the order its reads want) is described there.
+// layout (64 keys of 128 values, then the values transposed, both in the order its reads want) is described there.  The rope part of
+// the keys, the same for every head, stays in the cache.
 //
 //   Y^T [256 x tokens] = [W^{UK}_h ; (W^{UV}_h)^T] [256 x d_c] . C^T [d_c x tokens]
 //
@@ -24,8 +25,7 @@ namespace {
 typedef __attribute__((ext_vector_type(8))) short s16x8;
 
 constexpr int PF_DH = 128;      // head dimension
-constexpr int PF_KEY = 192;     // values per key: 128 + 64
-constexpr int PF_PAGE = 64 * (PF_KEY + PF_DH);    // values per materialised page: 64 keys, then the values transposed
+constexpr int PF_PAGE = 64 * 2 * PF_DH;           // values per materialised page: 64 keys, then the values transposed
 
 // Weights in LDS: row r (a dimension of the keys or of the values) of d_c values, its 16-byte piece c at position c ^ (r & 15):
 // the 16 lanes that share a cycle of an operand read meet 16 different units.  The values' weights are stored k-major by the caller
@@ -39,7 +39,7 @@ template <int D_C> constexpr int PM_WAVES = 4096 / D_C;            // wavefronts
 template <int D_C>
 __global__ __launch_bounds__(PM_WAVES<D_C> * 64, PM_WAVES<D_C> / 4) void prefill_materialise_kernel(const uint16_t* kv, const int32_t* page_table,
                                                                                const int32_t* seq_lens, const uint16_t* W_UK, const uint16_t* W_UV,
-                                                                               uint16_t* pool2, int32_t* table2, int32_t* lens2,
+                                                                               uint16_t* pool2, int32_t* lens2,
                                                                                int B, int heads, int num_pages, int max_pages, bool by_page)
 {
     constexpr int ROW = D_C + 64;
@@ -154,11 +154,10 @@ __global__ __launch_bounds__(PM_WAVES<D_C> * 64, PM_WAVES<D_C> / 4) void prefill
         const int pg = (((L + 63) >> 6) * 2 - left) >> 1, tok0 = (left & 1) * 32;         // page, and this wavefront's first token inside it
         const int page = ((const CONST_AS int32_t*)(page_table + (size_t)b * max_pages))[pg];
         const bool active = page >= 0 && page < num_pages;
-        // the pseudo-sequence (b, h) owns pages [bh * max_pages, +max_pages) of the materialised pool; a page id
-        // outside the cache pool is passed on as "skip these tokens" (-1), and its page, like the tokens past the
-        // sequence's end, gets zeros for values: what the skipped weights (zeros) are multiplied with
+        // the pseudo-sequence (b, h) owns pages [bh * max_pages, +max_pages) of the materialised pool; the page of an id
+        // outside the cache pool, like the tokens past the sequence's end, gets zeros for values: what the weights of tokens
+        // that the attention skips (zeros) are multiplied with
         const size_t page2 = ((size_t)b * heads + h) * max_pages + pg;
-        if (keys && tok0 == 0 && lane == 0) table2[page2] = active ? (int32_t)page2 : -1;
         const uint16_t* src = kv + (size_t)(active ? page : 0) * 64 * ROW;
         uint16_t* dst = pool2 + page2 * PF_PAGE;
 
@@ -169,16 +168,6 @@ __global__ __launch_bounds__(PM_WAVES<D_C> * 64, PM_WAVES<D_C> / 4) void prefill
 #pragma unroll
             for (int ks = 0; ks < NKS; ++ks)
                 cb[nt][ks] = *reinterpret_cast<const bf16x8*>(src + (tok0 + nt * 16 + n) * ROW + ks * 32 + g * 8);
-        if (keys) {
-            // decoupled-rope part of the key: copied as it is (16 NT tokens x 8 pieces)
-            u32x4 rope[2 * NT];
-#pragma unroll
-            for (int i = 0; i < 2 * NT; ++i)
-                rope[i] = *reinterpret_cast<const u32x4*>(src + (tok0 + i * 8 + (lane >> 3)) * ROW + D_C + (lane & 7) * 8);
-#pragma unroll
-            for (int i = 0; i < 2 * NT; ++i)
-                *reinterpret_cast<u32x4*>(dst + (tok0 + i * 8 + (lane >> 3)) * PF_KEY + PF_DH + (lane & 7) * 8) = rope[i];
-        }
         if (!active || pg * 64 + tok0 + NT * 16 > L) {
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt) {
@@ -225,7 +214,7 @@ __global__ __launch_bounds__(PM_WAVES<D_C> * 64, PM_WAVES<D_C> / 4) void prefill
                 // 32 dimensions of the tokens: position 8g + 4 ml + i of the 32 is dimension 16 ml + 4g + i
 #pragma unroll
                 for (int nt = 0; nt < NT; ++nt)
-                    *reinterpret_cast<u32x4*>(dst + (tok0 + nt * 16 + n) * PF_KEY + c * 32 + g * 8) = pack8(acc[0][nt], acc[1][nt]);
+                    *reinterpret_cast<u32x4*>(dst + (tok0 + nt * 16 + n) * PF_DH + c * 32 + g * 8) = pack8(acc[0][nt], acc[1][nt]);
             }
         }
         if (values) {
@@ -236,7 +225,7 @@ __global__ __launch_bounds__(PM_WAVES<D_C> * 64, PM_WAVES<D_C> / 4) void prefill
                 for (int ml = 0; ml < 2; ++ml)
 #pragma unroll
                     for (int nt = 0; nt < NT; nt += 2)
-                        *reinterpret_cast<u32x4*>(dst + 64 * PF_KEY + (tok0 + nt * 16) * PF_DH + (c * 2 + ml) * 512 + lane * 8) =
+                        *reinterpret_cast<u32x4*>(dst + 64 * PF_DH + (tok0 + nt * 16) * PF_DH + (c * 2 + ml) * 512 + lane * 8) =
                             pack8(acc[ml][nt], acc[ml][nt + 1]);
             }
         }
@@ -275,7 +264,7 @@ __global__ __launch_bounds__(256) void prefill_weights_kernel(const uint16_t* W_
 template <int D_C>
 __global__ __launch_bounds__(256, 2) void prefill_stream_kernel(const uint16_t* kv, const int32_t* page_table,
                                                                      const int32_t* seq_lens, const uint16_t* Wcat,
-                                                                     uint16_t* pool2, int32_t* table2, int32_t* lens2,
+                                                                     uint16_t* pool2, int32_t* lens2,
                                                                      int heads, int num_pages, int max_pages)
 {
     constexpr int ROW = D_C + 64;
@@ -306,11 +295,10 @@ __global__ __launch_bounds__(256, 2) void prefill_stream_kernel(const uint16_t* 
     const bool in_seq = pg < max_pages && pg * 64 < L;
     const int page = in_seq ? ((const CONST_AS int32_t*)(page_table + (size_t)b * max_pages))[pg] : -1;
     const bool active = in_seq && page >= 0 && page < num_pages;
-    // the pseudo-sequence (b, h) owns pages [bh * max_pages, +max_pages) of the materialised pool; a page id
-    // outside the cache pool is passed on as "skip these tokens" (-1), and its page, like the tokens past the
-    // sequence's end, gets zeros for values: what the skipped weights (zeros) are multiplied with
+    // the pseudo-sequence (b, h) owns pages [bh * max_pages, +max_pages) of the materialised pool; the page of an id
+    // outside the cache pool, like the tokens past the sequence's end, gets zeros for values: what the weights of tokens
+    // that the attention skips (zeros) are multiplied with
     const size_t page2 = (size_t)bh * max_pages + pg;
-    if (in_seq && (wave & 1) == 0 && lane == 0) table2[page2] = active ? (int32_t)page2 : -1;
     const uint16_t* src = kv + (size_t)(active ? page : 0) * 64 * ROW;
     uint16_t* dst = pool2 + (in_seq ? page2 : 0) * PF_PAGE;
     const int tok0 = (wave & 1) * 32;                 // this wavefront's first token inside its page
@@ -338,24 +326,16 @@ __global__ __launch_bounds__(256, 2) void prefill_stream_kernel(const uint16_t* 
     uint32_t a_base[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) a_base[e] = (uint32_t)(n * WROWB + (((4 * e + g) ^ n) << 4));
-    // Everything a workgroup reads before its first product is requested at once: a chunk of weights, the decoupled-rope part of
-    // its keys (32 tokens x 8 pieces per wavefront, copied as it is) and the latent rows.
+    // Everything a workgroup reads before its first product is requested at once: a chunk of weights and the latent rows.
     load_chunk(0);
     bf16x8 cb[2][NKS];
     if (in_seq) {
-        u32x4 rope[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-            rope[i] = *reinterpret_cast<const u32x4*>(src + (tok0 + i * 8 + (lane >> 3)) * ROW + D_C + (lane & 7) * 8);
         // B operands: latent rows of tokens tok0 + 16 nt + n, k = 32 ks + 8g .. + 7
 #pragma unroll
         for (int nt = 0; nt < 2; ++nt)
 #pragma unroll
             for (int ks = 0; ks < NKS; ++ks)
                 cb[nt][ks] = *reinterpret_cast<const bf16x8*>(src + (tok0 + nt * 16 + n) * ROW + ks * 32 + g * 8);
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-            *reinterpret_cast<u32x4*>(dst + (tok0 + i * 8 + (lane >> 3)) * PF_KEY + PF_DH + (lane & 7) * 8) = rope[i];
         if (!active || pg * 64 + tok0 + 32 > L) {
 #pragma unroll
             for (int nt = 0; nt < 2; ++nt) {
@@ -411,11 +391,11 @@ __global__ __launch_bounds__(256, 2) void prefill_stream_kernel(const uint16_t* 
                 // 32 dimensions of 32 tokens: position 8g + 4 ml + i of the 32 is dimension 16 ml + 4g + i
 #pragma unroll
                 for (int nt = 0; nt < 2; ++nt)
-                    *reinterpret_cast<u32x4*>(dst + (tok0 + nt * 16 + n) * PF_KEY + c * 32 + g * 8) = pack8(acc[0][nt], acc[1][nt]);
+                    *reinterpret_cast<u32x4*>(dst + (tok0 + nt * 16 + n) * PF_DH + c * 32 + g * 8) = pack8(acc[0][nt], acc[1][nt]);
             } else {
                 product(std::false_type{});
                 // 32 tokens (this wavefront's half page) of 32 dimensions: key 4 nt + i of group g is token 16 nt + 4g + i
-                uint16_t* half = dst + 64 * PF_KEY + tok0 * PF_DH;
+                uint16_t* half = dst + 64 * PF_DH + tok0 * PF_DH;
 #pragma unroll
                 for (int ml = 0; ml < 2; ++ml)
                     *reinterpret_cast<u32x4*>(half + ((c - NCHUNK / 2) * 2 + ml) * 512 + lane * 8) = pack8(acc[ml][0], acc[ml][1]);
@@ -433,8 +413,7 @@ bool prefill_supported(int d_head, int d_c, int d_rope, int page_size, mla_dtype
 }
 
 hipError_t launch_prefill_materialise(const void* kv, const int32_t* page_table, const int32_t* seq_lens,
-                                      const void* W_UK, const void* W_UV, void* Wcat, void* pool2, int32_t* table2,
-                                      int32_t* lens2, int B, int q_len, int heads, int d_c, int num_pages, int max_pages,
+                                      const void* W_UK, const void* W_UV, void* Wcat, void* pool2, int32_t* lens2, int B, int q_len, int heads, int d_c, int num_pages, int max_pages,
                                       hipStream_t s)
 {
     const uint16_t *rows = static_cast<const uint16_t*>(kv), *uk = static_cast<const uint16_t*>(W_UK), *uv = static_cast<const uint16_t*>(W_UV);
@@ -462,8 +441,8 @@ hipError_t launch_prefill_materialise(const void* kv, const int32_t* page_table,
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
         const dim3 grid((max_pages + 1) / 2, B * heads);
-        if (d_c == 512) prefill_stream_kernel<512><<<grid, 256, 0, s>>>(rows, page_table, seq_lens, cat, pool, table2, lens2, heads, num_pages, max_pages);
-        else            prefill_stream_kernel<256><<<grid, 256, 0, s>>>(rows, page_table, seq_lens, cat, pool, table2, lens2, heads, num_pages, max_pages);
+        if (d_c == 512) prefill_stream_kernel<512><<<grid, 256, 0, s>>>(rows, page_table, seq_lens, cat, pool, lens2, heads, num_pages, max_pages);
+        else            prefill_stream_kernel<256><<<grid, 256, 0, s>>>(rows, page_table, seq_lens, cat, pool, lens2, heads, num_pages, max_pages);
         return hipGetLastError();
     }
     // One workgroup per CU (its weights fill the LDS), the same number for every head: of one to eight rounds of them the number
@@ -487,8 +466,8 @@ hipError_t launch_prefill_materialise(const void* kv, const int32_t* page_table,
     // (752) 1002 / 1024.  Not multiples of eight: 28 heads by page 84 -> 91, 4000 x 4 200 -> 201.
     const bool by_page = d_c == 256 && heads % 8 == 0 && heads <= 32 && pages > std::max(160, 6 * heads);
     const dim3 grid = by_page ? dim3(per, kinds) : dim3(kinds, per);
-    if (d_c == 512) prefill_materialise_kernel<512><<<grid, PM_WAVES<512> * 64, 0, s>>>(rows, page_table, seq_lens, uk, uv, pool, table2, lens2, B, heads, num_pages, max_pages, by_page);
-    else            prefill_materialise_kernel<256><<<grid, PM_WAVES<256> * 64, 0, s>>>(rows, page_table, seq_lens, uk, uv, pool, table2, lens2, B, heads, num_pages, max_pages, by_page);
+    if (d_c == 512) prefill_materialise_kernel<512><<<grid, PM_WAVES<512> * 64, 0, s>>>(rows, page_table, seq_lens, uk, uv, pool, lens2, B, heads, num_pages, max_pages, by_page);
+    else            prefill_materialise_kernel<256><<<grid, PM_WAVES<256> * 64, 0, s>>>(rows, page_table, seq_lens, uk, uv, pool, lens2, B, heads, num_pages, max_pages, by_page);
     return hipGetLastError();
 }
 

@@ -5,9 +5,11 @@
 //     S^T [keys x queries]  = K [keys x 192] . Q^T [192 x queries]
 //     O^T [128 x queries]  += V^T [128 x keys] . P^T [keys x queries]
 //
-// A page of 64 keys is 40 KB: the keys [k = W^{UK}_h c_j ; k^R_j] as 64 rows of 192 bf16 values, then the
-// values TRANSPOSED, [half page][16-dimension tile][4 groups of 8 keys][16 dimensions][8 keys].  Both orders are made for the reads of this
-// kernel (the kernel that writes them has the choice for free): inside each 32 of the first 128 key
+// A page of 64 keys is 32 KB: the per-head part of the keys, W^{UK}_h c_j, as 64 rows of 128 bf16 values, then the
+// values TRANSPOSED, [half page][16-dimension tile][4 groups of 8 keys][16 dimensions][8 keys].  The decoupled-rope part k^R_j, which all
+// heads share, is read from the cache itself (copied to every head it was a fifth of what is written and read: 8 x 500 tokens on
+// 700 .. 6000 rows, 28 heads, d_c = 256 ROPEUS us).  Both orders are made for the reads of this
+// kernel (the kernel that writes them has the choice for free): inside each 32 of the 128 key
 // dimensions position 8g + 4m + i holds dimension 16m + 4g + i (the queries are loaded alike), and
 // key j of group g of a half page is its key 4g + j (j < 4) or 16 + 4g + j - 4, which is how the
 // exponentiated scores of two 16-key blocks lie in the registers after the first contraction.  So the
@@ -37,24 +39,24 @@
 namespace mla {
 namespace {
 
-constexpr int PA_DK = 192;                  // values per key
+constexpr int PA_DK = 128;                  // values per materialised key
+constexpr int PA_DR = 64;                   // and of its rope part
 constexpr int PA_DV = 128;                  // dimensions of a value
 constexpr int PA_ROWS = 128;                // query rows per workgroup
 
-template <int NBUF, int WPE>
-__global__ __launch_bounds__(MF_THREADS, WPE) void prefill_attention_kernel(DecodeParams p)
+__global__ __launch_bounds__(MF_THREADS, 2) void prefill_attention_kernel(DecodeParams p)
 {
-    constexpr int ROWB = PA_DK * 2;             // 384 bytes per key: 32 banks mod 64, as the decode tiles
-    constexpr int CPR = ROWB / 16;              // 24 chunks of 16 bytes
-    constexpr int K_B = TILE_ROWS * ROWB;       // 12288: a tile's keys
+    constexpr int ROWB = PA_DK * 2, ROPEB = PA_DR * 2;            // 256 and 128 bytes per key
+    constexpr int K_B = TILE_ROWS * ROWB;       // 8192: a tile's keys
+    constexpr int R_B = TILE_ROWS * ROPEB;      // 4096: their rope part
     constexpr int V_B = TILE_ROWS * PA_DV * 2;  // 8192: its values
-    constexpr int TILE_B = K_B + V_B;
-    constexpr int PAGE_B = 2 * TILE_B;
-    constexpr int NLK = K_B / (MF_THREADS * 16), NLV = V_B / (MF_THREADS * 16);   // loads per thread: 3 and 2
-    constexpr int NKS = PA_DK / 32;             // 6 k-steps of the score contraction
+    constexpr int PAGE_B = 2 * (K_B + V_B);     // of the pool
+    constexpr int SLOT_B = PAGE_B + 2 * R_B;    // of the LDS
+    constexpr int NLK = K_B / (MF_THREADS * 16), NLV = 2 * V_B / (MF_THREADS * 16);   // loads per thread: a tile's keys 2 (and rope 1), a page's values 4
+    constexpr int NKS = (PA_DK + PA_DR) / 32;   // 6 k-steps of the score contraction: 4 and 2
     constexpr int NCT = PA_DV / 16;             // 8 row tiles of the value contraction
 
-    __shared__ __attribute__((aligned(1024))) unsigned char smem[NBUF * TILE_B];
+    __shared__ __attribute__((aligned(1024))) unsigned char smem[2 * SLOT_B];
     LDS_AS unsigned char* lds = (LDS_AS unsigned char*)smem;
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -90,7 +92,7 @@ __global__ __launch_bounds__(MF_THREADS, WPE) void prefill_attention_kernel(Deco
     const size_t io_base = (size_t)(b / p.q_inner) * p.H * p.q_inner + (size_t)(b % p.q_inner);
     auto io_row = [&](int h) -> size_t { return io_base + (size_t)h * p.q_inner; };
 
-    const CONST_AS int32_t* ptab = (const CONST_AS int32_t*)(p.page_table + (size_t)b * p.max_pages);
+    const int32_t* const ptab = p.page_table + (size_t)(b / p.q_inner) * p.max_pages;      // pages of the cache
     const int L = __builtin_amdgcn_readfirstlane(max(0, min(p.seq_lens[b], p.max_pages * 64)));
 
     // ---- this wave's 32 query rows -> registers (B operands of the score contraction)
@@ -138,64 +140,91 @@ __global__ __launch_bounds__(MF_THREADS, WPE) void prefill_attention_kernel(Deco
     // first key that some query row of this workgroup must not see (its first row sees the least)
     const int causal_from = visible(hb);
 
-    // ---- staging: direct-to-LDS 128-bit loads.  What a step of the sweep needs is the values of tile t and
-    // the keys of tile t + 1 (its scores are made while tile t is accumulated): that is one unit, in ring slot
-    // (t + 1) % NBUF; unit -1 is the keys of the first tile.
-    const uint32_t lds_base = (uint32_t)(uintptr_t)lds;
-    uint32_t koff[NLK];
-#pragma unroll
-    for (int k = 0; k < NLK; ++k) {             // keys: chunk swizzle as in the decode kernels
-        const int P = (k * 4 + wave) * 64 + lane;
-        const int r = P / CPR, pc = P % CPR;
-        koff[k] = (uint32_t)(r * ROWB + ((pc ^ swz_key(r)) << 4));
-    }
-    const uint32_t voff = (uint32_t)(lane * 16);    // values: as they lie
-    const unsigned char* pool = static_cast<const unsigned char*>(p.kv) + (size_t)b * p.max_pages * PAGE_B;
-    auto load16 = [&](const unsigned char* base, uint32_t off, uint32_t dst) {   // (base and dst are uniform)
-        const uint32_t m0v = __builtin_amdgcn_readfirstlane(dst);
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-                     :: "s"(m0v), "v"(off), "s"(base) : "memory");
-    };
-    auto slot_of = [&](int u) { return (uint32_t)(((u + 1) % NBUF) * TILE_B); };
-    // returns the number of loads this thread issued (uniform)
-    auto fetch_unit = [&](int u) -> int {
-        int n_issued = 0;
-        const uint32_t dst = lds_base + slot_of(u) + (uint32_t)(wave * 1024);
-        if (u + 1 < t1) {
-            const unsigned char* src = pool + (size_t)((u + 1) >> 1) * PAGE_B + ((u + 1) & 1) * K_B;
-#pragma unroll
-            for (int k = 0; k < NLK; ++k) load16(src, koff[k], dst + k * 4096);
-            n_issued = NLK;
-        }
-        if (u >= 0 && u < t1) {
-            const unsigned char* src = pool + (size_t)(u >> 1) * PAGE_B + 2 * K_B + (u & 1) * V_B + wave * 1024;
-#pragma unroll
-            for (int k = 0; k < NLV; ++k) load16(src + k * 4096, voff, dst + K_B + k * 4096);
-            n_issued += NLV;
-        }
-        return n_issued;
-    };
-    int younger = 0;            // loads issued for the unit after the one the next step needs
-    // unit u is there, for everybody, and everybody is done with the step before: its slot receives unit u + 2
-    auto stage = [&](int u) {
-        if (younger >= NLK + NLV) wait_vmcnt<NLK + NLV>();
-        else if (younger >= NLK)  wait_vmcnt<NLK>();
-        else if (younger >= NLV)  wait_vmcnt<NLV>();
-        else                      wait_vmcnt<0>();
-        __syncthreads();
-        younger = fetch_unit(u + 2);
-    };
-    static_assert(NBUF == 3 && NLK == 3 && NLV == 2, "a step's unit, the next one, and the one being requested");
-    auto start = [&]() {
-        fetch_unit(-1);
-        younger = fetch_unit(0);
-        stage(-1);
-    };
-    // keys of tile t that are there: a page the cache did not have is in place (its values are zeros) and no
-    // query sees it
-    auto rows_valid = [&](int t) { return ptab[t >> 1] >= 0 ? min(TILE_ROWS, row1 - t * TILE_ROWS) : 0; };
+    // Page ids, 64 at a time, a lane each (asked for beside the queries; a scalar load in every step was a wait in every step), and
+    // whether all pages are there.  Of a page the cache does not have the values are zeros, and no query sees its keys.
+    const int pages = (t1 + 1) / 2;
+    auto ids_from = [&](int u) { return u + lane < pages ? ptab[u + lane] : 0; };
+    const int32_t first_ids = ids_from(0), more_ids[3] = {ids_from(64), ids_from(128), ids_from(192)};
+    auto missing = [&](int32_t id) { return (uint32_t)id >= (uint32_t)p.num_pages; };
+    auto usable = [&](int32_t id) { return missing(id) ? 0 : id; };
 
+    // ---- staging: direct-to-LDS 128-bit loads.  A step of the sweep needs the values of tile t and the keys of tile t + 1 (its
+    // scores are made while tile t is accumulated).  Unit u is what the steps 2 u and 2 u + 1 need: the keys of tile 2 u + 1, the
+    // values of both tiles of page u, the keys of tile 2 u + 2, which lie in this order in memory, from 8 KB behind the
+    // page's start on, and the rope parts of both.  Two slots; one barrier a unit, which says that unit u is there and unit u - 1 is
+    // done with.  The keys of the first tile come where they would lie in unit -1.
+    const uint32_t lds_base = (uint32_t)(uintptr_t)lds;
+    constexpr int K1 = 0, V0 = K_B, V1 = K_B + V_B, K2 = K_B + 2 * V_B, R1 = PAGE_B, R2 = PAGE_B + R_B;      // places in a slot
+    // Chunk swizzles: 16 bytes c of key row r at position c ^ (r & 15), of its rope part at c ^ (r >> 1 & 7): the 16 lanes that share a
+    // cycle of a score read meet 16 different units.
+    const int P = wave * 64 + lane;
+    uint32_t koff[NLK], voff[NLV];
+#pragma unroll
+    for (int k = 0; k < NLK; ++k) koff[k] = (uint32_t)((P >> 4) * ROWB + (((P & 15) ^ (P >> 4)) << 4) + k * 4096);     // (16 rows, alike)
+#pragma unroll
+    for (int k = 0; k < NLV; ++k) voff[k] = (uint32_t)(P * 16 + V0 + k * 4096);      // values: as they lie
+    const uint32_t roff = (uint32_t)((P >> 3) * p.rope_pitch + (((P & 7) ^ (P >> 4 & 7)) << 4));
+    const unsigned char* pool = static_cast<const unsigned char*>(p.kv) + (size_t)b * p.max_pages * PAGE_B;
+    auto load16 = [&](const unsigned char* base, uint32_t off, uint32_t dst, auto at) {   // (base and dst are uniform)
+        asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+                     :: "s"(dst), "v"(off), "s"(base), "i"(decltype(at)::value) : "memory", "scc");
+    };
+    auto fetch_keys = [&](const unsigned char* src, uint32_t dst, auto at) {
+        load16(src, koff[0], dst, at);
+        load16(src, koff[1], dst, std::integral_constant<int, decltype(at)::value + 4096>{});
+    };
+    static_assert(NLK == 2 && NLV == 4);
+    auto values_to = [&](const unsigned char* src, uint32_t dst) {
+        load16(src, voff[0], dst, std::integral_constant<int, V0>{});
+        load16(src, voff[1], dst, std::integral_constant<int, V0 + 4096>{});
+        load16(src, voff[2], dst, std::integral_constant<int, V0 + 8192>{});
+        load16(src, voff[3], dst, std::integral_constant<int, V0 + 12288>{});
+    };
+    const uint32_t rope_page = 64u * (uint32_t)p.rope_pitch;          // bytes from page to page
+    int32_t ids;                                // ids of 64 pages
+    const unsigned char* rope;                  // rope parts of the page of the unit fetched next
+    auto rope_of = [&](int u) { return static_cast<const unsigned char*>(p.rope_kv) + (uint64_t)(uint32_t)__builtin_amdgcn_readlane(ids, u & 63) * rope_page; };
+    using AtK1 = std::integral_constant<int, K1>;
+    using AtK2 = std::integral_constant<int, K2>;
+    using AtR1 = std::integral_constant<int, R1>;
+    using AtR2 = std::integral_constant<int, R2>;
+    // unit u (2 u < t1): all of its page behind the first tile's keys (the second tile's, where they are not asked for, are there but
+    // never used), and the next page's first keys if there is one.  Returns the number of loads this thread issued (uniform).
+    auto fetch_unit = [&](int u) -> int {
+        const unsigned char* src = pool + (size_t)u * PAGE_B + K_B;
+        const uint32_t dst = __builtin_amdgcn_readfirstlane(lds_base + (uint32_t)((u & 1) * SLOT_B + wave * 1024));
+        fetch_keys(src, dst, AtK1{});
+        values_to(src, dst);
+        load16(rope + rope_page / 2, roff, dst, AtR1{});
+        if (2 * u + 2 >= t1) return NLK + NLV + 1;
+        fetch_keys(src + K2, dst, AtK2{});
+        if (((u + 1) & 63) == 0) {
+            ids = usable(ids_from(u + 1));
+            asm volatile("" : "+v"(ids));       // (waited for here: behind the branch everybody would, for everything)
+        }
+        rope = rope_of(u + 1);
+        load16(rope, roff, dst, AtR2{});
+        return 2 * NLK + NLV + 2;
+    };
+    // the first tile's keys are there
+    auto start = [&]() {
+        const uint32_t dst = __builtin_amdgcn_readfirstlane(lds_base + (uint32_t)(SLOT_B + wave * 1024));
+        fetch_keys(pool, dst, AtK2{});
+        rope = rope_of(0);
+        load16(rope, roff, dst, AtR2{});
+        if (fetch_unit(0) > NLK + NLV + 1) wait_vmcnt<2 * NLK + NLV + 2>();
+        else                               wait_vmcnt<NLK + NLV + 1>();
+        __syncthreads();
+    };
+    ids = usable(first_ids);
     start();
+    bool hole = missing(first_ids) || missing(more_ids[0]) || missing(more_ids[1]) || missing(more_ids[2]);
+    for (int u = 256; u < pages; u += 64) hole |= missing(ids_from(u));
+    const bool all_there = !__any(hole);
+    // keys of tile t that are there
+    auto rows_valid = [&](int t) { return all_there || !missing(((const CONST_AS int32_t*)ptab)[t >> 1]) ? min(TILE_ROWS, row1 - t * TILE_ROWS) : 0; };
+    // leading tiles that every query row of this workgroup sees whole
+    const int n_full = all_there ? max(0, min(causal_from, row1)) / TILE_ROWS : 0;
 
     // ---- per-lane state: this lane's queries = column n of the D tiles of the two groups
     float m_ref[2] = {-INFINITY, -INFINITY};   // reference of the exponentials (log2 units)
@@ -206,13 +235,13 @@ __global__ __launch_bounds__(MF_THREADS, WPE) void prefill_attention_kernel(Deco
     const float sc = fmaxf(fabsf(p.scale) * LOG2E, 1.17549435e-38f);
     const int my_row = wave * 32 + n;           // + 16 hi; local to the workgroup
 
-    // score A operand: key row 16 rb + n, chunk 4 ks + g
-    const uint32_t a_key = (uint32_t)swz_key(n);
-    uint32_t a_base[2];
+    // score A operand: key row 16 rb + n, chunk 4 ks + g (ks 4, 5: chunk 4 (ks - 4) + g of its rope part)
+    uint32_t a_base[NKS];
 #pragma unroll
-    for (int e = 0; e < 2; ++e) a_base[e] = (uint32_t)(n * ROWB) + ((((uint32_t)(4 * e + g)) ^ a_key) << 4);
+    for (int ks = 0; ks < NKS; ++ks)
+        a_base[ks] = ks < 4 ? (uint32_t)(n * ROWB + (((4 * ks + g) ^ n) << 4)) : (uint32_t)(n * ROPEB + (((4 * (ks - 4) + g) ^ (n >> 1)) << 4));
     // value A operand: dimension 16 ct + n, the eight keys of lane group g
-    const uint32_t v_base = (uint32_t)(K_B + lane * 16);
+    const uint32_t v_base = (uint32_t)(lane * 16);
     const bf16x8 ones = __builtin_bit_cast(bf16x8, (u32x4){0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u});
 
     typedef f32x4 Scores[2][2];     // [block of 16 keys][query group]: keys 16 rb + 4g + i of query n, unscaled
@@ -254,7 +283,7 @@ __global__ __launch_bounds__(MF_THREADS, WPE) void prefill_attention_kernel(Deco
     auto drop_late_values = [&](int t) {
         const int there = row1 - t * TILE_ROWS;
         for (int u = tid; u < V_B / 16; u += MF_THREADS) {
-            LDS_AS u32x4* at = (LDS_AS u32x4*)(lds + slot_of(t) + K_B + u * 16);
+            LDS_AS u32x4* at = (LDS_AS u32x4*)(lds + ((t >> 1) & 1) * SLOT_B + (t & 1 ? V1 : V0) + u * 16);
             const int first = 4 * ((u >> 4) & 3);        // key of the unit's first value; the fifth is 16 further on
             u32x4 v = *at;
 #pragma unroll
@@ -267,23 +296,25 @@ __global__ __launch_bounds__(MF_THREADS, WPE) void prefill_attention_kernel(Deco
         __syncthreads();
     };
     const bool late_values = row1 < L && row1 % TILE_ROWS != 0;
-    auto full_tile = [&](int t) { return (t + 1) * TILE_ROWS <= causal_from && rows_valid(t) == TILE_ROWS; };
 
     // ---- one step: S^T of the next tile (QK), the weights of this one from its scores x, the normaliser and the
     // values (PV).  The weights (two exponentials, a conversion and two multiply-adds per pair of scores) are
     // placed between the matrix instructions of the next tile's scores, which they do not depend on: both pipes
     // of the SIMD work on one wavefront, where a step that scored, weighed and accumulated one tile in turn left
     // each idle for the other's share (matrix pipes busy 42 %, vector pipes 45 %, LDS 20 % of the time).
+    // Its first keys (k-steps 0 and 1) have been read before it, those of the page's second step by its first.  
     // PV = false: the scores alone (the first tile's).
-    auto step = [&](auto pv_tag, LDS_AS unsigned char* unit, const Scores& x, Scores& y) {
-        constexpr bool PV = decltype(pv_tag)::value;
-        bf16x8 ka[2][NKS], va[NCT];
-        auto rk = [&](int ks) {
+    bf16x8 ka[2][NKS];
+    auto rk = [&](uint32_t unit, bool second, int ks) {
 #pragma unroll
-            for (int rb = 0; rb < 2; ++rb)
-                ka[rb][ks] = *(LDS_AS bf16x8*)(unit + rb * 16 * ROWB + a_base[ks & 1] + (ks >> 1) * 128);
-        };
-        auto rv = [&](int ct) { va[ct] = *(LDS_AS bf16x8*)(unit + v_base + ct * 1024); };
+        for (int rb = 0; rb < 2; ++rb)
+            ka[rb][ks] = *(LDS_AS bf16x8*)(lds + unit + a_base[ks] + (ks < 4 ? (second ? K2 : K1) + rb * 16 * ROWB : (second ? R2 : R1) + rb * 16 * ROPEB));
+    };
+    auto step = [&](auto pv_tag, auto second_tag, uint32_t unit, const Scores& x, Scores& y) {
+        constexpr bool PV = decltype(pv_tag)::value, SECOND = decltype(second_tag)::value;
+        constexpr int V = SECOND ? V1 : V0;
+        bf16x8 va[NCT];
+        auto rv = [&](int ct) { va[ct] = *(LDS_AS bf16x8*)(lds + unit + v_base + V + ct * 1024); };
         float m_use[2];
         uint32_t w[2][4];
         auto weigh = [&](int j) {               // pair j of 8: query group j / 4, scores 2 (j % 4) and the one after
@@ -295,47 +326,49 @@ __global__ __launch_bounds__(MF_THREADS, WPE) void prefill_attention_kernel(Deco
 #pragma unroll
             for (int hi = 0; hi < 2; ++hi) m_use[hi] = m_ref[hi] == -INFINITY ? 0.f : m_ref[hi];
         }
-        rk(0);
-        rk(1);
         __builtin_amdgcn_sched_barrier(0);
-        {
 #pragma unroll
-            for (int ks = 0; ks < NKS; ++ks) {
-                if (ks + 2 < NKS) rk(ks + 2);
-                else if (PV) rv(ks + 2 - NKS);
-#pragma unroll
-                for (int rb = 0; rb < 2; ++rb)
-#pragma unroll
-                    for (int hi = 0; hi < 2; ++hi)
-                        y[rb][hi] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka[rb][ks], qreg[hi][ks],
-                                                                            ks == 0 ? (f32x4){0.f, 0.f, 0.f, 0.f} : y[rb][hi], 0, 0, 0);
-                if constexpr (PV) {
-                    if (ks == 0) { weigh(0); weigh(1); }
-                    else if (ks == 3) { weigh(4); weigh(5); }
-                    else weigh(ks < 3 ? ks + 1 : ks + 2);
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // an LDS read
-                        __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);     // a matrix instruction
-                        __builtin_amdgcn_sched_group_barrier(0x2, 3, 0);     // vector instructions in its shadow
-                    }
-                }
-                __builtin_amdgcn_sched_barrier(0);
+        for (int ks = 0; ks < NKS; ++ks) {
+            if (ks + 2 < NKS) rk(unit, SECOND, ks + 2);
+            else if (PV) {
+                rv(2 * (ks + 2 - NKS));
+                rv(2 * (ks + 2 - NKS) + 1);
             }
+#pragma unroll
+            for (int rb = 0; rb < 2; ++rb)
+#pragma unroll
+                for (int hi = 0; hi < 2; ++hi)
+                    y[rb][hi] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka[rb][ks], qreg[hi][ks],
+                                                                        ks == 0 ? (f32x4){0.f, 0.f, 0.f, 0.f} : y[rb][hi], 0, 0, 0);
+            if constexpr (PV) {
+                if (ks == 0) { weigh(0); weigh(1); }
+                else if (ks == 3) { weigh(4); weigh(5); }
+                else weigh(ks < 3 ? ks + 1 : ks + 2);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // an LDS read
+                    __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);     // a matrix instruction
+                    __builtin_amdgcn_sched_group_barrier(0x2, 3, 0);     // vector instructions in its shadow
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
         }
         if constexpr (PV) {
             bf16x8 pb[2];
 #pragma unroll
             for (int hi = 0; hi < 2; ++hi) pb[hi] = __builtin_bit_cast(bf16x8, (u32x4){w[hi][0], w[hi][1], w[hi][2], w[hi][3]});
 #pragma unroll
-            for (int hi = 0; hi < 2; ++hi) lacc[hi] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pb[hi], lacc[hi], 0, 0, 0);
-#pragma unroll
             for (int ct = 0; ct < NCT; ++ct) {
-                if (ct + 2 < NCT) rv(ct + 2);
+                if (ct + 4 < NCT) rv(ct + 4);
+                else if (!SECOND && ct + 2 >= NCT) rk(unit, true, ct + 2 - NCT);
+                if (ct == 0) {
+#pragma unroll
+                    for (int hi = 0; hi < 2; ++hi) lacc[hi] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pb[hi], lacc[hi], 0, 0, 0);
+                }
 #pragma unroll
                 for (int hi = 0; hi < 2; ++hi)
                     oacc[hi][ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va[ct], pb[hi], oacc[hi][ct], 0, 0, 0);
-                if (ct & 1) __builtin_amdgcn_sched_barrier(0);
+                __builtin_amdgcn_sched_barrier(0);
             }
         }
     };
@@ -368,29 +401,45 @@ __global__ __launch_bounds__(MF_THREADS, WPE) void prefill_attention_kernel(Deco
             for (int ct = 0; ct < NCT; ++ct) oacc[hi][ct] = (f32x4){0.f, 0.f, 0.f, 0.f};
         }
         auto look_at = [&](Scores& x, int t) {   // scores of tile t, just made
-            if (!full_tile(t)) mask(x, t);
+            if (__builtin_expect(t >= n_full, 0)) mask(x, t);
             raise_top(x);
             if (unset) set_reference(x);
         };
         // (one form of the step for all: the last one scores what the slot holds in the place of keys, the sweep
         // for the maxima accumulates too, and neither result is used)
-        auto one = [&](int t, const Scores& x, Scores& y) {
-            stage(t);
-            if (late_values && t + 1 == t1) drop_late_values(t);
-            step(std::true_type{}, lds + slot_of(t), x, y);
-            if (t + 1 < t1) look_at(y, t + 1);
-        };
+        using Yes = std::true_type;
+        using No = std::false_type;
         Scores x, y;
-        step(std::false_type{}, lds + slot_of(-1), x, x);
+        rk(SLOT_B, true, 0);
+        rk(SLOT_B, true, 1);
+        step(No{}, Yes{}, (uint32_t)SLOT_B, x, x);
         look_at(x, 0);
+        uint32_t unit = 0;
         for (int t = 0; t < t1; t += 2) {
-            one(t, x, y);
-            if (t + 1 < t1) one(t + 1, y, x);
+            wait_vmcnt<0>();
+            __syncthreads();
+            rk(unit, false, 0);
+            rk(unit, false, 1);
+            if (t + 2 < t1) fetch_unit((t >> 1) + 1);
+            if (late_values && t + 2 >= t1) drop_late_values(t1 - 1);
+            step(Yes{}, No{}, unit, x, y);
+            if (t + 1 >= t1) break;
+            look_at(y, t + 1);
+            step(Yes{}, Yes{}, unit, y, x);
+            if (t + 2 < t1) look_at(x, t + 2);
+            unit = SLOT_B - unit;
         }
+        __syncthreads();         // every wave is done with the units of this sweep
         if (pass == ACCUMULATE_AGAIN) break;
         if (pass == ACCUMULATE) {
             const bool jumped = top[0] * sc > m_ref[0] + FAST_GAP || top[1] * sc > m_ref[1] + FAST_GAP;
-            if (__builtin_expect(!__syncthreads_or(jumped), 1)) break;
+            // (a flag per wavefront, where start() puts nothing)
+            LDS_AS int* const flags = (LDS_AS int*)(lds + SLOT_B);
+            const bool mine = __any(jumped);
+            if (lane == 0) flags[wave] = mine;
+            __syncthreads();
+            const int any = flags[0] | flags[1] | flags[2] | flags[3];
+            if (__builtin_expect(!any, 1)) break;
             pass = MAXIMA;
             unset = false;
         } else {
@@ -399,17 +448,15 @@ __global__ __launch_bounds__(MF_THREADS, WPE) void prefill_attention_kernel(Deco
                 const float tm = over_groups(top[hi]);
                 m_ref[hi] = tm == -INFINITY ? tm : tm * sc;
             }
-            __syncthreads();     // every wave is done with the units of that sweep
             pass = ACCUMULATE_AGAIN;
         }
+        if (pages > 64) ids = usable(ids_from(0));
         start();
     }
-    __syncthreads();             // every wave is done with the tiles: the ring becomes exchange space
-
     // ---- normalise, round to bf16, transpose through LDS (a lane holds 4 consecutive columns of its
     // query per column tile) and store whole 256-byte rows
     constexpr int RSO = PA_DV * 2 + 16;         // row stride of the transposed block (padded)
-    static_assert(4 * 32 * RSO <= NBUF * TILE_B, "exchange space must fit in the tile ring");
+    static_assert(4 * 32 * RSO <= SLOT_B, "exchange space must fit in a slot");    // (the flags lie in the other one)
     LDS_AS unsigned char* mine = lds + wave * (32 * RSO);
     float lt[2];
 #pragma unroll
@@ -451,7 +498,7 @@ hipError_t launch_prefill_attention(const DecodeParams& p, hipStream_t s)
     const long long Z = (p.H + PA_ROWS - 1) / PA_ROWS;
     const long long nwg = ((long long)p.B + 7) / 8 * 8 * Z;
     if (nwg > 0x7FFFFFFFLL) return hipErrorInvalidValue;
-    prefill_attention_kernel<3, 2><<<dim3((unsigned)nwg), dim3(MF_THREADS), 0, s>>>(p);
+    prefill_attention_kernel<<<dim3((unsigned)nwg), dim3(MF_THREADS), 0, s>>>(p);
     return hipGetLastError();
 }
 
