@@ -492,7 +492,7 @@ def prefill_main(args):
            "config": {"workload": WORKLOADS[args.workload], "batch": B, "q_len": T, "heads": H,
                       "context_max": int(w.seq_lens.max())},
            "tokens_per_s": round(B * T / (ms * 1e-3), 1),
-           "roofline": {"bound": "mfma", "kernel": f"prefill_attention_kernel<3, 2> + {materialise}",
+           "roofline": {"bound": "mfma", "kernel": f"prefill_attention_kernel + {materialise}",
                         "achieved": round(tflops, 1), "peak": 2500.0, "unit": "TFLOP/s",
                         "frac": round(tflops / 2500.0, 4), "traffic": None,
                         "algorithmic_flop_per_step": attn_flop + mat_flop,

@@ -108,7 +108,7 @@ int mla_out_proj(const void* o_lat, const void* W_UV, void* out,
 
 /*
  * Bytes of device workspace mla_decode_paged needs for these sizes (split-KV
- * partial results for B * (S + 1) chunks, S as described under num_splits:
+ * partial results for B * (S + 1) chunks, S at its largest as described under num_splits:
  * partial outputs in the io dtype, sized here as if they were fp32, and fp32
  * log-sum-exps; plus a [B, 2] int32 table the balanced partition uses).  The
  * same size serves both partitions and both io dtypes.  What the workspace
@@ -149,16 +149,15 @@ size_t mla_decode_workspace_bytes(int B, int H, int d_c, int num_splits);
  *              bytes, 256-byte aligned; contents are scratch
  *   num_splits >= 1: each sequence's page list is cut into S contiguous
  *              chunks of ceil(max_pages_per_seq / S) pages (trailing chunks of
- *              short sequences are empty), S = num_splits, or 2x / 4x that
- *              while B * S stays below 256 (so a small batch still gives
- *              every compute unit a workgroup; mla_decode_workspace_bytes
- *              accounts for it).  Every chunk is reduced with its own running
+ *              short sequences are empty), S = num_splits, or up to 4x that
+ *              as long as B * S stays below one workgroup per compute unit
+ *              (mla_decode_workspace_bytes accounts for it).  Every chunk is reduced with its own running
  *              softmax and the chunks are merged by log-sum-exp.  The result
  *              does not depend on the chunking beyond fp32 rounding.
  *              With MLA_FLAG_BALANCED (matrix-core kernels with page_size 64
  *              only, otherwise MLA_ERR_UNSUPPORTED) the cut is made differently: the page lists
- *              of all sequences, laid end to end, are cut into B * S ranges of
- *              equal length (+-1 page), one per workgroup; a range that
+ *              of all sequences, laid end to end, are cut into at most B * S
+ *              ranges of equal length (+-1 page), one per workgroup; a range that
  *              crosses sequence boundaries gives one chunk per sequence.  Every
  *              workgroup then streams the same number of bytes whatever the
  *              mix of sequence lengths.  Same results up to fp32 rounding.
@@ -306,8 +305,8 @@ int mla_merge_out_proj_multi(const void* workspace, size_t workspace_bytes,
 /*
  * Bytes of device workspace mla_prefill_mha needs: the concatenated per-head
  * projections, the materialised keys and values (B * heads * max_pages_per_seq
- * pages of 64 rows of 320 bf16 values: 40 KB per page and head), and the page
- * table and lengths of the (sequence, head) pairs.  Pure host function; 0 if an
+ * pages of 64 rows, with room for 320 bf16 values each: 40 KB per page and
+ * head) and the lengths of the (sequence, head) pairs.  Pure host function; 0 if an
  * argument is invalid.
  */
 size_t mla_prefill_workspace_bytes(int B, int heads, int d_c, int max_pages_per_seq);

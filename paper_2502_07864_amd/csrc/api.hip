@@ -3,6 +3,7 @@
 // exercised on a machine without a GPU.
 #include "mla_internal.h"
 
+#include <algorithm>
 #include <mutex>
 
 using namespace mla;
@@ -13,26 +14,44 @@ bool io_ok(mla_dtype t) { return t == MLA_F32 || t == MLA_BF16; }
 
 size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
-// Chunks actually used for a request of num_splits chunks per sequence: when the batch is too
-// small for num_splits chunks to give every CU a workgroup, each requested chunk is cut again
-// (x2 or x4).  Every entry point derives the workspace layout from this same rule.
-int effective_splits(int B, int num_splits)
+// The most chunks that a request of num_splits chunks per sequence is cut into: x2 or x4 where the batch is too small for num_splits
+// to give every CU a workgroup.  Workspaces are sized for it.
+int most_splits(int B, int num_splits)
 {
     int m = 1;
     while (m < 4 && (long)B * num_splits * m < 256) m *= 2;
     return num_splits * m;
 }
 
-// Workspace: partial outputs, partial log-sum-exps, plan.  Sized for B * (S + 1) partial slots:
-// the uniform partition uses B * S of them ([B, H, S, d_c]), the balanced one up to B * S + B - 1
+// Chunks actually used (decode and merge derive them from this same rule).  As many as make one round of
+// workgroups, one per CU (a workgroup's ring of tiles fills the LDS) and per group of 64 query rows (balanced partition: 32): a second
+// round that is not full costs a whole one.  Step, us, at doubled chunks / at those of one round: 3 x 8192 tokens 26.7 (384 workgroups)
+// / 18.8, 5 x 8192 29.1 / 22.0, 20 x 8192 52.6 (480) / 44.1, 50 x 8192 95.8 (500) / 90.1, 100 x 5000 119.6 (400) / 109.2; fp8 7 x 16384
+// 40.0 / 31.1; 12 x 4096, 16-row pages 39.2 / 31.9; two query tokens 20 x 8192 67.2 / 54.4, three (two groups of rows) 3 x 12000 59.2 /
+// 32.1; fp32 5 x 4000 94.3 / 94.5, 8 x 4000 130.8 / 125.7.  Between 64 and 85 chunks of three sequences the merge decides (more than 64 take
+// its longer form): 64, 20.5 against 22.2 at 12000 tokens.  The uniform partition keeps at least the chunks asked for (its
+// chunks may be uneven); the ranges of the balanced one are equal, and fewer of them fill the round: 70 x 14285 ragged tokens, four asked
+// for, 167.0 / 122.7, 100 x 10000 140.3 / 127.4, 40 x 16384 107.1 (eight) / 85.1; 64 heads 64 x 7812 113.9 / 102.9.
+int used_splits(int B, int H, int num_splits, bool balanced)
+{
+    const long groups = balanced ? (H + 31) / 32 : (H + 63) / 64;
+    const long round = 256 / (B * groups);
+    if (balanced) return (int)std::max(1L, std::min(4L * num_splits, round));
+    if (round <= num_splits) return num_splits;
+    const long S = std::min(4L * num_splits, round);
+    return (int)(S > 64 && round < 128 ? std::max(64, num_splits) : S);
+}
+
+// Workspace: partial outputs, partial log-sum-exps, plan.  Sized for B * (S + 1) partial slots, S = most_splits:
+// the uniform partition uses at most B * S of them ([B, H, S, d_c]), the balanced one up to B * S + B - 1
 // ([slot, H, d_c]); the plan ([B, 2] int32) is written and read by the balanced partition only.
 struct WsLayout {
     size_t lse_off, plan_off, total;
 };
 
-WsLayout ws_layout(int B, int H, int d_c, int eff_splits)
+WsLayout ws_layout(int B, int H, int d_c, int num_splits)
 {
-    const size_t slots = (size_t)B * (eff_splits + 1);
+    const size_t slots = (size_t)B * (most_splits(B, num_splits) + 1);
     WsLayout l;
     l.lse_off = align_up(slots * H * d_c * sizeof(float), 256);
     l.plan_off = l.lse_off + align_up(slots * H * sizeof(float), 256);
@@ -40,15 +59,14 @@ WsLayout ws_layout(int B, int H, int d_c, int eff_splits)
     return l;
 }
 
-void fill_merge_params(MergeParams& m, const void* workspace, int B, int H, int d_c, int eff_splits,
-                       bool balanced)
+void fill_merge_params(MergeParams& m, const void* workspace, int B, int H, int d_c, int num_splits, bool balanced)
 {
-    const WsLayout l = ws_layout(B, H, d_c, eff_splits);
+    const WsLayout l = ws_layout(B, H, d_c, num_splits);
     m.o_part = static_cast<const float*>(workspace);
     m.lse_part = reinterpret_cast<const float*>(static_cast<const char*>(workspace) + l.lse_off);
     m.plan = balanced ? reinterpret_cast<const int32_t*>(static_cast<const char*>(workspace) + l.plan_off)
                       : nullptr;
-    m.B = B; m.H = H; m.d_c = d_c; m.num_splits = eff_splits;
+    m.B = B; m.H = H; m.d_c = d_c; m.num_splits = used_splits(B, H, num_splits, balanced);
 }
 
 // The merge kernels index their wavefronts (one per output row and block of 256 columns) with 32-bit
@@ -74,7 +92,7 @@ bool uses_mfma(const DecodeCall& c)
 {
     DecodeParams p = {};
     p.B = c.B; p.H = c.q_len * c.heads; p.d_c = c.d_c; p.d_rope = c.d_rope; p.page_size = c.page_size;
-    p.num_splits = effective_splits(c.B, c.num_splits);
+    p.num_splits = most_splits(c.B, c.num_splits);
     return !(c.flags & MLA_FLAG_PORTABLE_KERNEL) && decode_mfma_supported(p, c.io_dtype, c.cache_dtype);
 }
 
@@ -101,7 +119,7 @@ int decode_validate(const DecodeCall& c)
     if (c.flags & MLA_FLAG_BALANCED) {
         // only the matrix-core kernel has this partition; grid size; page counts are summed in 32 bits
         if (!uses_mfma(c)) return MLA_ERR_UNSUPPORTED;
-        const int S = effective_splits(c.B, c.num_splits);
+        const int S = most_splits(c.B, c.num_splits);
         if ((long long)c.B * S > 0x3FFFFF || (long long)c.B * c.max_pages_per_seq > 0x7FFFFFFFLL)
             return MLA_ERR_UNSUPPORTED;
     }
@@ -118,8 +136,9 @@ int decode_launch(const DecodeCall& c, void* workspace)
     p.q_abs = c.q_abs; p.q_rope = c.q_rope; p.kv = c.kv_cache; p.kv_scale = c.kv_scale;
     p.page_table = c.page_table; p.seq_lens = c.seq_lens;
     p.o_part = static_cast<float*>(workspace);
-    const int S = effective_splits(B, c.num_splits);
-    const WsLayout wl = ws_layout(B, H, c.d_c, S);
+    const bool balanced = (c.flags & MLA_FLAG_BALANCED) != 0;
+    const int S = used_splits(B, H, c.num_splits, balanced);
+    const WsLayout wl = ws_layout(B, H, c.d_c, c.num_splits);
     p.lse_part = reinterpret_cast<float*>(static_cast<char*>(workspace) + wl.lse_off);
     p.plan = reinterpret_cast<int32_t*>(static_cast<char*>(workspace) + wl.plan_off);
     p.B = B; p.H = H; p.d_c = c.d_c; p.d_rope = c.d_rope; p.page_size = c.page_size;
@@ -130,7 +149,6 @@ int decode_launch(const DecodeCall& c, void* workspace)
     p.rope_kv = nullptr; p.rope_pitch = 0;
     p.scale = c.softmax_scale;
 
-    const bool balanced = (c.flags & MLA_FLAG_BALANCED) != 0;
     const bool mfma = uses_mfma(c);
     hipError_t e;
     if (mfma && !balanced && decode_mfma_wide_supported(p, c.io_dtype, c.cache_dtype))
@@ -143,7 +161,7 @@ int decode_launch(const DecodeCall& c, void* workspace)
     if (skip_merge) return MLA_OK;
 
     MergeParams m;
-    fill_merge_params(m, workspace, B, H, c.d_c, S, balanced);
+    fill_merge_params(m, workspace, B, H, c.d_c, c.num_splits, balanced);
     m.o_lat = c.o_lat; m.lse = c.lse;
     e = launch_merge(m, c.io_dtype, stream);
     return e == hipSuccess ? MLA_OK : MLA_ERR_HIP;
@@ -221,8 +239,7 @@ int mla_out_proj(const void* o_lat, const void* W_UV, void* out, int B, int H, i
 size_t mla_decode_workspace_bytes(int B, int H, int d_c, int num_splits)
 {
     if (B <= 0 || H <= 0 || d_c <= 0 || num_splits <= 0) return 0;
-    const int S = effective_splits(B, num_splits);
-    return ws_layout(B, H, d_c, S).total;
+    return ws_layout(B, H, d_c, num_splits).total;
 }
 
 int mla_decode_paged(const void* q_abs, const void* q_rope, const void* kv_cache,
@@ -289,7 +306,7 @@ int mla_merge_partials(const void* workspace, size_t workspace_bytes, void* o_la
     if (!workspace || workspace_bytes < need || (reinterpret_cast<uintptr_t>(workspace) & 255u))
         return MLA_ERR_WORKSPACE;
     MergeParams m;
-    fill_merge_params(m, workspace, B, H, d_c, effective_splits(B, num_splits), (flags & MLA_FLAG_BALANCED) != 0);
+    fill_merge_params(m, workspace, B, H, d_c, num_splits, (flags & MLA_FLAG_BALANCED) != 0);
     m.o_lat = o_lat; m.lse = lse;
     hipError_t e = launch_merge(m, io_dtype, static_cast<hipStream_t>(hip_stream));
     return e == hipSuccess ? MLA_OK : MLA_ERR_HIP;
@@ -318,13 +335,12 @@ int mla_merge_out_proj_multi(const void* workspace, size_t workspace_bytes, cons
         return MLA_ERR_WORKSPACE;
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     const bool balanced = (flags & MLA_FLAG_BALANCED) != 0;
-    const int S = effective_splits(B, num_splits);
     // The partials of (sequence b, query token i, head h) lie where those of sequence b * q_len + i,
     // head h of a batch of B * q_len one-token sequences would: the merge and the projection see
     // that batch.  Only the balanced partition's plan is per sequence; with it and q_len > 1 the
     // merge runs over the q_len * heads rows of each sequence and the projection follows it.
     MergeParams m;
-    fill_merge_params(m, workspace, B, q_len * heads, d_c, S, balanced);
+    fill_merge_params(m, workspace, B, q_len * heads, d_c, num_splits, balanced);
     m.o_lat = o_lat; m.lse = lse;
     if (!(balanced && q_len > 1)) { m.B = B * q_len; m.H = heads; }
     hipError_t e;

@@ -8,7 +8,7 @@
 // A page of 64 keys is 32 KB: the per-head part of the keys, W^{UK}_h c_j, as 64 rows of 128 bf16 values, then the
 // values TRANSPOSED, [half page][16-dimension tile][4 groups of 8 keys][16 dimensions][8 keys].  The decoupled-rope part k^R_j, which all
 // heads share, is read from the cache itself (copied to every head it was a fifth of what is written and read: 8 x 500 tokens on
-// 700 .. 6000 rows, 28 heads, d_c = 256 ROPEUS us).  Both orders are made for the reads of this
+// 700 .. 6000 rows, 28 heads, d_c = 256: 387 us with the copies, 376).  Both orders are made for the reads of this
 // kernel (the kernel that writes them has the choice for free): inside each 32 of the 128 key
 // dimensions position 8g + 4m + i holds dimension 16m + 4g + i (the queries are loaded alike), and
 // key j of group g of a half page is its key 4g + j (j < 4) or 16 + 4g + j - 4, which is how the
@@ -19,19 +19,18 @@
 //
 // Workgroup = 128 query rows of one (sequence, head) x all the keys they see; 4 wavefronts, each
 // with 32 query rows of its own (two groups of 16) and a private running softmax, so the only
-// workgroup barrier per tile is the one that publishes a unit (32 keys and the values of the 32 before,
-// direct-to-LDS loads, ring of NBUF).  Every LDS read feeds two MFMAs (the two query groups).  The normaliser is a
+// workgroup barrier is the one that publishes a unit (what two tiles of 32 keys need, direct-to-LDS loads, two slots).  Every LDS read feeds two MFMAs (the two query groups).  The normaliser is a
 // product too: one MFMA with an A operand of ones per tile and group sums the rounded weights.  No
 // rescaling in the loop: the reference of a query is the maximum of its first tile; a later score more
 // than 2^64 above it is recorded and the workgroup then redoes its keys with the exact maxima (one sweep
 // that only scores, one that accumulates).
 //
-// What bounds it: the matrix pipes, at the clock the chip holds under them.  4 prompts of 8192 tokens, 32 heads (2.75
-// TFLOP), counters, time and clock of one profiled run: 5.10 M cycles in 2.71 ms (1.88 GHz), matrix pipes busy 55 % of
-// them, LDS 27 %; shorter kernels of the same call run at 1.95 to 2.3 GHz.  The form before this one, which scored,
-// weighed and accumulated one tile after the other from row-major values, took 6.7 M cycles with the pipes busy 42 %.
-// Whole call, timed in turn with that form: 3036 -> 2794 us (a library product of 8192^3 reaches 1.29 PFLOP/s on such a
-// card); 8 x 500 new tokens on 700 .. 6000, 28 heads: 552 -> 423.
+// What bounds it: power.  4 prompts of 8192 tokens, 32 heads (2.75 TFLOP): matrix pipes busy 60 % of 4.7 M cycles at 1.8 to 1.9 GHz;
+// a loop of the same instructions on registers alone sustains 2.0 PFLOP/s, of 32 x 32 x 16 ones 1.8 (not taken).  With a
+// barrier, five loads, ring slots modulo three and a scalar load of the page table on every tile (76 scalar instructions) the pipes
+// were busy 55 % of 5.1 M cycles at a higher clock: 8 % of the cycles gave 2 to 3 % of the time.  Scored, weighed and accumulated
+// one tile after the other from row-major values: 42 % of 6.7 M.  Whole call: 3036 us that way, then 2785, now 2736 in turn on one
+// card; 8 x 500 new tokens on 700 .. 6000, 28 heads: 552, 396, 376; 2 x 136 on 10539, whose workgroups have a CU each: 340, 288.
 #include "mla_internal.h"
 #include "mfma_tile.h"
 #include <type_traits>

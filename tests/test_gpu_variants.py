@@ -253,6 +253,48 @@ def test_prefill_skips_bad_pages(mla):
         assert max_abs_rel(widen_gpu(got)[b, t], ref) <= TOL["bf16"]
 
 
+@pytest.mark.parametrize("B,splits,T,H,cache,flags", [(3, 32, 1, 32, "bf16", 0), (3, 64, 1, 28, "bf16", 0), (5, 25, 1, 32, "fp8_e4m3", 0), (17, 15, 1, 32, "bf16", 0),
+                                                     (3, 32, 3, 32, "bf16", 0), (2, 16, 5, 64, "bf16", 0), (2, 32, 1, 32, "f32", 0), (20, 4, 1, 32, "bf16", 4),
+                                                     (70, 4, 1, 16, "bf16", 4), (70, 3, 1, 64, "fp8_e4m3", 4), (20, 4, 2, 32, "bf16", 4), (130, 7, 1, 64, "bf16", 4)])
+def test_chunks_of_one_round(mla, B, splits, T, H, cache, flags):
+    """Calls whose chunks are counted to fill one round of workgroups, above and (balanced) below what was asked for: decode and merge
+    cut alike, as one call and as the two with the projection, whatever the workspace held."""
+    from test_gpu_parity import check_multi
+    lens = [(97 * i) % 700 for i in range(B - 1)] + [3000 if B < 20 else 1100]
+    w = synth.make_workload("round", B=B, H=H, d_head=128, d_c=256, d_rope=64, seq_lens=lens, io_dtype="f32" if cache == "f32" else "bf16",
+                            cache_dtype=cache, free_frac=0.1, seed=135)
+    check_multi(mla, w, T, splits, flags)
+    check_multi(mla, w, T, splits, flags, fused_tail=True)
+
+
+@pytest.mark.parametrize("L,drop,late", [(4095, (), 0), (4096, (62, 63), 0), (4097, (64,), 0), (4161, (), 4100), (8191, (63, 64, 127), 8190), (16449, (255, 256), 0)])
+def test_prefill_page_ids_64_at_a_time(mla, L, drop, late):
+    """Contexts around 64 and 256 pages, whose ids a wavefront holds 64 at a time: pages outside the pool on both sides of a border (the
+    oracle gets the sequence without them), and a dominant late key, after which the sweeps start again from the first page."""
+    import torch
+    T, H, d_c = 3, 2, 256
+    w = synth.make_workload("prefill", B=1, H=H, d_head=128, d_c=d_c, d_rope=64, seq_lens=[L], io_dtype="bf16", cache_dtype="bf16",
+                            free_frac=0.1, seed=134)
+    if late:                                          # that token's rope part points along the last query's
+        qn, qr = synth.multi_queries(w, T)
+        w.pool[w.page_table[0, late // 64], late % 64, d_c:] = synth.store(50.0 * oracle.widen(qr[0, -1, 0]).astype(np.float32), "bf16")
+    qn, qr = synth.multi_queries(w, T)
+    bad, pt, n = w.page_table.copy(), w.page_table.copy(), w.seq_lens.copy()
+    for i in sorted(drop, reverse=True):
+        bad[0, i] = w.num_pages + 3 if i % 2 else -1
+        n[0] -= min(64, n[0] - 64 * i)
+        pt[0] = np.append(np.delete(pt[0], i), -1)
+    d = DeviceWorkload(w)
+    got, lse = mla.prefill_mha(to_torch(qn, "bf16"), to_torch(qr, "bf16"), d.W_UK, d.W_UV, d.pool, to_torch(bad, "i32"), d.seq_lens,
+                               w.softmax_scale, return_lse=True)
+    torch.cuda.synchronize()
+    ref, ref_lse = oracle.prefill_explicit(qn, qr, w.W_UK, w.W_UV, w.pool, None, pt, n, w.softmax_scale, w.d_c)
+    if 63 in drop and L == 4096:                      # the newest page is not there: earlier tokens' limits lie in the one before it
+        ref, ref_lse, got, lse = ref[:, -1:], ref_lse[:, -1:], got[:, -1:], lse[:, -1:]
+    assert max_abs_rel(widen_gpu(got), ref) <= TOL["bf16"]
+    assert lse_err(widen_gpu(lse), ref_lse) <= 2e-2 * max(1.0, np.abs(ref_lse).max() / 30)
+
+
 def weights_in_lds(B, T, lens, H, d_c):
     """The launcher's choice between the two kernels that write the keys and values."""
     pages = B * max(1, max((n + 63) // 64 for n in lens))
