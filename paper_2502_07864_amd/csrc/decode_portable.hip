@@ -26,8 +26,6 @@
 namespace mla {
 namespace {
 
-constexpr int PR_THREADS = 256;
-constexpr int PR_WAVES = 4;
 constexpr int PR_MAX_DC = 512;    // two groups of four latent values per lane; d_rope <= 64: one on the first 16 lanes
 
 struct bf16_tag {};
@@ -91,8 +89,9 @@ __device__ __forceinline__ float dot4(float4 a, float4 b, float s)
 
 // ROWS: rows of a wavefront's batch (the next batch is on its way while one is used): as many as fit
 // beside the queries and the sums of HG heads with two wavefronts per SIMD
-template <typename QT, typename CT, int HG, int ROWS>
-__global__ __launch_bounds__(PR_THREADS) void decode_portable_kernel(DecodeParams p)
+// WAVES: 4, or 8 where one workgroup per CU has it to itself
+template <typename QT, typename CT, int HG, int ROWS, int PR_WAVES>
+__global__ __launch_bounds__(64 * PR_WAVES) void decode_portable_kernel(DecodeParams p)
 {
     __shared__ __attribute__((aligned(16))) float o_s[PR_WAVES][HG][PR_MAX_DC];
     __shared__ float m_s[PR_WAVES][HG], l_s[PR_WAVES][HG];
@@ -260,20 +259,24 @@ __global__ __launch_bounds__(PR_THREADS) void decode_portable_kernel(DecodeParam
         fetch(at, sc_at, x0);
         locate(jb + jstep, at, sc_at);
         while (true) {
-            fetch(at, sc_at, x1);                // the next batch (its rows may all be absent: nothing is used then)
-            locate(jb + 2 * jstep, at, sc_at);
+            if (jb + jstep < j1) {               // the next batch
+                fetch(at, sc_at, x1);
+                locate(jb + 2 * jstep, at, sc_at);
+            }
             consume(x0, jb);
             jb += jstep;
             if (jb >= j1) break;
-            fetch(at, sc_at, x0);
-            locate(jb + 2 * jstep, at, sc_at);
+            if (jb + jstep < j1) {
+                fetch(at, sc_at, x0);
+                locate(jb + 2 * jstep, at, sc_at);
+            }
             consume(x1, jb);
             jb += jstep;
             if (jb >= j1) break;
         }
     }
 
-    // ---- the four wavefronts' softmax states joined: every thread finishes columns of every head
+    // ---- the wavefronts' softmax states joined: every thread finishes columns of every head
 #pragma unroll
     for (int h = 0; h < HG; ++h) {
         float lt = l[h] + __shfl_xor(l[h], 16);
@@ -511,9 +514,10 @@ __global__ __launch_bounds__(256) void gather_kernel(const uint32_t* kv, const i
 
 // Which form takes a call.  Both kernels hold two workgroups per CU, so their times go in rounds of 512 workgroups,
 // whatever the rest; measured on 32 .. 65536 workgroups of 200 rows each, back to back in a graph, us:
-//   rows in registers, 2 heads per workgroup: up to 256 workgroups 22, up to 512 40 (fp32 cache) and 28 (others);
-//     4 heads: up to 256 31, up to 512 40, 768 63, 1024 73, 1536 107, 2048 137, 4096 268, whatever the width (a row
-//     costs a whole wavefront, and is read once per 4 heads); 8 heads leave one wavefront per SIMD and are slower still;
+//   rows in registers, 2 heads per workgroup: up to 256 workgroups (eight wavefronts each) 15 to 23 by width, up to 512 40
+//     (fp32 cache) and 28 (others); 4 heads: up to 256 22 to 28, up to 512 40, 768 63, 1024 73, 1536 107, 2048 137, 4096 268,
+//     whatever the width (a row costs a whole wavefront, and is read once per 4 heads); 8 heads leave one wavefront per SIMD
+//     and are slower still.  Up to 256 workgroups have a CU each, where four wavefronts left a SIMD to one: 21 to 30 and 26 to 38;
 //   16-row tiles in LDS, 8 heads: fp32, d_c = 64 / 256: up to 256 32 / 44, 512 38 / 54, 1024 72 / 102, 2048 139 / 200;
 //     fp8 38 / 61, 42 / 67, 83 / 131, 162 / 259: a round costs what the width does (fp32 30 us at d_c = 8, 39 at 128, 70
 //     at 384), and 12 us more past 256, the second column of its threads.
@@ -526,8 +530,8 @@ static Form faster_form(const DecodeParams& p, mla_dtype cache)
 {
     const long long n = (long long)p.B * p.num_splits, n8 = (n + 7) / 8 * 8;
     const long long w2 = n8 * ((p.H + 1) / 2), w4 = n8 * ((p.H + 3) / 4), w8 = n * ((p.H + 7) / 8);
-    const double two = w2 <= 256 ? 22.0 : w2 > 512 ? INFINITY : cache == MLA_F32 ? 40.0 : 28.0;
-    const double four = 33.0 * (double)((w4 - 1) / 512) + ((w4 - 1) % 512 < 256 ? 31.0 : 40.0);
+    const double two = w2 <= 256 ? 17.0 : w2 > 512 ? INFINITY : cache == MLA_F32 ? 40.0 : 28.0;
+    const double four = w4 <= 256 ? 24.0 : 33.0 * (double)((w4 - 1) / 512) + ((w4 - 1) % 512 < 256 ? 31.0 : 40.0);
     const double round = (cache == MLA_F32 ? 28.0 + p.d_c / 10.0 : cache == MLA_BF16 ? 30.0 + p.d_c / 9.5 : 33.0 + p.d_c / 8.0) +
                          (p.d_c > 256 ? 12.0 : 0.0);
     const double tiles = w8 <= 256 ? 0.95 * round : round * (double)((w8 + 511) / 512);
@@ -537,13 +541,19 @@ static Form faster_form(const DecodeParams& p, mla_dtype cache)
 template <typename QT, typename CT>
 static hipError_t launch_portable(const DecodeParams& p, int hg, hipStream_t s)
 {
+    // Up to one workgroup per CU: eight wavefronts, half as many batches in a row for each (step, us, four -> eight: 1 x 1024
+    // fp32 rows 20.9 -> 19.3, 3 x 520, d_c = 256, 34.0 -> 28.7, 1 x 4000, 16 heads, 33.1 -> 27.8).  Batches of four rows: of eight, they
+    // spill (38 registers) and the last one is mostly rows that are not there (20.9).
     const long long n = ((long long)p.B * p.num_splits + 7) / 8 * 8;
     const long long wgs = n * ((p.H + hg - 1) / hg);
     const long long gx = wgs < (1 << 20) ? wgs : 1 << 20, gy = (wgs + gx - 1) / gx;   // a grid dimension holds 2^32 threads
     if (gy > 65535) return hipErrorInvalidValue;
     const dim3 grid((unsigned)gx, (unsigned)gy);
-    if (hg == 4) decode_portable_kernel<QT, CT, 4, 4><<<grid, PR_THREADS, 0, s>>>(p);
-    else         decode_portable_kernel<QT, CT, 2, 8><<<grid, PR_THREADS, 0, s>>>(p);
+    const bool alone = wgs <= 256;
+    if (hg == 4 && alone)  decode_portable_kernel<QT, CT, 4, 4, 8><<<grid, 512, 0, s>>>(p);
+    else if (hg == 4)      decode_portable_kernel<QT, CT, 4, 4, 4><<<grid, 256, 0, s>>>(p);
+    else if (alone)        decode_portable_kernel<QT, CT, 2, 4, 8><<<grid, 512, 0, s>>>(p);
+    else                   decode_portable_kernel<QT, CT, 2, 8, 4><<<grid, 256, 0, s>>>(p);
     return hipGetLastError();
 }
 

@@ -253,6 +253,17 @@ def test_prefill_skips_bad_pages(mla):
         assert max_abs_rel(widen_gpu(got)[b, t], ref) <= TOL["bf16"]
 
 
+@pytest.mark.parametrize("H,d_c,B,cache", [(1, 512, 1, "f32"), (3, 256, 2, "f32"), (32, 512, 1, "f32"), (5, 64, 9, "bf16"), (16, 256, 16, "fp8_e4m3"),
+                                           (4, 512, 256, "f32"), (4, 256, 257, "bf16"), (2, 512, 300, "f32")])
+def test_portable_decode_wavefronts(mla, H, d_c, B, cache):
+    """Eight wavefronts of four rows per batch where every workgroup has a CU, four beyond: chunks that end inside, at and behind a
+    wavefront's batch and a round of batches, none at all, at both sides of 256 workgroups of 2 and of 4 heads."""
+    ends = [1, 3, 4, 5, 31, 32, 33, 63, 64, 65, 0, 97, 129, 200]
+    w = synth.make_workload("waves", B=B, H=H, d_head=128, d_c=d_c, d_rope=64, seq_lens=[ends[(5 * i + B) % len(ends)] for i in range(B - 1)] + [150],
+                            io_dtype="f32", cache_dtype=cache, free_frac=0.1, page_size=40, seed=136)
+    check_decode(mla, w, 1)
+
+
 @pytest.mark.parametrize("B,splits,T,H,cache,flags", [(3, 32, 1, 32, "bf16", 0), (3, 64, 1, 28, "bf16", 0), (5, 25, 1, 32, "fp8_e4m3", 0), (17, 15, 1, 32, "bf16", 0),
                                                      (3, 32, 3, 32, "bf16", 0), (2, 16, 5, 64, "bf16", 0), (2, 32, 1, 32, "f32", 0), (20, 4, 1, 32, "bf16", 4),
                                                      (70, 4, 1, 16, "bf16", 4), (70, 3, 1, 64, "fp8_e4m3", 4), (20, 4, 2, 32, "bf16", 4), (130, 7, 1, 64, "bf16", 4)])
