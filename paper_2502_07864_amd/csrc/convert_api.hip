@@ -125,7 +125,7 @@ int top_eig(const Symmetric& S, const double* Q0, double* evals, double* R, cons
     e = launch_symmetrise(w.T, p, s);
     if (e != hipSuccess) return MLA_ERR_HIP;
     e = launch_jacobi(w.T, evals, w.Z, info + 1, 1, p, p > 128 ? RITZ_MAX_SWEEPS : JACOBI_MAX_SWEEPS, s,
-                      JacobiSpare{w.G, w.X, (size_t)p * p});
+                      JacobiSpare{w.G, w.part, w.part_doubles});
     if (e != hipSuccess) return MLA_ERR_HIP;
     return st(launch_gemm_f64(gemm_nn(w.Y, p, w.T, p, R, r, m, r, p, 1.0), s));
 }
@@ -284,7 +284,9 @@ int mla_convert_layer(const double* X, const double* W_K, const double* W_V, con
     // Sec. 4.1 / App. B: key activations before RoPE, their per-group moments, the bases U
     MLA_TRY(product(gemm_nt(X, D, W_K, D, w.K, gd, n, gd, D, 1.0)));
     MLA_TRY(launch_rope_moments(w.K, U, n, g, d, M, s));
-    MLA_TRY(launch_jacobi(U, evals_rope, w.sigma_work, info, groups, Mg, JACOBI_MAX_SWEEPS, s));
+    const size_t bases = (size_t)groups * Mg * Mg;
+    MLA_TRY(launch_jacobi(U, evals_rope, w.sigma_work, info, groups, Mg, JACOBI_MAX_SWEEPS, s,
+                          s_doubles > bases ? JacobiSpare{w.S, w.S + bases, s_doubles - bases} : JacobiSpare{}));
     // Sec. 4.2: rotate W^K; the RoPE key: W_KR = the first d_rope rows, W_QR = the same rows of the rotated selectors (W^UK_i)^T
     MLA_TRY(launch_rotate_rows(W_K, U, w.W_K_rot, g, d, M, keep, D, s));
     MLA_TRY(launch_copy_scaled(w.W_K_rot, D, W_KR, D, d_rope, D, nullptr, 0, s));

@@ -50,7 +50,8 @@ hipError_t launch_alpha(const double* norms, double* alpha, int n, hipStream_t s
 hipError_t launch_balance(const double* K, int ldk, const double* V, int ldv, const double* alpha, double* C, int n, int a, int b, hipStream_t s);
 // work: jacobi_work_bytes(batch, m) bytes
 size_t jacobi_work_bytes(int batch, int m);
-// spare, orders above 128: room for a second matrix and for `doubles` more, with which a step is one launch instead of two
+// spare: scratch for as many matrices again and `doubles` more, with which the launches of the solver over pairs of blocks take a
+// whole batch and a step is one of them instead of two (too little: it is not used)
 struct JacobiSpare { double* matrix = nullptr; double* rest = nullptr; size_t doubles = 0; };
 hipError_t launch_jacobi(double* A, double* evals, double* work, int* info, int batch, int m, int max_sweeps, hipStream_t s,
                          const JacobiSpare& spare = {});

@@ -535,25 +535,54 @@ struct WideState { double tot; int done, sweeps, at; };    // at: sweeps before 
 constexpr int JB = 16, JP = 2 * JB;                    // block, pair of blocks
 constexpr int JB_INNER = 4;                            // steps between rotations inside the blocks
 constexpr int JB_NORM_WGS = 64;
+// Orders up to it stay with one workgroup each.  Above, given scratch, a block of p columns without iterations, ms with one workgroup /
+// here: p = 65 1.68 / 1.06, 96 4.58 / 1.16, 128 11.6 / 1.47; layers whose groups have 128 components (16 of them) 12.0 / 2.1.  One of
+// order 64 1.24 / 0.74, but 32 at once 1.36 / 1.27 and 48 0.58 / 0.67.
+constexpr int WIDE_MIN = 64;
 
+// (of a batch, matrix blockIdx.y, or blockIdx.x where a workgroup has one)
 __global__ __launch_bounds__(256) void jw_init_kernel(double* __restrict__ V, int m, WideState* st) {
     const long total = (long)m * m;
+    V += blockIdx.y * total;
+    st += blockIdx.y;
     for (long idx = (long)blockIdx.x * 256 + threadIdx.x; idx < total; idx += (long)gridDim.x * 256)
         V[idx] = (idx / m == idx % m) ? 1.0 : 0.0;
     if (blockIdx.x == 0 && threadIdx.x == 0) { st->tot = 0.0; st->done = 0; st->sweeps = -1; }
 }
 
-// partial squared norms (off the diagonal, on it) of a share of the rows, from the blocks on and above the diagonal; then their
-// sums in order
-__global__ __launch_bounds__(256) void jw_partial_norm_kernel(const double* __restrict__ A, int m, double* __restrict__ part, const WideState* st) {
-    __shared__ double red[16];
-    if (st->done) return;
-    double off = 0.0, dia = 0.0;
-    for (int i = blockIdx.x; i < m; i += JB_NORM_WGS)
-        for (int j = i / JB * JB + threadIdx.x; j < m; j += 256) {
+// Squared norms (off the diagonal, on it) from the blocks on and above the diagonal.  Up to NORM_ONE_WG one workgroup has a matrix;
+// else partial ones of a share of the rows, then their sums in order.
+constexpr int NORM_ONE_WG = 128;
+__device__ __forceinline__ void squared_norms(const double* __restrict__ A, int m, int first, int stride, double& off, double& dia) {
+    const int per = blockDim.x / 64, wave = threadIdx.x >> 6, lane = threadIdx.x & 63;     // a row each
+    for (int i = first * per + wave; i < m; i += stride * per)
+        for (int j = i / JB * JB + lane; j < m; j += 64) {
             const double v = A[(long)i * m + j];
             if (i == j) dia += v * v; else off += j / JB == i / JB ? v * v : 2.0 * (v * v);
         }
+}
+__device__ __forceinline__ void look_at_norms(double off, double dia, int sweep, WideState* st) {
+    if (sweep == 0) st->tot = off + dia;
+    if (off <= 1e-26 * st->tot) { st->done = 1; st->sweeps = sweep > 0 ? sweep : 1; st->at = sweep; }
+}
+
+__global__ __launch_bounds__(1024) void jw_norm_one_kernel(const double* __restrict__ A, int m, int sweep, WideState* st) {
+    __shared__ double red[16];
+    st += blockIdx.x;
+    if (st->done) return;
+    double off = 0.0, dia = 0.0;
+    squared_norms(A + (long)blockIdx.x * m * m, m, 0, 1, off, dia);
+    off = block_sum(off, red);
+    dia = block_sum(dia, red);
+    if (threadIdx.x == 0) look_at_norms(off, dia, sweep, st);
+}
+
+__global__ __launch_bounds__(256) void jw_partial_norm_kernel(const double* __restrict__ A, int m, double* __restrict__ part, const WideState* st) {
+    __shared__ double red[16];
+    if (st[blockIdx.y].done) return;
+    part += blockIdx.y * 2 * JB_NORM_WGS;
+    double off = 0.0, dia = 0.0;
+    squared_norms(A + (long)blockIdx.y * m * m, m, blockIdx.x, JB_NORM_WGS, off, dia);
     off = block_sum(off, red);
     dia = block_sum(dia, red);
     if (threadIdx.x == 0) { part[2 * blockIdx.x] = off; part[2 * blockIdx.x + 1] = dia; }
@@ -561,12 +590,11 @@ __global__ __launch_bounds__(256) void jw_partial_norm_kernel(const double* __re
 
 __global__ __launch_bounds__(64) void jw_norm_kernel(const double* __restrict__ part, int sweep, WideState* st) {
     static_assert(JB_NORM_WGS == 64, "one lane per partial norm");
+    st += blockIdx.x;
+    part += blockIdx.x * 2 * JB_NORM_WGS;
     if (st->done) return;
     const double off = wave_sum(part[2 * threadIdx.x]), dia = wave_sum(part[2 * threadIdx.x + 1]);
-    if (threadIdx.x == 0) {
-        if (sweep == 0) st->tot = off + dia;
-        if (off <= 1e-26 * st->tot) { st->done = 1; st->sweeps = sweep > 0 ? sweep : 1; st->at = sweep; }
-    }
+    if (threadIdx.x == 0) look_at_norms(off, dia, sweep, st);
 }
 
 // blocks I < J of pair k of a step: the rotations inside a pair take its indices in their order in the matrix (in the
@@ -789,8 +817,18 @@ __device__ void wide_tile(const WideStep& w, WideLds& L, int P, int Q, bool on_v
 // block of V from the step before.
 __global__ __launch_bounds__(256) void wide_step_kernel(WideStep w) {
     __shared__ WideLds L;
-    if (w.st->done) return;
-    const int pairs = w.nbp / 2, tid = threadIdx.x;
+    const int z = blockIdx.y, pairs = w.nbp / 2, tid = threadIdx.x;
+    if (w.st[z].done) return;
+    if (z > 0) {
+        const long mat = (long)z * w.m * w.m, each = (long)z * pairs * JP * JP;
+        w.A += mat;
+        w.B += mat;
+        w.V += mat;
+        w.Z += each;
+        w.Z_next += each;
+        if (w.D) w.D += each;
+        if (w.D_next) w.D_next += each;
+    }
     int at = blockIdx.x;
     if (w.next >= 0) {
         if (at < pairs) wide_pair(w, L, at, tid);
@@ -813,7 +851,11 @@ __global__ __launch_bounds__(256) void wide_step_kernel(WideStep w) {
 __global__ __launch_bounds__(1024) void jw_rank_kernel(const double* __restrict__ even, const double* __restrict__ odd, int last, int m,
                                                        double* __restrict__ evals, int* __restrict__ rank, const WideState* st, int* info) {
     __shared__ double diag[EIG_MAX_M];
-    const double* A = (st->done ? st->at : last) & 1 ? odd : even;     // the matrix after that many sweeps
+    st += blockIdx.x;
+    evals += (long)blockIdx.x * m;
+    rank += (long)blockIdx.x * m;
+    info += blockIdx.x;
+    const double* A = ((st->done ? st->at : last) & 1 ? odd : even) + (long)blockIdx.x * m * m;     // the matrix after that many sweeps
     for (int i = threadIdx.x; i < m; i += 1024) diag[i] = A[(long)i * m + i];
     __syncthreads();
     for (int i = threadIdx.x; i < m; i += 1024) {
@@ -829,6 +871,9 @@ __global__ __launch_bounds__(1024) void jw_rank_kernel(const double* __restrict_
 __global__ __launch_bounds__(256) void jw_permute_kernel(double* __restrict__ A_out, const double* __restrict__ V,
                                                          const int* __restrict__ rank, int m) {
     const long total = (long)m * m;
+    A_out += blockIdx.y * total;
+    V += blockIdx.y * total;
+    rank += (long)blockIdx.y * m;
     for (long idx = (long)blockIdx.x * 256 + threadIdx.x; idx < total; idx += (long)gridDim.x * 256)
         A_out[(idx / m) * m + rank[idx % m]] = V[idx];
 }
@@ -1249,55 +1294,67 @@ static size_t jacobi_extra_bytes(int m) {
 }
 size_t jacobi_work_bytes(int batch, int m) { return (size_t)batch * m * m * sizeof(double) + jacobi_extra_bytes(m); }
 
-static hipError_t launch_jacobi_wide(double* A, double* evals, double* V, void* extra, int* info, int m, int max_sweeps,
+// One matrix with the scratch of jacobi_extra_bytes, or, given enough of the caller's, a batch with two matrices each.
+static size_t wide_spare_doubles(int batch, int m) {
+    const size_t pairs = ((m + JB - 1) / JB + 1) / 2;
+    return (size_t)batch * (4 * pairs * JP * JP + 2 * JB_NORM_WGS + (m + 1) / 2 + (sizeof(WideState) + 7) / 8) + 1;
+}
+
+static hipError_t launch_jacobi_wide(double* A, double* evals, double* V, void* extra, int* info, int batch, int m, int max_sweeps,
                                      const JacobiSpare& spare, hipStream_t s) {
     const int nb = (m + JB - 1) / JB, nbp = nb + (nb & 1), pairs = nbp / 2;
-    const size_t each = (size_t)pairs * JP * JP;
-    double* Z = static_cast<double*>(extra);
-    double* part = Z + each;
-    int* rank = reinterpret_cast<int*>(part + 2 * JB_NORM_WGS);
-    WideState* st = reinterpret_cast<WideState*>(rank + EIG_MAX_M);
+    const size_t each = (size_t)batch * pairs * JP * JP;
+    const bool two = spare.matrix;
+    double* Z = two ? spare.rest : static_cast<double*>(extra);
+    double* part = Z + (two ? 4 : 1) * each;
+    int* rank = reinterpret_cast<int*>(part + (size_t)batch * 2 * JB_NORM_WGS);
+    WideState* st = reinterpret_cast<WideState*>(two ? part + (size_t)batch * (2 * JB_NORM_WGS + (m + 1) / 2)
+                                                     : reinterpret_cast<double*>(rank + EIG_MAX_M));
     hipError_t e;
-    jw_init_kernel<<<grid_for((long)m * m), 256, 0, s>>>(V, m, st);
+    jw_init_kernel<<<dim3(grid_for((long)m * m), batch), 256, 0, s>>>(V, m, st);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     const int tiles = eights(pairs * (pairs + 1) / 2) + eights((m + JP - 1) / JP) * pairs, steps = nbp - 1;
-    const bool two = spare.matrix && spare.doubles >= 3 * each;
     double* const mat[2] = {A, two ? spare.matrix : A};
-    double* const Zs[2] = {Z, two ? spare.rest : Z};
-    double* const Ds[2] = {two ? spare.rest + each : nullptr, two ? spare.rest + 2 * each : nullptr};
+    double* const Zs[2] = {Z, two ? Z + each : Z};
+    double* const Ds[2] = {two ? Z + 2 * each : nullptr, two ? Z + 3 * each : nullptr};
     // (a sweep has an odd number of steps: after `sweep` of them the matrix lies in mat[sweep & 1]; step n is the n-th of all)
     for (int sweep = 0; sweep <= max_sweeps; ++sweep) {
-        jw_partial_norm_kernel<<<JB_NORM_WGS, 256, 0, s>>>(mat[sweep & 1], m, part, st);
-        jw_norm_kernel<<<1, 64, 0, s>>>(part, sweep, st);
+        if (m <= NORM_ONE_WG) jw_norm_one_kernel<<<batch, 1024, 0, s>>>(mat[sweep & 1], m, sweep, st);
+        else {
+            jw_partial_norm_kernel<<<dim3(JB_NORM_WGS, batch), 256, 0, s>>>(mat[sweep & 1], m, part, st);
+            jw_norm_kernel<<<batch, 64, 0, s>>>(part, sweep, st);
+        }
         if ((e = hipGetLastError()) != hipSuccess) return e;
         if (sweep == max_sweeps) break;
         for (int step = 0; step < steps; ++step) {
             const int x = (sweep + step) & 1;          // parity of n
             if (!two || (sweep == 0 && step == 0))
-                wide_step_kernel<<<pairs, 256, 0, s>>>(WideStep{mat[x], mat[x], V, nullptr, nullptr, Zs[x], Ds[x], m, nbp, -1, step, st});
+                wide_step_kernel<<<dim3(pairs, batch), 256, 0, s>>>(WideStep{mat[x], mat[x], V, Zs[x], nullptr, Zs[x], Ds[x], m, nbp, -1, step, st});
             const bool last = sweep + 1 == max_sweeps && step + 1 == steps;
             const int next = !two || last ? -1 : step + 1 < steps ? step + 1 : 0;
-            wide_step_kernel<<<tiles + (next < 0 ? 0 : eights(pairs)), 256, 0, s>>>(
+            wide_step_kernel<<<dim3(tiles + (next < 0 ? 0 : eights(pairs)), batch), 256, 0, s>>>(
                 WideStep{mat[x], mat[x ^ 1], V, Zs[x], Ds[x], Zs[x ^ 1], Ds[x ^ 1], m, nbp, step, next, st});
         }
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
-    jw_rank_kernel<<<1, 1024, 0, s>>>(mat[0], mat[1], max_sweeps, m, evals, rank, st, info);
-    jw_permute_kernel<<<grid_for((long)m * m), 256, 0, s>>>(A, V, rank, m);
+    jw_rank_kernel<<<batch, 1024, 0, s>>>(mat[0], mat[1], max_sweeps, m, evals, rank, st, info);
+    jw_permute_kernel<<<dim3(grid_for((long)m * m), batch), 256, 0, s>>>(A, V, rank, m);
     return hipGetLastError();
 }
 
 hipError_t launch_jacobi(double* A, double* evals, double* work, int* info, int batch, int m, int max_sweeps, hipStream_t s, const JacobiSpare& spare) {
+    // every sweep enqueued costs its launches even after convergence.  Single rotations over the whole
+    // matrix took up to 16 where they converged; sweeps over pairs of blocks take as many or fewer on full, graded and
+    // nearly diagonal spectra, but up to 7 more on low ranks and multiple eigenvalues (rank 40 or 100 of 256: 12 and 17 to 20;
+    // three eigenvalues 85 times each: 24 or 25)
+    const int sweeps = std::min(max_sweeps, 26);
+    if (m > WIDE_MIN && spare.matrix && spare.doubles >= wide_spare_doubles(batch, m))
+        return launch_jacobi_wide(A, evals, work, nullptr, info, batch, m, sweeps, spare, s);
     if (m > 128) {                                     // large matrices: the whole chip works on one at a time
         void* extra = work + (size_t)batch * m * m;
-        // every sweep enqueued costs its launches even after convergence.  Single rotations over the whole
-        // matrix took up to 16 where they converged; sweeps over pairs of blocks take as many or fewer on full, graded and
-        // nearly diagonal spectra, but up to 7 more on low ranks and multiple eigenvalues (rank 40 or 100 of 256: 12 and 17 to 20;
-        // three eigenvalues 85 times each: 24 or 25)
-        const int sweeps = std::min(max_sweeps, 26);
         for (int b = 0; b < batch; ++b) {
             hipError_t e = launch_jacobi_wide(A + (size_t)b * m * m, evals + (size_t)b * m, work + (size_t)b * m * m,
-                                              extra, info + b, m, sweeps, spare, s);
+                                              extra, info + b, 1, m, sweeps, JacobiSpare{}, s);
             if (e != hipSuccess) return e;
         }
         return hipSuccess;

@@ -449,9 +449,9 @@ def test_sym_eig_low_rank_and_multiple_eigenvalues_converge(mla, kind, m):
         assert np.abs(ritz.cpu().numpy()[:10] - np.linalg.eigvalsh(A[0])[::-1][:10]).max() <= 1e-10 * np.linalg.norm(A[0])
 
 
-@pytest.mark.parametrize("m", [129, 143, 144, 145, 161, 176, 177, 300])
+@pytest.mark.parametrize("m", [64, 65, 80, 81, 96, 97, 127, 128, 129, 143, 144, 145, 161, 176, 177, 300])
 def test_ritz_matrix_block_edges(mla, m):
-    """The solver with a second matrix of scratch (Rayleigh-Ritz matrices above order 128): a block as wide as the space, so that
+    """The solver with a second matrix of scratch (Rayleigh-Ritz matrices above order 64): a block as wide as the space, so that
     the matrix is S in another basis.  Odd and even numbers of blocks of 16, a last one of one row and a full one; the bounds
     of the eigensolver by itself."""
     import torch
@@ -466,6 +466,29 @@ def test_ritz_matrix_block_edges(mla, m):
     assert np.abs(evals - np.linalg.eigvalsh(S)[::-1]).max() <= 1e-12 * norm
     assert np.abs(R.T @ R - np.eye(m)).max() <= 1e-12
     assert np.abs(S @ R - R * evals).max() <= 1e-12 * norm
+
+
+@pytest.mark.parametrize("g,d,M", [(33, 8, 2), (17, 16, 4), (32, 16, 4), (64, 4, 2)])
+def test_wide_groups_as_a_batch(mla, g, d, M):
+    """Groups of 66 to 128 components: the layer's bases from the solver over pairs of blocks, all groups at once, against the
+    one-workgroup solver's on the same moments (eigenvalues, and the projector on the leading half)."""
+    import torch
+    from paper_2502_07864_amd import convert
+    r = np.random.default_rng(g * d)
+    n, D, p = 150, 64, 20
+    t = lambda *s: torch.from_numpy(r.standard_normal(s)).cuda()
+    X, W_K, W_V = t(n, D) * torch.arange(1, D + 1, device="cuda", dtype=torch.float64) ** -0.7, t(g * d, D), t(g * d, D)
+    out = convert.convert_layer(X, W_K, W_V, t(2 * g * d - d // M, p), g, g, d, M, 8, 3, keep=1)
+    sigma = convert.rope_moments(convert.project(X, W_K), g, d, M)
+    evals, U, info = convert.sym_eig(sigma)
+    assert (out["info"][:-2] >= 1).all() and (info >= 1).all()
+    scale = evals[:, :1]
+    assert ((out["evals_rope"] - evals).abs() <= 1e-12 * scale).all()
+    half = evals.shape[1] // 4
+    for a, b in zip(out["U"], U):
+        assert (a.T @ a - torch.eye(len(a), device="cuda", dtype=torch.float64)).abs().max() <= 1e-12
+        pa, pb = a[:, :half] @ a[:, :half].T, b[:, :half] @ b[:, :half].T
+        assert (pa - pb).abs().max() <= 1e-8
 
 
 # ------------------------------------------------------------------ cache append
