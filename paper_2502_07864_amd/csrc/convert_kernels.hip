@@ -14,6 +14,7 @@ namespace conv {
 namespace {
 
 typedef double f64x4 __attribute__((ext_vector_type(4)));
+typedef double f64x2 __attribute__((ext_vector_type(2)));
 
 // ------------------------------------------------------------------ block reductions
 __device__ __forceinline__ double wave_sum(double v) {
@@ -957,55 +958,106 @@ __device__ __forceinline__ double read_lane(double v, int lane) {
     return __longlong_as_double((long)hi << 32 | lo);
 }
 
-// S (64 x 64, its lower half; nb rows and columns of it) = L L^T -> V = L^{-1}.  Four wavefronts; pivots not above
+// S (64 x 64, its lower half; nb rows and columns of it, identity below) = L L^T -> V = L^{-1}.  Four wavefronts; pivots not above
 // floor_v are replaced by it, counted and marked in *marks (bit: column).  What stands below such a pivot is rounding: L has
 // zeros there (here, and in the blocks below, whose kernel reads the marks).  Kept, it is divided by a pivot that may be
 // hundreds of times smaller, and from a block that lacks some ten ranks on the factors grew past 1e308.
+// Sixteen columns are one wavefront's chain, pivot after pivot (its lanes are the rows): the next column's multiplier by lane
+// reads, the others' through LDS, whose products come a pivot later, beside its chain (all by lane reads: 382 cycles a pivot, three
+// quarters of them for issuing reads and saving scalar registers; now 268).  Meanwhile the other wavefronts do what the caller
+// has left (`beside`: from column 16 on S has to be there behind it, and V zero), then the inverse's rows above.
 // WHOLE: nb = 64, known at compile time.
-template <bool WHOLE>
-__device__ __forceinline__ void factor_invert(double* S, double* V, double* dinv, int nb, double floor_v, int* bad,
-                                              unsigned long long* marks, int tid) {
-    const int lane = tid & 63, wave = tid >> 6, li = lane & 15, kq = lane >> 4;
-    for (int idx = tid; idx < 64 * CP; idx += 256) {
-        const int r = idx / CP, c = idx % CP;
-        V[idx] = 0.0;
-        if (r >= nb) S[idx] = r == c ? 1.0 : 0.0;        // rows past the end: identity
-    }
-    __syncthreads();
+template <bool WHOLE, class Beside>
+__device__ __forceinline__ void factor_invert(double* S, double* V, double* dinv, double* col, int nb, double floor_v, int* bad,
+                                              unsigned long long* marks, int tid, Beside beside) {
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), li = lane & 15, kq = lane >> 4;
     unsigned long long dropped = 0;
     const int nsb = WHOLE ? 4 : (nb + 15) / 16;          // parts of 16 that hold rows: the others are left alone
+    // row i of the inverse: X_ii by wavefront 1 (lane = column); X_ij = -X_ii sum_k L_ik X_kj, the sum beside it, the product behind
+    // a barrier, by wavefront 2 (j = 0), 3 (1) or 0 (2)
+    const int mj = wave == 0 ? 2 : wave == 1 ? 4 : wave - 2;
+    f64x4 sum = {0.0, 0.0, 0.0, 0.0};
+    auto inverse_row = [&](int i) {
+        if (wave == 1 && lane < 16) {
+            const double* L = S + 16 * i * (CP + 1);
+            double x[16];
+#pragma unroll
+            for (int r = 0; r < 16; ++r) x[r] = r == lane ? 1.0 : 0.0;
+#pragma unroll
+            for (int k = 0; k < 16; ++k) {               // (a row's terms in the order of k, the rows side by side)
+                x[k] *= dinv[16 * i + k];
+                V[(16 * i + k) * CP + 16 * i + lane] = x[k];
+#pragma unroll
+                for (int r = k + 1; r < 16; ++r) x[r] -= L[r * CP + k] * x[k];
+            }
+        }
+        if (mj < i) {
+            sum = (f64x4){0.0, 0.0, 0.0, 0.0};
+            for (int k = mj; k < i; ++k)
+#pragma unroll
+                for (int ks = 0; ks < 4; ++ks)
+                    sum = __builtin_amdgcn_mfma_f64_16x16x4f64(S[(16 * i + li) * CP + 16 * k + 4 * ks + kq], V[(16 * k + 4 * ks + kq) * CP + 16 * mj + li], sum, 0, 0, 0);
+        }
+    };
+    auto inverse_row_products = [&](int i) {
+        if (mj >= i) return;
+        f64x4 c = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks)                   // (a result tile lies in the lanes as the right operand does)
+            c = __builtin_amdgcn_mfma_f64_16x16x4f64(-V[(16 * i + li) * CP + 16 * i + 4 * ks + kq], sum[ks], c, 0, 0, 0);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) V[(16 * i + 4 * r + kq) * CP + 16 * mj + li] = c[r];
+    };
     for (int sb = 0; sb < nsb; ++sb) {
         const int s0 = sb * 16;
         if (wave == 0) {
-            double a[16], mine = 0.0;
+            double a[16], b[16];
 #pragma unroll
-            for (int c = 0; c < 16; ++c) a[c] = S[lane * CP + s0 + c];
+            for (int c = 0; c < 16; c += 2) {
+                const f64x2 v = *reinterpret_cast<const f64x2*>(S + lane * CP + s0 + c);
+                a[c] = v[0];
+                a[c + 1] = v[1];
+            }
+            double* const mine = col + lane;
+            const double* const theirs = col + s0;
             auto columns = [&](auto whole) {             // (whole: all 16 rows are there, and nothing asks)
 #pragma unroll
                 for (int j = 0; j < 16; ++j) {
+                    if (j > 0) {                         // the column before, of which only column j had its product
+#pragma unroll
+                        for (int k = j + 1; k < 16; ++k) a[k] -= a[j - 1] * b[k];
+                    }
                     if (!decltype(whole)::value && s0 + j >= nb) {       // a row past the end
-                        if (lane == s0 + j) mine = 1.0;
+#pragma unroll
+                        for (int k = j + 1; k < 16; ++k) b[k] = 0.0;
                         continue;
                     }
                     double d = read_lane(a[j], s0 + j);
                     if (__builtin_expect(!(d > floor_v), 0)) {
                         asm volatile("");                // (a branch: selects would lie in every pivot's chain)
                         d = floor_v;
-                        a[j] = 0.0;
+                        a[j] = lane == s0 + j ? d : 0.0;
                         dropped |= 1ull << (s0 + j);
                     }
-                    const double inv = inv_sqrt(d);      // (d is at least 1e-300)
-                    if (lane == s0 + j) { a[j] = d; mine = inv; }
-                    a[j] *= inv;
+                    a[j] *= inv_sqrt(d);                 // (d is at least 1e-300)
+                    if (j < 15) a[j + 1] -= a[j] * read_lane(a[j], s0 + j + 1);
+                    if (j < 14) {
+                        mine[64 * j] = a[j];
 #pragma unroll
-                    for (int k = j + 1; k < 16; ++k) a[k] -= a[j] * read_lane(a[j], s0 + k);
+                        for (int k = j + 2; k < 16; ++k) b[k] = theirs[64 * j + k];
+                    }
                 }
             };
             if (WHOLE || s0 + 16 <= nb) columns(std::true_type{});
             else                        columns(std::false_type{});
 #pragma unroll
-            for (int c = 0; c < 16; ++c) S[lane * CP + s0 + c] = lane >= s0 + c ? a[c] : 0.0;
-            if (lane >= s0 && lane < s0 + 16) dinv[lane] = mine;
+            for (int c = 0; c < 16; c += 2)
+                *reinterpret_cast<f64x2*>(S + lane * CP + s0 + c) = (f64x2){lane >= s0 + c ? a[c] : 0.0, lane > s0 + c ? a[c + 1] : 0.0};
+            if (lane >= s0 && lane < s0 + 16) dinv[lane] = 1.0 / S[lane * (CP + 1)];
+        } else if (sb == 0) {
+            beside(wave, lane);
+        } else {
+            inverse_row(sb - 1);
         }
         __syncthreads();
         // what is left of the block: 16 x 16 tiles (bi, bj), bi >= bj > sb
@@ -1021,57 +1073,49 @@ __device__ __forceinline__ void factor_invert(double* S, double* V, double* dinv
 #pragma unroll
             for (int r = 0; r < 4; ++r) S[(16 * bi + 4 * r + kq) * CP + 16 * bj + li] = c[r];
         }
-        __syncthreads();
+        if (sb > 0 && wave > 0) inverse_row_products(sb - 1);
+        if (sb + 1 < nsb) __syncthreads();
     }
     if (tid == 0) {
         *marks = dropped;
         if (dropped) atomicAdd(bad, __popcll(dropped));
     }
-    // inverse: diagonal 16 x 16 blocks, a wavefront each, lane = column ...
-    if (lane < 16 && wave < nsb) {
-        const double* L = S + 16 * wave * (CP + 1);
-        double x[16];
-#pragma unroll
-        for (int r = 0; r < 16; ++r) x[r] = r == lane ? 1.0 : 0.0;
-#pragma unroll
-        for (int k = 0; k < 16; ++k) {                   // (a row's terms in the order of k, the rows side by side)
-            x[k] *= dinv[16 * wave + k];
-            V[(16 * wave + k) * CP + 16 * wave + lane] = x[k];
-#pragma unroll
-            for (int r = k + 1; r < 16; ++r) x[r] -= L[r * CP + k] * x[k];
-        }
-    }
+    // (the last row's sums read what the last products have just written)
     __syncthreads();
-    // ... then X_ij = -X_ii sum_k L_ik X_kj, one distance from the diagonal after the other
-    for (int dist = 1; dist < nsb; ++dist) {
-        const int bi = dist + wave, bj = wave;
-        if (bi < nsb) {
-            f64x4 m = {0.0, 0.0, 0.0, 0.0}, c = {0.0, 0.0, 0.0, 0.0};
-            for (int k = bj; k < bi; ++k)
-#pragma unroll
-                for (int ks = 0; ks < 4; ++ks)
-                    m = __builtin_amdgcn_mfma_f64_16x16x4f64(S[(16 * bi + li) * CP + 16 * k + 4 * ks + kq], V[(16 * k + 4 * ks + kq) * CP + 16 * bj + li], m, 0, 0, 0);
-#pragma unroll
-            for (int ks = 0; ks < 4; ++ks)      // (a result tile lies in the lanes as the right operand does)
-                c = __builtin_amdgcn_mfma_f64_16x16x4f64(-V[(16 * bi + li) * CP + 16 * bi + 4 * ks + kq], m[ks], c, 0, 0, 0);
-#pragma unroll
-            for (int r = 0; r < 4; ++r) V[(16 * bi + 4 * r + kq) * CP + 16 * bj + li] = c[r];
-        }
-        __syncthreads();
-    }
+    inverse_row(nsb - 1);
+    __syncthreads();
+    inverse_row_products(nsb - 1);
+    __syncthreads();
 }
 
 // Linv: p rows of 64, the inverse of diagonal block k in rows 64 k ..; marks[k]: its clamped pivots.  k = -1: only the first
 // diagonal block.
 __global__ __launch_bounds__(256) void chol_step_kernel(double* G, double* X, double* Linv, unsigned long long* marks, int p, int k,
                                                         const double* __restrict__ floor_in, int* bad) {
-    __shared__ double A[NB * CP], Z[NB * CP], D[NB * CP], dinv[NB];
+    __shared__ __attribute__((aligned(16))) double A[NB * CP], Z[NB * CP], D[NB * CP], dinv[NB], col[16 * NB];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int k1 = k + 1, nb = min(NB, p - k1 * NB);
     int i = 0, j = 0;
+    const double floor_v = *floor_in;                    // (asked for here: in front of the first pivot half a microsecond)
+    auto clear = [&](int w, int l) {                     // (by the wavefront that has the least beside it)
+        if (w != 1) return;
+#pragma unroll 6
+        for (int q = 0; q < CP / 2; ++q) *reinterpret_cast<f64x2*>(D + 2 * (64 * q + l)) = (f64x2){0.0, 0.0};
+    };
+    auto factor = [&](double* S, auto beside) {
+        if (nb == NB) factor_invert<true>(S, D, dinv, col, nb, floor_v, bad, marks + k1, tid, beside);
+        else          factor_invert<false>(S, D, dinv, col, nb, floor_v, bad, marks + k1, tid, beside);
+    };
     if (k < 0) {
         double v[16];
         block_get(G, p, 0, 0, p, p, tid, v);
-        block_stage<false>(A, tid, v);
+#pragma unroll
+        for (int q = 0; q < 16; ++q) {                   // (rows past the end: identity)
+            const int r = (tid >> 6) + 4 * q, c = tid & 63;
+            A[r * CP + c] = r < nb ? v[q] : r == c ? 1.0 : 0.0;
+        }
+        __syncthreads();
+        factor(A, clear);
     } else {
         // tile of the lower triangle, row by row from row k + 1
         const int t = (k + 1) * (k + 2) / 2 + (int)blockIdx.x;
@@ -1094,12 +1138,12 @@ __global__ __launch_bounds__(256) void chol_step_kernel(double* G, double* X, do
             for (int q = 0; q < 16; ++q) vz[q] = (tid >> 6) + 4 * q == (tid & 63) ? 1.0 : 0.0;
         }
         f64x4 c[4], u[4];
-        const int row = i * NB + 16 * wave + (lane >> 4), col = j * NB + (lane & 15);
+        const int row = i * NB + 16 * wave + (lane >> 4), col0 = j * NB + (lane & 15);
 #pragma unroll
         for (int t = 0; t < 4; ++t)
 #pragma unroll
             for (int r = 0; r < 4; ++r)
-                c[t][r] = j != k && row + 4 * r < p && col + 16 * t < p ? C[(long)(row + 4 * r) * p + col + 16 * t] : 0.0;
+                c[t][r] = j != k && row + 4 * r < p && col0 + 16 * t < p ? C[(long)(row + 4 * r) * p + col0 + 16 * t] : 0.0;
         block_stage<false>(D, tid, vd);
         block_stage<false>(A, tid, va);
         if (square) {
@@ -1121,23 +1165,39 @@ __global__ __launch_bounds__(256) void chol_step_kernel(double* G, double* X, do
         block_put(A, wave, lane, l);
         if (!square) block_put(Z, wave, lane, u);
         __syncthreads();
-        block_nt<false>(A, square ? A : Z, wave, lane, u);
-        const bool next = i == k + 1 && j == k + 1;
+        if (!(i == k1 && j == k1)) {
+            block_nt<false>(A, square ? A : Z, wave, lane, u);
 #pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            c[t] -= u[t];
+            for (int t = 0; t < 4; ++t) {
+                c[t] -= u[t];
 #pragma unroll
-            for (int r = 0; r < 4; ++r)
-                if (!next && row + 4 * r < p && col + 16 * t < p) C[(long)(row + 4 * r) * p + col + 16 * t] = c[t][r];
+                for (int r = 0; r < 4; ++r)
+                    if (row + 4 * r < p && col0 + 16 * t < p) C[(long)(row + 4 * r) * p + col0 + 16 * t] = c[t][r];
+            }
+            return;
         }
-        if (!next) return;
+        // the next diagonal block goes to Z: its first 16 columns, then what is left of its lower half beside the first pivots
+        auto tile = [&](int t, f64x4 have) {             // tile (wave, t)
+            const double* x = A + (16 * wave + (lane & 15)) * CP + (lane >> 4);
+            const double* y = A + (16 * t + (lane & 15)) * CP + (lane >> 4);
+            f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+            for (int ks = 0; ks < 16; ++ks) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(x[4 * ks], y[4 * ks], acc, 0, 0, 0);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int rr = 16 * wave + 4 * r + (lane >> 4), cc = 16 * t + (lane & 15);
+                Z[rr * CP + cc] = rr < nb ? have[r] - acc[r] : rr == cc ? 1.0 : 0.0;
+            }
+        };
+        tile(0, c[0]);
         __syncthreads();
-        block_put(A, wave, lane, c);
+        factor(Z, [&](int w, int l) {
+            clear(w, l);
+#pragma unroll
+            for (int t = 1; t < 4; ++t)
+                if (t <= w) tile(t, c[t]);
+        });
     }
-    __syncthreads();
-    const int k1 = k + 1, nb = min(NB, p - k1 * NB);
-    if (nb == NB) factor_invert<true>(A, D, dinv, nb, *floor_in, bad, marks + k1, tid);
-    else          factor_invert<false>(A, D, dinv, nb, *floor_in, bad, marks + k1, tid);
     for (int idx = tid; idx < nb * NB; idx += 256) Linv[(long)k1 * NB * NB + idx] = D[(idx >> 6) * CP + (idx & 63)];
 }
 
