@@ -355,15 +355,17 @@ int mla_merge_out_proj_multi(const void* workspace, size_t workspace_bytes, cons
 }
 
 namespace {
+// (Sized for keys with their rope part and a page table for every pair, as callers have sized it: the pool uses four fifths of its
+// room, the table's stays empty.)
 struct PrefillWs {
-    size_t pool_off, table_off, lens_off, total;
+    size_t pool_off, lens_off, total;
 };
 PrefillWs prefill_ws(int B, int heads, int d_c, int max_pages)
 {
     PrefillWs w;
     w.pool_off = align_up((size_t)heads * 256 * d_c * 2, 256);                                   // after Wcat
-    w.table_off = w.pool_off + align_up((size_t)B * heads * max_pages * 64 * 320 * 2, 256);      // after the pool
-    w.lens_off = w.table_off + align_up((size_t)B * heads * max_pages * sizeof(int32_t), 256);
+    w.lens_off = w.pool_off + align_up((size_t)B * heads * max_pages * 64 * 320 * 2, 256) +
+                 align_up((size_t)B * heads * max_pages * sizeof(int32_t), 256);
     w.total = w.lens_off + align_up((size_t)B * heads * sizeof(int32_t), 256);
     return w;
 }

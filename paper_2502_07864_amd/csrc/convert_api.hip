@@ -302,7 +302,7 @@ int mla_convert_layer(const double* X, const double* W_K, const double* W_V, con
     // The power iteration needs the moment S = C^T C / n only in products with a block, 2 m^2 p operations each; by the factor they
     // take 4 n m p and S itself (n m^2) is not formed, but a step has one product more, which costs about 12 us (8e8 operations)
     // whatever its size.  Ms a layer by the factor / by S (20 iterations unless said): m = 8128, p = 768, 4096
-    // tokens 69.3 / 75.0; m = 4032, p = 560: 1024 19.7 / 22.9, 2048 23.4 / 23.9, 2300 25.8 / 25.5; m = 1984, p = 320: 512 9.13 / 9.31,
+    // tokens 69.3 / 75.0 (these with slower solvers); m = 4032, p = 560: 1024 19.7 / 22.9, 2048 23.4 / 23.9, 2300 25.8 / 25.5; m = 1984, p = 320: 512 9.13 / 9.31,
     // 768 9.46 / 9.44, 1100 9.90 / 9.61; 4 iterations 768 6.89 / 6.97, 1100 7.12 / 7.14, 1400 7.27 / 7.26; m = 480, p = 80: 64 2.92 / 2.92,
     // 256 3.12 / 2.93.
     // Fewer tokens than dimensions: with K = C C^T / n (n^2 m), S^iters Q = C^T K^(iters - 1) C Q / n, so that all steps but the ends

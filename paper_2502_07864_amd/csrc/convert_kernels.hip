@@ -903,11 +903,12 @@ __global__ __launch_bounds__(1024) void max_diag_kernel(const double* __restrict
 // one workgroup each, all products on v_mfma_f64_16x16x4_f64; every workgroup multiplies the L_ik and L_jk or X_kj it
 // needs itself (K = 64: 1 us each), so that nothing is written that another one reads and a column is one launch.  The
 // workgroup of the next diagonal block goes on to factor and invert it: sixteen columns at a time in one wavefront's
-// registers (lane = row, pivots and multipliers by lane reads), the rest of the block on the matrix cores.  What
+// registers (lane = row), the rest of the block on the matrix cores.  What
 // bounds it is that chain, column after column.  As separate kernels (block, panel solve, trailing product; then the
 // inverse row by row with two products each) order 768 took 1330 us, then 300 (a column 27.5); with the pivots' reciprocal
 // roots refined from the instruction's estimate, the rows of the small inverses side by side and one product for a square
-// tile 284 (24.1).  Parts of 16 and columns past the end of the last block are left out: a call of top_eig with 5 columns
+// tile 284 (24.1); with the multipliers through LDS and the inverse beside the pivots 232 (18.8: loads 2.7, products 3, pivots
+// 7.5, what is left between them 1.5, the inverse's last row 1.6).  Parts of 16 and columns past the end of the last block are left out: a call of top_eig with 5 columns
 // and 5 iterations (eight of these) 345 us as separate kernels, 455 with them, 370 without.
 constexpr int CP = 66;                     // row pitch of a block in LDS: 32 lanes that read 16 rows x 2 columns hit 32 units of 8 bytes
 

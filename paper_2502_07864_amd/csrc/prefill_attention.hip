@@ -25,8 +25,8 @@
 // than 2^64 above it is recorded and the workgroup then redoes its keys with the exact maxima (one sweep
 // that only scores, one that accumulates).
 //
-// What bounds it: power.  4 prompts of 8192 tokens, 32 heads (2.75 TFLOP): matrix pipes busy 60 % of 4.7 M cycles at 1.8 to 1.9 GHz;
-// a loop of the same instructions on registers alone sustains 2.0 PFLOP/s, of 32 x 32 x 16 ones 1.8 (not taken).  With a
+// What bounds it: power.  4 prompts of 8192 tokens, 32 heads (2.75 TFLOP): matrix pipes busy 57 to 60 % of 4.7 to 5.0 M cycles, at 1.77
+// to 1.9 GHz; a loop of the same instructions on registers alone sustains 2.0 PFLOP/s, of 32 x 32 x 16 ones 1.8 (not taken).  With a
 // barrier, five loads, ring slots modulo three and a scalar load of the page table on every tile (76 scalar instructions) the pipes
 // were busy 55 % of 5.1 M cycles at a higher clock: 8 % of the cycles gave 2 to 3 % of the time.  Scored, weighed and accumulated
 // one tile after the other from row-major values: 42 % of 6.7 M.  Whole call: 3036 us that way, then 2785, now 2736 in turn on one
