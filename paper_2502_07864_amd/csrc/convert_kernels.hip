@@ -882,21 +882,6 @@ __global__ __launch_bounds__(256) void jw_permute_kernel(double* __restrict__ A_
 // ------------------------------------------------------------------ Cholesky factor and its inverse
 constexpr int NB = 64;
 
-// floor for the pivots: 1e-13 of the largest diagonal entry
-__global__ __launch_bounds__(1024) void max_diag_kernel(const double* __restrict__ G, int p, double* __restrict__ floor_out) {
-    __shared__ double red[16];
-    double mx = 0.0;
-    for (int i = threadIdx.x; i < p; i += 1024) mx = fmax(mx, G[(long)i * p + i]);
-    for (int o = 32; o > 0; o >>= 1) mx = fmax(mx, __shfl_xor(mx, o));
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = mx;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        mx = 0.0;
-        for (int w = 0; w < 16; ++w) mx = fmax(mx, red[w]);
-        *floor_out = fmax(mx * 1e-13, 1e-300);
-    }
-}
-
 // One launch per block column k eliminates it from both halves of [G | I]: tile (i, j) of 64 x 64 with i > k is
 //     j > k:  G_ij -= L_ik L_jk^T,      L_ik = G_ik L_kk^{-T}
 //     j <= k: B_ij -= L_ik X_kj,        X_kj = L_kk^{-1} B_kj      (B starts as I and lives in X)
@@ -1090,14 +1075,14 @@ __device__ __forceinline__ void factor_invert(double* S, double* V, double* dinv
 }
 
 // Linv: p rows of 64, the inverse of diagonal block k in rows 64 k ..; marks[k]: its clamped pivots.  k = -1: only the first
-// diagonal block.
+// diagonal block, and the floor.
 __global__ __launch_bounds__(256) void chol_step_kernel(double* G, double* X, double* Linv, unsigned long long* marks, int p, int k,
-                                                        const double* __restrict__ floor_in, int* bad) {
+                                                        double* floor_at, int* bad) {
     __shared__ __attribute__((aligned(16))) double A[NB * CP], Z[NB * CP], D[NB * CP], dinv[NB], col[16 * NB];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int k1 = k + 1, nb = min(NB, p - k1 * NB);
     int i = 0, j = 0;
-    const double floor_v = *floor_in;                    // (asked for here: in front of the first pivot half a microsecond)
+    double floor_v = k < 0 ? 0.0 : *floor_at;            // (asked for here: in front of the first pivot half a microsecond)
     auto clear = [&](int w, int l) {                     // (by the wavefront that has the least beside it)
         if (w != 1) return;
 #pragma unroll 6
@@ -1108,14 +1093,21 @@ __global__ __launch_bounds__(256) void chol_step_kernel(double* G, double* X, do
         else          factor_invert<false>(S, D, dinv, col, nb, floor_v, bad, marks + k1, tid, beside);
     };
     if (k < 0) {
-        double v[16];
+        double v[16], mx = 0.0;
         block_get(G, p, 0, 0, p, p, tid, v);
+        // floor for the pivots: 1e-13 of the largest diagonal entry (a launch of its own took 4.6 us)
+        for (int d = tid; d < p; d += 256) mx = fmax(mx, G[(long)d * p + d]);
+        for (int o = 32; o > 0; o >>= 1) mx = fmax(mx, __shfl_xor(mx, o));
+        if (lane == 0) dinv[wave] = mx;
 #pragma unroll
         for (int q = 0; q < 16; ++q) {                   // (rows past the end: identity)
             const int r = (tid >> 6) + 4 * q, c = tid & 63;
             A[r * CP + c] = r < nb ? v[q] : r == c ? 1.0 : 0.0;
         }
         __syncthreads();
+        floor_v = fmax(fmax(fmax(dinv[0], dinv[1]), fmax(dinv[2], dinv[3])) * 1e-13, 1e-300);
+        if (tid == 0) *floor_at = floor_v;
+        __syncthreads();                                 // (dinv is the factor's from here on)
         factor(A, clear);
     } else {
         // tile of the lower triangle, row by row from row k + 1
@@ -1436,8 +1428,7 @@ hipError_t launch_chol_inverse(double* G, double* X, double* tmp, int p, int* ba
     double* floor_v = tmp;                 // one double
     auto* marks = reinterpret_cast<unsigned long long*>(tmp + 1);      // a word per block column
     double* Linv = tmp + CHOL_HEAD;        // p x 64
-    max_diag_kernel<<<1, 1024, 0, s>>>(G, p, floor_v);
-    hipError_t e = hipGetLastError();
+    hipError_t e = hipSuccess;
     const int nblk = (p + NB - 1) / NB;
     for (int k = -1; k < nblk - 1 && e == hipSuccess; ++k) {
         const int tiles = k < 0 ? 1 : nblk * (nblk + 1) / 2 - (k + 1) * (k + 2) / 2;
