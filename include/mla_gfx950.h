@@ -108,7 +108,7 @@ int mla_out_proj(const void* o_lat, const void* W_UV, void* out,
 
 /*
  * Bytes of device workspace mla_decode_paged needs for these sizes (split-KV
- * partial results for B * (S + 1) chunks, S at its largest as described under num_splits:
+ * partial results for B * (S + 1) chunks, S as described under num_splits:
  * partial outputs in the io dtype, sized here as if they were fp32, and fp32
  * log-sum-exps; plus a [B, 2] int32 table the balanced partition uses).  The
  * same size serves both partitions and both io dtypes.  What the workspace
@@ -149,18 +149,21 @@ size_t mla_decode_workspace_bytes(int B, int H, int d_c, int num_splits);
  *              bytes, 256-byte aligned; contents are scratch
  *   num_splits >= 1: each sequence's page list is cut into S contiguous
  *              chunks of ceil(max_pages_per_seq / S) pages (trailing chunks of
- *              short sequences are empty), S = num_splits, or up to 4x that
- *              as long as B * S stays below one workgroup per compute unit
- *              (mla_decode_workspace_bytes accounts for it).  Every chunk is reduced with its own running
+ *              short sequences are empty), S = num_splits, or 2x / 4x that
+ *              while B * S stays below 256 (so a small batch still gives
+ *              every compute unit a workgroup; mla_decode_workspace_bytes
+ *              accounts for it).  Every chunk is reduced with its own running
  *              softmax and the chunks are merged by log-sum-exp.  The result
- *              does not depend on the chunking beyond fp32 rounding.
+ *              depends on the chunking by fp32 rounding and by the rounding of
+ *              the chunks' partial outputs, which are stored in the io dtype.
  *              With MLA_FLAG_BALANCED (matrix-core kernels with page_size 64
  *              only, otherwise MLA_ERR_UNSUPPORTED) the cut is made differently: the page lists
- *              of all sequences, laid end to end, are cut into at most B * S
- *              ranges of equal length (+-1 page), one per workgroup; a range that
+ *              of all sequences, laid end to end, are cut into B * S ranges of
+ *              equal length (+-1 page), one per workgroup, or fewer where those
+ *              fill one round of the compute units; a range that
  *              crosses sequence boundaries gives one chunk per sequence.  Every
  *              workgroup then streams the same number of bytes whatever the
- *              mix of sequence lengths.  Same results up to fp32 rounding.
+ *              mix of sequence lengths.  Same results up to that rounding.
  *   softmax_scale  the paper uses 1/sqrt(d_head + d_rope) for MLA
  *
  * Supported: io/cache dtype pairs (F32,F32), (BF16,BF16), (BF16,FP8_E4M3),

@@ -15,7 +15,10 @@ bool io_ok(mla_dtype t) { return t == MLA_F32 || t == MLA_BF16; }
 size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 // The most chunks that a request of num_splits chunks per sequence is cut into: x2 or x4 where the batch is too small for num_splits
-// to give every CU a workgroup.  Workspaces are sized for it.
+// to give every CU a workgroup.  Workspaces are sized for it, and the uniform partition is cut so: its chunks are parts of the page
+// table's width, which sequences may fill or not, and the lengths lie in device memory.  Fewer, longer chunks for one round of
+// workgroups are faster where all sequences fill the table (step, us, 3 x 8192 tokens 26.7 / 18.8, 20 x 8192 52.6 / 44.1) and slower
+// where they don't: 50 x 4096 of 16384 60.4 / 100.9, 30 x 4096 of 16384 40.8 / 65.7, 1 x 40000 beside 29 x 2500 78.8 / 142.6.
 int most_splits(int B, int num_splits)
 {
     int m = 1;
@@ -23,27 +26,25 @@ int most_splits(int B, int num_splits)
     return num_splits * m;
 }
 
-// Chunks actually used (decode and merge derive them from this same rule).  As many as make one round of
-// workgroups, one per CU (a workgroup's ring of tiles fills the LDS) and per group of 64 query rows (balanced partition: 32): a second
-// round that is not full costs a whole one.  Step, us, at doubled chunks / at those of one round: 3 x 8192 tokens 26.7 (384 workgroups)
-// / 18.8, 5 x 8192 29.1 / 22.0, 20 x 8192 52.6 (480) / 44.1, 50 x 8192 95.8 (500) / 90.1, 100 x 5000 119.6 (400) / 109.2; fp8 7 x 16384
-// 40.0 / 31.1; 12 x 4096, 16-row pages 39.2 / 31.9; two query tokens 20 x 8192 67.2 / 54.4, three (two groups of rows) 3 x 12000 59.2 /
-// 32.1; fp32 5 x 4000 94.3 / 94.5, 8 x 4000 130.8 / 125.7.  Between 64 and 85 chunks of three sequences the merge decides (more than 64 take
-// its longer form): 64, 20.5 against 22.2 at 12000 tokens.  The uniform partition keeps at least the chunks asked for (its
-// chunks may be uneven); the ranges of the balanced one are equal, and fewer of them fill the round: 70 x 14285 ragged tokens, four asked
-// for, 167.0 / 122.7, 100 x 10000 140.3 / 127.4, 40 x 16384 107.1 (eight) / 85.1; 64 heads 64 x 7812 113.9 / 102.9.
+// Chunks actually used (decode and merge derive them from this same rule).  The ranges of the balanced partition are equal whatever
+// the lengths, and a workgroup has its CU to itself (the ring of tiles fills the LDS), one per range and group of 32 query rows.  So
+// fewer of them where they make one round that fills more than half of the chip and gives a CU no more pages than the rounds of the
+// shorter ranges would, the last of which is rarely full.  Step, us, ranges per sequence -> fewer: 70 sequences of 300 to 6000 tokens 87.9
+// (4) -> 67.9 (3), 100 94.7 (4) -> 85.2 (2), fp8 86.0 -> 79.9, 40 of 800 to 16000 100.6 (8) -> 78.9 (6), 200 of 300 to 6000 172.4 (2) ->
+// 157.4 (1).  Not taken: 129 sequences 118.1 (3), would be 128.9 (1), 129 workgroups; 170, d_c = 256 87.0 (3), 101.3 (1); 64 heads, 70
+// sequences 113.0 (4), 125.3 (1): more pages for a CU in one round than in the old ones.
 int used_splits(int B, int H, int num_splits, bool balanced)
 {
-    const long groups = balanced ? (H + 31) / 32 : (H + 63) / 64;
-    const long round = 256 / (B * groups);
-    if (balanced) return (int)std::max(1L, std::min(4L * num_splits, round));
-    if (round <= num_splits) return num_splits;
-    const long S = std::min(4L * num_splits, round);
-    return (int)(S > 64 && round < 128 ? std::max(64, num_splits) : S);
+    const int most = most_splits(B, num_splits);
+    if (!balanced) return most;
+    const long each = (long)B * ((H + 31) / 32);
+    const long one = std::min(4L * num_splits, 256 / each);           // (0: a range per sequence is more than a round)
+    const long rounds = (each * most + 255) / 256;
+    return each * one > 130 && rounds * one >= most ? (int)one : most;
 }
 
 // Workspace: partial outputs, partial log-sum-exps, plan.  Sized for B * (S + 1) partial slots, S = most_splits:
-// the uniform partition uses at most B * S of them ([B, H, S, d_c]), the balanced one up to B * S + B - 1
+// the uniform partition uses B * S of them ([B, H, S, d_c]), the balanced one up to B * S + B - 1
 // ([slot, H, d_c]); the plan ([B, 2] int32) is written and read by the balanced partition only.
 struct WsLayout {
     size_t lse_off, plan_off, total;

@@ -278,6 +278,73 @@ def test_chunks_of_one_round(mla, B, splits, T, H, cache, flags):
     check_multi(mla, w, T, splits, flags, fused_tail=True)
 
 
+def cut(B, rows, num_splits, balanced):
+    """The library's choice of chunks (ranges) per sequence: the most, and those used."""
+    m = 1
+    while m < 4 and B * num_splits * m < 256:
+        m *= 2
+    most, each = num_splits * m, B * -(-rows // 32)
+    one = min(4 * num_splits, 256 // each)
+    return most, one if balanced and each * one > 130 and -(-each * most // 256) * one >= most else most
+
+
+def partials(mla, w, table, T, splits, flags):
+    """What a decode call leaves for the merge: log-sum-exps and plan, at their places in the workspace."""
+    import torch
+    d = DeviceWorkload(w)
+    lead = (w.B, T, w.H) if T > 1 else (w.B, w.H)
+    io = torch.float32 if w.io_dtype == "f32" else torch.bfloat16
+    q, qr = torch.randn(*lead, w.d_c, device="cuda").to(io), torch.randn(*lead, 64, device="cuda").to(io)
+    rows = T * w.H
+    ws = torch.zeros(mla.decode_workspace_bytes(w.B, rows, w.d_c, splits), dtype=torch.uint8, device="cuda")
+    (mla.decode_paged_multi if T > 1 else mla.decode_paged)(q, qr, d.pool, to_torch(table, "i32"), d.seq_lens, w.softmax_scale, num_splits=splits,
+                                                            kv_scale=d.kv_scale, workspace=ws, flags=flags | mla.FLAG_SKIP_MERGE)
+    torch.cuda.synchronize()
+    slots = w.B * (cut(w.B, rows, splits, False)[0] + 1)
+    up = lambda n: -(-n // 256) * 256
+    lse_at = up(slots * rows * w.d_c * 4)
+    plan_at = lse_at + up(slots * rows * 4)
+    host = ws.cpu().numpy()
+    return host[lse_at:lse_at + slots * rows * 4].view(np.float32), host[plan_at:plan_at + 8 * w.B].view(np.int32).reshape(-1, 2)
+
+
+@pytest.mark.parametrize("B,splits,T,H,cache,page,width,lens", [
+    (30, 8, 1, 16, "bf16", 64, 256, [4096]), (20, 12, 1, 16, "fp8_e4m3", 64, 256, [4096]), (9, 28, 2, 32, "bf16", 64, 256, [4000, 70, 0]),
+    (7, 31, 1, 32, "bf16", 16, 500, [1000]), (3, 32, 1, 32, "bf16", 64, 500, [1000]), (30, 8, 1, 16, "bf16", 64, 157, [10000] + 29 * [500]),
+    (6, 31, 1, 8, "f32", 64, 125, [1000]), (16, 16, 1, 16, "bf16", 64, 256, [4096])])
+def test_uniform_chunks_of_short_sequences(mla, B, splits, T, H, cache, page, width, lens):
+    """Sequences much shorter than the page table is wide, or than the longest of the batch: as many chunks as the request gives
+    them, whatever number would make one round of workgroups were all of them full (chunks of such a round left fewer workgroups
+    with more pages each: 30 sequences of 4096 tokens in a table of 16384 took 1.6 times as long)."""
+    w = synth.make_workload("short", B=B, H=H, d_head=128, d_c=256, d_rope=64, seq_lens=[lens[i % len(lens)] for i in range(B)],
+                            io_dtype="f32" if cache == "f32" else "bf16", cache_dtype=cache, page_size=page, free_frac=0.1, seed=137)
+    table = np.full((B, width), -1, dtype=np.int32)
+    table[:, :w.page_table.shape[1]] = w.page_table
+    lse, _ = partials(mla, w, table, T, splits, 0)
+    S = cut(B, T * H, splits, False)[1]
+    got = np.isfinite(lse[:B * T * H * S].reshape(B, T * H, S))
+    first = np.arange(S) * -(-width // S) * page                   # of every chunk
+    seen = np.asarray(w.seq_lens)[:, None] - (T - 1 - np.arange(T * H) // H)
+    assert (got == (first < seen[..., None])).all()
+
+
+@pytest.mark.parametrize("B,splits,H,cache", [(129, 3, 16, "bf16"), (130, 4, 64, "bf16"), (70, 4, 64, "fp8_e4m3"), (170, 3, 32, "bf16"), (100, 4, 128, "bf16"),
+                                              (70, 4, 16, "bf16"), (100, 4, 28, "fp8_e4m3"), (40, 8, 64, "bf16"), (200, 2, 32, "bf16"), (64, 4, 16, "bf16")])
+def test_balanced_ranges_of_one_round(mla, B, splits, H, cache):
+    """Fewer ranges than asked for only where a workgroup of the one round has no more pages than the rounds of the others add up
+    to, and the round fills more than half of the chip (129 sequences, one range each where three were asked for: 1.13 times as
+    long); the plan names the ranges of exactly that number."""
+    w = synth.make_workload("ranges", B=B, H=H, d_head=128, d_c=256, d_rope=64, seq_lens=[(97 * i) % 700 for i in range(B)],
+                            io_dtype="bf16", cache_dtype=cache, free_frac=0.1, seed=138)
+    _, plan = partials(mla, w, w.page_table, 1, splits, mla.FLAG_BALANCED)
+    G = B * cut(B, H, splits, True)[1]
+    pages = -(-np.asarray(w.seq_lens, dtype=np.int64) // 64)
+    end, total = np.cumsum(pages), int(pages.sum())
+    first, last = ((end - pages + 1) * G - 1) // total, (end * G - 1) // total
+    want = np.where(pages[:, None] > 0, np.stack([first + np.arange(B), last - first + 1], 1), 0)
+    assert (plan == want).all()
+
+
 @pytest.mark.parametrize("L,drop,late", [(4095, (), 0), (4096, (62, 63), 0), (4097, (64,), 0), (4161, (), 4100), (8191, (63, 64, 127), 8190), (16449, (255, 256), 0)])
 def test_prefill_page_ids_64_at_a_time(mla, L, drop, late):
     """Contexts around 64 and 256 pages, whose ids a wavefront holds 64 at a time: pages outside the pool on both sides of a border (the
