@@ -254,19 +254,23 @@ __global__ __launch_bounds__(64 * PR_WAVES) void decode_portable_kernel(DecodePa
         }
     };
 
+    // Whether there is a next batch is asked everywhere but in the four-wavefront form of four heads on fp8 caches, where the question
+    // took 2 % more time (100 sequences of 2000 rows, 32 heads, d_c = 256: 542 us without, 554 with) and elsewhere up to 4 % less:
+    // that form requests one more whose rows are all absent.
+    constexpr bool NO_QUESTION = PR_WAVES == 4 && HG == 4 && std::is_same<CT, fp8_tag>::value;
     if (jb < j1) {
         Batch x0, x1;
         fetch(at, sc_at, x0);
         locate(jb + jstep, at, sc_at);
         while (true) {
-            if (jb + jstep < j1) {               // the next batch
+            if (NO_QUESTION || jb + jstep < j1) {            // the next batch
                 fetch(at, sc_at, x1);
                 locate(jb + 2 * jstep, at, sc_at);
             }
             consume(x0, jb);
             jb += jstep;
             if (jb >= j1) break;
-            if (jb + jstep < j1) {
+            if (NO_QUESTION || jb + jstep < j1) {
                 fetch(at, sc_at, x0);
                 locate(jb + 2 * jstep, at, sc_at);
             }
