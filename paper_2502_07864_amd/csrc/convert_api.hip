@@ -305,20 +305,25 @@ int mla_convert_layer(const double* X, const double* W_K, const double* W_V, con
     // tokens 69.3 / 75.0 (these with slower solvers); m = 4032, p = 560: 1024 19.7 / 22.9, 2048 23.4 / 23.9, 2300 25.8 / 25.5; m = 1984, p = 320: 512 9.13 / 9.31,
     // 768 9.46 / 9.44, 1100 9.90 / 9.61; 4 iterations 768 6.89 / 6.97, 1100 7.12 / 7.14, 1400 7.27 / 7.26; m = 480, p = 80: 64 2.92 / 2.92,
     // 256 3.12 / 2.93.
-    // Fewer tokens than dimensions: with K = C C^T / n (n^2 m), S^iters Q = C^T K^(iters - 1) C Q / n, so that all steps but the ends
-    // of the first and the last are products of 2 n^2 p among n rows, as their orthonormal blocks are; a Cholesky pass more of the m
-    // rows, 2.4e7 p operations' time.  The better of the others / by K: 8128, 768, 4096 tokens 63.4 / 42.8; 4032, 768: 768 23.6 / 20.1,
-    // 2016 29.0 / 23.3, 3024 30.0 / 27.1, 3830 30.9 / 31.1; 1984, 320: 320 7.8 / 7.2, 992 8.7 / 8.2, 1884 8.9 / 9.1.
+    // Fewer tokens than dimensions: with K = C C^T / n (n^2 m, at three quarters of the other products' rate: equal tiles in rounds that
+    // do not come out even), S^iters Q = C^T K^(iters - 1) C Q / n, so that all steps but the ends of the first and the last are
+    // products of 2 n^2 p among n rows, as their orthonormal blocks are.  A Cholesky pass more of the m rows takes 3e7 p operations'
+    // time, and a step or three among n rows do not make up for it and for the launch of K: never one, and 2.4e9 more up to four.
+    // The better of the others / by K, ms: 8128, 768, 4096 tokens 63.4 / 42.8 (with slower solvers); 4032, 768: 2000 tokens 20.2 / 15.6, 3000
+    // 22.3 / 18.6, 3800 22.6 / 22.9 (not taken); 1984, 64, 1000 tokens: 20 iterations 2.47 / 2.18, 4 1.450 / 1.445 and 3 1.419 / 1.458 (neither
+    // taken), 1 1.436 / 1.524.
     Symmetric moment{nullptr, w.C, n, w.S};
     const double by_factor = (4.0 * iters + 2.0) * n * mj * p + 1.0 * n * p * p + 8e8 * iters;
     const double by_moment = 1.0 * n * mj * mj + (2.0 * iters + 2.0) * mj * mj * p + 2.0 * mj * p * p;
-    const double by_tokens = 1.0 * n * n * mj + 2.0 * (iters - 1) * n * n * p + 6.0 * n * mj * p + 1.0 * n * p * p +
-                             2.0 * (mj - 1.0 * iters * (mj - n)) * p * p + 2.4e7 * p;
-    if (iters >= 1 && n >= p && n < mj && by_tokens < std::min(by_moment, by_factor)) {
+    const double by_tokens = 1.3 * n * n * mj + 2.0 * (iters - 1) * n * n * p + 6.0 * n * mj * p + 1.0 * n * p * p +
+                             2.0 * (mj - 1.0 * iters * (mj - n)) * p * p + 3e7 * p + (iters <= 4 ? 2.4e9 : 0.0);
+    if (iters > 1 && n >= p && n < mj && by_tokens < std::min(by_moment, by_factor)) {
         GemmF64 cct = gemm_nt(w.C, mj, w.C, mj, w.S, n, n, n, mj, 1.0 / (double)n);
         cct.symmetric = 1;
-        cct.partial = top.part;
-        cct.partial_doubles = top.part_doubles;
+        // (scratch for its shares: what S would have taken beyond K, unless n is nearly m)
+        const size_t beyond = s_doubles - (size_t)n * n;
+        cct.partial = beyond > top.part_doubles ? w.S + (size_t)n * n : top.part;
+        cct.partial_doubles = std::max(beyond, top.part_doubles);
         MLA_TRY(launch_gemm_f64(cct, s));
         moment.K = w.S;
     } else if (by_moment <= by_factor || (size_t)n * p > s_doubles) {

@@ -308,41 +308,24 @@ def test_gpu_converted_layer_decodes_like_the_oracles_converted_layer(cv, M, kee
     assert np.abs(got - want).max() < 2e-5 * max(1.0, np.abs(want).max())
 
 
-def iterates_by_the_factor(n, m, p, iters):
-    """The library's choice between C^T (C Q) / n and S Q in the power iteration: operations, 8e8 for a step's extra product."""
-    by_factor = (4 * iters + 2) * n * m * p + n * p * p + 8e8 * iters
-    return by_factor < n * m * m + (2 * iters + 2) * m * m * p + 2 * m * p * p and n * p <= m * m
+def iteration_form(n, m, p, iters):
+    """The library's choice for the power iteration, by operations: products with C^T (C Q) / n ("factor"; 8e8 for a step's extra
+    product), with S itself ("moment"), or with C C^T / n among the tokens ("tokens")."""
+    factor = (4 * iters + 2) * n * m * p + n * p * p + 8e8 * iters
+    moment = n * m * m + (2 * iters + 2) * m * m * p + 2 * m * p * p
+    tokens = (1.3 * n * n * m + 2 * (iters - 1) * n * n * p + 6 * n * m * p + n * p * p + 2 * (m - iters * (m - n)) * p * p + 3e7 * p +
+              (2.4e9 if iters <= 4 else 0))
+    if iters > 1 and p <= n < m and tokens < min(factor, moment):
+        return "tokens"
+    return "moment" if moment <= factor or n * p > m * m else "factor"
 
 
-@pytest.mark.parametrize("g,d,n,p,iters,by_factor", [(8, 128, 300, 128, 20, True), (8, 128, 330, 128, 20, False), (8, 128, 129, 127, 4, True),
-                                                     (4, 64, 100, 80, 20, False), (8, 64, 40, 512, 20, True)])
-def test_convert_layer_iterates_as_top_eig_does(cv, g, d, n, p, iters, by_factor):
-    """Both forms of the iteration, on both sides of the rule, against top_eig of the moment itself from the same block: the
-    values to rounding, the spaces as far as blocks of condition 1e6 to 1e7 leave them (1.6e-5, four times that)."""
-    M, keep, D, r_kv = 2, 1, 256, min(64, n // 2)
+def check_iteration(cv, X, W_K, W_V, Q0, g, d, p, iters, r_kv, form):
+    """The layer's leading eigenpairs against top_eig of the moment itself from the same block: the values to rounding, the
+    spaces as far as blocks of condition 1e6 to 1e7 leave them (1.6e-5, four times that).  Both info entries of the layer."""
+    M, keep, n = 2, 1, len(X)
     d_rope = co.rope_width(d, M, keep)
-    m = 2 * g * d - d_rope
-    assert iterates_by_the_factor(n, m, p, iters) == by_factor
-    X, W_K, W_V, Q0 = chain_case(g, g, d, D, n, M, keep, r_kv, p, seed=n)
-    out = cv.convert_layer(dev(X), dev(W_K), dev(W_V), dev(Q0), g, g, d, M, r_kv, iters=iters, keep=keep)
-    W_rot = cv.rotate_rows(dev(W_K), out["U"], g, d, M, keep)
-    S, _ = cv.joint_moment(cv.project(dev(X), W_rot[d_rope:].contiguous()), cv.project(dev(X), dev(W_V)), out["alpha"])
-    evals, R, info = (host(x) for x in cv.top_eig(S, dev(Q0), r_kv, iters))
-    got = host(out["evals_joint"])
-    assert host(out["info"])[-1] >= 1 and info[1] >= 1
-    assert np.abs(got[:r_kv] - evals[:r_kv]).max() < 1e-10 * evals[0]
-    assert projector_gap(host(out["R_KV"]), R) < 6e-5
-
-
-@pytest.mark.parametrize("g,d,n,p,iters", [(8, 128, 128, 128, 20), (8, 128, 131, 128, 20), (8, 128, 1201, 130, 20), (8, 64, 950, 65, 20),
-                                           (8, 128, 500, 100, 2), (8, 128, 300, 64, 1), (4, 64, 479, 40, 30)])
-def test_convert_layer_iterates_among_tokens(cv, g, d, n, p, iters):
-    """Few tokens: the steps of the iteration as products with C C^T, whose blocks have a row per token (square blocks, odd
-    sizes, one step, nearly as many tokens as dimensions).  Against top_eig of the moment itself from the same block, with the
-    bounds of the other forms."""
-    M, keep, D, r_kv = 2, 1, 256, min(32, p // 2)
-    d_rope = co.rope_width(d, M, keep)
-    X, W_K, W_V, Q0 = chain_case(g, g, d, D, n, M, keep, r_kv, p, seed=n)
+    assert iteration_form(n, 2 * g * d - d_rope, p, iters) == form
     out = cv.convert_layer(dev(X), dev(W_K), dev(W_V), dev(Q0), g, g, d, M, r_kv, iters=iters, keep=keep)
     W_rot = cv.rotate_rows(dev(W_K), out["U"], g, d, M, keep)
     S, _ = cv.joint_moment(cv.project(dev(X), W_rot[d_rope:].contiguous()), cv.project(dev(X), dev(W_V)), out["alpha"])
@@ -350,6 +333,39 @@ def test_convert_layer_iterates_among_tokens(cv, g, d, n, p, iters):
     assert host(out["info"])[-1] >= 1 and info[1] >= 1
     assert np.abs(host(out["evals_joint"])[:r_kv] - evals[:r_kv]).max() < 1e-10 * evals[0]
     assert projector_gap(host(out["R_KV"]), R) < 6e-5
+    return host(out["info"])[-2:]
+
+
+@pytest.mark.parametrize("g,d,n,p,iters,form", [
+    (8, 128, 300, 128, 20, "tokens"), (8, 128, 330, 128, 20, "tokens"), (8, 128, 129, 127, 4, "factor"), (4, 64, 100, 80, 20, "moment"),
+    (8, 64, 40, 512, 20, "factor"), (8, 64, 138, 512, 20, "factor"), (8, 64, 139, 512, 20, "moment"), (8, 128, 1290, 320, 4, "factor"),
+    (8, 128, 1291, 320, 4, "moment"), (8, 128, 1215, 64, 5, "tokens"), (8, 128, 1216, 64, 5, "factor"), (8, 128, 1672, 64, 20, "tokens"),
+    (8, 128, 1673, 64, 20, "moment"), (8, 64, 550, 64, 20, "tokens"), (8, 64, 551, 64, 20, "moment"), (8, 128, 127, 127, 20, "tokens"),
+    (8, 128, 126, 127, 20, "factor"), (8, 128, 500, 100, 2, "factor"), (8, 128, 300, 64, 1, "factor"), (4, 64, 479, 40, 30, "moment"),
+    (8, 64, 950, 65, 20, "moment")])
+def test_convert_layer_iterates_as_top_eig_does(cv, g, d, n, p, iters, form):
+    """The three forms of the iteration, on both sides of every border between them."""
+    X, W_K, W_V, Q0 = chain_case(g, g, d, 256, n, 2, 1, min(64, n // 2), p, seed=n)
+    check_iteration(cv, X, W_K, W_V, Q0, g, d, p, iters, min(64, n // 2, p), form)
+
+
+@pytest.mark.parametrize("g,d,n,p,iters", [(8, 128, 128, 128, 20), (8, 128, 131, 128, 20), (8, 128, 1201, 130, 20), (8, 64, 65, 65, 20), (8, 64, 549, 130, 20),
+                                           (8, 128, 1100, 100, 5), (16, 128, 100, 20, 4), (16, 128, 619, 320, 4), (16, 128, 1250, 768, 3), (4, 64, 40, 40, 60)])
+def test_convert_layer_iterates_among_tokens(cv, g, d, n, p, iters):
+    """Few tokens: the steps of the iteration as products with C C^T, whose blocks have a row per token (square blocks, odd
+    sizes, as few steps and as many tokens as the rule takes, scratch for the shares of C C^T beyond it or elsewhere)."""
+    X, W_K, W_V, Q0 = chain_case(g, g, d, 256, n, 2, 1, min(32, p // 2), p, seed=n)
+    check_iteration(cv, X, W_K, W_V, Q0, g, d, p, iters, min(32, p // 2), "tokens")
+
+
+@pytest.mark.parametrize("n,p,rank", [(300, 64, 40), (128, 128, 100), (700, 130, 33)])
+def test_convert_layer_among_tokens_of_low_rank(cv, n, p, rank):
+    """Activations of lower rank than the block is wide: pivots of every step are clamped among the tokens too, and counted; the
+    directions that are there come out as from the moment itself."""
+    X, W_K, W_V, Q0 = chain_case(8, 8, 128, 256, n, 2, 1, 16, p, seed=n)
+    mix = rng(n).standard_normal((n, rank)) / np.sqrt(rank)
+    info = check_iteration(cv, mix @ X[:rank], W_K, W_V, Q0, 8, 128, p, 20, 16, "tokens")
+    assert info[0] >= 20 * (p - rank)
 
 
 # ------------------------------------------------------------------ the benchmark shape, by properties
