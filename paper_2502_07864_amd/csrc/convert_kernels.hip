@@ -521,8 +521,10 @@ __global__ __launch_bounds__(1024) void jacobi_kernel(double* A_all, double* eva
 // Block Jacobi over the chip: the indices are cut into blocks of 16; a step of the round-robin schedule over the
 // blocks takes disjoint pairs of blocks.  The workgroup of pair P = (I, J) rotates the 32 x 32 matrix A[P, P] in LDS,
 // accumulating its rotations in a 32 x 32 orthogonal matrix Z_P: every index of I with every one of J, and in every fourth
-// step those inside I and J first (they meet again in the next pairs; sweeps that took all 31 rotation steps every time
-// converged no sooner, on full, graded, low-rank and multiple spectra).  The tiles' workgroups apply the rotations:
+// step those inside I and J first (they meet again in the next pairs).  Sweeps that took all 31 rotation steps every time
+// converged no sooner on full and graded spectra; on low ranks and multiple eigenvalues a sweep sooner as a rule up to order 200,
+// two at most (order 144 of rank 72 15 sweeps / 17, 160 with four eigenvalues 22 / 23), and as often later above (300 with three 25 / 24).
+// The tiles' workgroups apply the rotations:
 // A[P, Q] <- Z_P^T A[P, Q] Z_Q, V[:, Q] <- V[:, Q] Z_Q, on the fp64 matrix instructions.  Launch order on the stream is the
 // only synchronisation.  A sweep of order m is m/16 - 1 such steps and annihilates every pair of indices at least once; single
 // rotations spread over the chip took m - 1 launches that each rewrote A and V: order 768, 47 ms for 6 sweeps.
@@ -1399,7 +1401,7 @@ hipError_t launch_jacobi(double* A, double* evals, double* work, int* info, int 
     // every sweep enqueued costs its launches even after convergence.  Single rotations over the whole
     // matrix took up to 16 where they converged; sweeps over pairs of blocks take as many or fewer on full, graded and
     // nearly diagonal spectra, but up to 7 more on low ranks and multiple eigenvalues (rank 40 or 100 of 256: 12 and 17 to 20;
-    // three eigenvalues 85 times each: 24 or 25)
+    // three eigenvalues 85 times each: 24 or 25).  Orders 65 to 128: 23 at most, of either kind, with single rotations or in pairs of blocks
     const int sweeps = std::min(max_sweeps, 26);
     if (m > WIDE_MIN && spare.matrix && spare.doubles >= wide_spare_doubles(batch, m))
         return launch_jacobi_wide(A, evals, work, nullptr, info, batch, m, sweeps, spare, s);

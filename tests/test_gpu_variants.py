@@ -535,6 +535,26 @@ def test_ritz_matrix_block_edges(mla, m):
     assert np.abs(S @ R - R * evals).max() <= 1e-12 * norm
 
 
+@pytest.mark.parametrize("m,p,rank", [(80, 80, 20), (96, 96, 40), (128, 128, 20), (288, 144, 100), (144, 144, 72), (144, 144, 40), (176, 176, 88), (192, 192, 40),
+                                      (200, 150, 100), (200, 200, 100), (256, 256, 40), (256, 256, 100), (300, 300, 100), (300, 300, 150), (400, 360, 100)])
+def test_ritz_matrix_of_low_rank_without_iterations(mla, m, p, rank):
+    """A block that was not iterated over a moment of low rank: the Rayleigh-Ritz matrix is no nearer to diagonal than any, and its
+    solver runs until it is (16 sweeps, enough after one iteration, stopped ranks of a half and a third short)."""
+    import torch
+    from paper_2502_07864_amd import convert
+    r = np.random.default_rng(m + rank)
+    X = r.standard_normal((m, rank))
+    S, Q0 = X @ X.T, r.standard_normal((m, p))
+    evals, R, info = convert.top_eig(torch.from_numpy(S).cuda(), torch.from_numpy(Q0).cuda(), p, 0)
+    evals, R = evals.cpu().numpy(), R.cpu().numpy()
+    assert info[0].item() == 0 and info[1].item() >= 1
+    Q = np.linalg.qr(Q0)[0]
+    norm = np.linalg.norm(S)
+    assert np.abs(evals - np.linalg.eigvalsh(Q.T @ S @ Q)[::-1]).max() <= 1e-11 * norm
+    assert np.abs(R.T @ R - np.eye(p)).max() <= 1e-12
+    assert np.abs(R.T @ S @ R - np.diag(evals)).max() <= 1e-12 * norm
+
+
 @pytest.mark.parametrize("g,d,M", [(33, 8, 2), (17, 16, 4), (32, 16, 4), (64, 4, 2)])
 def test_wide_groups_as_a_batch(mla, g, d, M):
     """Groups of 66 to 128 components: the layer's bases from the solver over pairs of blocks, all groups at once, against the
