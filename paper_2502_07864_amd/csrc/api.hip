@@ -2,6 +2,7 @@
 // Validation never touches the HIP runtime, so every error path can be
 // exercised on a machine without a GPU.
 #include "mla_internal.h"
+#include "prefill_internal.h"
 
 #include <algorithm>
 #include <mutex>
@@ -146,8 +147,6 @@ int decode_launch(const DecodeCall& c, void* workspace)
     p.num_pages = c.num_pages; p.max_pages = c.max_pages_per_seq; p.num_splits = S;
     p.chunk_pages = (c.max_pages_per_seq + S - 1) / S;
     p.q_len = c.q_len; p.heads = c.heads;
-    p.q_inner = 1; p.o_final = nullptr; p.lse_final = nullptr;
-    p.rope_kv = nullptr; p.rope_pitch = 0;
     p.scale = c.softmax_scale;
 
     const bool mfma = uses_mfma(c);
@@ -408,15 +407,11 @@ int mla_prefill_mha(const void* q_nope, const void* q_rope, const void* W_UK, co
                                               B, q_len, heads, d_c, num_pages, max_pages_per_seq, stream);
     if (e != hipSuccess) return MLA_ERR_HIP;
     // the attention: every (sequence, head) pair is a sequence of q_len query rows over its own rows
-    DecodeParams p;
-    p.q_abs = q_nope; p.q_rope = q_rope; p.kv = pool2; p.kv_scale = nullptr;
-    p.page_table = page_table; p.seq_lens = lens2;
-    p.o_part = nullptr; p.lse_part = nullptr; p.plan = nullptr;
-    p.B = (int)pseudo; p.H = q_len; p.d_c = d_head; p.d_rope = d_rope; p.page_size = page_size;
-    p.num_pages = num_pages; p.max_pages = max_pages_per_seq;
-    p.num_splits = 1; p.chunk_pages = max_pages_per_seq;
-    p.q_len = q_len; p.heads = 1; p.q_inner = heads; p.o_final = out; p.lse_final = lse;
-    p.rope_kv = static_cast<const uint16_t*>(kv_cache) + d_c; p.rope_pitch = (d_c + d_rope) * 2;
+    PrefillParams p;
+    p.q_nope = q_nope; p.q_rope = q_rope; p.pool = pool2; p.lens = lens2;
+    p.rope = static_cast<const uint16_t*>(kv_cache) + d_c; p.rope_pitch = (d_c + d_rope) * 2;
+    p.page_table = page_table; p.num_pages = num_pages; p.max_pages = max_pages_per_seq;
+    p.pairs = (int)pseudo; p.q_len = q_len; p.heads = heads; p.out = out; p.lse = lse;
     p.scale = softmax_scale;
     e = launch_prefill_attention(p, stream);
     return e == hipSuccess ? MLA_OK : MLA_ERR_HIP;
@@ -487,7 +482,7 @@ int mla_diag_stream_tiles(const void* kv_cache, const int32_t* page_table, const
     if ((d_c != 256 && d_c != 512) || B > 65535 || num_splits > 65535) return MLA_ERR_UNSUPPORTED;
     DecodeParams p = {};
     p.kv = kv_cache; p.page_table = page_table; p.seq_lens = seq_lens;
-    p.B = B; p.H = 32; p.heads = 32; p.q_len = 1; p.q_inner = 1;
+    p.B = B; p.H = 32; p.heads = 32; p.q_len = 1;
     p.d_c = d_c; p.d_rope = 64; p.page_size = 64; p.num_pages = num_pages; p.max_pages = max_pages_per_seq;
     p.num_splits = min(num_splits, max_pages_per_seq);
     p.chunk_pages = (max_pages_per_seq + p.num_splits - 1) / p.num_splits;

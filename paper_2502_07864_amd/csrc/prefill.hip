@@ -14,7 +14,7 @@
 // rows into registers as one operand, 128-bit LDS reads of the weights as the other, results rounded to bf16 and stored 16
 // bytes per lane (the page layout leaves a lane eight neighbouring values of a key, or of a value dimension: the
 // latter a contiguous kilobyte per wavefront).  No barrier and no weight traffic after the start.
-#include "mla_internal.h"
+#include "prefill_internal.h"
 #include "mfma_tile.h"
 #include <algorithm>
 #include <type_traits>

@@ -31,7 +31,7 @@
 // were busy 55 % of 5.1 M cycles at a higher clock: 8 % of the cycles gave 2 to 3 % of the time.  Scored, weighed and accumulated
 // one tile after the other from row-major values: 42 % of 6.7 M.  Whole call: 3036 us that way, then 2785, now 2736 in turn on one
 // card; 8 x 500 new tokens on 700 .. 6000, 28 heads: 552, 396, 376; 2 x 136 on 10539, whose workgroups have a CU each: 340, 288.
-#include "mla_internal.h"
+#include "prefill_internal.h"
 #include "mfma_tile.h"
 #include <type_traits>
 
@@ -43,7 +43,7 @@ constexpr int PA_DR = 64;                   // and of its rope part
 constexpr int PA_DV = 128;                  // dimensions of a value
 constexpr int PA_ROWS = 128;                // query rows per workgroup
 
-__global__ __launch_bounds__(MF_THREADS, 2) void prefill_attention_kernel(DecodeParams p)
+__global__ __launch_bounds__(MF_THREADS, 2) void prefill_attention_kernel(PrefillParams p)
 {
     constexpr int ROWB = PA_DK * 2, ROPEB = PA_DR * 2;            // 256 and 128 bytes per key
     constexpr int K_B = TILE_ROWS * ROWB;       // 8192: a tile's keys
@@ -68,36 +68,36 @@ __global__ __launch_bounds__(MF_THREADS, 2) void prefill_attention_kernel(Decode
     // (up to 64 of them: every workgroup ranks the lengths by itself): a long one started last would run
     // on alone at the end.  8 x 500 new tokens on contexts of 700 .. 6000 rows, 28 heads (the form before this one):
     // 389 us in the order of the batch, 346 longest first.
-    const int Z = (p.H + PA_ROWS - 1) / PA_ROWS;
+    const int Z = (p.q_len + PA_ROWS - 1) / PA_ROWS;
     const int id = blockIdx.x, rr = id >> 3;
     const int zi = Z - 1 - rr % Z;
     int b = (rr / Z) * 8 + (id & 7);
-    if (b >= p.B) return;                       // padding of the last group of 8
-    const int nseq = p.B / p.q_inner;
+    if (b >= p.pairs) return;                       // padding of the last group of 8
+    const int nseq = p.pairs / p.heads;
     if (nseq > 1 && nseq <= 64) {
-        const int mine = lane < nseq ? p.seq_lens[lane * p.q_inner] : -1;
+        const int mine = lane < nseq ? p.lens[lane * p.heads] : -1;
         int rank = 0;
         for (int j = 0; j < nseq; ++j) {
             const int other = __builtin_amdgcn_readlane(mine, j);
             rank += other > mine || (other == mine && j < lane);
         }
-        const unsigned long long hit = __ballot(lane < nseq && rank == b / p.q_inner);
-        b = (__builtin_ffsll((long long)hit) - 1) * p.q_inner + b % p.q_inner;
+        const unsigned long long hit = __ballot(lane < nseq && rank == b / p.heads);
+        b = (__builtin_ffsll((long long)hit) - 1) * p.heads + b % p.heads;
     }
     b = __builtin_amdgcn_readfirstlane(b);      // (uniform, and said so: what hangs on it stays in scalar registers)
     const int hb = zi * PA_ROWS;
-    const int HL = min(PA_ROWS, p.H - hb);      // query rows of this workgroup
+    const int HL = min(PA_ROWS, p.q_len - hb);      // query rows of this workgroup
     // rows of q / out: sequence b stands for (b / q_inner, b % q_inner), its tokens q_inner rows apart
-    const size_t io_base = (size_t)(b / p.q_inner) * p.H * p.q_inner + (size_t)(b % p.q_inner);
-    auto io_row = [&](int h) -> size_t { return io_base + (size_t)h * p.q_inner; };
+    const size_t io_base = (size_t)(b / p.heads) * p.q_len * p.heads + (size_t)(b % p.heads);
+    auto io_row = [&](int h) -> size_t { return io_base + (size_t)h * p.heads; };
 
-    const int32_t* const ptab = p.page_table + (size_t)(b / p.q_inner) * p.max_pages;      // pages of the cache
-    const int L = __builtin_amdgcn_readfirstlane(max(0, min(p.seq_lens[b], p.max_pages * 64)));
+    const int32_t* const ptab = p.page_table + (size_t)(b / p.heads) * p.max_pages;      // pages of the cache
+    const int L = __builtin_amdgcn_readfirstlane(max(0, min(p.lens[b], p.max_pages * 64)));
 
     // ---- this wave's 32 query rows -> registers (B operands of the score contraction)
     bf16x8 qreg[2][NKS];
     {
-        const uint16_t* qa = static_cast<const uint16_t*>(p.q_abs);
+        const uint16_t* qa = static_cast<const uint16_t*>(p.q_nope);
         const uint16_t* qr = static_cast<const uint16_t*>(p.q_rope);
 #pragma unroll
         for (int hi = 0; hi < 2; ++hi) {
@@ -124,12 +124,12 @@ __global__ __launch_bounds__(MF_THREADS, 2) void prefill_attention_kernel(Decode
 
     auto visible = [&](int h) { return L - (p.q_len - 1 - h); };   // keys that query row h sees (one head: rows are tokens)
     // keys [0, row1): what the last query row of the workgroup sees (the rows are ordered by token)
-    const int row1 = min(L, visible(min(hb + PA_ROWS, p.H) - 1));
+    const int row1 = min(L, visible(min(hb + PA_ROWS, p.q_len) - 1));
     auto store_nothing = [&]() {                // zeros and -inf for the rows of this workgroup
         for (int i = tid; i < HL * (PA_DV / 4); i += MF_THREADS)
-            *reinterpret_cast<u32x2*>(static_cast<uint16_t*>(p.o_final) + io_row(hb + i / (PA_DV / 4)) * PA_DV +
+            *reinterpret_cast<u32x2*>(static_cast<uint16_t*>(p.out) + io_row(hb + i / (PA_DV / 4)) * PA_DV +
                                       (i % (PA_DV / 4)) * 4) = (u32x2){0u, 0u};
-        if (tid < HL && p.lse_final) p.lse_final[io_row(hb + tid)] = -INFINITY;
+        if (tid < HL && p.lse) p.lse[io_row(hb + tid)] = -INFINITY;
     };
     if (row1 <= 0) {
         store_nothing();
@@ -163,7 +163,7 @@ __global__ __launch_bounds__(MF_THREADS, 2) void prefill_attention_kernel(Decode
 #pragma unroll
     for (int k = 0; k < NLV; ++k) voff[k] = (uint32_t)(P * 16 + V0 + k * 4096);      // values: as they lie
     const uint32_t roff = (uint32_t)((P >> 3) * p.rope_pitch + (((P & 7) ^ (P >> 4 & 7)) << 4));
-    const unsigned char* pool = static_cast<const unsigned char*>(p.kv) + (size_t)b * p.max_pages * PAGE_B;
+    const unsigned char* pool = static_cast<const unsigned char*>(p.pool) + (size_t)b * p.max_pages * PAGE_B;
     auto load16 = [&](const unsigned char* base, uint32_t off, uint32_t dst, auto at) {   // (base and dst are uniform)
         asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
                      :: "s"(dst), "v"(off), "s"(base), "i"(decltype(at)::value) : "memory", "scc");
@@ -182,7 +182,7 @@ __global__ __launch_bounds__(MF_THREADS, 2) void prefill_attention_kernel(Decode
     const uint32_t rope_page = 64u * (uint32_t)p.rope_pitch;          // bytes from page to page
     int32_t ids;                                // ids of 64 pages
     const unsigned char* rope;                  // rope parts of the page of the unit fetched next
-    auto rope_of = [&](int u) { return static_cast<const unsigned char*>(p.rope_kv) + (uint64_t)(uint32_t)__builtin_amdgcn_readlane(ids, u & 63) * rope_page; };
+    auto rope_of = [&](int u) { return static_cast<const unsigned char*>(p.rope) + (uint64_t)(uint32_t)__builtin_amdgcn_readlane(ids, u & 63) * rope_page; };
     using AtK1 = std::integral_constant<int, K1>;
     using AtK2 = std::integral_constant<int, K2>;
     using AtR1 = std::integral_constant<int, R1>;
@@ -475,27 +475,25 @@ __global__ __launch_bounds__(MF_THREADS, 2) void prefill_attention_kernel(Decode
         const int r = r0 + (lane >> 4), c = lane & 15;   // 16 lanes x 16 bytes = one row
         if (r < nrow) {
             const u32x4 v = *(LDS_AS u32x4*)(mine + r * RSO + c * 16);
-            *reinterpret_cast<u32x4*>(static_cast<uint16_t*>(p.o_final) + io_row(hb + wave * 32 + r) * PA_DV + c * 8) = v;
+            *reinterpret_cast<u32x4*>(static_cast<uint16_t*>(p.out) + io_row(hb + wave * 32 + r) * PA_DV + c * 8) = v;
         }
     }
-    if (g == 0 && p.lse_final) {
+    if (g == 0 && p.lse) {
 #pragma unroll
         for (int hi = 0; hi < 2; ++hi)
             if (my_row + hi * 16 < HL)
-                p.lse_final[io_row(hb + my_row + hi * 16)] =
+                p.lse[io_row(hb + my_row + hi * 16)] =
                     lt[hi] > 0.f ? (m_ref[hi] + __builtin_amdgcn_logf(lt[hi])) * LN2 : -INFINITY;
     }
 }
 
 }  // namespace
 
-// Causal attention over materialised keys and values: p.B pseudo-sequences ((sequence, head) pairs)
-// of p.H query rows each, results straight to o_final / lse_final.
-hipError_t launch_prefill_attention(const DecodeParams& p, hipStream_t s)
+hipError_t launch_prefill_attention(const PrefillParams& p, hipStream_t s)
 {
-    if (!p.o_final || p.heads != 1 || p.q_inner < 1) return hipErrorInvalidValue;
-    const long long Z = (p.H + PA_ROWS - 1) / PA_ROWS;
-    const long long nwg = ((long long)p.B + 7) / 8 * 8 * Z;
+    if (!p.out || p.heads < 1) return hipErrorInvalidValue;
+    const long long Z = (p.q_len + PA_ROWS - 1) / PA_ROWS;
+    const long long nwg = ((long long)p.pairs + 7) / 8 * 8 * Z;
     if (nwg > 0x7FFFFFFFLL) return hipErrorInvalidValue;
     prefill_attention_kernel<<<dim3((unsigned)nwg), dim3(MF_THREADS), 0, s>>>(p);
     return hipGetLastError();
