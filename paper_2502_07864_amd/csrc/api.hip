@@ -355,17 +355,18 @@ int mla_merge_out_proj_multi(const void* workspace, size_t workspace_bytes, cons
 }
 
 namespace {
-// (Sized for keys with their rope part and a page table for every pair, as callers have sized it: the pool uses four fifths of its
-// room, the table's stays empty.)
+// (Sized for keys with their rope part and a page table for every pair, as callers have sized it: the keys and values take four fifths
+// of the pool's room, and rope parts that have to be copied, once for all heads, and their ids what they leave.)
 struct PrefillWs {
-    size_t pool_off, lens_off, total;
+    size_t pool_off, rope_off, ids_off, lens_off, total;
 };
 PrefillWs prefill_ws(int B, int heads, int d_c, int max_pages)
 {
     PrefillWs w;
     w.pool_off = align_up((size_t)heads * 256 * d_c * 2, 256);                                   // after Wcat
-    w.lens_off = w.pool_off + align_up((size_t)B * heads * max_pages * 64 * 320 * 2, 256) +
-                 align_up((size_t)B * heads * max_pages * sizeof(int32_t), 256);
+    w.rope_off = w.pool_off + (size_t)B * heads * max_pages * 64 * 256 * 2;
+    w.ids_off = w.pool_off + align_up((size_t)B * heads * max_pages * 64 * 320 * 2, 256);
+    w.lens_off = w.ids_off + align_up((size_t)B * heads * max_pages * sizeof(int32_t), 256);
     w.total = w.lens_off + align_up((size_t)B * heads * sizeof(int32_t), 256);
     return w;
 }
@@ -411,6 +412,13 @@ int mla_prefill_mha(const void* q_nope, const void* q_rope, const void* W_UK, co
     p.q_nope = q_nope; p.q_rope = q_rope; p.pool = pool2; p.lens = lens2;
     p.rope = static_cast<const uint16_t*>(kv_cache) + d_c; p.rope_pitch = (d_c + d_rope) * 2;
     p.page_table = page_table; p.num_pages = num_pages; p.max_pages = max_pages_per_seq;
+    if (reinterpret_cast<uintptr_t>(kv_cache) & 15u) {       // direct-to-LDS loads are not documented to take it
+        int32_t* ids = reinterpret_cast<int32_t*>(ws + wl.ids_off);
+        e = launch_prefill_rope(kv_cache, page_table, seq_lens, ws + wl.rope_off, ids, B, d_c, num_pages, max_pages_per_seq, stream);
+        if (e != hipSuccess) return MLA_ERR_HIP;
+        p.rope = ws + wl.rope_off; p.rope_pitch = d_rope * 2;
+        p.page_table = ids; p.num_pages = B * max_pages_per_seq;
+    }
     p.pairs = (int)pseudo; p.q_len = q_len; p.heads = heads; p.out = out; p.lse = lse;
     p.scale = softmax_scale;
     e = launch_prefill_attention(p, stream);

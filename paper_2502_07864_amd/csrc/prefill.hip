@@ -404,12 +404,34 @@ __global__ __launch_bounds__(256, 2) void prefill_stream_kernel(const uint16_t* 
     }
 }
 
+// a page of a sequence: 64 rows of 64 values
+__global__ __launch_bounds__(256) void prefill_rope_kernel(const uint16_t* kv, const int32_t* page_table, const int32_t* seq_lens,
+                                                           uint16_t* dst, int32_t* ids, int d_c, int num_pages, int max_pages)
+{
+    const int pg = blockIdx.x, b = blockIdx.y;
+    const size_t at = (size_t)b * max_pages + pg;
+    const int page = (long long)pg * 64 < seq_lens[b] ? page_table[at] : -1;
+    const bool there = page >= 0 && page < num_pages;
+    if (threadIdx.x == 0) ids[at] = there ? (int32_t)at : -1;
+    if (!there) return;
+    for (int i = threadIdx.x; i < 64 * 64; i += 256)
+        dst[at * 64 * 64 + i] = kv[((size_t)page * 64 + (i >> 6)) * (d_c + 64) + d_c + (i & 63)];
+}
+
 }  // namespace
 
 bool prefill_supported(int d_head, int d_c, int d_rope, int page_size, mla_dtype io, mla_dtype cache)
 {
     return io == MLA_BF16 && cache == MLA_BF16 && d_head == PF_DH && d_rope == 64 && page_size == 64 &&
            (d_c == 256 || d_c == 512);
+}
+
+hipError_t launch_prefill_rope(const void* kv, const int32_t* page_table, const int32_t* seq_lens, void* dst, int32_t* ids,
+                               int B, int d_c, int num_pages, int max_pages, hipStream_t s)
+{
+    prefill_rope_kernel<<<dim3(max_pages, B), 256, 0, s>>>(static_cast<const uint16_t*>(kv), page_table, seq_lens, static_cast<uint16_t*>(dst), ids,
+                                                           d_c, num_pages, max_pages);
+    return hipGetLastError();
 }
 
 hipError_t launch_prefill_materialise(const void* kv, const int32_t* page_table, const int32_t* seq_lens,

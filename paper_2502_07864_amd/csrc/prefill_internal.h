@@ -27,6 +27,10 @@ hipError_t launch_prefill_materialise(const void* kv, const int32_t* page_table,
                                       const void* W_UK, const void* W_UV, void* Wcat, void* pool2, int32_t* lens2,
                                       int B, int q_len, int heads, int d_c, int num_pages, int max_pages,
                                       hipStream_t s);
+// the rope parts of a cache that is not on 16 bytes: copied to dst, page by page of the sequences, [B * max_pages, 64, 64], and their
+// ids there, [B, max_pages] (-1: not in the cache)
+hipError_t launch_prefill_rope(const void* kv, const int32_t* page_table, const int32_t* seq_lens, void* dst, int32_t* ids,
+                               int B, int d_c, int num_pages, int max_pages, hipStream_t s);
 hipError_t launch_prefill_attention(const PrefillParams& p, hipStream_t s);
 
 }  // namespace mla

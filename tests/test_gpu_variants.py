@@ -373,6 +373,36 @@ def test_prefill_page_ids_64_at_a_time(mla, L, drop, late):
     assert lse_err(widen_gpu(lse), ref_lse) <= 2e-2 * max(1.0, np.abs(ref_lse).max() / 30)
 
 
+@pytest.mark.parametrize("by", [2, 4, 6])
+@pytest.mark.parametrize("B,T,H,d_c,lens,drop", [(1, 3, 2, 256, [5], []), (3, 100, 4, 512, [100, 700, 129], [(1, 3)]), (2, 130, 28, 256, [4200, 131], [(0, 0), (0, 64)])])
+def test_prefill_of_a_cache_off_its_16_bytes(mla, B, T, H, d_c, lens, drop, by):
+    """The cache as a view into a larger buffer, `by` values behind a multiple of 16 bytes: the bits of the call on an aligned one,
+    with pages outside the pool and NaN in free pages and behind the sequences' ends."""
+    import torch
+    w = synth.make_workload("prefill", B=B, H=H, d_head=128, d_c=d_c, d_rope=64, seq_lens=lens, io_dtype="bf16", cache_dtype="bf16",
+                            free_frac=0.1, seed=139)
+    d = DeviceWorkload(w)
+    qn, qr = (to_torch(a, "bf16") for a in synth.multi_queries(w, T))
+    table = w.page_table.copy()
+    for b, i in drop:
+        table[b, i] = w.num_pages + 1 if i % 2 else -1
+    table = to_torch(table, "i32")
+    room = torch.full((d.pool.numel() + 16,), float("nan"), dtype=torch.bfloat16, device="cuda")
+    assert room.data_ptr() % 16 == 0
+    view = room[by:by + d.pool.numel()].view(d.pool.shape)
+    view.copy_(d.pool)
+    assert view.data_ptr() % 16 == 2 * by
+
+    def run(pool):
+        ws = torch.full((mla.prefill_workspace_bytes(B, H, d_c, table.shape[1]),), 0xFF, dtype=torch.uint8, device="cuda")
+        return mla.prefill_mha(qn, qr, d.W_UK, d.W_UV, pool, table, d.seq_lens, w.softmax_scale, return_lse=True, workspace=ws)
+
+    (a, la), (c, lc) = run(d.pool), run(view)
+    torch.cuda.synchronize()
+    assert torch.isfinite(a.float()).all()
+    assert torch.equal(a.view(torch.int16), c.view(torch.int16)) and torch.equal(la.view(torch.int32), lc.view(torch.int32))
+
+
 def weights_in_lds(B, T, lens, H, d_c):
     """The launcher's choice between the two kernels that write the keys and values."""
     pages = B * max(1, max((n + 63) // 64 for n in lens))
