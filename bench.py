@@ -316,7 +316,7 @@ def main():
     # which kernel mla_decode_paged launches for this call (the library's dispatch rule, restated)
     fp8 = w.cache_dtype == "fp8_e4m3"
     if w.io_dtype != "bf16":
-        kernel_name = "decode_portable_kernel<float, float, 2, 8>"   # (C1: up to 256 workgroups of two heads)
+        kernel_name = "decode_portable_kernel<float, float, 2, 4, 8>"   # (C1: up to 256 workgroups of two heads)
     elif T > 1:
         kernel_name = f"decode_mfma_wide_kernel<{d_c}, {'true' if T * H <= 64 else 'false'}>"
     elif fp8:
@@ -606,7 +606,7 @@ def convert_main(args):
            "checks": {"ritz_residual_over_lambda1": resid, "orthonormality": orth,
                       "captured_second_moment": round(captured, 6), "alpha": out["alpha"].item(),
                       "rope_basis_sweeps_max": int(info[:-2].max()), "ritz_sweeps": int(info[-1])},
-           "roofline": {"bound": "mfma", "kernel": f"gemm_f64_kernel<true, false, true> (S Q, {mj} x {mj} x {p}, K steps in equal shares) "
+           "roofline": {"bound": "mfma", "kernel": f"gemm_f64_kernel<true, false, true, false> (S Q, {mj} x {mj} x {p}, K steps in equal shares) "
                                                    "+ gemm_f64_reduce_kernel",
                         "achieved": round(tflops, 2), "peak": 78.6, "unit": "TFLOP/s", "frac": round(tflops / 78.6, 4),
                         "traffic": None, "algorithmic_flop_per_launch": flop, "launch_us": round(launch_ms * 1e3, 1),
