@@ -31,8 +31,8 @@ constexpr int PF_PAGE = 64 * 2 * PF_DH;           // values per materialised pag
 // the 16 lanes that share a cycle of an operand read meet 16 different units.  The values' weights are stored k-major by the caller
 // and are transposed once, at the start, by the transposing LDS read.
 // Bound by the matrix pipe and the LDS reads that feed it (1 KB for two instructions of a wavefront), by the latent rows and by
-// writing 512 bytes per (token, head): 26800 tokens, 28 heads, d_c = 256, 145 us with 640 (the rope part copied), now 118; weights streamed through the LDS by every
-// workgroup, laid out by a launch of its own, took 172 + 9.  Two pages, 28 heads, d_c = 512: 11.3 (15 + 8).
+// writing 512 bytes per (token, head): 26800 tokens, 28 heads, d_c = 256, mean of 100 traced launches, 152 us with 640 (the rope part copied), now 121 to
+// 128 by card; weights streamed through the LDS by every workgroup, laid out by a launch of its own, took 172 + 9.  Two pages, 28 heads, d_c = 512: 11.3 (15 + 8).
 // Whole pages per wavefront (eight of them): 149; a wavefront's rows requested a unit ahead: 160 to 200 (registers).
 template <int D_C> constexpr int PM_WAVES = 4096 / D_C;            // wavefronts of a workgroup: 16 / 8
 

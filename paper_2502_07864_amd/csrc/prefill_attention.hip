@@ -87,7 +87,7 @@ __global__ __launch_bounds__(MF_THREADS, 2) void prefill_attention_kernel(Prefil
     b = __builtin_amdgcn_readfirstlane(b);      // (uniform, and said so: what hangs on it stays in scalar registers)
     const int hb = zi * PA_ROWS;
     const int HL = min(PA_ROWS, p.q_len - hb);      // query rows of this workgroup
-    // rows of q / out: sequence b stands for (b / q_inner, b % q_inner), its tokens q_inner rows apart
+    // rows of q / out: pair b is (sequence b / heads, head b % heads), its tokens heads rows apart
     const size_t io_base = (size_t)(b / p.heads) * p.q_len * p.heads + (size_t)(b % p.heads);
     auto io_row = [&](int h) -> size_t { return io_base + (size_t)h * p.heads; };
 
