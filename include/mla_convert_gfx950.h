@@ -118,7 +118,7 @@ int mla_conv_joint_moment(const double* K_nope, int ldk, const double* V, int ld
  *   R      [m, r]   Ritz vectors of the r largest, in columns
  *   info   [2] int  info[0]: 0, or the number of Cholesky pivots that had to be clamped (the block
  *                   lost rank: as many directions of it are arbitrary); info[1]: sweeps of the final eigendecomposition, -1 if not converged
- *                   (within 16 sweeps for p > 128, 26 where iters = 0 and for p from 65 to 128)
+ *                   (within 16 sweeps for p > 256, 18 for p > 128, 26 where iters = 0 and for p from 65 to 128)
  */
 size_t mla_conv_top_eig_workspace_bytes(int m, int p);
 /* One application of the moment matrix to a block, Y = S Q (the product each step of the

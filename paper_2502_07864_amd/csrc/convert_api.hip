@@ -11,10 +11,12 @@ namespace {
 constexpr int JACOBI_MAX_SWEEPS = 60;
 // Rayleigh-Ritz matrix of the power iteration above order 128.  After some iterations it is nearly diagonal (4 to 8 sweeps; where
 // the moment has few eigenvalues, each many times, up to 16 and beyond).  Every sweep enqueued beyond convergence costs its launches,
-// which return at once: 49 at order 768, 0.08 ms.  A matrix that needs more is reported through info (-1).  Without iterations the
+// which return at once: 49 at order 768, 0.08 ms.  A matrix that needs more is reported through info (-1).  Up to order 256 two more:
+// rotations inside the blocks in every fourth step cost moments of two or three eigenvalues a sweep or two there (34 of 3600 of orders
+// 129 to 228 took 17 or 18 sweeps where rotations at every step took 16 or fewer; none of 1080 of orders 229 to 359 did).  Without iterations the
 // block is no nearer to the eigenvectors than it was given: low ranks and multiple eigenvalues take 14 to 25 sweeps (order 144 of
 // rank 72 17, 256 of rank 100 19), so as many are run as for a matrix of unknown form.
-constexpr int RITZ_MAX_SWEEPS = 16;
+constexpr int ritz_max_sweeps(int p) { return p > 256 ? 16 : 18; }
 
 inline size_t align256(size_t b) { return (b + 255) & ~size_t(255); }
 inline int st(hipError_t e) { return e == hipSuccess ? MLA_OK : MLA_ERR_HIP; }
@@ -125,7 +127,7 @@ int top_eig(const Symmetric& S, const double* Q0, double* evals, double* R, cons
     if (e != hipSuccess) return MLA_ERR_HIP;
     e = launch_symmetrise(w.T, p, s);
     if (e != hipSuccess) return MLA_ERR_HIP;
-    e = launch_jacobi(w.T, evals, w.Z, info + 1, 1, p, p > 128 && iters > 0 ? RITZ_MAX_SWEEPS : JACOBI_MAX_SWEEPS, s,
+    e = launch_jacobi(w.T, evals, w.Z, info + 1, 1, p, p > 128 && iters > 0 ? ritz_max_sweeps(p) : JACOBI_MAX_SWEEPS, s,
                       JacobiSpare{w.G, w.part, w.part_doubles});
     if (e != hipSuccess) return MLA_ERR_HIP;
     return st(launch_gemm_f64(gemm_nn(w.Y, p, w.T, p, R, r, m, r, p, 1.0), s));

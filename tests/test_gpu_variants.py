@@ -585,6 +585,24 @@ def test_ritz_matrix_of_low_rank_without_iterations(mla, m, p, rank):
     assert np.abs(R.T @ S @ R - np.diag(evals)).max() <= 1e-12 * norm
 
 
+@pytest.mark.parametrize("m,p,values,ratio,iters,seed", [(266, 170, 2, .95, 4, 1370), (208, 164, 2, .999, 40, 3493), (164, 129, 2, .99, 12, 2561), (255, 165, 2, .999, 1, 132),
+                                                         (172, 140, 2, .999, 8, 2064), (230, 180, 3, .999, 12, 2673), (283, 185, 2, .999, 40, 3593), (307, 228, 3, .999, 3, 865)])
+def test_ritz_matrix_of_few_eigenvalues(mla, m, p, values, ratio, iters, seed):
+    """A moment of two or three eigenvalues, each many times, after some iterations: its Rayleigh-Ritz matrix takes up to 18 sweeps where
+    rotations inside the blocks at every step took 16."""
+    import torch
+    from paper_2502_07864_amd import convert
+    r = np.random.default_rng(seed)
+    V = np.linalg.qr(r.standard_normal((m, m)))[0]
+    S = (V * np.repeat(ratio ** np.arange(values), -(-m // values))[:m]) @ V.T
+    S = (S + S.T) / 2
+    evals, R, info = convert.top_eig(torch.from_numpy(S).cuda(), torch.from_numpy(r.standard_normal((m, p))).cuda(), p, iters)
+    evals, R = evals.cpu().numpy(), R.cpu().numpy()
+    assert info[0].item() == 0 and info[1].item() >= 1
+    assert np.abs(R.T @ R - np.eye(p)).max() <= 1e-12
+    assert np.abs(R.T @ S @ R - np.diag(evals)).max() <= 1e-12 * np.linalg.norm(S)
+
+
 @pytest.mark.parametrize("g,d,M", [(33, 8, 2), (17, 16, 4), (32, 16, 4), (64, 4, 2)])
 def test_wide_groups_as_a_batch(mla, g, d, M):
     """Groups of 66 to 128 components: the layer's bases from the solver over pairs of blocks, all groups at once, against the
