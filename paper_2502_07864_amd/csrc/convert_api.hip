@@ -12,8 +12,9 @@ constexpr int JACOBI_MAX_SWEEPS = 60;
 // Rayleigh-Ritz matrix of the power iteration above order 128.  After some iterations it is nearly diagonal (4 to 8 sweeps; where
 // the moment has few eigenvalues, each many times, up to 16 and beyond).  Every sweep enqueued beyond convergence costs its launches,
 // which return at once: 49 at order 768, 0.08 ms.  A matrix that needs more is reported through info (-1).  Up to order 256 two more:
-// rotations inside the blocks in every fourth step cost moments of two or three eigenvalues a sweep or two there (34 of 3600 of orders
-// 129 to 228 took 17 or 18 sweeps where rotations at every step took 16 or fewer; none of 1080 of orders 229 to 359 did).  Without iterations the
+// rotations inside the blocks in every fourth step, not in all, shift the count of moments of two or three eigenvalues by a sweep or two
+// either way (34 of 3600, orders 129 to 228, took 17 or 18 where it had been 16 or fewer; none of 1080 of orders 229 to 359).  They
+// take 40 us of a layer of 192 columns, 1 %.  Without iterations the
 // block is no nearer to the eigenvectors than it was given: low ranks and multiple eigenvalues take 14 to 25 sweeps (order 144 of
 // rank 72 17, 256 of rank 100 19), so as many are run as for a matrix of unknown form.
 constexpr int ritz_max_sweeps(int p) { return p > 256 ? 16 : 18; }
